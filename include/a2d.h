@@ -104,7 +104,7 @@ typedef struct {
   int32_t heads;   /* B * M, >= 1                                                     */
   int32_t nq;      /* query rows of the tile, 1 .. 2^22                               */
   int32_t nkv;     /* key/value rows of the tile, 1 .. 2^22                           */
-  int32_t hdim;    /* H: 64, 80, 96 or 128 (bf16: MFMA kernels; fp32: vector-ALU ones) */
+  int32_t hdim;    /* H: 64, 80, 96 or 128 (bf16 and fp32: MFMA kernels of that type)   */
   int64_t q_off;   /* global index of query row 0 (used only when causal != 0)        */
   int64_t kv_off;  /* global index of key row 0   (used only when causal != 0)        */
   int32_t causal;  /* 0: no mask; 1: hide key r from query i iff q_off+i < kv_off+r   */
@@ -435,7 +435,8 @@ void a2d_debug_force_generic(int on);
  * off.  While a trace is set - per host thread - every call of this library made by that thread
  * records the next unused event on the call's stream once before its first kernel and once
  * after each kernel it launches; consecutive events of one call then bracket one kernel each
- * (a tile forward: 2 events; a2d_partial_bwd: 4 - delta, dK/dV, dQ kernels; a merge: 2).  Events
+ * (a tile forward: 2 events; a2d_partial_bwd: 4 - delta, dK/dV, dQ kernels - or, on fp32 inputs,
+ * 3: dQ with delta, dK/dV; a merge: 2).  Events
  * beyond n are not recorded.  a2d_debug_trace_count: events recorded since the trace was set.
  */
 void a2d_debug_trace(void** events, int n);

@@ -174,9 +174,13 @@ a2d_status partial_fwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
   hipStream_t s = static_cast<hipStream_t>(stream);
   a2d_tile_desc dd;
   A2D_TRY(resolve_layouts(desc, g.group, false, who, &dd));
-  if (!a2d::force_generic() && a2d::fwd_mfma_supported(dd)) {
+  if (!a2d::force_generic()) {
     a2d::SegList go = g;
     go.by_size = blocks_differ(desc, g);
+    if (dd.dtype == A2D_F32) {
+      a2d::trace_mark(s);
+      return hip_result(a2d::launch_fwd_f32(dd, go, Q, K, V, O_part, m, l, s), who);
+    }
     A2D_TRY(hip_result(a2d::launch_fwd_mfma(a2d::PREPARE, dd, go, Q, K, V, O_part, m, l, s), who));
     a2d::trace_mark(s);
     return hip_result(a2d::launch_fwd_mfma(a2d::LAUNCH, dd, go, Q, K, V, O_part, m, l, s), who);
@@ -225,14 +229,18 @@ a2d_status partial_bwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
                                         a2d_workspace_bytes(desc, A2D_OP_PARTIAL_BWD_DS, 0));
   }
   float* delta = static_cast<float*>(workspace);
-  if (!a2d::force_generic() && a2d::bwd_mfma_supported(dd)) {
+  if (!a2d::force_generic()) {
+    a2d::SegList go = g;
+    go.by_size = blocks_differ(desc, g);
+    if (dd.dtype == A2D_F32) {
+      a2d::trace_mark(s);
+      return hip_result(a2d::launch_bwd_f32(dd, go, Q, K, V, O, dO, lse, delta, dQ_part, dK_part, dV_part, s), who);
+    }
     // the dS hand-over when the caller asked for it and this tile allows it (`need` covers the
     // plain tile's dS area; a gathered tile of the same nkv has the same size or none)
     const size_t ds_bytes = keep_ds ? a2d::bwd_ds_bytes(dd, g) : 0;
     void* ds_ws = (ds_bytes > 0 && workspace_bytes >= delta_bytes + ds_bytes) ? static_cast<char*>(workspace) + delta_bytes
                                                                               : nullptr;
-    a2d::SegList go = g;
-    go.by_size = blocks_differ(desc, g);
     A2D_TRY(hip_result(a2d::launch_bwd_mfma(a2d::PREPARE, dd, go, Q, K, V, dO, lse, delta, dQ_part, dK_part,
                                             dV_part, ds_ws, split_ws, s), who));
     a2d::trace_mark(s);

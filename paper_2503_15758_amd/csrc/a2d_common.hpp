@@ -108,8 +108,16 @@ void trace_mark(hipStream_t s);
 // launches and returns the launch's hipError_t.
 enum Phase { PREPARE = 0, LAUNCH = 1 };
 
+// fp32 tile kernels on the fp32 matrix units (H in {64, 80, 96, 128}); nothing to prepare.  The
+// backward also computes delta (into `delta`).
+hipError_t launch_fwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                          float* O_part, float* m, float* l, hipStream_t s);
+hipError_t launch_bwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                          const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK,
+                          float* dV, hipStream_t s);
+
 // Generic tile kernels: fp32 arithmetic on the vector ALUs for fp32 or bf16
-// inputs, any nq / nkv, H in {64, 80, 96, 128}.
+// inputs, any nq / nkv, H in {64, 80, 96, 128}.  Reached with force_generic() only.
 hipError_t launch_fwd_generic(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                               const void* V, float* O_part, float* m, float* l, hipStream_t s);
 hipError_t launch_bwd_generic(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,

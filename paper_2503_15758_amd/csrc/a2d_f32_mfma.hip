@@ -1,0 +1,653 @@
+// fp32 tile kernels on the fp32 matrix units: forward (Sec. 3.1, Eq. (3), block by block with the
+// recurrence of Sec. 2.2) and the per-tile gradient call of Alg. 3 line 3, for H = 64, 80, 96, 128.
+// fp32 throughout: v_mfma_f32_16x16x4_f32 multiplies and accumulates in fp32 (2048 flop in 32 cycles
+// of a SIMD, 157 TFLOP/s over the chip - twice what unpacked vector FMAs reach).
+//
+// What bounds them: the fp32 MFMA rate.  A step of 16 keys (queries) against 16 rows is H / 4 MFMAs
+// of 32 cycles per contraction, 8 KiB of operands at H = 128 - slow enough that the operands come
+// straight from L2 into registers, one contraction ahead of their use; LDS is only used at the end.
+//   - A wavefront owns 16 * RT rows and walks blocks of 16 keys (queries); the KL wavefronts of a
+//     workgroup own the SAME rows and take every KL-th block of the walk ("key lanes"), because fp32
+//     tiles are small: it is the walk that has to be spread over the SIMDs.  Their results are
+//     merged at the end through LDS, by halves, in a fixed order (bitwise reproducible).
+//   - MFMA layout (A: 16 x 4, B: 4 x 16, D: 16 x 16): lane = row of A / column of B (lane & 15), the
+//     lane's group g = lane >> 4 is the contraction index; D: lane = column, register r = row
+//     4 g + r.  As in the bf16 kernels the score contraction is issued transposed, so that a lane
+//     holds 4 keys (4 g + r) of ONE query, and its D is the B operand of the next contraction: step r
+//     contracts the keys r, 4 + r, 8 + r, 12 + r.
+//   - Contractions over H read rows "naturally": lane (row l15, group g) loads the 16 bytes
+//     16 y + 4 g .. + 3 of its row, which serve four MFMAs (the contraction index may be permuted as
+//     long as both operands use the same permutation).
+//   - Contractions over rows need the transposed operand (lane = column): lane l15 loads 16 bytes of
+//     row 4 g + r, columns 64 G + 4 l15 + t, and MFMA t of the group takes one of the four, i.e. row
+//     i of its result is column 64 G + 4 i + t.  A lane then holds 16 consecutive columns of the
+//     result (64 G + 16 g + 4 r + t), stored as four 16-byte pieces.  (H = 96 and 80 end in a group of
+//     32 or 16 columns with 8- or 4-byte pieces: Cols<H> below.)
+// Measured against the vector-ALU kernels of a2d_generic.hip: 16 heads x 700 x 900, H = 96, causal,
+// backward call 1034 -> 128 us (65 us dQ, 76 us dK/dV under the profiler); 2 heads x 128 x 128, H = 64,
+// forward 29 -> 6.4 us; 16 heads x 4096 x 4096, H = 128: forward 1.1 ms (125 TFLOP/s, 80 % of the fp32
+// matrix peak), dQ 2.0 ms (101 TFLOP/s executed), dK/dV 2.5 ms (111 TFLOP/s); the two backward kernels
+// then draw 13-14 TB/s from L2.
+#include "a2d_mfma.hpp"
+
+namespace a2d {
+namespace {
+
+using mfma::gptr_t;
+using mfma::static_for;
+using mfma::uniform_gptr;
+using mfma::xcd_grid;
+using mfma::xcd_map;
+
+constexpr int BLK = 16;                      // rows of one step of a walk
+constexpr float kRescaleThreshold = 8.0f;    // log2 units (lazy rescaling, as in the bf16 forward)
+
+__device__ __forceinline__ f32x4 mma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
+template <typename T>
+__device__ __forceinline__ T gload(gptr_t base, unsigned byte_off) {
+  return *reinterpret_cast<const __attribute__((address_space(1))) T*>(base + byte_off);
+}
+
+// Natural rows: H / 16 pieces of 16 bytes per lane
+template <int H>
+struct Nat {
+  f32x4 v[H / 16];
+  __device__ __forceinline__ void load(gptr_t base, unsigned row, unsigned row_bytes, int g4) {
+    const unsigned off = __umul24(row, row_bytes) + 16 * g4;
+#pragma unroll
+    for (int y = 0; y < H / 16; ++y) v[y] = gload<f32x4>(base, off + 64 * y);
+  }
+};
+
+// Column groups of a row for the transposed operand: H / 64 groups of 64 columns (4 per lane) and a
+// rest of 32 (2 per lane) or 16 (1 per lane); T = tile index 0 .. H / 16 - 1
+template <int H>
+struct Cols {
+  static constexpr int N4 = H / 64, REST = H % 64;
+  f32x4 a[N4];
+  f32x4 b;                                   // 1, 2 of it used when there is a rest
+  __device__ __forceinline__ void load(gptr_t base, unsigned row, unsigned row_bytes, int l15) {
+    const unsigned off = __umul24(row, row_bytes);
+#pragma unroll
+    for (int G = 0; G < N4; ++G) a[G] = gload<f32x4>(base, off + 256 * G + 16 * l15);
+    if constexpr (REST == 32) {
+      const f32x2 w = gload<f32x2>(base, off + 256 * N4 + 8 * l15);
+      b[0] = w[0]; b[1] = w[1];
+    }
+    if constexpr (REST == 16) b[0] = gload<float>(base, off + 256 * N4 + 4 * l15);
+  }
+  template <int T>
+  __device__ __forceinline__ float get() const {
+    if constexpr (T < 4 * N4) return a[T / 4][T % 4]; else return b[T - 4 * N4];
+  }
+};
+
+// D layout of the transposed results: acc[T][r] is column col<T>(g, r) of the lane's row (l15)
+template <int H>
+struct Out {
+  f32x4 acc[H / 16];
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int t = 0; t < H / 16; ++t) acc[t] = zero4();
+  }
+  __device__ __forceinline__ void scale(float f) {
+#pragma unroll
+    for (int t = 0; t < H / 16; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[t][r] *= f;
+  }
+  // The 16-byte pieces of the lane's row: f(column, four places (t, r) of the accumulators)
+  template <class F>
+  __device__ __forceinline__ void pieces(int g4, F&& f) {
+    constexpr int N4 = Cols<H>::N4, REST = Cols<H>::REST;
+#pragma unroll
+    for (int G = 0; G < N4; ++G)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        f(64 * G + 16 * g4 + 4 * r, [=](int e) { return 4 * G + e; }, [=](int) { return r; });
+    if constexpr (REST == 32) {
+#pragma unroll
+      for (int r = 0; r < 4; r += 2)
+        f(64 * N4 + 8 * g4 + 2 * r, [=](int e) { return 4 * N4 + (e & 1); }, [=](int e) { return r + (e >> 1); });
+    }
+    if constexpr (REST == 16) f(64 * N4 + 4 * g4, [=](int) { return 4 * N4; }, [=](int e) { return e; });
+  }
+  __device__ __forceinline__ void store(float* row, int g4, float mul, bool add = false) {
+    pieces(g4, [&](int col, auto t, auto r) {
+      f32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = acc[t(e)][r(e)] * mul;
+      if (add) {
+        const f32x4 o = *reinterpret_cast<const f32x4*>(row + col);
+        v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
+      }
+      *reinterpret_cast<f32x4*>(row + col) = v;
+    });
+  }
+  __device__ __forceinline__ void load(const float* row, int g4) {
+    pieces(g4, [&](int col, auto t, auto r) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(row + col);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t(e)][r(e)] = v[e];
+    });
+  }
+  // acc += rows^T * b over the 4 rows (one per group) `c` holds
+  __device__ __forceinline__ void contract(const Cols<H>& c, float b) {
+    static_for<0, H / 16>([&](auto T) {
+      constexpr int t = decltype(T)::value;
+      acc[t] = mma4(c.template get<t>(), b, acc[t]);
+    });
+  }
+};
+
+// 16 x 16 result of a contraction over H (two accumulators: an MFMA that accumulates onto the
+// result of the one issued just before it would wait for that result)
+template <int H>
+__device__ __forceinline__ f32x4 dot_rows(const Nat<H>& a, const Nat<H>& b) {
+  f32x4 s0 = zero4(), s1 = zero4();
+#pragma unroll
+  for (int y = 0; y < H / 16; ++y) {
+    s0 = mma4(a.v[y][0], b.v[y][0], s0);
+    s1 = mma4(a.v[y][1], b.v[y][1], s1);
+    s0 = mma4(a.v[y][2], b.v[y][2], s0);
+    s1 = mma4(a.v[y][3], b.v[y][3], s1);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) s0[r] += s1[r];
+  return s0;
+}
+
+// Sum of N results over the KL wavefronts of the workgroup, by halves: the upper half writes, the
+// lower half adds; wavefront 0 ends up with the total.  xch: KL / 2 areas of N * 64 16-byte pieces.
+template <int KL, int N, class Get>
+__device__ __forceinline__ void merge_lanes(f32x4* xch, int kl, int lane, Get&& get) {
+#pragma unroll
+  for (int half = KL / 2; half >= 1; half /= 2) {
+    __syncthreads();
+    if (kl >= half && kl < 2 * half) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) xch[((kl - half) * N + i) * 64 + lane] = get(i);
+    }
+    __syncthreads();
+    if (kl < half) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const f32x4 v = xch[(kl * N + i) * 64 + lane];
+        f32x4& a = get(i);
+        a[0] += v[0]; a[1] += v[1]; a[2] += v[2]; a[3] += v[3];
+      }
+    }
+  }
+}
+
+// The walk over the 16-key blocks that some row of the workgroup sees, sub-block by sub-block; key
+// lane kl takes every KL-th block.  (s == g.n: past the end)
+struct Walk {
+  int s, j, nblk;
+  template <class SegBlocks>
+  __device__ __forceinline__ void open(int from, int n, SegBlocks&& blocks) {
+    s = from; j = 0;
+    while (s < n && (nblk = blocks(s)) == 0) ++s;
+  }
+  template <class SegBlocks>
+  __device__ __forceinline__ void advance(int by, int n, SegBlocks&& blocks) {
+    j += by;
+    while (s < n && j >= nblk) {
+      j -= nblk;
+      do { ++s; } while (s < n && (nblk = blocks(s)) == 0);
+    }
+  }
+};
+
+// workgroup -> (head, first row): as in the bf16 kernels the row blocks of the query heads that share a
+// key/value head go to one XCD, late (heavy) blocks first
+__device__ __forceinline__ bool query_block(const a2d_tile_desc& d, const SegList& g, int rows, int& head, int& q0) {
+  const int nqb = (d.nq + rows - 1) / rows, per_unit = g.group / g.split;
+  int unit, blk;
+  if (!xcd_map(d.heads / per_unit, per_unit * nqb, g.by_size != 0, unit, blk)) return false;
+  head = unit * per_unit + (g.by_size ? blk % per_unit : blk / nqb);
+  q0 = (nqb - 1 - (g.by_size ? blk / per_unit : blk % nqb)) * rows;
+  return true;
+}
+
+__device__ __forceinline__ int vis_count(const a2d_tile_desc& d, const SegList& g, int i, int s) {
+  if (!d.causal) return g.rows[s];
+  const int64_t v = (int64_t)i + g.rel[s] + 1;
+  return v <= 0 ? 0 : (v < g.rows[s] ? (int)v : g.rows[s]);
+}
+
+// max / sum over the four groups of a row (lanes l15 + 16 g)
+__device__ __forceinline__ float row_max(float v) {
+  v = fmaxf(v, __shfl_xor(v, 16, 64));
+  return fmaxf(v, __shfl_xor(v, 32, 64));
+}
+__device__ __forceinline__ float row_sum(float v) {
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
+
+// ------------------------------------------------------------------ forward
+template <int H, int RT, int KL>
+__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 ? 4 : 2))) void fwd_f32_kernel(
+    a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
+    const float* __restrict__ V, float* __restrict__ O_part, float* __restrict__ m_out, float* __restrict__ l_out) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  int head, q0;
+  if (!query_block(d, g, BLK * RT, head, q0)) return;
+  const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l15 = lane & 15, g4 = lane >> 4;
+  const int kvh = head / g.group;
+  const gptr_t kb = uniform_gptr(K + (int64_t)kvh * d.lk.head), vb = uniform_gptr(V + (int64_t)kvh * d.lv.head);
+  const gptr_t qb = uniform_gptr(Q + (int64_t)head * d.lq.head);
+  const unsigned k_row = (unsigned)d.lk.row * 4, v_row = (unsigned)d.lv.row * 4;
+  const float c = d.scale * kLog2e;
+
+  Nat<H> qf[RT];
+  Out<H> o[RT];
+  float m_lane[RT], m_ref[RT], l_run[RT];
+  int q_row[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    q_row[t] = q0 + BLK * t + l15;
+    qf[t].load(qb, min(q_row[t], d.nq - 1), (unsigned)d.lq.row * 4, g4);
+    o[t].zero();
+    m_lane[t] = -INFINITY;
+    l_run[t] = 0.f;
+    if (g.acc && kl == 0 && q_row[t] < d.nq) {     // continue from the triple in the output buffers
+      const int64_t row = (int64_t)head * d.nq + q_row[t];
+      o[t].load(O_part + row * H, g4);
+      m_lane[t] = m_out[row] / d.scale;             // -inf stays -inf
+      l_run[t] = g4 == 0 ? l_out[row] : 0.f;
+    }
+    m_ref[t] = m_lane[t];
+  }
+
+  const int blk_last = min(q0 + BLK * RT, d.nq) - 1;
+  auto seg_blocks = [&](int s) { return (vis_count(d, g, blk_last, s) + BLK - 1) / BLK; };
+  Walk w;
+  w.open(0, g.n, seg_blocks);
+  w.advance(kl, g.n, seg_blocks);
+  Nat<H> kn;
+  Cols<H> vt[4];
+  auto load_k = [&](const Walk& x) {
+    const int r = min(x.j * BLK + l15, g.rows[x.s] - 1);
+    kn.load(kb, g.start[x.s] + r, k_row, g4);
+  };
+  if (w.s < g.n) load_k(w);
+  while (w.s < g.n) {
+    const int s = w.s, k0 = w.j * BLK, rows = g.rows[s];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) vt[r].load(vb, g.start[s] + min(k0 + 4 * g4 + r, rows - 1), v_row, l15);
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 p[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) p[t] = dot_rows<H>(kn, qf[t]);
+    w.advance(KL, g.n, seg_blocks);
+    if (w.s < g.n) load_k(w);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const int my_vis = vis_count(d, g, min(q_row[t], d.nq - 1), s);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (k0 + 4 * g4 + r >= my_vis) p[t][r] = -INFINITY;
+        m_lane[t] = fmaxf(m_lane[t], p[t][r]);
+      }
+      // (m_lane - m_ref) is +inf on the first visible block, NaN (-> false) while nothing is visible
+      const bool grow = (m_lane[t] - m_ref[t]) * c > kRescaleThreshold;
+      if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+        const float m_row = row_max(m_lane[t]);
+        const float alpha = m_ref[t] == -INFINITY ? 0.f : fast_exp2((m_ref[t] - m_row) * c);
+        m_ref[t] = m_row;
+        l_run[t] *= alpha;
+        o[t].scale(alpha);
+      }
+      const float mr = m_ref[t] == -INFINITY ? 0.f : m_ref[t];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        p[t][r] = fast_exp2((p[t][r] - mr) * c);
+        l_run[t] += p[t][r];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) o[t].contract(vt[r], p[t][r]);
+  }
+
+  // ---- to the true row maximum over all key lanes, then the sums over the lanes
+  float m_all[RT];
+  float* stat = reinterpret_cast<float*>(smem);      // [kl][t][16]
+#pragma unroll
+  for (int t = 0; t < RT; ++t) m_all[t] = row_max(m_lane[t]);
+  if constexpr (KL > 1) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+      if (g4 == 0) stat[(kl * RT + t) * 16 + l15] = m_all[t];
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int x = 0; x < KL; ++x) m_all[t] = fmaxf(m_all[t], stat[(x * RT + t) * 16 + l15]);
+  }
+  f32x4 lsum[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const float f = m_ref[t] == -INFINITY ? 0.f : fast_exp2((m_ref[t] - m_all[t]) * c);
+    o[t].scale(f);
+    lsum[t] = f32x4{row_sum(l_run[t]) * f, 0.f, 0.f, 0.f};
+  }
+  if constexpr (KL > 1) {
+    constexpr int N = RT * (H / 16 + 1);
+    merge_lanes<KL, N>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& {
+      return i < RT ? lsum[i] : o[(i - RT) / (H / 16)].acc[(i - RT) % (H / 16)];
+    });
+    if (kl != 0) return;
+  }
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    if (q_row[t] >= d.nq) continue;
+    const int64_t row = (int64_t)head * d.nq + q_row[t];
+    const float l = lsum[t][0];
+    if (g.norm) {                                     // O' = N / l, lse' = m + ln l
+      o[t].store(O_part + row * H, g4, l > 0.f ? 1.0f / l : 0.f);
+      if (g4 == 0) m_out[row] = l > 0.f ? m_all[t] * d.scale + logf(l) : -INFINITY;
+    } else {
+      o[t].store(O_part + row * H, g4, 1.0f);
+      if (g4 == 0) { m_out[row] = m_all[t] * d.scale; l_out[row] = l; }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- backward: dQ (and delta)
+// Owns 16 query rows per workgroup.  Also computes delta = rowsum(dO o O) of its rows (every key lane
+// for itself) and leaves it for the dK/dV kernel, which runs after it: no separate pass over O and dO.
+template <int H, int KL>
+__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void bwd_dq_f32_kernel(
+    a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
+    const float* __restrict__ V, const float* __restrict__ O, const float* __restrict__ dO,
+    const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dQ) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  int head, q0;
+  if (!query_block(d, g, BLK, head, q0)) return;
+  const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l15 = lane & 15, g4 = lane >> 4;
+  const int kvh = head / g.group;
+  const gptr_t kb = uniform_gptr(K + (int64_t)kvh * d.lk.head), vb = uniform_gptr(V + (int64_t)kvh * d.lv.head);
+  const unsigned k_row = (unsigned)d.lk.row * 4, v_row = (unsigned)d.lv.row * 4;
+  const int q_row = q0 + l15, q_ld = min(q_row, d.nq - 1);
+
+  Nat<H> qf, gf, kn, vn;
+  qf.load(uniform_gptr(Q + (int64_t)head * d.lq.head), q_ld, (unsigned)d.lq.row * 4, g4);
+  gf.load(uniform_gptr(dO + (int64_t)head * d.ldo.head), q_ld, (unsigned)d.ldo.row * 4, g4);
+  kn.load(uniform_gptr(O + (int64_t)head * d.lo.head), q_ld, (unsigned)d.lo.row * 4, g4);   // O, for delta only
+  const float lse_i = q_row < d.nq ? lse[(int64_t)head * d.nq + q_ld] : -INFINITY;
+  float del = 0.f;
+#pragma unroll
+  for (int y = 0; y < H / 16; ++y)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) del = fmaf(gf.v[y][e], kn.v[y][e], del);
+  del = row_sum(del);
+  if (kl == 0 && g4 == 0 && q_row < d.nq) delta[(int64_t)head * d.nq + q_row] = del;
+
+  const int blk_last = min(q0 + BLK, d.nq) - 1;
+  auto seg_blocks = [&](int s) { return (vis_count(d, g, blk_last, s) + BLK - 1) / BLK; };
+  Walk w;
+  w.open(0, g.n, seg_blocks);
+  w.advance(kl, g.n, seg_blocks);
+  Out<H> dq;
+  dq.zero();
+  auto load_k = [&](const Walk& x) {
+    kn.load(kb, g.start[x.s] + min(x.j * BLK + l15, g.rows[x.s] - 1), k_row, g4);
+  };
+  if (w.s < g.n) load_k(w);
+  while (w.s < g.n) {
+    const int s = w.s, k0 = w.j * BLK, rows = g.rows[s], start = g.start[s];
+    vn.load(vb, start + min(k0 + l15, rows - 1), v_row, g4);
+    __builtin_amdgcn_sched_barrier(0);
+    const f32x4 sc = dot_rows<H>(kn, qf);
+    Cols<H> kt[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) kt[r].load(kb, start + min(k0 + 4 * g4 + r, rows - 1), k_row, l15);
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 ds = dot_rows<H>(vn, gf);
+    const int my_vis = vis_count(d, g, q_ld, s);
+    w.advance(KL, g.n, seg_blocks);
+    if (w.s < g.n) load_k(w);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool vis = lse_i != -INFINITY && k0 + 4 * g4 + r < my_vis;
+      const float p = vis ? fast_exp2(fmaf(sc[r], d.scale, -lse_i) * kLog2e) : 0.f;
+      ds[r] = p * (ds[r] - del);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) dq.contract(kt[r], ds[r]);
+  }
+  if constexpr (KL > 1) {
+    merge_lanes<KL, H / 16>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& { return dq.acc[i]; });
+    if (kl != 0) return;
+  }
+  if (q_row < d.nq) {
+    float* row = dQ + ((int64_t)head * d.nq + q_row) * H;
+    dq.store(row, g4, d.scale, g.acc != 0);
+  }
+}
+
+// ---------------------------------------------------------------- backward: dK, dV
+// Owns 16 keys of a key/value head per workgroup and walks the query rows of all its group's query
+// heads, 16 at a time: S = Q K^T and dP = dO V^T leave a lane holding 4 queries of ONE key.
+template <int H, int KL>
+__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void bwd_dkdv_f32_kernel(
+    a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
+    const float* __restrict__ V, const float* __restrict__ dO, const float* __restrict__ lse,
+    const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  int head, blk;                                      // key/value head
+  if (!xcd_map(d.heads / g.group, (d.nkv + BLK - 1) / BLK, g.by_size != 0, head, blk)) return;
+  const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l15 = lane & 15, g4 = lane >> 4;
+  const int k0 = blk * BLK, key = k0 + l15, k_ld = min(key, d.nkv - 1);
+  const gptr_t qb = uniform_gptr(Q + (int64_t)head * g.group * d.lq.head);
+  const gptr_t gb = uniform_gptr(dO + (int64_t)head * g.group * d.ldo.head);
+  const float* lse_b = lse + (int64_t)head * g.group * d.nq;
+  const float* del_b = delta + (int64_t)head * g.group * d.nq;
+  const unsigned q_row = (unsigned)d.lq.row * 4, g_row = (unsigned)d.ldo.row * 4;
+  const unsigned q_head = (unsigned)d.lq.head * 4, g_head = (unsigned)d.ldo.head * 4;
+
+  Nat<H> kf, vf;
+  kf.load(uniform_gptr(K + (int64_t)head * d.lk.head), k_ld, (unsigned)d.lk.row * 4, g4);
+  vf.load(uniform_gptr(V + (int64_t)head * d.lv.head), k_ld, (unsigned)d.lv.row * 4, g4);
+
+  // first query row that sees this lane's key, and the first that sees any of the block's keys
+  auto first_row = [&](int s, int k) -> int {
+    const int64_t f = (int64_t)(k - g.start[s]) - g.rel[s];
+    return f <= 0 ? 0 : (f >= d.nq ? d.nq : (int)f);
+  };
+  int my_first = 0, i_first = 0;
+  if (d.causal) {
+    my_first = i_first = d.nq;
+    for (int s = 0; s < g.n; ++s) {
+      const int a = max(k0, g.start[s]), b = min(k0 + BLK, g.start[s] + g.rows[s]);
+      if (a < b) i_first = min(i_first, first_row(s, a));
+      if (key >= g.start[s] && key < g.start[s] + g.rows[s]) my_first = first_row(s, key);
+    }
+  }
+  if (key >= d.nkv) my_first = d.nq;                  // padding keys see nothing
+  const int b0 = i_first / BLK, nblk = (d.nq + BLK - 1) / BLK - b0;
+  const int total = nblk * g.group;                   // the group's query heads one after the other
+
+  Out<H> dk, dv;
+  dk.zero();
+  dv.zero();
+  Nat<H> x, y;                                        // operands, each loaded one contraction ahead
+  // position of walk step n: query head (inside the group) and first row
+  int qh = 0, rb = kl;                                // of the next step to be loaded
+  auto wrap = [&]() { while (rb >= nblk && qh < g.group) { rb -= nblk; ++qh; } };
+  if (nblk > 0) wrap();
+  auto load_q = [&]() {
+    const unsigned base = qh * q_head;
+    const unsigned row = min((b0 + rb) * BLK + l15, d.nq - 1);
+    const unsigned off = base + __umul24(row, q_row) + 16 * g4;
+#pragma unroll
+    for (int i = 0; i < H / 16; ++i) x.v[i] = gload<f32x4>(qb, off + 64 * i);
+  };
+  if (kl < total) load_q();
+  for (int n = kl; n < total; n += KL) {
+    const int i0 = (b0 + rb) * BLK, ch = qh;
+    {
+      const unsigned row = min(i0 + l15, d.nq - 1);
+      const unsigned off = ch * g_head + __umul24(row, g_row) + 16 * g4;
+#pragma unroll
+      for (int i = 0; i < H / 16; ++i) y.v[i] = gload<f32x4>(gb, off + 64 * i);
+    }
+    float ls[4], de[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = ch * d.nq + min(i0 + 4 * g4 + r, d.nq - 1);
+      ls[r] = lse_b[i];
+      de[r] = del_b[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 p = dot_rows<H>(x, kf);
+    __builtin_amdgcn_sched_barrier(0);                // (x's registers are free from here on)
+    Cols<H> gt[4], qt[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const unsigned row = min(i0 + 4 * g4 + r, d.nq - 1);
+      gt[r].load(gb + ch * g_head, row, g_row, l15);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 ds = dot_rows<H>(y, vf);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 4 * g4 + r;
+      const bool vis = i < d.nq && i >= my_first && ls[r] != -INFINITY;
+      p[r] = vis ? fast_exp2(fmaf(p[r], d.scale, -ls[r]) * kLog2e) : 0.f;
+      ds[r] = p[r] * (ds[r] - de[r]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {                     // (each row of dO makes room for one of Q)
+      dv.contract(gt[r], p[r]);
+      const unsigned row = min(i0 + 4 * g4 + r, d.nq - 1);
+      qt[r].load(qb + ch * q_head, row, q_row, l15);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    rb += KL;
+    wrap();
+    dk.contract(qt[0], ds[0]);
+    dk.contract(qt[1], ds[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (n + KL < total) load_q();
+    __builtin_amdgcn_sched_barrier(0);
+    dk.contract(qt[2], ds[2]);
+    dk.contract(qt[3], ds[3]);
+  }
+  if constexpr (KL > 1) {
+    merge_lanes<KL, H / 8>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& {
+      return i < H / 16 ? dk.acc[i] : dv.acc[i - H / 16];
+    });
+    if (kl != 0) return;
+  }
+  if (key < d.nkv) {
+    const int64_t row = (int64_t)head * d.nkv + key;
+    dk.store(dK + row * H, g4, d.scale);
+    dv.store(dV + row * H, g4, 1.0f);
+  }
+}
+
+template <int H, int RT, int KL>
+hipError_t fwd_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                  float* O_part, float* m, float* l, hipStream_t s) {
+  constexpr int lds = KL > 1 ? KL / 2 * RT * (H / 16 + 1) * 1024 : 0;
+  static_assert(lds <= 80 * 1024, "two workgroups per compute unit");
+  const int per_unit = g.group / g.split;
+  dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BLK * RT - 1) / (BLK * RT)))), block(64 * KL);
+  A2D_LAUNCH((fwd_f32_kernel<H, RT, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
+             (const float*)V, O_part, m, l);
+  return hipGetLastError();
+}
+
+template <int H, int KL>
+hipError_t dq_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V, const void* O,
+                 const void* dO, const float* lse, float* delta, float* dQ, hipStream_t s) {
+  constexpr int lds = KL / 2 * (H / 16) * 1024;
+  const int per_unit = g.group / g.split;
+  dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BLK - 1) / BLK))), block(64 * KL);
+  A2D_LAUNCH((bwd_dq_f32_kernel<H, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
+             (const float*)V, (const float*)O, (const float*)dO, lse, delta, dQ);
+  return hipGetLastError();
+}
+
+template <int H, int KL>
+hipError_t dkdv_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                   const void* dO, const float* lse, const float* delta, float* dK, float* dV, hipStream_t s) {
+  constexpr int lds = KL / 2 * (H / 8) * 1024;
+  dim3 grid(xcd_grid(d.heads / g.group, (d.nkv + BLK - 1) / BLK)), block(64 * KL);
+  A2D_LAUNCH((bwd_dkdv_f32_kernel<H, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
+             (const float*)V, (const float*)dO, lse, delta, dK, dV);
+  return hipGetLastError();
+}
+
+// Key lanes of a workgroup: four, eight when that still leaves compute units without two workgroups'
+// worth of wavefronts (8 wavefronts fill a compute unit's SIMDs twice)
+bool eight_lanes(int64_t row_blocks, int cus) { return row_blocks <= cus; }
+
+template <int H>
+hipError_t fwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                 float* O_part, float* m, float* l, int cus, hipStream_t s) {
+  // 32 rows per workgroup halve the operand traffic per MFMA; 16 rows when those come to fewer than
+  // four workgroups per compute unit
+  const int64_t b32 = (int64_t)d.heads * ((d.nq + 31) / 32), b16 = (int64_t)d.heads * ((d.nq + 15) / 16);
+  if (b32 >= 4 * (int64_t)cus) return fwd_go<H, 2, 4>(d, g, Q, K, V, O_part, m, l, s);
+  if (eight_lanes(b16, cus)) return fwd_go<H, 1, 8>(d, g, Q, K, V, O_part, m, l, s);
+  return fwd_go<H, 1, 4>(d, g, Q, K, V, O_part, m, l, s);
+}
+
+template <int H>
+hipError_t bwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                 const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK, float* dV,
+                 int cus, hipStream_t s) {
+  const hipError_t e = eight_lanes((int64_t)d.heads * ((d.nq + 15) / 16), cus)
+                           ? dq_go<H, 8>(d, g, Q, K, V, O, dO, lse, delta, dQ, s)
+                           : dq_go<H, 4>(d, g, Q, K, V, O, dO, lse, delta, dQ, s);
+  if (e != hipSuccess) return e;
+  return eight_lanes((int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16), cus)
+             ? dkdv_go<H, 8>(d, g, Q, K, V, dO, lse, delta, dK, dV, s)
+             : dkdv_go<H, 4>(d, g, Q, K, V, dO, lse, delta, dK, dV, s);
+}
+
+}  // namespace
+
+hipError_t launch_fwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                          float* O_part, float* m, float* l, hipStream_t s) {
+  int cus = 0;
+  const hipError_t e = device_cus(&cus);
+  if (e != hipSuccess) return e;
+  switch (d.hdim) {
+    case 128: return fwd_h<128>(d, g, Q, K, V, O_part, m, l, cus, s);
+    case 96: return fwd_h<96>(d, g, Q, K, V, O_part, m, l, cus, s);
+    case 80: return fwd_h<80>(d, g, Q, K, V, O_part, m, l, cus, s);
+    default: return fwd_h<64>(d, g, Q, K, V, O_part, m, l, cus, s);
+  }
+}
+
+hipError_t launch_bwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                          const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK,
+                          float* dV, hipStream_t s) {
+  int cus = 0;
+  const hipError_t e = device_cus(&cus);
+  if (e != hipSuccess) return e;
+  switch (d.hdim) {
+    case 128: return bwd_h<128>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, cus, s);
+    case 96: return bwd_h<96>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, cus, s);
+    case 80: return bwd_h<80>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, cus, s);
+    default: return bwd_h<64>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, cus, s);
+  }
+}
+
+}  // namespace a2d

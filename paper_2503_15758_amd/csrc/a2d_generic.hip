@@ -1,6 +1,6 @@
 // Generic tile kernels: fp32 arithmetic on the vector ALUs, for fp32 or bf16
-// inputs, any nq / nkv, H in {64, 80, 96, 128}.  They serve the fp32 path and every shape
-// the MFMA kernels do not cover.  Structure: a 16 x 16 thread grid computes
+// inputs, any nq / nkv, H in {64, 80, 96, 128}.  A debugging aid: they run when
+// a2d_debug_force_generic() asks for them.  Structure: a 16 x 16 thread grid computes
 // register-blocked score tiles out of LDS-resident operand tiles (all widened to
 // fp32, rows padded by one word against bank conflicts); probabilities go through
 // LDS to the second contraction.
