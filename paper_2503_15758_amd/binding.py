@@ -1,8 +1,10 @@
-"""ctypes binding of liba2d.so: the same four calls as include/a2d.h, on torch tensors.
+"""Binding of liba2d.so: the calls of include/a2d.h on torch tensors.
 
 Argument marshalling only: every step of the path runs in the library's HIP
-kernels.  torch supplies device memory and the current stream.  If the library
-has not been built (python -m paper_2503_15758_amd.build) every call raises.
+kernels.  torch supplies device memory and the current stream.  The compute calls
+are marshalled by the extension module _native (csrc/a2d_torch.cpp), the queries,
+diagnostics and raw exports through ctypes.  If the library or the extension has
+not been built (python -m paper_2503_15758_amd.build) every call raises.
 """
 import ctypes
 import math
@@ -156,6 +158,24 @@ def lib():
     return _lib
 
 
+_native = None
+
+
+def _ext():
+    """The extension module that marshals the compute calls; raises if it has not been built."""
+    global _native
+    if _native is None:
+        lib()
+        try:
+            from . import _native as ext
+        except ImportError as e:
+            raise RuntimeError("the extension module _native is missing in %s: build it with "
+                               "`python -m paper_2503_15758_amd.build`" % _PKG) from e
+        ext.set_error_class(A2DError)
+        _native = ext
+    return _native
+
+
 def _check(status):
     if status != 0:
         raise A2DError(status, lib().a2d_last_error().decode())
@@ -177,17 +197,6 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
 
-def _ptr_array(ts):
-    return (ctypes.c_void_p * len(ts))(*[t.data_ptr() for t in ts])
-
-
-def _dev3(t, name):
-    """The tile calls' inputs: [heads][rows][H] device tensors (or views) whose rows of H elements are
-    contiguous; the head and row strides travel in the descriptor."""
-    if not (t.is_cuda and t.dim() == 3 and (t.stride(2) == 1 or t.shape[2] == 1)):
-        raise A2DError(-1, "%s must be a [heads][rows][H] device tensor with contiguous rows" % name)
-
-
 def _plain(ts, name):
     """What the library writes is always in the plain layout."""
     for t in ts:
@@ -196,7 +205,7 @@ def _plain(ts, name):
 
 
 def _layout(t):
-    """a2d_layout of a tensor or view accepted by _dev3 ((0, 0) for the plain layout)."""
+    """a2d_layout of a tensor or view of contiguous rows ((0, 0) for the plain layout)."""
     if t is None or t.is_contiguous():
         return Layout(0, 0)
     heads, rows, H = t.shape
@@ -217,151 +226,30 @@ def workspace_bytes(desc, op, k=0):
     return int(lib().a2d_workspace_bytes(ctypes.byref(desc), op, k))
 
 
-def _segments(segments):
-    arr = (KvSegment * len(segments))()
-    for i, (off, rows) in enumerate(segments):
-        arr[i].kv_off, arr[i].rows, arr[i].pad = int(off), int(rows), 0
-    return arr
-
-
 def partial_fwd(Q, K, V, q_off=0, kv_off=0, causal=False, scale=None, out=None, segments=None,
                 accumulate=False):
     """a2d_partial_fwd. Returns (O_part fp32 [heads][nq][H], m, l fp32 [heads][nq])."""
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
-        _dev3(t, n)
-    if K.shape != V.shape or K.shape[2] != Q.shape[2] or K.dtype != Q.dtype or V.dtype != Q.dtype:
-        raise A2DError(-1, "Q, K, V shapes / dtypes do not match")
-    d = tile_desc(Q, K, q_off, kv_off, causal, scale, V)
-    if out is None:
-        O_part = torch.empty(Q.shape, dtype=torch.float32, device=Q.device)
-        m = torch.empty(Q.shape[:2], dtype=torch.float32, device=Q.device)
-        l = torch.empty(Q.shape[:2], dtype=torch.float32, device=Q.device)
-    else:
-        O_part, m, l = out
-        _plain(out, "out=(O_part, m, l)")
-    if accumulate and out is None:
-        raise A2DError(-1, "accumulate needs out=(O_part, m, l)")
-    if K.shape[0] != Q.shape[0]:   # grouped queries: K, V hold fewer heads than Q
-        n = len(segments) if segments is not None else 0
-        _check(lib().a2d_partial_fwd_gqa(ctypes.byref(d), int(K.shape[0]), n, _segments(segments) if n else None,
-                                         TILE_ACCUMULATE if accumulate else 0, _ptr(Q), _ptr(K), _ptr(V),
-                                         _ptr(O_part), _ptr(m), _ptr(l), None, 0, _stream()))
-        return O_part, m, l
-    if accumulate:                 # out holds a partial triple of the same query block: merged in place
-        if out is None:
-            raise A2DError(-1, "accumulate needs out=(O_part, m, l)")
-        n = len(segments) if segments is not None else 0
-        _check(lib().a2d_partial_fwd_acc(ctypes.byref(d), n, _segments(segments) if n else None, _ptr(Q),
-                                         _ptr(K), _ptr(V), _ptr(O_part), _ptr(m), _ptr(l), None, 0,
-                                         _stream()))
-        return O_part, m, l
-    if segments is not None:       # gathered tile: list of (kv_off, rows) sub-blocks, kv_off unused
-        _check(lib().a2d_partial_fwd_seg(ctypes.byref(d), len(segments), _segments(segments), _ptr(Q),
-                                         _ptr(K), _ptr(V), _ptr(O_part), _ptr(m), _ptr(l), None, 0,
-                                         _stream()))
-        return O_part, m, l
-    _check(lib().a2d_partial_fwd(ctypes.byref(d), _ptr(Q), _ptr(K), _ptr(V), _ptr(O_part), _ptr(m),
-                                 _ptr(l), None, 0, _stream()))
-    return O_part, m, l
+    return (_native or _ext()).partial_fwd(Q, K, V, q_off, kv_off, causal, scale, out, segments, accumulate)
 
 
 def partial_fwd_norm(Q, K, V, q_off=0, kv_off=0, causal=False, scale=None, out=None, segments=None):
     """a2d_partial_fwd_norm: the normalised partial (O' in Q's dtype, lse' fp32) of a plain or gathered tile."""
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
-        _dev3(t, n)
-    if K.shape != V.shape or K.shape[2] != Q.shape[2] or K.dtype != Q.dtype or V.dtype != Q.dtype:
-        raise A2DError(-1, "Q, K, V shapes / dtypes do not match")
-    d = tile_desc(Q, K, q_off, kv_off, causal, scale, V)
-    if out is None:
-        O_norm = torch.empty(Q.shape, dtype=Q.dtype, device=Q.device)
-        lse = torch.empty(Q.shape[:2], dtype=torch.float32, device=Q.device)
-    else:
-        O_norm, lse = out
-        _plain(out, "out=(O_norm, lse)")
-    n = len(segments) if segments is not None else 0
-    if K.shape[0] != Q.shape[0]:   # grouped queries
-        _check(lib().a2d_partial_fwd_gqa(ctypes.byref(d), int(K.shape[0]), n, _segments(segments) if n else None,
-                                         TILE_NORMALISED, _ptr(Q), _ptr(K), _ptr(V), _ptr(O_norm), _ptr(lse),
-                                         None, None, 0, _stream()))
-        return O_norm, lse
-    _check(lib().a2d_partial_fwd_norm(ctypes.byref(d), n, _segments(segments) if n else None, _ptr(Q),
-                                      _ptr(K), _ptr(V), _ptr(O_norm), _ptr(lse), None, 0, _stream()))
-    return O_norm, lse
+    return (_native or _ext()).partial_fwd_norm(Q, K, V, q_off, kv_off, causal, scale, out, segments)
 
 
 def fix_norm(O_norms, lses, out_dtype=torch.bfloat16, out=None):
     """a2d_fix_norm over k normalised partials. Returns (O in out_dtype, lse fp32)."""
-    k = len(O_norms)
-    if k < 1 or len(lses) != k:
-        raise A2DError(-1, "need k >= 1 normalised partials")
-    shape = O_norms[0].shape
-    rows = 1
-    for s in shape[:-1]:
-        rows *= s
-    if out is None:
-        O = torch.empty(shape, dtype=out_dtype, device=O_norms[0].device)
-        lse = torch.empty(shape[:-1], dtype=torch.float32, device=O_norms[0].device)
-    else:
-        O, lse = out
-    _plain(list(O_norms) + list(lses) + [lse], "the partials and lse")
-    if not O.is_contiguous():      # a [heads][nq][H] view: written in place through its strides
-        _dev3(O, "O")
-        lo = _layout(O)
-        _check(lib().a2d_fix_norm_strided(k, O.shape[0], O.shape[1], shape[-1], _dtype_code(O_norms[0].dtype),
-                                          _dtype_code(O.dtype), _ptr_array(O_norms), _ptr_array(lses), _ptr(O),
-                                          ctypes.byref(lo), _ptr(lse), _stream()))
-        return O, lse
-    _check(lib().a2d_fix_norm(k, rows, shape[-1], _dtype_code(O_norms[0].dtype), _dtype_code(O.dtype),
-                              _ptr_array(O_norms), _ptr_array(lses), _ptr(O), _ptr(lse), _stream()))
-    return O, lse
+    return (_native or _ext()).fix_norm(O_norms, lses, out_dtype, out)
 
 
 def fix(O_parts, ms, ls, out_dtype=torch.bfloat16, out=None):
     """a2d_fix over k partial triples. Returns (O [heads][nq][H] in out_dtype, lse fp32)."""
-    k = len(O_parts)
-    if k < 1 or len(ms) != k or len(ls) != k:
-        raise A2DError(-1, "need k >= 1 partial triples")
-    shape = O_parts[0].shape
-    rows = 1
-    for s in shape[:-1]:
-        rows *= s
-    if out is None:
-        O = torch.empty(shape, dtype=out_dtype, device=O_parts[0].device)
-        lse = torch.empty(shape[:-1], dtype=torch.float32, device=O_parts[0].device)
-    else:
-        O, lse = out
-    _plain(list(O_parts) + list(ms) + list(ls) + [lse], "the partials and lse")
-    if not O.is_contiguous():      # a [heads][nq][H] view: written in place through its strides
-        _dev3(O, "O")
-        lo = _layout(O)
-        _check(lib().a2d_fix_strided(k, O.shape[0], O.shape[1], shape[-1], _dtype_code(O.dtype),
-                                     _ptr_array(O_parts), _ptr_array(ms), _ptr_array(ls), _ptr(O),
-                                     ctypes.byref(lo), _ptr(lse), _stream()))
-        return O, lse
-    _check(lib().a2d_fix(k, rows, shape[-1], _dtype_code(O.dtype), _ptr_array(O_parts),
-                         _ptr_array(ms), _ptr_array(ls), _ptr(O), _ptr(lse), _stream()))
-    return O, lse
+    return (_native or _ext()).fix(O_parts, ms, ls, out_dtype, out)
 
 
 def attnfix(O_parts, ms, ls, out=None):
     """a2d_attnfix: AttnFix alone over k partial triples. Returns one partial (N, m, l), fp32, not normalised."""
-    k = len(O_parts)
-    if k < 1 or len(ms) != k or len(ls) != k:
-        raise A2DError(-1, "need k >= 1 partial triples")
-    shape = O_parts[0].shape
-    rows = 1
-    for s in shape[:-1]:
-        rows *= s
-    if out is None:
-        N = torch.empty(shape, dtype=torch.float32, device=O_parts[0].device)
-        m = torch.empty(shape[:-1], dtype=torch.float32, device=O_parts[0].device)
-        l = torch.empty(shape[:-1], dtype=torch.float32, device=O_parts[0].device)
-    else:
-        N, m, l = out
-    _plain(list(O_parts) + list(ms) + list(ls) + [N, m, l], "the partials")
-    _check(lib().a2d_attnfix(k, rows, shape[-1], _ptr_array(O_parts), _ptr_array(ms), _ptr_array(ls),
-                             _ptr(N), _ptr(m), _ptr(l), _stream()))
-    return N, m, l
+    return (_native or _ext()).attnfix(O_parts, ms, ls, out)
 
 
 def partial_bwd(Q, K, V, O, dO, lse, q_off=0, kv_off=0, causal=False, scale=None, out=None,
@@ -373,54 +261,8 @@ def partial_bwd(Q, K, V, O, dO, lse, q_off=0, kv_off=0, causal=False, scale=None
     (grouped heads only) passes A2D_TILE_SPLIT_GROUPS: a key block may go to several workgroups,
     each summing over a share of the group's query heads (workspace of A2D_OP_PARTIAL_BWD_SPLIT
     size, which includes the dS area)."""
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (O, "O"), (dO, "dO")):
-        _dev3(t, n)
-    if O.shape != Q.shape or dO.shape != Q.shape or O.dtype != Q.dtype or dO.dtype != Q.dtype or \
-            lse.shape != Q.shape[:2] or lse.dtype != torch.float32 or K.shape != V.shape or \
-            not lse.is_contiguous():
-        raise A2DError(-1, "O, dO, lse do not match Q (lse: plain fp32 [heads][nq])")
-    d = tile_desc(Q, K, q_off, kv_off, causal, scale, V, O, dO, flags=DESC_KEEP_DS if ds_handover else 0)
-    need = workspace_bytes(d, OP_PARTIAL_BWD_DS if ds_handover else OP_PARTIAL_BWD)
-    split_groups = bool(split_groups) and K.shape[0] != Q.shape[0]
-    if split_groups:
-        need = workspace_bytes(d, OP_PARTIAL_BWD_SPLIT, int(K.shape[0]))
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
-    if out is None:
-        dQ = torch.empty(Q.shape, dtype=torch.float32, device=Q.device)
-        dK = torch.empty(K.shape, dtype=torch.float32, device=Q.device)
-        dV = torch.empty(K.shape, dtype=torch.float32, device=Q.device)
-    else:
-        dQ, dK, dV = out
-        _plain(out, "out=(dQ_part, dK_part, dV_part)")
-    if accumulate and out is None:
-        raise A2DError(-1, "accumulate needs out=(dQ_part, dK_part, dV_part)")
-    if K.shape[0] != Q.shape[0]:   # grouped queries: dK_part, dV_part have K's heads
-        n = len(segments) if segments is not None else 0
-        _check(lib().a2d_partial_bwd_gqa(ctypes.byref(d), int(K.shape[0]), n, _segments(segments) if n else None,
-                                         (TILE_ACCUMULATE if accumulate else 0) |
-                                         (TILE_SPLIT_GROUPS if split_groups else 0), _ptr(Q), _ptr(K), _ptr(V),
-                                         _ptr(O), _ptr(dO), _ptr(lse), _ptr(dQ), _ptr(dK), _ptr(dV),
-                                         _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                         _stream()))
-        return dQ, dK, dV
-    if accumulate:                 # out[0] (dQ_part) is added to
-        n = len(segments) if segments is not None else 0
-        _check(lib().a2d_partial_bwd_acc(ctypes.byref(d), n, _segments(segments) if n else None, _ptr(Q),
-                                         _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(lse), _ptr(dQ),
-                                         _ptr(dK), _ptr(dV), _ptr(workspace),
-                                         workspace.numel() * workspace.element_size(), _stream()))
-        return dQ, dK, dV
-    if segments is not None:
-        _check(lib().a2d_partial_bwd_seg(ctypes.byref(d), len(segments), _segments(segments), _ptr(Q),
-                                         _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(lse), _ptr(dQ),
-                                         _ptr(dK), _ptr(dV), _ptr(workspace),
-                                         workspace.numel() * workspace.element_size(), _stream()))
-        return dQ, dK, dV
-    _check(lib().a2d_partial_bwd(ctypes.byref(d), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO),
-                                 _ptr(lse), _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(workspace),
-                                 workspace.numel() * workspace.element_size(), _stream()))
-    return dQ, dK, dV
+    return (_native or _ext()).partial_bwd(Q, K, V, O, dO, lse, q_off, kv_off, causal, scale, out, workspace, segments,
+                                           accumulate, ds_handover, split_groups)
 
 
 STATIC_MAX_ROWS = 1 << 20
@@ -430,41 +272,12 @@ def partial_bwd_static(Q, K, V, O, dO, lse, q_off=0, kv_off=0, causal=False, sca
     """a2d_partial_bwd_static: a2d_partial_bwd without a workspace argument (the library's own static
     scratch holds delta; heads * nq <= STATIC_MAX_ROWS).  `out` = (dQ_part, dK_part, dV_part) fp32;
     with out given this function allocates nothing either."""
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (O, "O"), (dO, "dO")):
-        _dev3(t, n)
-    if O.shape != Q.shape or dO.shape != Q.shape or O.dtype != Q.dtype or dO.dtype != Q.dtype or \
-            lse.shape != Q.shape[:2] or lse.dtype != torch.float32 or K.shape != V.shape or \
-            K.shape[0] != Q.shape[0] or not lse.is_contiguous():
-        raise A2DError(-1, "O, dO, lse do not match Q (lse: plain fp32 [heads][nq]); K, V need Q's head count")
-    d = tile_desc(Q, K, q_off, kv_off, causal, scale, V, O, dO)
-    if out is None:
-        out = (torch.empty(Q.shape, dtype=torch.float32, device=Q.device),
-               torch.empty(K.shape, dtype=torch.float32, device=Q.device),
-               torch.empty(K.shape, dtype=torch.float32, device=Q.device))
-    _plain(out, "out=(dQ_part, dK_part, dV_part)")
-    dQ, dK, dV = out
-    _check(lib().a2d_partial_bwd_static(ctypes.byref(d), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(lse),
-                                        _ptr(dQ), _ptr(dK), _ptr(dV), _stream()))
-    return dQ, dK, dV
+    return (_native or _ext()).partial_bwd_static(Q, K, V, O, dO, lse, q_off, kv_off, causal, scale, out)
 
 
 def fix_bwd(parts, out_dtype=torch.bfloat16, out=None):
     """a2d_fix_bwd: sum of k fp32 partials, rounded once to out_dtype."""
-    k = len(parts)
-    if k < 1:
-        raise A2DError(-1, "need k >= 1 partials")
-    if out is None:
-        out = torch.empty(parts[0].shape, dtype=out_dtype, device=parts[0].device)
-    _plain(parts, "the partials")
-    if not out.is_contiguous():    # a [heads][rows][H] view: written in place through its strides
-        _dev3(out, "out")
-        lo = _layout(out)
-        _check(lib().a2d_fix_bwd_strided(k, out.shape[0], out.shape[1], out.shape[2], _dtype_code(out.dtype),
-                                         _ptr_array(parts), _ptr(out), ctypes.byref(lo), _stream()))
-        return out
-    _check(lib().a2d_fix_bwd(k, parts[0].numel(), _dtype_code(out.dtype), _ptr_array(parts), _ptr(out),
-                             _stream()))
-    return out
+    return (_native or _ext()).fix_bwd(parts, out_dtype, out)
 
 
 def mfma_ceiling(iters=20000, random_data=True):

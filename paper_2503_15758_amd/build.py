@@ -1,10 +1,12 @@
-"""Builds liba2d.so (the C-ABI library) from csrc/ with hipcc for gfx950.
+"""Builds liba2d.so (the C-ABI library) from csrc/ with hipcc for gfx950, and _native.so (its calls on
+torch tensors, host code only) with g++.
 
 Usage: python -m paper_2503_15758_amd.build [--force]
 """
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -12,8 +14,9 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liba2d.so")
+EXT = os.path.join(PKG, "_native.so")
 SOURCES = ["a2d_api.hip", "a2d_device.hip", "a2d_fix.hip", "a2d_generic.hip", "a2d_f32_mfma.hip",
-           "a2d_fwd_mfma.hip", "a2d_bwd_mfma.hip", "a2d_probe.hip"]
+           "a2d_fwd_mfma.hip", "a2d_bwd_mfma.hip", "a2d_grid.hip", "a2d_probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC,
@@ -37,10 +40,22 @@ def _stale(target, deps):
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def _ext_command():
+    import torch
+    t = os.path.dirname(torch.__file__)
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+            "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-isystem", os.path.join(t, "include"),
+            "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+            "-isystem", os.environ.get("ROCM_PATH", "/opt/rocm") + "/include", "-I", sysconfig.get_paths()["include"],
+            os.path.join(CSRC, "a2d_torch.cpp"), "-o", EXT, "-L", PKG, "-l:liba2d.so", "-L", os.path.join(t, "lib"),
+            "-lc10", "-lc10_hip", "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+
+
 def build(force=False, verbose=True):
     os.makedirs(OBJ, exist_ok=True)
     headers = [os.path.join(CSRC, "a2d_common.hpp"), os.path.join(CSRC, "a2d_mfma.hpp"),
-               os.path.join(ROOT, "include", "a2d.h")]
+               os.path.join(CSRC, "a2d_grid.hpp"), os.path.join(ROOT, "include", "a2d.h")]
     jobs, objs = [], []
     for src in SOURCES:
         s = os.path.join(CSRC, src)
@@ -52,6 +67,9 @@ def build(force=False, verbose=True):
         list(ex.map(_run, jobs))
     if force or jobs or _stale(LIB, objs):
         _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+    if force or _stale(EXT, [os.path.join(CSRC, "a2d_torch.cpp"), os.path.join(CSRC, "a2d_grid.hpp"),
+                             os.path.join(ROOT, "include", "a2d.h")]):
+        _run(_ext_command())
     if verbose:
         print("built", LIB, "(%d objects recompiled)" % len(jobs))
     return LIB

@@ -284,9 +284,10 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   const int qsplit = GROUPED ? g.qsplit : 1;
   const int group = GROUPED ? g.group / qsplit : 1;          // query heads this workgroup walks
   int qh0 = 0;                                               // the first of them, as a head of Q
+  const TilePos tp = tile_pos(d, g);
   {
     int unit;
-    if (!xcd_map((GROUPED ? d.heads / g.group : d.heads) * qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS, g.by_size != 0,
+    if (!xcd_map((GROUPED ? d.heads / g.group : d.heads) * qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS, tp.by_size != 0,
                  unit, blk)) return;
     head = unit / qsplit;
     const int z = unit - head * qsplit;
@@ -304,12 +305,17 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int pair = wave & 3, role = wave >> 2;   // wavefronts w and w + 4 share 32 keys
   const int l32 = lane & 31;
-  Q += (int64_t)qh0 * d.lq.head;
-  dO += (int64_t)qh0 * d.ldo.head;
-  K += (int64_t)head * d.lk.head;
-  V += (int64_t)head * d.lv.head;
-  lse += (int64_t)qh0 * d.nq;
-  delta += (int64_t)qh0 * d.nq;
+  Q += (int64_t)qh0 * d.lq.head + tp.r * g.b.q;
+  dO += (int64_t)qh0 * d.ldo.head + tp.r * g.b.g;
+  K += (int64_t)head * d.lk.head + tp.c * g.b.k;
+  V += (int64_t)head * d.lv.head + tp.c * g.b.v;
+  lse += ((int64_t)tp.r * d.heads + qh0) * d.nq;
+  delta += ((int64_t)tp.r * d.heads + qh0) * d.nq;
+  {
+    const int64_t slot = (int64_t)row_slot(g.b, tp.r, tp.c) * (GROUPED ? d.heads / g.group : d.heads) * d.nkv * H;
+    dK += slot;
+    dV += slot;
+  }
 
   DkCtx<HD> cx;
   cx.half = lane >> 5;
@@ -333,7 +339,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   // Query i sees key kk of key/value sub-block s iff i >= kk - rel[s].  seg_first_row(sb, r): first
   // local query row that sees local key r of sub-block sb (nq if none does).
   auto seg_first_row = [&](int sb, int r) -> int {
-    const int64_t f = (int64_t)(r - g.start[sb]) - g.rel[sb];
+    const int64_t f = (int64_t)(r - g.start[sb]) - g.rel[sb] - tp.rel;
     return f <= 0 ? 0 : (f >= d.nq ? d.nq : (int)f);
   };
   // smallest / largest such row over the local keys a .. b - 1 (inside a sub-block it grows with
@@ -473,7 +479,8 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   const unsigned ds_lane_off = (unsigned)(2 * blk + (pair >> 1)) * DS_TILE_BYTES + (pair & 1) * 2048 + lane * 16;
   gwptr_t ds_base = nullptr;
   if constexpr (WRITE_DS)
-    ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) + (int64_t)qh0 * ds_head_bytes(d.nq, d.nkv));
+    ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) +
+                            ((int64_t)blockIdx.y * d.heads + qh0) * ds_head_bytes(d.nq, d.nkv));
 
   // A step is skipped (by both wavefronts of its pair) when none of its rows sees any of the
   // pair's keys; it is masked unless every row sees every key.
@@ -945,15 +952,17 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   // placement as in bwd_dq_kernel (grouped heads: the query heads of a key/value head share an XCD)
   int unit, blk;
   const int per_unit = g.group / g.split;
-  if (!xcd_map(d.heads / per_unit, per_unit * nqb, g.by_size != 0, unit, blk)) return;
+  const TilePos tp = tile_pos(d, g);
+  if (!xcd_map(d.heads / per_unit, per_unit * nqb, tp.by_size != 0, unit, blk)) return;
   // (blocks numbered by size first when the workgroups are ordered by size)
-  const int head = unit * per_unit + (g.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
-  blk = g.by_size ? blk / per_unit : blk % nqb;
+  const int head = unit * per_unit + (tp.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
+  blk = tp.by_size ? blk / per_unit : blk % nqb;
   const int q0 = (nqb - 1 - blk) * DQ_ROWS;            // heavy blocks first under a causal mask
   const int tid = (int)threadIdx.x - kl * DQ_THREADS;  // within the key lane
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31;
-  K += (int64_t)kvh * d.lk.head;
+  K += (int64_t)kvh * d.lk.head + tp.c * g.b.k;
+  dQ += (int64_t)col_slot(g.b, tp.r, tp.c) * d.heads * d.nq * H;
 
   DsqCtx<HD> cx;
   cx.half = lane >> 5;
@@ -968,13 +977,14 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   // results are never stored)
   const int n_rt = ds_row_tiles(d.nq), n_kb = ds_key_blocks(d.nkv);
   const int rt = min((q0 + wave * 32) / 32, n_rt - 1);
-  const gptr_t ds_base = uniform_gptr(reinterpret_cast<const char*>(dS) + (int64_t)head * ds_head_bytes(d.nq, d.nkv) +
+  const gptr_t ds_base = uniform_gptr(reinterpret_cast<const char*>(dS) +
+                                      ((int64_t)blockIdx.y * d.heads + head) * ds_head_bytes(d.nq, d.nkv) +
                                       (int64_t)rt * n_kb * DS_TILE_BYTES);
 
   // visibility per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
   auto vis_count = [&](int i, int s) -> int {
     if (!d.causal) return g.rows[s];
-    const int64_t v = (int64_t)i + g.rel[s] + 1;
+    const int64_t v = (int64_t)i + g.rel[s] + tp.rel + 1;
     return v <= 0 ? 0 : (v < g.rows[s] ? (int)v : g.rows[s]);
   };
   const int blk_last = min(q0 + DQ_ROWS, d.nq) - 1;
@@ -1152,9 +1162,11 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   int cus = 0;
   hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
-  const bool big = (int64_t)d.heads * ((d.nq + 255) / 256) >= cus;
+  const int tiles = g.b.n ? g.b.n : 1;
+  const int64_t heads = (int64_t)d.heads * tiles;
+  const bool big = heads * ((d.nq + 255) / 256) >= cus;
   // the dQ kernel walks the keys in two lanes when at most one 128-row block comes to a compute unit
-  const bool lanes = !big && (int64_t)d.heads * ((d.nq + 127) / 128) <= cus;
+  const bool lanes = !big && heads * ((d.nq + 127) / 128) <= cus;
   if (ph == PREPARE) {
     e = ensure_dynamic_lds(grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, true>)
                                    : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, true>), DK_LDS);
@@ -1163,10 +1175,10 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
                  : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 1>)
                                           : reinterpret_cast<const void*>(bwd_dq_ds_kernel<4, HR, 1>), DSQ_LDS);
   }
-  dim3 grid_kv(xcd_grid(d.heads / g.group * g.qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS));
+  dim3 grid_kv(xcd_grid(d.heads / g.group * g.qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS), tiles);
   const int dq_rows = big ? 256 : 128;
   const int per_unit = g.group / g.split;
-  dim3 grid_q(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + dq_rows - 1) / dq_rows)));
+  dim3 grid_q(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + dq_rows - 1) / dq_rows)), tiles);
   if (grouped)
     A2D_LAUNCH((bwd_dkdv_kernel<HR, true, true>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV,

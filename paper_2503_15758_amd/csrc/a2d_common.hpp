@@ -47,6 +47,16 @@ template <> struct dtype_of<bf16_t> { static constexpr int value = A2D_BF16; };
 // separate runs (1 = all of them on one XCD; chosen by group_split()).
 // `by_size` != 0: the blocks of the tile differ in cost (a causal mask crosses it); the kernels then
 // order their workgroups by block, heaviest first, over a whole XCD (see xcd_map).
+// A launch over many tiles of one emulated side x side grid (one tile per grid.y; n = 0: a plain
+// call).  All blocks of the grid are views of the same tensors: block b of Q starts b * q elements
+// after block 0, and so on.  Tile (r, c) = query block r against key block c; under the causal mask
+// rel = q_off - kv_off is (r - c) * rows for contiguous blocks, 0 / -1 (r >= c / r < c) for cyclic
+// ones.  tri != 0: only the tiles c <= r exist.
+struct TileBatch {
+  int n, first;        // tiles of this launch, number of its first tile
+  int side, tri, cyclic;
+  int64_t q, k, v, g;  // elements between blocks of Q, K, V, dO
+};
 struct SegList {
   int n;
   int acc;
@@ -54,6 +64,7 @@ struct SegList {
   int group;
   int split;
   int by_size;
+  TileBatch b;
   int qsplit;     // dK/dV kernel, grouped heads: workgroups per key block, each walking group / qsplit query heads
   int start[A2D_MAX_SEGMENTS];
   int rows[A2D_MAX_SEGMENTS];
@@ -66,6 +77,45 @@ inline int group_split(int kv_heads, int group) {
   for (int s = 1; s <= group; ++s)
     if (group % s == 0 && (kv_heads * s) % 8 == 0) return s;
   return group;
+}
+
+// The tile this workgroup belongs to (all zero for a plain call).
+// Partials of a batch are stored by slot: col_slot() puts the tiles of one grid column next to each
+// other (what the merge over a grid row reads as one array per column), row_slot() those of one row.
+struct TilePos {
+  int r, c, by_size;
+  int64_t rel;
+};
+__device__ __forceinline__ TilePos tile_pos(const a2d_tile_desc& d, const SegList& g) {
+  TilePos p{0, 0, g.by_size, 0};
+  if (g.b.n == 0) return p;
+  int t = g.b.first + blockIdx.y;
+  if (g.b.tri) {                                 // whole tiles first, then those on the diagonal
+    const int whole = g.b.side * (g.b.side - 1) / 2;
+    if (t < whole) {
+      p.r = 1;
+      while (t >= p.r) { t -= p.r; ++p.r; }
+      p.c = t;
+    } else {
+      p.r = p.c = t - whole;
+    }
+  } else {
+    p.r = t / g.b.side;
+    p.c = t - p.r * g.b.side;
+  }
+  if (d.causal) {
+    p.rel = g.b.cyclic ? (p.r >= p.c ? 0 : -1) : (int64_t)(p.r - p.c) * d.nq;
+    p.by_size = g.b.cyclic || p.r == p.c;        // the mask crosses the tile
+  } else {
+    p.by_size = 0;
+  }
+  return p;
+}
+__host__ __device__ inline int col_slot(const TileBatch& b, int r, int c) {
+  return b.n == 0 ? 0 : b.tri ? c * b.side - c * (c - 1) / 2 + r - c : c * b.side + r;
+}
+__host__ __device__ inline int row_slot(const TileBatch& b, int r, int c) {
+  return b.n == 0 ? 0 : b.tri ? r * (r + 1) / 2 + c : r * b.side + c;
 }
 
 // sub-block that holds local key c (c < nkv)
@@ -158,6 +208,27 @@ struct OutMap {
   int plain;
 };
 inline OutMap plain_out() { return OutMap{0, 0, 1, 1}; }
+// The merged output of a whole emulated grid: block b, head h, row i of the merge's input is token
+// i * side + b (cyclic) or b * rows + i of head h in a plain [heads][side * rows][H] tensor.  dir: which
+// partials block b has - 0: all `side`; 1: those x <= b (a grid row under the causal mask,
+// contiguous blocks); 2: those x >= b (a grid column).
+struct GridMap {
+  int side, rows, heads, cyclic, dir;
+  __host__ __device__ __forceinline__ bool has(int b, int x) const { return dir == 0 || (dir == 1 ? x <= b : x >= b); }
+};
+// O, lse of a whole grid from its partial triples; sums of up to three sets of gradient partials
+hipError_t launch_fix_grid(const GridMap& gm, int hdim, int out_dtype, const FixPtrs& p, void* O, float* lse,
+                           hipStream_t s);
+struct SumSet {
+  SumPtrs p;
+  GridMap gm;
+  void* out;
+};
+hipError_t launch_sum_grid(int nsets, const SumSet* sets, int hdim, int out_dtype, hipStream_t s);
+// delta and lse of a whole [heads][side * rows] sequence, block by block: [side][heads][rows]
+hipError_t launch_delta_grid(const GridMap& gm, int hdim, const a2d_layout& lo, const a2d_layout& ldo, const bf16_t* O,
+                             const bf16_t* dO, const float* lse, float* delta_blk, float* lse_blk, hipStream_t s);
+
 hipError_t launch_fix(int k, int64_t rows, int hdim, int out_dtype, const FixPtrs& p, const OutMap& om, void* O,
                       float* lse, hipStream_t s);
 hipError_t launch_attnfix(int k, int64_t rows, int hdim, const FixPtrs& p, float* N, float* m, float* l,

@@ -190,6 +190,89 @@ __global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_
   }
 }
 
+// ---- the merges of a whole emulated grid, one launch for all its blocks.  Same arithmetic and
+// order of sums as above; which partials a block has and where its rows go follows from GridMap.
+// (Everything but the partials' addresses fits 32 bits: the launcher checks it.)
+struct GridRow {
+  int b, h, i;                                     // block, head, row inside the block
+  __device__ __forceinline__ GridRow(const GridMap& g, unsigned row) {
+    const unsigned hb = row / (unsigned)g.rows;
+    i = row - hb * g.rows;
+    b = hb / (unsigned)g.heads;
+    h = hb - b * g.heads;
+  }
+  __device__ __forceinline__ int64_t token(const GridMap& g) const {
+    return (int64_t)h * g.side * g.rows + (g.cyclic ? i * g.side + b : b * g.rows + i);
+  }
+};
+
+template <typename OutT, int KMAX>
+__global__ __launch_bounds__(256) void fix_grid_kernel(FixPtrs p, GridMap g, int hv, OutT* __restrict__ O,
+                                                       float* __restrict__ lse) {
+  const unsigned idx = blockIdx.x * 256 + threadIdx.x;
+  const unsigned row = idx / (unsigned)hv, col = idx - row * hv;
+  if (row >= (unsigned)(g.side * g.heads * g.rows)) return;
+  const GridRow gr(g, row);
+  f32x4 n[KMAX];
+  float mk[KMAX], lk[KMAX];
+#pragma unroll
+  for (int x = 0; x < KMAX; ++x) {
+    if (x < g.side && g.has(gr.b, x)) {
+      n[x] = A2D_LD(reinterpret_cast<const f32x4*>(p.o[x]) + idx);
+      mk[x] = p.m[x][row];
+      lk[x] = p.l[x][row];
+    } else {
+      n[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+      mk[x] = -INFINITY;
+      lk[x] = 0.f;
+    }
+  }
+  float M = -INFINITY;
+#pragma unroll
+  for (int x = 0; x < KMAX; ++x) M = fmaxf(M, mk[x]);
+  float D = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int x = 0; x < KMAX; ++x) {
+    const float w = (mk[x] == -INFINITY) ? 0.f : fast_exp2((mk[x] - M) * kLog2e);
+    D = fmaf(w, lk[x], D);
+    acc[0] = fmaf(w, n[x][0], acc[0]);
+    acc[1] = fmaf(w, n[x][1], acc[1]);
+    acc[2] = fmaf(w, n[x][2], acc[2]);
+    acc[3] = fmaf(w, n[x][3], acc[3]);
+  }
+  const float inv = (D > 0.f) ? 1.0f / D : 0.f;
+  acc[0] *= inv; acc[1] *= inv; acc[2] *= inv; acc[3] *= inv;
+  const int64_t t = gr.token(g);
+  store_out4(O, (t * hv + col) * 4, acc);
+  if (col == 0) lse[t] = (D > 0.f) ? M + logf(D) : -INFINITY;
+}
+
+struct SumSets {
+  SumSet s[3];
+};
+template <typename OutT, int KMAX>
+__global__ __launch_bounds__(256) void sum_grid_kernel(SumSets a, int hv) {
+  const SumSet& s = a.s[blockIdx.y];
+  const GridMap& g = s.gm;
+  const unsigned idx = blockIdx.x * 256 + threadIdx.x;
+  const unsigned row = idx / (unsigned)hv, col = idx - row * hv;
+  if (row >= (unsigned)(g.side * g.heads * g.rows)) return;
+  const GridRow gr(g, row);
+  f32x4 v[KMAX];
+#pragma unroll
+  for (int x = 0; x < KMAX; ++x) {
+    if (x < g.side && g.has(gr.b, x)) v[x] = A2D_LD(reinterpret_cast<const f32x4*>(s.p.p[x]) + idx);
+    else v[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  f32x4 acc = v[0];
+#pragma unroll
+  for (int x = 1; x < KMAX; ++x) {
+    acc[0] += v[x][0]; acc[1] += v[x][1]; acc[2] += v[x][2]; acc[3] += v[x][3];
+  }
+  store_out4(static_cast<OutT*>(s.out), (gr.token(g) * hv + col) * 4, acc);
+}
+
 template <typename OutT, int KMAX, bool TRIPLE = false>
 void fix_launch(int k, int64_t rows, int hv, const FixPtrs& p, const OutMap& om, OutT* O, float* lse, float* l_out,
                 hipStream_t s) {
@@ -267,6 +350,52 @@ hipError_t launch_fix(int k, int64_t rows, int hdim, int out_dtype, const FixPtr
                       float* lse, hipStream_t s) {
   if (out_dtype == A2D_BF16) return fix_dispatch<bf16_t>(k, rows, hdim, p, om, (bf16_t*)O, lse, nullptr, s);
   return fix_dispatch<float>(k, rows, hdim, p, om, (float*)O, lse, nullptr, s);
+}
+
+namespace {
+template <typename OutT>
+void fix_grid_dispatch(const GridMap& gm, int hv, const FixPtrs& p, OutT* O, float* lse, hipStream_t s) {
+  const dim3 grid((unsigned)(((int64_t)gm.side * gm.heads * gm.rows * hv + 255) / 256)), block(256);
+#define A2D_GO(KMAX) A2D_LAUNCH((fix_grid_kernel<OutT, KMAX>), grid, block, 0, s, p, gm, hv, O, lse)
+  if (gm.side <= 2) A2D_GO(2);
+  else if (gm.side <= 4) A2D_GO(4);
+  else if (gm.side <= 8) A2D_GO(8);
+  else if (gm.side <= 16) A2D_GO(16);
+  else A2D_GO(32);
+#undef A2D_GO
+}
+template <typename OutT>
+void sum_grid_dispatch(int nsets, const SumSets& a, int hv, int64_t blocks, hipStream_t s) {
+  const dim3 grid((unsigned)blocks, nsets), block(256);
+  const int side = a.s[0].gm.side;
+#define A2D_GO(KMAX) A2D_LAUNCH((sum_grid_kernel<OutT, KMAX>), grid, block, 0, s, a, hv)
+  if (side <= 2) A2D_GO(2);
+  else if (side <= 4) A2D_GO(4);
+  else if (side <= 8) A2D_GO(8);
+  else if (side <= 16) A2D_GO(16);
+  else A2D_GO(32);
+#undef A2D_GO
+}
+}  // namespace
+
+hipError_t launch_fix_grid(const GridMap& gm, int hdim, int out_dtype, const FixPtrs& p, void* O, float* lse,
+                           hipStream_t s) {
+  if (out_dtype == A2D_BF16) fix_grid_dispatch<bf16_t>(gm, hdim / 4, p, (bf16_t*)O, lse, s);
+  else fix_grid_dispatch<float>(gm, hdim / 4, p, (float*)O, lse, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_grid(int nsets, const SumSet* sets, int hdim, int out_dtype, hipStream_t s) {
+  SumSets a;
+  int64_t most = 0;
+  for (int x = 0; x < 3; ++x) {
+    a.s[x] = sets[x < nsets ? x : 0];
+    const int64_t n = (int64_t)a.s[x].gm.side * a.s[x].gm.heads * a.s[x].gm.rows * (hdim / 4);
+    if (n > most) most = n;
+  }
+  if (out_dtype == A2D_BF16) sum_grid_dispatch<bf16_t>(nsets, a, hdim / 4, (most + 255) / 256, s);
+  else sum_grid_dispatch<float>(nsets, a, hdim / 4, (most + 255) / 256, s);
+  return hipGetLastError();
 }
 
 // the merge alone: k partials in, one unnormalised partial (N, m, l) out

@@ -173,19 +173,26 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // the query blocks of the query heads that share a key/value head go to one XCD (to g.split
   // XCDs, an equal share of the heads each, when that is what spreads the load evenly)
   int unit, blk;
+  const TilePos tp = tile_pos(d, g);
   const int per_unit = g.group / g.split;
-  if (!xcd_map(d.heads / per_unit, per_unit * nqb, g.by_size != 0, unit, blk)) return;
+  if (!xcd_map(d.heads / per_unit, per_unit * nqb, tp.by_size != 0, unit, blk)) return;
   // (blocks numbered by size first when the workgroups are ordered by size)
-  const int head = unit * per_unit + (g.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
-  blk = g.by_size ? blk / per_unit : blk % nqb;
+  const int head = unit * per_unit + (tp.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
+  blk = tp.by_size ? blk / per_unit : blk % nqb;
   // heavy (late) query blocks first: under a causal mask they walk more key blocks
   const int q0 = (nqb - 1 - blk) * BM;
   const int tid = (int)threadIdx.x - kl * kThreads;     // within the key lane
   const int wave = tid >> 6, lane = tid & 63;
   const int half = lane >> 5, l32 = lane & 31;
-  Q += (int64_t)head * d.lq.head;
-  K += (int64_t)kvh * d.lk.head;
-  V += (int64_t)kvh * d.lv.head;
+  Q += (int64_t)head * d.lq.head + tp.r * g.b.q;
+  K += (int64_t)kvh * d.lk.head + tp.c * g.b.k;
+  V += (int64_t)kvh * d.lv.head + tp.c * g.b.v;
+  {
+    const int64_t slot = (int64_t)col_slot(g.b, tp.r, tp.c) * d.heads * d.nq;
+    O_part += slot * HR;
+    m_out += slot;
+    l_out += slot;
+  }
 
   // ---- Q^T fragments: lane holds query row (l32), h = 16*step + 8*half + 0..7.
   // Rows beyond nq re-read the last row (their results are never stored).
@@ -264,7 +271,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // (key kk of the sub-block iff kk <= i + rel[s])
   auto vis_count = [&](int i, int s) -> int {
     if (!d.causal) return g.rows[s];
-    const int64_t v = (int64_t)i + g.rel[s] + 1;
+    const int64_t v = (int64_t)i + g.rel[s] + tp.rel + 1;
     return v <= 0 ? 0 : (v < g.rows[s] ? (int)v : g.rows[s]);
   };
   const int blk_last = min(q0 + BM, d.nq) - 1;
@@ -460,7 +467,7 @@ hipError_t fwd_launch(Phase ph, const a2d_tile_desc& d, const SegList& g, const 
   if (ph == PREPARE)
     return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_mfma_kernel<WAVES, HR, KL>), bytes);
   const int per_unit = g.group / g.split;
-  dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BM - 1) / BM))), block(64 * WAVES);
+  dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BM - 1) / BM)), g.b.n ? g.b.n : 1), block(64 * WAVES);
   A2D_LAUNCH((fwd_mfma_kernel<WAVES, HR, KL>), grid, block, bytes, s, d, g, (const bf16_t*)Q,
                      (const bf16_t*)K, (const bf16_t*)V, O_part, m, l);
   return hipGetLastError();
@@ -474,8 +481,9 @@ hipError_t launch_fwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, c
   int cus = 0;
   const hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
-  const bool big = (int64_t)d.heads * ((d.nq + 255) / 256) >= cus;
-  const bool lanes = !big && (int64_t)d.heads * ((d.nq + 127) / 128) <= cus;
+  const int64_t heads = (int64_t)d.heads * (g.b.n ? g.b.n : 1);
+  const bool big = heads * ((d.nq + 255) / 256) >= cus;
+  const bool lanes = !big && heads * ((d.nq + 127) / 128) <= cus;
 #define A2D_FWD(HR)                                                                      \
   return big     ? fwd_launch<8, HR, 1>(ph, d, g, Q, K, V, O_part, m, l, s)              \
          : lanes ? fwd_launch<8, HR, 2>(ph, d, g, Q, K, V, O_part, m, l, s)              \

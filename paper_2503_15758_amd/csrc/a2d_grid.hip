@@ -1,0 +1,180 @@
+// The whole-grid launches (see a2d_grid.hpp).  Host code only.
+//
+// Why batched: a grid of small tiles is bound by everything but the tiles' arithmetic when each tile is
+// a call of its own - index gathers of the blocks, stream events, a handful of launches per tile, tiles
+// that fill an eighth of the chip.  512 tokens on a 2 x 2 grid took 52 launches and 680 us for 60 us of
+// kernels; 8192 tokens x 16 heads on 4 x 4 took 2.8 ms for 1.3 ms' worth of work.
+#include "a2d_grid.hpp"
+
+#include <cstring>
+
+#include "a2d_common.hpp"
+
+namespace a2d {
+namespace {
+
+// dS kept at a time by the batched backward: enough tiles to fill the chip many times over, and small
+// beside what a grid's own partials take
+constexpr size_t kGridDsBytes = (size_t)2 << 30;
+
+int rows_of(const GridProblem& p) { return p.seq / p.side; }
+int tri_of(const GridProblem& p) { return p.causal && !p.cyclic; }
+int slots_of(const GridProblem& p) { return tri_of(p) ? p.side * (p.side + 1) / 2 : p.side * p.side; }
+size_t up256(size_t n) { return (n + 255) / 256 * 256; }
+
+int64_t block_step(const GridProblem& p, const a2d_layout& l) { return p.cyclic ? l.row : l.row * rows_of(p); }
+a2d_layout block_layout(const GridProblem& p, const a2d_layout& l) {
+  return a2d_layout{l.head, p.cyclic ? l.row * p.side : l.row};
+}
+
+void describe(const GridProblem& p, a2d_tile_desc* d, SegList* g) {
+  memset(d, 0, sizeof(*d));
+  memset(g, 0, sizeof(*g));
+  d->heads = p.heads;
+  d->nq = d->nkv = rows_of(p);
+  d->hdim = p.hdim;
+  d->causal = p.causal;
+  d->scale = p.scale;
+  d->dtype = A2D_BF16;
+  d->lq = block_layout(p, p.q);
+  d->lk = block_layout(p, p.k);
+  d->lv = block_layout(p, p.v);
+  d->lo = block_layout(p, p.o);
+  d->ldo = block_layout(p, p.g);
+  g->n = 1;
+  g->group = p.heads / p.kv_heads;
+  g->split = group_split(p.kv_heads, g->group);
+  g->qsplit = 1;
+  g->rows[0] = rows_of(p);
+  g->b.n = slots_of(p);
+  g->b.side = p.side;
+  g->b.tri = tri_of(p);
+  g->b.cyclic = p.cyclic;
+  g->b.q = block_step(p, p.q);
+  g->b.k = block_step(p, p.k);
+  g->b.v = block_step(p, p.v);
+  g->b.g = block_step(p, p.g);
+}
+
+// tiles whose dS is kept at a time
+int chunk_of(const GridProblem& p, const a2d_tile_desc& d, const SegList& g) {
+  const size_t per_tile = bwd_ds_bytes(d, g);
+  const size_t n = per_tile ? kGridDsBytes / per_tile : 1;
+  return n < 1 ? 1 : n > (size_t)slots_of(p) ? slots_of(p) : (int)n;
+}
+
+GridMap map_of(const GridProblem& p, int heads, int dir) {
+  return GridMap{p.side, rows_of(p), heads, p.cyclic, tri_of(p) ? dir : 0};
+}
+
+}  // namespace
+
+bool grid_supported(const GridProblem& p) {
+  if (p.heads < 1 || p.kv_heads < 1 || p.heads % p.kv_heads || p.heads > 65535 || p.side < 1 ||
+      p.side > A2D_MAX_PARTS || p.seq < p.side || p.seq % p.side || p.seq > (1 << 22) || !(p.scale > 0.f))
+    return false;
+  if (p.hdim != 64 && p.hdim != 80 && p.hdim != 96 && p.hdim != 128) return false;
+  if ((int64_t)p.heads * p.seq * (p.hdim / 4) >= ((int64_t)1 << 31)) return false;   // 32-bit indices of the merges
+  const int group = p.heads / p.kv_heads;
+  if ((int64_t)group * rows_of(p) > (1 << 22)) return false;
+  const a2d_layout* all[5] = {&p.q, &p.k, &p.v, &p.o, &p.g};
+  for (int i = 0; i < 5; ++i) {
+    const a2d_layout& l = *all[i];
+    const int64_t heads = (i == 1 || i == 2) ? 1 : group;
+    if (l.row < p.hdim || l.head < 1 || l.row % 8 || l.head % 8 || l.row > ((int64_t)1 << 30) ||
+        l.head > ((int64_t)1 << 40))
+      return false;
+    if (l.row * (p.cyclic ? p.side : 1) * 2 >= ((int64_t)1 << 24)) return false;
+    if (((heads - 1) * l.head + (int64_t)p.seq * l.row) * 2 >= ((int64_t)1 << 32)) return false;
+  }
+  a2d_tile_desc d;
+  SegList g;
+  describe(p, &d, &g);
+  return bwd_ds_bytes(d, g) > 0;
+}
+
+size_t grid_forward_bytes(const GridProblem& p) {
+  return (size_t)slots_of(p) * p.heads * rows_of(p) * (p.hdim + 2) * sizeof(float);
+}
+
+size_t grid_backward_bytes(const GridProblem& p) {
+  a2d_tile_desc d;
+  SegList g;
+  describe(p, &d, &g);
+  const size_t stats = 2 * up256((size_t)p.heads * p.seq * sizeof(float));
+  const size_t parts = (size_t)slots_of(p) * rows_of(p) * p.hdim * (p.heads + 2 * (size_t)p.kv_heads) * sizeof(float);
+  return stats + up256(parts) + (size_t)chunk_of(p, d, g) * bwd_ds_bytes(d, g);
+}
+
+hipError_t grid_forward(const GridProblem& p, const void* Q, const void* K, const void* V, void* O, float* lse,
+                        void* ws, hipStream_t s) {
+  a2d_tile_desc d;
+  SegList g;
+  describe(p, &d, &g);
+  const size_t per = (size_t)p.heads * rows_of(p), slots = slots_of(p);
+  float* N = static_cast<float*>(ws);
+  float* m = N + slots * per * p.hdim;
+  float* l = m + slots * per;
+  hipError_t e = launch_fwd_mfma(PREPARE, d, g, Q, K, V, N, m, l, s);
+  if (e != hipSuccess) return e;
+  trace_mark(s);
+  e = launch_fwd_mfma(LAUNCH, d, g, Q, K, V, N, m, l, s);      // Alg. 1 line 4, every tile
+  if (e != hipSuccess) return e;
+  FixPtrs f;
+  memset(&f, 0, sizeof(f));
+  for (int c = 0; c < p.side; ++c) {                           // column c's partials, indexed by (row block, head, row)
+    const size_t at = (size_t)(col_slot(g.b, c, c) - c) * per;
+    f.o[c] = N + at * p.hdim;
+    f.m[c] = m + at;
+    f.l[c] = l + at;
+  }
+  return launch_fix_grid(map_of(p, p.heads, 1), p.hdim, A2D_BF16, f, O, lse, s);   // Alg. 1 lines 5-6
+}
+
+hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, const void* V, const void* O,
+                         const void* dO, const float* lse, void* dQ, void* dK, void* dV, void* ws, hipStream_t s) {
+  a2d_tile_desc d;
+  SegList g;
+  describe(p, &d, &g);
+  const size_t rows = rows_of(p), slots = slots_of(p);
+  const size_t stat = up256((size_t)p.heads * p.seq * sizeof(float));
+  char* w = static_cast<char*>(ws);
+  float* delta = reinterpret_cast<float*>(w);
+  float* lse_blk = reinterpret_cast<float*>(w + stat);
+  float* dq = reinterpret_cast<float*>(w + 2 * stat);
+  float* dk = dq + slots * p.heads * rows * p.hdim;
+  float* dv = dk + slots * p.kv_heads * rows * p.hdim;
+  const size_t parts = slots * rows * p.hdim * (p.heads + 2 * (size_t)p.kv_heads) * sizeof(float);
+  void* ds = w + 2 * stat + up256(parts);
+  const int chunk = chunk_of(p, d, g), total = slots_of(p);
+  for (int pass = 0; pass < 2; ++pass) {                       // everything that can fail on the host first
+    if (pass == 1) {
+      trace_mark(s);
+      const hipError_t e = launch_delta_grid(map_of(p, p.heads, 0), p.hdim, p.o, p.g, (const bf16_t*)O,
+                                             (const bf16_t*)dO, lse, delta, lse_blk, s);
+      if (e != hipSuccess) return e;
+    }
+    for (int t = 0; t < total; t += chunk) {                   // Alg. 3 line 3, every tile
+      g.b.first = t;
+      g.b.n = total - t < chunk ? total - t : chunk;
+      const hipError_t e = launch_bwd_mfma(pass == 0 ? PREPARE : LAUNCH, d, g, Q, K, V, dO, lse_blk, delta, dq, dk, dv,
+                                           ds, nullptr, s);
+      if (e != hipSuccess) return e;
+    }
+  }
+  SumSet sets[3];
+  memset(sets, 0, sizeof(sets));
+  for (int x = 0; x < p.side; ++x) {
+    sets[0].p.p[x] = dq + (size_t)(col_slot(g.b, x, x) - x) * p.heads * rows * p.hdim;
+    sets[1].p.p[x] = dk + (size_t)row_slot(g.b, x, 0) * p.kv_heads * rows * p.hdim;
+    sets[2].p.p[x] = dv + (size_t)row_slot(g.b, x, 0) * p.kv_heads * rows * p.hdim;
+  }
+  sets[0].gm = map_of(p, p.heads, 1);
+  sets[1].gm = sets[2].gm = map_of(p, p.kv_heads, 2);
+  sets[0].out = dQ;
+  sets[1].out = dK;
+  sets[2].out = dV;
+  return launch_sum_grid(3, sets, p.hdim, A2D_BF16, s);        // Alg. 3 lines 4-5
+}
+
+}  // namespace a2d

@@ -1,0 +1,31 @@
+// Alg. 1 and Alg. 3 over a whole emulated side x side grid in a handful of launches: every tile of the
+// grid is computed by the tile kernels as in the single calls, many tiles per launch (TileBatch), on
+// the blocks where they lie in the sequence (contiguous or cyclic: a stride, not a copy).
+#pragma once
+#include <hip/hip_runtime_api.h>
+
+#include "a2d.h"
+
+namespace a2d {
+
+bool force_generic();            // the debug switch a2d_debug_force_generic() sets
+
+struct GridProblem {
+  int heads, kv_heads, seq, side, hdim, causal, cyclic;
+  float scale;
+  a2d_layout q, k, v, o, g;      // layouts of Q, K, V, O, dO over the whole sequence (elements)
+};
+
+// Whether the batched path covers the problem (bf16; the kernels' 32-bit offsets, the dS hand-over)
+bool grid_supported(const GridProblem& p);
+// Workspace in bytes; dS of as many tiles as fit kGridDsBytes is kept at a time (at least one tile's)
+size_t grid_forward_bytes(const GridProblem& p);
+size_t grid_backward_bytes(const GridProblem& p);
+// O: plain bf16 [heads][seq][H], lse [heads][seq].  Both only enqueue on `s`.
+hipError_t grid_forward(const GridProblem& p, const void* Q, const void* K, const void* V, void* O, float* lse,
+                        void* ws, hipStream_t s);
+// O, dO with the layouts p.o, p.g; lse plain; dQ, dK, dV plain bf16
+hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, const void* V, const void* O,
+                         const void* dO, const float* lse, void* dQ, void* dK, void* dV, void* ws, hipStream_t s);
+
+}  // namespace a2d

@@ -1,11 +1,14 @@
 """The non-overlapped Attention2D forward and backward (Alg. 1 and Alg. 3) over an emulated
 sqrt(P) x sqrt(P) device grid on ONE GPU.
 
-Every "device" (r, c) of the paper becomes one tile call of the library; the collectives become
-plain data movement on the one GPU (the row / column all-gathers are index gathers of the blocks,
-the reduce-scatters are the library's merge calls).  Tiles are independent (Sec. 3.2), so they are
-issued round-robin on several HIP streams of default priority.  This module only marshals: all
-arithmetic of the method runs in the library's kernels.
+Every "device" (r, c) of the paper is one tile of the library's tile kernels; the collectives become
+plain data movement on the one GPU.  Tiles are independent (Sec. 3.2).  For bf16 tensors a grid is a
+handful of launches, each over all its tiles, which read their blocks where they lie in the sequence
+(csrc/a2d_grid.hip).  Otherwise (fp32, merge="ring", ds_handover=False, strides the kernels do not
+take) every tile is a call of its own: the row / column all-gathers are index gathers of the blocks,
+the reduce-scatters the library's merge calls, and the calls go round-robin onto several HIP streams
+of default priority; `streams` says how many.  Either way the result does not depend on `streams`.
+This module only marshals: all arithmetic of the method runs in the library's kernels.
 
 Layouts of the sequence over the grid (Sec. 3.2):
   "cyclic"      Q block r = tokens {r + i sqrtP}, K/V block c = tokens {c + j sqrtP}: under the causal
@@ -19,16 +22,20 @@ import torch
 from . import binding as a2d
 
 
-def block_indices(n, grid, layout, device):
-    """Token indices of block b = 0 .. grid - 1 (the same sets serve queries and keys)."""
+def _check_blocks(n, grid, layout):
     if n % grid:
         raise ValueError("sequence length %d is not a multiple of the grid side %d" % (n, grid))
+    if layout not in ("cyclic", "contiguous"):
+        raise ValueError("layout must be 'cyclic' or 'contiguous'")
+
+
+def block_indices(n, grid, layout, device):
+    """Token indices of block b = 0 .. grid - 1 (the same sets serve queries and keys)."""
+    _check_blocks(n, grid, layout)
     T = n // grid
     if layout == "cyclic":
         return [torch.arange(b, n, grid, device=device) for b in range(grid)]
-    if layout == "contiguous":
-        return [torch.arange(b * T, (b + 1) * T, device=device) for b in range(grid)]
-    raise ValueError("layout must be 'cyclic' or 'contiguous'")
+    return [torch.arange(b * T, (b + 1) * T, device=device) for b in range(grid)]
 
 
 def tile_offsets(r, c, T, layout):
@@ -73,6 +80,11 @@ def forward(Q, K, V, grid, causal=True, layout="cyclic", scale=None, streams=4, 
     (Alg. 1 line 5), then the division of line 6 (a2d_fix of the one remaining partial)."""
     heads, n, H = Q.shape
     scale = float(scale if scale is not None else 1.0 / math.sqrt(H))
+    _check_blocks(n, grid, layout)
+    if merge == "kway":
+        got = a2d._ext().grid_forward(Q, K, V, grid, causal, layout == "cyclic", scale)
+        if got is not None:
+            return got
     idx = block_indices(n, grid, layout, Q.device)
     T = n // grid
     Qb = [Q.index_select(1, i) for i in idx]           # row all-gather of the query blocks
@@ -108,10 +120,15 @@ def forward(Q, K, V, grid, causal=True, layout="cyclic", scale=None, streams=4, 
 def backward(Q, K, V, O, dO, lse, grid, causal=True, layout="cyclic", scale=None, streams=4,
              ds_handover=True):
     """Alg. 3: dQ, dK, dV [heads][n][H] in the input dtype from the saved O and lse.
-    ds_handover: give every stream the larger workspace with which the tile call keeps dS for its dQ
-    contraction instead of recomputing the scores (about 2 T^2 bytes per head and stream more)."""
+    ds_handover: keep dS for the dQ contraction instead of recomputing the scores (about 2 T^2 bytes per
+    head and tile more, for at most 2 GiB worth of tiles - or one tile - at a time)."""
     heads, n, H = Q.shape
     scale = float(scale if scale is not None else 1.0 / math.sqrt(H))
+    _check_blocks(n, grid, layout)
+    if ds_handover:
+        got = a2d._ext().grid_backward(Q, K, V, O, dO, lse, grid, causal, layout == "cyclic", scale)
+        if got is not None:
+            return got
     idx = block_indices(n, grid, layout, Q.device)
     T = n // grid
     gather = lambda X: [X.index_select(1, i) for i in idx]
