@@ -268,7 +268,9 @@ __device__ __forceinline__ void ds_turn_read(unsigned piece, int lane, bf16x8 (&
 // contraction-only dQ kernel.
 // PLAIN: Q and dO are in the plain layout (row stride H, head stride nq * H): the staging offsets
 // are then compile-time multiples and one offset serves both tensors (3 % on the recomputing path).
-template <int HR, bool GROUPED, bool WRITE_DS, bool PLAIN = false>
+// BATCH: may be launched over many tiles (g.b.n > 0); the kernels of single tiles are compiled without
+// it (1 % of the 4096 x 4096 backward).
+template <int HR, bool GROUPED, bool WRITE_DS, bool PLAIN = false, bool BATCH = false>
 __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
     const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO, const float* __restrict__ lse,
@@ -284,7 +286,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   const int qsplit = GROUPED ? g.qsplit : 1;
   const int group = GROUPED ? g.group / qsplit : 1;          // query heads this workgroup walks
   int qh0 = 0;                                               // the first of them, as a head of Q
-  const TilePos tp = tile_pos(d, g);
+  const TilePos tp = tile_pos<BATCH>(d, g);
   {
     int unit;
     if (!xcd_map((GROUPED ? d.heads / g.group : d.heads) * qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS, tp.by_size != 0,
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   V += (int64_t)head * d.lv.head + tp.c * g.b.v;
   lse += ((int64_t)tp.r * d.heads + qh0) * d.nq;
   delta += ((int64_t)tp.r * d.heads + qh0) * d.nq;
-  {
+  if (BATCH) {
     const int64_t slot = (int64_t)row_slot(g.b, tp.r, tp.c) * (GROUPED ? d.heads / g.group : d.heads) * d.nkv * H;
     dK += slot;
     dV += slot;
@@ -480,7 +482,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   gwptr_t ds_base = nullptr;
   if constexpr (WRITE_DS)
     ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) +
-                            ((int64_t)blockIdx.y * d.heads + qh0) * ds_head_bytes(d.nq, d.nkv));
+                            ((BATCH ? (int64_t)blockIdx.y * d.heads : 0) + qh0) * ds_head_bytes(d.nq, d.nkv));
 
   // A step is skipped (by both wavefronts of its pair) when none of its rows sees any of the
   // pair's keys; it is masked unless every row sees every key.
@@ -937,7 +939,7 @@ __device__ __forceinline__ void dsq_piece(DsqCtx<HD>& cx, const u32x4 (&ds)[4], 
 // the key blocks in two lanes (alternate blocks, own K buffers) whose dQ sums are added through LDS
 // at the end - for tiles with at most one 128-row block per compute unit, so that a SIMD still
 // holds two wavefronts and twice the dS requests are in flight.
-template <int WAVES, int HR, int KL>
+template <int WAVES, int HR, int KL, bool BATCH>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ K, const bf16_t* __restrict__ dS,
     float* __restrict__ dQ) {
@@ -952,7 +954,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   // placement as in bwd_dq_kernel (grouped heads: the query heads of a key/value head share an XCD)
   int unit, blk;
   const int per_unit = g.group / g.split;
-  const TilePos tp = tile_pos(d, g);
+  const TilePos tp = tile_pos<BATCH>(d, g);
   if (!xcd_map(d.heads / per_unit, per_unit * nqb, tp.by_size != 0, unit, blk)) return;
   // (blocks numbered by size first when the workgroups are ordered by size)
   const int head = unit * per_unit + (tp.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
@@ -962,7 +964,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31;
   K += (int64_t)kvh * d.lk.head + tp.c * g.b.k;
-  dQ += (int64_t)col_slot(g.b, tp.r, tp.c) * d.heads * d.nq * H;
+  if (BATCH) dQ += (int64_t)col_slot(g.b, tp.r, tp.c) * d.heads * d.nq * H;
 
   DsqCtx<HD> cx;
   cx.half = lane >> 5;
@@ -978,7 +980,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   const int n_rt = ds_row_tiles(d.nq), n_kb = ds_key_blocks(d.nkv);
   const int rt = min((q0 + wave * 32) / 32, n_rt - 1);
   const gptr_t ds_base = uniform_gptr(reinterpret_cast<const char*>(dS) +
-                                      ((int64_t)blockIdx.y * d.heads + head) * ds_head_bytes(d.nq, d.nkv) +
+                                      ((BATCH ? (int64_t)blockIdx.y * d.heads : 0) + head) * ds_head_bytes(d.nq, d.nkv) +
                                       (int64_t)rt * n_kb * DS_TILE_BYTES);
 
   // visibility per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
@@ -1153,7 +1155,7 @@ size_t bwd_ds_bytes(const a2d_tile_desc& d, const SegList& g) {
 }
 
 namespace {
-template <int HR>
+template <int HR, bool BATCH>
 hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                          const void* V, const void* dO, const float* lse, const float* delta, float* dQ, float* dK,
                          float* dV, void* ds_ws, hipStream_t s) {
@@ -1168,35 +1170,35 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   // the dQ kernel walks the keys in two lanes when at most one 128-row block comes to a compute unit
   const bool lanes = !big && heads * ((d.nq + 127) / 128) <= cus;
   if (ph == PREPARE) {
-    e = ensure_dynamic_lds(grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, true>)
-                                   : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, true>), DK_LDS);
+    e = ensure_dynamic_lds(grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, true, false, BATCH>)
+                                   : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, true, false, BATCH>), DK_LDS);
     if (e != hipSuccess) return e;
-    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 2>), 2 * DSQ_LDS)
-                 : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 1>)
-                                          : reinterpret_cast<const void*>(bwd_dq_ds_kernel<4, HR, 1>), DSQ_LDS);
+    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 2, BATCH>), 2 * DSQ_LDS)
+                 : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 1, BATCH>)
+                                          : reinterpret_cast<const void*>(bwd_dq_ds_kernel<4, HR, 1, BATCH>), DSQ_LDS);
   }
   dim3 grid_kv(xcd_grid(d.heads / g.group * g.qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS), tiles);
   const int dq_rows = big ? 256 : 128;
   const int per_unit = g.group / g.split;
   dim3 grid_q(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + dq_rows - 1) / dq_rows)), tiles);
   if (grouped)
-    A2D_LAUNCH((bwd_dkdv_kernel<HR, true, true>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g,
+    A2D_LAUNCH((bwd_dkdv_kernel<HR, true, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV,
                        (bf16_t*)ds_ws);
   else
-    A2D_LAUNCH((bwd_dkdv_kernel<HR, false, true>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g,
+    A2D_LAUNCH((bwd_dkdv_kernel<HR, false, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV,
                        (bf16_t*)ds_ws);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (big)
-    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 1>), grid_q, dim3(512), DSQ_LDS, s, d, g, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 1, BATCH>), grid_q, dim3(512), DSQ_LDS, s, d, g, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   else if (lanes)
-    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 2>), grid_q, dim3(512), 2 * DSQ_LDS, s, d, g, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 2, BATCH>), grid_q, dim3(512), 2 * DSQ_LDS, s, d, g, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   else
-    A2D_LAUNCH((bwd_dq_ds_kernel<4, HR, 1>), grid_q, dim3(256), DSQ_LDS, s, d, g, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<4, HR, 1, BATCH>), grid_q, dim3(256), DSQ_LDS, s, d, g, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   return hipGetLastError();
 }
@@ -1205,7 +1207,8 @@ template <int HR>
 hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                          const void* V, const void* dO, const float* lse, const float* delta, float* dQ, float* dK,
                          float* dV, void* ds_ws, hipStream_t s) {
-  if (ds_ws) return bwd_launch_ds<HR>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, s);
+  if (ds_ws && g.b.n) return bwd_launch_ds<HR, true>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, s);
+  if (ds_ws) return bwd_launch_ds<HR, false>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, s);
   constexpr int DQ_LDS = dq_lds(padded_head(HR));
   const bool grouped = g.group > 1;
   // Q and dO in the plain layout: the variant with compile-time staging offsets

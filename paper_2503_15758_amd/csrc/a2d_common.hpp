@@ -86,9 +86,10 @@ struct TilePos {
   int r, c, by_size;
   int64_t rel;
 };
+template <bool BATCH>
 __device__ __forceinline__ TilePos tile_pos(const a2d_tile_desc& d, const SegList& g) {
   TilePos p{0, 0, g.by_size, 0};
-  if (g.b.n == 0) return p;
+  if (!BATCH || g.b.n == 0) return p;
   int t = g.b.first + blockIdx.y;
   if (g.b.tri) {                                 // whole tiles first, then those on the diagonal
     const int whole = g.b.side * (g.b.side - 1) / 2;

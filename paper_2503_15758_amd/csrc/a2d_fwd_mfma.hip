@@ -173,7 +173,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // the query blocks of the query heads that share a key/value head go to one XCD (to g.split
   // XCDs, an equal share of the heads each, when that is what spreads the load evenly)
   int unit, blk;
-  const TilePos tp = tile_pos(d, g);
+  const TilePos tp = tile_pos<true>(d, g);
   const int per_unit = g.group / g.split;
   if (!xcd_map(d.heads / per_unit, per_unit * nqb, tp.by_size != 0, unit, blk)) return;
   // (blocks numbered by size first when the workgroups are ordered by size)
