@@ -110,7 +110,6 @@ a2d::SegList one_segment(const a2d_tile_desc* d) {
   memset(&g, 0, sizeof(g));
   g.n = 1;
   g.group = 1;
-  g.split = 1;
   g.qsplit = 1;
   g.start[0] = 0;
   g.rows[0] = d->nkv;
@@ -126,7 +125,6 @@ a2d_status make_segments(const a2d_tile_desc* d, int nseg, const a2d_kv_segment*
   memset(g, 0, sizeof(*g));
   g->n = nseg;
   g->group = 1;
-  g->split = 1;
   g->qsplit = 1;
   int64_t total = 0;
   for (int s = 0; s < nseg; ++s) {
@@ -411,7 +409,6 @@ static a2d_status group_of(const a2d_tile_desc* desc, int kv_heads, const char* 
   if ((int64_t)*group * desc->nq > ((int64_t)1 << 22))
     return fail(A2D_ERR_INVALID_ARG, "%s: group * nq = %lld exceeds 2^22 rows", who,
                 (long long)*group * desc->nq);
-  g->split = a2d::group_split(kv_heads, *group);
   return A2D_OK;
 }
 

@@ -697,10 +697,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   char* const lds = lds_all + kl * (2 * DQ_BUF);
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   const int nqb = (d.nq + DQ_ROWS - 1) / DQ_ROWS;
-  // the query blocks of the query heads that share a key/value head go to one XCD (to g.split
-  // XCDs, an equal share of the heads each, when that is what spreads the load evenly)
+  // (the query blocks of the query heads that share a key/value head are placed as one unit)
   int unit, blk;
-  const int per_unit = g.group / g.split;
+  const int per_unit = g.group;
   if (!xcd_map(d.heads / per_unit, per_unit * nqb, g.by_size != 0, unit, blk)) return;
   // (blocks numbered by size first when the workgroups are ordered by size)
   const int head = unit * per_unit + (g.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
@@ -953,7 +952,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   const int nqb = (d.nq + DQ_ROWS - 1) / DQ_ROWS;
   // placement as in bwd_dq_kernel (grouped heads: the query heads of a key/value head share an XCD)
   int unit, blk;
-  const int per_unit = g.group / g.split;
+  const int per_unit = g.group;
   const TilePos tp = tile_pos<BATCH>(d, g);
   if (!xcd_map(d.heads / per_unit, per_unit * nqb, tp.by_size != 0, unit, blk)) return;
   // (blocks numbered by size first when the workgroups are ordered by size)
@@ -1179,7 +1178,7 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   }
   dim3 grid_kv(xcd_grid(d.heads / g.group * g.qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS), tiles);
   const int dq_rows = big ? 256 : 128;
-  const int per_unit = g.group / g.split;
+  const int per_unit = g.group;
   dim3 grid_q(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + dq_rows - 1) / dq_rows)), tiles);
   if (grouped)
     A2D_LAUNCH((bwd_dkdv_kernel<HR, true, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g,
@@ -1233,7 +1232,7 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   }
   dim3 grid_kv(xcd_grid(d.heads / g.group * g.qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS));
   const int dq_rows = big ? 256 : 128;
-  const int per_unit = g.group / g.split;
+  const int per_unit = g.group;
   dim3 grid_q(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + dq_rows - 1) / dq_rows)));
 #define A2D_DKDV(GR, PL)                                                                                          \
   A2D_LAUNCH((bwd_dkdv_kernel<HR, GR, false, PL>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g, (const bf16_t*)Q, \

@@ -42,9 +42,7 @@ template <> struct dtype_of<bf16_t> { static constexpr int value = A2D_BF16; };
 // `norm` != 0: the forward writes the NORMALISED partial O' = N / l in the input dtype (into the
 // buffer passed as O_part) and lse' = m + ln l (into the buffer passed as m) instead of (N, m, l).
 // `group` >= 1: query heads per key/value head (grouped-query attention: query head h reads
-// key/value head h / group; K, V, dK, dV have heads / group heads).  `split` divides `group`:
-// kernels that own query blocks place the query heads of a key/value head on XCDs in `split`
-// separate runs (1 = all of them on one XCD; chosen by group_split()).
+// key/value head h / group; K, V, dK, dV have heads / group heads).
 // `by_size` != 0: the blocks of the tile differ in cost (a causal mask crosses it); the kernels then
 // order their workgroups by block, heaviest first, over a whole XCD (see xcd_map).
 // A launch over many tiles of one emulated side x side grid (one tile per grid.y; n = 0: a plain
@@ -62,7 +60,6 @@ struct SegList {
   int acc;
   int norm;
   int group;
-  int split;
   int by_size;
   TileBatch b;
   int qsplit;     // dK/dV kernel, grouped heads: workgroups per key block, each walking group / qsplit query heads
@@ -70,14 +67,6 @@ struct SegList {
   int rows[A2D_MAX_SEGMENTS];
   int64_t rel[A2D_MAX_SEGMENTS];
 };
-
-// Smallest divisor s of `group` that makes kv_heads * s a multiple of the 8 XCDs (an even load per
-// XCD); `group` itself (one run per query head) when there is none.
-inline int group_split(int kv_heads, int group) {
-  for (int s = 1; s <= group; ++s)
-    if (group % s == 0 && (kv_heads * s) % 8 == 0) return s;
-  return group;
-}
 
 // The tile this workgroup belongs to (all zero for a plain call).
 // Partials of a batch are stored by slot: col_slot() puts the tiles of one grid column next to each

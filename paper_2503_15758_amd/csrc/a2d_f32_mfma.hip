@@ -205,7 +205,7 @@ struct Walk {
 // workgroup -> (head, first row): as in the bf16 kernels the row blocks of the query heads that share a
 // key/value head go to one XCD, late (heavy) blocks first
 __device__ __forceinline__ bool query_block(const a2d_tile_desc& d, const SegList& g, int rows, int& head, int& q0) {
-  const int nqb = (d.nq + rows - 1) / rows, per_unit = g.group / g.split;
+  const int nqb = (d.nq + rows - 1) / rows, per_unit = g.group;
   int unit, blk;
   if (!xcd_map(d.heads / per_unit, per_unit * nqb, g.by_size != 0, unit, blk)) return false;
   head = unit * per_unit + (g.by_size ? blk % per_unit : blk / nqb);
@@ -565,7 +565,7 @@ hipError_t fwd_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const
                   float* O_part, float* m, float* l, hipStream_t s) {
   constexpr int lds = KL > 1 ? KL / 2 * RT * (H / 16 + 1) * 1024 : 0;
   static_assert(lds <= 80 * 1024, "two workgroups per compute unit");
-  const int per_unit = g.group / g.split;
+  const int per_unit = g.group;
   dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BLK * RT - 1) / (BLK * RT)))), block(64 * KL);
   A2D_LAUNCH((fwd_f32_kernel<H, RT, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
              (const float*)V, O_part, m, l);
@@ -576,7 +576,7 @@ template <int H, int KL>
 hipError_t dq_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V, const void* O,
                  const void* dO, const float* lse, float* delta, float* dQ, hipStream_t s) {
   constexpr int lds = KL / 2 * (H / 16) * 1024;
-  const int per_unit = g.group / g.split;
+  const int per_unit = g.group;
   dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BLK - 1) / BLK))), block(64 * KL);
   A2D_LAUNCH((bwd_dq_f32_kernel<H, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
              (const float*)V, (const float*)O, (const float*)dO, lse, delta, dQ);

@@ -170,11 +170,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
   const int nqb = (d.nq + BM - 1) / BM;
-  // the query blocks of the query heads that share a key/value head go to one XCD (to g.split
-  // XCDs, an equal share of the heads each, when that is what spreads the load evenly)
+  // (the query blocks of the query heads that share a key/value head are placed as one unit)
   int unit, blk;
   const TilePos tp = tile_pos<true>(d, g);
-  const int per_unit = g.group / g.split;
+  const int per_unit = g.group;
   if (!xcd_map(d.heads / per_unit, per_unit * nqb, tp.by_size != 0, unit, blk)) return;
   // (blocks numbered by size first when the workgroups are ordered by size)
   const int head = unit * per_unit + (tp.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
@@ -466,7 +465,7 @@ hipError_t fwd_launch(Phase ph, const a2d_tile_desc& d, const SegList& g, const 
   constexpr int bytes = KL * lds_bytes(padded_head(HR)), BM = 32 * WAVES / KL;
   if (ph == PREPARE)
     return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_mfma_kernel<WAVES, HR, KL>), bytes);
-  const int per_unit = g.group / g.split;
+  const int per_unit = g.group;
   dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BM - 1) / BM)), g.b.n ? g.b.n : 1), block(64 * WAVES);
   A2D_LAUNCH((fwd_mfma_kernel<WAVES, HR, KL>), grid, block, bytes, s, d, g, (const bf16_t*)Q,
                      (const bf16_t*)K, (const bf16_t*)V, O_part, m, l);

@@ -43,7 +43,6 @@ void describe(const GridProblem& p, a2d_tile_desc* d, SegList* g) {
   d->ldo = block_layout(p, p.g);
   g->n = 1;
   g->group = p.heads / p.kv_heads;
-  g->split = group_split(p.kv_heads, g->group);
   g->qsplit = 1;
   g->rows[0] = rows_of(p);
   g->b.n = slots_of(p);

@@ -131,26 +131,47 @@ __device__ __forceinline__ int dual_store_off(int r, int c) { return r * DUAL_LD
 //            compute units finish together (diagonal forward tile -7 %); chunks of 2 to 12 heads
 //            all gave the same time, 4 keeps most of a head's rows shared in L2 (the unmasked
 //            tile loses 2-3 % with this order, which is why it is not the default).
-// Grid size: 8 * ceil(heads / 8) * nblocks; workgroups whose head is out of range exit.
+// That holds for the first 8 * (heads / 8) heads.  The blocks of the remaining heads % 8 heads are
+// spread evenly over all XCDs instead (a head on an XCD of its own would leave the other XCDs
+// without work: a tile of 1 head used 32 of the 256 compute units, one of 12 heads ran 8 and then
+// 4) and start first: by head in runs - XCD x takes the x-th eighth of the blocks, head after head, so
+// that few XCDs read the same rows - or, by block, heaviest first across the XCDs.
+// Grid size: 8 * (heads / 8 * nblocks + ceil(heads % 8 * nblocks / 8)); the few workgroups without
+// a block exit.
 constexpr int kXcds = 8;
 constexpr int kSizeChunk = 4;
 __host__ __device__ inline int xcd_grid(int heads, int nblocks) {
-  return kXcds * ((heads + kXcds - 1) / kXcds) * nblocks;
+  return kXcds * (heads / kXcds * nblocks + (heads % kXcds * nblocks + kXcds - 1) / kXcds);
 }
 __device__ __forceinline__ bool xcd_map(int heads, int nblocks, bool by_size, int& head, int& block) {
   const int id = blockIdx.x;
-  const int x = id % kXcds, k = id / kXcds;
+  const int x = id % kXcds;
+  int k = id / kXcds;
+  const int whole = heads / kXcds, rest = heads % kXcds, spread = rest * nblocks;
+  const int per_xcd = (spread + kXcds - 1) / kXcds;
+  if (k < per_xcd) {                               // blocks of the last `rest` heads
+    if (by_size) {
+      const int t = kXcds * k + x;
+      head = kXcds * whole + t % rest;
+      block = t / rest;
+      return t < spread;
+    }
+    const int first = x * spread / kXcds, end = (x + 1) * spread / kXcds;
+    head = kXcds * whole + (first + k) / nblocks;
+    block = (first + k) % nblocks;
+    return first + k < end;
+  }
+  k -= per_xcd;
   if (by_size) {
-    const int hpx = (heads + kXcds - 1) / kXcds;
     const int c = k / (kSizeChunk * nblocks), kk = k - c * (kSizeChunk * nblocks);
-    const int width = min(kSizeChunk, hpx - c * kSizeChunk);   // the last chunk may hold fewer heads
+    const int width = min(kSizeChunk, whole - c * kSizeChunk);   // the last chunk may hold fewer heads
     head = kXcds * (c * kSizeChunk + kk % width) + x;
     block = kk / width;
   } else {
     head = kXcds * (k / nblocks) + x;
     block = k % nblocks;
   }
-  return head < heads;
+  return true;
 }
 
 }  // namespace mfma
