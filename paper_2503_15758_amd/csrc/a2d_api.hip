@@ -110,7 +110,7 @@ a2d::SegList one_segment(const a2d_tile_desc* d) {
   memset(&g, 0, sizeof(g));
   g.n = 1;
   g.group = 1;
-  g.qsplit = 1;
+  g.parts = 1;
   g.start[0] = 0;
   g.rows[0] = d->nkv;
   g.rel[0] = d->q_off - d->kv_off;
@@ -125,7 +125,7 @@ a2d_status make_segments(const a2d_tile_desc* d, int nseg, const a2d_kv_segment*
   memset(g, 0, sizeof(*g));
   g->n = nseg;
   g->group = 1;
-  g->qsplit = 1;
+  g->parts = 1;
   int64_t total = 0;
   for (int s = 0; s < nseg; ++s) {
     if (segs[s].rows < 1 || segs[s].pad != 0)
@@ -160,6 +160,12 @@ int blocks_differ(const a2d_tile_desc* d, const a2d::SegList& g) {
   return last >= 2 * first && last > first;
 }
 
+// parts of `floats` floats each that fit a call's share of the scratch memory
+int cap_of(int64_t floats) {
+  const int64_t n = (int64_t)(a2d::kSplitBytes / sizeof(float)) / floats;
+  return n < 1 ? 1 : n > A2D_MAX_PARTS ? A2D_MAX_PARTS : (int)n;
+}
+
 a2d_status partial_fwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, const void* Q, const void* K,
                             const void* V, float* O_part, float* m, float* l, void* stream,
                             const char* who) {
@@ -175,13 +181,37 @@ a2d_status partial_fwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
   if (!a2d::force_generic()) {
     a2d::SegList go = g;
     go.by_size = blocks_differ(desc, g);
+    // N, m, l: where the tile kernel leaves its result - the outputs, or the partials of a split walk
+    const int64_t rows = (int64_t)dd.heads * dd.nq, H = dd.hdim;
+    float *N = O_part, *tm = m, *tl = l;
+    A2D_TRY(hip_result(a2d::plan_fwd(dd, &go, a2d::scratch_offered()), who));
+    if (go.parts > 1) {
+      N = static_cast<float*>(a2d::scratch_get((size_t)go.parts * rows * (H + 2) * sizeof(float)));
+      if (N) {
+        tm = N + go.parts * rows * H;
+        tl = tm + go.parts * rows;
+        go.norm = 0;
+      } else {
+        N = O_part;
+        A2D_TRY(hip_result(a2d::plan_fwd(dd, &go, false), who));
+      }
+    }
+    const a2d::FwdInput in{O_part, m, l};
     if (dd.dtype == A2D_F32) {
       a2d::trace_mark(s);
-      return hip_result(a2d::launch_fwd_f32(dd, go, Q, K, V, O_part, m, l, s), who);
+      A2D_TRY(hip_result(a2d::launch_fwd_f32(dd, go, Q, K, V, N, tm, tl, in, s), who));
+    } else {
+      A2D_TRY(hip_result(a2d::launch_fwd_mfma(a2d::PREPARE, dd, go, Q, K, V, N, tm, tl, in, s), who));
+      a2d::trace_mark(s);
+      A2D_TRY(hip_result(a2d::launch_fwd_mfma(a2d::LAUNCH, dd, go, Q, K, V, N, tm, tl, in, s), who));
     }
-    A2D_TRY(hip_result(a2d::launch_fwd_mfma(a2d::PREPARE, dd, go, Q, K, V, O_part, m, l, s), who));
-    a2d::trace_mark(s);
-    return hip_result(a2d::launch_fwd_mfma(a2d::LAUNCH, dd, go, Q, K, V, O_part, m, l, s), who);
+    if (go.parts == 1) return A2D_OK;
+    a2d::FixPtrs p;
+    memset(&p, 0, sizeof(p));
+    for (int z = 0; z < go.parts; ++z) { p.o[z] = N + z * rows * H; p.m[z] = tm + z * rows; p.l[z] = tl + z * rows; }
+    if (g.norm)
+      return hip_result(a2d::launch_fix(go.parts, rows, dd.hdim, dd.dtype, p, a2d::plain_out(), O_part, m, s), who);
+    return hip_result(a2d::launch_attnfix(go.parts, rows, dd.hdim, p, O_part, m, l, s), who);
   }
   A2D_TRY(hip_result(a2d::launch_fwd_generic(a2d::PREPARE, dd, g, Q, K, V, O_part, m, l, s), who));
   a2d::trace_mark(s);
@@ -230,21 +260,57 @@ a2d_status partial_bwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
   if (!a2d::force_generic()) {
     a2d::SegList go = g;
     go.by_size = blocks_differ(desc, g);
-    if (dd.dtype == A2D_F32) {
-      a2d::trace_mark(s);
-      return hip_result(a2d::launch_bwd_f32(dd, go, Q, K, V, O, dO, lse, delta, dQ_part, dK_part, dV_part, s), who);
-    }
     // the dS hand-over when the caller asked for it and this tile allows it (`need` covers the
     // plain tile's dS area; a gathered tile of the same nkv has the same size or none)
-    const size_t ds_bytes = keep_ds ? a2d::bwd_ds_bytes(dd, g) : 0;
+    const size_t ds_bytes = keep_ds && dd.dtype == A2D_BF16 ? a2d::bwd_ds_bytes(dd, g) : 0;
     void* ds_ws = (ds_bytes > 0 && workspace_bytes >= delta_bytes + ds_bytes) ? static_cast<char*>(workspace) + delta_bytes
                                                                               : nullptr;
-    A2D_TRY(hip_result(a2d::launch_bwd_mfma(a2d::PREPARE, dd, go, Q, K, V, dO, lse, delta, dQ_part, dK_part,
-                                            dV_part, ds_ws, split_ws, s), who));
-    a2d::trace_mark(s);
-    A2D_TRY(hip_result(a2d::launch_delta(dd, O, dO, delta, s), who));
-    return hip_result(a2d::launch_bwd_mfma(a2d::LAUNCH, dd, go, Q, K, V, dO, lse, delta, dQ_part, dK_part,
-                                           dV_part, ds_ws, split_ws, s), who);
+    // Partial sums of split walks: in offered scratch memory, those of dK, dV otherwise in the
+    // caller's split area
+    const int64_t nq = (int64_t)dd.heads * dd.nq * dd.hdim, nk = (int64_t)(dd.heads / g.group) * dd.nkv * dd.hdim;
+    const bool offered = a2d::scratch_offered();
+    const int cap_kv = offered ? cap_of(2 * nk) : 1, cap_q = offered ? cap_of(nq) : 1;
+    const int cap_ws = split_ws ? (g.group < A2D_MAX_PARTS ? g.group : A2D_MAX_PARTS) : 1;
+    int cus = 0;
+    A2D_TRY(hip_result(a2d::device_cus(&cus), who));
+    const auto plan = [&](int ckv, int cq) {
+      return dd.dtype == A2D_F32 ? a2d::plan_bwd_f32(dd, go, cus, ckv, cq)
+                                 : a2d::plan_bwd_mfma(dd, go, ds_ws != nullptr, cus, ckv, cq);
+    };
+    a2d::BwdParts parts = plan(cap_kv > cap_ws ? cap_kv : cap_ws, cap_q);
+    bool kv_in_ws = parts.kv > 1 && parts.kv <= cap_ws;
+    const auto scratch_floats = [&] { return (parts.kv > 1 && !kv_in_ws ? 2 * parts.kv * nk : 0) + (parts.q > 1 ? parts.q * nq : 0); };
+    float* more = nullptr;
+    if (scratch_floats() > 0 && !(more = static_cast<float*>(a2d::scratch_get(scratch_floats() * sizeof(float))))) {
+      parts = plan(cap_ws, 1);
+      kv_in_ws = parts.kv > 1;
+    }
+    float *dk = dK_part, *dv = dV_part, *dq = dQ_part;
+    if (parts.kv > 1) {
+      dk = kv_in_ws ? split_ws : more;
+      dv = dk + parts.kv * nk;
+      if (!kv_in_ws) more += 2 * parts.kv * nk;
+    }
+    if (parts.q > 1) dq = more;
+    if (dd.dtype == A2D_F32) {
+      a2d::trace_mark(s);
+      A2D_TRY(hip_result(a2d::launch_bwd_f32(dd, go, Q, K, V, O, dO, lse, delta, dq, dk, dv, parts, s), who));
+    } else {
+      A2D_TRY(hip_result(a2d::launch_bwd_mfma(a2d::PREPARE, dd, go, Q, K, V, dO, lse, delta, dq, dk, dv, ds_ws, parts, s),
+                         who));
+      a2d::trace_mark(s);
+      A2D_TRY(hip_result(a2d::launch_delta(dd, O, dO, delta, s), who));
+      A2D_TRY(hip_result(a2d::launch_bwd_mfma(a2d::LAUNCH, dd, go, Q, K, V, dO, lse, delta, dq, dk, dv, ds_ws, parts, s),
+                         who));
+    }
+    a2d::PartSet sets[3];
+    int n = 0;
+    if (parts.kv > 1) {
+      sets[n++] = a2d::PartSet{dk, dK_part, nk, parts.kv, 0};
+      sets[n++] = a2d::PartSet{dv, dV_part, nk, parts.kv, 0};
+    }
+    if (parts.q > 1) sets[n++] = a2d::PartSet{dq, dQ_part, nq, parts.q, g.acc};
+    return n ? hip_result(a2d::launch_sum_parts(n, sets, s), who) : A2D_OK;
   }
   A2D_TRY(hip_result(a2d::launch_bwd_generic(a2d::PREPARE, dd, g, Q, K, V, dO, lse, delta, dQ_part, dK_part,
                                              dV_part, s), who));
@@ -258,9 +324,16 @@ a2d_status partial_bwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
 // sums delta of one backward call, at most A2D_STATIC_MAX_ROWS of them, in a file-scope device
 // array.  Every GPU the library runs on holds its own copy at its own address until the process
 // ends; host code only ever uses the address hipGetSymbolAddress returned for the current device.
-__device__ __align__(256) float scratch[A2D_STATIC_MAX_ROWS];
+// Behind them the partial sums of split walks (at most kSplitBytes for dK, dV and for dQ).
+constexpr size_t kStaticFloats = A2D_STATIC_MAX_ROWS + 2 * a2d::kSplitBytes / sizeof(float);
+__device__ __align__(256) float scratch[kStaticFloats];
 constexpr int kMaxDevices = 64;
 std::atomic<float*> g_scratch_ptr[kMaxDevices];
+
+struct Offer {
+  explicit Offer(const a2d::ScratchSource* s) { a2d::scratch_offer(s); }
+  ~Offer() { a2d::scratch_offer(nullptr); }
+};
 
 a2d_status static_scratch(float** out, const char* who) {
   int dev = 0;
@@ -300,6 +373,9 @@ a2d_status a2d_partial_bwd_static(const a2d_tile_desc* desc, const void* Q, cons
   A2D_TRY(static_scratch(&ptr, who));
   // delta is written in full by the call's first kernel before the others read it: nothing in
   // the array has to start at zero
+  const a2d::ScratchSource rest{[](void* p, size_t bytes) -> void* { return bytes <= 2 * a2d::kSplitBytes ? p : nullptr; },
+                                ptr + A2D_STATIC_MAX_ROWS};
+  const Offer offer(&rest);
   return partial_bwd_impl(desc, one_segment(desc), Q, K, V, O, dO, lse, dQ_part, dK_part, dV_part, ptr,
                           sizeof(float) * (size_t)A2D_STATIC_MAX_ROWS, stream, who);
 }

@@ -70,6 +70,10 @@ __device__ __forceinline__ bf16x8 dual_nat(const DualAddr& a, int extra) {
   return lds_load_b128(((X & 1) ? a.nat_o : a.nat_e) + 64 * (X >> 1) + extra);
 }
 
+// steps of the walks for the split model: 32 query rows against 128 keys; 64 keys against 128
+// query rows in each of two lanes, recomputing and from dS
+constexpr double kKvStepUs = 0.9, kDqStepUs = 1.8, kDsqStepUs = 0.9;
+
 // ------------------------------------------------------------------ dK, dV
 constexpr int DK_THREADS = 512;
 constexpr int DK_KEYS = 128;      // keys per workgroup
@@ -280,25 +284,21 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   int head, blk;
   // `head` is the KEY/VALUE head; its g.group query heads are consecutive rows of Q, dO, lse, delta.
-  // With g.qsplit = Z > 1 (grouped heads only) Z workgroups share a key block: workgroup z walks the
-  // query heads z * group / Z ... of the group and leaves its sums in partial buffer z (dK, dV then
-  // point at Z buffers of [key/value heads][nkv][H], added up by a sum kernel afterwards).
-  const int qsplit = GROUPED ? g.qsplit : 1;
-  const int group = GROUPED ? g.group / qsplit : 1;          // query heads this workgroup walks
-  int qh0 = 0;                                               // the first of them, as a head of Q
+  // With g.parts > 1 that many workgroups share a key block: workgroup `part` walks its share of the
+  // steps over the group's query rows and leaves its sums in partial buffer `part` (dK, dV then point
+  // at parts buffers of [key/value heads][nkv][H], added up by a sum kernel afterwards).
+  const int group = GROUPED ? g.group : 1;
   const TilePos tp = tile_pos<BATCH>(d, g);
+  int unit;
+  if (!xcd_map((GROUPED ? d.heads / g.group : d.heads) * g.parts, (d.nkv + DK_KEYS - 1) / DK_KEYS, tp.by_size != 0,
+               unit, blk)) return;
+  head = unit / g.parts;
+  const int part = unit - head * g.parts;
+  const int qh0 = GROUPED ? head * g.group : head;           // the first query head, as a head of Q
   {
-    int unit;
-    if (!xcd_map((GROUPED ? d.heads / g.group : d.heads) * qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS, tp.by_size != 0,
-                 unit, blk)) return;
-    head = unit / qsplit;
-    const int z = unit - head * qsplit;
-    qh0 = GROUPED ? head * g.group + z * group : head;
-    if (GROUPED && qsplit > 1) {
-      const int64_t part = (int64_t)z * (d.heads / g.group) * d.nkv * HR;
-      dK += part;
-      dV += part;
-    }
+    const int64_t first = (int64_t)part * (GROUPED ? d.heads / g.group : d.heads) * d.nkv * HR;
+    dK += first;
+    dV += first;
   }
   constexpr int HD = padded_head(HR), H = HR, KS = HD / 16, CT = HD / 32;
   constexpr int KSR = (HR + 15) / 16;       // slices of H that hold data
@@ -359,9 +359,23 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   };
   int wg_lo, wg_hi;
   first_row_range(k0, min(k0 + DK_KEYS, d.nkv), wg_lo, wg_hi);
-  const int i_start = (wg_lo / BQ) * BQ;
-  const int nsteps = (d.nq - i_start + BQ - 1) / BQ;   // steps per query head
-  const int total = nsteps * group;                    // the group's query heads one after the other
+  // The walk: nsteps steps of BQ rows per query head, the group's heads one after the other.  A part
+  // takes an equal run of it: `total` steps from step s0 of head h0 of the group on.
+  int i_start = (wg_lo / BQ) * BQ;
+  int nsteps = (d.nq - i_start + BQ - 1) / BQ;
+  int total = nsteps * group, s0 = 0, h0 = 0;
+  if (g.parts > 1) {
+    const int all = total, first = (int)((int64_t)part * all / g.parts);
+    total = (int)((int64_t)(part + 1) * all / g.parts) - first;
+    if (!GROUPED) {
+      i_start += first * BQ;
+      nsteps = total;
+    } else if (nsteps > 0) {
+      h0 = first / nsteps;
+      s0 = first - h0 * nsteps;
+    }
+    if (total == 0) nsteps = 0;
+  }
   const int wk_first = k0 + pair * 32, wk_end = min(wk_first + 32, d.nkv);
   cx.my_first = d.nq;                                         // padding keys see nothing
   if (key < d.nkv) {
@@ -418,12 +432,12 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   // ld_left follow the next step's position - its step inside the query head, the head's first
   // row - without a division)
   // (ld_qh / ld_gh: byte offset of the query head's first row of Q / dO from the group's first head)
-  int ld_s = 0, ld_row0 = 0, ld_left = total - 1;
-  unsigned ld_qh = 0, ld_gh = 0;
+  int ld_s = s0, ld_row0 = h0 * d.nq, ld_left = total - 1;
   const unsigned q_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lq.row * 2);
   const unsigned g_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.row * 2);
   const unsigned q_head_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lq.head * 2);
   const unsigned g_head_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.head * 2);
+  unsigned ld_qh = h0 * q_head_bytes, ld_gh = h0 * g_head_bytes;
   auto load_step = [&](int step, auto set_tag) {
     constexpr int SET = decltype(set_tag)::value;
     const int i0 = i_start + (GROUPED ? ld_s : min(step, nsteps - 1)) * BQ;
@@ -492,9 +506,10 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   auto active = [&](int step, int s) {
     return step >= 0 && step < total && min(i_start + s * BQ + BQ - 1, d.nq - 1) >= w_any;
   };
-  int cs = 0;                                                   // s of the iteration's step j
+  int cs = s0;                                                  // s of the iteration's step j
   auto next_s = [&](int s) { return (GROUPED && s + 1 == nsteps) ? 0 : s + 1; };
-  int c_rt = i_start / BQ;                                      // dS row tile of step j, counted over the group's heads
+  // dS row tile of step j, counted over the group's heads
+  int c_rt = (GROUPED ? h0 * ds_row_tiles(d.nq) + s0 : 0) + i_start / BQ;
   // (a head's steps end at its last row tile; the next head's start i_start / BQ tiles into its own)
   auto next_rt = [&](int rt, int s) { return (GROUPED && s + 1 == nsteps) ? rt + 1 + i_start / BQ : rt + 1; };
   auto advance = [&](int slot_delta) {   // to this wave's next step: tile buffer and mailbox slot
@@ -699,11 +714,12 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   const int nqb = (d.nq + DQ_ROWS - 1) / DQ_ROWS;
   // (the query blocks of the query heads that share a key/value head are placed as one unit)
   int unit, blk;
-  const int per_unit = g.group;
-  if (!xcd_map(d.heads / per_unit, per_unit * nqb, g.by_size != 0, unit, blk)) return;
-  // (blocks numbered by size first when the workgroups are ordered by size)
-  const int head = unit * per_unit + (g.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
-  blk = g.by_size ? blk / per_unit : blk % nqb;
+  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, g.by_size != 0, unit, blk)) return;
+  // (unit = part `part` of the walks over one key/value head; blocks numbered by size first when the
+  // workgroups are ordered by size)
+  const int kvh = unit / g.parts, part = unit - kvh * g.parts;
+  const int head = kvh * g.group + (g.by_size ? blk % g.group : blk / nqb);
+  blk = g.by_size ? blk / g.group : blk % nqb;
   const int q0 = (nqb - 1 - blk) * DQ_ROWS;            // heavy blocks first under a causal mask
   const int tid = (int)threadIdx.x - kl * DQ_THREADS;  // within the key lane
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -801,25 +817,26 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
     }
   };
 
-  // Walk over the entries (sub-block, key block); key lane kl takes entries kl, kl + KL, ...  The
-  // sub-block table lives in kernel-argument memory, and scalar loads share a wait counter with the
-  // LDS reads in flight, so it is only touched when a walk moves to another sub-block; in between
-  // its values sit in registers.  An entry is (sub-block sb, block j of its nblk); sb == g.n: past
-  // the end.
-  auto open_segment = [&](int s, int& sb, int& j, int& nblk) {   // first sub-block after s with visible keys
-    do { ++s; } while (s < g.n && seg_blocks(s) == 0);
-    sb = s; j = 0;
+  // Walk over the entries (sub-block, key block): lane part * KL + kl of parts * KL takes every
+  // (parts * KL)-th entry.  The sub-block table lives in kernel-argument memory, and scalar loads
+  // share a wait counter with the LDS reads in flight, so it is only touched when a walk moves to
+  // another sub-block; in between its values sit in registers.  An entry is (sub-block sb, block j
+  // of its nblk); sb == g.n: past the end.
+  const int stride = KL * g.parts;
+  auto open_segment = [&](int s, int& sb, int& nblk) {           // first sub-block from s on with visible keys
+    while (s < g.n && seg_blocks(s) == 0) ++s;
+    sb = s;
     if (s < g.n) nblk = seg_blocks(s);
   };
-  auto advance = [&](int& sb, int& j, int& nblk) {
-    if (sb < g.n && ++j >= nblk) open_segment(sb, sb, j, nblk);
+  auto advance = [&](int by, int& sb, int& j, int& nblk) {
+    j += by;
+    while (sb < g.n && j >= nblk) { j -= nblk; open_segment(sb + 1, sb, nblk); }
   };
-  int sb, j, nblk = 0;                             // this key lane's current entry
-  open_segment(-1, sb, j, nblk);
-  int lead_sb = sb, lead_j = j, lead_nblk = nblk;  // key lane 0's: every lane loops while it exists
-  if (KL > 1) {
-    for (int x = 0; x < kl; ++x) advance(sb, j, nblk);
-  }
+  int sb, j = 0, nblk = 0;                         // this key lane's current entry
+  open_segment(0, sb, nblk);
+  advance(part * KL, sb, j, nblk);
+  int lead_sb = sb, lead_j = j, lead_nblk = nblk;  // key lane 0's: every lane of the workgroup loops while it exists
+  if (KL > 1) advance(kl, sb, j, nblk);
   int nx_start = 0, nx_rows = 0;                   // start / rows of the next entry's sub-block
   if (sb < g.n) {
     enter_segment(sb);
@@ -832,8 +849,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   int buf = 0;
   while ((KL == 1 ? sb : lead_sb) < g.n) {
     int nsb = sb, nj = j, nnblk = nblk;
-#pragma unroll
-    for (int x = 0; x < KL; ++x) advance(nsb, nj, nnblk);
+    advance(stride, nsb, nj, nnblk);
     const bool more = nsb < g.n;
     if (more && nsb != sb) { nx_start = g.start[nsb]; nx_rows = g.rows[nsb]; }
     const bool here = KL == 1 || sb < g.n;         // this lane has a block in this round
@@ -852,10 +868,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
     cx.vnat += tog;
     __syncthreads();
     if (more && nsb != sb) enter_segment(nsb);
-    if (KL > 1) {
-#pragma unroll
-      for (int x = 0; x < KL; ++x) advance(lead_sb, lead_j, lead_nblk);
-    }
+    if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
     sb = nsb; j = nj; nblk = nnblk;
     buf ^= 1;
   }
@@ -877,7 +890,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) cx.dq[t][r] += xch[(16 * t + r) * 64];
   }
-  if (q_ok) store_acc_t<CT>(dQ + ((int64_t)head * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
+  if (q_ok) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
 }
 
 // ---------------------------------------------------------------------- dQ from a stored dS
@@ -952,12 +965,11 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   const int nqb = (d.nq + DQ_ROWS - 1) / DQ_ROWS;
   // placement as in bwd_dq_kernel (grouped heads: the query heads of a key/value head share an XCD)
   int unit, blk;
-  const int per_unit = g.group;
   const TilePos tp = tile_pos<BATCH>(d, g);
-  if (!xcd_map(d.heads / per_unit, per_unit * nqb, tp.by_size != 0, unit, blk)) return;
-  // (blocks numbered by size first when the workgroups are ordered by size)
-  const int head = unit * per_unit + (tp.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
-  blk = tp.by_size ? blk / per_unit : blk % nqb;
+  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, tp.by_size != 0, unit, blk)) return;
+  const int kvh = unit / g.parts, part = unit - kvh * g.parts;
+  const int head = kvh * g.group + (tp.by_size ? blk % g.group : blk / nqb);
+  blk = tp.by_size ? blk / g.group : blk % nqb;
   const int q0 = (nqb - 1 - blk) * DQ_ROWS;            // heavy blocks first under a causal mask
   const int tid = (int)threadIdx.x - kl * DQ_THREADS;  // within the key lane
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -996,38 +1008,39 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   for (int s = 0; s < g.n; ++s) count += seg_blocks(s);
 
   // Walk over the visible blocks, as global block numbers (start of the sub-block / 64 + block
-  // inside it).  The fetch walker runs ahead of the compute walker; once it has run out it keeps
-  // returning its last block (loads stay unconditional).
-  // (a key lane takes every KL-th block: each walker moves KL blocks per call, after kl at the start)
-  int f_sb = -1, f_j = 0, f_nblk = 0, f_base = 0, f_id = 0;
-  auto fetch_one = [&]() {
-    if (f_j + 1 < f_nblk) { ++f_j; f_id = f_base + f_j; return; }
-    int s = f_sb + 1;
-    while (s < g.n && seg_blocks(s) == 0) ++s;
-    if (s < g.n) { f_sb = s; f_j = 0; f_nblk = seg_blocks(s); f_base = g.start[s] / BKS; f_id = f_base; }
-  };
-  auto fetch_next = [&]() {
-#pragma unroll
-    for (int x = 0; x < KL; ++x) fetch_one();
+  // inside it): lane part * KL + kl of parts * KL takes every (parts * KL)-th.  The fetch walker runs
+  // ahead of the compute walker; once it has run out it keeps returning its last block (loads stay
+  // unconditional).
+  const int stride = KL * g.parts;
+  int f_sb = -1, f_j = 0, f_nblk = 0, f_id = 0;
+  auto fetch_by = [&](int by) {
+    int sb = f_sb, j = f_j + by, nblk = f_nblk;
+    while (j >= nblk) {
+      j -= nblk;
+      nblk = 0;
+      do { ++sb; } while (sb < g.n && (nblk = seg_blocks(sb)) == 0);
+      if (sb >= g.n) return;
+    }
+    f_id = g.start[sb] / BKS + j;
+    f_sb = sb; f_j = j; f_nblk = nblk;
   };
   int c_sb = -1, c_j = 0, c_nblk = 0;              // compute walker: sub-block, block inside it
   int nvis_wave = 0, nfull_wave = 0;
-  auto compute_one = [&]() {
-    if (c_j + 1 < c_nblk) { ++c_j; return; }
-    int s = c_sb + 1;
-    while (s < g.n && seg_blocks(s) == 0) ++s;
-    if (s < g.n) {
-      c_sb = s; c_j = 0; c_nblk = seg_blocks(s);
-      nvis_wave = vis_count(w_last, s);
-      nfull_wave = vis_count(w_first, s);
-      cx.my_vis = vis_count(q_ld, s);
-    } else {
-      nvis_wave = 0;                               // past the last block: nothing to compute
+  auto compute_by = [&](int by) {
+    c_j += by;
+    while (c_j >= c_nblk) {
+      c_j -= c_nblk;
+      c_nblk = 0;
+      do { ++c_sb; } while (c_sb < g.n && (c_nblk = seg_blocks(c_sb)) == 0);
+      if (c_sb >= g.n) {                           // past the last block: nothing to compute
+        c_sb = g.n - 1; c_j = 0; c_nblk = 0;
+        nvis_wave = 0;
+        return;
+      }
+      nvis_wave = vis_count(w_last, c_sb);
+      nfull_wave = vis_count(w_first, c_sb);
+      cx.my_vis = vis_count(q_ld, c_sb);
     }
-  };
-  auto compute_next = [&]() {
-#pragma unroll
-    for (int x = 0; x < KL; ++x) compute_one();
   };
 
   // ---- K staging: thread moves chunk (tid & 15) of rows (tid >> 4) + ST_ROWS p of the 64-row tile
@@ -1066,26 +1079,25 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     }
   };
 
+  count = count > part * KL ? count - part * KL : 0;           // from this part's first block on
   if (count == 0) {                                // no visible key: dQ share is zero
-    if (q_ok && !g.acc && kl == 0) store_acc_t<CT>(dQ + ((int64_t)head * d.nq + q_row) * H, cx.dq, cx.half, 0.f, H, false);
+    if (q_ok && !g.acc && kl == 0) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, 0.f, H, false);
     return;
   }
-  if (KL > 1) {
-    for (int x = 0; x < kl; ++x) { fetch_one(); compute_one(); }
-    fetch_one();                                   // this lane's first block (the last one, if it has none)
-  } else {
-    fetch_next();                                  // block 0
-  }
+  // (the first block is block 0; a lane without one re-reads the last block it passed)
+  fetch_by(0);
+  fetch_by(part * KL);
+  if (KL > 1) fetch_by(kl);
   load_k(f_id);
   load_ds(f_id, std::integral_constant<int, 0>{});
   store_k(0);
   int idq[DSQ_SETS - 2];                           // blocks t + 1 .. t + DSQ_SETS - 2 of iteration t
   static_for<1, DSQ_SETS - 1>([&](auto S) {        // blocks 1 .. DSQ_SETS - 2
-    fetch_next();
+    fetch_by(stride);
     idq[decltype(S)::value - 1] = f_id;
     load_ds(f_id, S);
   });
-  if (KL > 1) compute_one(); else compute_next();
+  compute_by(part * KL + kl);
   __syncthreads();
 
   int buf = 0;
@@ -1095,7 +1107,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   auto iteration = [&](auto cur_tag) {
     constexpr int CUR = decltype(cur_tag)::value;
     load_k(idq[0]);
-    fetch_next();
+    fetch_by(stride);
     load_ds(f_id, std::integral_constant<int, (CUR + DSQ_SETS - 1) % DSQ_SETS>{});
     const int k0 = c_j * BKS;                      // local to the sub-block
     if (k0 < nvis_wave) {
@@ -1110,10 +1122,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     idq[DSQ_SETS - 3] = f_id;
     cx.ka.shift(buf ? -DUAL64_BYTES : DUAL64_BYTES);
     buf ^= 1;
-    compute_next();
+    compute_by(stride);
     __syncthreads();
   };
-  for (int t = 0; t < (count + KL - 1) / KL; t += DSQ_SETS)   // blocks past the last find nvis_wave = 0
+  for (int t = 0; t < (count + stride - 1) / stride; t += DSQ_SETS)   // blocks past the last find nvis_wave = 0
     static_for<0, DSQ_SETS>([&](auto S) { iteration(S); });
   if constexpr (KL == 2) {
     // lane 1 hands its sums to lane 0 through LDS (the K tiles are no longer read: every wavefront
@@ -1133,7 +1145,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) cx.dq[t][r] += xch[(16 * t + r) * 64];
   }
-  if (q_ok) store_acc_t<CT>(dQ + ((int64_t)head * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
+  if (q_ok) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
 }
 
 }  // namespace
@@ -1157,14 +1169,18 @@ namespace {
 template <int HR, bool BATCH>
 hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                          const void* V, const void* dO, const float* lse, const float* delta, float* dQ, float* dK,
-                         float* dV, void* ds_ws, hipStream_t s) {
+                         float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
   constexpr int DSQ_LDS = 2 * DUAL64_BYTES;
   const bool grouped = g.group > 1;
   int cus = 0;
   hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
   const int tiles = g.b.n ? g.b.n : 1;
-  const int64_t heads = (int64_t)d.heads * tiles;
+  SegList gk = g, gq = g;
+  gk.parts = parts.kv;
+  gq.parts = parts.q;
+  if (parts.q > 1) gq.acc = 0;                         // (the sum over the parts adds)
+  const int64_t heads = (int64_t)d.heads * tiles * parts.q;
   const bool big = heads * ((d.nq + 255) / 256) >= cus;
   // the dQ kernel walks the keys in two lanes when at most one 128-row block comes to a compute unit
   const bool lanes = !big && heads * ((d.nq + 127) / 128) <= cus;
@@ -1176,28 +1192,27 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
                  : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 1, BATCH>)
                                           : reinterpret_cast<const void*>(bwd_dq_ds_kernel<4, HR, 1, BATCH>), DSQ_LDS);
   }
-  dim3 grid_kv(xcd_grid(d.heads / g.group * g.qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS), tiles);
+  dim3 grid_kv(xcd_grid(d.heads / g.group * parts.kv, (d.nkv + DK_KEYS - 1) / DK_KEYS), tiles);
   const int dq_rows = big ? 256 : 128;
-  const int per_unit = g.group;
-  dim3 grid_q(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + dq_rows - 1) / dq_rows)), tiles);
+  dim3 grid_q(xcd_grid(d.heads / g.group * parts.q, g.group * ((d.nq + dq_rows - 1) / dq_rows)), tiles);
   if (grouped)
-    A2D_LAUNCH((bwd_dkdv_kernel<HR, true, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g,
+    A2D_LAUNCH((bwd_dkdv_kernel<HR, true, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV,
                        (bf16_t*)ds_ws);
   else
-    A2D_LAUNCH((bwd_dkdv_kernel<HR, false, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g,
+    A2D_LAUNCH((bwd_dkdv_kernel<HR, false, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV,
                        (bf16_t*)ds_ws);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (big)
-    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 1, BATCH>), grid_q, dim3(512), DSQ_LDS, s, d, g, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 1, BATCH>), grid_q, dim3(512), DSQ_LDS, s, d, gq, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   else if (lanes)
-    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 2, BATCH>), grid_q, dim3(512), 2 * DSQ_LDS, s, d, g, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 2, BATCH>), grid_q, dim3(512), 2 * DSQ_LDS, s, d, gq, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   else
-    A2D_LAUNCH((bwd_dq_ds_kernel<4, HR, 1, BATCH>), grid_q, dim3(256), DSQ_LDS, s, d, g, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<4, HR, 1, BATCH>), grid_q, dim3(256), DSQ_LDS, s, d, gq, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   return hipGetLastError();
 }
@@ -1205,9 +1220,9 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 template <int HR>
 hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                          const void* V, const void* dO, const float* lse, const float* delta, float* dQ, float* dK,
-                         float* dV, void* ds_ws, hipStream_t s) {
-  if (ds_ws && g.b.n) return bwd_launch_ds<HR, true>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, s);
-  if (ds_ws) return bwd_launch_ds<HR, false>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, s);
+                         float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
+  if (ds_ws && g.b.n) return bwd_launch_ds<HR, true>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+  if (ds_ws) return bwd_launch_ds<HR, false>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
   constexpr int DQ_LDS = dq_lds(padded_head(HR));
   const bool grouped = g.group > 1;
   // Q and dO in the plain layout: the variant with compile-time staging offsets
@@ -1216,9 +1231,14 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   int cus = 0;
   hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
-  const bool big = (int64_t)d.heads * ((d.nq + 255) / 256) >= cus;
+  SegList gk = g, gq = g;
+  gk.parts = parts.kv;
+  gq.parts = parts.q;
+  if (parts.q > 1) gq.acc = 0;                         // (the sum over the parts adds)
+  const int64_t heads = (int64_t)d.heads * parts.q;
+  const bool big = heads * ((d.nq + 255) / 256) >= cus;
   // two key lanes when at most one 128-row block comes to a compute unit
-  const bool lanes = !big && (int64_t)d.heads * ((d.nq + 127) / 128) <= cus;
+  const bool lanes = !big && heads * ((d.nq + 127) / 128) <= cus;
   if (ph == PREPARE) {
     const void* dkdv = plain ? (grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, false, true>)
                                         : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, false, true>))
@@ -1230,12 +1250,11 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
                  : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 1>)
                                           : reinterpret_cast<const void*>(bwd_dq_kernel<4, HR, 1>), DQ_LDS);
   }
-  dim3 grid_kv(xcd_grid(d.heads / g.group * g.qsplit, (d.nkv + DK_KEYS - 1) / DK_KEYS));
+  dim3 grid_kv(xcd_grid(d.heads / g.group * parts.kv, (d.nkv + DK_KEYS - 1) / DK_KEYS));
   const int dq_rows = big ? 256 : 128;
-  const int per_unit = g.group;
-  dim3 grid_q(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + dq_rows - 1) / dq_rows)));
+  dim3 grid_q(xcd_grid(d.heads / g.group * parts.q, g.group * ((d.nq + dq_rows - 1) / dq_rows)));
 #define A2D_DKDV(GR, PL)                                                                                          \
-  A2D_LAUNCH((bwd_dkdv_kernel<HR, GR, false, PL>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, g, (const bf16_t*)Q, \
+  A2D_LAUNCH((bwd_dkdv_kernel<HR, GR, false, PL>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk, (const bf16_t*)Q, \
                      (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV, (bf16_t*)nullptr)
   if (grouped && plain) A2D_DKDV(true, true);
   else if (grouped) A2D_DKDV(true, false);
@@ -1245,70 +1264,43 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (big)
-    A2D_LAUNCH((bwd_dq_kernel<8, HR, 1>), grid_q, dim3(512), DQ_LDS, s, d, g, (const bf16_t*)Q,
+    A2D_LAUNCH((bwd_dq_kernel<8, HR, 1>), grid_q, dim3(512), DQ_LDS, s, d, gq, (const bf16_t*)Q,
                        (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dQ);
   else if (lanes)
-    A2D_LAUNCH((bwd_dq_kernel<8, HR, 2>), grid_q, dim3(512), 2 * DQ_LDS, s, d, g, (const bf16_t*)Q,
+    A2D_LAUNCH((bwd_dq_kernel<8, HR, 2>), grid_q, dim3(512), 2 * DQ_LDS, s, d, gq, (const bf16_t*)Q,
                        (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dQ);
   else
-    A2D_LAUNCH((bwd_dq_kernel<4, HR, 1>), grid_q, dim3(256), DQ_LDS, s, d, g, (const bf16_t*)Q,
+    A2D_LAUNCH((bwd_dq_kernel<4, HR, 1>), grid_q, dim3(256), DQ_LDS, s, d, gq, (const bf16_t*)Q,
                        (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dQ);
   return hipGetLastError();
 }
 }  // namespace
 
-// How many workgroups should share a key block of a grouped-head dK/dV launch (each walking
-// group / Z of the query heads): the divisor Z of `group` (at most A2D_MAX_PARTS) that minimises
-// rounds of workgroups over the compute units x query heads per workgroup; the smallest on a tie.
-int choose_qsplit(int kv_heads, int group, int key_blocks, int cus) {
-  int best = 1;
-  int64_t best_cost = -1;
-  for (int z = 1; z <= group && z <= A2D_MAX_PARTS; ++z) {
-    if (group % z != 0) continue;
-    const int64_t wgs = (int64_t)kv_heads * z * key_blocks;
-    const int64_t cost = ((wgs + cus - 1) / cus) * (group / z);
-    if (best_cost < 0 || cost < best_cost) { best = z; best_cost = cost; }
-  }
-  return best;
+// Parts of the dK/dV and dQ walks where their row blocks leave compute units idle (see WalkModel).
+// The choice for dK/dV does not depend on `ds`, nor either choice on the grouping alone, so that
+// the two dQ paths give the same dK, dV.
+BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q) {
+  const int kv_heads = d.heads / g.group;
+  BwdParts p;
+  const double rows = (double)g.group * ((d.nq + BQ - 1) / BQ);
+  const WalkModel kv = {(int64_t)kv_heads * ((d.nkv + DK_KEYS - 1) / DK_KEYS), cus, rows, rows, kKvStepUs, 8.0};
+  p.kv = best_parts(kv, cap_kv, (double)kv_heads * d.nkv * d.hdim * 16 / 5e6, nullptr);
+  const double keys = (double)visible_keys(d, g, d.nq - 1) / BKS + 1;
+  const int64_t b128 = (int64_t)d.heads * ((d.nq + 127) / 128);
+  const WalkModel q = {b128, cus, keys / 2, keys / 2, ds ? kDsqStepUs : kDqStepUs, 6.0};
+  p.q = best_parts(q, cap_q, (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
+  return p;
 }
 
 // ds_ws != NULL: a workspace of bwd_ds_bytes(d, g) bytes; the dK/dV kernel leaves dS there and the
 // dQ kernel is the contraction-only one.
-// split_ws != NULL (grouped heads): room for 2 * min(group, A2D_MAX_PARTS) partial buffers of
-// [key/value heads][nkv][H] floats; the query heads of a group may then be split over several
-// workgroups per key block (choose_qsplit) whose dK / dV sums a sum kernel adds up.
 hipError_t launch_bwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                            const void* V, const void* dO, const float* lse, const float* delta, float* dQ,
-                           float* dK, float* dV, void* ds_ws, float* split_ws, hipStream_t s) {
-  SegList gg = g;
-  gg.qsplit = 1;
-  float* dKo = dK;
-  float* dVo = dV;
-  const int kv_heads = d.heads / g.group;
-  const int64_t n = (int64_t)kv_heads * d.nkv * d.hdim;        // elements of dK (of dV)
-  if (split_ws && g.group > 1) {
-    int cus = 0;
-    const hipError_t e = device_cus(&cus);
-    if (e != hipSuccess) return e;
-    gg.qsplit = choose_qsplit(kv_heads, g.group, (d.nkv + DK_KEYS - 1) / DK_KEYS, cus);
-    if (gg.qsplit > 1) {
-      dKo = split_ws;
-      dVo = split_ws + (int64_t)gg.qsplit * n;
-    }
-  }
-  hipError_t e;
-  if (d.hdim == 128) e = bwd_launch_hd<128>(ph, d, gg, Q, K, V, dO, lse, delta, dQ, dKo, dVo, ds_ws, s);
-  else if (d.hdim == 96) e = bwd_launch_hd<96>(ph, d, gg, Q, K, V, dO, lse, delta, dQ, dKo, dVo, ds_ws, s);
-  else if (d.hdim == 80) e = bwd_launch_hd<80>(ph, d, gg, Q, K, V, dO, lse, delta, dQ, dKo, dVo, ds_ws, s);
-  else e = bwd_launch_hd<64>(ph, d, gg, Q, K, V, dO, lse, delta, dQ, dKo, dVo, ds_ws, s);
-  if (e != hipSuccess || gg.qsplit == 1 || ph == PREPARE) return e;   // (the sum kernel needs no preparation)
-  // dK = sum_z partial z (in order of z: bitwise reproducible), the same for dV
-  SumPtrs pk, pv;
-  for (int z = 0; z < A2D_MAX_PARTS; ++z) { pk.p[z] = nullptr; pv.p[z] = nullptr; }
-  for (int z = 0; z < gg.qsplit; ++z) { pk.p[z] = dKo + (int64_t)z * n; pv.p[z] = dVo + (int64_t)z * n; }
-  e = launch_fix_bwd(gg.qsplit, n, d.hdim / 4, A2D_F32, pk, plain_out(), dK, s);
-  if (e != hipSuccess) return e;
-  return launch_fix_bwd(gg.qsplit, n, d.hdim / 4, A2D_F32, pv, plain_out(), dV, s);
+                           float* dK, float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
+  if (d.hdim == 128) return bwd_launch_hd<128>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+  if (d.hdim == 96) return bwd_launch_hd<96>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+  if (d.hdim == 80) return bwd_launch_hd<80>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+  return bwd_launch_hd<64>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
 }
 
 }  // namespace a2d

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "a2d.h"
+#include "a2d_grid.hpp"
 
 namespace a2d {
 
@@ -62,7 +63,8 @@ struct SegList {
   int group;
   int by_size;
   TileBatch b;
-  int qsplit;     // dK/dV kernel, grouped heads: workgroups per key block, each walking group / qsplit query heads
+  int parts;      // workgroups that share the walk of one block, each leaving a partial result (>= 1)
+  int form;       // which of its workgroup shapes a forward / dQ launch takes (plan_* below)
   int start[A2D_MAX_SEGMENTS];
   int rows[A2D_MAX_SEGMENTS];
   int64_t rel[A2D_MAX_SEGMENTS];
@@ -141,6 +143,38 @@ void trace_mark(hipStream_t s);
     ::a2d::trace_mark(stream);                                          \
   } while (0)
 
+// Scratch memory for the partial results of split walks, offered by the caller's thread for the
+// duration of a call (it must stay valid for the stream's work); without an offer, or with NULL from
+// it, a call runs unsplit (scratch_offer() in a2d_grid.hpp).  At most kSplitBytes for each of the results a call splits.
+bool scratch_offered();
+void* scratch_get(size_t bytes);
+constexpr size_t kSplitBytes = (size_t)32 << 20;
+
+// ---- splitting a walk ----
+// A tile kernel's workgroup owns a block of rows and walks the other side of the tile.  When the row
+// blocks are too few for the chip, `parts` workgroups share each block's walk and leave partial
+// results that a merge or sum kernel adds up in order.  The time of such a launch is modelled as turns
+// of workgroups over the slots of the chip (constants measured on MI355X, microseconds), and the
+// number of parts - and the workgroup shape, where a kernel has several - is the one with the least.
+struct WalkModel {
+  int64_t blocks;          // row blocks
+  int slots;               // workgroups the chip holds at a time
+  double mean, most;       // steps of a block's walk: on average, the longest
+  double step, fixed;      // time of a step, of everything else in a workgroup
+};
+inline double walk_time(const WalkModel& w, int parts) {
+  const auto len = [&](double steps) { const double n = steps / parts; return (n < 1.0 ? 1.0 : n) * w.step + w.fixed; };
+  const int64_t wgs = w.blocks * parts;
+  if (wgs <= w.slots) return len(w.most);
+  if (w.mean >= w.most) return (double)((wgs + w.slots - 1) / w.slots) * len(w.most);
+  const double even = ((double)wgs / w.slots + 0.5) * len(w.mean);        // longest first: half a workgroup of tail
+  return even > len(w.most) ? even : len(w.most);
+}
+// the best number of parts up to `cap` (ties: the smaller), each part costing part_us to write and merge
+int best_parts(const WalkModel& w, int cap, double part_us, double* time);
+// keys that query row i of the tile sees
+int64_t visible_keys(const a2d_tile_desc& d, const SegList& g, int64_t i);
+
 // ---- launchers (none synchronises) ----
 // Every tile launcher runs in two phases so that a call can finish everything that may fail on the
 // host side before its first kernel is enqueued: PREPARE only raises the dynamic-LDS limits of the
@@ -148,13 +182,29 @@ void trace_mark(hipStream_t s);
 // launches and returns the launch's hipError_t.
 enum Phase { PREPARE = 0, LAUNCH = 1 };
 
+// the partial an accumulating forward call starts from
+struct FwdInput {
+  const float *N, *m, *l;
+};
+// Workgroup shape and parts of a forward tile (sets g->form, g->parts); may_split: partial results
+// of parts > 1 workgroups per block ([parts][heads][nq] each of N, m, l) can be stored and merged.
+hipError_t plan_fwd(const a2d_tile_desc& d, SegList* g, bool may_split);
+void plan_fwd_f32(const a2d_tile_desc& d, SegList* g, int cus, int cap);
+void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap);
+// Parts of the two kernels of a backward tile, each at most its cap
+struct BwdParts {
+  int kv, q;
+};
+BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q);
+BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q);
+
 // fp32 tile kernels on the fp32 matrix units (H in {64, 80, 96, 128}); nothing to prepare.  The
 // backward also computes delta (into `delta`).
 hipError_t launch_fwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
-                          float* O_part, float* m, float* l, hipStream_t s);
+                          float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s);
 hipError_t launch_bwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                           const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK,
-                          float* dV, hipStream_t s);
+                          float* dV, const BwdParts& parts, hipStream_t s);
 
 // Generic tile kernels: fp32 arithmetic on the vector ALUs for fp32 or bf16
 // inputs, any nq / nkv, H in {64, 80, 96, 128}.  Reached with force_generic() only.
@@ -170,16 +220,15 @@ hipError_t launch_delta(const a2d_tile_desc& d, const void* O, const void* dO, f
 // bf16 MFMA tile kernels (H in {64, 80, 96, 128}).  `supported` tells whether the shape is covered.
 bool fwd_mfma_supported(const a2d_tile_desc& d);
 hipError_t launch_fwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
-                           const void* V, float* O_part, float* m, float* l, hipStream_t s);
+                           const void* V, float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s);
 bool bwd_mfma_supported(const a2d_tile_desc& d);
 // ds_ws: NULL, or a workspace of bwd_ds_bytes(d, g) (> 0) bytes through which the dK/dV kernel
 // hands dS to a contraction-only dQ kernel (instead of the dQ kernel recomputing S and dP)
 size_t bwd_ds_bytes(const a2d_tile_desc& d, const SegList& g);
+// (parts > 1: the outputs are the partial buffers, [parts][heads][rows][H] each)
 hipError_t launch_bwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                            const void* V, const void* dO, const float* lse, const float* delta, float* dQ,
-                           float* dK, float* dV, void* ds_ws, float* split_ws, hipStream_t s);
-// the dK/dV kernel's choice of workgroups per key block for grouped heads (see launch_bwd_mfma)
-int choose_qsplit(int kv_heads, int group, int key_blocks, int cus);
+                           float* dK, float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s);
 
 struct FixPtrs {
   const float* o[A2D_MAX_PARTS];
@@ -218,6 +267,15 @@ hipError_t launch_sum_grid(int nsets, const SumSet* sets, int hdim, int out_dtyp
 // delta and lse of a whole [heads][side * rows] sequence, block by block: [side][heads][rows]
 hipError_t launch_delta_grid(const GridMap& gm, int hdim, const a2d_layout& lo, const a2d_layout& ldo, const bf16_t* O,
                              const bf16_t* dO, const float* lse, float* delta_blk, float* lse_blk, hipStream_t s);
+
+// out[i] (+)= sum of k partials of n floats that follow one another, up to three sets in one launch
+struct PartSet {
+  const float* p;
+  float* out;
+  int64_t n;
+  int k, add;
+};
+hipError_t launch_sum_parts(int nsets, const PartSet* sets, hipStream_t s);
 
 hipError_t launch_fix(int k, int64_t rows, int hdim, int out_dtype, const FixPtrs& p, const OutMap& om, void* O,
                       float* lse, hipStream_t s);

@@ -13,6 +13,8 @@
 namespace a2d {
 namespace {
 
+constexpr double kMergeUs = 5.0;     // a merge or sum launch behind a tile kernel, small data
+
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_cus[kMaxDevices];                       // 0 = not asked yet
 std::mutex g_mu;
@@ -23,6 +25,8 @@ std::atomic<int> g_force_generic{-1};                      // -1 = environment n
 thread_local hipEvent_t* t_trace_events = nullptr;
 thread_local int t_trace_cap = 0;
 thread_local int t_trace_used = 0;
+
+thread_local const ScratchSource* t_scratch = nullptr;
 
 }  // namespace
 
@@ -82,6 +86,42 @@ int trace_count() { return t_trace_used; }
 void trace_mark(hipStream_t s) {
   if (!t_trace_events || t_trace_used >= t_trace_cap) return;
   if (hipEventRecord(t_trace_events[t_trace_used], s) == hipSuccess) ++t_trace_used;
+}
+
+void scratch_offer(const ScratchSource* src) { t_scratch = src; }
+bool scratch_offered() { return t_scratch != nullptr; }
+void* scratch_get(size_t bytes) { return t_scratch ? t_scratch->get(t_scratch->ctx, bytes) : nullptr; }
+
+int best_parts(const WalkModel& w, int cap, double part_us, double* time) {
+  int best = 1;
+  double least = walk_time(w, 1);
+  for (int z = 2; z <= cap && z <= A2D_MAX_PARTS && z <= w.most; ++z) {
+    const double t = walk_time(w, z) + kMergeUs + z * part_us;
+    if (t < 0.95 * least) { best = z; least = t; }             // (a split has to be clearly better)
+  }
+  if (time) *time = least;
+  return best;
+}
+
+hipError_t plan_fwd(const a2d_tile_desc& d, SegList* g, bool may_split) {
+  int cus = 0;
+  const hipError_t e = device_cus(&cus);
+  if (e != hipSuccess) return e;
+  const int64_t part = (int64_t)d.heads * d.nq * (d.hdim + 2) * sizeof(float);
+  const int64_t cap = may_split ? (int64_t)kSplitBytes / part : 1;
+  if (d.dtype == A2D_F32) plan_fwd_f32(d, g, cus, cap < 1 ? 1 : (int)cap);
+  else plan_fwd_mfma(d, g, cus, cap < 1 ? 1 : (int)cap);
+  return hipSuccess;
+}
+
+int64_t visible_keys(const a2d_tile_desc& d, const SegList& g, int64_t i) {
+  if (!d.causal) return d.nkv;
+  int64_t n = 0;
+  for (int s = 0; s < g.n; ++s) {
+    const int64_t v = i + g.rel[s] + 1;
+    n += v <= 0 ? 0 : (v < g.rows[s] ? v : g.rows[s]);
+  }
+  return n;
 }
 
 }  // namespace a2d

@@ -202,14 +202,17 @@ struct Walk {
   }
 };
 
-// workgroup -> (head, first row): as in the bf16 kernels the row blocks of the query heads that share a
-// key/value head go to one XCD, late (heavy) blocks first
-__device__ __forceinline__ bool query_block(const a2d_tile_desc& d, const SegList& g, int rows, int& head, int& q0) {
-  const int nqb = (d.nq + rows - 1) / rows, per_unit = g.group;
+// workgroup -> (head, first row, part of the walk): as in the bf16 kernels the row blocks of the query
+// heads that share a key/value head are placed together, late (heavy) blocks first
+__device__ __forceinline__ bool query_block(const a2d_tile_desc& d, const SegList& g, int rows, int& head, int& q0,
+                                            int& part) {
+  const int nqb = (d.nq + rows - 1) / rows;
   int unit, blk;
-  if (!xcd_map(d.heads / per_unit, per_unit * nqb, g.by_size != 0, unit, blk)) return false;
-  head = unit * per_unit + (g.by_size ? blk % per_unit : blk / nqb);
-  q0 = (nqb - 1 - (g.by_size ? blk / per_unit : blk % nqb)) * rows;
+  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, g.by_size != 0, unit, blk)) return false;
+  const int kvh = unit / g.parts;
+  part = unit - kvh * g.parts;
+  head = kvh * g.group + (g.by_size ? blk % g.group : blk / nqb);
+  q0 = (nqb - 1 - (g.by_size ? blk / g.group : blk % nqb)) * rows;
   return true;
 }
 
@@ -233,10 +236,12 @@ __device__ __forceinline__ float row_sum(float v) {
 template <int H, int RT, int KL>
 __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 ? 4 : 2))) void fwd_f32_kernel(
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
-    const float* __restrict__ V, float* __restrict__ O_part, float* __restrict__ m_out, float* __restrict__ l_out) {
+    const float* __restrict__ V, float* __restrict__ O_part, float* __restrict__ m_out, float* __restrict__ l_out,
+    FwdInput in) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  int head, q0;
-  if (!query_block(d, g, BLK * RT, head, q0)) return;
+  int head, q0, part;
+  if (!query_block(d, g, BLK * RT, head, q0, part)) return;
+  const int lanes = KL * g.parts;
   const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l15 = lane & 15, g4 = lane >> 4;
   const int kvh = head / g.group;
@@ -256,11 +261,11 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 
     o[t].zero();
     m_lane[t] = -INFINITY;
     l_run[t] = 0.f;
-    if (g.acc && kl == 0 && q_row[t] < d.nq) {     // continue from the triple in the output buffers
+    if (g.acc && kl == 0 && part == 0 && q_row[t] < d.nq) {     // continue from the triple given
       const int64_t row = (int64_t)head * d.nq + q_row[t];
-      o[t].load(O_part + row * H, g4);
-      m_lane[t] = m_out[row] / d.scale;             // -inf stays -inf
-      l_run[t] = g4 == 0 ? l_out[row] : 0.f;
+      o[t].load(in.N + row * H, g4);
+      m_lane[t] = in.m[row] / d.scale;             // -inf stays -inf
+      l_run[t] = g4 == 0 ? in.l[row] : 0.f;
     }
     m_ref[t] = m_lane[t];
   }
@@ -269,7 +274,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 
   auto seg_blocks = [&](int s) { return (vis_count(d, g, blk_last, s) + BLK - 1) / BLK; };
   Walk w;
   w.open(0, g.n, seg_blocks);
-  w.advance(kl, g.n, seg_blocks);
+  w.advance(part * KL + kl, g.n, seg_blocks);
   Nat<H> kn;
   Cols<H> vt[4];
   auto load_k = [&](const Walk& x) {
@@ -285,7 +290,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 
     f32x4 p[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t) p[t] = dot_rows<H>(kn, qf[t]);
-    w.advance(KL, g.n, seg_blocks);
+    w.advance(lanes, g.n, seg_blocks);
     if (w.s < g.n) load_k(w);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -350,7 +355,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
     if (q_row[t] >= d.nq) continue;
-    const int64_t row = (int64_t)head * d.nq + q_row[t];
+    const int64_t row = ((int64_t)part * d.heads + head) * d.nq + q_row[t];
     const float l = lsum[t][0];
     if (g.norm) {                                     // O' = N / l, lse' = m + ln l
       o[t].store(O_part + row * H, g4, l > 0.f ? 1.0f / l : 0.f);
@@ -371,8 +376,9 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     const float* __restrict__ V, const float* __restrict__ O, const float* __restrict__ dO,
     const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dQ) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  int head, q0;
-  if (!query_block(d, g, BLK, head, q0)) return;
+  int head, q0, part;
+  if (!query_block(d, g, BLK, head, q0, part)) return;
+  const int lanes = KL * g.parts;
   const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l15 = lane & 15, g4 = lane >> 4;
   const int kvh = head / g.group;
@@ -391,13 +397,13 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
     for (int e = 0; e < 4; ++e) del = fmaf(gf.v[y][e], kn.v[y][e], del);
   del = row_sum(del);
-  if (kl == 0 && g4 == 0 && q_row < d.nq) delta[(int64_t)head * d.nq + q_row] = del;
+  if (kl == 0 && part == 0 && g4 == 0 && q_row < d.nq) delta[(int64_t)head * d.nq + q_row] = del;
 
   const int blk_last = min(q0 + BLK, d.nq) - 1;
   auto seg_blocks = [&](int s) { return (vis_count(d, g, blk_last, s) + BLK - 1) / BLK; };
   Walk w;
   w.open(0, g.n, seg_blocks);
-  w.advance(kl, g.n, seg_blocks);
+  w.advance(part * KL + kl, g.n, seg_blocks);
   Out<H> dq;
   dq.zero();
   auto load_k = [&](const Walk& x) {
@@ -415,7 +421,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     __builtin_amdgcn_sched_barrier(0);
     f32x4 ds = dot_rows<H>(vn, gf);
     const int my_vis = vis_count(d, g, q_ld, s);
-    w.advance(KL, g.n, seg_blocks);
+    w.advance(lanes, g.n, seg_blocks);
     if (w.s < g.n) load_k(w);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -432,7 +438,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     if (kl != 0) return;
   }
   if (q_row < d.nq) {
-    float* row = dQ + ((int64_t)head * d.nq + q_row) * H;
+    float* row = dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H;
     dq.store(row, g4, d.scale, g.acc != 0);
   }
 }
@@ -447,7 +453,10 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int head, blk;                                      // key/value head
-  if (!xcd_map(d.heads / g.group, (d.nkv + BLK - 1) / BLK, g.by_size != 0, head, blk)) return;
+  if (!xcd_map(d.heads / g.group * g.parts, (d.nkv + BLK - 1) / BLK, g.by_size != 0, head, blk)) return;
+  const int unit = head, lanes = KL * g.parts;
+  head = unit / g.parts;
+  const int part = unit - head * g.parts;
   const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l15 = lane & 15, g4 = lane >> 4;
   const int k0 = blk * BLK, key = k0 + l15, k_ld = min(key, d.nkv - 1);
@@ -485,7 +494,8 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   dv.zero();
   Nat<H> x, y;                                        // operands, each loaded one contraction ahead
   // position of walk step n: query head (inside the group) and first row
-  int qh = 0, rb = kl;                                // of the next step to be loaded
+  const int n0 = part * KL + kl;
+  int qh = 0, rb = n0;                                // of the next step to be loaded
   auto wrap = [&]() { while (rb >= nblk && qh < g.group) { rb -= nblk; ++qh; } };
   if (nblk > 0) wrap();
   auto load_q = [&]() {
@@ -495,8 +505,8 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
     for (int i = 0; i < H / 16; ++i) x.v[i] = gload<f32x4>(qb, off + 64 * i);
   };
-  if (kl < total) load_q();
-  for (int n = kl; n < total; n += KL) {
+  if (n0 < total) load_q();
+  for (int n = n0; n < total; n += lanes) {
     const int i0 = (b0 + rb) * BLK, ch = qh;
     {
       const unsigned row = min(i0 + l15, d.nq - 1);
@@ -537,12 +547,12 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
       qt[r].load(qb + ch * q_head, row, q_row, l15);
       __builtin_amdgcn_sched_barrier(0);
     }
-    rb += KL;
+    rb += lanes;
     wrap();
     dk.contract(qt[0], ds[0]);
     dk.contract(qt[1], ds[1]);
     __builtin_amdgcn_sched_barrier(0);
-    if (n + KL < total) load_q();
+    if (n + lanes < total) load_q();
     __builtin_amdgcn_sched_barrier(0);
     dk.contract(qt[2], ds[2]);
     dk.contract(qt[3], ds[3]);
@@ -554,7 +564,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     if (kl != 0) return;
   }
   if (key < d.nkv) {
-    const int64_t row = (int64_t)head * d.nkv + key;
+    const int64_t row = ((int64_t)part * (d.heads / g.group) + head) * d.nkv + key;
     dk.store(dK + row * H, g4, d.scale);
     dv.store(dV + row * H, g4, 1.0f);
   }
@@ -562,13 +572,12 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
 
 template <int H, int RT, int KL>
 hipError_t fwd_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
-                  float* O_part, float* m, float* l, hipStream_t s) {
+                  float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
   constexpr int lds = KL > 1 ? KL / 2 * RT * (H / 16 + 1) * 1024 : 0;
   static_assert(lds <= 80 * 1024, "two workgroups per compute unit");
-  const int per_unit = g.group;
-  dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BLK * RT - 1) / (BLK * RT)))), block(64 * KL);
+  dim3 grid(xcd_grid(d.heads / g.group * g.parts, g.group * ((d.nq + BLK * RT - 1) / (BLK * RT)))), block(64 * KL);
   A2D_LAUNCH((fwd_f32_kernel<H, RT, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
-             (const float*)V, O_part, m, l);
+             (const float*)V, O_part, m, l, in);
   return hipGetLastError();
 }
 
@@ -576,8 +585,7 @@ template <int H, int KL>
 hipError_t dq_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V, const void* O,
                  const void* dO, const float* lse, float* delta, float* dQ, hipStream_t s) {
   constexpr int lds = KL / 2 * (H / 16) * 1024;
-  const int per_unit = g.group;
-  dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BLK - 1) / BLK))), block(64 * KL);
+  dim3 grid(xcd_grid(d.heads / g.group * g.parts, g.group * ((d.nq + BLK - 1) / BLK))), block(64 * KL);
   A2D_LAUNCH((bwd_dq_f32_kernel<H, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
              (const float*)V, (const float*)O, (const float*)dO, lse, delta, dQ);
   return hipGetLastError();
@@ -587,7 +595,7 @@ template <int H, int KL>
 hipError_t dkdv_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                    const void* dO, const float* lse, const float* delta, float* dK, float* dV, hipStream_t s) {
   constexpr int lds = KL / 2 * (H / 8) * 1024;
-  dim3 grid(xcd_grid(d.heads / g.group, (d.nkv + BLK - 1) / BLK)), block(64 * KL);
+  dim3 grid(xcd_grid(d.heads / g.group * g.parts, (d.nkv + BLK - 1) / BLK)), block(64 * KL);
   A2D_LAUNCH((bwd_dkdv_f32_kernel<H, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
              (const float*)V, (const float*)dO, lse, delta, dK, dV);
   return hipGetLastError();
@@ -595,58 +603,89 @@ hipError_t dkdv_go(const a2d_tile_desc& d, const SegList& g, const void* Q, cons
 
 // Key lanes of a workgroup: four, eight when that still leaves compute units without two workgroups'
 // worth of wavefronts (8 wavefronts fill a compute unit's SIMDs twice)
-bool eight_lanes(int64_t row_blocks, int cus) { return row_blocks <= cus; }
+bool eight_lanes(int64_t workgroups, int cus) { return workgroups <= cus; }
+
+enum { F32_ROWS32 = 0, F32_LANES4 = 1, F32_LANES8 = 2 };   // <2, 4>, <1, 4>, <1, 8>
 
 template <int H>
 hipError_t fwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
-                 float* O_part, float* m, float* l, int cus, hipStream_t s) {
-  // 32 rows per workgroup halve the operand traffic per MFMA; 16 rows when those come to fewer than
-  // four workgroups per compute unit
-  const int64_t b32 = (int64_t)d.heads * ((d.nq + 31) / 32), b16 = (int64_t)d.heads * ((d.nq + 15) / 16);
-  if (b32 >= 4 * (int64_t)cus) return fwd_go<H, 2, 4>(d, g, Q, K, V, O_part, m, l, s);
-  if (eight_lanes(b16, cus)) return fwd_go<H, 1, 8>(d, g, Q, K, V, O_part, m, l, s);
-  return fwd_go<H, 1, 4>(d, g, Q, K, V, O_part, m, l, s);
+                 float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
+  if (g.form == F32_ROWS32) return fwd_go<H, 2, 4>(d, g, Q, K, V, O_part, m, l, in, s);
+  if (g.form == F32_LANES8) return fwd_go<H, 1, 8>(d, g, Q, K, V, O_part, m, l, in, s);
+  return fwd_go<H, 1, 4>(d, g, Q, K, V, O_part, m, l, in, s);
 }
 
 template <int H>
 hipError_t bwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                  const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK, float* dV,
-                 int cus, hipStream_t s) {
-  const hipError_t e = eight_lanes((int64_t)d.heads * ((d.nq + 15) / 16), cus)
-                           ? dq_go<H, 8>(d, g, Q, K, V, O, dO, lse, delta, dQ, s)
-                           : dq_go<H, 4>(d, g, Q, K, V, O, dO, lse, delta, dQ, s);
+                 const BwdParts& parts, int cus, hipStream_t s) {
+  SegList gq = g, gk = g;
+  gq.parts = parts.q;
+  if (parts.q > 1) gq.acc = 0;                       // (the sum over the parts adds)
+  gk.parts = parts.kv;
+  const hipError_t e = eight_lanes((int64_t)d.heads * ((d.nq + 15) / 16) * parts.q, cus)
+                           ? dq_go<H, 8>(d, gq, Q, K, V, O, dO, lse, delta, dQ, s)
+                           : dq_go<H, 4>(d, gq, Q, K, V, O, dO, lse, delta, dQ, s);
   if (e != hipSuccess) return e;
-  return eight_lanes((int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16), cus)
-             ? dkdv_go<H, 8>(d, g, Q, K, V, dO, lse, delta, dK, dV, s)
-             : dkdv_go<H, 4>(d, g, Q, K, V, dO, lse, delta, dK, dV, s);
+  return eight_lanes((int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16) * parts.kv, cus)
+             ? dkdv_go<H, 8>(d, gk, Q, K, V, dO, lse, delta, dK, dV, s)
+             : dkdv_go<H, 4>(d, gk, Q, K, V, dO, lse, delta, dK, dV, s);
+}
+
+// The walk of 16-row blocks as a model: a turn is one wavefront per SIMD (4 * cus of them), a step
+// of `contractions` contractions over H takes 32 H / 4 cycles each (at about 2.3 GHz).
+constexpr double kF32FixedUs = 4.0;
+WalkModel f32_walk(int64_t blocks, double steps, int lanes, int contractions, int hdim, int cus) {
+  // (KL key lanes: a workgroup is lanes / 4 turns' worth of wavefronts)
+  return WalkModel{blocks, lanes <= 4 ? cus : cus / 2, steps / lanes, steps / lanes,
+                   contractions * hdim * 8 / 2.1e3, kF32FixedUs};
 }
 
 }  // namespace
 
+// 32 rows per workgroup halve the operand traffic per MFMA; 16 rows when those come to fewer than
+// four workgroups per compute unit, with eight key lanes (or parts) when those are few
+void plan_fwd_f32(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
+  const int64_t b32 = (int64_t)d.heads * ((d.nq + 31) / 32), b16 = (int64_t)d.heads * ((d.nq + 15) / 16);
+  g->parts = 1;
+  if (b32 >= 4 * (int64_t)cus) { g->form = F32_ROWS32; return; }
+  const double steps = (double)visible_keys(d, *g, d.nq - 1) / BLK + 1;
+  const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 5e6;
+  g->parts = best_parts(f32_walk(b16, steps, 4, 2, d.hdim, cus), cap, part_us, nullptr);
+  g->form = eight_lanes(b16 * g->parts, cus) ? F32_LANES8 : F32_LANES4;
+}
+
+BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q) {
+  const int64_t bq = (int64_t)d.heads * ((d.nq + 15) / 16), bk = (int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16);
+  const double sq = (double)visible_keys(d, g, d.nq - 1) / BLK + 1, sk = (double)g.group * ((d.nq + 15) / 16);
+  BwdParts p;
+  p.q = best_parts(f32_walk(bq, sq, 4, 3, d.hdim, cus), cap_q, (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
+  p.kv = best_parts(f32_walk(bk, sk, 4, 4, d.hdim, cus), cap_kv,
+                    (double)d.heads / g.group * d.nkv * d.hdim * 16 / 5e6, nullptr);
+  return p;
+}
+
 hipError_t launch_fwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
-                          float* O_part, float* m, float* l, hipStream_t s) {
-  int cus = 0;
-  const hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
+                          float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
   switch (d.hdim) {
-    case 128: return fwd_h<128>(d, g, Q, K, V, O_part, m, l, cus, s);
-    case 96: return fwd_h<96>(d, g, Q, K, V, O_part, m, l, cus, s);
-    case 80: return fwd_h<80>(d, g, Q, K, V, O_part, m, l, cus, s);
-    default: return fwd_h<64>(d, g, Q, K, V, O_part, m, l, cus, s);
+    case 128: return fwd_h<128>(d, g, Q, K, V, O_part, m, l, in, s);
+    case 96: return fwd_h<96>(d, g, Q, K, V, O_part, m, l, in, s);
+    case 80: return fwd_h<80>(d, g, Q, K, V, O_part, m, l, in, s);
+    default: return fwd_h<64>(d, g, Q, K, V, O_part, m, l, in, s);
   }
 }
 
 hipError_t launch_bwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                           const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK,
-                          float* dV, hipStream_t s) {
+                          float* dV, const BwdParts& parts, hipStream_t s) {
   int cus = 0;
   const hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
   switch (d.hdim) {
-    case 128: return bwd_h<128>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, cus, s);
-    case 96: return bwd_h<96>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, cus, s);
-    case 80: return bwd_h<80>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, cus, s);
-    default: return bwd_h<64>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, cus, s);
+    case 128: return bwd_h<128>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, cus, s);
+    case 96: return bwd_h<96>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, cus, s);
+    case 80: return bwd_h<80>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, cus, s);
+    default: return bwd_h<64>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, cus, s);
   }
 }
 

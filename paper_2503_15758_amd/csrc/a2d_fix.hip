@@ -273,6 +273,36 @@ __global__ __launch_bounds__(256) void sum_grid_kernel(SumSets a, int hv) {
   store_out4(static_cast<OutT*>(s.out), (gr.token(g) * hv + col) * 4, acc);
 }
 
+// The partial results of a split walk, which lie one behind the other: out (+)= sum over the parts,
+// in their order.  Small data that the kernel before it left in L2: one 16-byte group per thread, four
+// loads in flight.  blockIdx.y picks the set.
+struct PartSets {
+  PartSet s[3];
+};
+__global__ __launch_bounds__(256) void sum_parts_kernel(PartSets a) {
+  const PartSet& s = a.s[blockIdx.y];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, n4 = s.n / 4;
+  if (i >= n4) return;
+  const f32x4* p = reinterpret_cast<const f32x4*>(s.p) + i;
+  f32x4* out = reinterpret_cast<f32x4*>(s.out) + i;
+  f32x4 acc = s.add ? *out : f32x4{0.f, 0.f, 0.f, 0.f};
+  int z = 0;
+  for (; z + 4 <= s.k; z += 4) {
+    f32x4 v[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) v[x] = p[(z + x) * n4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      acc[0] += v[x][0]; acc[1] += v[x][1]; acc[2] += v[x][2]; acc[3] += v[x][3];
+    }
+  }
+  for (; z < s.k; ++z) {
+    const f32x4 v = p[z * n4];
+    acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
+  }
+  *out = acc;
+}
+
 template <typename OutT, int KMAX, bool TRIPLE = false>
 void fix_launch(int k, int64_t rows, int hv, const FixPtrs& p, const OutMap& om, OutT* O, float* lse, float* l_out,
                 hipStream_t s) {
@@ -395,6 +425,17 @@ hipError_t launch_sum_grid(int nsets, const SumSet* sets, int hdim, int out_dtyp
   }
   if (out_dtype == A2D_BF16) sum_grid_dispatch<bf16_t>(nsets, a, hdim / 4, (most + 255) / 256, s);
   else sum_grid_dispatch<float>(nsets, a, hdim / 4, (most + 255) / 256, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_parts(int nsets, const PartSet* sets, hipStream_t s) {
+  PartSets a;
+  int64_t most = 0;
+  for (int x = 0; x < 3; ++x) {
+    a.s[x] = sets[x < nsets ? x : 0];
+    if (a.s[x].n > most) most = a.s[x].n;
+  }
+  A2D_LAUNCH(sum_parts_kernel, dim3((unsigned)((most / 4 + 255) / 256), nsets), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

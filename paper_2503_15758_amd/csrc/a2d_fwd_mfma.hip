@@ -43,6 +43,7 @@ __host__ __device__ constexpr int kld(int hd) { return hd * 2 + 16; }
 __host__ __device__ constexpr int buf_bytes(int hd) { return BN * kld(hd) + BN * VLD; }
 __host__ __device__ constexpr int lds_bytes(int hd) { return 2 * buf_bytes(hd); }
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
+constexpr double kStepUs[3] = {1.5, 1.8, 2.1};   // a 64-key step of a 256-row workgroup, H = 64 / 96 / 128
 
 template <int HD>
 struct FwdState {
@@ -155,7 +156,7 @@ template <int WAVES, int HR, int KL>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
     const bf16_t* __restrict__ V, float* __restrict__ O_part, float* __restrict__ m_out,
-    float* __restrict__ l_out) {
+    float* __restrict__ l_out, FwdInput in) {
   constexpr int RW = WAVES / KL;          // wavefronts of one key lane
   constexpr int BM = 32 * RW;             // query rows per workgroup
   constexpr int kThreads = 64 * RW;       // threads of one key lane (they stage its tiles)
@@ -173,11 +174,12 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // (the query blocks of the query heads that share a key/value head are placed as one unit)
   int unit, blk;
   const TilePos tp = tile_pos<true>(d, g);
-  const int per_unit = g.group;
-  if (!xcd_map(d.heads / per_unit, per_unit * nqb, tp.by_size != 0, unit, blk)) return;
-  // (blocks numbered by size first when the workgroups are ordered by size)
-  const int head = unit * per_unit + (tp.by_size ? blk % per_unit : blk / nqb), kvh = head / g.group;
-  blk = tp.by_size ? blk / per_unit : blk % nqb;
+  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, tp.by_size != 0, unit, blk)) return;
+  // (unit = part `part` of the walks over one key/value head; blocks numbered by size first when the
+  // workgroups are ordered by size)
+  const int kvh = unit / g.parts, part = unit - kvh * g.parts;
+  const int head = kvh * g.group + (tp.by_size ? blk % g.group : blk / nqb);
+  blk = tp.by_size ? blk / g.group : blk % nqb;
   // heavy (late) query blocks first: under a causal mask they walk more key blocks
   const int q0 = (nqb - 1 - blk) * BM;
   const int tid = (int)threadIdx.x - kl * kThreads;     // within the key lane
@@ -187,7 +189,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   K += (int64_t)kvh * d.lk.head + tp.c * g.b.k;
   V += (int64_t)kvh * d.lv.head + tp.c * g.b.v;
   {
-    const int64_t slot = (int64_t)col_slot(g.b, tp.r, tp.c) * d.heads * d.nq;
+    const int64_t slot = ((int64_t)col_slot(g.b, tp.r, tp.c) + part) * d.heads * d.nq;
     O_part += slot * HR;
     m_out += slot;
     l_out += slot;
@@ -211,9 +213,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   st.l_run = 0.f;
   const float c = d.scale * kLog2e;
   float m_in = -INFINITY;
-  if (g.acc) {
-    // (key lane 0 continues the stored partial; the barriers are the whole workgroup's)
-    // Continue from the (N, m, l) already in the output buffers: N into the accumulators (same
+  if (g.acc && part == 0) {
+    // (key lane 0 of the first part continues the stored partial; the barriers are the whole workgroup's)
+    // Continue from the (N, m, l) of `in`: N into the accumulators (same
     // element mapping as the epilogue's stores), m as the exponent reference, l into one of the two
     // lanes of the row.  A lane's share of N is 16 scattered 16-byte pieces of its row, so the
     // rows come in through LDS: each wavefront reads 16 of its rows at a time with whole-row
@@ -232,7 +234,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
         const int64_t r = wrow0 + 16 * pass + 2 * i + (lane >> 5);
         t[i] = u32x4{0, 0, 0, 0};
         if (col_ok && kl == 0)
-          t[i] = *reinterpret_cast<const u32x4*>(O_part + (r < last_row ? r : last_row) * H + 4 * (lane & 31));
+          t[i] = *reinterpret_cast<const u32x4*>(in.N + (r < last_row ? r : last_row) * H + 4 * (lane & 31));
       }
       if (4 * (lane & 31) < HD && kl == 0) {
 #pragma unroll
@@ -256,8 +258,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
       // the other key lane starts from nothing
     } else if (q_row < d.nq) {
       const int64_t row = (int64_t)head * d.nq + q_row;
-      m_in = m_out[row];
-      st.l_run = half == 0 ? l_out[row] : 0.f;
+      m_in = in.m[row];
+      st.l_run = half == 0 ? in.l[row] : 0.f;
     } else {
 #pragma unroll
       for (int t = 0; t < CT; ++t) st.o[t] = zero16();       // rows beyond nq: nothing to continue
@@ -333,25 +335,26 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   const unsigned v_rd0 =
       lds_base + K_BYTES + (4 * (g16 >> 1) + (j16 >> 2)) * VLD + (16 * (g16 & 1) + 4 * (j16 & 3)) * 2;
 
-  // Walk over the entries (sub-block, key block); key lane kl takes entries kl, kl + KL, ...  The
-  // sub-block table lives in kernel-argument memory, and scalar loads share a wait counter with the
-  // LDS reads in flight, so it is only touched when a walk moves to another sub-block; in between
-  // its values sit in registers.
+  // Walk over the entries (sub-block, key block): lane part * KL + kl of parts * KL takes every
+  // (parts * KL)-th entry.  The sub-block table lives in kernel-argument memory, and scalar loads
+  // share a wait counter with the LDS reads in flight, so it is only touched when a walk moves to
+  // another sub-block; in between its values sit in registers.
   // An entry is (sub-block sb, block j of its nblk); sb == g.n: past the end.
-  auto open_segment = [&](int s, int& sb, int& j, int& nblk) {   // first sub-block after s with visible keys
-    do { ++s; } while (s < g.n && seg_blocks(s) == 0);
-    sb = s; j = 0;
+  const int stride = KL * g.parts;
+  auto open_segment = [&](int s, int& sb, int& nblk) {           // first sub-block from s on with visible keys
+    while (s < g.n && seg_blocks(s) == 0) ++s;
+    sb = s;
     if (s < g.n) nblk = seg_blocks(s);
   };
-  auto advance = [&](int& sb, int& j, int& nblk) {
-    if (sb < g.n && ++j >= nblk) open_segment(sb, sb, j, nblk);
+  auto advance = [&](int by, int& sb, int& j, int& nblk) {
+    j += by;
+    while (sb < g.n && j >= nblk) { j -= nblk; open_segment(sb + 1, sb, nblk); }
   };
-  int sb, j, nblk = 0;                             // this key lane's current entry
-  open_segment(-1, sb, j, nblk);
-  int lead_sb = sb, lead_j = j, lead_nblk = nblk;  // key lane 0's: every lane loops while it exists
-  if (KL > 1) {
-    for (int x = 0; x < kl; ++x) advance(sb, j, nblk);
-  }
+  int sb, j = 0, nblk = 0;                         // this key lane's current entry
+  open_segment(0, sb, nblk);
+  advance(part * KL, sb, j, nblk);
+  int lead_sb = sb, lead_j = j, lead_nblk = nblk;  // key lane 0's: every lane of the workgroup loops while it exists
+  if (KL > 1) advance(kl, sb, j, nblk);
   int nx_start = 0, nx_rows = 0;                   // start / rows of the next entry's sub-block
   if (sb < g.n) {
     enter_segment(sb);
@@ -364,8 +367,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   int boff = 0;
   while ((KL == 1 ? sb : lead_sb) < g.n) {
     int nsb = sb, nj = j, nnblk = nblk;
-#pragma unroll
-    for (int x = 0; x < KL; ++x) advance(nsb, nj, nnblk);
+    advance(stride, nsb, nj, nnblk);
     const bool more = nsb < g.n;
     if (more && nsb != sb) { nx_start = g.start[nsb]; nx_rows = g.rows[nsb]; }
     if (more) load_tile(nx_start, nx_rows, nj);
@@ -377,10 +379,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     if (more) store_tile(BUF_BYTES - boff);
     __syncthreads();
     if (more && nsb != sb) enter_segment(nsb);
-    if (KL > 1) {
-#pragma unroll
-      for (int x = 0; x < KL; ++x) advance(lead_sb, lead_j, lead_nblk);
-    }
+    if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
     sb = nsb; j = nj; nblk = nnblk;
     boff = BUF_BYTES - boff;
   }
@@ -461,32 +460,49 @@ bool fwd_mfma_supported(const a2d_tile_desc& d) {
 namespace {
 template <int WAVES, int HR, int KL>
 hipError_t fwd_launch(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
-                      float* O_part, float* m, float* l, hipStream_t s) {
+                      float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
   constexpr int bytes = KL * lds_bytes(padded_head(HR)), BM = 32 * WAVES / KL;
   if (ph == PREPARE)
     return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_mfma_kernel<WAVES, HR, KL>), bytes);
-  const int per_unit = g.group;
-  dim3 grid(xcd_grid(d.heads / per_unit, per_unit * ((d.nq + BM - 1) / BM)), g.b.n ? g.b.n : 1), block(64 * WAVES);
+  dim3 grid(xcd_grid(d.heads / g.group * g.parts, g.group * ((d.nq + BM - 1) / BM)), g.b.n ? g.b.n : 1), block(64 * WAVES);
   A2D_LAUNCH((fwd_mfma_kernel<WAVES, HR, KL>), grid, block, bytes, s, d, g, (const bf16_t*)Q,
-                     (const bf16_t*)K, (const bf16_t*)V, O_part, m, l);
+                     (const bf16_t*)K, (const bf16_t*)V, O_part, m, l, in);
   return hipGetLastError();
 }
+enum { FWD_BIG = 0, FWD_LANES = 1, FWD_PAIRS = 2 };   // <8, HR, 1>, <8, HR, 2>, <4, HR, 1>
 }  // namespace
 
+// Shape and parts.  Three shapes: 256-row workgroups, one per compute unit; 128-row workgroups whose two
+// key lanes walk alternate key blocks, one per compute unit; 128-row workgroups of four wavefronts, two
+// per compute unit (each K / V tile staged twice: 6 % slower per key block, but no merge of lanes and
+// a finer last turn).  By model, with parts > 1 where even the 128-row blocks leave compute units idle.
+void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
+  const int64_t heads = (int64_t)d.heads * (g->b.n ? g->b.n : 1);
+  double mean = 0;
+  for (int i = 0; i < 8; ++i) mean += (double)visible_keys(d, *g, (2 * i + 1) * (int64_t)d.nq / 16) / 8;
+  const double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 1;
+  const bool uneven = g->by_size || g->b.n;
+  mean = uneven ? mean / BN + 1 : most;
+  const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 6.0;
+  const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 5e6;        // written and read back at 5 TB/s
+  const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
+  const WalkModel m[3] = {{b256, cus, mean, most, step, fixed},
+                          {b128, cus, mean / 2, most / 2, step * 1.05, fixed + 2},
+                          {b128, 2 * cus, mean, most, b128 <= cus ? step * 0.6 : step * 1.06, fixed}};
+  double least = 0;
+  for (int f = 0; f < 3; ++f) {
+    double t;
+    const int z = best_parts(m[f], cap, part_us, &t);
+    if (f == 0 || t < 0.97 * least) { least = t; g->form = f; g->parts = z; }
+  }
+}
+
 hipError_t launch_fwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
-                           const void* V, float* O_part, float* m, float* l, hipStream_t s) {
-  // 256-row workgroups unless that leaves compute units without one; then 128-row workgroups, with
-  // two key lanes when at most one of those comes to a compute unit either
-  int cus = 0;
-  const hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
-  const int64_t heads = (int64_t)d.heads * (g.b.n ? g.b.n : 1);
-  const bool big = heads * ((d.nq + 255) / 256) >= cus;
-  const bool lanes = !big && heads * ((d.nq + 127) / 128) <= cus;
+                           const void* V, float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
 #define A2D_FWD(HR)                                                                      \
-  return big     ? fwd_launch<8, HR, 1>(ph, d, g, Q, K, V, O_part, m, l, s)              \
-         : lanes ? fwd_launch<8, HR, 2>(ph, d, g, Q, K, V, O_part, m, l, s)              \
-                 : fwd_launch<4, HR, 1>(ph, d, g, Q, K, V, O_part, m, l, s)
+  return g.form == FWD_BIG     ? fwd_launch<8, HR, 1>(ph, d, g, Q, K, V, O_part, m, l, in, s) \
+         : g.form == FWD_LANES ? fwd_launch<8, HR, 2>(ph, d, g, Q, K, V, O_part, m, l, in, s) \
+                               : fwd_launch<4, HR, 1>(ph, d, g, Q, K, V, O_part, m, l, in, s)
   if (d.hdim == 128) { A2D_FWD(128); }
   if (d.hdim == 96) { A2D_FWD(96); }
   if (d.hdim == 80) { A2D_FWD(80); }

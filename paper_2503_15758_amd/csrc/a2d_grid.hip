@@ -43,7 +43,7 @@ void describe(const GridProblem& p, a2d_tile_desc* d, SegList* g) {
   d->ldo = block_layout(p, p.g);
   g->n = 1;
   g->group = p.heads / p.kv_heads;
-  g->qsplit = 1;
+  g->parts = 1;
   g->rows[0] = rows_of(p);
   g->b.n = slots_of(p);
   g->b.side = p.side;
@@ -114,10 +114,13 @@ hipError_t grid_forward(const GridProblem& p, const void* Q, const void* K, cons
   float* N = static_cast<float*>(ws);
   float* m = N + slots * per * p.hdim;
   float* l = m + slots * per;
-  hipError_t e = launch_fwd_mfma(PREPARE, d, g, Q, K, V, N, m, l, s);
+  hipError_t e = plan_fwd(d, &g, false);
+  if (e != hipSuccess) return e;
+  const FwdInput none{nullptr, nullptr, nullptr};
+  e = launch_fwd_mfma(PREPARE, d, g, Q, K, V, N, m, l, none, s);
   if (e != hipSuccess) return e;
   trace_mark(s);
-  e = launch_fwd_mfma(LAUNCH, d, g, Q, K, V, N, m, l, s);      // Alg. 1 line 4, every tile
+  e = launch_fwd_mfma(LAUNCH, d, g, Q, K, V, N, m, l, none, s);      // Alg. 1 line 4, every tile
   if (e != hipSuccess) return e;
   FixPtrs f;
   memset(&f, 0, sizeof(f));
@@ -157,7 +160,7 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
       g.b.first = t;
       g.b.n = total - t < chunk ? total - t : chunk;
       const hipError_t e = launch_bwd_mfma(pass == 0 ? PREPARE : LAUNCH, d, g, Q, K, V, dO, lse_blk, delta, dq, dk, dv,
-                                           ds, nullptr, s);
+                                           ds, BwdParts{1, 1}, s);
       if (e != hipSuccess) return e;
     }
   }

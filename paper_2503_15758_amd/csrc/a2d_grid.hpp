@@ -10,6 +10,13 @@ namespace a2d {
 
 bool force_generic();            // the debug switch a2d_debug_force_generic() sets
 
+// scratch memory offered to the tile calls of this host thread (see a2d_common.hpp)
+struct ScratchSource {
+  void* (*get)(void* ctx, size_t bytes);
+  void* ctx;
+};
+void scratch_offer(const ScratchSource* src);
+
 struct GridProblem {
   int heads, kv_heads, seq, side, hdim, causal, cyclic;
   float scale;

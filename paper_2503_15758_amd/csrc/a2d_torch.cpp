@@ -261,6 +261,31 @@ void qkv(const at::Tensor& Q, const at::Tensor& K, const at::Tensor& V) {
     fail(A2D_ERR_INVALID_ARG, "Q, K, V shapes / dtypes do not match");
 }
 
+// Offers the library scratch memory from torch's allocator for the partial results of split walks while
+// it lives; the blocks go back when it does (the allocator orders their reuse on the stream).
+class Scratch {
+  std::vector<at::Tensor> held_;
+  at::TensorOptions options_;
+  a2d::ScratchSource source_;
+  static void* get(void* self, size_t bytes) {
+    Scratch* s = static_cast<Scratch*>(self);
+    try {
+      s->held_.push_back(at::empty({(int64_t)bytes}, s->options_));
+    } catch (...) {                                  // no memory: the call runs unsplit
+      return nullptr;
+    }
+    return s->held_.back().data_ptr();
+  }
+
+ public:
+  explicit Scratch(const at::Tensor& like)
+      : options_(like.options().dtype(at::kByte).requires_grad(false)), source_{&Scratch::get, this} {
+    a2d::scratch_offer(&source_);
+  }
+  ~Scratch() { a2d::scratch_offer(nullptr); }
+  Scratch(const Scratch&) = delete;
+};
+
 // runs f with the GIL released
 template <class F>
 a2d_status unlocked(F&& f) {
@@ -291,6 +316,7 @@ PyObject* partial_fwd(Args a) {
   const void *q = Q.data_ptr(), *k = K.data_ptr(), *v = V.data_ptr();
   float *N = data<float>(o.t[0]), *m = data<float>(o.t[1]), *l = data<float>(o.t[2]);
   const int kvh = (int)K.size(0);
+  const Scratch scratch(Q);
   check(unlocked([&] {
     if (kvh != d.heads)                                // grouped queries: K, V hold fewer heads than Q
       return a2d_partial_fwd_gqa(&d, kvh, segs.n(), segs.ptr(), acc ? A2D_TILE_ACCUMULATE : 0, q, k, v, N, m, l, nullptr,
@@ -320,6 +346,7 @@ PyObject* partial_fwd_norm(Args a) {
   void* O = o.t[0].data_ptr();
   float* lse = data<float>(o.t[1]);
   const int kvh = (int)K.size(0);
+  const Scratch scratch(Q);
   check(unlocked([&] {
     if (kvh != d.heads)
       return a2d_partial_fwd_gqa(&d, kvh, segs.n(), segs.ptr(), A2D_TILE_NORMALISED, q, k, v, O, lse, nullptr, nullptr, 0,
@@ -384,6 +411,7 @@ PyObject* partial_bwd(Args a) {
   const void *q = x.Q.data_ptr(), *k = x.K.data_ptr(), *v = x.V.data_ptr(), *O = x.O.data_ptr(), *g = x.dO.data_ptr();
   const float* lse = data<float>(x.lse);
   float *dq = data<float>(o.t[0]), *dk = data<float>(o.t[1]), *dv = data<float>(o.t[2]);
+  const Scratch scratch(x.Q);
   check(unlocked([&] {
     if (kvh != d.heads)                                // dK_part, dV_part have K's heads
       return a2d_partial_bwd_gqa(&d, kvh, segs.n(), segs.ptr(),
