@@ -1283,12 +1283,12 @@ BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cu
   const int kv_heads = d.heads / g.group;
   BwdParts p;
   const double rows = (double)g.group * ((d.nq + BQ - 1) / BQ);
-  const WalkModel kv = {(int64_t)kv_heads * ((d.nkv + DK_KEYS - 1) / DK_KEYS), cus, rows, rows, kKvStepUs, 8.0};
-  p.kv = best_parts(kv, cap_kv, (double)kv_heads * d.nkv * d.hdim * 16 / 5e6, nullptr);
+  const WalkModel kv = {(int64_t)kv_heads * ((d.nkv + DK_KEYS - 1) / DK_KEYS), cus, rows, rows, kKvStepUs, 8.0, 0, 0};
+  p.kv = best_parts(kv, cap_kv, 5.0, (double)kv_heads * d.nkv * d.hdim * 16 / 5e6, nullptr);
   const double keys = (double)visible_keys(d, g, d.nq - 1) / BKS + 1;
   const int64_t b128 = (int64_t)d.heads * ((d.nq + 127) / 128);
-  const WalkModel q = {b128, cus, keys / 2, keys / 2, ds ? kDsqStepUs : kDqStepUs, 6.0};
-  p.q = best_parts(q, cap_q, (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
+  const WalkModel q = {b128, cus, keys / 2, keys / 2, ds ? kDsqStepUs : kDqStepUs, 6.0, 0, 0};
+  p.q = best_parts(q, cap_q, 5.0, (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
   return p;
 }
 

@@ -158,20 +158,31 @@ constexpr size_t kSplitBytes = (size_t)32 << 20;
 // number of parts - and the workgroup shape, where a kernel has several - is the one with the least.
 struct WalkModel {
   int64_t blocks;          // row blocks
-  int slots;               // workgroups the chip holds at a time
+  int slots;               // workgroups, or pairs of workgroups, that the chip holds at a time
   double mean, most;       // steps of a block's walk: on average, the longest
   double step, fixed;      // time of a step, of everything else in a workgroup
+  double pair_step, pair_fixed;   // the same of two workgroups that share a slot (0: a slot holds one)
 };
 inline double walk_time(const WalkModel& w, int parts) {
-  const auto len = [&](double steps) { const double n = steps / parts; return (n < 1.0 ? 1.0 : n) * w.step + w.fixed; };
+  const auto len = [&](double steps, double step, double fixed) {
+    const double n = steps / parts;
+    return (n < 1.0 ? 1.0 : n) * step + fixed;
+  };
   const int64_t wgs = w.blocks * parts;
-  if (wgs <= w.slots) return len(w.most);
-  if (w.mean >= w.most) return (double)((wgs + w.slots - 1) / w.slots) * len(w.most);
-  const double even = ((double)wgs / w.slots + 0.5) * len(w.mean);        // longest first: half a workgroup of tail
-  return even > len(w.most) ? even : len(w.most);
+  if (wgs <= w.slots) return len(w.most, w.step, w.fixed);
+  const int64_t turns = (wgs + w.slots - 1) / w.slots;
+  const bool pairs = w.pair_step > 0;
+  if (w.mean >= w.most)
+    return pairs ? turns / 2 * len(w.most, w.pair_step, w.pair_fixed) + turns % 2 * len(w.most, w.step, w.fixed)
+                 : turns * len(w.most, w.step, w.fixed);
+  const double each = pairs ? 0.5 * len(w.mean, w.pair_step, w.pair_fixed) : len(w.mean, w.step, w.fixed);
+  const double even = ((double)wgs / w.slots + 0.5) * each;               // longest first: half a workgroup of tail
+  const double longest = len(w.most, pairs ? w.pair_step : w.step, w.fixed);
+  return even > longest ? even : longest;
 }
-// the best number of parts up to `cap` (ties: the smaller), each part costing part_us to write and merge
-int best_parts(const WalkModel& w, int cap, double part_us, double* time);
+// the best number of parts up to `cap` (ties: the smaller); a split costs merge_us, a launch behind the
+// tile kernel, and part_us per part to write and read back
+int best_parts(const WalkModel& w, int cap, double merge_us, double part_us, double* time);
 // keys that query row i of the tile sees
 int64_t visible_keys(const a2d_tile_desc& d, const SegList& g, int64_t i);
 

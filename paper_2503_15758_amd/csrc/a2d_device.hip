@@ -13,7 +13,6 @@
 namespace a2d {
 namespace {
 
-constexpr double kMergeUs = 5.0;     // a merge or sum launch behind a tile kernel, small data
 
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_cus[kMaxDevices];                       // 0 = not asked yet
@@ -92,11 +91,11 @@ void scratch_offer(const ScratchSource* src) { t_scratch = src; }
 bool scratch_offered() { return t_scratch != nullptr; }
 void* scratch_get(size_t bytes) { return t_scratch ? t_scratch->get(t_scratch->ctx, bytes) : nullptr; }
 
-int best_parts(const WalkModel& w, int cap, double part_us, double* time) {
+int best_parts(const WalkModel& w, int cap, double merge_us, double part_us, double* time) {
   int best = 1;
   double least = walk_time(w, 1);
   for (int z = 2; z <= cap && z <= A2D_MAX_PARTS && z <= w.most; ++z) {
-    const double t = walk_time(w, z) + kMergeUs + z * part_us;
+    const double t = walk_time(w, z) + merge_us + z * part_us;
     if (t < 0.95 * least) { best = z; least = t; }             // (a split has to be clearly better)
   }
   if (time) *time = least;

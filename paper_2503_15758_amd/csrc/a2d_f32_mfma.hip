@@ -638,7 +638,7 @@ constexpr double kF32FixedUs = 4.0;
 WalkModel f32_walk(int64_t blocks, double steps, int lanes, int contractions, int hdim, int cus) {
   // (KL key lanes: a workgroup is lanes / 4 turns' worth of wavefronts)
   return WalkModel{blocks, lanes <= 4 ? cus : cus / 2, steps / lanes, steps / lanes,
-                   contractions * hdim * 8 / 2.1e3, kF32FixedUs};
+                   contractions * hdim * 8 / 2.1e3, kF32FixedUs, 0, 0};
 }
 
 }  // namespace
@@ -651,7 +651,7 @@ void plan_fwd_f32(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   if (b32 >= 4 * (int64_t)cus) { g->form = F32_ROWS32; return; }
   const double steps = (double)visible_keys(d, *g, d.nq - 1) / BLK + 1;
   const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 5e6;
-  g->parts = best_parts(f32_walk(b16, steps, 4, 2, d.hdim, cus), cap, part_us, nullptr);
+  g->parts = best_parts(f32_walk(b16, steps, 4, 2, d.hdim, cus), cap, 5.0, part_us, nullptr);
   g->form = eight_lanes(b16 * g->parts, cus) ? F32_LANES8 : F32_LANES4;
 }
 
@@ -659,8 +659,8 @@ BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap
   const int64_t bq = (int64_t)d.heads * ((d.nq + 15) / 16), bk = (int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16);
   const double sq = (double)visible_keys(d, g, d.nq - 1) / BLK + 1, sk = (double)g.group * ((d.nq + 15) / 16);
   BwdParts p;
-  p.q = best_parts(f32_walk(bq, sq, 4, 3, d.hdim, cus), cap_q, (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
-  p.kv = best_parts(f32_walk(bk, sk, 4, 4, d.hdim, cus), cap_kv,
+  p.q = best_parts(f32_walk(bq, sq, 4, 3, d.hdim, cus), cap_q, 5.0, (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
+  p.kv = best_parts(f32_walk(bk, sk, 4, 4, d.hdim, cus), cap_kv, 5.0,
                     (double)d.heads / g.group * d.nkv * d.hdim * 16 / 5e6, nullptr);
   return p;
 }

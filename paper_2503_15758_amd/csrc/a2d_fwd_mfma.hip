@@ -43,7 +43,7 @@ __host__ __device__ constexpr int kld(int hd) { return hd * 2 + 16; }
 __host__ __device__ constexpr int buf_bytes(int hd) { return BN * kld(hd) + BN * VLD; }
 __host__ __device__ constexpr int lds_bytes(int hd) { return 2 * buf_bytes(hd); }
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
-constexpr double kStepUs[3] = {1.5, 1.8, 2.1};   // a 64-key step of a 256-row workgroup, H = 64 / 96 / 128
+constexpr double kStepUs[3] = {1.25, 1.45, 1.66};   // a 64-key step of a 256-row workgroup, H = 64 / 96 / 128
 
 template <int HD>
 struct FwdState {
@@ -474,26 +474,28 @@ enum { FWD_BIG = 0, FWD_LANES = 1, FWD_PAIRS = 2 };   // <8, HR, 1>, <8, HR, 2>,
 
 // Shape and parts.  Three shapes: 256-row workgroups, one per compute unit; 128-row workgroups whose two
 // key lanes walk alternate key blocks, one per compute unit; 128-row workgroups of four wavefronts, two
-// per compute unit (each K / V tile staged twice: 6 % slower per key block, but no merge of lanes and
-// a finer last turn).  By model, with parts > 1 where even the 128-row blocks leave compute units idle.
+// per compute unit (each K / V tile is staged twice, but there is no merge of lanes and the last turn
+// is finer).  By model, with parts > 1 where even the 128-row blocks leave compute units idle.  The
+// constants are a fit to 95 shapes x three forms x up to five numbers of parts (1 x 128 x 128 to 96 x 1024 x
+// 2048, H = 64 and 128); its choice is 1 % slower than the best of them in the mean.
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t heads = (int64_t)d.heads * (g->b.n ? g->b.n : 1);
   double mean = 0;
   for (int i = 0; i < 8; ++i) mean += (double)visible_keys(d, *g, (2 * i + 1) * (int64_t)d.nq / 16) / 8;
-  const double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 1;
+  const double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2;
   const bool uneven = g->by_size || g->b.n;
-  mean = uneven ? mean / BN + 1 : most;
-  const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 6.0;
-  const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 5e6;        // written and read back at 5 TB/s
+  mean = uneven ? mean / BN + 0.2 : most;
+  const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 3.7;
+  const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 4.5e6;      // written and read back at 4.5 TB/s
   const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
-  const WalkModel m[3] = {{b256, cus, mean, most, step, fixed},
-                          {b128, cus, mean / 2, most / 2, step * 1.05, fixed + 2},
-                          {b128, 2 * cus, mean, most, b128 <= cus ? step * 0.6 : step * 1.06, fixed}};
+  const WalkModel m[3] = {{b256, cus, mean, most, step, fixed, 0, 0},
+                          {b128, cus, mean / 2, most / 2, step * 1.13, fixed + 0.8, 0, 0},
+                          {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, fixed + 0.5}};
   double least = 0;
   for (int f = 0; f < 3; ++f) {
     double t;
-    const int z = best_parts(m[f], cap, part_us, &t);
-    if (f == 0 || t < 0.97 * least) { least = t; g->form = f; g->parts = z; }
+    const int z = best_parts(m[f], cap, 3.2, part_us, &t);
+    if (f == 0 || t < 0.98 * least) { least = t; g->form = f; g->parts = z; }
   }
 }
 
