@@ -46,11 +46,13 @@ def tile_flops(w, nq, nkv, causal_diag):
 def call_kernels(call, w, recompute):
     """The library kernels one call of the step launches, in launch order."""
     if call.startswith("partial_fwd"):
-        return ["fwd_mfma_kernel" if w.dtype == "bf16" else "fwd_generic_kernel"]
+        return ["fwd_mfma_kernel" if w.dtype == "bf16" else "fwd_f32_kernel"]
     if call.startswith("partial_bwd"):
         if w.dtype != "bf16":
-            return ["delta_kernel", "bwd_dkdv_generic_kernel", "bwd_dq_generic_kernel"]
-        return ["delta_kernel", "bwd_dkdv_kernel", "bwd_dq_kernel" if recompute else "bwd_dq_ds_kernel"]
+            return ["bwd_dq_f32_kernel", "bwd_dkdv_f32_kernel"]
+        if recompute:
+            return ["bwd_dq_kernel", "bwd_dkdv_kernel"]
+        return ["delta_kernel", "bwd_dkdv_kernel", "bwd_dq_ds_kernel"]
     if call == "fix":
         return ["fix_kernel"]
     if call.startswith("fix_bwd"):

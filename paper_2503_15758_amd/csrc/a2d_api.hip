@@ -296,11 +296,11 @@ a2d_status partial_bwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
       a2d::trace_mark(s);
       A2D_TRY(hip_result(a2d::launch_bwd_f32(dd, go, Q, K, V, O, dO, lse, delta, dq, dk, dv, parts, s), who));
     } else {
-      A2D_TRY(hip_result(a2d::launch_bwd_mfma(a2d::PREPARE, dd, go, Q, K, V, dO, lse, delta, dq, dk, dv, ds_ws, parts, s),
+      A2D_TRY(hip_result(a2d::launch_bwd_mfma(a2d::PREPARE, dd, go, Q, K, V, O, dO, lse, delta, dq, dk, dv, ds_ws, parts, s),
                          who));
       a2d::trace_mark(s);
-      A2D_TRY(hip_result(a2d::launch_delta(dd, O, dO, delta, s), who));
-      A2D_TRY(hip_result(a2d::launch_bwd_mfma(a2d::LAUNCH, dd, go, Q, K, V, dO, lse, delta, dq, dk, dv, ds_ws, parts, s),
+      if (ds_ws) A2D_TRY(hip_result(a2d::launch_delta(dd, O, dO, delta, s), who));
+      A2D_TRY(hip_result(a2d::launch_bwd_mfma(a2d::LAUNCH, dd, go, Q, K, V, O, dO, lse, delta, dq, dk, dv, ds_ws, parts, s),
                          who));
     }
     a2d::PartSet sets[3];

@@ -22,7 +22,8 @@
 //                    wavefront, Q and dO fragments in registers), two wavefronts per
 //                    SIMD; walks the key blocks, 64 keys per step.  S^T = K Q^T
 //                    and dP^T = V dO^T leave a lane holding ONE query column;
-//                    dQ^T += K^T dS^T with K^T from the LDS transpose read.
+//                    dQ^T += K^T dS^T with K^T from the LDS transpose read.  Runs first and
+//                    computes delta = rowsum(dO o O) of its rows for both kernels.
 //   bwd_dq_ds_kernel owns query rows like bwd_dq_kernel, but reads dS from a workspace the
 //                    dK/dV kernel filled (its WRITE_DS variant) and only contracts it with K:
 //                    used when the caller's workspace is large enough, so that S and dP are
@@ -70,17 +71,13 @@ __device__ __forceinline__ bf16x8 dual_nat(const DualAddr& a, int extra) {
   return lds_load_b128(((X & 1) ? a.nat_o : a.nat_e) + 64 * (X >> 1) + extra);
 }
 
-// steps of the walks for the split model: 32 query rows against 128 keys; 64 keys against 128
-// query rows in each of two lanes, recomputing and from dS
-constexpr double kKvStepUs = 0.9, kDqStepUs = 1.8, kDsqStepUs = 0.9;
-
 // ------------------------------------------------------------------ dK, dV
 constexpr int DK_THREADS = 512;
 constexpr int DK_KEYS = 128;      // keys per workgroup
 constexpr int BQ = 32;            // query rows per step
 constexpr int DK_NBUF = 4;        // tile buffers: gradient waves' step, score waves' step, next, incoming
 // LDS: [buf]{ Q tile, dO tile } (dual layout, 32 rows each) | [buf]{ lse*log2e [32], delta [32] } |
-//      [slot][pair] probabilities handed from the score wave to the gradient wave (fp32)
+//      (the latter negated) | [slot][pair] probabilities handed from the score wave to the gradient wave (fp32)
 constexpr int DK_TILE = BQ * DUAL_LD;
 constexpr int DK_BUF = 2 * DK_TILE;
 constexpr int DK_STAT = DK_NBUF * DK_BUF;
@@ -122,21 +119,25 @@ __device__ __forceinline__ void dk_first_pre(const DkCtx<HD>& cx, bf16x8 (&n)[4]
   n[0] = A2D_NAT(0); n[1] = A2D_NAT(1); n[2] = A2D_NAT(2); n[3] = A2D_NAT(3);
   A2D_FENCE
 }
-// `init` is the starting value of the sum (zero for S, -delta for dP - delta).  Two accumulators
-// (even / odd 16-wide slices of H): an MFMA that accumulates onto the result of the one issued
-// just before it would wait for that result.
+// `init` is the starting value of the sum (zero for S, -delta for dP - delta).  One chain (an MFMA
+// accumulates onto the result of the one issued just before it without waiting: 33 cycles apart, as
+// independent ones): adding up two costs 4-7 % of the call at H = 64 to 96; at H = 128 the two
+// chains measured up to 2 % faster.
 // KS: the slices that hold data (a head size of 80 fills five of the padded six)
 template <int HD, int KS = HD / 16>
 __device__ __forceinline__ f32x16 dk_first(const DkCtx<HD>& cx, bf16x8 (&n)[4], f32x16 init) {
-  f32x16 sa = init, sb = zero16();
+  constexpr bool TWO = HD == 128;
+  f32x16 s = init, s2 = zero16();
   static_for<0, KS>([&](auto X) {
     constexpr int x = decltype(X)::value;
-    if constexpr (x & 1) sb = mma(n[x & 3], cx.frag[x], sb); else sa = mma(n[x & 3], cx.frag[x], sa);
+    if constexpr (TWO && (x & 1)) s2 = mma(n[x & 3], cx.frag[x], s2); else s = mma(n[x & 3], cx.frag[x], s);
     if constexpr (x + 4 < KS) { n[x & 3] = A2D_NAT(x + 4); A2D_FENCE }
   });
+  if constexpr (TWO) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) sa[r] += sb[r];
-  return sa;
+    for (int r = 0; r < 16; ++r) s[r] += s2[r];
+  }
+  return s;
 }
 
 // The 32 per-query statistics of the step (lse for the score wave, delta for the gradient wave)
@@ -334,7 +335,6 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
       else cx.frag[x] = bf16x8{};                              // columns past the head size are zero
     }
   }
-  wait_vmem_all();
 #pragma unroll
   for (int t = 0; t < CT; ++t) cx.acc[t] = zero16();
 
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
     if (tid < 2 * BQ) {
       float v = stat[SET];
       if (tid < BQ) v = (!stat_ok[SET] || v == -INFINITY) ? INFINITY : v * kLog2e;
-      else v = stat_ok[SET] ? v : 0.f;
+      else v = stat_ok[SET] ? -v : 0.f;                        // -delta: where the sum of dP starts
       reinterpret_cast<float*>(lds + DK_STAT + buf * DK_STAT_BUF)[tid] = v;
     }
   };
@@ -485,6 +485,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
 
   if (nsteps > 0) {
     load_step(0, set0{}); load_step(1, set1{});
+    wait_vmem_all();                                 // (the K / V rows and the first steps together)
     store_step(0, set0{}); store_step(1, set1{});
     load_step(2, set0{}); load_step(3, set1{});
   }
@@ -600,7 +601,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
         dk_stat_pre(cx, st);
         f32x16 init;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) init[r] = -st[r >> 2][r & 3];
+        for (int r = 0; r < 16; ++r) init[r] = st[r >> 2][r & 3];
         dp = dk_first<HD, KSR>(cx, n, init);
       }
       __syncthreads();
@@ -625,7 +626,8 @@ __host__ __device__ constexpr int vt_ld(int hd) { return hd * 2 + 16; }
 constexpr int DQ_VT = DUAL64_BYTES;
 __host__ __device__ constexpr int dq_buf(int hd) { return DUAL64_BYTES + BKS * vt_ld(hd); }
 __host__ __device__ constexpr int dq_lds(int hd) { return 2 * dq_buf(hd); }
-constexpr int DQ_RING = 2;        // fragment ring depth (registers are tight: 256 per wavefront)
+// fragment ring depth (registers are tight above H = 64: 256 per wavefront)
+__host__ __device__ constexpr int dq_ring(int hd) { return hd == 64 ? 4 : 2; }
 
 template <int HD>
 struct DqCtx {
@@ -644,7 +646,7 @@ struct DqCtx {
 // (KS: the slices that hold data - a head size of 80 fills five of the padded six)
 template <int T, bool MASK, int HD, int KS = HD / 16>
 __device__ __forceinline__ void dq_piece(DqCtx<HD>& cx, int key0) {
-  constexpr int CT = HD / 32, VT_LD = vt_ld(HD);
+  constexpr int CT = HD / 32, VT_LD = vt_ld(HD), DQ_RING = dq_ring(HD);
   constexpr int RB = T * 32 * DUAL_LD;
   constexpr int VB = T * 32 * VT_LD;
   bf16x8 kr[DQ_RING], vr[DQ_RING], kt[DQ_RING];
@@ -699,8 +701,8 @@ __device__ __forceinline__ void dq_piece(DqCtx<HD>& cx, int key0) {
 template <int WAVES, int HR, int KL>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
-    const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO, const float* __restrict__ lse,
-    const float* __restrict__ delta, float* __restrict__ dQ) {
+    const bf16_t* __restrict__ V, const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO,
+    const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dQ) {
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
   constexpr int RW = WAVES / KL;           // wavefronts of one key lane
   constexpr int DQ_ROWS = 32 * RW;         // query rows per workgroup
@@ -725,6 +727,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31;
   Q += (int64_t)head * d.lq.head;
+  O += (int64_t)head * d.lo.head;
   dO += (int64_t)head * d.ldo.head;
   K += (int64_t)kvh * d.lk.head;
   V += (int64_t)kvh * d.lv.head;
@@ -747,11 +750,15 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
         cx.gf[x] = bf16x8{};
       }
     }
-    const float v = lse[(int64_t)head * d.nq + q_ld];
-    cx.lse2 = (!q_ok || v == -INFINITY) ? INFINITY : v * kLog2e;    // +inf: exp2(s - lse2) = 0
-    cx.del = delta[(int64_t)head * d.nq + q_ld];
   }
-  wait_vmem_all();
+  const float lse_i = lse[(int64_t)head * d.nq + q_ld];
+  // delta = rowsum(dO o O) of the wavefront's rows, left for the dK/dV kernel, which runs after this one
+  bf16x8 of[KS];
+#pragma unroll
+  for (int x = 0; x < KS; ++x) {
+    if (16 * x < H) of[x] = *reinterpret_cast<const bf16x8*>(O + (int64_t)q_ld * d.lo.row + 8 * cx.half + 16 * x);
+    else of[x] = bf16x8{};
+  }
 
   // visibility per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
   auto vis_count = [&](int i, int s) -> int {
@@ -841,7 +848,27 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   if (sb < g.n) {
     enter_segment(sb);
     nx_start = g.start[sb]; nx_rows = g.rows[sb];
-    load_half(nx_start, nx_rows, j, 0); store_half(0, 0);
+    load_half(nx_start, nx_rows, j, 0);
+  }
+  wait_vmem_all();                                 // (the rows of Q, dO, O and the first half together)
+  cx.lse2 = (!q_ok || lse_i == -INFINITY) ? INFINITY : lse_i * kLog2e;      // +inf: exp2(s - lse2) = 0
+  {
+    // (the order of sums of delta_kernel, so that both dQ paths give the same dK, dV: 16-byte chunks,
+    // then chunks 1, 2, 4, 8 apart; this lane holds the chunks 2 x + half)
+    float t[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      t[x] = 0.f;
+      if (x >= KS) continue;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t[x] = fmaf((float)of[x][e], (float)cx.gf[x][e], t[x]);
+      t[x] += __shfl_xor(t[x], 32, 64);
+    }
+    cx.del = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+  }
+  if (part == 0 && kl == 0 && cx.half == 0 && q_ok) delta[(int64_t)head * d.nq + q_row] = cx.del;
+  if (sb < g.n) {
+    store_half(0, 0);
     load_half(nx_start, nx_rows, j, 1); store_half(0, 1);
   }
   __syncthreads();
@@ -1166,24 +1193,21 @@ size_t bwd_ds_bytes(const a2d_tile_desc& d, const SegList& g) {
 }
 
 namespace {
+enum { DQ_BIG = 0, DQ_LANES = 1, DQ_PAIRS = 2 };   // <8, HR, 1>, <8, HR, 2>, <4, HR, 1>
+
 template <int HR, bool BATCH>
 hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                          const void* V, const void* dO, const float* lse, const float* delta, float* dQ, float* dK,
                          float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
   constexpr int DSQ_LDS = 2 * DUAL64_BYTES;
   const bool grouped = g.group > 1;
-  int cus = 0;
-  hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
   const int tiles = g.b.n ? g.b.n : 1;
   SegList gk = g, gq = g;
   gk.parts = parts.kv;
   gq.parts = parts.q;
   if (parts.q > 1) gq.acc = 0;                         // (the sum over the parts adds)
-  const int64_t heads = (int64_t)d.heads * tiles * parts.q;
-  const bool big = heads * ((d.nq + 255) / 256) >= cus;
-  // the dQ kernel walks the keys in two lanes when at most one 128-row block comes to a compute unit
-  const bool lanes = !big && heads * ((d.nq + 127) / 128) <= cus;
+  const bool big = parts.form == DQ_BIG, lanes = parts.form == DQ_LANES;
   if (ph == PREPARE) {
     e = ensure_dynamic_lds(grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, true, false, BATCH>)
                                    : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, true, false, BATCH>), DK_LDS);
@@ -1219,7 +1243,7 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 
 template <int HR>
 hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
-                         const void* V, const void* dO, const float* lse, const float* delta, float* dQ, float* dK,
+                         const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK,
                          float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
   if (ds_ws && g.b.n) return bwd_launch_ds<HR, true>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
   if (ds_ws) return bwd_launch_ds<HR, false>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
@@ -1227,18 +1251,12 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   const bool grouped = g.group > 1;
   // Q and dO in the plain layout: the variant with compile-time staging offsets
   const bool plain = d.lq.row == HR && d.ldo.row == HR && d.lq.head == (int64_t)d.nq * HR && d.ldo.head == d.lq.head;
-  // dQ kernel: 256-row workgroups unless that leaves compute units without a workgroup
-  int cus = 0;
-  hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
   SegList gk = g, gq = g;
   gk.parts = parts.kv;
   gq.parts = parts.q;
   if (parts.q > 1) gq.acc = 0;                         // (the sum over the parts adds)
-  const int64_t heads = (int64_t)d.heads * parts.q;
-  const bool big = heads * ((d.nq + 255) / 256) >= cus;
-  // two key lanes when at most one 128-row block comes to a compute unit
-  const bool lanes = !big && heads * ((d.nq + 127) / 128) <= cus;
+  const bool big = parts.form == DQ_BIG, lanes = parts.form == DQ_LANES;
+  hipError_t e = hipSuccess;
   if (ph == PREPARE) {
     const void* dkdv = plain ? (grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, false, true>)
                                         : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, false, true>))
@@ -1253,6 +1271,17 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   dim3 grid_kv(xcd_grid(d.heads / g.group * parts.kv, (d.nkv + DK_KEYS - 1) / DK_KEYS));
   const int dq_rows = big ? 256 : 128;
   dim3 grid_q(xcd_grid(d.heads / g.group * parts.q, g.group * ((d.nq + dq_rows - 1) / dq_rows)));
+  if (big)
+    A2D_LAUNCH((bwd_dq_kernel<8, HR, 1>), grid_q, dim3(512), DQ_LDS, s, d, gq, (const bf16_t*)Q,
+                       (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ);
+  else if (lanes)
+    A2D_LAUNCH((bwd_dq_kernel<8, HR, 2>), grid_q, dim3(512), 2 * DQ_LDS, s, d, gq, (const bf16_t*)Q,
+                       (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ);
+  else
+    A2D_LAUNCH((bwd_dq_kernel<4, HR, 1>), grid_q, dim3(256), DQ_LDS, s, d, gq, (const bf16_t*)Q,
+                       (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
 #define A2D_DKDV(GR, PL)                                                                                          \
   A2D_LAUNCH((bwd_dkdv_kernel<HR, GR, false, PL>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk, (const bf16_t*)Q, \
                      (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV, (bf16_t*)nullptr)
@@ -1261,46 +1290,51 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   else if (plain) A2D_DKDV(false, true);
   else A2D_DKDV(false, false);
 #undef A2D_DKDV
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (big)
-    A2D_LAUNCH((bwd_dq_kernel<8, HR, 1>), grid_q, dim3(512), DQ_LDS, s, d, gq, (const bf16_t*)Q,
-                       (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dQ);
-  else if (lanes)
-    A2D_LAUNCH((bwd_dq_kernel<8, HR, 2>), grid_q, dim3(512), 2 * DQ_LDS, s, d, gq, (const bf16_t*)Q,
-                       (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dQ);
-  else
-    A2D_LAUNCH((bwd_dq_kernel<4, HR, 1>), grid_q, dim3(256), DQ_LDS, s, d, gq, (const bf16_t*)Q,
-                       (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dQ);
   return hipGetLastError();
 }
 }  // namespace
 
-// Parts of the dK/dV and dQ walks where their row blocks leave compute units idle (see WalkModel).
-// The choice for dK/dV does not depend on `ds`, nor either choice on the grouping alone, so that
-// the two dQ paths give the same dK, dV.
+// Parts of the dK/dV and dQ walks where their row blocks leave compute units idle, and the dQ kernels'
+// workgroup shape, as in plan_fwd_mfma.  Steps in microseconds, measured over 30 shapes (1 x 300 x 8000
+// to 32 x 2000 x 2700): 32 query rows against 128 keys; 64 keys against 256 query rows, recomputing
+// and from dS; H = 64, 96, 128.  The choice for dK/dV does not depend on `ds`, so that the two dQ
+// paths give the same dK, dV.
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q) {
-  const int kv_heads = d.heads / g.group;
+  constexpr double kKvUs[3] = {0.75, 0.87, 0.9}, kDqUs[3] = {1.6, 1.75, 2.1}, kDsqUs[3] = {0.7, 0.8, 0.85};
+  const int hx = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, kv_heads = d.heads / g.group, tiles = g.b.n ? g.b.n : 1;
+  const bool uneven = g.by_size || g.b.n;
+  const double seen = mean_visible_keys(d, g);
   BwdParts p;
   const double rows = (double)g.group * ((d.nq + BQ - 1) / BQ);
-  const WalkModel kv = {(int64_t)kv_heads * ((d.nkv + DK_KEYS - 1) / DK_KEYS), cus, rows, rows, kKvStepUs, 8.0, 0, 0};
-  p.kv = best_parts(kv, cap_kv, 5.0, (double)kv_heads * d.nkv * d.hdim * 16 / 5e6, nullptr);
-  const double keys = (double)visible_keys(d, g, d.nq - 1) / BKS + 1;
-  const int64_t b128 = (int64_t)d.heads * ((d.nq + 127) / 128);
-  const WalkModel q = {b128, cus, keys / 2, keys / 2, ds ? kDsqStepUs : kDqStepUs, 6.0, 0, 0};
-  p.q = best_parts(q, cap_q, 5.0, (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
+  const WalkModel kv = {(int64_t)kv_heads * tiles * ((d.nkv + DK_KEYS - 1) / DK_KEYS), cus,
+                        uneven ? rows * seen / d.nkv + 1 : rows, rows, kKvUs[hx], 8.0, 0, 0};
+  p.kv = best_parts(kv, cap_kv, 4.0, (double)kv_heads * d.nkv * d.hdim * 16 / 4.5e6, nullptr);
+  const double most = (double)visible_keys(d, g, d.nq - 1) / BKS + 0.2, mean = uneven ? seen / BKS + 0.2 : most;
+  const double step = ds ? kDsqUs[hx] : kDqUs[hx], fixed = 7.0;
+  const double part_us = (double)d.heads * d.nq * d.hdim * 8 / 4.5e6;
+  const int64_t heads = (int64_t)d.heads * tiles, b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
+  const WalkModel q[3] = {{b256, cus, mean, most, step, fixed, 0, 0},
+                          {b128, cus, mean / 2, most / 2, step * 1.17, fixed + 0.5, 0, 0},
+                          {b128, cus, mean, most, step * 0.8, fixed, step * 1.06, fixed + 0.5}};
+  double least = 0;
+  for (int f = 0; f < 3; ++f) {
+    double t;
+    const int z = best_parts(q[f], cap_q, p.kv > 1 ? 1.0 : 4.0, part_us, &t);   // (one launch sums both)
+    if (f == 0 || t < (p.form == 0 ? 0.98 : 1.0) * least) { least = t; p.form = f; p.q = z; }
+  }
   return p;
 }
 
 // ds_ws != NULL: a workspace of bwd_ds_bytes(d, g) bytes; the dK/dV kernel leaves dS there and the
-// dQ kernel is the contraction-only one.
+// dQ kernel is the contraction-only one; `delta` holds rowsum(dO o O) then.  Otherwise the dQ kernel
+// runs first and computes delta from O for itself and the dK/dV kernel (a launch less).
 hipError_t launch_bwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
-                           const void* V, const void* dO, const float* lse, const float* delta, float* dQ,
+                           const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ,
                            float* dK, float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
-  if (d.hdim == 128) return bwd_launch_hd<128>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
-  if (d.hdim == 96) return bwd_launch_hd<96>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
-  if (d.hdim == 80) return bwd_launch_hd<80>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
-  return bwd_launch_hd<64>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+  if (d.hdim == 128) return bwd_launch_hd<128>(ph, d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+  if (d.hdim == 96) return bwd_launch_hd<96>(ph, d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+  if (d.hdim == 80) return bwd_launch_hd<80>(ph, d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+  return bwd_launch_hd<64>(ph, d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
 }
 
 }  // namespace a2d

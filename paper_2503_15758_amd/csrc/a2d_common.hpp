@@ -185,6 +185,7 @@ inline double walk_time(const WalkModel& w, int parts) {
 int best_parts(const WalkModel& w, int cap, double merge_us, double part_us, double* time);
 // keys that query row i of the tile sees
 int64_t visible_keys(const a2d_tile_desc& d, const SegList& g, int64_t i);
+double mean_visible_keys(const a2d_tile_desc& d, const SegList& g);     // over the rows (sampled)
 
 // ---- launchers (none synchronises) ----
 // Every tile launcher runs in two phases so that a call can finish everything that may fail on the
@@ -202,9 +203,9 @@ struct FwdInput {
 hipError_t plan_fwd(const a2d_tile_desc& d, SegList* g, bool may_split);
 void plan_fwd_f32(const a2d_tile_desc& d, SegList* g, int cus, int cap);
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap);
-// Parts of the two kernels of a backward tile, each at most its cap
+// Parts of the two kernels of a backward tile, each at most its cap, and the dQ kernel's workgroup shape
 struct BwdParts {
-  int kv, q;
+  int kv, q, form;
 };
 BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q);
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q);
@@ -238,7 +239,7 @@ bool bwd_mfma_supported(const a2d_tile_desc& d);
 size_t bwd_ds_bytes(const a2d_tile_desc& d, const SegList& g);
 // (parts > 1: the outputs are the partial buffers, [parts][heads][rows][H] each)
 hipError_t launch_bwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
-                           const void* V, const void* dO, const float* lse, const float* delta, float* dQ,
+                           const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ,
                            float* dK, float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s);
 
 struct FixPtrs {

@@ -265,8 +265,6 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
       for (int t = 0; t < CT; ++t) st.o[t] = zero16();       // rows beyond nq: nothing to continue
     }
   }
-  wait_vmem_all();
-  st.m_lane = st.m_ref = m_in / d.scale;               // -inf stays -inf
 
   // ---- visibility, per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
   // (key kk of the sub-block iff kk <= i + rel[s])
@@ -360,8 +358,11 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     enter_segment(sb);
     nx_start = g.start[sb]; nx_rows = g.rows[sb];
     load_tile(nx_start, nx_rows, j);
-    store_tile(0);
   }
+  // (one wait for the Q rows and the first tile: the two latencies overlap)
+  wait_vmem_all();
+  st.m_lane = st.m_ref = m_in / d.scale;               // -inf stays -inf
+  if (sb < g.n) store_tile(0);
   __syncthreads();
 
   int boff = 0;
@@ -480,11 +481,9 @@ enum { FWD_BIG = 0, FWD_LANES = 1, FWD_PAIRS = 2 };   // <8, HR, 1>, <8, HR, 2>,
 // 2048, H = 64 and 128); its choice is 1 % slower than the best of them in the mean.
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t heads = (int64_t)d.heads * (g->b.n ? g->b.n : 1);
-  double mean = 0;
-  for (int i = 0; i < 8; ++i) mean += (double)visible_keys(d, *g, (2 * i + 1) * (int64_t)d.nq / 16) / 8;
   const double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2;
   const bool uneven = g->by_size || g->b.n;
-  mean = uneven ? mean / BN + 0.2 : most;
+  const double mean = uneven ? mean_visible_keys(d, *g) / BN + 0.2 : most;
   const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 3.7;
   const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 4.5e6;      // written and read back at 4.5 TB/s
   const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
@@ -495,7 +494,7 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   for (int f = 0; f < 3; ++f) {
     double t;
     const int z = best_parts(m[f], cap, 3.2, part_us, &t);
-    if (f == 0 || t < 0.98 * least) { least = t; g->form = f; g->parts = z; }
+    if (f == 0 || t < (g->form == 0 ? 0.98 : 1.0) * least) { least = t; g->form = f; g->parts = z; }
   }
 }
 

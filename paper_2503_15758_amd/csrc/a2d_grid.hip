@@ -149,6 +149,9 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
   const size_t parts = slots * rows * p.hdim * (p.heads + 2 * (size_t)p.kv_heads) * sizeof(float);
   void* ds = w + 2 * stat + up256(parts);
   const int chunk = chunk_of(p, d, g), total = slots_of(p);
+  int cus = 0;
+  const hipError_t dev = device_cus(&cus);
+  if (dev != hipSuccess) return dev;
   for (int pass = 0; pass < 2; ++pass) {                       // everything that can fail on the host first
     if (pass == 1) {
       trace_mark(s);
@@ -159,8 +162,8 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
     for (int t = 0; t < total; t += chunk) {                   // Alg. 3 line 3, every tile
       g.b.first = t;
       g.b.n = total - t < chunk ? total - t : chunk;
-      const hipError_t e = launch_bwd_mfma(pass == 0 ? PREPARE : LAUNCH, d, g, Q, K, V, dO, lse_blk, delta, dq, dk, dv,
-                                           ds, BwdParts{1, 1}, s);
+      const hipError_t e = launch_bwd_mfma(pass == 0 ? PREPARE : LAUNCH, d, g, Q, K, V, O, dO, lse_blk, delta, dq, dk, dv,
+                                           ds, plan_bwd_mfma(d, g, true, cus, 1, 1), s);
       if (e != hipSuccess) return e;
     }
   }
