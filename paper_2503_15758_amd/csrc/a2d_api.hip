@@ -111,9 +111,10 @@ a2d::SegList one_segment(const a2d_tile_desc* d) {
   g.n = 1;
   g.group = 1;
   g.parts = 1;
-  g.start[0] = 0;
-  g.rows[0] = d->nkv;
-  g.rel[0] = d->q_off - d->kv_off;
+  g.b.slots = 1;
+  g.seg[0].start = 0;
+  g.seg[0].rows = d->nkv;
+  g.seg[0].rel = d->q_off - d->kv_off;
   return g;
 }
 
@@ -126,15 +127,16 @@ a2d_status make_segments(const a2d_tile_desc* d, int nseg, const a2d_kv_segment*
   g->n = nseg;
   g->group = 1;
   g->parts = 1;
+  g->b.slots = 1;
   int64_t total = 0;
   for (int s = 0; s < nseg; ++s) {
     if (segs[s].rows < 1 || segs[s].pad != 0)
       return fail(A2D_ERR_INVALID_ARG, "%s: segs[%d]: rows=%d must be >= 1 and pad 0", who, s, segs[s].rows);
     if (segs[s].kv_off < -((int64_t)1 << 60) || segs[s].kv_off > ((int64_t)1 << 60))
       return fail(A2D_ERR_INVALID_ARG, "%s: segs[%d].kv_off out of range", who, s);
-    g->start[s] = (int)total;
-    g->rows[s] = segs[s].rows;
-    g->rel[s] = d->q_off - segs[s].kv_off;
+    g->seg[s].start = (int)total;
+    g->seg[s].rows = segs[s].rows;
+    g->seg[s].rel = d->q_off - segs[s].kv_off;
     total += segs[s].rows;
     if (total > d->nkv) break;
   }
@@ -152,8 +154,8 @@ a2d_status make_segments(const a2d_tile_desc* d, int nseg, const a2d_kv_segment*
 int blocks_differ(const a2d_tile_desc* d, const a2d::SegList& g) {
   if (!d->causal) return 0;
   auto vis = [&](int64_t i, int s) -> int64_t {
-    const int64_t v = i + g.rel[s] + 1;
-    return v <= 0 ? 0 : (v < g.rows[s] ? v : g.rows[s]);
+    const int64_t v = i + g.seg[s].rel + 1;
+    return v <= 0 ? 0 : (v < g.seg[s].rows ? v : g.seg[s].rows);
   };
   int64_t first = 0, last = 0;
   for (int s = 0; s < g.n; ++s) { first += vis(0, s); last += vis(d->nq - 1, s); }

@@ -281,6 +281,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
     const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO, const float* __restrict__ lse,
     const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV,
     bf16_t* __restrict__ dS) {
+  warm_arguments<9 * 8>();
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   int head, blk;
@@ -297,7 +298,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   const int part = unit - head * g.parts;
   const int qh0 = GROUPED ? head * g.group : head;           // the first query head, as a head of Q
   {
-    const int64_t first = (int64_t)part * (GROUPED ? d.heads / g.group : d.heads) * d.nkv * HR;
+    const int64_t first = (int64_t)part * g.b.slots * (GROUPED ? d.heads / g.group : d.heads) * d.nkv * HR;
     dK += first;
     dV += first;
   }
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   // Query i sees key kk of key/value sub-block s iff i >= kk - rel[s].  seg_first_row(sb, r): first
   // local query row that sees local key r of sub-block sb (nq if none does).
   auto seg_first_row = [&](int sb, int r) -> int {
-    const int64_t f = (int64_t)(r - g.start[sb]) - g.rel[sb] - tp.rel;
+    const int64_t f = (int64_t)(r - g.seg[sb].start) - g.seg[sb].rel - tp.rel;
     return f <= 0 ? 0 : (f >= d.nq ? d.nq : (int)f);
   };
   // smallest / largest such row over the local keys a .. b - 1 (inside a sub-block it grows with
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
     lo = d.nq; hi = 0;
     if (!d.causal) { lo = 0; return; }
     for (int sb = 0; sb < g.n; ++sb) {
-      const int x = max(a, g.start[sb]), y = min(b, g.start[sb] + g.rows[sb]);
+      const int x = max(a, g.seg[sb].start), y = min(b, g.seg[sb].start + g.seg[sb].rows);
       if (x >= y) continue;
       lo = min(lo, seg_first_row(sb, x));
       hi = max(hi, seg_first_row(sb, y - 1));
@@ -382,7 +383,7 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
     cx.my_first = 0;
     if (d.causal) {
       for (int sb = 0; sb < g.n; ++sb)                        // uniform loop, per-lane select
-        if (key >= g.start[sb] && key < g.start[sb] + g.rows[sb]) cx.my_first = seg_first_row(sb, key);
+        if (key >= g.seg[sb].start && key < g.seg[sb].start + g.seg[sb].rows) cx.my_first = seg_first_row(sb, key);
     }
   }
   int w_any = d.nq, w_all = d.nq;   // rows below w_any see none of the pair's keys, rows from w_all on all
@@ -703,6 +704,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
     const bf16_t* __restrict__ V, const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO,
     const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dQ) {
+  warm_arguments<8 * 8>();
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
   constexpr int RW = WAVES / KL;           // wavefronts of one key lane
   constexpr int DQ_ROWS = 32 * RW;         // query rows per workgroup
@@ -762,9 +764,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
 
   // visibility per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
   auto vis_count = [&](int i, int s) -> int {
-    if (!d.causal) return g.rows[s];
-    const int64_t v = (int64_t)i + g.rel[s] + 1;
-    return v <= 0 ? 0 : (v < g.rows[s] ? (int)v : g.rows[s]);
+    if (!d.causal) return g.seg[s].rows;
+    const int64_t v = (int64_t)i + g.seg[s].rel + 1;
+    return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
   };
   const int blk_last = min(q0 + DQ_ROWS, d.nq) - 1;
   const int w_first = min(q0 + wave * 32, d.nq - 1);
@@ -847,7 +849,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   int nx_start = 0, nx_rows = 0;                   // start / rows of the next entry's sub-block
   if (sb < g.n) {
     enter_segment(sb);
-    nx_start = g.start[sb]; nx_rows = g.rows[sb];
+    nx_start = g.seg[sb].start; nx_rows = g.seg[sb].rows;
     load_half(nx_start, nx_rows, j, 0);
   }
   wait_vmem_all();                                 // (the rows of Q, dO, O and the first half together)
@@ -878,7 +880,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
     int nsb = sb, nj = j, nnblk = nblk;
     advance(stride, nsb, nj, nnblk);
     const bool more = nsb < g.n;
-    if (more && nsb != sb) { nx_start = g.start[nsb]; nx_rows = g.rows[nsb]; }
+    if (more && nsb != sb) { nx_start = g.seg[nsb].start; nx_rows = g.seg[nsb].rows; }
     const bool here = KL == 1 || sb < g.n;         // this lane has a block in this round
     const int k0 = j * BKS;                        // local to the sub-block
     if (more) load_half(nx_start, nx_rows, nj, 0);
@@ -982,6 +984,7 @@ template <int WAVES, int HR, int KL, bool BATCH>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ K, const bf16_t* __restrict__ dS,
     float* __restrict__ dQ) {
+  warm_arguments<3 * 8>();
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
   constexpr int RW = WAVES / KL;                       // wavefronts of one key lane
   constexpr int DQ_ROWS = 32 * RW, DQ_THREADS = 64 * RW;   // rows of the workgroup, threads of one key lane
@@ -1023,9 +1026,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 
   // visibility per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
   auto vis_count = [&](int i, int s) -> int {
-    if (!d.causal) return g.rows[s];
-    const int64_t v = (int64_t)i + g.rel[s] + tp.rel + 1;
-    return v <= 0 ? 0 : (v < g.rows[s] ? (int)v : g.rows[s]);
+    if (!d.causal) return g.seg[s].rows;
+    const int64_t v = (int64_t)i + g.seg[s].rel + tp.rel + 1;
+    return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
   };
   const int blk_last = min(q0 + DQ_ROWS, d.nq) - 1;
   const int w_first = min(q0 + wave * 32, d.nq - 1);
@@ -1048,7 +1051,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
       do { ++sb; } while (sb < g.n && (nblk = seg_blocks(sb)) == 0);
       if (sb >= g.n) return;
     }
-    f_id = g.start[sb] / BKS + j;
+    f_id = g.seg[sb].start / BKS + j;
     f_sb = sb; f_j = j; f_nblk = nblk;
   };
   int c_sb = -1, c_j = 0, c_nblk = 0;              // compute walker: sub-block, block inside it
@@ -1108,7 +1111,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 
   count = count > part * KL ? count - part * KL : 0;           // from this part's first block on
   if (count == 0) {                                // no visible key: dQ share is zero
-    if (q_ok && !g.acc && kl == 0) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, 0.f, H, false);
+    if (q_ok && !g.acc && kl == 0) store_acc_t<CT>(dQ + (((int64_t)part * g.b.slots * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, 0.f, H, false);
     return;
   }
   // (the first block is block 0; a lane without one re-reads the last block it passed)
@@ -1172,7 +1175,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) cx.dq[t][r] += xch[(16 * t + r) * 64];
   }
-  if (q_ok) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
+  if (q_ok) store_acc_t<CT>(dQ + (((int64_t)part * g.b.slots * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
 }
 
 }  // namespace
@@ -1186,7 +1189,7 @@ bool bwd_mfma_supported(const a2d_tile_desc& d) {
 size_t bwd_ds_bytes(const a2d_tile_desc& d, const SegList& g) {
   if (!bwd_mfma_supported(d)) return 0;
   for (int s = 0; s < g.n; ++s)
-    if (g.start[s] % 64 != 0) return 0;
+    if (g.seg[s].start % 64 != 0) return 0;
   const size_t per_head = ds_head_bytes(d.nq, d.nkv);
   if (per_head * (size_t)g.group >= ((size_t)1 << 32)) return 0;   // 32-bit offsets inside a key/value head's share
   return per_head * (size_t)d.heads;
@@ -1308,18 +1311,18 @@ BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cu
   const double rows = (double)g.group * ((d.nq + BQ - 1) / BQ);
   const WalkModel kv = {(int64_t)kv_heads * tiles * ((d.nkv + DK_KEYS - 1) / DK_KEYS), cus,
                         uneven ? rows * seen / d.nkv + 1 : rows, rows, kKvUs[hx], 8.0, 0, 0};
-  p.kv = best_parts(kv, cap_kv, 4.0, (double)kv_heads * d.nkv * d.hdim * 16 / 4.5e6, nullptr);
+  p.kv = best_parts(kv, cap_kv, g.b.n ? 0.0 : 4.0, (double)tiles * kv_heads * d.nkv * d.hdim * 16 / 4.5e6, nullptr);
   const double most = (double)visible_keys(d, g, d.nq - 1) / BKS + 0.2, mean = uneven ? seen / BKS + 0.2 : most;
   const double step = ds ? kDsqUs[hx] : kDqUs[hx], fixed = 7.0;
-  const double part_us = (double)d.heads * d.nq * d.hdim * 8 / 4.5e6;
   const int64_t heads = (int64_t)d.heads * tiles, b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
+  const double part_us = (double)heads * d.nq * d.hdim * 8 / 4.5e6;
   const WalkModel q[3] = {{b256, cus, mean, most, step, fixed, 0, 0},
                           {b128, cus, mean / 2, most / 2, step * 1.17, fixed + 0.5, 0, 0},
                           {b128, cus, mean, most, step * 0.8, fixed, step * 1.06, fixed + 0.5}};
   double least = 0;
   for (int f = 0; f < 3; ++f) {
     double t;
-    const int z = best_parts(q[f], cap_q, p.kv > 1 ? 1.0 : 4.0, part_us, &t);   // (one launch sums both)
+    const int z = best_parts(q[f], cap_q, g.b.n ? 0.0 : p.kv > 1 ? 1.0 : 4.0, part_us, &t);   // (one launch sums both)
     if (f == 0 || t < (p.form == 0 ? 0.98 : 1.0) * least) { least = t; p.form = f; p.q = z; }
   }
   return p;

@@ -2,6 +2,7 @@
 // (a2d_api.hip) and the kernel translation units.  gfx950 only.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "a2d.h"
@@ -35,9 +36,9 @@ template <> struct dtype_of<float> { static constexpr int value = A2D_F32; };
 template <> struct dtype_of<bf16_t> { static constexpr int value = A2D_BF16; };
 
 // Key/value sub-blocks of a tile for the causal mask.  Sub-block s covers the local keys
-// start[s] .. start[s] + rows[s] - 1 (the sub-blocks tile 0 .. nkv - 1 in order) and its keys are
-// consecutive tokens; rel[s] = q_off - (global index of its first key).  Query row i (local) sees
-// key start[s] + kk of sub-block s iff kk <= i + rel[s].  A plain tile is one sub-block.
+// seg[s].start .. + rows - 1 (the sub-blocks tile 0 .. nkv - 1 in order) and its keys are
+// consecutive tokens; rel = q_off - (global index of its first key).  Query row i (local) sees
+// key start[s] + kk of sub-block s iff kk <= i + rel.  A plain tile is one sub-block.
 // `acc` rides along: != 0 makes the forward start from the (N, m, l) already in its output
 // buffers and the backward add to the dQ partial already in its output buffer.
 // `norm` != 0: the forward writes the NORMALISED partial O' = N / l in the input dtype (into the
@@ -53,8 +54,13 @@ template <> struct dtype_of<bf16_t> { static constexpr int value = A2D_BF16; };
 // ones.  tri != 0: only the tiles c <= r exist.
 struct TileBatch {
   int n, first;        // tiles of this launch, number of its first tile
+  int slots;           // tiles of the whole grid (1: a plain call); part z of a split walk is stored slots tiles on
   int side, tri, cyclic;
   int64_t q, k, v, g;  // elements between blocks of Q, K, V, dO
+};
+struct Segment {
+  int start, rows;
+  int64_t rel;
 };
 struct SegList {
   int n;
@@ -65,9 +71,7 @@ struct SegList {
   TileBatch b;
   int parts;      // workgroups that share the walk of one block, each leaving a partial result (>= 1)
   int form;       // which of its workgroup shapes a forward / dQ launch takes (plan_* below)
-  int start[A2D_MAX_SEGMENTS];
-  int rows[A2D_MAX_SEGMENTS];
-  int64_t rel[A2D_MAX_SEGMENTS];
+  Segment seg[A2D_MAX_SEGMENTS];
 };
 
 // The tile this workgroup belongs to (all zero for a plain call).
@@ -110,16 +114,36 @@ __host__ __device__ inline int row_slot(const TileBatch& b, int r, int c) {
   return b.n == 0 ? 0 : b.tri ? r * (r + 1) / 2 + c : r * b.side + c;
 }
 
+// Brings the kernel's arguments - the tile's descriptor, the list's head and first sub-block, and the
+// pointers behind them - into the scalar cache in one go.  A cold line costs about half a microsecond,
+// and read one after another as the prologue comes to them they were a good part of the time of small
+// tiles.
+// (for kernels whose arguments begin with a2d_tile_desc, SegList; `more`: bytes of those that follow)
+template <int MORE>
+__device__ __forceinline__ void warm_arguments() {
+  constexpr int head = (int)(sizeof(a2d_tile_desc) + offsetof(SegList, seg) + sizeof(Segment) + 63) / 64;
+  constexpr int tail = (int)(sizeof(a2d_tile_desc) + sizeof(SegList)) / 64;
+  constexpr int last = (int)(sizeof(a2d_tile_desc) + sizeof(SegList) + MORE - 1) / 64;
+  static_assert(head <= 5 && last - tail <= 2, "lines to touch");
+  int v[8];
+  asm volatile(
+      "s_load_dword %0, %8, 0x0\n\ts_load_dword %1, %8, 0x40\n\ts_load_dword %2, %8, 0x80\n\t"
+      "s_load_dword %3, %8, 0xc0\n\ts_load_dword %4, %8, 0x100\n\ts_load_dword %5, %8, %9\n\t"
+      "s_load_dword %6, %8, %10\n\ts_load_dword %7, %8, %11\n\ts_waitcnt lgkmcnt(0)"
+      : "=&s"(v[0]), "=&s"(v[1]), "=&s"(v[2]), "=&s"(v[3]), "=&s"(v[4]), "=&s"(v[5]), "=&s"(v[6]), "=&s"(v[7])
+      : "s"(__builtin_amdgcn_kernarg_segment_ptr()), "i"(64 * tail), "i"(64 * (tail + (last > tail))), "i"(64 * last));
+}
+
 // sub-block that holds local key c (c < nkv)
 __device__ __forceinline__ int seg_of_key(const SegList& g, int c) {
   int s = 0;
-  while (s + 1 < g.n && c >= g.start[s + 1]) ++s;
+  while (s + 1 < g.n && c >= g.seg[s + 1].start) ++s;
   return s;
 }
 // does query row i see local key c (causal mask)?
 __device__ __forceinline__ bool seg_visible(const SegList& g, int i, int c) {
   const int s = seg_of_key(g, c);
-  return (int64_t)(c - g.start[s]) <= (int64_t)i + g.rel[s];
+  return (int64_t)(c - g.seg[s].start) <= (int64_t)i + g.seg[s].rel;
 }
 
 // ---- per-process caches of HIP runtime queries (a2d_device.hip; thread-safe) ----
@@ -262,10 +286,17 @@ inline OutMap plain_out() { return OutMap{0, 0, 1, 1}; }
 // The merged output of a whole emulated grid: block b, head h, row i of the merge's input is token
 // i * side + b (cyclic) or b * rows + i of head h in a plain [heads][side * rows][H] tensor.  dir: which
 // partials block b has - 0: all `side`; 1: those x <= b (a grid row under the causal mask,
-// contiguous blocks); 2: those x >= b (a grid column).
+// contiguous blocks); 2: those x >= b (a grid column).  Each is in `parts` parts: partial e of the
+// pointer lists is part e % parts of partial e / parts.
 struct GridMap {
-  int side, rows, heads, cyclic, dir;
-  __host__ __device__ __forceinline__ bool has(int b, int x) const { return dir == 0 || (dir == 1 ? x <= b : x >= b); }
+  int side, rows, heads, cyclic, dir, parts;
+  // walks the pointer lists: does block b have the list's next entry?
+  struct Walk { int x = 0, z = 0; };
+  __host__ __device__ __forceinline__ bool next(Walk& w, int b) const {
+    const bool has = w.x < side && (dir == 0 || (dir == 1 ? w.x <= b : w.x >= b));
+    if (++w.z == parts) { w.z = 0; ++w.x; }
+    return has;
+  }
 };
 // O, lse of a whole grid from its partial triples; sums of up to three sets of gradient partials
 hipError_t launch_fix_grid(const GridMap& gm, int hdim, int out_dtype, const FixPtrs& p, void* O, float* lse,

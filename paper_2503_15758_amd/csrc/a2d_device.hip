@@ -123,8 +123,8 @@ int64_t visible_keys(const a2d_tile_desc& d, const SegList& g, int64_t i) {
   if (!d.causal) return d.nkv;
   int64_t n = 0;
   for (int s = 0; s < g.n; ++s) {
-    const int64_t v = i + g.rel[s] + 1;
-    n += v <= 0 ? 0 : (v < g.rows[s] ? v : g.rows[s]);
+    const int64_t v = i + g.seg[s].rel + 1;
+    n += v <= 0 ? 0 : (v < g.seg[s].rows ? v : g.seg[s].rows);
   }
   return n;
 }

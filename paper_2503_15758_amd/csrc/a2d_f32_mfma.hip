@@ -217,9 +217,9 @@ __device__ __forceinline__ bool query_block(const a2d_tile_desc& d, const SegLis
 }
 
 __device__ __forceinline__ int vis_count(const a2d_tile_desc& d, const SegList& g, int i, int s) {
-  if (!d.causal) return g.rows[s];
-  const int64_t v = (int64_t)i + g.rel[s] + 1;
-  return v <= 0 ? 0 : (v < g.rows[s] ? (int)v : g.rows[s]);
+  if (!d.causal) return g.seg[s].rows;
+  const int64_t v = (int64_t)i + g.seg[s].rel + 1;
+  return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
 }
 
 // max / sum over the four groups of a row (lanes l15 + 16 g)
@@ -238,6 +238,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, float* __restrict__ O_part, float* __restrict__ m_out, float* __restrict__ l_out,
     FwdInput in) {
+  warm_arguments<6 * 8 + sizeof(FwdInput)>();
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int head, q0, part;
   if (!query_block(d, g, BLK * RT, head, q0, part)) return;
@@ -278,14 +279,14 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 
   Nat<H> kn;
   Cols<H> vt[4];
   auto load_k = [&](const Walk& x) {
-    const int r = min(x.j * BLK + l15, g.rows[x.s] - 1);
-    kn.load(kb, g.start[x.s] + r, k_row, g4);
+    const int r = min(x.j * BLK + l15, g.seg[x.s].rows - 1);
+    kn.load(kb, g.seg[x.s].start + r, k_row, g4);
   };
   if (w.s < g.n) load_k(w);
   while (w.s < g.n) {
-    const int s = w.s, k0 = w.j * BLK, rows = g.rows[s];
+    const int s = w.s, k0 = w.j * BLK, rows = g.seg[s].rows;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) vt[r].load(vb, g.start[s] + min(k0 + 4 * g4 + r, rows - 1), v_row, l15);
+    for (int r = 0; r < 4; ++r) vt[r].load(vb, g.seg[s].start + min(k0 + 4 * g4 + r, rows - 1), v_row, l15);
     __builtin_amdgcn_sched_barrier(0);
     f32x4 p[RT];
 #pragma unroll
@@ -375,6 +376,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, const float* __restrict__ O, const float* __restrict__ dO,
     const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dQ) {
+  warm_arguments<8 * 8>();
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int head, q0, part;
   if (!query_block(d, g, BLK, head, q0, part)) return;
@@ -407,11 +409,11 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   Out<H> dq;
   dq.zero();
   auto load_k = [&](const Walk& x) {
-    kn.load(kb, g.start[x.s] + min(x.j * BLK + l15, g.rows[x.s] - 1), k_row, g4);
+    kn.load(kb, g.seg[x.s].start + min(x.j * BLK + l15, g.seg[x.s].rows - 1), k_row, g4);
   };
   if (w.s < g.n) load_k(w);
   while (w.s < g.n) {
-    const int s = w.s, k0 = w.j * BLK, rows = g.rows[s], start = g.start[s];
+    const int s = w.s, k0 = w.j * BLK, rows = g.seg[s].rows, start = g.seg[s].start;
     vn.load(vb, start + min(k0 + l15, rows - 1), v_row, g4);
     __builtin_amdgcn_sched_barrier(0);
     const f32x4 sc = dot_rows<H>(kn, qf);
@@ -451,6 +453,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, const float* __restrict__ dO, const float* __restrict__ lse,
     const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV) {
+  warm_arguments<8 * 8>();
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int head, blk;                                      // key/value head
   if (!xcd_map(d.heads / g.group * g.parts, (d.nkv + BLK - 1) / BLK, g.by_size != 0, head, blk)) return;
@@ -473,16 +476,16 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
 
   // first query row that sees this lane's key, and the first that sees any of the block's keys
   auto first_row = [&](int s, int k) -> int {
-    const int64_t f = (int64_t)(k - g.start[s]) - g.rel[s];
+    const int64_t f = (int64_t)(k - g.seg[s].start) - g.seg[s].rel;
     return f <= 0 ? 0 : (f >= d.nq ? d.nq : (int)f);
   };
   int my_first = 0, i_first = 0;
   if (d.causal) {
     my_first = i_first = d.nq;
     for (int s = 0; s < g.n; ++s) {
-      const int a = max(k0, g.start[s]), b = min(k0 + BLK, g.start[s] + g.rows[s]);
+      const int a = max(k0, g.seg[s].start), b = min(k0 + BLK, g.seg[s].start + g.seg[s].rows);
       if (a < b) i_first = min(i_first, first_row(s, a));
-      if (key >= g.start[s] && key < g.start[s] + g.rows[s]) my_first = first_row(s, key);
+      if (key >= g.seg[s].start && key < g.seg[s].start + g.seg[s].rows) my_first = first_row(s, key);
     }
   }
   if (key >= d.nkv) my_first = d.nq;                  // padding keys see nothing

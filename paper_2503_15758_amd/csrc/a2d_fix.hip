@@ -215,9 +215,10 @@ __global__ __launch_bounds__(256) void fix_grid_kernel(FixPtrs p, GridMap g, int
   const GridRow gr(g, row);
   f32x4 n[KMAX];
   float mk[KMAX], lk[KMAX];
+  GridMap::Walk walk;
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    if (x < g.side && g.has(gr.b, x)) {
+    if (g.next(walk, gr.b)) {
       n[x] = A2D_LD(reinterpret_cast<const f32x4*>(p.o[x]) + idx);
       mk[x] = p.m[x][row];
       lk[x] = p.l[x][row];
@@ -260,9 +261,10 @@ __global__ __launch_bounds__(256) void sum_grid_kernel(SumSets a, int hv) {
   if (row >= (unsigned)(g.side * g.heads * g.rows)) return;
   const GridRow gr(g, row);
   f32x4 v[KMAX];
+  GridMap::Walk walk;
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    if (x < g.side && g.has(gr.b, x)) v[x] = A2D_LD(reinterpret_cast<const f32x4*>(s.p.p[x]) + idx);
+    if (g.next(walk, gr.b)) v[x] = A2D_LD(reinterpret_cast<const f32x4*>(s.p.p[x]) + idx);
     else v[x] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   f32x4 acc = v[0];
@@ -386,23 +388,25 @@ namespace {
 template <typename OutT>
 void fix_grid_dispatch(const GridMap& gm, int hv, const FixPtrs& p, OutT* O, float* lse, hipStream_t s) {
   const dim3 grid((unsigned)(((int64_t)gm.side * gm.heads * gm.rows * hv + 255) / 256)), block(256);
+  const int k = gm.side * gm.parts;
 #define A2D_GO(KMAX) A2D_LAUNCH((fix_grid_kernel<OutT, KMAX>), grid, block, 0, s, p, gm, hv, O, lse)
-  if (gm.side <= 2) A2D_GO(2);
-  else if (gm.side <= 4) A2D_GO(4);
-  else if (gm.side <= 8) A2D_GO(8);
-  else if (gm.side <= 16) A2D_GO(16);
+  if (k <= 2) A2D_GO(2);
+  else if (k <= 4) A2D_GO(4);
+  else if (k <= 8) A2D_GO(8);
+  else if (k <= 16) A2D_GO(16);
   else A2D_GO(32);
 #undef A2D_GO
 }
 template <typename OutT>
 void sum_grid_dispatch(int nsets, const SumSets& a, int hv, int64_t blocks, hipStream_t s) {
   const dim3 grid((unsigned)blocks, nsets), block(256);
-  const int side = a.s[0].gm.side;
+  int k = 0;
+  for (int x = 0; x < nsets; ++x) k = a.s[x].gm.side * a.s[x].gm.parts > k ? a.s[x].gm.side * a.s[x].gm.parts : k;
 #define A2D_GO(KMAX) A2D_LAUNCH((sum_grid_kernel<OutT, KMAX>), grid, block, 0, s, a, hv)
-  if (side <= 2) A2D_GO(2);
-  else if (side <= 4) A2D_GO(4);
-  else if (side <= 8) A2D_GO(8);
-  else if (side <= 16) A2D_GO(16);
+  if (k <= 2) A2D_GO(2);
+  else if (k <= 4) A2D_GO(4);
+  else if (k <= 8) A2D_GO(8);
+  else if (k <= 16) A2D_GO(16);
   else A2D_GO(32);
 #undef A2D_GO
 }

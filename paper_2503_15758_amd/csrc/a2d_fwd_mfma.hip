@@ -189,7 +189,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   K += (int64_t)kvh * d.lk.head + tp.c * g.b.k;
   V += (int64_t)kvh * d.lv.head + tp.c * g.b.v;
   {
-    const int64_t slot = ((int64_t)col_slot(g.b, tp.r, tp.c) + part) * d.heads * d.nq;
+    const int64_t slot = ((int64_t)part * g.b.slots + col_slot(g.b, tp.r, tp.c)) * d.heads * d.nq;
     O_part += slot * HR;
     m_out += slot;
     l_out += slot;
@@ -269,9 +269,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // ---- visibility, per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
   // (key kk of the sub-block iff kk <= i + rel[s])
   auto vis_count = [&](int i, int s) -> int {
-    if (!d.causal) return g.rows[s];
-    const int64_t v = (int64_t)i + g.rel[s] + tp.rel + 1;
-    return v <= 0 ? 0 : (v < g.rows[s] ? (int)v : g.rows[s]);
+    if (!d.causal) return g.seg[s].rows;
+    const int64_t v = (int64_t)i + g.seg[s].rel + tp.rel + 1;
+    return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
   };
   const int blk_last = min(q0 + BM, d.nq) - 1;
   const int w_first = min(q0 + wave * 32, d.nq - 1);
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   int nx_start = 0, nx_rows = 0;                   // start / rows of the next entry's sub-block
   if (sb < g.n) {
     enter_segment(sb);
-    nx_start = g.start[sb]; nx_rows = g.rows[sb];
+    nx_start = g.seg[sb].start; nx_rows = g.seg[sb].rows;
     load_tile(nx_start, nx_rows, j);
   }
   // (one wait for the Q rows and the first tile: the two latencies overlap)
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     int nsb = sb, nj = j, nnblk = nblk;
     advance(stride, nsb, nj, nnblk);
     const bool more = nsb < g.n;
-    if (more && nsb != sb) { nx_start = g.start[nsb]; nx_rows = g.rows[nsb]; }
+    if (more && nsb != sb) { nx_start = g.seg[nsb].start; nx_rows = g.seg[nsb].rows; }
     if (more) load_tile(nx_start, nx_rows, nj);
     const int k0 = j * BN;                         // local to the sub-block
     if ((KL == 1 || sb < g.n) && k0 < nvis_wave) {
@@ -485,7 +485,7 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const bool uneven = g->by_size || g->b.n;
   const double mean = uneven ? mean_visible_keys(d, *g) / BN + 0.2 : most;
   const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 3.7;
-  const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 4.5e6;      // written and read back at 4.5 TB/s
+  const double part_us = (double)heads * d.nq * (d.hdim + 2) * 8 / 4.5e6;      // written and read back at 4.5 TB/s
   const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
   const WalkModel m[3] = {{b256, cus, mean, most, step, fixed, 0, 0},
                           {b128, cus, mean / 2, most / 2, step * 1.13, fixed + 0.8, 0, 0},
@@ -493,7 +493,7 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   double least = 0;
   for (int f = 0; f < 3; ++f) {
     double t;
-    const int z = best_parts(m[f], cap, 3.2, part_us, &t);
+    const int z = best_parts(m[f], cap, g->b.n ? 0.0 : 3.2, part_us, &t);   // (a grid's partials are merged anyway)
     if (f == 0 || t < (g->form == 0 ? 0.98 : 1.0) * least) { least = t; g->form = f; g->parts = z; }
   }
 }

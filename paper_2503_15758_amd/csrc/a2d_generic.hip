@@ -51,9 +51,9 @@ __device__ __forceinline__ int visible_keys(const a2d_tile_desc& d, const SegLis
   if (!d.causal) return d.nkv;
   int nvis = 0;
   for (int s = 0; s < g.n; ++s) {
-    const int64_t v = (int64_t)q_last + g.rel[s] + 1;          // visible keys of sub-block s
-    const int vs = v <= 0 ? 0 : (v < g.rows[s] ? (int)v : g.rows[s]);
-    if (vs > 0) nvis = g.start[s] + vs;
+    const int64_t v = (int64_t)q_last + g.seg[s].rel + 1;          // visible keys of sub-block s
+    const int vs = v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
+    if (vs > 0) nvis = g.seg[s].start + vs;
   }
   return nvis;
 }
@@ -219,9 +219,9 @@ __global__ __launch_bounds__(kThreads) void bwd_dkdv_generic_kernel(
     i_first = d.nq;
     const int k_end = min(k0 + BK, d.nkv);
     for (int sb = 0; sb < g.n; ++sb) {
-      const int a = max(k0, g.start[sb]), b = min(k_end, g.start[sb] + g.rows[sb]);
+      const int a = max(k0, g.seg[sb].start), b = min(k_end, g.seg[sb].start + g.seg[sb].rows);
       if (a >= b) continue;
-      const int64_t f = (int64_t)(a - g.start[sb]) - g.rel[sb];      // first row that sees key a
+      const int64_t f = (int64_t)(a - g.seg[sb].start) - g.seg[sb].rel;      // first row that sees key a
       const int fr = f <= 0 ? 0 : (f >= d.nq ? d.nq : (int)f);
       i_first = min(i_first, fr);
     }

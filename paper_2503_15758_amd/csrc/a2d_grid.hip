@@ -44,8 +44,8 @@ void describe(const GridProblem& p, a2d_tile_desc* d, SegList* g) {
   g->n = 1;
   g->group = p.heads / p.kv_heads;
   g->parts = 1;
-  g->rows[0] = rows_of(p);
-  g->b.n = slots_of(p);
+  g->seg[0].rows = rows_of(p);
+  g->b.n = g->b.slots = slots_of(p);
   g->b.side = p.side;
   g->b.tri = tri_of(p);
   g->b.cyclic = p.cyclic;
@@ -62,8 +62,26 @@ int chunk_of(const GridProblem& p, const a2d_tile_desc& d, const SegList& g) {
   return n < 1 ? 1 : n > (size_t)slots_of(p) ? slots_of(p) : (int)n;
 }
 
-GridMap map_of(const GridProblem& p, int heads, int dir) {
-  return GridMap{p.side, rows_of(p), heads, p.cyclic, tri_of(p) ? dir : 0};
+GridMap map_of(const GridProblem& p, int heads, int dir, int parts) {
+  return GridMap{p.side, rows_of(p), heads, p.cyclic, tri_of(p) ? dir : 0, parts};
+}
+
+// Parts of the tiles' walks (few, small tiles): the merges of the grid take the parts along, so that only
+// their bytes count.  At most what the merges can take, and kSplitBytes of partials.
+int cap_of(const GridProblem& p, size_t floats) {
+  const int64_t room = (int64_t)(kSplitBytes / sizeof(float) / floats), most = A2D_MAX_PARTS / p.side;
+  return room < 1 || most < 1 ? 1 : (int)(room < most ? room : most);
+}
+size_t out_floats(const GridProblem& p, int heads) { return (size_t)slots_of(p) * heads * rows_of(p) * p.hdim; }
+
+// The forward's shape and parts, the backward's parts.  Both depend on the problem alone (the chunks
+// of the backward share its parts).  false: no device
+bool plan(const GridProblem& p, const a2d_tile_desc& d, SegList* g, BwdParts* b) {
+  int cus = 0;
+  if (device_cus(&cus) != hipSuccess) return false;
+  plan_fwd_mfma(d, g, cus, cap_of(p, out_floats(p, p.heads)));
+  *b = plan_bwd_mfma(d, *g, true, cus, cap_of(p, 2 * out_floats(p, p.kv_heads)), cap_of(p, out_floats(p, p.heads)));
+  return true;
 }
 
 }  // namespace
@@ -93,15 +111,22 @@ bool grid_supported(const GridProblem& p) {
 }
 
 size_t grid_forward_bytes(const GridProblem& p) {
-  return (size_t)slots_of(p) * p.heads * rows_of(p) * (p.hdim + 2) * sizeof(float);
+  a2d_tile_desc d;
+  SegList g;
+  BwdParts b;
+  describe(p, &d, &g);
+  if (!plan(p, d, &g, &b)) return 0;
+  return (size_t)g.parts * slots_of(p) * p.heads * rows_of(p) * (p.hdim + 2) * sizeof(float);
 }
 
 size_t grid_backward_bytes(const GridProblem& p) {
   a2d_tile_desc d;
   SegList g;
+  BwdParts b;
   describe(p, &d, &g);
+  if (!plan(p, d, &g, &b)) return 0;
   const size_t stats = 2 * up256((size_t)p.heads * p.seq * sizeof(float));
-  const size_t parts = (size_t)slots_of(p) * rows_of(p) * p.hdim * (p.heads + 2 * (size_t)p.kv_heads) * sizeof(float);
+  const size_t parts = (b.q * out_floats(p, p.heads) + 2 * b.kv * out_floats(p, p.kv_heads)) * sizeof(float);
   return stats + up256(parts) + (size_t)chunk_of(p, d, g) * bwd_ds_bytes(d, g);
 }
 
@@ -112,12 +137,13 @@ hipError_t grid_forward(const GridProblem& p, const void* Q, const void* K, cons
   describe(p, &d, &g);
   const size_t per = (size_t)p.heads * rows_of(p), slots = slots_of(p);
   float* N = static_cast<float*>(ws);
-  float* m = N + slots * per * p.hdim;
-  float* l = m + slots * per;
-  hipError_t e = plan_fwd(d, &g, false);
-  if (e != hipSuccess) return e;
+  float *m = nullptr, *l = nullptr;
+  BwdParts unused;
+  if (!plan(p, d, &g, &unused)) return hipErrorInvalidDevice;
   const FwdInput none{nullptr, nullptr, nullptr};
-  e = launch_fwd_mfma(PREPARE, d, g, Q, K, V, N, m, l, none, s);
+  m = N + g.parts * slots * per * p.hdim;
+  l = m + g.parts * slots * per;
+  hipError_t e = launch_fwd_mfma(PREPARE, d, g, Q, K, V, N, m, l, none, s);
   if (e != hipSuccess) return e;
   trace_mark(s);
   e = launch_fwd_mfma(LAUNCH, d, g, Q, K, V, N, m, l, none, s);      // Alg. 1 line 4, every tile
@@ -125,12 +151,14 @@ hipError_t grid_forward(const GridProblem& p, const void* Q, const void* K, cons
   FixPtrs f;
   memset(&f, 0, sizeof(f));
   for (int c = 0; c < p.side; ++c) {                           // column c's partials, indexed by (row block, head, row)
-    const size_t at = (size_t)(col_slot(g.b, c, c) - c) * per;
-    f.o[c] = N + at * p.hdim;
-    f.m[c] = m + at;
-    f.l[c] = l + at;
+    for (int z = 0; z < g.parts; ++z) {
+      const size_t at = (size_t)(z * (int)slots + col_slot(g.b, c, c) - c) * per;
+      f.o[c * g.parts + z] = N + at * p.hdim;
+      f.m[c * g.parts + z] = m + at;
+      f.l[c * g.parts + z] = l + at;
+    }
   }
-  return launch_fix_grid(map_of(p, p.heads, 1), p.hdim, A2D_BF16, f, O, lse, s);   // Alg. 1 lines 5-6
+  return launch_fix_grid(map_of(p, p.heads, 1, g.parts), p.hdim, A2D_BF16, f, O, lse, s);   // Alg. 1 lines 5-6
 }
 
 hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, const void* V, const void* O,
@@ -144,18 +172,18 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
   float* delta = reinterpret_cast<float*>(w);
   float* lse_blk = reinterpret_cast<float*>(w + stat);
   float* dq = reinterpret_cast<float*>(w + 2 * stat);
-  float* dk = dq + slots * p.heads * rows * p.hdim;
-  float* dv = dk + slots * p.kv_heads * rows * p.hdim;
-  const size_t parts = slots * rows * p.hdim * (p.heads + 2 * (size_t)p.kv_heads) * sizeof(float);
+  BwdParts bp;
+  if (!plan(p, d, &g, &bp)) return hipErrorInvalidDevice;
+  g.parts = 1;
+  float* dk = dq + bp.q * out_floats(p, p.heads);
+  float* dv = dk + bp.kv * out_floats(p, p.kv_heads);
+  const size_t parts = (bp.q * out_floats(p, p.heads) + 2 * bp.kv * out_floats(p, p.kv_heads)) * sizeof(float);
   void* ds = w + 2 * stat + up256(parts);
   const int chunk = chunk_of(p, d, g), total = slots_of(p);
-  int cus = 0;
-  const hipError_t dev = device_cus(&cus);
-  if (dev != hipSuccess) return dev;
   for (int pass = 0; pass < 2; ++pass) {                       // everything that can fail on the host first
     if (pass == 1) {
       trace_mark(s);
-      const hipError_t e = launch_delta_grid(map_of(p, p.heads, 0), p.hdim, p.o, p.g, (const bf16_t*)O,
+      const hipError_t e = launch_delta_grid(map_of(p, p.heads, 0, 1), p.hdim, p.o, p.g, (const bf16_t*)O,
                                              (const bf16_t*)dO, lse, delta, lse_blk, s);
       if (e != hipSuccess) return e;
     }
@@ -163,19 +191,23 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
       g.b.first = t;
       g.b.n = total - t < chunk ? total - t : chunk;
       const hipError_t e = launch_bwd_mfma(pass == 0 ? PREPARE : LAUNCH, d, g, Q, K, V, O, dO, lse_blk, delta, dq, dk, dv,
-                                           ds, plan_bwd_mfma(d, g, true, cus, 1, 1), s);
+                                           ds, bp, s);
       if (e != hipSuccess) return e;
     }
   }
   SumSet sets[3];
   memset(sets, 0, sizeof(sets));
   for (int x = 0; x < p.side; ++x) {
-    sets[0].p.p[x] = dq + (size_t)(col_slot(g.b, x, x) - x) * p.heads * rows * p.hdim;
-    sets[1].p.p[x] = dk + (size_t)row_slot(g.b, x, 0) * p.kv_heads * rows * p.hdim;
-    sets[2].p.p[x] = dv + (size_t)row_slot(g.b, x, 0) * p.kv_heads * rows * p.hdim;
+    for (int z = 0; z < bp.q; ++z)
+      sets[0].p.p[x * bp.q + z] = dq + (size_t)(z * (int)slots + col_slot(g.b, x, x) - x) * p.heads * rows * p.hdim;
+    for (int z = 0; z < bp.kv; ++z) {
+      const size_t at = (size_t)(z * (int)slots + row_slot(g.b, x, 0)) * p.kv_heads * rows * p.hdim;
+      sets[1].p.p[x * bp.kv + z] = dk + at;
+      sets[2].p.p[x * bp.kv + z] = dv + at;
+    }
   }
-  sets[0].gm = map_of(p, p.heads, 1);
-  sets[1].gm = sets[2].gm = map_of(p, p.kv_heads, 2);
+  sets[0].gm = map_of(p, p.heads, 1, bp.q);
+  sets[1].gm = sets[2].gm = map_of(p, p.kv_heads, 2, bp.kv);
   sets[0].out = dQ;
   sets[1].out = dK;
   sets[2].out = dV;

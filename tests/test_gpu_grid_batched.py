@@ -19,6 +19,8 @@ CASES = [
     (8, 2, 65, 7, 64, True, "cyclic", True),
     (5, 5, 300, 1, 128, True, "contiguous", False),   # a grid of one tile
     (64, 64, 2048, 2, 64, False, "cyclic", False),    # dS of three of the four tiles fits the workspace
+    (2, 2, 700, 2, 128, True, "contiguous", False),   # few tiles: the walks are split
+    (8, 1, 90, 4, 96, True, "cyclic", False),         # ... over the heads of a group
 ]
 
 
