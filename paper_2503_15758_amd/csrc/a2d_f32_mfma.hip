@@ -4,8 +4,11 @@
 // of a SIMD, 157 TFLOP/s over the chip - twice what unpacked vector FMAs reach).
 //
 // What bounds them: the fp32 MFMA rate.  A step of 16 keys (queries) against 16 rows is H / 4 MFMAs
-// of 32 cycles per contraction, 8 KiB of operands at H = 128 - slow enough that the operands come
-// straight from L2 into registers, one contraction ahead of their use; LDS is only used at the end.
+// of 32 cycles per contraction, on 8 KiB of operands at H = 128.
+//   - Operands of a step come in by whole rows (16 lanes on 256 bytes), one step ahead, and pass through
+//     a tile in LDS that is the wavefront's own (no barriers): a contraction over H needs lane = row, and
+//     loading that from memory is 64 separate accesses per instruction, which kept the matrix units
+//     half idle (16 heads x 1024 x 1024, H = 96: 6.4e7 cache accesses for 1.2 GB, 50 % MFMA busy).
 //   - A wavefront owns 16 * RT rows and walks blocks of 16 keys (queries); the KL wavefronts of a
 //     workgroup own the SAME rows and take every KL-th block of the walk ("key lanes"), because fp32
 //     tiles are small: it is the walk that has to be spread over the SIMDs.  Their results are
@@ -15,9 +18,9 @@
 //     4 g + r.  As in the bf16 kernels the score contraction is issued transposed, so that a lane
 //     holds 4 keys (4 g + r) of ONE query, and its D is the B operand of the next contraction: step r
 //     contracts the keys r, 4 + r, 8 + r, 12 + r.
-//   - Contractions over H read rows "naturally": lane (row l15, group g) loads the 16 bytes
+//   - Contractions over H read rows "naturally": lane (row l15, group g) reads the 16 bytes
 //     16 y + 4 g .. + 3 of its row, which serve four MFMAs (the contraction index may be permuted as
-//     long as both operands use the same permutation).
+//     long as both operands use the same permutation).  Tile rows are padded by 16 bytes: no conflicts.
 //   - Contractions over rows need the transposed operand (lane = column): lane l15 loads 16 bytes of
 //     row 4 g + r, columns 64 G + 4 l15 + t, and MFMA t of the group takes one of the four, i.e. row
 //     i of its result is column 64 G + 4 i + t.  A lane then holds 16 consecutive columns of the
@@ -40,6 +43,7 @@ using mfma::xcd_grid;
 using mfma::xcd_map;
 
 constexpr int BLK = 16;                      // rows of one step of a walk
+constexpr int KL = 4;                        // key lanes (wavefronts) of a workgroup
 constexpr float kRescaleThreshold = 8.0f;    // log2 units (lazy rescaling, as in the bf16 forward)
 
 __device__ __forceinline__ f32x4 mma4(float a, float b, f32x4 c) {
@@ -82,6 +86,47 @@ struct Cols {
   template <int T>
   __device__ __forceinline__ float get() const {
     if constexpr (T < 4 * N4) return a[T / 4][T % 4]; else return b[T - 4 * N4];
+  }
+};
+
+typedef __attribute__((address_space(3))) char* lds_t;
+template <typename T>
+__device__ __forceinline__ T lload(lds_t p) { return *reinterpret_cast<__attribute__((address_space(3))) T*>(p); }
+template <typename T>
+__device__ __forceinline__ void lstore(lds_t p, T v) { *reinterpret_cast<__attribute__((address_space(3))) T*>(p) = v; }
+
+// A wavefront's tile of 16 rows in LDS.  It is written and read by that wavefront alone, whose LDS
+// operations complete in order.
+template <int H>
+struct Tile {
+  static constexpr int LD = H * 4 + 16, BYTES = 16 * LD;
+  lds_t base, nat, col;                      // + this lane's place for natural rows, and for columns (row 4 g)
+  __device__ __forceinline__ void init(lds_t b, int l15, int g4) {
+    base = b;
+    nat = b + l15 * LD + 16 * g4;
+    col = b + 4 * g4 * LD + 16 * l15;
+  }
+  // rows 4 g + r, as Cols holds them
+  __device__ __forceinline__ void store(const Cols<H> (&c)[4], int l15) {
+    constexpr int N4 = Cols<H>::N4, REST = Cols<H>::REST;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+      for (int G = 0; G < N4; ++G) lstore(col + r * LD + 256 * G, c[r].a[G]);
+      if constexpr (REST == 32) lstore(col - 8 * l15 + r * LD + 256 * N4, f32x2{c[r].b[0], c[r].b[1]});
+      if constexpr (REST == 16) lstore(col - 12 * l15 + r * LD + 256 * N4, c[r].b[0]);
+    }
+  }
+  __device__ __forceinline__ f32x4 row(int y) const { return lload<f32x4>(nat + 64 * y); }
+  __device__ __forceinline__ void cols(Cols<H>& c, int r, int l15) const {
+    constexpr int N4 = Cols<H>::N4, REST = Cols<H>::REST;
+#pragma unroll
+    for (int G = 0; G < N4; ++G) c.a[G] = lload<f32x4>(col + r * LD + 256 * G);
+    if constexpr (REST == 32) {
+      const f32x2 w = lload<f32x2>(col - 8 * l15 + r * LD + 256 * N4);
+      c.b[0] = w[0]; c.b[1] = w[1];
+    }
+    if constexpr (REST == 16) c.b[0] = lload<float>(col - 12 * l15 + r * LD + 256 * N4);
   }
 };
 
@@ -143,21 +188,49 @@ struct Out {
   }
 };
 
-// 16 x 16 result of a contraction over H (two accumulators: an MFMA that accumulates onto the
-// result of the one issued just before it would wait for that result)
+// 16 x 16 results of contractions over H of a tile's rows with RT sets of rows in registers (two
+// accumulators each).  The tile's pieces are requested one ahead of their use.
+template <int H, int RT>
+__device__ __forceinline__ void dot_rows(f32x4 (&out)[RT], const Tile<H>& a, const Nat<H> (&b)[RT]) {
+  constexpr int N = H / 16;
+  f32x4 s1[RT], ring[2];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) { out[t] = zero4(); s1[t] = zero4(); }
+  ring[0] = a.row(0);
+  ring[1] = a.row(1);
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<0, N>([&](auto Y) {
+    constexpr int y = decltype(Y)::value;
+    const f32x4 v = ring[y & 1];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      out[t] = mma4(v[0], b[t].v[y][0], out[t]);
+      s1[t] = mma4(v[1], b[t].v[y][1], s1[t]);
+      out[t] = mma4(v[2], b[t].v[y][2], out[t]);
+      s1[t] = mma4(v[3], b[t].v[y][3], s1[t]);
+    }
+    if constexpr (y + 2 < N) ring[y & 1] = a.row(y + 2);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[t][r] += s1[t][r];
+}
+
+// acc += tile^T * b: rows 4 g + r in step r
 template <int H>
-__device__ __forceinline__ f32x4 dot_rows(const Nat<H>& a, const Nat<H>& b) {
-  f32x4 s0 = zero4(), s1 = zero4();
-#pragma unroll
-  for (int y = 0; y < H / 16; ++y) {
-    s0 = mma4(a.v[y][0], b.v[y][0], s0);
-    s1 = mma4(a.v[y][1], b.v[y][1], s1);
-    s0 = mma4(a.v[y][2], b.v[y][2], s0);
-    s1 = mma4(a.v[y][3], b.v[y][3], s1);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) s0[r] += s1[r];
-  return s0;
+__device__ __forceinline__ void contract_tile(Out<H>& acc, const Tile<H>& a, const f32x4& b, int l15) {
+  Cols<H> ring[2];
+  a.cols(ring[0], 0, l15);
+  a.cols(ring[1], 1, l15);
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<0, 4>([&](auto R) {
+    constexpr int r = decltype(R)::value;
+    acc.contract(ring[r & 1], b[r]);
+    if constexpr (r < 2) a.cols(ring[r & 1], r + 2, l15);
+    __builtin_amdgcn_sched_barrier(0);
+  });
 }
 
 // Sum of N results over the KL wavefronts of the workgroup, by halves: the upper half writes, the
@@ -185,19 +258,28 @@ __device__ __forceinline__ void merge_lanes(f32x4* xch, int kl, int lane, Get&& 
 
 // The walk over the 16-key blocks that some row of the workgroup sees, sub-block by sub-block; key
 // lane kl takes every KL-th block.  (s == g.n: past the end)
+// The current sub-block's entry is kept in registers: read from the kernel arguments in every step it
+// would be scalar loads, which share a wait counter with the LDS operations in flight.
 struct Walk {
   int s, j, nblk;
+  int start, rows;                           // of the sub-block
   template <class SegBlocks>
-  __device__ __forceinline__ void open(int from, int n, SegBlocks&& blocks) {
-    s = from; j = 0;
-    while (s < n && (nblk = blocks(s)) == 0) ++s;
+  __device__ __forceinline__ void find(const SegList& g, SegBlocks&& blocks) {   // from sub-block s on
+    while (s < g.n && (nblk = blocks(s)) == 0) ++s;
+    if (s < g.n) { start = g.seg[s].start; rows = g.seg[s].rows; }
   }
   template <class SegBlocks>
-  __device__ __forceinline__ void advance(int by, int n, SegBlocks&& blocks) {
+  __device__ __forceinline__ void open(const SegList& g, SegBlocks&& blocks) {
+    s = 0; j = 0; nblk = start = rows = 0;
+    find(g, blocks);
+  }
+  template <class SegBlocks>
+  __device__ __forceinline__ void advance(int by, const SegList& g, SegBlocks&& blocks) {
     j += by;
-    while (s < n && j >= nblk) {
+    while (s < g.n && j >= nblk) {
       j -= nblk;
-      do { ++s; } while (s < n && (nblk = blocks(s)) == 0);
+      ++s;
+      find(g, blocks);
     }
   }
 };
@@ -233,8 +315,8 @@ __device__ __forceinline__ float row_sum(float v) {
 }
 
 // ------------------------------------------------------------------ forward
-template <int H, int RT, int KL>
-__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 ? 4 : 2))) void fwd_f32_kernel(
+template <int H, int RT>
+__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void fwd_f32_kernel(
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, float* __restrict__ O_part, float* __restrict__ m_out, float* __restrict__ l_out,
     FwdInput in) {
@@ -274,32 +356,38 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 
   const int blk_last = min(q0 + BLK * RT, d.nq) - 1;
   auto seg_blocks = [&](int s) { return (vis_count(d, g, blk_last, s) + BLK - 1) / BLK; };
   Walk w;
-  w.open(0, g.n, seg_blocks);
-  w.advance(part * KL + kl, g.n, seg_blocks);
-  Nat<H> kn;
-  Cols<H> vt[4];
+  w.open(g, seg_blocks);
+  w.advance(part * KL + kl, g, seg_blocks);
+  Tile<H> kt;
+  kt.init((lds_t)smem + kl * Tile<H>::BYTES, l15, g4);
+  Cols<H> kc[4], vt[4];
   auto load_k = [&](const Walk& x) {
-    const int r = min(x.j * BLK + l15, g.seg[x.s].rows - 1);
-    kn.load(kb, g.seg[x.s].start + r, k_row, g4);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) kc[r].load(kb, x.start + min(x.j * BLK + 4 * g4 + r, x.rows - 1), k_row, l15);
   };
+  int vis_s = -1, my_vis[RT];                         // keys of sub-block vis_s that this lane's rows see
   if (w.s < g.n) load_k(w);
   while (w.s < g.n) {
-    const int s = w.s, k0 = w.j * BLK, rows = g.seg[s].rows;
+    const int k0 = w.j * BLK;
+    if (w.s != vis_s) {
+      vis_s = w.s;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) vt[r].load(vb, g.seg[s].start + min(k0 + 4 * g4 + r, rows - 1), v_row, l15);
+      for (int t = 0; t < RT; ++t) my_vis[t] = vis_count(d, g, min(q_row[t], d.nq - 1), w.s);
+    }
+    kt.store(kc, l15);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) vt[r].load(vb, w.start + min(k0 + 4 * g4 + r, w.rows - 1), v_row, l15);
     __builtin_amdgcn_sched_barrier(0);
     f32x4 p[RT];
-#pragma unroll
-    for (int t = 0; t < RT; ++t) p[t] = dot_rows<H>(kn, qf[t]);
-    w.advance(lanes, g.n, seg_blocks);
+    dot_rows<H, RT>(p, kt, qf);
+    w.advance(lanes, g, seg_blocks);
     if (w.s < g.n) load_k(w);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-      const int my_vis = vis_count(d, g, min(q_row[t], d.nq - 1), s);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        if (k0 + 4 * g4 + r >= my_vis) p[t][r] = -INFINITY;
+        if (k0 + 4 * g4 + r >= my_vis[t]) p[t][r] = -INFINITY;
         m_lane[t] = fmaxf(m_lane[t], p[t][r]);
       }
       // (m_lane - m_ref) is +inf on the first visible block, NaN (-> false) while nothing is visible
@@ -330,6 +418,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 
 #pragma unroll
   for (int t = 0; t < RT; ++t) m_all[t] = row_max(m_lane[t]);
   if constexpr (KL > 1) {
+    __syncthreads();                                 // (the tiles are written over)
 #pragma unroll
     for (int t = 0; t < RT; ++t)
       if (g4 == 0) stat[(kl * RT + t) * 16 + l15] = m_all[t];
@@ -371,7 +460,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(KL > 8 
 // ---------------------------------------------------------------- backward: dQ (and delta)
 // Owns 16 query rows per workgroup.  Also computes delta = rowsum(dO o O) of its rows (every key lane
 // for itself) and leaves it for the dK/dV kernel, which runs after it: no separate pass over O and dO.
-template <int H, int KL>
+template <int H>
 __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void bwd_dq_f32_kernel(
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, const float* __restrict__ O, const float* __restrict__ dO,
@@ -388,52 +477,60 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   const unsigned k_row = (unsigned)d.lk.row * 4, v_row = (unsigned)d.lv.row * 4;
   const int q_row = q0 + l15, q_ld = min(q_row, d.nq - 1);
 
-  Nat<H> qf, gf, kn, vn;
-  qf.load(uniform_gptr(Q + (int64_t)head * d.lq.head), q_ld, (unsigned)d.lq.row * 4, g4);
-  gf.load(uniform_gptr(dO + (int64_t)head * d.ldo.head), q_ld, (unsigned)d.ldo.row * 4, g4);
-  kn.load(uniform_gptr(O + (int64_t)head * d.lo.head), q_ld, (unsigned)d.lo.row * 4, g4);   // O, for delta only
+  Nat<H> qf[1], gf[1], of;
+  qf[0].load(uniform_gptr(Q + (int64_t)head * d.lq.head), q_ld, (unsigned)d.lq.row * 4, g4);
+  gf[0].load(uniform_gptr(dO + (int64_t)head * d.ldo.head), q_ld, (unsigned)d.ldo.row * 4, g4);
+  of.load(uniform_gptr(O + (int64_t)head * d.lo.head), q_ld, (unsigned)d.lo.row * 4, g4);     // for delta only
   const float lse_i = q_row < d.nq ? lse[(int64_t)head * d.nq + q_ld] : -INFINITY;
   float del = 0.f;
 #pragma unroll
   for (int y = 0; y < H / 16; ++y)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) del = fmaf(gf.v[y][e], kn.v[y][e], del);
+    for (int e = 0; e < 4; ++e) del = fmaf(gf[0].v[y][e], of.v[y][e], del);
   del = row_sum(del);
   if (kl == 0 && part == 0 && g4 == 0 && q_row < d.nq) delta[(int64_t)head * d.nq + q_row] = del;
 
   const int blk_last = min(q0 + BLK, d.nq) - 1;
   auto seg_blocks = [&](int s) { return (vis_count(d, g, blk_last, s) + BLK - 1) / BLK; };
   Walk w;
-  w.open(0, g.n, seg_blocks);
-  w.advance(part * KL + kl, g.n, seg_blocks);
+  w.open(g, seg_blocks);
+  w.advance(part * KL + kl, g, seg_blocks);
   Out<H> dq;
   dq.zero();
-  auto load_k = [&](const Walk& x) {
-    kn.load(kb, g.seg[x.s].start + min(x.j * BLK + l15, g.seg[x.s].rows - 1), k_row, g4);
-  };
-  if (w.s < g.n) load_k(w);
-  while (w.s < g.n) {
-    const int s = w.s, k0 = w.j * BLK, rows = g.seg[s].rows, start = g.seg[s].start;
-    vn.load(vb, start + min(k0 + l15, rows - 1), v_row, g4);
-    __builtin_amdgcn_sched_barrier(0);
-    const f32x4 sc = dot_rows<H>(kn, qf);
-    Cols<H> kt[4];
+  Tile<H> kt, vt;
+  kt.init((lds_t)smem + 2 * kl * Tile<H>::BYTES, l15, g4);
+  vt.init((lds_t)smem + (2 * kl + 1) * Tile<H>::BYTES, l15, g4);
+  Cols<H> kc[4], vc[4];
+  auto load = [&](const Walk& x) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) kt[r].load(kb, start + min(k0 + 4 * g4 + r, rows - 1), k_row, l15);
+    for (int r = 0; r < 4; ++r) {
+      const unsigned row = x.start + min(x.j * BLK + 4 * g4 + r, x.rows - 1);
+      kc[r].load(kb, row, k_row, l15);
+      vc[r].load(vb, row, v_row, l15);
+    }
+  };
+  int vis_s = -1, my_vis = 0;                         // keys of sub-block vis_s that this lane's row sees
+  if (w.s < g.n) load(w);
+  while (w.s < g.n) {
+    const int k0 = w.j * BLK;
+    if (w.s != vis_s) { vis_s = w.s; my_vis = vis_count(d, g, q_ld, w.s); }
+    kt.store(kc, l15);
+    vt.store(vc, l15);
+    w.advance(lanes, g, seg_blocks);
+    if (w.s < g.n) load(w);
     __builtin_amdgcn_sched_barrier(0);
-    f32x4 ds = dot_rows<H>(vn, gf);
-    const int my_vis = vis_count(d, g, q_ld, s);
-    w.advance(lanes, g.n, seg_blocks);
-    if (w.s < g.n) load_k(w);
-    __builtin_amdgcn_sched_barrier(0);
+    f32x4 sx[1], dx[1];
+    dot_rows<H, 1>(sx, kt, qf);
+    dot_rows<H, 1>(dx, vt, gf);
+    const f32x4 sc = sx[0];
+    f32x4 ds = dx[0];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const bool vis = lse_i != -INFINITY && k0 + 4 * g4 + r < my_vis;
       const float p = vis ? fast_exp2(fmaf(sc[r], d.scale, -lse_i) * kLog2e) : 0.f;
       ds[r] = p * (ds[r] - del);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) dq.contract(kt[r], ds[r]);
+    contract_tile(dq, kt, ds, l15);
   }
   if constexpr (KL > 1) {
     merge_lanes<KL, H / 16>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& { return dq.acc[i]; });
@@ -448,7 +545,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
 // ---------------------------------------------------------------- backward: dK, dV
 // Owns 16 keys of a key/value head per workgroup and walks the query rows of all its group's query
 // heads, 16 at a time: S = Q K^T and dP = dO V^T leave a lane holding 4 queries of ONE key.
-template <int H, int KL>
+template <int H>
 __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void bwd_dkdv_f32_kernel(
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, const float* __restrict__ dO, const float* __restrict__ lse,
@@ -470,9 +567,9 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   const unsigned q_row = (unsigned)d.lq.row * 4, g_row = (unsigned)d.ldo.row * 4;
   const unsigned q_head = (unsigned)d.lq.head * 4, g_head = (unsigned)d.ldo.head * 4;
 
-  Nat<H> kf, vf;
-  kf.load(uniform_gptr(K + (int64_t)head * d.lk.head), k_ld, (unsigned)d.lk.row * 4, g4);
-  vf.load(uniform_gptr(V + (int64_t)head * d.lv.head), k_ld, (unsigned)d.lv.row * 4, g4);
+  Nat<H> kf[1], vf[1];
+  kf[0].load(uniform_gptr(K + (int64_t)head * d.lk.head), k_ld, (unsigned)d.lk.row * 4, g4);
+  vf[0].load(uniform_gptr(V + (int64_t)head * d.lv.head), k_ld, (unsigned)d.lv.row * 4, g4);
 
   // first query row that sees this lane's key, and the first that sees any of the block's keys
   auto first_row = [&](int s, int k) -> int {
@@ -495,70 +592,52 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   Out<H> dk, dv;
   dk.zero();
   dv.zero();
-  Nat<H> x, y;                                        // operands, each loaded one contraction ahead
+  Tile<H> qt, gt;
+  qt.init((lds_t)smem + 2 * kl * Tile<H>::BYTES, l15, g4);
+  gt.init((lds_t)smem + (2 * kl + 1) * Tile<H>::BYTES, l15, g4);
+  Cols<H> qc[4], gc[4];                               // the rows of the step to come, and their statistics
+  float ln[4], dn[4];
   // position of walk step n: query head (inside the group) and first row
   const int n0 = part * KL + kl;
   int qh = 0, rb = n0;                                // of the next step to be loaded
   auto wrap = [&]() { while (rb >= nblk && qh < g.group) { rb -= nblk; ++qh; } };
   if (nblk > 0) wrap();
-  auto load_q = [&]() {
-    const unsigned base = qh * q_head;
-    const unsigned row = min((b0 + rb) * BLK + l15, d.nq - 1);
-    const unsigned off = base + __umul24(row, q_row) + 16 * g4;
+  auto load = [&]() {
 #pragma unroll
-    for (int i = 0; i < H / 16; ++i) x.v[i] = gload<f32x4>(qb, off + 64 * i);
-  };
-  if (n0 < total) load_q();
-  for (int n = n0; n < total; n += lanes) {
-    const int i0 = (b0 + rb) * BLK, ch = qh;
-    {
-      const unsigned row = min(i0 + l15, d.nq - 1);
-      const unsigned off = ch * g_head + __umul24(row, g_row) + 16 * g4;
-#pragma unroll
-      for (int i = 0; i < H / 16; ++i) y.v[i] = gload<f32x4>(gb, off + 64 * i);
+    for (int r = 0; r < 4; ++r) {
+      const unsigned row = min((b0 + rb) * BLK + 4 * g4 + r, d.nq - 1);
+      qc[r].load(qb + qh * q_head, row, q_row, l15);
+      gc[r].load(gb + qh * g_head, row, g_row, l15);
+      ln[r] = lse_b[qh * d.nq + row];
+      dn[r] = del_b[qh * d.nq + row];
     }
+  };
+  if (n0 < total) load();
+  for (int n = n0; n < total; n += lanes) {
+    const int i0 = (b0 + rb) * BLK;
     float ls[4], de[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = ch * d.nq + min(i0 + 4 * g4 + r, d.nq - 1);
-      ls[r] = lse_b[i];
-      de[r] = del_b[i];
-    }
+    for (int r = 0; r < 4; ++r) { ls[r] = ln[r]; de[r] = dn[r]; }
+    qt.store(qc, l15);
+    gt.store(gc, l15);
+    rb += lanes;
+    wrap();
+    if (n + lanes < total) load();
     __builtin_amdgcn_sched_barrier(0);
-    f32x4 p = dot_rows<H>(x, kf);
-    __builtin_amdgcn_sched_barrier(0);                // (x's registers are free from here on)
-    Cols<H> gt[4], qt[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const unsigned row = min(i0 + 4 * g4 + r, d.nq - 1);
-      gt[r].load(gb + ch * g_head, row, g_row, l15);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    f32x4 ds = dot_rows<H>(y, vf);
+    f32x4 px[1], dx[1];
+    dot_rows<H, 1>(px, qt, kf);
+    dot_rows<H, 1>(dx, gt, vf);
+    f32x4 p, ds;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = i0 + 4 * g4 + r;
       const bool vis = i < d.nq && i >= my_first && ls[r] != -INFINITY;
-      p[r] = vis ? fast_exp2(fmaf(p[r], d.scale, -ls[r]) * kLog2e) : 0.f;
-      ds[r] = p[r] * (ds[r] - de[r]);
+      p[r] = vis ? fast_exp2(fmaf(px[0][r], d.scale, -ls[r]) * kLog2e) : 0.f;
+      ds[r] = p[r] * (dx[0][r] - de[r]);
     }
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {                     // (each row of dO makes room for one of Q)
-      dv.contract(gt[r], p[r]);
-      const unsigned row = min(i0 + 4 * g4 + r, d.nq - 1);
-      qt[r].load(qb + ch * q_head, row, q_row, l15);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    rb += lanes;
-    wrap();
-    dk.contract(qt[0], ds[0]);
-    dk.contract(qt[1], ds[1]);
-    __builtin_amdgcn_sched_barrier(0);
-    if (n + lanes < total) load_q();
-    __builtin_amdgcn_sched_barrier(0);
-    dk.contract(qt[2], ds[2]);
-    dk.contract(qt[3], ds[3]);
+    contract_tile(dv, gt, p, l15);
+    contract_tile(dk, qt, ds, l15);
   }
   if constexpr (KL > 1) {
     merge_lanes<KL, H / 8>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& {
@@ -573,89 +652,79 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   }
 }
 
-template <int H, int RT, int KL>
+// LDS of a workgroup: the wavefronts' tiles, over which their results are merged at the end
+constexpr int most(int a, int b) { return a > b ? a : b; }
+template <int H, int RT>
+constexpr int fwd_lds() { return most(KL * Tile<H>::BYTES, KL / 2 * RT * (H / 16 + 1) * 1024); }
+template <int H>
+constexpr int dq_lds() { return most(2 * KL * Tile<H>::BYTES, KL / 2 * (H / 16) * 1024); }
+template <int H>
+constexpr int dkdv_lds() { return most(2 * KL * Tile<H>::BYTES, KL / 2 * (H / 8) * 1024); }
+static_assert(dkdv_lds<128>() <= 80 * 1024 && dq_lds<128>() <= 80 * 1024 && fwd_lds<128, 2>() <= 80 * 1024,
+              "two workgroups per compute unit");
+
+template <int H, int RT>
 hipError_t fwd_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                   float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
-  constexpr int lds = KL > 1 ? KL / 2 * RT * (H / 16 + 1) * 1024 : 0;
-  static_assert(lds <= 80 * 1024, "two workgroups per compute unit");
-  dim3 grid(xcd_grid(d.heads / g.group * g.parts, g.group * ((d.nq + BLK * RT - 1) / (BLK * RT)))), block(64 * KL);
-  A2D_LAUNCH((fwd_f32_kernel<H, RT, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
+  constexpr int lds = fwd_lds<H, RT>(), rows = BLK * RT;
+  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_f32_kernel<H, RT>), lds);
+  if (e != hipSuccess) return e;
+  dim3 grid(xcd_grid(d.heads / g.group * g.parts, g.group * ((d.nq + rows - 1) / rows))), block(64 * KL);
+  A2D_LAUNCH((fwd_f32_kernel<H, RT>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
              (const float*)V, O_part, m, l, in);
   return hipGetLastError();
 }
 
-template <int H, int KL>
-hipError_t dq_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V, const void* O,
-                 const void* dO, const float* lse, float* delta, float* dQ, hipStream_t s) {
-  constexpr int lds = KL / 2 * (H / 16) * 1024;
-  dim3 grid(xcd_grid(d.heads / g.group * g.parts, g.group * ((d.nq + BLK - 1) / BLK))), block(64 * KL);
-  A2D_LAUNCH((bwd_dq_f32_kernel<H, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
-             (const float*)V, (const float*)O, (const float*)dO, lse, delta, dQ);
-  return hipGetLastError();
-}
-
-template <int H, int KL>
-hipError_t dkdv_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
-                   const void* dO, const float* lse, const float* delta, float* dK, float* dV, hipStream_t s) {
-  constexpr int lds = KL / 2 * (H / 8) * 1024;
-  dim3 grid(xcd_grid(d.heads / g.group * g.parts, (d.nkv + BLK - 1) / BLK)), block(64 * KL);
-  A2D_LAUNCH((bwd_dkdv_f32_kernel<H, KL>), grid, block, lds, s, d, g, (const float*)Q, (const float*)K,
-             (const float*)V, (const float*)dO, lse, delta, dK, dV);
-  return hipGetLastError();
-}
-
-// Key lanes of a workgroup: four, eight when that still leaves compute units without two workgroups'
-// worth of wavefronts (8 wavefronts fill a compute unit's SIMDs twice)
-bool eight_lanes(int64_t workgroups, int cus) { return workgroups <= cus; }
-
-enum { F32_ROWS32 = 0, F32_LANES4 = 1, F32_LANES8 = 2 };   // <2, 4>, <1, 4>, <1, 8>
+enum { F32_ROWS16 = 0, F32_ROWS32 = 1 };
 
 template <int H>
 hipError_t fwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                  float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
-  if (g.form == F32_ROWS32) return fwd_go<H, 2, 4>(d, g, Q, K, V, O_part, m, l, in, s);
-  if (g.form == F32_LANES8) return fwd_go<H, 1, 8>(d, g, Q, K, V, O_part, m, l, in, s);
-  return fwd_go<H, 1, 4>(d, g, Q, K, V, O_part, m, l, in, s);
+  return g.form == F32_ROWS32 ? fwd_go<H, 2>(d, g, Q, K, V, O_part, m, l, in, s)
+                              : fwd_go<H, 1>(d, g, Q, K, V, O_part, m, l, in, s);
 }
 
 template <int H>
 hipError_t bwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                  const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK, float* dV,
-                 const BwdParts& parts, int cus, hipStream_t s) {
+                 const BwdParts& parts, hipStream_t s) {
   SegList gq = g, gk = g;
   gq.parts = parts.q;
   if (parts.q > 1) gq.acc = 0;                       // (the sum over the parts adds)
   gk.parts = parts.kv;
-  const hipError_t e = eight_lanes((int64_t)d.heads * ((d.nq + 15) / 16) * parts.q, cus)
-                           ? dq_go<H, 8>(d, gq, Q, K, V, O, dO, lse, delta, dQ, s)
-                           : dq_go<H, 4>(d, gq, Q, K, V, O, dO, lse, delta, dQ, s);
+  hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_f32_kernel<H>), dq_lds<H>());
+  if (e == hipSuccess) e = ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dkdv_f32_kernel<H>), dkdv_lds<H>());
   if (e != hipSuccess) return e;
-  return eight_lanes((int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16) * parts.kv, cus)
-             ? dkdv_go<H, 8>(d, gk, Q, K, V, dO, lse, delta, dK, dV, s)
-             : dkdv_go<H, 4>(d, gk, Q, K, V, dO, lse, delta, dK, dV, s);
+  const dim3 block(64 * KL);
+  A2D_LAUNCH((bwd_dq_f32_kernel<H>), dim3(xcd_grid(d.heads / g.group * gq.parts, g.group * ((d.nq + BLK - 1) / BLK))), block,
+             dq_lds<H>(), s, d, gq, (const float*)Q, (const float*)K, (const float*)V, (const float*)O, (const float*)dO,
+             lse, delta, dQ);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  A2D_LAUNCH((bwd_dkdv_f32_kernel<H>), dim3(xcd_grid(d.heads / g.group * gk.parts, (d.nkv + BLK - 1) / BLK)), block,
+             dkdv_lds<H>(), s, d, gk, (const float*)Q, (const float*)K, (const float*)V, (const float*)dO, lse, delta, dK,
+             dV);
+  return hipGetLastError();
 }
 
-// The walk of 16-row blocks as a model: a turn is one wavefront per SIMD (4 * cus of them), a step
-// of `contractions` contractions over H takes 32 H / 4 cycles each (at about 2.3 GHz).
-constexpr double kF32FixedUs = 4.0;
-WalkModel f32_walk(int64_t blocks, double steps, int lanes, int contractions, int hdim, int cus) {
-  // (KL key lanes: a workgroup is lanes / 4 turns' worth of wavefronts)
-  return WalkModel{blocks, lanes <= 4 ? cus : cus / 2, steps / lanes, steps / lanes,
-                   contractions * hdim * 8 / 2.1e3, kF32FixedUs, 0, 0};
+// The walk of 16-row blocks as a model: a turn is one wavefront per SIMD, a step of `contractions`
+// contractions over H takes 8 H cycles each (at about 2.1 GHz).
+WalkModel f32_walk(int64_t blocks, double steps, int contractions, int hdim, int cus) {
+  return WalkModel{blocks, cus, steps / KL, steps / KL, contractions * hdim * 8 / 2.1e3, 4.0, 0, 0};
 }
 
 }  // namespace
 
 // 32 rows per workgroup halve the operand traffic per MFMA; 16 rows when those come to fewer than
-// four workgroups per compute unit, with eight key lanes (or parts) when those are few
+// four workgroups per compute unit
 void plan_fwd_f32(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t b32 = (int64_t)d.heads * ((d.nq + 31) / 32), b16 = (int64_t)d.heads * ((d.nq + 15) / 16);
   g->parts = 1;
-  if (b32 >= 4 * (int64_t)cus) { g->form = F32_ROWS32; return; }
+  g->form = b32 >= 4 * (int64_t)cus ? F32_ROWS32 : F32_ROWS16;
+  if (g->form == F32_ROWS32) return;
   const double steps = (double)visible_keys(d, *g, d.nq - 1) / BLK + 1;
   const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 5e6;
-  g->parts = best_parts(f32_walk(b16, steps, 4, 2, d.hdim, cus), cap, 5.0, part_us, nullptr);
-  g->form = eight_lanes(b16 * g->parts, cus) ? F32_LANES8 : F32_LANES4;
+  g->parts = best_parts(f32_walk(b16, steps, 2, d.hdim, cus), cap, 5.0, part_us, nullptr);
 }
 
 BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q) {
@@ -663,9 +732,10 @@ BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap
   const double sq = (double)visible_keys(d, g, d.nq - 1) / BLK + 1, sk = (double)g.group * ((d.nq + 15) / 16);
   BwdParts p;
   p.form = 0;
-  p.q = best_parts(f32_walk(bq, sq, 4, 3, d.hdim, cus), cap_q, 5.0, (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
-  p.kv = best_parts(f32_walk(bk, sk, 4, 4, d.hdim, cus), cap_kv, 5.0,
+  p.kv = best_parts(f32_walk(bk, sk, 4, d.hdim, cus), cap_kv, 5.0,
                     (double)d.heads / g.group * d.nkv * d.hdim * 16 / 5e6, nullptr);
+  p.q = best_parts(f32_walk(bq, sq, 3, d.hdim, cus), cap_q, p.kv > 1 ? 1.0 : 5.0,
+                   (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
   return p;
 }
 
@@ -682,14 +752,11 @@ hipError_t launch_fwd_f32(const a2d_tile_desc& d, const SegList& g, const void* 
 hipError_t launch_bwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                           const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK,
                           float* dV, const BwdParts& parts, hipStream_t s) {
-  int cus = 0;
-  const hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
   switch (d.hdim) {
-    case 128: return bwd_h<128>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, cus, s);
-    case 96: return bwd_h<96>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, cus, s);
-    case 80: return bwd_h<80>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, cus, s);
-    default: return bwd_h<64>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, cus, s);
+    case 128: return bwd_h<128>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s);
+    case 96: return bwd_h<96>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s);
+    case 80: return bwd_h<80>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s);
+    default: return bwd_h<64>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s);
   }
 }
 
