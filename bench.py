@@ -685,7 +685,7 @@ def rectangular_tiles(a2d, synth, w, scale):
     mk = lambda rows: torch.randn(heads, rows, H, device="cuda", generator=gen).to(torch.bfloat16)
     out = {"what": "%d heads, unmasked tiles of equal area, Nq x Nkv; fwd_wg / dq_wg = query rows per workgroup of the "
                    "forward / dQ kernels (256: eight wavefronts; 128: four, or eight in two key lanes when at most one block "
-                   "comes to a compute unit), dkdv_wgs = workgroups of 128 keys" % heads,
+                   "comes to a compute unit), dkdv_wgs = blocks of 128 keys (two to a workgroup where there are many)" % heads,
            "cases": []}
     for nq, nkv in ((4096, 4096), (2048, 8192), (8192, 2048), (1024, 16384), (16384, 1024)):
         Q, dO, K, V = mk(nq), mk(nq), mk(nkv), mk(nkv)

@@ -1,0 +1,98 @@
+// Shared by the bf16 backward kernels (a2d_bwd_mfma.hip, a2d_bwd_wide.hip).
+#pragma once
+#include "a2d_mfma.hpp"
+
+namespace a2d {
+namespace mfma {
+
+// stores a transposed accumulator (lane = one output row, registers = 4-column groups)
+// (add: onto what the row already holds)
+// CT column tiles of 32; pieces whose columns lie past the head size h are skipped
+template <int CT>
+__device__ __forceinline__ void store_acc_t(float* __restrict__ out_row, const f32x16 (&acc)[CT],
+                                            int half, float mul, int h, bool add = false) {
+#pragma unroll
+  for (int ht = 0; ht < CT; ++ht)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if (32 * ht + 8 * g + 4 * half >= h) continue;
+      f32x4 v = {acc[ht][4 * g] * mul, acc[ht][4 * g + 1] * mul, acc[ht][4 * g + 2] * mul,
+                 acc[ht][4 * g + 3] * mul};
+      f32x4* p = reinterpret_cast<f32x4*>(out_row + 32 * ht + 8 * g + 4 * half);
+      if (add) {
+        const f32x4 o = *p;
+        v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
+      }
+      *p = v;
+    }
+}
+
+__device__ __forceinline__ f32x4 lds_load_f32x4(unsigned addr) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>((uintptr_t)addr);
+}
+
+// natural fragment x of a dual tile (rows RB .. RB+31 relative to the per-lane bases in `a`)
+template <int X>
+__device__ __forceinline__ bf16x8 dual_nat(const DualAddr& a, int extra) {
+  return lds_load_b128(((X & 1) ? a.nat_o : a.nat_e) + 64 * (X >> 1) + extra);
+}
+
+// A step of the dK/dV kernels: BQ query rows, staged through LDS as a buffer { Q tile, dO tile } (dual
+// layout) and two statistics per row
+constexpr int BQ = 32;
+constexpr int DK_TILE = BQ * DUAL_LD;
+constexpr int DK_BUF = 2 * DK_TILE;
+constexpr int DK_STAT_BUF = 2 * BQ * 4;
+
+// ---- dS hand-over to the dQ kernel (optional).  The dK/dV kernel can leave dS (bf16, already
+// multiplied out: P o (dP - delta)) in a workspace, so that the dQ kernel is a plain contraction
+// dQ = scale dS K instead of recomputing S and dP.  Workspace layout: per head, per 32-row tile rt,
+// per 64-key block kb one 4 KiB tile [piece T = 0, 1 (32 keys each)][u = 0, 1 (16 keys each)]
+// [lane 0..63][8 bf16]: lane (row = lane & 31, half = lane >> 5) holds, for the 16 keys
+// 64 kb + 32 T + 16 u + .., the keys 4 half + {0..3} and 8 + 4 half + {0..3} - exactly the B
+// fragment of the dQ kernel's MFMA, so the consumer reads it with one coalesced 16-byte load per
+// lane and the producer writes it with one coalesced 16-byte store per lane.
+constexpr int DS_TILE_BYTES = 4096;
+__host__ __device__ inline int ds_row_tiles(int nq) { return (nq + 31) / 32; }
+__host__ __device__ inline int ds_key_blocks(int nkv) { return (nkv + 63) / 64; }
+__host__ __device__ inline size_t ds_head_bytes(int nq, int nkv) {
+  return (size_t)ds_row_tiles(nq) * ds_key_blocks(nkv) * DS_TILE_BYTES;
+}
+
+typedef __attribute__((address_space(1))) char* gwptr_t;
+__device__ __forceinline__ gwptr_t uniform_gwptr(void* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<gwptr_t>(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ void gstore_b128(gwptr_t base, unsigned byte_off, bf16x8 v) {
+  // streamed once, read back by another kernel: keep it from displacing the Q / dO tiles in L2
+  __builtin_nontemporal_store(v, reinterpret_cast<__attribute__((address_space(1))) bf16x8*>(base + byte_off));
+}
+
+// The gradient wave holds dS with lane = key and registers = query rows; the dQ kernel needs
+// lane = query row and registers = keys.  The wave turns its 32 x 32 piece around through LDS (its
+// own mailbox piece, free once the probabilities have been read): each lane writes its four
+// 4-row groups as 8-byte pieces of a [key][row] tile (rows of 72 bytes: conflict-free), and the
+// transposing read returns, per lane, four keys of one row.
+constexpr int DS_TR_LD = 72;
+__device__ __forceinline__ void ds_turn_write(unsigned piece, int l32, int half, const bf16x8 (&bf)[2]) {
+  const unsigned a = piece + l32 * DS_TR_LD + 8 * half;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const u32x4 w = __builtin_bit_cast(u32x4, bf[u]);
+    // register group g = 2u (w.x, w.y) and g = 2u + 1 (w.z, w.w): rows 8g + 4 half + 0..3
+    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * (2 * u))) = u32x2{w[0], w[1]};
+    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * (2 * u + 1))) = u32x2{w[2], w[3]};
+  }
+}
+__device__ __forceinline__ void ds_turn_read(unsigned piece, int lane, bf16x8 (&out)[2]) {
+  const int g16 = lane >> 4, j16 = lane & 15;
+  const unsigned a = piece + (4 * (g16 >> 1) + (j16 >> 2)) * DS_TR_LD + (16 * (g16 & 1) + 4 * (j16 & 3)) * 2;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) out[u] = lds_load_tr(a + 16 * u * DS_TR_LD, a + (16 * u + 8) * DS_TR_LD);
+}
+
+}  // namespace mfma
+}  // namespace a2d

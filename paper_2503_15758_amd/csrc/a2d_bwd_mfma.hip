@@ -32,56 +32,20 @@
 // layout of a2d_mfma.hpp: every fragment address is a per-lane base plus an immediate.
 #include <type_traits>
 
-#include "a2d_mfma.hpp"
+#include "a2d_bwd.hpp"
 
 namespace a2d {
 namespace {
 
 using namespace mfma;
 
-// stores a transposed accumulator (lane = one output row, registers = 4-column groups)
-// (add: onto what the row already holds)
-// CT column tiles of 32; pieces whose columns lie past the head size h are skipped
-template <int CT>
-__device__ __forceinline__ void store_acc_t(float* __restrict__ out_row, const f32x16 (&acc)[CT],
-                                            int half, float mul, int h, bool add = false) {
-#pragma unroll
-  for (int ht = 0; ht < CT; ++ht)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (32 * ht + 8 * g + 4 * half >= h) continue;
-      f32x4 v = {acc[ht][4 * g] * mul, acc[ht][4 * g + 1] * mul, acc[ht][4 * g + 2] * mul,
-                 acc[ht][4 * g + 3] * mul};
-      f32x4* p = reinterpret_cast<f32x4*>(out_row + 32 * ht + 8 * g + 4 * half);
-      if (add) {
-        const f32x4 o = *p;
-        v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
-      }
-      *p = v;
-    }
-}
-
-__device__ __forceinline__ f32x4 lds_load_f32x4(unsigned addr) {
-  return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>((uintptr_t)addr);
-}
-
-// natural fragment x of a dual tile (rows RB .. RB+31 relative to the per-lane bases in `a`)
-template <int X>
-__device__ __forceinline__ bf16x8 dual_nat(const DualAddr& a, int extra) {
-  return lds_load_b128(((X & 1) ? a.nat_o : a.nat_e) + 64 * (X >> 1) + extra);
-}
-
 // ------------------------------------------------------------------ dK, dV
 constexpr int DK_THREADS = 512;
 constexpr int DK_KEYS = 128;      // keys per workgroup
-constexpr int BQ = 32;            // query rows per step
 constexpr int DK_NBUF = 4;        // tile buffers: gradient waves' step, score waves' step, next, incoming
 // LDS: [buf]{ Q tile, dO tile } (dual layout, 32 rows each) | [buf]{ lse*log2e [32], delta [32] } |
 //      (the latter negated) | [slot][pair] probabilities handed from the score wave to the gradient wave (fp32)
-constexpr int DK_TILE = BQ * DUAL_LD;
-constexpr int DK_BUF = 2 * DK_TILE;
 constexpr int DK_STAT = DK_NBUF * DK_BUF;
-constexpr int DK_STAT_BUF = 2 * BQ * 4;
 constexpr int DK_MBOX = DK_STAT + DK_NBUF * DK_STAT_BUF;
 constexpr int DK_MBOX_PIECE = 32 * 32 * 4;
 constexpr int DK_MBOX_SLOT = 4 * DK_MBOX_PIECE;
@@ -214,56 +178,6 @@ __device__ __forceinline__ void dk_second(DkCtx<HD>& cx, bf16x8 (&t)[HD / 32], c
 #undef A2D_FENCE
 #undef A2D_TR
 #undef A2D_NAT
-
-// ---- dS hand-over to the dQ kernel (optional).  The dK/dV kernel can leave dS (bf16, already
-// multiplied out: P o (dP - delta)) in a workspace, so that the dQ kernel is a plain contraction
-// dQ = scale dS K instead of recomputing S and dP.  Workspace layout: per head, per 32-row tile rt,
-// per 64-key block kb one 4 KiB tile [piece T = 0, 1 (32 keys each)][u = 0, 1 (16 keys each)]
-// [lane 0..63][8 bf16]: lane (row = lane & 31, half = lane >> 5) holds, for the 16 keys
-// 64 kb + 32 T + 16 u + .., the keys 4 half + {0..3} and 8 + 4 half + {0..3} - exactly the B
-// fragment of the dQ kernel's MFMA, so the consumer reads it with one coalesced 16-byte load per
-// lane and the producer writes it with one coalesced 16-byte store per lane.
-constexpr int DS_TILE_BYTES = 4096;
-__host__ __device__ inline int ds_row_tiles(int nq) { return (nq + 31) / 32; }
-__host__ __device__ inline int ds_key_blocks(int nkv) { return (nkv + 63) / 64; }
-__host__ __device__ inline size_t ds_head_bytes(int nq, int nkv) {
-  return (size_t)ds_row_tiles(nq) * ds_key_blocks(nkv) * DS_TILE_BYTES;
-}
-
-typedef __attribute__((address_space(1))) char* gwptr_t;
-__device__ __forceinline__ gwptr_t uniform_gwptr(void* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<gwptr_t>(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ void gstore_b128(gwptr_t base, unsigned byte_off, bf16x8 v) {
-  // streamed once, read back by another kernel: keep it from displacing the Q / dO tiles in L2
-  __builtin_nontemporal_store(v, reinterpret_cast<__attribute__((address_space(1))) bf16x8*>(base + byte_off));
-}
-
-// The gradient wave holds dS with lane = key and registers = query rows; the dQ kernel needs
-// lane = query row and registers = keys.  The wave turns its 32 x 32 piece around through LDS (its
-// own mailbox piece, free once the probabilities have been read): each lane writes its four
-// 4-row groups as 8-byte pieces of a [key][row] tile (rows of 72 bytes: conflict-free), and the
-// transposing read returns, per lane, four keys of one row.
-constexpr int DS_TR_LD = 72;
-__device__ __forceinline__ void ds_turn_write(unsigned piece, int l32, int half, const bf16x8 (&bf)[2]) {
-  const unsigned a = piece + l32 * DS_TR_LD + 8 * half;
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const u32x4 w = __builtin_bit_cast(u32x4, bf[u]);
-    // register group g = 2u (w.x, w.y) and g = 2u + 1 (w.z, w.w): rows 8g + 4 half + 0..3
-    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * (2 * u))) = u32x2{w[0], w[1]};
-    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * (2 * u + 1))) = u32x2{w[2], w[3]};
-  }
-}
-__device__ __forceinline__ void ds_turn_read(unsigned piece, int lane, bf16x8 (&out)[2]) {
-  const int g16 = lane >> 4, j16 = lane & 15;
-  const unsigned a = piece + (4 * (g16 >> 1) + (j16 >> 2)) * DS_TR_LD + (16 * (g16 & 1) + 4 * (j16 & 3)) * 2;
-#pragma unroll
-  for (int u = 0; u < 2; ++u) out[u] = lds_load_tr(a + 16 * u * DS_TR_LD, a + (16 * u + 8) * DS_TR_LD);
-}
 
 // HR: head size = row length in memory (80, 96 or 128); the LDS tiles and fragments are laid out
 // for the padded head size HD = padded_head(HR) (96 or 128).
@@ -1212,7 +1126,8 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   if (parts.q > 1) gq.acc = 0;                         // (the sum over the parts adds)
   const bool big = parts.form == DQ_BIG, lanes = parts.form == DQ_LANES;
   if (ph == PREPARE) {
-    e = ensure_dynamic_lds(grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, true, false, BATCH>)
+    e = parts.wide ? launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, ds_ws, s)
+        : ensure_dynamic_lds(grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, true, false, BATCH>)
                                    : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, true, false, BATCH>), DK_LDS);
     if (e != hipSuccess) return e;
     return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 2, BATCH>), 2 * DSQ_LDS)
@@ -1222,7 +1137,9 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   dim3 grid_kv(xcd_grid(d.heads / g.group * parts.kv, (d.nkv + DK_KEYS - 1) / DK_KEYS), tiles);
   const int dq_rows = big ? 256 : 128;
   dim3 grid_q(xcd_grid(d.heads / g.group * parts.q, g.group * ((d.nq + dq_rows - 1) / dq_rows)), tiles);
-  if (grouped)
+  if (parts.wide)
+    e = launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, ds_ws, s);
+  else if (grouped)
     A2D_LAUNCH((bwd_dkdv_kernel<HR, true, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV,
                        (bf16_t*)ds_ws);
@@ -1230,7 +1147,7 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
     A2D_LAUNCH((bwd_dkdv_kernel<HR, false, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV,
                        (bf16_t*)ds_ws);
-  e = hipGetLastError();
+  if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (big)
     A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 1, BATCH>), grid_q, dim3(512), DSQ_LDS, s, d, gq, (const bf16_t*)K,
@@ -1265,7 +1182,7 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
                                         : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, false, true>))
                              : (grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, false, false>)
                                         : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, false, false>));
-    e = ensure_dynamic_lds(dkdv, DK_LDS);
+    e = parts.wide ? launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, nullptr, s) : ensure_dynamic_lds(dkdv, DK_LDS);
     if (e != hipSuccess) return e;
     return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 2>), 2 * DQ_LDS)
                  : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 1>)
@@ -1288,6 +1205,7 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 #define A2D_DKDV(GR, PL)                                                                                          \
   A2D_LAUNCH((bwd_dkdv_kernel<HR, GR, false, PL>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk, (const bf16_t*)Q, \
                      (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV, (bf16_t*)nullptr)
+  if (parts.wide) return launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, nullptr, s);
   if (grouped && plain) A2D_DKDV(true, true);
   else if (grouped) A2D_DKDV(true, false);
   else if (plain) A2D_DKDV(false, true);
@@ -1299,19 +1217,30 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 
 // Parts of the dK/dV and dQ walks where their row blocks leave compute units idle, and the dQ kernels'
 // workgroup shape, as in plan_fwd_mfma.  Steps in microseconds, measured over 30 shapes (1 x 300 x 8000
-// to 32 x 2000 x 2700): 32 query rows against 128 keys; 64 keys against 256 query rows, recomputing
-// and from dS; H = 64, 96, 128.  The choice for dK/dV does not depend on `ds`, so that the two dQ
-// paths give the same dK, dV.
+// to 32 x 2000 x 2700): 32 query rows against 128 keys, and against 256; 64 keys against 256 query
+// rows, recomputing and from dS; H = 64, 96, 128.  Half as many workgroups of 256 keys pay from the point where
+// those of 128 no longer run at once.  The choice for dK/dV does not depend on `ds`, so that the two dQ paths
+// give the same dK, dV.
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q) {
-  constexpr double kKvUs[3] = {0.75, 0.87, 0.9}, kDqUs[3] = {1.6, 1.75, 2.1}, kDsqUs[3] = {0.7, 0.8, 0.85};
+  constexpr double kKvUs[3] = {0.78, 0.9, 1.0}, kWideUs[3] = {1.0, 1.2, 1.5};
+  constexpr double kDqUs[3] = {1.6, 1.75, 2.1}, kDsqUs[3] = {0.7, 0.8, 0.85};
   const int hx = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, kv_heads = d.heads / g.group, tiles = g.b.n ? g.b.n : 1;
   const bool uneven = g.by_size || g.b.n;
   const double seen = mean_visible_keys(d, g);
   BwdParts p;
   const double rows = (double)g.group * ((d.nq + BQ - 1) / BQ);
-  const WalkModel kv = {(int64_t)kv_heads * tiles * ((d.nkv + DK_KEYS - 1) / DK_KEYS), cus,
-                        uneven ? rows * seen / d.nkv + 1 : rows, rows, kKvUs[hx], 8.0, 0, 0};
-  p.kv = best_parts(kv, cap_kv, g.b.n ? 0.0 : 4.0, (double)tiles * kv_heads * d.nkv * d.hdim * 16 / 4.5e6, nullptr);
+  const double kv_part_us = (double)tiles * kv_heads * d.nkv * d.hdim * 16 / 4.5e6, kv_merge_us = g.b.n ? 0.0 : 4.0;
+  const double kv_mean = uneven ? rows * seen / d.nkv + 1 : rows;
+  double kv_us[2];
+  int kv_parts[2];
+  for (int w = 0; w < 2; ++w) {                        // 128 keys per workgroup, 256
+    const int keys = w ? 256 : DK_KEYS;
+    const WalkModel kv = {(int64_t)kv_heads * tiles * ((d.nkv + keys - 1) / keys), cus, kv_mean, rows,
+                          (w ? kWideUs : kKvUs)[hx], w ? 10.0 : 8.0, 0, 0};
+    kv_parts[w] = best_parts(kv, cap_kv, kv_merge_us, kv_part_us, &kv_us[w]);
+  }
+  p.wide = kv_us[1] < kv_us[0] && d.scale > 1e-30f;    // (it takes lse / scale, which has to stay finite)
+  p.kv = kv_parts[p.wide];
   const double most = (double)visible_keys(d, g, d.nq - 1) / BKS + 0.2, mean = uneven ? seen / BKS + 0.2 : most;
   const double step = ds ? kDsqUs[hx] : kDqUs[hx], fixed = 7.0;
   const int64_t heads = (int64_t)d.heads * tiles, b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);

@@ -229,7 +229,7 @@ void plan_fwd_f32(const a2d_tile_desc& d, SegList* g, int cus, int cap);
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap);
 // Parts of the two kernels of a backward tile, each at most its cap, and the dQ kernel's workgroup shape
 struct BwdParts {
-  int kv, q, form;
+  int kv, q, form, wide;     // wide: dK/dV in workgroups of 256 keys (launch_dkdv_wide)
 };
 BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q);
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q);
@@ -261,6 +261,10 @@ bool bwd_mfma_supported(const a2d_tile_desc& d);
 // ds_ws: NULL, or a workspace of bwd_ds_bytes(d, g) (> 0) bytes through which the dK/dV kernel
 // hands dS to a contraction-only dQ kernel (instead of the dQ kernel recomputing S and dP)
 size_t bwd_ds_bytes(const a2d_tile_desc& d, const SegList& g);
+// the dK/dV kernel of 256-key workgroups; dS as in launch_bwd_mfma, NULL or the workspace
+hipError_t launch_dkdv_wide(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
+                            const void* V, const void* dO, const float* lse, const float* delta, float* dK, float* dV,
+                            void* dS, hipStream_t s);
 // (parts > 1: the outputs are the partial buffers, [parts][heads][rows][H] each)
 hipError_t launch_bwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                            const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ,

@@ -731,7 +731,7 @@ BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap
   const int64_t bq = (int64_t)d.heads * ((d.nq + 15) / 16), bk = (int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16);
   const double sq = (double)visible_keys(d, g, d.nq - 1) / BLK + 1, sk = (double)g.group * ((d.nq + 15) / 16);
   BwdParts p;
-  p.form = 0;
+  p.form = p.wide = 0;
   p.kv = best_parts(f32_walk(bk, sk, 4, d.hdim, cus), cap_kv, 5.0,
                     (double)d.heads / g.group * d.nkv * d.hdim * 16 / 5e6, nullptr);
   p.q = best_parts(f32_walk(bq, sq, 3, d.hdim, cus), cap_q, p.kv > 1 ? 1.0 : 5.0,

@@ -105,7 +105,8 @@ def collect(args):
 def short_name(k):
     m = re.match(r"_ZN3a2d12_GLOBAL__N_1\d+([a-z_0-9]+kernel)", k) or \
         re.search(r"a2d::\(anonymous namespace\)::([a-z_0-9]+kernel)", k)
-    return m.group(1) if m else None
+    # the two forms of the dK/dV kernel (128 and 256 keys per workgroup) are one entry
+    return m.group(1).replace("bwd_dkdv_wide_", "bwd_dkdv_") if m else None
 
 
 def _find(out_dir, pattern):

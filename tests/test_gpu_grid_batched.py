@@ -21,6 +21,8 @@ CASES = [
     (64, 64, 2048, 2, 64, False, "cyclic", False),    # dS of three of the four tiles fits the workspace
     (2, 2, 700, 2, 128, True, "contiguous", False),   # few tiles: the walks are split
     (8, 1, 90, 4, 96, True, "cyclic", False),         # ... over the heads of a group
+    (30, 30, 300, 3, 128, True, "contiguous", False),  # dK / dV in workgroups of 256 keys
+    (60, 30, 270, 2, 80, True, "cyclic", True),
 ]
 
 
