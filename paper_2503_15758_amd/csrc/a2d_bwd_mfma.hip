@@ -1216,17 +1216,19 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 }  // namespace
 
 // Parts of the dK/dV and dQ walks where their row blocks leave compute units idle, and the dQ kernels'
-// workgroup shape, as in plan_fwd_mfma.  Steps in microseconds, measured over 30 shapes (1 x 300 x 8000
-// to 32 x 2000 x 2700): 32 query rows against 128 keys, and against 256; 64 keys against 256 query
-// rows, recomputing and from dS; H = 64, 96, 128.  Half as many workgroups of 256 keys pay from the point where
-// those of 128 no longer run at once.  The choice for dK/dV does not depend on `ds`, so that the two dQ paths
-// give the same dK, dV.
+// workgroup shape, as in plan_fwd_mfma.  Steps in microseconds, measured over 30 unmasked shapes (1 x 300 x
+// 8000 to 32 x 2000 x 2700) and 44 causal ones: 32 query rows against 128 keys, and against 256; 64 keys
+// against 256 query rows, recomputing and from dS; H = 64, 96, 128.  Half as many workgroups of 256 keys
+// pay from the point where those of 128 no longer run at once.  The choice for dK/dV does not depend on
+// `ds`, so that the two dQ paths give the same dK, dV.
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q) {
-  constexpr double kKvUs[3] = {0.78, 0.9, 1.0}, kWideUs[3] = {1.0, 1.2, 1.5};
+  constexpr double kKvUs[3] = {0.75, 0.85, 1.0}, kWideUs[3] = {1.0, 1.2, 1.5};
   constexpr double kDqUs[3] = {1.6, 1.75, 2.1}, kDsqUs[3] = {0.7, 0.8, 0.85};
   const int hx = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, kv_heads = d.heads / g.group, tiles = g.b.n ? g.b.n : 1;
   const bool uneven = g.by_size || g.b.n;
-  const double seen = mean_visible_keys(d, g);
+  double of_rows[8];                                   // keys that rows see
+  const double seen = mean_visible_keys(d, g, of_rows);
+  const double* sorted = g.by_size && !g.b.n ? of_rows : nullptr;
   BwdParts p;
   const double rows = (double)g.group * ((d.nq + BQ - 1) / BQ);
   const double kv_part_us = (double)tiles * kv_heads * d.nkv * d.hdim * 16 / 4.5e6, kv_merge_us = g.b.n ? 0.0 : 4.0;
@@ -1236,7 +1238,7 @@ BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cu
   for (int w = 0; w < 2; ++w) {                        // 128 keys per workgroup, 256
     const int keys = w ? 256 : DK_KEYS;
     const WalkModel kv = {(int64_t)kv_heads * tiles * ((d.nkv + keys - 1) / keys), cus, kv_mean, rows,
-                          (w ? kWideUs : kKvUs)[hx], w ? 10.0 : 8.0, 0, 0};
+                          (w ? kWideUs : kKvUs)[hx], w ? 10.0 : 8.0, 0, 0, nullptr, 0};
     kv_parts[w] = best_parts(kv, cap_kv, kv_merge_us, kv_part_us, &kv_us[w]);
   }
   p.wide = kv_us[1] < kv_us[0] && d.scale > 1e-30f;    // (it takes lse / scale, which has to stay finite)
@@ -1245,9 +1247,9 @@ BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cu
   const double step = ds ? kDsqUs[hx] : kDqUs[hx], fixed = 7.0;
   const int64_t heads = (int64_t)d.heads * tiles, b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
   const double part_us = (double)heads * d.nq * d.hdim * 8 / 4.5e6;
-  const WalkModel q[3] = {{b256, cus, mean, most, step, fixed, 0, 0},
-                          {b128, cus, mean / 2, most / 2, step * 1.17, fixed + 0.5, 0, 0},
-                          {b128, cus, mean, most, step * 0.8, fixed, step * 1.06, fixed + 0.5}};
+  const WalkModel q[3] = {{b256, cus, mean, most, step, fixed, 0, 0, sorted, 1.0 / BKS},
+                          {b128, cus, mean / 2, most / 2, step * 1.2, fixed + 0.5, 0, 0, sorted, 0.5 / BKS},
+                          {b128, cus, mean, most, step * 0.74, fixed, step, fixed + 0.5, nullptr, 0}};
   double least = 0;
   for (int f = 0; f < 3; ++f) {
     double t;

@@ -186,6 +186,8 @@ struct WalkModel {
   double mean, most;       // steps of a block's walk: on average, the longest
   double step, fixed;      // time of a step, of everything else in a workgroup
   double pair_step, pair_fixed;   // the same of two workgroups that share a slot (0: a slot holds one)
+  const double* sorted;    // the steps at 8 places, longest first, as multiples of 1 / `per` (NULL: not known)
+  double per;
 };
 inline double walk_time(const WalkModel& w, int parts) {
   const auto len = [&](double steps, double step, double fixed) {
@@ -193,7 +195,8 @@ inline double walk_time(const WalkModel& w, int parts) {
     return (n < 1.0 ? 1.0 : n) * step + fixed;
   };
   const int64_t wgs = w.blocks * parts;
-  if (wgs <= w.slots) return len(w.most, w.step, w.fixed);
+  // (uneven walks on more than half of the chip: the longest one runs at the clock of a busy chip)
+  if (wgs <= w.slots) return len(w.most, w.step, w.fixed) * (w.mean < w.most && parts == 1 && 2 * wgs > w.slots ? 1.05 : 1.0);
   const int64_t turns = (wgs + w.slots - 1) / w.slots;
   const bool pairs = w.pair_step > 0;
   if (w.mean >= w.most)
@@ -201,7 +204,12 @@ inline double walk_time(const WalkModel& w, int parts) {
                  : turns * len(w.most, w.step, w.fixed);
   const double each = pairs ? 0.5 * len(w.mean, w.pair_step, w.pair_fixed) : len(w.mean, w.step, w.fixed);
   const double even = ((double)wgs / w.slots + 0.5) * each;               // longest first: half a workgroup of tail
-  const double longest = len(w.most, pairs ? w.pair_step : w.step, w.fixed);
+  double longest = len(w.most, pairs ? w.pair_step : w.step, w.fixed);
+  if (w.sorted && !pairs) {
+    // the first walk of the last turn: every slot then holds walks no shorter
+    const double last = turns * len(w.sorted[(turns - 1) * w.slots * 8 / wgs] * w.per, w.step, w.fixed);
+    if (last > longest) longest = last;
+  }
   return even > longest ? even : longest;
 }
 // the best number of parts up to `cap` (ties: the smaller); a split costs merge_us, a launch behind the
@@ -209,7 +217,8 @@ inline double walk_time(const WalkModel& w, int parts) {
 int best_parts(const WalkModel& w, int cap, double merge_us, double part_us, double* time);
 // keys that query row i of the tile sees
 int64_t visible_keys(const a2d_tile_desc& d, const SegList& g, int64_t i);
-double mean_visible_keys(const a2d_tile_desc& d, const SegList& g);     // over the rows (sampled)
+// of 8 rows spread over the tile, last rows first; returns the mean
+double mean_visible_keys(const a2d_tile_desc& d, const SegList& g, double seen[8]);
 
 // ---- launchers (none synchronises) ----
 // Every tile launcher runs in two phases so that a call can finish everything that may fail on the

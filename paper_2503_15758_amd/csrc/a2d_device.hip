@@ -102,9 +102,12 @@ int best_parts(const WalkModel& w, int cap, double merge_us, double part_us, dou
   return best;
 }
 
-double mean_visible_keys(const a2d_tile_desc& d, const SegList& g) {
+double mean_visible_keys(const a2d_tile_desc& d, const SegList& g, double seen[8]) {
   double mean = 0;
-  for (int i = 0; i < 8; ++i) mean += (double)visible_keys(d, g, (2 * i + 1) * (int64_t)d.nq / 16) / 8;
+  for (int i = 0; i < 8; ++i) {
+    seen[i] = (double)visible_keys(d, g, (15 - 2 * i) * (int64_t)d.nq / 16);
+    mean += seen[i] / 8;
+  }
   return mean;
 }
 

@@ -710,7 +710,7 @@ hipError_t bwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const 
 // The walk of 16-row blocks as a model: a turn is one wavefront per SIMD, a step of `contractions`
 // contractions over H takes 8 H cycles each (at about 2.1 GHz).
 WalkModel f32_walk(int64_t blocks, double steps, int contractions, int hdim, int cus) {
-  return WalkModel{blocks, cus, steps / KL, steps / KL, contractions * hdim * 8 / 2.1e3, 4.0, 0, 0};
+  return WalkModel{blocks, cus, steps / KL, steps / KL, contractions * hdim * 8 / 2.1e3, 4.0, 0, 0, nullptr, 0};
 }
 
 }  // namespace

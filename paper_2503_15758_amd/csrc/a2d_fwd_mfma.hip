@@ -483,13 +483,14 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t heads = (int64_t)d.heads * (g->b.n ? g->b.n : 1);
   const double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2;
   const bool uneven = g->by_size || g->b.n;
-  const double mean = uneven ? mean_visible_keys(d, *g) / BN + 0.2 : most;
+  double seen[8];
+  const double mean = uneven ? mean_visible_keys(d, *g, seen) / BN + 0.2 : most;
   const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 3.7;
   const double part_us = (double)heads * d.nq * (d.hdim + 2) * 8 / 4.5e6;      // written and read back at 4.5 TB/s
   const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
-  const WalkModel m[3] = {{b256, cus, mean, most, step, fixed, 0, 0},
-                          {b128, cus, mean / 2, most / 2, step * 1.13, fixed + 0.8, 0, 0},
-                          {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, fixed + 0.5}};
+  const WalkModel m[3] = {{b256, cus, mean, most, step, fixed, 0, 0, nullptr, 0},
+                          {b128, cus, mean / 2, most / 2, step * 1.13, fixed + 0.8, 0, 0, nullptr, 0},
+                          {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, fixed + 0.5, nullptr, 0}};
   double least = 0;
   for (int f = 0; f < 3; ++f) {
     double t;

@@ -128,9 +128,11 @@ __device__ __forceinline__ int dual_store_off(int r, int c) { return r * DUAL_LD
 //   by block (by_size = true):  the XCD's heads in chunks of kSizeChunk; inside a chunk block b of
 //            every head before any block b + 1.  The callers number the blocks heaviest first, so
 //            under a causal mask that crosses the tile the workgroups start longest first and the
-//            compute units finish together (diagonal forward tile -7 %); chunks of 2 to 12 heads
-//            all gave the same time, 4 keeps most of a head's rows shared in L2 (the unmasked
-//            tile loses 2-3 % with this order, which is why it is not the default).
+//            compute units finish together (diagonal forward tile of 96 heads -7 %).  A chunk has to hold
+//            all heads of a launch of few turns, or its second chunk starts the longest walks last: chunks of
+//            4 took 51 us (forward) and 144 us (backward) at 40 x 1300 x 1300 causal H = 128, chunks of 16 take 40 and
+//            108; at 96 x 4096 x 4096 sizes from 2 to 16 are the same.  (The unmasked tile loses 2-3 % with
+//            this order, which is why it is not the default.)
 // That holds for the first 8 * (heads / 8) heads.  The blocks of the remaining heads % 8 heads are
 // spread evenly over all XCDs instead (a head on an XCD of its own would leave the other XCDs
 // without work: a tile of 1 head used 32 of the 256 compute units, one of 12 heads ran 8 and then
@@ -139,7 +141,7 @@ __device__ __forceinline__ int dual_store_off(int r, int c) { return r * DUAL_LD
 // Grid size: 8 * (heads / 8 * nblocks + ceil(heads % 8 * nblocks / 8)); the few workgroups without
 // a block exit.
 constexpr int kXcds = 8;
-constexpr int kSizeChunk = 4;
+constexpr int kSizeChunk = 16;
 __host__ __device__ inline int xcd_grid(int heads, int nblocks) {
   return kXcds * (heads / kXcds * nblocks + (heads % kXcds * nblocks + kXcds - 1) / kXcds);
 }
