@@ -346,7 +346,11 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   };
   auto advance = [&](int by, int& sb, int& j, int& nblk) {
     j += by;
-    while (sb < g.n && j >= nblk) { j -= nblk; open_segment(sb + 1, sb, nblk); }
+    while (seldom(j >= nblk)) {
+      if (sb >= g.n) break;
+      j -= nblk;
+      open_segment(sb + 1, sb, nblk);
+    }
   };
   int sb, j = 0, nblk = 0;                         // this key lane's current entry
   open_segment(0, sb, nblk);
@@ -370,7 +374,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     int nsb = sb, nj = j, nnblk = nblk;
     advance(stride, nsb, nj, nnblk);
     const bool more = nsb < g.n;
-    if (more && nsb != sb) { nx_start = g.seg[nsb].start; nx_rows = g.seg[nsb].rows; }
+    if (seldom(more && nsb != sb)) { nx_start = g.seg[nsb].start; nx_rows = g.seg[nsb].rows; }
     if (more) load_tile(nx_start, nx_rows, nj);
     const int k0 = j * BN;                         // local to the sub-block
     if ((KL == 1 || sb < g.n) && k0 < nvis_wave) {
@@ -379,7 +383,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     }
     if (more) store_tile(BUF_BYTES - boff);
     __syncthreads();
-    if (more && nsb != sb) enter_segment(nsb);
+    if (seldom(more && nsb != sb)) enter_segment(nsb);
     if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
     sb = nsb; j = nj; nblk = nnblk;
     boff = BUF_BYTES - boff;
