@@ -228,14 +228,17 @@ def main():
             n = "partial_bwd_" + tag
             flops[n] = b
             ks = call_kernels(n, w, args.recompute_bwd)
-            kbytes[(n, ks[0])] = rows * (2 * H * esz + 4)
-            kflops[(n, ks[1])] = 0.8 * b                      # four of the five counted contractions: S, dP, dV, dK
-            if ks[2] == "bwd_dq_ds_kernel":
+            k_kv, = [k for k in ks if k.startswith("bwd_dkdv")]
+            k_dq, = [k for k in ks if k.startswith("bwd_dq")]
+            if "delta_kernel" in ks:
+                kbytes[(n, "delta_kernel")] = rows * (2 * H * esz + 4)
+            kflops[(n, k_kv)] = 0.8 * b                       # four of the five counted contractions: S, dP, dV, dK
+            if k_dq == "bwd_dq_ds_kernel":
                 # one contraction over the stored dS: dS (2 bytes per visible score) + K read, dQ written
-                kbytes[(n, ks[2])] = w.heads * (2.0 * T * T * vis + T * H * esz + T * H * 4)
-                knote[(n, ks[2])] = "bytes = dS read back (2 per visible score) + K + the fp32 dQ partial; " \
-                                    "mfma_frac = its one contraction against the MFMA peak"
-            kflops[(n, ks[2])] = 0.2 * b                      # dQ = scale dS K (recomputation of S and dP not counted)
+                kbytes[(n, k_dq)] = w.heads * (2.0 * T * T * vis + T * H * esz + T * H * 4)
+                knote[(n, k_dq)] = "bytes = dS read back (2 per visible score) + K + the fp32 dQ partial; " \
+                                   "mfma_frac = its one contraction against the MFMA peak"
+            kflops[(n, k_dq)] = 0.2 * b                       # dQ = scale dS K (recomputation of S and dP not counted)
     bytes_["fix"] = rows * (G * (H + 2) * 4 + H * esz + 4)
     kbytes[("fix", "fix_kernel")] = bytes_["fix"]
     if w.backward:

@@ -203,11 +203,13 @@ a2d_status a2d_partial_bwd(const a2d_tile_desc* desc, const void* Q, const void*
 /*
  * a2d_partial_bwd for callers that cannot allocate device memory or pass a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments (minus
- * the workspace), same kernels and bitwise the same results as a2d_partial_bwd with its minimum
- * workspace (A2D_DESC_KEEP_DS is refused: A2D_ERR_UNSUPPORTED).  The per-row sums delta live in
- * a device array inside the library (4 MiB per GPU the library runs on, held until the process
- * ends) of A2D_STATIC_MAX_ROWS floats: heads * nq beyond that is A2D_ERR_WORKSPACE.  The call
- * itself allocates and frees nothing; its first call on a device looks the array's address up.
+ * the workspace), same kernels and the same results as a2d_partial_bwd with its minimum workspace
+ * (A2D_DESC_KEEP_DS is refused: A2D_ERR_UNSUPPORTED): bitwise those of the torch binding's call, which has
+ * memory for shared walks too; a C caller's a2d_partial_bwd may add the same sums in another order.  The
+ * per-row sums delta live in a device array inside the library (68 MiB per GPU the library runs on, held
+ * until the process ends: A2D_STATIC_MAX_ROWS floats, and 64 MiB for the partial sums of walks that several
+ * workgroups share): heads * nq beyond A2D_STATIC_MAX_ROWS is A2D_ERR_WORKSPACE.  The call itself
+ * allocates and frees nothing; its first call on a device looks the array's address up.
  * All calls on one GPU share the array: calls that may overlap on that GPU (different streams,
  * different host threads) race and must be ordered by the caller.
  */
@@ -435,8 +437,8 @@ void a2d_debug_force_generic(int on);
  * off.  While a trace is set - per host thread - every call of this library made by that thread
  * records the next unused event on the call's stream once before its first kernel and once
  * after each kernel it launches; consecutive events of one call then bracket one kernel each
- * (a tile forward: 2 events; a2d_partial_bwd: 4 - delta, dK/dV, dQ kernels - or, on fp32 inputs,
- * 3: dQ with delta, dK/dV; a merge: 2).  Events
+ * (a tile forward: 2 events; a2d_partial_bwd: 3 - dQ with delta, dK/dV - or, with dS handed over, 4 - delta,
+ * dK/dV, dQ kernels; a merge: 2; one more where workgroups share walks and their results are merged).  Events
  * beyond n are not recorded.  a2d_debug_trace_count: events recorded since the trace was set.
  */
 void a2d_debug_trace(void** events, int n);

@@ -2,7 +2,7 @@
 // line 3 with P = exp(S - lse) rebuilt from the FINAL log-sum-exp of the query block,
 //   dV = P^T dO,  dP = dO V^T,  dS = P o (dP - delta),  dQ = scale dS K,  dK = scale dS^T Q.
 //
-// Two kernels, so that every output has exactly one writer and no atomics are needed
+// Two kernels per call, so that every output has exactly one writer and no atomics are needed
 // (bitwise reproducible results):
 //   bwd_dkdv_kernel  owns key rows.  Workgroup = 8 wavefronts = 128 keys: four PAIRS of
 //                    wavefronts (w, w + 4; both on SIMD w), 32 keys per pair.  The "score"
@@ -18,6 +18,8 @@
 //                    one barrier per step is the only synchronisation.  S and dP leave a lane
 //                    holding ONE key column, so P and dS feed the second contractions directly
 //                    as B operands; dO^T / Q^T come from the LDS transpose read.
+//                    Tiles with many keys take bwd_dkdv_wide_kernel (a2d_bwd_wide.hip) instead: 256 keys
+//                    per workgroup, every wavefront doing all four contractions for 32 of them.
 //   bwd_dq_kernel    owns query rows.  Workgroup = 8 wavefronts = 256 queries (32 per
 //                    wavefront, Q and dO fragments in registers), two wavefronts per
 //                    SIMD; walks the key blocks, 64 keys per step.  S^T = K Q^T
