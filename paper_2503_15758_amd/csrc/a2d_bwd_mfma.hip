@@ -122,17 +122,19 @@ __device__ __forceinline__ void dk_mbox_pre(const DkCtx<HD>& cx, f32x4 (&pm)[4])
 }
 
 // score wave: P = exp2(c S - lse2), masked; handed on in fp32 and kept as bf16 B fragments.
-// register r <-> query qs0 + 8*(r>>2) + 4*half + (r&3); lane <-> key
+// register r <-> query qs0 + 8*(r>>2) + 4*half + (r&3); lane <-> key.  (Queries from nq on are re-reads of the
+// last one: their statistic of +inf makes p = 0 only while q.k is finite.)
 template <bool MASK, int HD>
 __device__ __forceinline__ void dk_probs(const DkCtx<HD>& cx, const f32x4 (&st)[4], f32x16& s,
-                                         bf16x8 (&bf)[2], int qs0) {
+                                         bf16x8 (&bf)[2], int qs0, int nq) {
+  const int first = qs0 + 4 * cx.half - cx.my_first;
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     f32x4 p4;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float p = fast_exp2(fmaf(s[4 * g + e], cx.c, -st[g][e]));
-      if (MASK && (qs0 + 8 * g + 4 * cx.half + e < cx.my_first)) p = 0.f;
+      if (MASK && (unsigned)(first + 8 * g + e) >= (unsigned)(nq - cx.my_first)) p = 0.f;
       s[4 * g + e] = p;
       p4[e] = p;
     }
@@ -458,8 +460,8 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
         bf16x8 t[CT], bf[2];
         f32x16 s = dk_first<HD, KSR>(cx, n, zero16());
         dk_second_pre(cx, t);
-        if (i0 >= w_all && i0 + BQ <= d.nq) dk_probs<false>(cx, st, s, bf, i0);
-        else dk_probs<true>(cx, st, s, bf, i0);
+        if (i0 >= w_all && i0 + BQ <= d.nq) dk_probs<false>(cx, st, s, bf, i0, d.nq);
+        else dk_probs<true>(cx, st, s, bf, i0, d.nq);
         dk_second(cx, t, bf);
       }
       advance(SET ? -DK_MBOX_SLOT : DK_MBOX_SLOT);

@@ -14,8 +14,8 @@ using namespace mfma;
 // the pairs of bwd_dkdv_kernel nothing passes between wavefronts (no mailbox: a fifth of the LDS
 // traffic), the two wavefronts of a SIMD run freely against each other, and a step - its barrier,
 // its staging, its LDS latencies - holds twice the MFMAs.  In program order the exponentials stand
-// under the dP MFMAs and the products dS under the dV MFMAs.  The scores start from -lse / scale (-inf
-// where hidden) and dP from -delta, so that p = exp2(c s) and dS = p dP need no further operand.
+// under the dP MFMAs and the products dS under the dV MFMAs.  The scores start from -lse / scale
+// and dP from -delta, so that p = exp2(c s) and dS = p dP need no further operand.
 // Measured per 32 rows x 256 keys, H = 128 / 96 / 80 / 64: 1.51 / 1.22 / 1.17 / 0.99 us against 2.26 / 1.92 /
 // 1.86 / 1.58 us in pairs; the call at 96 x 4096 x 4096 H = 128 2.79 -> 2.59 ms (dS kept: 2.61 -> 2.48 ms - the
 // chip's power limit takes the rest back), at 32 x 1999 x 2777 H = 80 217 -> 187 us.
@@ -235,12 +235,6 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e) s[4 * q + e] = v[e];
     }
-    // register r of a tile <-> row i0 + 8 (r >> 2) + 4 half + (r & 3).  Hidden scores start from -inf.
-    if (masked) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (i0 + 8 * (r >> 2) + 4 * half + (r & 3) < my_first) s[r] = -INFINITY;
-    }
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, KS>([&](auto X) {
       constexpr int x = decltype(X)::value;
@@ -271,6 +265,17 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
       ldv(std::integral_constant<int, x + 2>{});
       __builtin_amdgcn_sched_barrier(0);
     });
+    // Register r of a tile <-> row i0 + 8 (r >> 2) + 4 half + (r & 3).  Hidden pairs, and rows past the end, are
+    // taken out after the exponential, not by where their scores start from: q.k may have overflowed there.
+    if (seldom(masked)) {
+      const int first = i0 + 4 * half - my_first;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const bool seen = (unsigned)(first + 8 * (r >> 2) + (r & 3)) < (unsigned)(d.nq - my_first);
+        s[r] = seen ? s[r] : 0.f;
+        pb[r >> 3][r & 7] = (bf16_t)s[r];
+      }
+    }
     static_for<0, 2 * CT>([&](auto Y) {
       constexpr int y = decltype(Y)::value;
       dv[y % CT] = mma(a[(N2 + y) % RING], pb[y / CT], dv[y % CT]);
