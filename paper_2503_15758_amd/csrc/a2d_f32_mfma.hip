@@ -315,11 +315,11 @@ __device__ __forceinline__ float row_sum(float v) {
 }
 
 // ------------------------------------------------------------------ forward
+// (O_part, m_out and l_out are not __restrict__: an accumulating call's `in` is the same memory)
 template <int H, int RT>
 __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void fwd_f32_kernel(
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
-    const float* __restrict__ V, float* __restrict__ O_part, float* __restrict__ m_out, float* __restrict__ l_out,
-    FwdInput in) {
+    const float* __restrict__ V, float* O_part, float* m_out, float* l_out, FwdInput in) {
   warm_arguments<6 * 8 + sizeof(FwdInput)>();
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int head, q0, part;

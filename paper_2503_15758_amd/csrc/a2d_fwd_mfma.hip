@@ -152,11 +152,11 @@ __device__ __forceinline__ void fwd_block(FwdState<HD>& st, const bf16x8 (&qf)[H
 //           query block are (Alg. 2).
 // HR: head size = row length in memory (80, 96 or 128); the LDS tiles and fragments are laid out
 // for the padded head size HD = padded_head(HR) (96 or 128).
+// (O_part, m_out and l_out are not __restrict__: an accumulating call's `in` is the same memory)
 template <int WAVES, int HR, int KL>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
-    const bf16_t* __restrict__ V, float* __restrict__ O_part, float* __restrict__ m_out,
-    float* __restrict__ l_out, FwdInput in) {
+    const bf16_t* __restrict__ V, float* O_part, float* m_out, float* l_out, FwdInput in) {
   constexpr int RW = WAVES / KL;          // wavefronts of one key lane
   constexpr int BM = 32 * RW;             // query rows per workgroup
   constexpr int kThreads = 64 * RW;       // threads of one key lane (they stage its tiles)

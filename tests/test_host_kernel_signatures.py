@@ -1,0 +1,22 @@
+"""What the kernels' signatures promise the compiler (read from the sources: a broken promise shows only where a
+compiler makes use of it)."""
+import os
+import re
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2503_15758_amd", "csrc")
+
+
+@pytest.mark.parametrize("source, kernel", [("a2d_fwd_mfma.hip", "fwd_mfma_kernel"), ("a2d_f32_mfma.hip", "fwd_f32_kernel")])
+def test_forward_outputs_may_alias_the_running_partial(source, kernel):
+    """An accumulating forward call reads the triple it writes (`in` and the outputs are the same buffers), so the
+    outputs must not be declared __restrict__."""
+    text = open(os.path.join(CSRC, source)).read()
+    parameters = re.search(r"\b%s\(\s*a2d_tile_desc(.*?)\)\s*\{" % kernel, text, re.S).group(1)
+    assert "FwdInput in" in parameters
+    for name in ("O_part", "m_out", "l_out"):
+        (declared,) = [p for p in parameters.split(",") if re.search(r"\b%s$" % name, p.strip())]
+        assert "__restrict__" not in declared, "%s: %s" % (kernel, declared.strip())
+    # (what it only reads stays promised: the tile loads depend on it)
+    assert all("__restrict__" in p for p in parameters.split(",") if re.search(r"\bconst \w+\*", p))
