@@ -297,7 +297,7 @@ struct OutMap {
 };
 inline OutMap plain_out() { return OutMap{0, 0, 1, 1}; }
 // The merged output of a whole emulated grid: block b, head h, row i of the merge's input is token
-// i * side + b (cyclic) or b * rows + i of head h in a plain [heads][side * rows][H] tensor.  dir: which
+// i * side + b (cyclic) or b * rows + i of head h in a [heads][side * rows][H] tensor.  dir: which
 // partials block b has - 0: all `side`; 1: those x <= b (a grid row under the causal mask,
 // contiguous blocks); 2: those x >= b (a grid column).  Each is in `parts` parts: partial e of the
 // pointer lists is part e % parts of partial e / parts.
@@ -311,13 +311,14 @@ struct GridMap {
     return has;
   }
 };
-// O, lse of a whole grid from its partial triples; sums of up to three sets of gradient partials
-hipError_t launch_fix_grid(const GridMap& gm, int hdim, int out_dtype, const FixPtrs& p, void* O, float* lse,
-                           hipStream_t s);
+// O (layout lo), lse of a whole grid from its partial triples; sums of up to three sets of gradient partials
+hipError_t launch_fix_grid(const GridMap& gm, int hdim, int out_dtype, const FixPtrs& p, const a2d_layout& lo, void* O,
+                           float* lse, hipStream_t s);
 struct SumSet {
   SumPtrs p;
   GridMap gm;
   void* out;
+  a2d_layout lo;
 };
 hipError_t launch_sum_grid(int nsets, const SumSet* sets, int hdim, int out_dtype, hipStream_t s);
 // delta and lse of a whole [heads][side * rows] sequence, block by block: [side][heads][rows]

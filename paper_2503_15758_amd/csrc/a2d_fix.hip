@@ -201,14 +201,13 @@ struct GridRow {
     b = hb / (unsigned)g.heads;
     h = hb - b * g.heads;
   }
-  __device__ __forceinline__ int64_t token(const GridMap& g) const {
-    return (int64_t)h * g.side * g.rows + (g.cyclic ? i * g.side + b : b * g.rows + i);
-  }
+  // inside the head's sequence
+  __device__ __forceinline__ int token(const GridMap& g) const { return g.cyclic ? i * g.side + b : b * g.rows + i; }
 };
 
 template <typename OutT, int KMAX>
-__global__ __launch_bounds__(256) void fix_grid_kernel(FixPtrs p, GridMap g, int hv, OutT* __restrict__ O,
-                                                       float* __restrict__ lse) {
+__global__ __launch_bounds__(256) void fix_grid_kernel(FixPtrs p, GridMap g, int hv, a2d_layout lo,
+                                                       OutT* __restrict__ O, float* __restrict__ lse) {
   const unsigned idx = blockIdx.x * 256 + threadIdx.x;
   const unsigned row = idx / (unsigned)hv, col = idx - row * hv;
   if (row >= (unsigned)(g.side * g.heads * g.rows)) return;
@@ -244,9 +243,9 @@ __global__ __launch_bounds__(256) void fix_grid_kernel(FixPtrs p, GridMap g, int
   }
   const float inv = (D > 0.f) ? 1.0f / D : 0.f;
   acc[0] *= inv; acc[1] *= inv; acc[2] *= inv; acc[3] *= inv;
-  const int64_t t = gr.token(g);
-  store_out4(O, (t * hv + col) * 4, acc);
-  if (col == 0) lse[t] = (D > 0.f) ? M + logf(D) : -INFINITY;
+  const int t = gr.token(g);
+  store_out4(O, gr.h * lo.head + t * lo.row + col * 4, acc);
+  if (col == 0) lse[(int64_t)gr.h * g.side * g.rows + t] = (D > 0.f) ? M + logf(D) : -INFINITY;
 }
 
 struct SumSets {
@@ -272,7 +271,7 @@ __global__ __launch_bounds__(256) void sum_grid_kernel(SumSets a, int hv) {
   for (int x = 1; x < KMAX; ++x) {
     acc[0] += v[x][0]; acc[1] += v[x][1]; acc[2] += v[x][2]; acc[3] += v[x][3];
   }
-  store_out4(static_cast<OutT*>(s.out), (gr.token(g) * hv + col) * 4, acc);
+  store_out4(static_cast<OutT*>(s.out), gr.h * s.lo.head + gr.token(g) * s.lo.row + col * 4, acc);
 }
 
 // The partial results of a split walk, which lie one behind the other: out (+)= sum over the parts,
@@ -386,10 +385,11 @@ hipError_t launch_fix(int k, int64_t rows, int hdim, int out_dtype, const FixPtr
 
 namespace {
 template <typename OutT>
-void fix_grid_dispatch(const GridMap& gm, int hv, const FixPtrs& p, OutT* O, float* lse, hipStream_t s) {
+void fix_grid_dispatch(const GridMap& gm, int hv, const FixPtrs& p, const a2d_layout& lo, OutT* O, float* lse,
+                       hipStream_t s) {
   const dim3 grid((unsigned)(((int64_t)gm.side * gm.heads * gm.rows * hv + 255) / 256)), block(256);
   const int k = gm.side * gm.parts;
-#define A2D_GO(KMAX) A2D_LAUNCH((fix_grid_kernel<OutT, KMAX>), grid, block, 0, s, p, gm, hv, O, lse)
+#define A2D_GO(KMAX) A2D_LAUNCH((fix_grid_kernel<OutT, KMAX>), grid, block, 0, s, p, gm, hv, lo, O, lse)
   if (k <= 2) A2D_GO(2);
   else if (k <= 4) A2D_GO(4);
   else if (k <= 8) A2D_GO(8);
@@ -412,10 +412,10 @@ void sum_grid_dispatch(int nsets, const SumSets& a, int hv, int64_t blocks, hipS
 }
 }  // namespace
 
-hipError_t launch_fix_grid(const GridMap& gm, int hdim, int out_dtype, const FixPtrs& p, void* O, float* lse,
-                           hipStream_t s) {
-  if (out_dtype == A2D_BF16) fix_grid_dispatch<bf16_t>(gm, hdim / 4, p, (bf16_t*)O, lse, s);
-  else fix_grid_dispatch<float>(gm, hdim / 4, p, (float*)O, lse, s);
+hipError_t launch_fix_grid(const GridMap& gm, int hdim, int out_dtype, const FixPtrs& p, const a2d_layout& lo, void* O,
+                           float* lse, hipStream_t s) {
+  if (out_dtype == A2D_BF16) fix_grid_dispatch<bf16_t>(gm, hdim / 4, p, lo, (bf16_t*)O, lse, s);
+  else fix_grid_dispatch<float>(gm, hdim / 4, p, lo, (float*)O, lse, s);
   return hipGetLastError();
 }
 

@@ -158,7 +158,7 @@ hipError_t grid_forward(const GridProblem& p, const void* Q, const void* K, cons
       f.l[c * g.parts + z] = l + at;
     }
   }
-  return launch_fix_grid(map_of(p, p.heads, 1, g.parts), p.hdim, A2D_BF16, f, O, lse, s);   // Alg. 1 lines 5-6
+  return launch_fix_grid(map_of(p, p.heads, 1, g.parts), p.hdim, A2D_BF16, f, p.o, O, lse, s);   // Alg. 1 lines 5-6
 }
 
 hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, const void* V, const void* O,
@@ -211,6 +211,9 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
   sets[0].out = dQ;
   sets[1].out = dK;
   sets[2].out = dV;
+  sets[0].lo = p.dq;
+  sets[1].lo = p.dk;
+  sets[2].lo = p.dv;
   return launch_sum_grid(3, sets, p.hdim, A2D_BF16, s);        // Alg. 3 lines 4-5
 }
 

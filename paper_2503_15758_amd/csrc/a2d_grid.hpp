@@ -21,6 +21,7 @@ struct GridProblem {
   int heads, kv_heads, seq, side, hdim, causal, cyclic;
   float scale;
   a2d_layout q, k, v, o, g;      // layouts of Q, K, V, O, dO over the whole sequence (elements)
+  a2d_layout dq, dk, dv;         // of the gradients
 };
 
 // Whether the batched path covers the problem (bf16; the kernels' 32-bit offsets, the dS hand-over)
@@ -28,10 +29,10 @@ bool grid_supported(const GridProblem& p);
 // Workspace in bytes; dS of as many tiles as fit kGridDsBytes is kept at a time (at least one tile's)
 size_t grid_forward_bytes(const GridProblem& p);
 size_t grid_backward_bytes(const GridProblem& p);
-// O: plain bf16 [heads][seq][H], lse [heads][seq].  Both only enqueue on `s`.
+// O with the layout p.o, lse plain [heads][seq].  Both only enqueue on `s`.
 hipError_t grid_forward(const GridProblem& p, const void* Q, const void* K, const void* V, void* O, float* lse,
                         void* ws, hipStream_t s);
-// O, dO with the layouts p.o, p.g; lse plain; dQ, dK, dV plain bf16
+// O, dO and the gradients with the problem's layouts; lse plain
 hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, const void* V, const void* O,
                          const void* dO, const float* lse, void* dQ, void* dK, void* dV, void* ws, hipStream_t s);
 

@@ -573,7 +573,14 @@ PyObject* fix_bwd(Args a) {
   return o.one(0);
 }
 
-// ---- the whole grid.  Both return None when the batched path does not cover the problem.
+// the layout with its strides written out
+a2d_layout full(const at::Tensor& t) {
+  const a2d_layout l = layout(t);
+  return l.row ? l : a2d_layout{t.size(1) * t.size(2), t.size(2)};
+}
+
+// ---- the whole grid.  Both return None when the batched path does not cover the problem.  Outputs have
+// the strides of the inputs they belong to.
 bool grid_problem(const at::Tensor& Q, const at::Tensor& K, const at::Tensor& V, const at::Tensor& O,
                   const at::Tensor& dO, Args a, a2d::GridProblem* p) {
   // a: side, causal, cyclic, scale
@@ -584,14 +591,10 @@ bool grid_problem(const at::Tensor& Q, const at::Tensor& K, const at::Tensor& V,
   if (K.sizes() != V.sizes() || K.size(1) != Q.size(1) || K.size(2) != Q.size(2) || O.sizes() != Q.sizes() ||
       dO.sizes() != Q.sizes() || Q.numel() == 0)
     return false;
-  const auto full = [](const at::Tensor& t) {
-    const a2d_layout l = layout(t);
-    return l.row ? l : a2d_layout{t.size(1) * t.size(2), t.size(2)};
-  };
   const int64_t side = integer(a[0]);
   if (side < 1 || side > A2D_MAX_PARTS || Q.size(0) > 65535 || Q.size(1) > (1 << 22) || Q.size(2) > 128) return false;
   *p = a2d::GridProblem{(int)Q.size(0), (int)K.size(0), (int)Q.size(1), (int)side, (int)Q.size(2), truth(a[1]), truth(a[2]),
-                        scale_of(a[3], Q.size(2)), full(Q), full(K), full(V), full(O), full(dO)};
+                        scale_of(a[3], Q.size(2)), full(Q), full(K), full(V), full(O), full(dO), full(Q), full(K), full(V)};
   return !a2d::force_generic() && a2d::grid_supported(*p);
 }
 void hip_check(hipError_t e, const char* who) {
@@ -604,8 +607,10 @@ PyObject* grid_forward(Args a) {
   a2d::GridProblem p;
   if (!grid_problem(Q, K, V, Q, Q, a + 3, &p)) Py_RETURN_NONE;
   Outputs o;
-  o.add(empty_like_shape(Q, Q.sizes(), at::kBFloat16));
+  o.add(at::empty_like(Q));
   o.add(empty_like_shape(Q, rows_shape(Q), at::kFloat));
+  if (o.t[0].stride(2) != 1) Py_RETURN_NONE;
+  p.o = full(o.t[0]);
   const at::Tensor ws = empty_like_shape(Q, {(int64_t)a2d::grid_forward_bytes(p)}, at::kByte);
   hipStream_t s = static_cast<hipStream_t>(stream());
   hipError_t e;
@@ -625,9 +630,12 @@ PyObject* grid_backward(Args a) {
       lse.sizes() != rows_shape(Q) || !lse.is_contiguous())
     Py_RETURN_NONE;
   Outputs o;
-  o.add(empty_like_shape(Q, Q.sizes(), at::kBFloat16));
-  o.add(empty_like_shape(Q, K.sizes(), at::kBFloat16));
-  o.add(empty_like_shape(Q, K.sizes(), at::kBFloat16));
+  for (const at::Tensor* t : {&Q, &K, &V}) o.add(at::empty_like(*t));
+  for (int i = 0; i < 3; ++i)
+    if (o.t[i].stride(2) != 1) Py_RETURN_NONE;
+  p.dq = full(o.t[0]);
+  p.dk = full(o.t[1]);
+  p.dv = full(o.t[2]);
   const at::Tensor ws = empty_like_shape(Q, {(int64_t)a2d::grid_backward_bytes(p)}, at::kByte);
   hipStream_t s = static_cast<hipStream_t>(stream());
   hipError_t e;
