@@ -203,12 +203,10 @@ a2d_status a2d_partial_bwd(const a2d_tile_desc* desc, const void* Q, const void*
 /*
  * a2d_partial_bwd for callers that cannot allocate device memory or pass a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments (minus
- * the workspace), same kernels and the same results as a2d_partial_bwd with its minimum workspace
- * (A2D_DESC_KEEP_DS is refused: A2D_ERR_UNSUPPORTED): bitwise those of the torch binding's call, which has
- * memory for shared walks too; a C caller's a2d_partial_bwd may add the same sums in another order.  The
- * per-row sums delta live in a device array inside the library (68 MiB per GPU the library runs on, held
- * until the process ends: A2D_STATIC_MAX_ROWS floats, and 64 MiB for the partial sums of walks that several
- * workgroups share): heads * nq beyond A2D_STATIC_MAX_ROWS is A2D_ERR_WORKSPACE.  The call itself
+ * the workspace), same kernels and bitwise the results of a2d_partial_bwd with its minimum workspace
+ * (A2D_DESC_KEEP_DS is refused: A2D_ERR_UNSUPPORTED).  The per-row sums delta live in a device array inside
+ * the library (4 MiB per GPU the call is used on, held until the process ends: A2D_STATIC_MAX_ROWS
+ * floats): heads * nq beyond A2D_STATIC_MAX_ROWS is A2D_ERR_WORKSPACE.  The call itself
  * allocates and frees nothing; its first call on a device looks the array's address up.
  * All calls on one GPU share the array: calls that may overlap on that GPU (different streams,
  * different host threads) race and must be ordered by the caller.

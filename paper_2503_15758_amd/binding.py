@@ -271,7 +271,9 @@ STATIC_MAX_ROWS = 1 << 20
 def partial_bwd_static(Q, K, V, O, dO, lse, q_off=0, kv_off=0, causal=False, scale=None, out=None):
     """a2d_partial_bwd_static: a2d_partial_bwd without a workspace argument (the library's own static
     scratch holds delta; heads * nq <= STATIC_MAX_ROWS).  `out` = (dQ_part, dK_part, dV_part) fp32;
-    with out given this function allocates nothing either."""
+    with out given this function allocates nothing either: the partial results of shared walks go into a
+    device array of the library (64 MiB, held from the first call that shares a walk on), and the results are
+    bitwise those of partial_bwd.  All calls on one GPU share the library's arrays and must be ordered."""
     return (_native or _ext()).partial_bwd_static(Q, K, V, O, dO, lse, q_off, kv_off, causal, scale, out)
 
 

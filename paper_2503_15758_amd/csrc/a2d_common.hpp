@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "a2d.h"
 #include "a2d_grid.hpp"
 
@@ -151,6 +153,12 @@ __device__ __forceinline__ bool seg_visible(const SegList& g, int i, int c) {
 hipError_t device_cus(int* cus);
 // raises the kernel's dynamic-LDS limit to `bytes` once per (device, kernel)
 hipError_t ensure_dynamic_lds(const void* kernel, int bytes);
+// Address of a device array on the current device (the first lookup on a device loads it there)
+constexpr int kMaxDevices = 64;
+struct SymbolCache {
+  std::atomic<void*> at[kMaxDevices];
+};
+hipError_t symbol_address(const void* symbol, SymbolCache* cache, void** out);
 // Debugging aid: route every tile call to the vector-ALU kernels.  The default comes from
 // A2D_FORCE_GENERIC=1 in the environment, read once per process; a2d_debug_force_generic() sets it.
 bool force_generic();

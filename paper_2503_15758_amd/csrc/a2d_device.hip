@@ -13,8 +13,6 @@
 namespace a2d {
 namespace {
 
-
-constexpr int kMaxDevices = 64;
 std::atomic<int> g_cus[kMaxDevices];                       // 0 = not asked yet
 std::mutex g_mu;
 std::vector<std::pair<int, const void*>> g_prepared;       // (device, kernel): limit already raised
@@ -60,6 +58,22 @@ hipError_t ensure_dynamic_lds(const void* kernel, int bytes) {
   if (e != hipSuccess) return e;
   std::lock_guard<std::mutex> lock(g_mu);
   g_prepared.push_back(key);
+  return hipSuccess;
+}
+
+hipError_t symbol_address(const void* symbol, SymbolCache* cache, void** out) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  void* p = cache->at[dev].load(std::memory_order_acquire);
+  if (!p) {
+    e = hipGetSymbolAddress(&p, symbol);
+    if (e != hipSuccess) return e;
+    if (!p) return hipErrorInvalidSymbol;
+    cache->at[dev].store(p, std::memory_order_release);   // (two first calls at once store the same address)
+  }
+  *out = p;
   return hipSuccess;
 }
 

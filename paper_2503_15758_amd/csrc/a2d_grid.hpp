@@ -16,6 +16,8 @@ struct ScratchSource {
   void* ctx;
 };
 void scratch_offer(const ScratchSource* src);
+// `bytes` of a device array of the library's own, the same at every call (a2d_static.hip); NULL: not to be had
+void* static_partial_sums(size_t bytes);
 
 struct GridProblem {
   int heads, kv_heads, seq, side, hdim, causal, cyclic;

@@ -286,6 +286,16 @@ class Scratch {
   Scratch(const Scratch&) = delete;
 };
 
+// Offers the library's own device array instead: the static calls allocate nothing.
+class StaticScratch {
+  a2d::ScratchSource source_{[](void*, size_t bytes) { return a2d::static_partial_sums(bytes); }, nullptr};
+
+ public:
+  StaticScratch() { a2d::scratch_offer(&source_); }
+  ~StaticScratch() { a2d::scratch_offer(nullptr); }
+  StaticScratch(const StaticScratch&) = delete;
+};
+
 // runs f with the GIL released
 template <class F>
 a2d_status unlocked(F&& f) {
@@ -435,6 +445,7 @@ PyObject* partial_bwd_static(Args a) {
   Outputs o;
   gradients(&o, x, a[10]);
   void* s = stream();
+  const StaticScratch scratch;
   check(unlocked([&] {
     return a2d_partial_bwd_static(&d, x.Q.data_ptr(), x.K.data_ptr(), x.V.data_ptr(), x.O.data_ptr(), x.dO.data_ptr(),
                                   data<float>(x.lse), data<float>(o.t[0]), data<float>(o.t[1]), data<float>(o.t[2]), s);
