@@ -5,6 +5,14 @@ kernels.  torch supplies device memory and the current stream.  The compute call
 are marshalled by the extension module _native (csrc/a2d_torch.cpp), the queries,
 diagnostics and raw exports through ctypes.  If the library or the extension has
 not been built (python -m paper_2503_15758_amd.build) every call raises.
+
+Memory: a tile call whose row blocks are too few for the chip shares their walks
+among several workgroups and takes up to 32 MiB for each result it shares (forward;
+dQ; dK and dV) from torch's allocator while it runs, also where `out` and `workspace`
+are given.  Under torch.cuda.graph that is the graph's own pool.  On a stream that the
+program captures by other means, no memory is taken and no walk is shared: the same
+results up to the order of fp32 sums.  The same where there is no memory, with a
+RuntimeWarning.
 """
 import ctypes
 import math

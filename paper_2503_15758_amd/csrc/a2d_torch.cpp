@@ -8,12 +8,14 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/hip/HIPGeneratorImpl.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cmath>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -261,39 +263,72 @@ void qkv(const at::Tensor& Q, const at::Tensor& K, const at::Tensor& V) {
     fail(A2D_ERR_INVALID_ARG, "Q, K, V shapes / dtypes do not match");
 }
 
-// Offers the library scratch memory from torch's allocator for the partial results of split walks while
-// it lives; the blocks go back when it does (the allocator orders their reuse on the stream).
+// Is the stream being captured by torch?  Its allocator then serves it from a pool that lives as long as the
+// graph; a capture begun by other means it knows nothing of.  torch's default generator takes part in torch's
+// captures, and on a capturing stream it can be asked for its state (here: moved on by nothing) in those only.
+bool torch_captures(const at::Device& device) {
+  try {
+    at::Generator g = at::cuda::detail::getDefaultCUDAGenerator(device.index());
+    std::lock_guard<std::mutex> lock(g.mutex());
+    g.get<at::CUDAGeneratorImpl>()->philox_cuda_state(0);
+    return true;
+  } catch (const c10::Error&) {
+    return false;
+  }
+}
+
+// Offers the library memory for the partial results of shared walks while it lives: from torch's allocator (the
+// blocks go back when it dies; the allocator orders their reuse on the stream) or, for the static calls, the
+// library's own device array.  A foreign capture gets none: its graph would replay into memory that has been
+// handed out again.  tell() says it where there was no memory, and the call's sums were added in another order.
 class Scratch {
   std::vector<at::Tensor> held_;
-  at::TensorOptions options_;
+  const at::Tensor* like_;                           // NULL: the library's array
+  hipStream_t stream_;
+  size_t missing_ = 0;
   a2d::ScratchSource source_;
-  static void* get(void* self, size_t bytes) {
-    Scratch* s = static_cast<Scratch*>(self);
+
+  bool capturable() const {
+    hipStreamCaptureStatus now = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream_, &now) != hipSuccess) {
+      (void)hipGetLastError();                       // (not an error of the launches to come)
+      return false;
+    }
+    return now == hipStreamCaptureStatusNone || torch_captures(like_->device());
+  }
+  void* allocate(size_t bytes) {
+    if (!capturable()) return nullptr;
     try {
-      s->held_.push_back(at::empty({(int64_t)bytes}, s->options_));
-    } catch (...) {                                  // no memory: the call runs unsplit
+      held_.push_back(at::empty({(int64_t)bytes}, like_->options().dtype(at::kByte).requires_grad(false)));
+      return held_.back().data_ptr();
+    } catch (...) {
+      missing_ = bytes;
       return nullptr;
     }
-    return s->held_.back().data_ptr();
   }
-
- public:
-  explicit Scratch(const at::Tensor& like)
-      : options_(like.options().dtype(at::kByte).requires_grad(false)), source_{&Scratch::get, this} {
+  static void* get(void* self, size_t bytes) {
+    Scratch* s = static_cast<Scratch*>(self);
+    if (s->like_) return s->allocate(bytes);
+    void* p = a2d::static_partial_sums(bytes);
+    if (!p) s->missing_ = bytes;
+    return p;
+  }
+  Scratch(const at::Tensor* like, void* stream)
+      : like_(like), stream_(static_cast<hipStream_t>(stream)), source_{&Scratch::get, this} {
     a2d::scratch_offer(&source_);
   }
-  ~Scratch() { a2d::scratch_offer(nullptr); }
-  Scratch(const Scratch&) = delete;
-};
-
-// Offers the library's own device array instead: the static calls allocate nothing.
-class StaticScratch {
-  a2d::ScratchSource source_{[](void*, size_t bytes) { return a2d::static_partial_sums(bytes); }, nullptr};
 
  public:
-  StaticScratch() { a2d::scratch_offer(&source_); }
-  ~StaticScratch() { a2d::scratch_offer(nullptr); }
-  StaticScratch(const StaticScratch&) = delete;
+  Scratch(const at::Tensor& like, void* stream) : Scratch(&like, stream) {}
+  explicit Scratch(void* stream) : Scratch(nullptr, stream) {}
+  ~Scratch() { a2d::scratch_offer(nullptr); }
+  Scratch(const Scratch&) = delete;
+  void tell() const {
+    if (missing_ && PyErr_WarnFormat(PyExc_RuntimeWarning, 1,
+                                     "no memory for partial results (%zu bytes): the call did not share its walks among "
+                                     "workgroups, its sums are added in another order", missing_) != 0)
+      throw PythonError();
+  }
 };
 
 // runs f with the GIL released
@@ -326,7 +361,7 @@ PyObject* partial_fwd(Args a) {
   const void *q = Q.data_ptr(), *k = K.data_ptr(), *v = V.data_ptr();
   float *N = data<float>(o.t[0]), *m = data<float>(o.t[1]), *l = data<float>(o.t[2]);
   const int kvh = (int)K.size(0);
-  const Scratch scratch(Q);
+  const Scratch scratch(Q, s);
   check(unlocked([&] {
     if (kvh != d.heads)                                // grouped queries: K, V hold fewer heads than Q
       return a2d_partial_fwd_gqa(&d, kvh, segs.n(), segs.ptr(), acc ? A2D_TILE_ACCUMULATE : 0, q, k, v, N, m, l, nullptr,
@@ -335,6 +370,7 @@ PyObject* partial_fwd(Args a) {
     if (segs.given) return a2d_partial_fwd_seg(&d, segs.n(), segs.ptr(), q, k, v, N, m, l, nullptr, 0, s);
     return a2d_partial_fwd(&d, q, k, v, N, m, l, nullptr, 0, s);
   }));
+  scratch.tell();
   return o.give();
 }
 
@@ -356,13 +392,14 @@ PyObject* partial_fwd_norm(Args a) {
   void* O = o.t[0].data_ptr();
   float* lse = data<float>(o.t[1]);
   const int kvh = (int)K.size(0);
-  const Scratch scratch(Q);
+  const Scratch scratch(Q, s);
   check(unlocked([&] {
     if (kvh != d.heads)
       return a2d_partial_fwd_gqa(&d, kvh, segs.n(), segs.ptr(), A2D_TILE_NORMALISED, q, k, v, O, lse, nullptr, nullptr, 0,
                                  s);
     return a2d_partial_fwd_norm(&d, segs.n(), segs.ptr(), q, k, v, O, lse, nullptr, 0, s);
   }));
+  scratch.tell();
   return o.give();
 }
 
@@ -421,7 +458,7 @@ PyObject* partial_bwd(Args a) {
   const void *q = x.Q.data_ptr(), *k = x.K.data_ptr(), *v = x.V.data_ptr(), *O = x.O.data_ptr(), *g = x.dO.data_ptr();
   const float* lse = data<float>(x.lse);
   float *dq = data<float>(o.t[0]), *dk = data<float>(o.t[1]), *dv = data<float>(o.t[2]);
-  const Scratch scratch(x.Q);
+  const Scratch scratch(x.Q, s);
   check(unlocked([&] {
     if (kvh != d.heads)                                // dK_part, dV_part have K's heads
       return a2d_partial_bwd_gqa(&d, kvh, segs.n(), segs.ptr(),
@@ -431,6 +468,7 @@ PyObject* partial_bwd(Args a) {
     if (segs.given) return a2d_partial_bwd_seg(&d, segs.n(), segs.ptr(), q, k, v, O, g, lse, dq, dk, dv, w, wb, s);
     return a2d_partial_bwd(&d, q, k, v, O, g, lse, dq, dk, dv, w, wb, s);
   }));
+  scratch.tell();
   return o.give();
 }
 
@@ -445,11 +483,12 @@ PyObject* partial_bwd_static(Args a) {
   Outputs o;
   gradients(&o, x, a[10]);
   void* s = stream();
-  const StaticScratch scratch;
+  const Scratch scratch(s);
   check(unlocked([&] {
     return a2d_partial_bwd_static(&d, x.Q.data_ptr(), x.K.data_ptr(), x.V.data_ptr(), x.O.data_ptr(), x.dO.data_ptr(),
                                   data<float>(x.lse), data<float>(o.t[0]), data<float>(o.t[1]), data<float>(o.t[2]), s);
   }));
+  scratch.tell();
   return o.give();
 }
 

@@ -1146,10 +1146,11 @@ def test_generic_kernels_on_bf16_inputs(a2d, H):
 # ----------------------------------------------------------------------------- HIP graph capture
 @pytest.mark.gpu
 def test_step_replays_from_a_hip_graph(a2d):
-    """The calls only enqueue kernels on the given stream (no allocation, no memset, no
-    synchronisation), so a whole step - tiles, merge, gradient tiles, gradient sums - can be
-    captured into a HIP graph.  Several replays, with eager work and synchronisations between
-    them, must each reproduce the eager results bit for bit."""
+    """The calls only enqueue kernels on the given stream (no memset, no synchronisation; memory for
+    the partial results of shared walks comes from torch's allocator, here from the graph's pool), so a
+    whole step - tiles, merge, gradient tiles, gradient sums - can be captured into a HIP graph.  Several
+    replays, with eager work and synchronisations between them, must each reproduce the eager results bit
+    for bit."""
     heads, T, H, G = 2, 256, 128, 2
     scale = 1.0 / math.sqrt(H)
     r = G - 1

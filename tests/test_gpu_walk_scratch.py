@@ -146,7 +146,7 @@ def test_no_memory_is_said_aloud(a2d):
     held = []
     try:
         torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / total)   # no new segments
-        for size in (1 << 20, 1 << 16, 512):       # and what is free in those there are is taken
+        for size in (16 << 20, 2 << 20, 1 << 20, 1 << 16, 512):     # and what is free in those there are is taken
             while True:
                 try:
                     held.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
