@@ -250,6 +250,16 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
       for (int e = 0; e < 4; ++e) dp[4 * q + e] = v[e];
     }
     bf16x8 pb[2], sb[2];
+    // Register r of a tile <-> row i0 + 8 (r >> 2) + 4 half + (r & 3).  Hidden pairs, and rows past the end, are
+    // taken out of the finished scores, not by where these start from: q.k may have overflowed there.
+    auto mask = [&]() {
+      if (masked) {
+        const int first = i0 + 4 * half - my_first;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if ((unsigned)(first + 8 * (r >> 2) + (r & 3)) >= (unsigned)(d.nq - my_first)) s[r] = -INFINITY;
+      }
+    };
     auto prob = [&](int r) {
       const float p = fast_exp2(s[r] * c);
       s[r] = p;
@@ -259,23 +269,13 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
     static_for<0, KS>([&](auto X) {
       constexpr int x = decltype(X)::value;
       dp = mma(a[(N1 + x) % RING], V_LDS ? va[x & 1] : vf[x], dp);
+      if constexpr (x == 0) mask();
 #pragma unroll
       for (int r = 16 * x / KS; r < 16 * (x + 1) / KS; ++r) prob(r);
       ld(std::integral_constant<int, N1 + x + RING>{});
       ldv(std::integral_constant<int, x + 2>{});
       __builtin_amdgcn_sched_barrier(0);
     });
-    // Register r of a tile <-> row i0 + 8 (r >> 2) + 4 half + (r & 3).  Hidden pairs, and rows past the end, are
-    // taken out after the exponential, not by where their scores start from: q.k may have overflowed there.
-    if (seldom(masked)) {
-      const int first = i0 + 4 * half - my_first;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const bool seen = (unsigned)(first + 8 * (r >> 2) + (r & 3)) < (unsigned)(d.nq - my_first);
-        s[r] = seen ? s[r] : 0.f;
-        pb[r >> 3][r & 7] = (bf16_t)s[r];
-      }
-    }
     static_for<0, 2 * CT>([&](auto Y) {
       constexpr int y = decltype(Y)::value;
       dv[y % CT] = mma(a[(N2 + y) % RING], pb[y / CT], dv[y % CT]);
