@@ -636,7 +636,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   const int nqb = (d.nq + DQ_ROWS - 1) / DQ_ROWS;
   // (the query blocks of the query heads that share a key/value head are placed as one unit)
   int unit, blk;
-  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, g.by_size != 0, unit, blk)) return;
+  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, g.by_size != 0, unit, blk, kXcdCus * 8 / WAVES)) return;
   // (unit = part `part` of the walks over one key/value head; blocks numbered by size first when the
   // workgroups are ordered by size)
   const int kvh = unit / g.parts, part = unit - kvh * g.parts;

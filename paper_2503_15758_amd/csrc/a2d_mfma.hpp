@@ -130,14 +130,11 @@ __device__ __forceinline__ int dual_store_off(int r, int c) { return r * DUAL_LD
 // id = 8 k + x):
 //   by head  (by_size = false): head 8 * (k / nblocks) + x, block k % nblocks - a head's blocks run
 //            back to back and share its rows in L2; used when all blocks cost the same;
-//   by block (by_size = true):  the XCD's heads in chunks of kSizeChunk; inside a chunk block b of
+//   by block (by_size = true):  the XCD's heads in chunks (size_chunk); inside a chunk block b of
 //            every head before any block b + 1.  The callers number the blocks heaviest first, so
 //            under a causal mask that crosses the tile the workgroups start longest first and the
-//            compute units finish together (diagonal forward tile of 96 heads -7 %).  A chunk has to hold
-//            all heads of a launch of few turns, or its second chunk starts the longest walks last: chunks of
-//            4 took 51 us (forward) and 144 us (backward) at 40 x 1300 x 1300 causal H = 128, chunks of 16 take 40 and
-//            108; at 96 x 4096 x 4096 sizes from 2 to 16 are the same.  (The unmasked tile loses 2-3 % with
-//            this order, which is why it is not the default.)
+//            compute units finish together (diagonal forward tile of 96 heads -7 %).  (The unmasked tile
+//            loses 2-3 % with this order, which is why it is not the default.)
 // That holds for the first 8 * (heads / 8) heads.  The blocks of the remaining heads % 8 heads are
 // spread evenly over all XCDs instead (a head on an XCD of its own would leave the other XCDs
 // without work: a tile of 1 head used 32 of the 256 compute units, one of 12 heads ran 8 and then
@@ -146,11 +143,26 @@ __device__ __forceinline__ int dual_store_off(int r, int c) { return r * DUAL_LD
 // Grid size: 8 * (heads / 8 * nblocks + ceil(heads % 8 * nblocks / 8)); the few workgroups without
 // a block exit.
 constexpr int kXcds = 8;
-constexpr int kSizeChunk = 16;
+constexpr int kXcdCus = 32;                        // compute units of an XCD
+// Heads of a chunk, for `whole` heads of nblocks blocks on an XCD that holds `turn` workgroups at a time.  Few heads at a
+// time share their rows in L2; but every chunk starts its longest walks after the chunk before it, and the last one
+// must not start them late.
+//   - Launches of six turns or more whose heads make whole chunks of four: four.  Diagonal tiles, H = 128, one chunk of
+//     up to 16 heads -> chunks of 4: 96 x 4096 x 4096 reads 854 -> 468 MiB (forward) and 1611 -> 717 (recomputing dQ) in the same
+//     time; forward 128 x 4096 x 4096 597 -> 587 us, 192 x 4096 x 4096 887 -> 876, 64 x 8192 x 8192 1073 -> 1067.
+//   - Fewer turns, or a rest: one chunk, equal ones from 17 heads on.  Chunks of 4 cost 48 x 4096 x 4096 (three turns) 224 ->
+//     229 us, 96 x 2048 x 2048 (three) 128 -> 134, 40 x 1300 x 1300 37.5 -> 46.8 and, with a rest, 80 x 4096 x 4096 369 -> 390.
+//   - So do kernels that stream a score-sized operand or share little (turn = 0: dK/dV, dQ from dS).  With chunks of 4 dK/dV
+//     reads 1049 -> 966 MiB at 96 x 4096 x 4096, and the backward with dS takes 1397 -> 1415 us, at H = 64 964 -> 1010.
+__host__ __device__ inline int size_chunk(int whole, int nblocks, int turn) {
+  if (turn > 0 && whole % 4 == 0 && whole * nblocks >= 6 * turn) return 4;
+  const int n = (whole + 15) / 16;
+  return n <= 1 ? whole : (whole + n - 1) / n;
+}
 __host__ __device__ inline int xcd_grid(int heads, int nblocks) {
   return kXcds * (heads / kXcds * nblocks + (heads % kXcds * nblocks + kXcds - 1) / kXcds);
 }
-__device__ __forceinline__ bool xcd_map(int heads, int nblocks, bool by_size, int& head, int& block) {
+__device__ __forceinline__ bool xcd_map(int heads, int nblocks, bool by_size, int& head, int& block, int turn = 0) {
   const int id = blockIdx.x;
   const int x = id % kXcds;
   int k = id / kXcds;
@@ -170,9 +182,10 @@ __device__ __forceinline__ bool xcd_map(int heads, int nblocks, bool by_size, in
   }
   k -= per_xcd;
   if (by_size) {
-    const int c = k / (kSizeChunk * nblocks), kk = k - c * (kSizeChunk * nblocks);
-    const int width = min(kSizeChunk, whole - c * kSizeChunk);   // the last chunk may hold fewer heads
-    head = kXcds * (c * kSizeChunk + kk % width) + x;
+    const int chunk = size_chunk(whole, nblocks, turn);
+    const int c = k / (chunk * nblocks), kk = k - c * (chunk * nblocks);
+    const int width = min(chunk, whole - c * chunk);             // the last chunk may hold fewer heads
+    head = kXcds * (c * chunk + kk % width) + x;
     block = kk / width;
   } else {
     head = kXcds * (k / nblocks) + x;
