@@ -24,14 +24,12 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(bf16_t x) { return (float)x; }
 
-// 2^x and log2(x) on the hardware transcendental unit (about 1 ulp).
+// 2^x on the hardware transcendental unit (about 1 ulp).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
 template <typename T> struct dtype_of;
 template <> struct dtype_of<float> { static constexpr int value = A2D_F32; };
@@ -271,7 +269,6 @@ hipError_t launch_bwd_generic(Phase ph, const a2d_tile_desc& d, const SegList& g
 hipError_t launch_delta(const a2d_tile_desc& d, const void* O, const void* dO, float* delta, hipStream_t s);
 
 // bf16 MFMA tile kernels (H in {64, 80, 96, 128}).  `supported` tells whether the shape is covered.
-bool fwd_mfma_supported(const a2d_tile_desc& d);
 hipError_t launch_fwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                            const void* V, float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s);
 bool bwd_mfma_supported(const a2d_tile_desc& d);

@@ -235,7 +235,7 @@ __device__ __forceinline__ void contract_tile(Out<H>& acc, const Tile<H>& a, con
 
 // Sum of N results over the KL wavefronts of the workgroup, by halves: the upper half writes, the
 // lower half adds; wavefront 0 ends up with the total.  xch: KL / 2 areas of N * 64 16-byte pieces.
-template <int KL, int N, class Get>
+template <int N, class Get>
 __device__ __forceinline__ void merge_lanes(f32x4* xch, int kl, int lane, Get&& get) {
 #pragma unroll
   for (int half = KL / 2; half >= 1; half /= 2) {
@@ -417,17 +417,15 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   float* stat = reinterpret_cast<float*>(smem);      // [kl][t][16]
 #pragma unroll
   for (int t = 0; t < RT; ++t) m_all[t] = row_max(m_lane[t]);
-  if constexpr (KL > 1) {
-    __syncthreads();                                 // (the tiles are written over)
+  __syncthreads();                                   // (the tiles are written over)
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
-      if (g4 == 0) stat[(kl * RT + t) * 16 + l15] = m_all[t];
-    __syncthreads();
+  for (int t = 0; t < RT; ++t)
+    if (g4 == 0) stat[(kl * RT + t) * 16 + l15] = m_all[t];
+  __syncthreads();
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
+  for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int x = 0; x < KL; ++x) m_all[t] = fmaxf(m_all[t], stat[(x * RT + t) * 16 + l15]);
-  }
+    for (int x = 0; x < KL; ++x) m_all[t] = fmaxf(m_all[t], stat[(x * RT + t) * 16 + l15]);
   f32x4 lsum[RT];
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
@@ -435,13 +433,10 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     o[t].scale(f);
     lsum[t] = f32x4{row_sum(l_run[t]) * f, 0.f, 0.f, 0.f};
   }
-  if constexpr (KL > 1) {
-    constexpr int N = RT * (H / 16 + 1);
-    merge_lanes<KL, N>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& {
-      return i < RT ? lsum[i] : o[(i - RT) / (H / 16)].acc[(i - RT) % (H / 16)];
-    });
-    if (kl != 0) return;
-  }
+  merge_lanes<RT * (H / 16 + 1)>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& {
+    return i < RT ? lsum[i] : o[(i - RT) / (H / 16)].acc[(i - RT) % (H / 16)];
+  });
+  if (kl != 0) return;
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
     if (q_row[t] >= d.nq) continue;
@@ -532,10 +527,8 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
     contract_tile(dq, kt, ds, l15);
   }
-  if constexpr (KL > 1) {
-    merge_lanes<KL, H / 16>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& { return dq.acc[i]; });
-    if (kl != 0) return;
-  }
+  merge_lanes<H / 16>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& { return dq.acc[i]; });
+  if (kl != 0) return;
   if (q_row < d.nq) {
     float* row = dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H;
     dq.store(row, g4, d.scale, g.acc != 0);
@@ -639,12 +632,10 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     contract_tile(dv, gt, p, l15);
     contract_tile(dk, qt, ds, l15);
   }
-  if constexpr (KL > 1) {
-    merge_lanes<KL, H / 8>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& {
-      return i < H / 16 ? dk.acc[i] : dv.acc[i - H / 16];
-    });
-    if (kl != 0) return;
-  }
+  merge_lanes<H / 8>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& {
+    return i < H / 16 ? dk.acc[i] : dv.acc[i - H / 16];
+  });
+  if (kl != 0) return;
   if (key < d.nkv) {
     const int64_t row = ((int64_t)part * (d.heads / g.group) + head) * d.nkv + key;
     dk.store(dK + row * H, g4, d.scale);

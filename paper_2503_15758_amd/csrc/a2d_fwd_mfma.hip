@@ -458,10 +458,6 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
 
 }  // namespace
 
-bool fwd_mfma_supported(const a2d_tile_desc& d) {
-  return d.dtype == A2D_BF16 && (d.hdim == 128 || d.hdim == 96 || d.hdim == 80 || d.hdim == 64);
-}
-
 namespace {
 template <int WAVES, int HR, int KL>
 hipError_t fwd_launch(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
