@@ -44,7 +44,8 @@ def tile_flops(w, nq, nkv, causal_diag):
 
 
 def call_kernels(call, w, recompute):
-    """The library kernels one call of the step launches, in launch order."""
+    """The library kernels one call of the step launches, in launch order (bwd_dkdv_kernel: whichever form of it the
+    call takes, 128 or 256 keys per workgroup; the profiles name the one that ran)."""
     if call.startswith("partial_fwd"):
         return ["fwd_mfma_kernel" if w.dtype == "bf16" else "fwd_f32_kernel"]
     if call.startswith("partial_bwd"):
@@ -403,7 +404,8 @@ def main():
                 "dkdv_loop_model": {"tflops": round(tf_b, 1), "shader_mhz": round(mhz_b),
                                     "what": "paired score / gradient wavefronts, natural and transposing LDS fragments, "
                                             "fp32 mailbox, one barrier per 32-row step, random operands, nothing else "
-                                            "of the kernel",
+                                            "of the kernel: the form with 128 keys per workgroup (large tiles take "
+                                            "the one with 256, which hands nothing from wavefront to wavefront)",
                                     "tflops_without": without},
                 "lds_read_tbytes_per_s": {"b128": round(lds_n, 1), "b64_transposing": round(lds_t, 1),
                                           "what": "eight wavefronts per compute unit that only read LDS"},

@@ -314,9 +314,10 @@ a2d_status a2d_fix_norm(int k, int64_t rows, int32_t hdim, int32_t in_dtype, int
  *     a key/value head is the SUM over the query heads of its group (taken inside the kernel, in
  *     head order; one writer per element, no atomics).  flags: 0 or A2D_TILE_ACCUMULATE (dQ +=),
  *     optionally | A2D_TILE_SPLIT_GROUPS: the library may then give a key block to several
- *     workgroups, each summing over a share of the group's query heads into an fp32 partial buffer
- *     in the workspace, and add the partials up in a fixed order afterwards - for key/value head
- *     counts that leave compute units idle (few key/value heads, short key rows).  Same results
+ *     workgroups, each summing over an equal run of the group's query rows (it may end inside a head)
+ *     into an fp32 partial buffer in the workspace, and add the partials up in a fixed order
+ *     afterwards - for key/value head counts that leave compute units idle (few key/value heads, short
+ *     key rows).  Same results
  *     up to fp32 summation order, still bitwise reproducible; needs a workspace of
  *     a2d_workspace_bytes(desc, A2D_OP_PARTIAL_BWD_SPLIT, kv_heads) bytes.
  *     workspace otherwise as for a2d_partial_bwd.

@@ -267,7 +267,7 @@ def partial_bwd(Q, K, V, O, dO, lse, q_off=0, kv_off=0, causal=False, scale=None
     recomputing it, and the workspace (allocated here when none is given) must then hold
     a2d_workspace_bytes(A2D_OP_PARTIAL_BWD_DS) bytes.  split_groups=True
     (grouped heads only) passes A2D_TILE_SPLIT_GROUPS: a key block may go to several workgroups,
-    each summing over a share of the group's query heads (workspace of A2D_OP_PARTIAL_BWD_SPLIT
+    each summing over a run of the group's query rows (workspace of A2D_OP_PARTIAL_BWD_SPLIT
     size, which includes the dS area)."""
     return (_native or _ext()).partial_bwd(Q, K, V, O, dO, lse, q_off, kv_off, causal, scale, out, workspace, segments,
                                            accumulate, ds_handover, split_groups)

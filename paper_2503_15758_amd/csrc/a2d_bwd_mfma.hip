@@ -183,8 +183,8 @@ __device__ __forceinline__ void dk_second(DkCtx<HD>& cx, bf16x8 (&t)[HD / 32], c
 #undef A2D_TR
 #undef A2D_NAT
 
-// HR: head size = row length in memory (80, 96 or 128); the LDS tiles and fragments are laid out
-// for the padded head size HD = padded_head(HR) (96 or 128).
+// HR: head size = row length in memory (64, 80, 96 or 128); the LDS tiles and fragments are laid out
+// for the padded head size HD = padded_head(HR) (64, 96 or 128).
 // GROUPED: several query heads per key/value head (g.group > 1); the plain kernel is compiled
 // without the bookkeeping that walks them.
 // WRITE_DS: the gradient waves also leave dS in the workspace `dS` (layout above) for the
@@ -616,7 +616,7 @@ __device__ __forceinline__ void dq_piece(DqCtx<HD>& cx, int key0) {
 // the key blocks in two lanes (alternate blocks, own tile buffers) whose dQ sums are added through
 // LDS at the end - for tiles with at most one 128-row block per compute unit, so that a SIMD still
 // holds two wavefronts.
-// HR: head size (80, 96 or 128), HD its padded size, as in the dK/dV kernel.
+// HR: head size (64, 80, 96 or 128), HD its padded size, as in the dK/dV kernel.
 template <int WAVES, int HR, int KL>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,

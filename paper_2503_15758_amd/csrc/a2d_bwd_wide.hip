@@ -17,8 +17,8 @@ using namespace mfma;
 // under the dP MFMAs and the products dS under the dV MFMAs.  The scores start from -lse / scale
 // and dP from -delta, so that p = exp2(c s) and dS = p dP need no further operand.
 // Measured per 32 rows x 256 keys, H = 128 / 96 / 80 / 64: 1.51 / 1.22 / 1.17 / 0.99 us against 2.26 / 1.92 /
-// 1.86 / 1.58 us in pairs; the call at 96 x 4096 x 4096 H = 128 2.79 -> 2.59 ms (dS kept: 2.61 -> 2.48 ms - the
-// chip's power limit takes the rest back), at 32 x 1999 x 2777 H = 80 217 -> 187 us.
+// 1.86 / 1.58 us in pairs; the call at 96 x 4096 x 4096 H = 128 2.80 -> 2.60 ms (dS kept: 2.60 -> 2.43 ms), at
+// 32 x 1999 x 2777 H = 80 causal 217 -> 190 us.
 // (One wavefront per SIMD with two tiles of 32 keys, which halves the LDS reads again, issues too
 // slowly: 2.8 us at H = 128.)
 // Not for tiles with few keys, whose workgroups it halves (see plan_bwd_mfma).

@@ -27,10 +27,9 @@
 //     result (64 G + 16 g + 4 r + t), stored as four 16-byte pieces.  (H = 96 and 80 end in a group of
 //     32 or 16 columns with 8- or 4-byte pieces: Cols<H> below.)
 // Measured against the vector-ALU kernels of a2d_generic.hip: 16 heads x 700 x 900, H = 96, causal,
-// backward call 1034 -> 128 us (65 us dQ, 76 us dK/dV under the profiler); 2 heads x 128 x 128, H = 64,
-// forward 29 -> 6.4 us; 16 heads x 4096 x 4096, H = 128: forward 1.1 ms (125 TFLOP/s, 80 % of the fp32
-// matrix peak), dQ 2.0 ms (101 TFLOP/s executed), dK/dV 2.5 ms (111 TFLOP/s); the two backward kernels
-// then draw 13-14 TB/s from L2.
+// backward call 1034 -> 109 us (128 with the operands loaded lane = row; 52 us dQ, 69 us dK/dV by events around
+// them); 2 heads x 128 x 128, H = 64, forward 29 -> 5.2 us; 16 heads x 4096 x 4096, H = 128: forward 1.07 ms (129
+// TFLOP/s, 82 % of the fp32 matrix peak), dQ 1.73 ms (119 TFLOP/s executed), dK/dV 2.22 ms (124 TFLOP/s).
 #include "a2d_mfma.hpp"
 
 namespace a2d {

@@ -150,8 +150,8 @@ __device__ __forceinline__ void fwd_block(FwdState<HD>& st, const bf16x8 (&qf)[H
 //           blocks of the walk, each staging its own tiles into its own pair of LDS buffers, and
 //           their (N, m, l) are merged through LDS at the end exactly as two partials of one
 //           query block are (Alg. 2).
-// HR: head size = row length in memory (80, 96 or 128); the LDS tiles and fragments are laid out
-// for the padded head size HD = padded_head(HR) (96 or 128).
+// HR: head size = row length in memory (64, 80, 96 or 128); the LDS tiles and fragments are laid out
+// for the padded head size HD = padded_head(HR) (64, 96 or 128).
 // (O_part, m_out and l_out are not __restrict__: an accumulating call's `in` is the same memory)
 template <int WAVES, int HR, int KL>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(

@@ -105,8 +105,13 @@ def collect(args):
 def short_name(k):
     m = re.match(r"_ZN3a2d12_GLOBAL__N_1\d+([a-z_0-9]+kernel)", k) or \
         re.search(r"a2d::\(anonymous namespace\)::([a-z_0-9]+kernel)", k)
-    # the two forms of the dK/dV kernel (128 and 256 keys per workgroup) are one entry
-    return m.group(1).replace("bwd_dkdv_wide_", "bwd_dkdv_") if m else None
+    return m.group(1) if m else None
+
+
+def family(k):
+    """The launch log's name of a kernel: bench.py cannot see which form of the dK/dV kernel a call took (128 or
+    256 keys per workgroup) and logs both as one.  The tables name the form that ran."""
+    return k.replace("bwd_dkdv_wide_", "bwd_dkdv_")
 
 
 def _find(out_dir, pattern):
@@ -135,7 +140,7 @@ def kernel_rows(out_dir):
     out = []
     for r, e in zip(rows, log):
         k = short_name(r["Kernel_Name"])
-        if k != e["kernel"]:
+        if family(k) != e["kernel"]:
             sys.exit("%s: trace has %s where the launch log has %s" % (out_dir, k, e["kernel"]))
         out.append((k, e["call"], e["phase"], (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3,
                     r.get("Grid_Size_X", r.get("Grid_Size", "")), r.get("Workgroup_Size_X", r.get("Workgroup_Size", ""))))
@@ -160,7 +165,7 @@ def counter_rows(out_dir):
         vals = list(by_dispatch.values())
         if len(vals) != len(log):
             sys.exit("%s: %d dispatches carry %s, the launch log has %d" % (out_dir, len(vals), ctr, len(log)))
-        out[ctr] = [(k, e["call"], e["phase"], v) for (k, v), e in zip(vals, log) if k == e["kernel"]]
+        out[ctr] = [(k, e["call"], e["phase"], v) for (k, v), e in zip(vals, log) if family(k) == e["kernel"]]
         if len(out[ctr]) != len(log):
             sys.exit("%s: kernel names of %s do not follow the launch log" % (out_dir, ctr))
     return out
@@ -191,9 +196,9 @@ def tables(args):
         groups.setdefault((k, call, grid, wg), []).append(us)
     out = ["rocprofv3 kernel-trace summary of bench.py"] + head + ["command:", cmd("kt"), "",
            "Per kernel and call of the step (warm-up and timed steps; set-up launches left out), microseconds:", "",
-           "%-22s %-18s %10s %5s %6s %10s %10s %10s" % ("kernel", "call", "grid", "wg", "calls", "avg_us", "min_us", "max_us")]
+           "%-24s %-18s %10s %5s %6s %10s %10s %10s" % ("kernel", "call", "grid", "wg", "calls", "avg_us", "min_us", "max_us")]
     for (k, call, grid, wg), v in sorted(groups.items(), key=lambda kv: -sum(kv[1])):
-        out.append("%-22s %-18s %10s %5s %6d %10.1f %10.1f %10.1f" % (k, call, grid, wg, len(v), _avg(v), min(v), max(v)))
+        out.append("%-24s %-18s %10s %5s %6d %10.1f %10.1f %10.1f" % (k, call, grid, wg, len(v), _avg(v), min(v), max(v)))
     out += ["", "bench.py line of the same run (per-kernel times there come from HIP events on the launch stream):",
             _bench_line(os.path.join(args.dir, "kt"))]
     open(os.path.join(args.out, "%s_kernel_trace.txt" % name), "w").write("\n".join(out) + "\n")
@@ -217,10 +222,10 @@ def tables(args):
            "Scale factors from the library's copy kernel (a2d_copy_probe, 1 GiB read and 1 GiB written per launch):",
            "  FETCH_SIZE reads %.0f KiB -> factor %.3f;  WRITE_SIZE reads %.0f KiB -> factor %.3f" % (_avg(pf), fs, _avg(pw), ws),
            "", "Per launch, averaged over the steps, scaled, MiB:", "",
-           "%-18s %-22s %12s %12s" % ("call", "kernel", "read MiB", "written MiB")]
+           "%-18s %-24s %12s %12s" % ("call", "kernel", "read MiB", "written MiB")]
     per_call = collections.OrderedDict()
     for (call, k), (rv, wv) in per.items():
-        out.append("%-18s %-22s %12.1f %12.1f" % (call, k, _avg(rv) / 2 ** 20, _avg(wv) / 2 ** 20))
+        out.append("%-18s %-24s %12.1f %12.1f" % (call, k, _avg(rv) / 2 ** 20, _avg(wv) / 2 ** 20))
         per_call[call] = per_call.get(call, 0.0) + _avg(rv) + _avg(wv)
     out += ["", "# machine-readable (bench.py reads the lines below; bytes per launch of the whole call / of one kernel)",
             "source_sha256 %s" % stamp["source_sha256"], "git_head %s" % stamp["git_head"]]
@@ -254,7 +259,7 @@ def tables(args):
            "working); VALU = 4 x SQ_ACTIVE_INST_VALU / (1024 x cycles); LDS = SQ_LDS_IDX_ACTIVE / (256 CUs x cycles); conflicts =",
            "SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE; wait any / wait LDS = SQ_WAIT_INST_ANY / SQ_WAIT_INST_LDS over SQ_WAVE_CYCLES;",
            "MFMA TFLOP = 512 x SQ_INSTS_VALU_MFMA_MOPS_BF16 (executed, recomputation included).", "",
-           "%-18s %-20s %8s %6s %9s %8s %6s %6s %9s %9s %9s %10s" % ("call", "kernel", "time us", "GHz", "MFMA busy", "co-exec",
+           "%-18s %-24s %8s %6s %9s %8s %6s %6s %9s %9s %9s %10s" % ("call", "kernel", "time us", "GHz", "MFMA busy", "co-exec",
                                                                   "VALU", "LDS", "conflicts", "wait any", "wait LDS", "MFMA TFLOP")]
     for key in m1.get("GRBM_GUI_ACTIVE", {}):
         call, k = key
@@ -263,7 +268,7 @@ def tables(args):
         us = _avg(kt_us.get(key, []))
         g = lambda m, c: m.get(c, {}).get(key, float("nan"))
         lds_act = g(m1, "SQ_LDS_IDX_ACTIVE")
-        out.append("%-18s %-20s %8.0f %6.2f %8.1f%% %7.1f%% %5.1f%% %5.1f%% %8.1f%% %8.1f%% %8.1f%% %10.3f" % (
+        out.append("%-18s %-24s %8.0f %6.2f %8.1f%% %7.1f%% %5.1f%% %5.1f%% %8.1f%% %8.1f%% %8.1f%% %10.3f" % (
             call, k, us, cyc / us / 1e3 if us == us else float("nan"),
             100 * g(m1, "SQ_VALU_MFMA_BUSY_CYCLES") / (1024 * cyc),
             100 * g(m2, "SQ_VALU_MFMA_COEXEC_CYCLES") / (1024 * cyc2),
@@ -286,9 +291,9 @@ def tables(args):
         out = ["Vector-memory path per launch from rocprofv3 PMC counters over bench.py (raw counter values, mean per launch;"] + \
               ["SQ_* summed over the chip's SIMDs / wavefronts, TCP_* / TCC_* over their instances; cycles = GRBM_GUI_ACTIVE / 8)"] + head + \
               ["commands:", cmd("vmem"), cmd("tc"), ""]
-        out.append("%-18s %-20s %12s " % ("call", "kernel", "cycles") + " ".join("%14s" % c.replace("SQ_", "").replace("_sum", "")[:14] for c in cols))
+        out.append("%-18s %-24s %12s " % ("call", "kernel", "cycles") + " ".join("%14s" % c.replace("SQ_", "").replace("_sum", "")[:14] for c in cols))
         for key in mm.get("GRBM_GUI_ACTIVE", {}):
-            out.append("%-18s %-20s %12.0f " % (key[0], key[1], mm["GRBM_GUI_ACTIVE"][key] / 8.0) +
+            out.append("%-18s %-24s %12.0f " % (key[0], key[1], mm["GRBM_GUI_ACTIVE"][key] / 8.0) +
                        " ".join("%14.4g" % mm[c].get(key, float("nan")) for c in cols))
         open(os.path.join(args.out, "%s_memory_path.txt" % name), "w").write("\n".join(out) + "\n")
         shown.append("memory_path")
@@ -298,7 +303,7 @@ def tables(args):
 
 def read_traffic(workload, profiles_dir=None):
     """(dict name -> bytes, source hash the table was measured on) from profiles/<workload>_hbm_traffic.txt,
-    or ({}, None) when there is no such file."""
+    or ({}, None) when there is no such file.  Kernels by the launch log's names (family())."""
     path = os.path.join(profiles_dir or os.path.join(ROOT, "profiles"), "%s_hbm_traffic.txt" % workload)
     if not os.path.exists(path):
         return {}, None
@@ -306,7 +311,7 @@ def read_traffic(workload, profiles_dir=None):
     for line in open(path):
         p = line.split()
         if len(p) == 3 and p[0] == "traffic_bytes":
-            table[p[1]] = int(p[2])
+            table[family(p[1])] = int(p[2])
         elif len(p) == 2 and p[0] == "source_sha256":
             sha = p[1]
     return table, sha

@@ -1,6 +1,6 @@
-"""fp32 tile kernels at each launch shape, against the fp64 oracle: 16-row workgroups of eight and of four key
-lanes and 32-row workgroups of four, at ragged sizes, for every head size, with masks and grouped heads.
-(The small cases of test_gpu_parity.py all take the eight-lane shape.)"""
+"""fp32 tile kernels at each launch shape, against the fp64 oracle: 16-row and (forward) 32-row workgroups, each of
+four key lanes, at ragged sizes, for every head size, with masks and grouped heads.
+(The small cases of test_gpu_parity.py all take 16 rows.)"""
 import math
 
 import numpy as np
@@ -26,12 +26,12 @@ def a2d():
 
 # heads, kv_heads, nq, nkv, H, causal, q_off, segments (kv_off, rows)
 CASES = [
-    (9, 9, 479, 131, 64, False, 0, [(0, 131)]),                    # 30 row blocks per head: four lanes, one ragged row block
+    (9, 9, 479, 131, 64, False, 0, [(0, 131)]),                    # 30 row blocks per head, the last one ragged
     (6, 2, 700, 77, 80, True, 30, [(0, 77)]),                      # grouped; keys the first rows do not see
     (67, 67, 497, 50, 96, True, 20, [(0, 17), (40, 33)]),          # 16 blocks of 32 rows per head: 32-row workgroups
-    (64, 8, 513, 19, 128, True, 0, [(0, 3), (1, 16)]),             # the last block holds one row; fewer key blocks than lanes
+    (64, 8, 513, 19, 128, True, 0, [(0, 3), (1, 16)]),             # 32-row workgroups, the last with one row; fewer key blocks than lanes
     (34, 34, 961, 33, 80, False, 0, [(0, 33)]),
-    (2, 1, 17, 1000, 96, True, 990, [(5, 999), (0, 1)]),           # few row blocks: eight lanes; many key blocks
+    (2, 1, 17, 1000, 96, True, 990, [(5, 999), (0, 1)]),           # few row blocks, many key blocks: the walks are shared
 ]
 
 
