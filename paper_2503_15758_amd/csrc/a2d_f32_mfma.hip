@@ -3,8 +3,9 @@
 // fp32 throughout: v_mfma_f32_16x16x4_f32 multiplies and accumulates in fp32 (2048 flop in 32 cycles
 // of a SIMD, 157 TFLOP/s over the chip - twice what unpacked vector FMAs reach).
 //
-// What bounds them: the fp32 MFMA rate.  A step of 16 keys (queries) against 16 rows is H / 4 MFMAs
-// of 32 cycles per contraction, on 8 KiB of operands at H = 128.
+// What bounds them: the fp32 MFMA rate where there are many rows; at 16 x 700 x 900 two ragged launches, one
+// behind the other, in which the matrix units work 42-44 % of the cycles.  A step of 16 keys (queries)
+// against 16 rows is H / 4 MFMAs of 32 cycles per contraction, on 8 KiB of operands at H = 128.
 //   - Operands of a step come in by whole rows (16 lanes on 256 bytes), one step ahead, and pass through
 //     a tile in LDS that is the wavefront's own (no barriers): a contraction over H needs lane = row, and
 //     loading that from memory is 64 separate accesses per instruction, which kept the matrix units
@@ -20,7 +21,8 @@
 //     contracts the keys r, 4 + r, 8 + r, 12 + r.
 //   - Contractions over H read rows "naturally": lane (row l15, group g) reads the 16 bytes
 //     16 y + 4 g .. + 3 of its row, which serve four MFMAs (the contraction index may be permuted as
-//     long as both operands use the same permutation).  Tile rows are padded by 16 bytes: no conflicts.
+//     long as both operands use the same permutation).  Tile rows are padded by 16 bytes (the backward kernels'
+//     LDS cycles are 27-29 % bank conflicts all the same, at 18 % of the time in LDS and 42-44 % MFMA busy).
 //   - Contractions over rows need the transposed operand (lane = column): lane l15 loads 16 bytes of
 //     row 4 g + r, columns 64 G + 4 l15 + t, and MFMA t of the group takes one of the four, i.e. row
 //     i of its result is column 64 G + 4 i + t.  A lane then holds 16 consecutive columns of the
