@@ -266,13 +266,14 @@ void qkv(const at::Tensor& Q, const at::Tensor& K, const at::Tensor& V) {
 // Is the stream being captured by torch?  Its allocator then serves it from a pool that lives as long as the
 // graph; a capture begun by other means it knows nothing of.  torch's default generator takes part in torch's
 // captures, and on a capturing stream it can be asked for its state (here: moved on by nothing) in those only.
-bool torch_captures(const at::Device& device) {
+// (Called inside the library's frames: nothing may be thrown through them.)
+bool torch_captures(const at::Device& device) noexcept {
   try {
     at::Generator g = at::cuda::detail::getDefaultCUDAGenerator(device.index());
     std::lock_guard<std::mutex> lock(g.mutex());
     g.get<at::CUDAGeneratorImpl>()->philox_cuda_state(0);
     return true;
-  } catch (const c10::Error&) {
+  } catch (...) {
     return false;
   }
 }
