@@ -47,16 +47,16 @@ template <> struct dtype_of<bf16_t> { static constexpr int value = A2D_BF16; };
 // key/value head h / group; K, V, dK, dV have heads / group heads).
 // `by_size` != 0: the blocks of the tile differ in cost (a causal mask crosses it); the kernels then
 // order their workgroups by block, heaviest first, over a whole XCD (see xcd_map).
-// A launch over many tiles of one emulated side x side grid (one tile per grid.y; n = 0: a plain
-// call).  All blocks of the grid are views of the same tensors: block b of Q starts b * q elements
-// after block 0, and so on.  Tile (r, c) = query block r against key block c; under the causal mask
-// rel = q_off - kv_off is (r - c) * rows for contiguous blocks, 0 / -1 (r >= c / r < c) for cyclic
-// ones.  tri != 0: only the tiles c <= r exist.
+// A launch over a whole emulated side x side grid (side = 0: a plain call).  All blocks of the grid are
+// views of the same tensors: block b of Q starts b * q elements after block 0, and so on.  Tile (r, c) =
+// query block r against key block c; under the causal mask rel = q_off - kv_off is (r - c) * rows for
+// contiguous blocks, 0 / -1 (r >= c / r < c) for cyclic ones.  The forward walks whole grid rows.  The backward's
+// launches are over many tiles, one per grid.y (n = 0: a plain call); tri != 0: only the tiles c <= r exist.
 struct TileBatch {
   int n, first;        // tiles of this launch, number of its first tile
   int slots;           // tiles of the whole grid (1: a plain call); part z of a split walk is stored slots tiles on
   int side, tri, cyclic;
-  int64_t q, k, v, g;  // elements between blocks of Q, K, V, dO
+  int64_t q, k, v, g, o;  // elements between blocks of Q, K, V, dO, O
 };
 struct Segment {
   int start, rows;
@@ -134,6 +134,24 @@ __device__ __forceinline__ void warm_arguments() {
       : "s"(__builtin_amdgcn_kernarg_segment_ptr()), "i"(64 * tail), "i"(64 * (tail + (last > tail))), "i"(64 * last));
 }
 
+// ---- a whole grid: block t (all of them cost-ordered, heaviest first) of the side x nblk blocks of rows that a
+// head's row blocks are cut into, nblk each: row block r, block blk of it as the tile kernels number them
+struct GridBlock {
+  int r, blk;
+};
+__device__ __forceinline__ GridBlock grid_block(const TileBatch& b, int nblk, int t) {
+  const int per = b.cyclic ? b.side : nblk, x = t / per, y = t - x * per;
+  // (cyclic: equal positions of all row blocks cost the same; contiguous: later row blocks cost more)
+  return GridBlock{b.cyclic ? y : b.side - 1 - x, b.cyclic ? x : y};
+}
+__device__ __forceinline__ int grid_rel(const TileBatch& b, int rows, int r, int c) {
+  return b.cyclic ? (r >= c ? 0 : -1) : (r - c) * rows;
+}
+// token of row i of row block r
+__device__ __forceinline__ int grid_token(const TileBatch& b, int rows, int r, int i) {
+  return b.cyclic ? i * b.side + r : r * rows + i;
+}
+
 // sub-block that holds local key c (c < nkv)
 __device__ __forceinline__ int seg_of_key(const SegList& g, int c) {
   int s = 0;
@@ -194,6 +212,7 @@ struct WalkModel {
   double pair_step, pair_fixed;   // the same of two workgroups that share a slot (0: a slot holds one)
   const double* sorted;    // the steps at 8 places, longest first, as multiples of 1 / `per` (NULL: not known)
   double per;
+  double tail = 0.5;       // of a workgroup, while the last turn of uneven walks ends
 };
 inline double walk_time(const WalkModel& w, int parts) {
   const auto len = [&](double steps, double step, double fixed) {
@@ -209,7 +228,7 @@ inline double walk_time(const WalkModel& w, int parts) {
     return pairs ? turns / 2 * len(w.most, w.pair_step, w.pair_fixed) + turns % 2 * len(w.most, w.step, w.fixed)
                  : turns * len(w.most, w.step, w.fixed);
   const double each = pairs ? 0.5 * len(w.mean, w.pair_step, w.pair_fixed) : len(w.mean, w.step, w.fixed);
-  const double even = ((double)wgs / w.slots + 0.5) * each;               // longest first: half a workgroup of tail
+  const double even = ((double)wgs / w.slots + w.tail) * each;            // longest first
   double longest = len(w.most, pairs ? w.pair_step : w.step, w.fixed);
   if (w.sorted && !pairs) {
     // the first walk of the last turn: every slot then holds walks no shorter
@@ -303,15 +322,15 @@ struct OutMap {
 inline OutMap plain_out() { return OutMap{0, 0, 1, 1}; }
 // The merged output of a whole emulated grid: block b, head h, row i of the merge's input is token
 // i * side + b (cyclic) or b * rows + i of head h in a [heads][side * rows][H] tensor.  dir: which
-// partials block b has - 0: all `side`; 1: those x <= b (a grid row under the causal mask,
+// of the `from` partials block b has - 0: all; 1: those x <= b (a grid row under the causal mask,
 // contiguous blocks); 2: those x >= b (a grid column).  Each is in `parts` parts: partial e of the
 // pointer lists is part e % parts of partial e / parts.
 struct GridMap {
-  int side, rows, heads, cyclic, dir, parts;
+  int side, rows, heads, cyclic, dir, parts, from;
   // walks the pointer lists: does block b have the list's next entry?
   struct Walk { int x = 0, z = 0; };
   __host__ __device__ __forceinline__ bool next(Walk& w, int b) const {
-    const bool has = w.x < side && (dir == 0 || (dir == 1 ? w.x <= b : w.x >= b));
+    const bool has = w.x < from && (dir == 0 || (dir == 1 ? w.x <= b : w.x >= b));
     if (++w.z == parts) { w.z = 0; ++w.x; }
     return has;
   }

@@ -388,7 +388,7 @@ template <typename OutT>
 void fix_grid_dispatch(const GridMap& gm, int hv, const FixPtrs& p, const a2d_layout& lo, OutT* O, float* lse,
                        hipStream_t s) {
   const dim3 grid((unsigned)(((int64_t)gm.side * gm.heads * gm.rows * hv + 255) / 256)), block(256);
-  const int k = gm.side * gm.parts;
+  const int k = gm.from * gm.parts;
 #define A2D_GO(KMAX) A2D_LAUNCH((fix_grid_kernel<OutT, KMAX>), grid, block, 0, s, p, gm, hv, lo, O, lse)
   if (k <= 2) A2D_GO(2);
   else if (k <= 4) A2D_GO(4);
@@ -401,7 +401,7 @@ template <typename OutT>
 void sum_grid_dispatch(int nsets, const SumSets& a, int hv, int64_t blocks, hipStream_t s) {
   const dim3 grid((unsigned)blocks, nsets), block(256);
   int k = 0;
-  for (int x = 0; x < nsets; ++x) k = a.s[x].gm.side * a.s[x].gm.parts > k ? a.s[x].gm.side * a.s[x].gm.parts : k;
+  for (int x = 0; x < nsets; ++x) k = a.s[x].gm.from * a.s[x].gm.parts > k ? a.s[x].gm.from * a.s[x].gm.parts : k;
 #define A2D_GO(KMAX) A2D_LAUNCH((sum_grid_kernel<OutT, KMAX>), grid, block, 0, s, a, hv)
   if (k <= 2) A2D_GO(2);
   else if (k <= 4) A2D_GO(4);

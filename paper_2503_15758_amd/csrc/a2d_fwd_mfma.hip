@@ -153,7 +153,12 @@ __device__ __forceinline__ void fwd_block(FwdState<HD>& st, const bf16x8 (&qf)[H
 // HR: head size = row length in memory (64, 80, 96 or 128); the LDS tiles and fragments are laid out
 // for the padded head size HD = padded_head(HR) (64, 96 or 128).
 // (O_part, m_out and l_out are not __restrict__: an accumulating call's `in` is the same memory)
-template <int WAVES, int HR, int KL>
+// GRID: all query blocks of an emulated grid (g.b; 1: contiguous blocks, 2: cyclic ones).  A workgroup walks the
+// tiles of its whole grid row, so that AttnFix over the row happens in its registers, and writes rows of O and lse of
+// the sequence (or, of a split walk, a partial of them: [part][row block][head][row]).  The tiles of a row of
+// contiguous blocks are one run of keys.  Of cyclic ones, block j of every column comes before block j + 1 of any:
+// the workgroups of a head, which see different numbers of keys, then read the same part of the sequence at a time.
+template <int WAVES, int HR, int KL, int GRID>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
     const bf16_t* __restrict__ V, float* O_part, float* m_out, float* l_out, FwdInput in) {
@@ -164,6 +169,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   constexpr int KS = HD / 16, CT = HD / 32, KLD = kld(HD), K_BYTES = BN * KLD, BUF_BYTES = buf_bytes(HD);
   constexpr int KSR = (HR + 15) / 16;     // slices of H that hold data
   constexpr int kLdsBytes = lds_bytes(HD);
+  if constexpr (GRID) warm_arguments<9 * 8>();
   extern __shared__ __attribute__((aligned(16))) char lds_all[];
   // per key lane: [buf]{ K tile (BN x KLD), V tile (BN x VLD) }
   const int kl = KL == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);   // key lane of this wavefront
@@ -173,23 +179,27 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   const int nqb = (d.nq + BM - 1) / BM;
   // (the query blocks of the query heads that share a key/value head are placed as one unit)
   int unit, blk;
-  const TilePos tp = tile_pos<true>(d, g);
-  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, tp.by_size != 0, unit, blk, kXcdCus * 8 / WAVES)) return;
+  const int by_size = GRID ? d.causal : g.by_size;
+  if (!xcd_map(d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * nqb, by_size != 0, unit, blk,
+               kXcdCus * 8 / WAVES)) return;
   // (unit = part `part` of the walks over one key/value head; blocks numbered by size first when the
   // workgroups are ordered by size)
   const int kvh = unit / g.parts, part = unit - kvh * g.parts;
-  const int head = kvh * g.group + (tp.by_size ? blk % g.group : blk / nqb);
-  blk = tp.by_size ? blk / g.group : blk % nqb;
+  const int head = kvh * g.group + (GRID || by_size ? blk % g.group : blk / nqb);
+  blk = GRID || by_size ? blk / g.group : blk % nqb;
+  const GridBlock gb = GRID ? grid_block(g.b, nqb, blk) : GridBlock{0, blk};
+  const int row_blk = gb.r;                             // of the grid
+  blk = gb.blk;
   // heavy (late) query blocks first: under a causal mask they walk more key blocks
   const int q0 = (nqb - 1 - blk) * BM;
   const int tid = (int)threadIdx.x - kl * kThreads;     // within the key lane
   const int wave = tid >> 6, lane = tid & 63;
   const int half = lane >> 5, l32 = lane & 31;
-  Q += (int64_t)head * d.lq.head + tp.r * g.b.q;
-  K += (int64_t)kvh * d.lk.head + tp.c * g.b.k;
-  V += (int64_t)kvh * d.lv.head + tp.c * g.b.v;
-  {
-    const int64_t slot = ((int64_t)part * g.b.slots + col_slot(g.b, tp.r, tp.c)) * d.heads * d.nq;
+  Q += (int64_t)head * d.lq.head + (GRID ? row_blk * g.b.q : 0);
+  K += (int64_t)kvh * d.lk.head;
+  V += (int64_t)kvh * d.lv.head;
+  if (!GRID || !g.norm) {
+    const int64_t slot = ((int64_t)part * (GRID ? g.b.side : 1) + row_blk) * d.heads * d.nq;
     O_part += slot * HR;
     m_out += slot;
     l_out += slot;
@@ -213,7 +223,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   st.l_run = 0.f;
   const float c = d.scale * kLog2e;
   float m_in = -INFINITY;
-  if (g.acc && part == 0) {
+  if (!GRID && g.acc && part == 0) {
     // (key lane 0 of the first part continues the stored partial; the barriers are the whole workgroup's)
     // Continue from the (N, m, l) of `in`: N into the accumulators (same
     // element mapping as the epilogue's stores), m as the exponent reference, l into one of the two
@@ -269,8 +279,11 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // ---- visibility, per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
   // (key kk of the sub-block iff kk <= i + rel[s])
   auto vis_count = [&](int i, int s) -> int {
+    // (cyclic: of a column up to the row block's own; of the others one less, see `shift`)
+    if (GRID == 1) return d.causal ? row_blk * d.nq + i + 1 : g.b.side * d.nkv;
+    if (GRID == 2) return d.causal ? i + 1 : d.nkv;
     if (!d.causal) return g.seg[s].rows;
-    const int64_t v = (int64_t)i + g.seg[s].rel + tp.rel + 1;
+    const int64_t v = (int64_t)i + g.seg[s].rel + 1;
     return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
   };
   const int blk_last = min(q0 + BM, d.nq) - 1;
@@ -304,10 +317,14 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // span less than 4 GiB - the API layer checks it - so row index times stride fits 32 bits.)
   const unsigned k_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lk.row * 2);
   const unsigned v_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lv.row * 2);
+  // (cyclic: seg_start is the number of the grid's column, whose first row that is in the sequence)
+  const unsigned k_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.k * 2)) : k_row_bytes;
+  const unsigned v_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.v * 2)) : v_row_bytes;
   auto load_tile = [&](int seg_start, int seg_rows, int j) {
-    const int k0 = seg_start + j * BN;
-    const gptr_t kb = uniform_gptr(reinterpret_cast<const char*>(K) + (unsigned)k0 * k_row_bytes);   // scalar bases
-    const gptr_t vb = uniform_gptr(reinterpret_cast<const char*>(V) + (unsigned)k0 * v_row_bytes);
+    const unsigned k_at = seg_start * k_col_bytes + (unsigned)(j * BN) * k_row_bytes;
+    const unsigned v_at = seg_start * v_col_bytes + (unsigned)(j * BN) * v_row_bytes;
+    const gptr_t kb = uniform_gptr(reinterpret_cast<const char*>(K) + k_at);   // scalar bases
+    const gptr_t vb = uniform_gptr(reinterpret_cast<const char*>(V) + v_at);
     const int last = seg_rows - 1 - j * BN;
     if (ld_ok) {
 #pragma unroll
@@ -337,53 +354,72 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // (parts * KL)-th entry.  The sub-block table lives in kernel-argument memory, and scalar loads
   // share a wait counter with the LDS reads in flight, so it is only touched when a walk moves to
   // another sub-block; in between its values sit in registers.
-  // An entry is (sub-block sb, block j of its nblk); sb == g.n: past the end.
-  const int stride = KL * g.parts;
+  // An entry is (sub-block sb, block j of its nblk); sb == segs: past the end.
+  // (cyclic grids: block j of all columns first, see above)
+  constexpr bool PLAIN = GRID == 0, CYCLIC = GRID == 2;
+  const int stride = KL * g.parts, segs = PLAIN ? g.n : CYCLIC ? __builtin_amdgcn_readfirstlane(g.b.side) : 1;
+  const int grid_rows = GRID == 1 ? g.b.side * d.nkv : d.nkv;
+  auto seg_start = [&](int s) { return PLAIN ? g.seg[s].start : s; };
+  auto seg_rows = [&](int s) { return PLAIN ? g.seg[s].rows : grid_rows; };
+  const int jump = CYCLIC ? stride / segs : 0, jump_rest = stride - jump * segs;
   auto open_segment = [&](int s, int& sb, int& nblk) {           // first sub-block from s on with visible keys
-    while (s < g.n && seg_blocks(s) == 0) ++s;
+    while (s < segs && seg_blocks(s) == 0) ++s;
     sb = s;
-    if (s < g.n) nblk = seg_blocks(s);
+    if (s < segs) nblk = seg_blocks(s);
   };
   auto advance = [&](int by, int& sb, int& j, int& nblk) {
-    j += by;
-    while (seldom(j >= nblk)) {
-      if (sb >= g.n) break;
-      j -= nblk;
-      open_segment(sb + 1, sb, nblk);
+    if constexpr (CYCLIC) {
+      if (sb >= segs) return;
+      const int q = by == stride ? jump : by / segs;
+      j += q;
+      sb += by == stride ? jump_rest : by - q * segs;
+      if (sb >= segs) { sb -= segs; ++j; }
+      if (j >= nblk) sb = segs;
+    } else {
+      j += by;
+      while (seldom(j >= nblk)) {
+        if (sb >= segs) break;
+        j -= nblk;
+        open_segment(sb + 1, sb, nblk);
+      }
     }
   };
+  // cyclic: query i sees the keys kk <= i of columns up to its row block's own, kk < i of the others - the mask of the
+  // former with the keys numbered one higher
+  const int shift_from = CYCLIC && d.causal ? row_blk : segs;
   int sb, j = 0, nblk = 0;                         // this key lane's current entry
   open_segment(0, sb, nblk);
   advance(part * KL, sb, j, nblk);
   int lead_sb = sb, lead_j = j, lead_nblk = nblk;  // key lane 0's: every lane of the workgroup loops while it exists
   if (KL > 1) advance(kl, sb, j, nblk);
   int nx_start = 0, nx_rows = 0;                   // start / rows of the next entry's sub-block
-  if (sb < g.n) {
+  if (sb < segs) {
     enter_segment(sb);
-    nx_start = g.seg[sb].start; nx_rows = g.seg[sb].rows;
+    nx_start = seg_start(sb); nx_rows = seg_rows(sb);
     load_tile(nx_start, nx_rows, j);
   }
   // (one wait for the Q rows and the first tile: the two latencies overlap)
   wait_vmem_all();
   st.m_lane = st.m_ref = m_in / d.scale;               // -inf stays -inf
-  if (sb < g.n) store_tile(0);
+  if (sb < segs) store_tile(0);
   __syncthreads();
 
   int boff = 0;
-  while ((KL == 1 ? sb : lead_sb) < g.n) {
+  while ((KL == 1 ? sb : lead_sb) < segs) {
     int nsb = sb, nj = j, nnblk = nblk;
     advance(stride, nsb, nj, nnblk);
-    const bool more = nsb < g.n;
-    if (seldom(more && nsb != sb)) { nx_start = g.seg[nsb].start; nx_rows = g.seg[nsb].rows; }
+    const bool more = nsb < segs;
+    if (CYCLIC) nx_start = nsb;
+    else if (seldom(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
     if (more) load_tile(nx_start, nx_rows, nj);
-    const int k0 = j * BN;                         // local to the sub-block
-    if ((KL == 1 || sb < g.n) && k0 < nvis_wave) {
+    const int k0 = j * BN + (CYCLIC && sb > shift_from);       // local to the sub-block
+    if ((KL == 1 || sb < segs) && k0 < nvis_wave) {
       if (k0 + BN > nfull_wave) fwd_block<HD, true, KSR>(st, qf, k_rd0 + boff, v_rd0 + boff, k0, my_vis, half, c);
       else fwd_block<HD, false, KSR>(st, qf, k_rd0 + boff, v_rd0 + boff, k0, my_vis, half, c);
     }
     if (more) store_tile(BUF_BYTES - boff);
     __syncthreads();
-    if (seldom(more && nsb != sb)) enter_segment(nsb);
+    if (!CYCLIC && seldom(more && nsb != sb)) enter_segment(nsb);
     if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
     sb = nsb; j = nj; nblk = nnblk;
     boff = BUF_BYTES - boff;
@@ -425,9 +461,12 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // a lane's piece (column tile ht, group gq) covers columns 32 ht + 8 gq + 4 half + 0..3
   if (q_row < d.nq && g.norm) {
     // normalised partial: O' = N / l rounded to bf16, lse' = m + ln l (Sec. 3.2, footnote)
-    const int64_t row = (int64_t)head * d.nq + q_row;
+    // (GRID: the row of O and lse itself)
+    const int64_t row = GRID ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, q_row)
+                             : (int64_t)head * d.nq + q_row;
+    const int64_t o_at = GRID ? head * d.lo.head + row_blk * g.b.o + q_row * d.lo.row : row * H;
     const float fn = l_tot > 0.f ? f / l_tot : 0.f;
-    bf16_t* op = reinterpret_cast<bf16_t*>(O_part) + row * H + 4 * half;
+    bf16_t* op = reinterpret_cast<bf16_t*>(O_part) + o_at + 4 * half;
 #pragma unroll
     for (int ht = 0; ht < CT; ++ht)
 #pragma unroll
@@ -459,18 +498,34 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
 }  // namespace
 
 namespace {
-template <int WAVES, int HR, int KL>
+template <int WAVES, int HR, int KL, int GRID>
 hipError_t fwd_launch(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                       float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
   constexpr int bytes = KL * lds_bytes(padded_head(HR)), BM = 32 * WAVES / KL;
   if (ph == PREPARE)
-    return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_mfma_kernel<WAVES, HR, KL>), bytes);
-  dim3 grid(xcd_grid(d.heads / g.group * g.parts, g.group * ((d.nq + BM - 1) / BM)), g.b.n ? g.b.n : 1), block(64 * WAVES);
-  A2D_LAUNCH((fwd_mfma_kernel<WAVES, HR, KL>), grid, block, bytes, s, d, g, (const bf16_t*)Q,
+    return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_mfma_kernel<WAVES, HR, KL, GRID>), bytes);
+  dim3 grid(xcd_grid(d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * ((d.nq + BM - 1) / BM))), block(64 * WAVES);
+  A2D_LAUNCH((fwd_mfma_kernel<WAVES, HR, KL, GRID>), grid, block, bytes, s, d, g, (const bf16_t*)Q,
                      (const bf16_t*)K, (const bf16_t*)V, O_part, m, l, in);
   return hipGetLastError();
 }
 enum { FWD_BIG = 0, FWD_LANES = 1, FWD_PAIRS = 2 };   // <8, HR, 1>, <8, HR, 2>, <4, HR, 1>
+}  // namespace
+
+namespace {
+template <int GRID>
+hipError_t fwd_form(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                    float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
+#define A2D_FWD(HR)                                                                            \
+  return g.form == FWD_BIG     ? fwd_launch<8, HR, 1, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s) \
+         : g.form == FWD_LANES ? fwd_launch<8, HR, 2, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s) \
+                               : fwd_launch<4, HR, 1, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s)
+  if (d.hdim == 128) { A2D_FWD(128); }
+  if (d.hdim == 96) { A2D_FWD(96); }
+  if (d.hdim == 80) { A2D_FWD(80); }
+  A2D_FWD(64);
+#undef A2D_FWD
+}
 }  // namespace
 
 // Shape and parts.  Three shapes: 256-row workgroups, one per compute unit; 128-row workgroups whose two
@@ -480,36 +535,36 @@ enum { FWD_BIG = 0, FWD_LANES = 1, FWD_PAIRS = 2 };   // <8, HR, 1>, <8, HR, 2>,
 // constants are a fit to 95 shapes x three forms x up to five numbers of parts (1 x 128 x 128 to 96 x 1024 x
 // 2048, H = 64 and 128); its choice is 1 % slower than the best of them in the mean.
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
-  const int64_t heads = (int64_t)d.heads * (g->b.n ? g->b.n : 1);
-  const double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2;
-  const bool uneven = g->by_size || g->b.n;
+  const int64_t heads = (int64_t)d.heads * (g->b.side ? g->b.side : 1);
+  double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2, mean = most;
   double seen[8];
-  const double mean = uneven ? mean_visible_keys(d, *g, seen) / BN + 0.2 : most;
+  if (g->b.side) {                                             // (the rows of a whole sequence see half of it in the mean)
+    most = (double)g->b.side * ((d.nkv + BN - 1) / BN) + 0.2;
+    mean = d.causal ? 0.5 * most + 0.5 * (g->b.cyclic ? g->b.side : 1) : most;
+  } else if (g->by_size) {
+    mean = mean_visible_keys(d, *g, seen) / BN + 0.2;
+  }
   const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 3.7;
   const double part_us = (double)heads * d.nq * (d.hdim + 2) * 8 / 4.5e6;      // written and read back at 4.5 TB/s
   const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
-  const WalkModel m[3] = {{b256, cus, mean, most, step, fixed, 0, 0, nullptr, 0},
-                          {b128, cus, mean / 2, most / 2, step * 1.13, fixed + 0.8, 0, 0, nullptr, 0},
-                          {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, fixed + 0.5, nullptr, 0}};
+  // (the walks of a causal grid are of every length down to a few steps, so that the last ones end nearly together)
+  const double tail = g->b.side ? 0.1 : 0.5, big = g->b.side ? fixed + 1.5 : fixed;
+  const WalkModel m[3] = {{b256, cus, mean, most, step, big, 0, 0, nullptr, 0, tail},
+                          {b128, cus, mean / 2, most / 2, step * 1.13, fixed + 0.8, 0, 0, nullptr, 0, tail},
+                          {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, fixed + 0.5, nullptr, 0, tail}};
   double least = 0;
   for (int f = 0; f < 3; ++f) {
     double t;
-    const int z = best_parts(m[f], cap, g->b.n ? 0.0 : 3.2, part_us, &t);   // (a grid's partials are merged anyway)
+    const int z = best_parts(m[f], cap, 3.2, part_us, &t);
     if (f == 0 || t < (g->form == 0 ? 0.98 : 1.0) * least) { least = t; g->form = f; g->parts = z; }
   }
 }
 
 hipError_t launch_fwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                            const void* V, float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
-#define A2D_FWD(HR)                                                                      \
-  return g.form == FWD_BIG     ? fwd_launch<8, HR, 1>(ph, d, g, Q, K, V, O_part, m, l, in, s) \
-         : g.form == FWD_LANES ? fwd_launch<8, HR, 2>(ph, d, g, Q, K, V, O_part, m, l, in, s) \
-                               : fwd_launch<4, HR, 1>(ph, d, g, Q, K, V, O_part, m, l, in, s)
-  if (d.hdim == 128) { A2D_FWD(128); }
-  if (d.hdim == 96) { A2D_FWD(96); }
-  if (d.hdim == 80) { A2D_FWD(80); }
-  A2D_FWD(64);
-#undef A2D_FWD
+  return g.b.side == 0 ? fwd_form<0>(ph, d, g, Q, K, V, O_part, m, l, in, s)
+         : g.b.cyclic  ? fwd_form<2>(ph, d, g, Q, K, V, O_part, m, l, in, s)
+                       : fwd_form<1>(ph, d, g, Q, K, V, O_part, m, l, in, s);
 }
 
 }  // namespace a2d

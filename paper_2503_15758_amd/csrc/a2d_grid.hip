@@ -4,6 +4,9 @@
 // a call of its own - index gathers of the blocks, stream events, a handful of launches per tile, tiles
 // that fill an eighth of the chip.  512 tokens on a 2 x 2 grid took 52 launches and 680 us for 60 us of
 // kernels; 8192 tokens x 16 heads on 4 x 4 took 2.8 ms for 1.3 ms' worth of work.
+// The forward walks all tiles of a grid row in one workgroup: AttnFix over the row in registers, no partials in
+// memory, walks four times as long.  8192 tokens x 16 heads on 4 x 4, cyclic: tile launch and merge 441 + 49 us, one
+// launch 329 us.
 #include "a2d_grid.hpp"
 
 #include <cstring>
@@ -53,6 +56,7 @@ void describe(const GridProblem& p, a2d_tile_desc* d, SegList* g) {
   g->b.k = block_step(p, p.k);
   g->b.v = block_step(p, p.v);
   g->b.g = block_step(p, p.g);
+  g->b.o = block_step(p, p.o);
 }
 
 // tiles whose dS is kept at a time
@@ -63,7 +67,7 @@ int chunk_of(const GridProblem& p, const a2d_tile_desc& d, const SegList& g) {
 }
 
 GridMap map_of(const GridProblem& p, int heads, int dir, int parts) {
-  return GridMap{p.side, rows_of(p), heads, p.cyclic, tri_of(p) ? dir : 0, parts};
+  return GridMap{p.side, rows_of(p), heads, p.cyclic, tri_of(p) ? dir : 0, parts, p.side};
 }
 
 // Parts of the tiles' walks (few, small tiles): the merges of the grid take the parts along, so that only
@@ -76,10 +80,17 @@ size_t out_floats(const GridProblem& p, int heads) { return (size_t)slots_of(p) 
 
 // The forward's shape and parts, the backward's parts.  Both depend on the problem alone (the chunks
 // of the backward share its parts).  false: no device
+bool plan_forward(const GridProblem& p, const a2d_tile_desc& d, SegList* g) {
+  int cus = 0;
+  if (device_cus(&cus) != hipSuccess) return false;
+  const size_t floats = (size_t)p.heads * p.seq * (p.hdim + 2);
+  const size_t room = kSplitBytes / sizeof(float) / floats;
+  plan_fwd_mfma(d, g, cus, room < 1 ? 1 : room < A2D_MAX_PARTS ? (int)room : A2D_MAX_PARTS);
+  return true;
+}
 bool plan(const GridProblem& p, const a2d_tile_desc& d, SegList* g, BwdParts* b) {
   int cus = 0;
   if (device_cus(&cus) != hipSuccess) return false;
-  plan_fwd_mfma(d, g, cus, cap_of(p, out_floats(p, p.heads)));
   *b = plan_bwd_mfma(d, *g, true, cus, cap_of(p, 2 * out_floats(p, p.kv_heads)), cap_of(p, out_floats(p, p.heads)));
   return true;
 }
@@ -113,10 +124,9 @@ bool grid_supported(const GridProblem& p) {
 size_t grid_forward_bytes(const GridProblem& p) {
   a2d_tile_desc d;
   SegList g;
-  BwdParts b;
   describe(p, &d, &g);
-  if (!plan(p, d, &g, &b)) return 0;
-  return (size_t)g.parts * slots_of(p) * p.heads * rows_of(p) * (p.hdim + 2) * sizeof(float);
+  if (!plan_forward(p, d, &g) || g.parts == 1) return 0;
+  return (size_t)g.parts * p.heads * p.seq * (p.hdim + 2) * sizeof(float);
 }
 
 size_t grid_backward_bytes(const GridProblem& p) {
@@ -135,30 +145,30 @@ hipError_t grid_forward(const GridProblem& p, const void* Q, const void* K, cons
   a2d_tile_desc d;
   SegList g;
   describe(p, &d, &g);
-  const size_t per = (size_t)p.heads * rows_of(p), slots = slots_of(p);
-  float* N = static_cast<float*>(ws);
-  float *m = nullptr, *l = nullptr;
-  BwdParts unused;
-  if (!plan(p, d, &g, &unused)) return hipErrorInvalidDevice;
+  if (!plan_forward(p, d, &g)) return hipErrorInvalidDevice;
   const FwdInput none{nullptr, nullptr, nullptr};
-  m = N + g.parts * slots * per * p.hdim;
-  l = m + g.parts * slots * per;
+  const size_t rows = (size_t)p.heads * p.seq;
+  float *N = static_cast<float*>(O), *m = lse, *l = nullptr;   // lines 4-6 of Alg. 1 in one launch ...
+  g.norm = g.parts == 1;
+  if (g.parts > 1) {                                           // ... or the partials of split walks
+    N = static_cast<float*>(ws);
+    m = N + g.parts * rows * p.hdim;
+    l = m + g.parts * rows;
+  }
   hipError_t e = launch_fwd_mfma(PREPARE, d, g, Q, K, V, N, m, l, none, s);
   if (e != hipSuccess) return e;
   trace_mark(s);
-  e = launch_fwd_mfma(LAUNCH, d, g, Q, K, V, N, m, l, none, s);      // Alg. 1 line 4, every tile
-  if (e != hipSuccess) return e;
+  e = launch_fwd_mfma(LAUNCH, d, g, Q, K, V, N, m, l, none, s);
+  if (e != hipSuccess || g.parts == 1) return e;
   FixPtrs f;
   memset(&f, 0, sizeof(f));
-  for (int c = 0; c < p.side; ++c) {                           // column c's partials, indexed by (row block, head, row)
-    for (int z = 0; z < g.parts; ++z) {
-      const size_t at = (size_t)(z * (int)slots + col_slot(g.b, c, c) - c) * per;
-      f.o[c * g.parts + z] = N + at * p.hdim;
-      f.m[c * g.parts + z] = m + at;
-      f.l[c * g.parts + z] = l + at;
-    }
+  for (int z = 0; z < g.parts; ++z) {                          // each [row block][head][row]
+    f.o[z] = N + z * rows * p.hdim;
+    f.m[z] = m + z * rows;
+    f.l[z] = l + z * rows;
   }
-  return launch_fix_grid(map_of(p, p.heads, 1, g.parts), p.hdim, A2D_BF16, f, p.o, O, lse, s);   // Alg. 1 lines 5-6
+  const GridMap parts{p.side, rows_of(p), p.heads, p.cyclic, 0, g.parts, 1};
+  return launch_fix_grid(parts, p.hdim, A2D_BF16, f, p.o, O, lse, s);
 }
 
 hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, const void* V, const void* O,

@@ -1,6 +1,6 @@
-// Alg. 1 and Alg. 3 over a whole emulated side x side grid in a handful of launches: every tile of the
-// grid is computed by the tile kernels as in the single calls, many tiles per launch (TileBatch), on
-// the blocks where they lie in the sequence (contiguous or cyclic: a stride, not a copy).
+// Alg. 1 and Alg. 3 over a whole emulated side x side grid in a handful of launches: the tile kernels, on all
+// grid rows (forward) or many tiles (backward) per launch (TileBatch), on the blocks where they lie in the
+// sequence (contiguous or cyclic: a stride, not a copy).
 #pragma once
 #include <hip/hip_runtime_api.h>
 

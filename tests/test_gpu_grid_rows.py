@@ -1,0 +1,53 @@
+"""The whole-grid launches, which walk all tiles of a grid row (forward) at once, against full attention in fp64 on the GPU:
+edges of the key blocks and workgroups in blocks of every kind, one-row blocks, split walks, every workgroup shape."""
+import math
+
+import pytest
+import torch
+
+from test_gpu_split_walks import _rel
+
+pytestmark = pytest.mark.gpu
+
+# heads, kv_heads, rows per block, grid, H
+CASES = [
+    (1, 1, 1, 2, 64),
+    (3, 1, 1, 32, 128),            # one row of every column
+    (2, 2, 63, 2, 128),
+    (2, 1, 64, 3, 80),
+    (4, 4, 65, 8, 96),             # more columns than the parts of a split walk step over
+    (1, 1, 129, 5, 128),
+    (40, 40, 257, 2, 64),          # a workgroup shape each: 128-row pairs ...
+    (48, 24, 255, 4, 128),         # ... and 256 rows
+    (16, 8, 513, 3, 96),
+    (2, 2, 2000, 1, 128),          # a grid of one tile, in two key lanes and parts
+]
+
+
+@pytest.mark.parametrize("layout", ["cyclic", "contiguous"])
+@pytest.mark.parametrize("causal", [True, False], ids=["causal", "full"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%dq%dkv_%dx%d_H%d" % c)
+def test_grid_rows(case, causal, layout):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_15758_amd import binding as a2d, grid as g2d
+    heads, kvh, rows, side, H = case
+    n, scale, gen = rows * side, 1.0 / math.sqrt(H), torch.Generator(device="cuda")
+    gen.manual_seed(29)
+    print("grid rows case", case, causal, layout, flush=True)
+    make = lambda h: torch.randn(h, n, H, generator=gen, device="cuda").to(torch.bfloat16)
+    Q, K, V = make(heads), make(kvh), make(kvh)
+    q = Q.double()
+    k, v = (x.double().repeat_interleave(heads // kvh, 0) for x in (K, V))
+    S = torch.bmm(q, k.transpose(1, 2).contiguous()) * scale
+    if causal:
+        S = S.masked_fill(torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1), -math.inf)
+    lse = torch.logsumexp(S, 2)
+    O = torch.bmm(torch.exp(S - lse[..., None]), v)
+    assert a2d._ext().grid_forward(Q, K, V, side, causal, layout == "cyclic", scale) is not None
+    got, got_lse = g2d.forward(Q, K, V, side, causal, layout, scale)
+    # P and O rounded to bf16 once each: 2^-9 a term at most, 3e-3 of the norm and less
+    assert _rel(got, O) < 5e-3, "O: %.2e" % _rel(got, O)
+    assert (got_lse.double() - lse).abs().max() < 1e-4
+    again, again_lse = g2d.forward(Q, K, V, side, causal, layout, scale)
+    assert torch.equal(got, again) and torch.equal(got_lse, again_lse)
