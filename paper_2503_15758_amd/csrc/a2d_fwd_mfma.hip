@@ -235,21 +235,22 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     char* area = lds_all + wave * 16 * ALD;
     const int64_t wrow0 = (int64_t)head * d.nq + q0 + wave * 32;   // first row of the wavefront
     const int64_t last_row = (int64_t)head * d.nq + d.nq - 1;
-    const bool col_ok = 4 * (lane & 31) < H;                 // this lane's 16-byte piece exists in the row
+    // (a lane whose 16-byte piece lies past the row's end re-reads its last piece and stores zeros, or nothing)
+    const int col = 4 * (lane & 31), col_ld = min(col, H - 4);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-      u32x4 t[8];
+      if (KL == 1 || kl == 0) {
+        u32x4 t[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {                          // two whole rows per load instruction
-        const int64_t r = wrow0 + 16 * pass + 2 * i + (lane >> 5);
-        t[i] = u32x4{0, 0, 0, 0};
-        if (col_ok && kl == 0)
-          t[i] = *reinterpret_cast<const u32x4*>(in.N + (r < last_row ? r : last_row) * H + 4 * (lane & 31));
-      }
-      if (4 * (lane & 31) < HD && kl == 0) {
+        for (int i = 0; i < 8; ++i) {                        // two whole rows per load instruction
+          const int64_t r = wrow0 + 16 * pass + 2 * i + (lane >> 5);
+          t[i] = *reinterpret_cast<const u32x4*>(in.N + (r < last_row ? r : last_row) * H + col_ld);
+        }
+        if (HD == 128 || col < HD) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          *reinterpret_cast<u32x4*>(area + (2 * i + (lane >> 5)) * ALD + 16 * (lane & 31)) = t[i];
+          for (int i = 0; i < 8; ++i)
+            *reinterpret_cast<u32x4*>(area + (2 * i + (lane >> 5)) * ALD + 4 * col) = H == HD || col < H ? t[i] : u32x4{0, 0, 0, 0};
+        }
       }
       __syncthreads();
       if ((l32 >> 4) == pass && kl == 0) {
