@@ -110,7 +110,6 @@ a2d::SegList one_segment(const a2d_tile_desc* d) {
   g.n = 1;
   g.group = 1;
   g.parts = 1;
-  g.b.slots = 1;
   g.seg[0].start = 0;
   g.seg[0].rows = d->nkv;
   g.seg[0].rel = d->q_off - d->kv_off;
@@ -126,7 +125,6 @@ a2d_status make_segments(const a2d_tile_desc* d, int nseg, const a2d_kv_segment*
   g->n = nseg;
   g->group = 1;
   g->parts = 1;
-  g->b.slots = 1;
   int64_t total = 0;
   for (int s = 0; s < nseg; ++s) {
     if (segs[s].rows < 1 || segs[s].pad != 0)

@@ -5,6 +5,22 @@
 namespace a2d {
 namespace mfma {
 
+// a transposed accumulator rounded to bf16 (see store_acc_t)
+template <int CT>
+__device__ __forceinline__ void store_acc_t(bf16_t* __restrict__ out_row, const f32x16 (&acc)[CT], int half, float mul,
+                                            int h) {
+#pragma unroll
+  for (int ht = 0; ht < CT; ++ht)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if (32 * ht + 8 * g + 4 * half >= h) continue;
+      bf16x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = (bf16_t)(acc[ht][4 * g + e] * mul);
+      *reinterpret_cast<bf16x4*>(out_row + 32 * ht + 8 * g + 4 * half) = v;
+    }
+}
+
 // stores a transposed accumulator (lane = one output row, registers = 4-column groups)
 // (add: onto what the row already holds)
 // CT column tiles of 32; pieces whose columns lie past the head size h are skipped

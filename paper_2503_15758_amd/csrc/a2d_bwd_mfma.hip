@@ -128,13 +128,14 @@ template <bool MASK, int HD>
 __device__ __forceinline__ void dk_probs(const DkCtx<HD>& cx, const f32x4 (&st)[4], f32x16& s,
                                          bf16x8 (&bf)[2], int qs0, int nq) {
   const int first = qs0 + 4 * cx.half - cx.my_first;
+  const unsigned limit = max(nq - cx.my_first, 0);            // (padding keys: none)
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     f32x4 p4;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float p = fast_exp2(fmaf(s[4 * g + e], cx.c, -st[g][e]));
-      if (MASK && (unsigned)(first + 8 * g + e) >= (unsigned)(nq - cx.my_first)) p = 0.f;
+      if (MASK && (unsigned)(first + 8 * g + e) >= limit) p = 0.f;
       s[4 * g + e] = p;
       p4[e] = p;
     }
@@ -191,9 +192,8 @@ __device__ __forceinline__ void dk_second(DkCtx<HD>& cx, bf16x8 (&t)[HD / 32], c
 // contraction-only dQ kernel.
 // PLAIN: Q and dO are in the plain layout (row stride H, head stride nq * H): the staging offsets
 // are then compile-time multiples and one offset serves both tensors (3 % on the recomputing path).
-// BATCH: may be launched over many tiles (g.b.n > 0); the kernels of single tiles are compiled without
-// it (1 % of the 4096 x 4096 backward).
-template <int HR, bool GROUPED, bool WRITE_DS, bool PLAIN = false, bool BATCH = false>
+// GRID: all key blocks of an emulated grid, as in bwd_dkdv_wide_kernel.
+template <int HR, bool GROUPED, bool WRITE_DS, bool PLAIN = false, int GRID = 0>
 __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
     const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO, const float* __restrict__ lse,
@@ -207,19 +207,26 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   // With g.parts > 1 that many workgroups share a key block: workgroup `part` walks its share of the
   // steps over the group's query rows and leaves its sums in partial buffer `part` (dK, dV then point
   // at parts buffers of [key/value heads][nkv][H], added up by a sum kernel afterwards).
-  const int group = GROUPED ? g.group : 1;
-  const TilePos tp = tile_pos<BATCH>(d, g);
+  static_assert(!GRID || (GROUPED && !WRITE_DS && !PLAIN), "the grid's form");
+  constexpr bool CYCLIC = GRID == 2;
+  const int group = GROUPED ? g.group : 1, kv_heads = GROUPED ? d.heads / g.group : d.heads;
+  const int nkb = (d.nkv + DK_KEYS - 1) / DK_KEYS;
   int unit;
-  if (!xcd_map((GROUPED ? d.heads / g.group : d.heads) * g.parts, (d.nkv + DK_KEYS - 1) / DK_KEYS, tp.by_size != 0,
-               unit, blk)) return;
+  if (!xcd_map(kv_heads * g.parts, (GRID ? g.b.side : 1) * nkb, (GRID ? d.causal : g.by_size) != 0, unit, blk)) return;
   head = unit / g.parts;
   const int part = unit - head * g.parts;
   const int qh0 = GROUPED ? head * g.group : head;           // the first query head, as a head of Q
-  {
-    const int64_t first = (int64_t)part * g.b.slots * (GROUPED ? d.heads / g.group : d.heads) * d.nkv * HR;
+  const GridBlock gb = GRID ? grid_column(g.b, nkb, blk) : GridBlock{0, blk};
+  const int col = gb.r;                                      // of the grid
+  blk = gb.blk;
+  if (!GRID || g.parts > 1) {
+    const int64_t first = ((int64_t)part * (GRID ? g.b.side : 1) + col) * kv_heads * d.nkv * HR;
     dK += first;
     dV += first;
   }
+  const int side = CYCLIC ? __builtin_amdgcn_readfirstlane(g.b.side) : 1;      // row blocks that are walked in turn
+  const int nq = GRID == 1 ? g.b.side * d.nq : d.nq, head_rows = nq * side;    // rows of a run; of a query head
+  const int col_first = GRID == 1 && d.causal ? col * d.nkv : 0;               // the row that sees the column's first key
   constexpr int HD = padded_head(HR), H = HR, KS = HD / 16, CT = HD / 32;
   constexpr int KSR = (HR + 15) / 16;       // slices of H that hold data
   const int k0 = blk * DK_KEYS;
@@ -227,17 +234,12 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int pair = wave & 3, role = wave >> 2;   // wavefronts w and w + 4 share 32 keys
   const int l32 = lane & 31;
-  Q += (int64_t)qh0 * d.lq.head + tp.r * g.b.q;
-  dO += (int64_t)qh0 * d.ldo.head + tp.r * g.b.g;
-  K += (int64_t)head * d.lk.head + tp.c * g.b.k;
-  V += (int64_t)head * d.lv.head + tp.c * g.b.v;
-  lse += ((int64_t)tp.r * d.heads + qh0) * d.nq;
-  delta += ((int64_t)tp.r * d.heads + qh0) * d.nq;
-  if (BATCH) {
-    const int64_t slot = (int64_t)row_slot(g.b, tp.r, tp.c) * (GROUPED ? d.heads / g.group : d.heads) * d.nkv * H;
-    dK += slot;
-    dV += slot;
-  }
+  Q += (int64_t)qh0 * d.lq.head;
+  dO += (int64_t)qh0 * d.ldo.head;
+  K += (int64_t)head * d.lk.head + (GRID ? col * g.b.k : 0);
+  V += (int64_t)head * d.lv.head + (GRID ? col * g.b.v : 0);
+  lse += (int64_t)qh0 * head_rows;
+  delta += (int64_t)qh0 * head_rows;
 
   DkCtx<HD> cx;
   cx.half = lane >> 5;
@@ -260,15 +262,16 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   // Query i sees key kk of key/value sub-block s iff i >= kk - rel[s].  seg_first_row(sb, r): first
   // local query row that sees local key r of sub-block sb (nq if none does).
   auto seg_first_row = [&](int sb, int r) -> int {
-    const int64_t f = (int64_t)(r - g.seg[sb].start) - g.seg[sb].rel - tp.rel;
+    const int64_t f = (int64_t)(r - g.seg[sb].start) - g.seg[sb].rel;
     return f <= 0 ? 0 : (f >= d.nq ? d.nq : (int)f);
   };
   // smallest / largest such row over the local keys a .. b - 1 (inside a sub-block it grows with
   // the key, so only the ends of the covered part of each sub-block matter).  Each sub-block's
   // table entries are read once, with no load depending on another.
   auto first_row_range = [&](int a, int b, int& lo, int& hi) {
-    lo = d.nq; hi = 0;
+    lo = nq; hi = 0;
     if (!d.causal) { lo = 0; return; }
+    if (GRID) { lo = col_first + a; hi = col_first + b - 1; return; }
     for (int sb = 0; sb < g.n; ++sb) {
       const int x = max(a, g.seg[sb].start), y = min(b, g.seg[sb].start + g.seg[sb].rows);
       if (x >= y) continue;
@@ -280,9 +283,10 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   first_row_range(k0, min(k0 + DK_KEYS, d.nkv), wg_lo, wg_hi);
   // The walk: nsteps steps of BQ rows per query head, the group's heads one after the other.  A part
   // takes an equal run of it: `total` steps from step s0 of head h0 of the group on.
+  // (cyclic grids: step s of every row block before step s + 1 of any)
   int i_start = (wg_lo / BQ) * BQ;
-  int nsteps = (d.nq - i_start + BQ - 1) / BQ;
-  int total = nsteps * group, s0 = 0, h0 = 0;
+  int nsteps = (nq - i_start + BQ - 1) / BQ;
+  int total = nsteps * side * group, s0 = 0, r0 = 0, h0 = 0;
   if (g.parts > 1) {
     const int all = total, first = (int)((int64_t)part * all / g.parts);
     total = (int)((int64_t)(part + 1) * all / g.parts) - first;
@@ -290,25 +294,28 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
       i_start += first * BQ;
       nsteps = total;
     } else if (nsteps > 0) {
-      h0 = first / nsteps;
-      s0 = first - h0 * nsteps;
+      h0 = first / (nsteps * side);
+      s0 = first - h0 * (nsteps * side);
+      if (CYCLIC) { r0 = s0 % side; s0 /= side; }
     }
     if (total == 0) nsteps = 0;
   }
   const int wk_first = k0 + pair * 32, wk_end = min(wk_first + 32, d.nkv);
-  cx.my_first = d.nq;                                         // padding keys see nothing
+  cx.my_first = nq;                                           // padding keys see nothing
   if (key < d.nkv) {
-    cx.my_first = 0;
-    if (d.causal) {
+    cx.my_first = GRID && d.causal ? col_first + key : 0;
+    if (!GRID && d.causal) {
       for (int sb = 0; sb < g.n; ++sb)                        // uniform loop, per-lane select
         if (key >= g.seg[sb].start && key < g.seg[sb].start + g.seg[sb].rows) cx.my_first = seg_first_row(sb, key);
     }
   }
-  int w_any = d.nq, w_all = d.nq;   // rows below w_any see none of the pair's keys, rows from w_all on all
+  int w_any = nq, w_all = nq;       // rows below w_any see none of the pair's keys, rows from w_all on all
   if (wk_first < wk_end) {
     first_row_range(wk_first, wk_end, w_any, w_all);
-    if (wk_end < wk_first + 32) w_all = d.nq;                 // padding keys in the pair: always masked
+    if (wk_end < wk_first + 32) w_all = nq;                   // padding keys in the pair: always masked
   }
+  // cyclic: the row blocks before the column see a key a row later than the others
+  const int late = CYCLIC && d.causal ? col : 0;
 
   // ---- The gradient waves run ONE STEP BEHIND the score waves: in iteration j the score wave
   // computes S, P, dV of step j and leaves P in mailbox slot j & 1, while the gradient wave of
@@ -351,11 +358,13 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   // ld_left follow the next step's position - its step inside the query head, the head's first
   // row - without a division)
   // (ld_qh / ld_gh: byte offset of the query head's first row of Q / dO from the group's first head)
-  int ld_s = s0, ld_row0 = h0 * d.nq, ld_left = total - 1;
+  int ld_s = s0, ld_r = r0, ld_row0 = h0 * head_rows, ld_left = total - 1;
   const unsigned q_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lq.row * 2);
   const unsigned g_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.row * 2);
   const unsigned q_head_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lq.head * 2);
   const unsigned g_head_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.head * 2);
+  const unsigned q_blk_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.q * 2)) : 0;
+  const unsigned g_blk_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.g * 2)) : 0;
   unsigned ld_qh = h0 * q_head_bytes, ld_gh = h0 * g_head_bytes;
   auto load_step = [&](int step, auto set_tag) {
     constexpr int SET = decltype(set_tag)::value;
@@ -365,20 +374,27 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
       qreg[SET] = gload_b128(q_base, off);
       greg[SET] = gload_b128(g_base, off);
     } else {
-      const unsigned r = (unsigned)min(i0 + st_row, d.nq - 1);
-      qreg[SET] = gload_b128(q_base, ld_qh + __umul24(r, q_row_bytes) + ld_ch * 16);
-      greg[SET] = gload_b128(g_base, ld_gh + __umul24(r, g_row_bytes) + ld_ch * 16);
+      const unsigned r = (unsigned)min(i0 + st_row, nq - 1);
+      qreg[SET] = gload_b128(q_base, ld_qh + (CYCLIC ? ld_r * q_blk_bytes : 0u) + __umul24(r, q_row_bytes) + ld_ch * 16);
+      greg[SET] = gload_b128(g_base, ld_gh + (CYCLIC ? ld_r * g_blk_bytes : 0u) + __umul24(r, g_row_bytes) + ld_ch * 16);
     }
     // raw statistic loads only: converting here would make the wave wait for everything just
     // issued.  Every thread loads one (only the first 64 values are used) so that each set is
     // the same number of loads in every wavefront.
-    const int i = ld_row0 + min(i0 + (tid & (BQ - 1)), d.nq - 1);
+    const int ir = min(i0 + (tid & (BQ - 1)), nq - 1);
+    const int i = ld_row0 + (CYCLIC ? ir * side + ld_r : ir);
     stat[SET] = (tid & BQ) ? delta[i] : lse[i];
-    stat_ok[SET] = (i0 + (tid & (BQ - 1))) < d.nq;
+    stat_ok[SET] = (i0 + (tid & (BQ - 1))) < nq;
     if constexpr (GROUPED) {   // next step; the last one repeats
-      const bool more = ld_left > 0, wrap = ld_s + 1 == nsteps;
+      bool more = ld_left > 0;
       ld_left -= more ? 1 : 0;
-      ld_row0 += (more && wrap) ? d.nq : 0;
+      if constexpr (CYCLIC) {
+        const bool last = ld_r + 1 == side;
+        ld_r = more ? (last ? 0 : ld_r + 1) : ld_r;
+        more = more && last;
+      }
+      const bool wrap = ld_s + 1 == nsteps;
+      ld_row0 += (more && wrap) ? head_rows : 0;
       ld_qh += (more && wrap) ? q_head_bytes : 0u;
       ld_gh += (more && wrap) ? g_head_bytes : 0u;
       ld_s = more ? (wrap ? 0 : ld_s + 1) : ld_s;
@@ -415,19 +431,26 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
   const unsigned ds_lane_off = (unsigned)(2 * blk + (pair >> 1)) * DS_TILE_BYTES + (pair & 1) * 2048 + lane * 16;
   gwptr_t ds_base = nullptr;
   if constexpr (WRITE_DS)
-    ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) +
-                            ((BATCH ? (int64_t)blockIdx.y * d.heads : 0) + qh0) * ds_head_bytes(d.nq, d.nkv));
+    ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) + qh0 * ds_head_bytes(d.nq, d.nkv));
 
   // A step is skipped (by both wavefronts of its pair) when none of its rows sees any of the
   // pair's keys; it is masked unless every row sees every key.
-  // (step = position in the whole walk, s = its step inside its query head)
+  // (step = position in the whole walk, s = its step inside its run of rows, r its row block)
   // (rows past nq do not count: a pair without keys, w_any = nq, is never active - it has no
   // place in the dS workspace either)
-  auto active = [&](int step, int s) {
-    return step >= 0 && step < total && min(i_start + s * BQ + BQ - 1, d.nq - 1) >= w_any;
+  auto shift = [&](int r) { return CYCLIC && r < late ? 1 : 0; };
+  auto active = [&](int step, int s, int r) {
+    return step >= 0 && step < total && min(i_start + s * BQ + BQ - 1, nq - 1) - shift(r) >= w_any;
   };
-  int cs = s0;                                                  // s of the iteration's step j
-  auto next_s = [&](int s) { return (GROUPED && s + 1 == nsteps) ? 0 : s + 1; };
+  int cs = s0, cr = r0;                                         // s, r of the iteration's step j
+  auto next_step = [&](int& s, int& r) {
+    if (CYCLIC) {
+      const bool last = r + 1 == side;
+      r = last ? 0 : r + 1;
+      if (!last) return;
+    }
+    s = (GROUPED && s + 1 == nsteps) ? 0 : s + 1;
+  };
   // dS row tile of step j, counted over the group's heads
   int c_rt = (GROUPED ? h0 * ds_row_tiles(d.nq) + s0 : 0) + i_start / BQ;
   // (a head's steps end at its last row tile; the next head's start i_start / BQ tiles into its own)
@@ -455,17 +478,18 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
       constexpr int SET = decltype(set_tag)::value;
       store_step((j + 2) % DK_NBUF, set_tag);
       load_step(j + 4, set_tag);
-      if (active(j, cs)) {
-        const int i0 = i_start + cs * BQ;
+      if (active(j, cs, cr)) {
+        // (first row, rows of the run: both one less where the keys are seen a row later)
+        const int i0 = i_start + cs * BQ - shift(cr), rows = nq - shift(cr);
         bf16x8 t[CT], bf[2];
         f32x16 s = dk_first<HD, KSR>(cx, n, zero16());
         dk_second_pre(cx, t);
-        if (i0 >= w_all && i0 + BQ <= d.nq) dk_probs<false>(cx, st, s, bf, i0, d.nq);
-        else dk_probs<true>(cx, st, s, bf, i0, d.nq);
+        if (i0 >= w_all && i0 + BQ <= rows) dk_probs<false>(cx, st, s, bf, i0, rows);
+        else dk_probs<true>(cx, st, s, bf, i0, rows);
         dk_second(cx, t, bf);
       }
       advance(SET ? -DK_MBOX_SLOT : DK_MBOX_SLOT);
-      cs = next_s(cs);
+      next_step(cs, cr);
       dk_first_pre(cx, n);
       dk_stat_pre(cx, st);
       __syncthreads();
@@ -479,13 +503,13 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
     }
   } else if (nsteps > 0) {
     f32x16 dp = zero16();   // dP - delta of the step whose dS, dK come next iteration
-    int ps = 0;             // s of step j - 1
+    int ps = 0, pr = 0;     // s, r of step j - 1
     int p_rt = 0;           // and its dS row tile
     auto iteration = [&](int j, auto set_tag) {
       constexpr int SET = decltype(set_tag)::value;
       store_step((j + 2) % DK_NBUF, set_tag);
       load_step(j + 4, set_tag);
-      if (active(j - 1, ps)) {
+      if (active(j - 1, ps, pr)) {
         bf16x8 t[CT], bf[2];
         f32x4 pm[4];
         dk_mbox_pre(cx, pm);
@@ -512,8 +536,9 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
       p_rt = c_rt;
       c_rt = next_rt(c_rt, cs);
       ps = cs;
-      cs = next_s(cs);
-      if (active(j, ps)) {
+      pr = cr;
+      next_step(cs, cr);
+      if (active(j, ps, pr)) {
         bf16x8 n[4];
         f32x4 st[4];
         dk_first_pre(cx, n);
@@ -531,7 +556,14 @@ __global__ __launch_bounds__(DK_THREADS) void bwd_dkdv_kernel(
     }
   }
 
-  if (key < d.nkv) {
+  if (GRID && g.parts == 1) {
+    if (key < d.nkv) {
+      const int x = role ? 0 : 1;                                // dK, dV
+      bf16_t* const out = reinterpret_cast<bf16_t*>(role ? dK : dV) + head * g.b.out[x].head + col * g.b.out_step[x] +
+                          key * g.b.out[x].row;
+      store_acc_t<CT>(out, cx.acc, cx.half, role ? d.scale : 1.0f, H);
+    }
+  } else if (key < d.nkv) {
     const int64_t row = (int64_t)head * d.nkv + key;
     if (role == 0) store_acc_t<CT>(dV + row * H, cx.acc, cx.half, 1.0f, H);
     else store_acc_t<CT>(dK + row * H, cx.acc, cx.half, d.scale, H);
@@ -617,7 +649,9 @@ __device__ __forceinline__ void dq_piece(DqCtx<HD>& cx, int key0) {
 // LDS at the end - for tiles with at most one 128-row block per compute unit, so that a SIMD still
 // holds two wavefronts.
 // HR: head size (64, 80, 96 or 128), HD its padded size, as in the dK/dV kernel.
-template <int WAVES, int HR, int KL>
+// GRID: all query blocks of an emulated grid, walked as in fwd_mfma_kernel; dQ goes to rows of the sequence's
+// (of a split walk: a partial, [part][row block][head][row]).
+template <int WAVES, int HR, int KL, int GRID>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
     const bf16_t* __restrict__ V, const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO,
@@ -636,19 +670,24 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   const int nqb = (d.nq + DQ_ROWS - 1) / DQ_ROWS;
   // (the query blocks of the query heads that share a key/value head are placed as one unit)
   int unit, blk;
-  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, g.by_size != 0, unit, blk, kXcdCus * 8 / WAVES)) return;
+  const int by_size = GRID ? d.causal : g.by_size;
+  if (!xcd_map(d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * nqb, by_size != 0, unit, blk,
+               kXcdCus * 8 / WAVES)) return;
   // (unit = part `part` of the walks over one key/value head; blocks numbered by size first when the
   // workgroups are ordered by size)
   const int kvh = unit / g.parts, part = unit - kvh * g.parts;
-  const int head = kvh * g.group + (g.by_size ? blk % g.group : blk / nqb);
-  blk = g.by_size ? blk / g.group : blk % nqb;
+  const int head = kvh * g.group + (GRID || by_size ? blk % g.group : blk / nqb);
+  blk = GRID || by_size ? blk / g.group : blk % nqb;
+  const GridBlock gb = GRID ? grid_block(g.b, nqb, blk) : GridBlock{0, blk};
+  const int row_blk = gb.r;                            // of the grid
+  blk = gb.blk;
   const int q0 = (nqb - 1 - blk) * DQ_ROWS;            // heavy blocks first under a causal mask
   const int tid = (int)threadIdx.x - kl * DQ_THREADS;  // within the key lane
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31;
-  Q += (int64_t)head * d.lq.head;
-  O += (int64_t)head * d.lo.head;
-  dO += (int64_t)head * d.ldo.head;
+  Q += (int64_t)head * d.lq.head + (GRID ? row_blk * g.b.q : 0);
+  O += (int64_t)head * d.lo.head + (GRID ? row_blk * g.b.o : 0);
+  dO += (int64_t)head * d.ldo.head + (GRID ? row_blk * g.b.g : 0);
   K += (int64_t)kvh * d.lk.head;
   V += (int64_t)kvh * d.lv.head;
 
@@ -671,7 +710,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
       }
     }
   }
-  const float lse_i = lse[(int64_t)head * d.nq + q_ld];
+  // (lse and delta: of the tile, or of the whole sequence)
+  const int64_t stat_at = GRID ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, q_ld)
+                               : (int64_t)head * d.nq + q_ld;
+  const float lse_i = lse[stat_at];
   // delta = rowsum(dO o O) of the wavefront's rows, left for the dK/dV kernel, which runs after this one
   bf16x8 of[KS];
 #pragma unroll
@@ -682,6 +724,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
 
   // visibility per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
   auto vis_count = [&](int i, int s) -> int {
+    if (GRID == 1) return d.causal ? row_blk * d.nq + i + 1 : g.b.side * d.nkv;
+    if (GRID == 2) return d.causal ? i + 1 : d.nkv;    // (of columns up to the row block's own, see shift_from)
     if (!d.causal) return g.seg[s].rows;
     const int64_t v = (int64_t)i + g.seg[s].rel + 1;
     return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
@@ -719,10 +763,12 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   // span less than 4 GiB - the API layer checks it - so row index times stride fits 32 bits.)
   const unsigned k_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lk.row * 2);
   const unsigned v_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lv.row * 2);
+  // (cyclic grids: seg_start is the number of the grid's column, whose first row that is in the sequence)
+  const unsigned k_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.k * 2)) : k_row_bytes;
+  const unsigned v_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.v * 2)) : v_row_bytes;
   auto load_half = [&](int seg_start, int seg_rows, int j, int hf) {
-    const int k0 = seg_start + j * BKS;
-    const gptr_t kb = uniform_gptr(reinterpret_cast<const char*>(K) + (unsigned)k0 * k_row_bytes);
-    const gptr_t vb = uniform_gptr(reinterpret_cast<const char*>(V) + (unsigned)k0 * v_row_bytes);
+    const gptr_t kb = uniform_gptr(reinterpret_cast<const char*>(K) + (seg_start * k_col_bytes + (unsigned)(j * BKS) * k_row_bytes));
+    const gptr_t vb = uniform_gptr(reinterpret_cast<const char*>(V) + (seg_start * v_col_bytes + (unsigned)(j * BKS) * v_row_bytes));
     const int last = seg_rows - 1 - j * BKS;       // rows beyond the sub-block re-read its last row
 #pragma unroll
     for (int p = 0; p < ST_N; ++p) {
@@ -749,25 +795,43 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
   // share a wait counter with the LDS reads in flight, so it is only touched when a walk moves to
   // another sub-block; in between its values sit in registers.  An entry is (sub-block sb, block j
   // of its nblk); sb == g.n: past the end.
-  const int stride = KL * g.parts;
+  // (cyclic grids: block j of all columns before block j + 1 of any)
+  constexpr bool PLAIN = GRID == 0, CYCLIC = GRID == 2;
+  const int stride = KL * g.parts, segs = PLAIN ? g.n : CYCLIC ? __builtin_amdgcn_readfirstlane(g.b.side) : 1;
+  const int grid_rows = GRID == 1 ? g.b.side * d.nkv : d.nkv;
+  auto seg_start = [&](int s) { return PLAIN ? g.seg[s].start : s; };
+  auto seg_rows = [&](int s) { return PLAIN ? g.seg[s].rows : grid_rows; };
+  const int jump = CYCLIC ? stride / segs : 0, jump_rest = stride - jump * segs;
   auto open_segment = [&](int s, int& sb, int& nblk) {           // first sub-block from s on with visible keys
-    while (s < g.n && seg_blocks(s) == 0) ++s;
+    while (s < segs && seg_blocks(s) == 0) ++s;
     sb = s;
-    if (s < g.n) nblk = seg_blocks(s);
+    if (s < segs) nblk = seg_blocks(s);
   };
   auto advance = [&](int by, int& sb, int& j, int& nblk) {
-    j += by;
-    while (sb < g.n && j >= nblk) { j -= nblk; open_segment(sb + 1, sb, nblk); }
+    if constexpr (CYCLIC) {
+      if (sb >= segs) return;
+      const int q = by == stride ? jump : by / segs;
+      j += q;
+      sb += by == stride ? jump_rest : by - q * segs;
+      if (sb >= segs) { sb -= segs; ++j; }
+      if (j >= nblk) sb = segs;
+    } else {
+      j += by;
+      while (sb < segs && j >= nblk) { j -= nblk; open_segment(sb + 1, sb, nblk); }
+    }
   };
+  // cyclic: query i sees the keys kk <= i of columns up to its row block's own, kk < i of the others - the mask of the
+  // former with the keys numbered one higher
+  const int shift_from = CYCLIC && d.causal ? row_blk : segs;
   int sb, j = 0, nblk = 0;                         // this key lane's current entry
   open_segment(0, sb, nblk);
   advance(part * KL, sb, j, nblk);
   int lead_sb = sb, lead_j = j, lead_nblk = nblk;  // key lane 0's: every lane of the workgroup loops while it exists
   if (KL > 1) advance(kl, sb, j, nblk);
   int nx_start = 0, nx_rows = 0;                   // start / rows of the next entry's sub-block
-  if (sb < g.n) {
+  if (sb < segs) {
     enter_segment(sb);
-    nx_start = g.seg[sb].start; nx_rows = g.seg[sb].rows;
+    nx_start = seg_start(sb); nx_rows = seg_rows(sb);
     load_half(nx_start, nx_rows, j, 0);
   }
   wait_vmem_all();                                 // (the rows of Q, dO, O and the first half together)
@@ -786,21 +850,22 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
     }
     cx.del = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
   }
-  if (part == 0 && kl == 0 && cx.half == 0 && q_ok) delta[(int64_t)head * d.nq + q_row] = cx.del;
-  if (sb < g.n) {
+  if (part == 0 && kl == 0 && cx.half == 0 && q_ok) delta[stat_at] = cx.del;
+  if (sb < segs) {
     store_half(0, 0);
     load_half(nx_start, nx_rows, j, 1); store_half(0, 1);
   }
   __syncthreads();
 
   int buf = 0;
-  while ((KL == 1 ? sb : lead_sb) < g.n) {
+  while ((KL == 1 ? sb : lead_sb) < segs) {
     int nsb = sb, nj = j, nnblk = nblk;
     advance(stride, nsb, nj, nnblk);
-    const bool more = nsb < g.n;
-    if (more && nsb != sb) { nx_start = g.seg[nsb].start; nx_rows = g.seg[nsb].rows; }
-    const bool here = KL == 1 || sb < g.n;         // this lane has a block in this round
-    const int k0 = j * BKS;                        // local to the sub-block
+    const bool more = nsb < segs;
+    if (CYCLIC) nx_start = nsb;
+    else if (more && nsb != sb) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
+    const bool here = KL == 1 || sb < segs;         // this lane has a block in this round
+    const int k0 = j * BKS + (CYCLIC && sb > shift_from);      // local to the sub-block
     if (more) load_half(nx_start, nx_rows, nj, 0);
     if (here && k0 < nvis_wave) {
       if (k0 + 32 > nfull_wave) dq_piece<0, true, HD, KSR>(cx, k0); else dq_piece<0, false, HD, KSR>(cx, k0);
@@ -814,7 +879,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
     cx.ka.shift(tog);
     cx.vnat += tog;
     __syncthreads();
-    if (more && nsb != sb) enter_segment(nsb);
+    if (!CYCLIC && more && nsb != sb) enter_segment(nsb);
     if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
     sb = nsb; j = nj; nblk = nnblk;
     buf ^= 1;
@@ -837,7 +902,13 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) cx.dq[t][r] += xch[(16 * t + r) * 64];
   }
-  if (q_ok) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
+  if (GRID && g.parts == 1) {
+    bf16_t* const out = reinterpret_cast<bf16_t*>(dQ) + head * g.b.out[0].head + row_blk * g.b.out_step[0];
+    if (q_ok) store_acc_t<CT>(out + q_row * g.b.out[0].row, cx.dq, cx.half, d.scale, H);
+  } else if (q_ok) {
+    const int64_t slot = (int64_t)part * (GRID ? g.b.side : 1) + row_blk;
+    store_acc_t<CT>(dQ + ((slot * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, !GRID && g.acc != 0);
+  }
 }
 
 // ---------------------------------------------------------------------- dQ from a stored dS
@@ -898,7 +969,7 @@ __device__ __forceinline__ void dsq_piece(DsqCtx<HD>& cx, const u32x4 (&ds)[4], 
 // the key blocks in two lanes (alternate blocks, own K buffers) whose dQ sums are added through LDS
 // at the end - for tiles with at most one 128-row block per compute unit, so that a SIMD still
 // holds two wavefronts and twice the dS requests are in flight.
-template <int WAVES, int HR, int KL, bool BATCH>
+template <int WAVES, int HR, int KL>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ K, const bf16_t* __restrict__ dS,
     float* __restrict__ dQ) {
@@ -913,17 +984,15 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   const int nqb = (d.nq + DQ_ROWS - 1) / DQ_ROWS;
   // placement as in bwd_dq_kernel (grouped heads: the query heads of a key/value head share an XCD)
   int unit, blk;
-  const TilePos tp = tile_pos<BATCH>(d, g);
-  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, tp.by_size != 0, unit, blk)) return;
+  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, g.by_size != 0, unit, blk)) return;
   const int kvh = unit / g.parts, part = unit - kvh * g.parts;
-  const int head = kvh * g.group + (tp.by_size ? blk % g.group : blk / nqb);
-  blk = tp.by_size ? blk / g.group : blk % nqb;
+  const int head = kvh * g.group + (g.by_size ? blk % g.group : blk / nqb);
+  blk = g.by_size ? blk / g.group : blk % nqb;
   const int q0 = (nqb - 1 - blk) * DQ_ROWS;            // heavy blocks first under a causal mask
   const int tid = (int)threadIdx.x - kl * DQ_THREADS;  // within the key lane
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31;
-  K += (int64_t)kvh * d.lk.head + tp.c * g.b.k;
-  if (BATCH) dQ += (int64_t)col_slot(g.b, tp.r, tp.c) * d.heads * d.nq * H;
+  K += (int64_t)kvh * d.lk.head;
 
   DsqCtx<HD> cx;
   cx.half = lane >> 5;
@@ -939,13 +1008,13 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   const int n_rt = ds_row_tiles(d.nq), n_kb = ds_key_blocks(d.nkv);
   const int rt = min((q0 + wave * 32) / 32, n_rt - 1);
   const gptr_t ds_base = uniform_gptr(reinterpret_cast<const char*>(dS) +
-                                      ((BATCH ? (int64_t)blockIdx.y * d.heads : 0) + head) * ds_head_bytes(d.nq, d.nkv) +
+                                      head * ds_head_bytes(d.nq, d.nkv) +
                                       (int64_t)rt * n_kb * DS_TILE_BYTES);
 
   // visibility per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
   auto vis_count = [&](int i, int s) -> int {
     if (!d.causal) return g.seg[s].rows;
-    const int64_t v = (int64_t)i + g.seg[s].rel + tp.rel + 1;
+    const int64_t v = (int64_t)i + g.seg[s].rel + 1;
     return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
   };
   const int blk_last = min(q0 + DQ_ROWS, d.nq) - 1;
@@ -1029,7 +1098,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 
   count = count > part * KL ? count - part * KL : 0;           // from this part's first block on
   if (count == 0) {                                // no visible key: dQ share is zero
-    if (q_ok && !g.acc && kl == 0) store_acc_t<CT>(dQ + (((int64_t)part * g.b.slots * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, 0.f, H, false);
+    if (q_ok && !g.acc && kl == 0) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, 0.f, H, false);
     return;
   }
   // (the first block is block 0; a lane without one re-reads the last block it passed)
@@ -1093,7 +1162,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) cx.dq[t][r] += xch[(16 * t + r) * 64];
   }
-  if (q_ok) store_acc_t<CT>(dQ + (((int64_t)part * g.b.slots * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
+  if (q_ok) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
 }
 
 }  // namespace
@@ -1116,14 +1185,13 @@ size_t bwd_ds_bytes(const a2d_tile_desc& d, const SegList& g) {
 namespace {
 enum { DQ_BIG = 0, DQ_LANES = 1, DQ_PAIRS = 2 };   // <8, HR, 1>, <8, HR, 2>, <4, HR, 1>
 
-template <int HR, bool BATCH>
+template <int HR>
 hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                          const void* V, const void* dO, const float* lse, const float* delta, float* dQ, float* dK,
                          float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
   constexpr int DSQ_LDS = 2 * DUAL64_BYTES;
   const bool grouped = g.group > 1;
   hipError_t e = hipSuccess;
-  const int tiles = g.b.n ? g.b.n : 1;
   SegList gk = g, gq = g;
   gk.parts = parts.kv;
   gq.parts = parts.q;
@@ -1131,37 +1199,70 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   const bool big = parts.form == DQ_BIG, lanes = parts.form == DQ_LANES;
   if (ph == PREPARE) {
     e = parts.wide ? launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, ds_ws, s)
-        : ensure_dynamic_lds(grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, true, false, BATCH>)
-                                   : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, true, false, BATCH>), DK_LDS);
+        : ensure_dynamic_lds(grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, true>)
+                                   : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, true>), DK_LDS);
     if (e != hipSuccess) return e;
-    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 2, BATCH>), 2 * DSQ_LDS)
-                 : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 1, BATCH>)
-                                          : reinterpret_cast<const void*>(bwd_dq_ds_kernel<4, HR, 1, BATCH>), DSQ_LDS);
+    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 2>), 2 * DSQ_LDS)
+                 : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 1>)
+                                          : reinterpret_cast<const void*>(bwd_dq_ds_kernel<4, HR, 1>), DSQ_LDS);
   }
-  dim3 grid_kv(xcd_grid(d.heads / g.group * parts.kv, (d.nkv + DK_KEYS - 1) / DK_KEYS), tiles);
+  dim3 grid_kv(xcd_grid(d.heads / g.group * parts.kv, (d.nkv + DK_KEYS - 1) / DK_KEYS));
   const int dq_rows = big ? 256 : 128;
-  dim3 grid_q(xcd_grid(d.heads / g.group * parts.q, g.group * ((d.nq + dq_rows - 1) / dq_rows)), tiles);
+  dim3 grid_q(xcd_grid(d.heads / g.group * parts.q, g.group * ((d.nq + dq_rows - 1) / dq_rows)));
   if (parts.wide)
     e = launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, ds_ws, s);
   else if (grouped)
-    A2D_LAUNCH((bwd_dkdv_kernel<HR, true, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk,
+    A2D_LAUNCH((bwd_dkdv_kernel<HR, true, true>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV,
                        (bf16_t*)ds_ws);
   else
-    A2D_LAUNCH((bwd_dkdv_kernel<HR, false, true, false, BATCH>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk,
+    A2D_LAUNCH((bwd_dkdv_kernel<HR, false, true>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV,
                        (bf16_t*)ds_ws);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (big)
-    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 1, BATCH>), grid_q, dim3(512), DSQ_LDS, s, d, gq, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 1>), grid_q, dim3(512), DSQ_LDS, s, d, gq, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   else if (lanes)
-    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 2, BATCH>), grid_q, dim3(512), 2 * DSQ_LDS, s, d, gq, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 2>), grid_q, dim3(512), 2 * DSQ_LDS, s, d, gq, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   else
-    A2D_LAUNCH((bwd_dq_ds_kernel<4, HR, 1, BATCH>), grid_q, dim3(256), DSQ_LDS, s, d, gq, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<4, HR, 1>), grid_q, dim3(256), DSQ_LDS, s, d, gq, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
+  return hipGetLastError();
+}
+
+// A whole grid: dQ of all its rows (which leaves delta), then dK and dV of all its columns
+template <int HR, int GRID>
+hipError_t bwd_launch_grid(Phase ph, const a2d_tile_desc& d, const SegList& gq, const SegList& gk, const void* Q,
+                           const void* K, const void* V, const void* O, const void* dO, const float* lse, float* delta,
+                           float* dQ, float* dK, float* dV, const BwdParts& parts, hipStream_t s) {
+  constexpr int DQ_LDS = dq_lds(padded_head(HR));
+  const bool big = parts.form == DQ_BIG, lanes = parts.form == DQ_LANES;
+  if (ph == PREPARE) {
+    const hipError_t e = parts.wide ? launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, nullptr, s)
+                                    : ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, false, false, GRID>), DK_LDS);
+    if (e != hipSuccess) return e;
+    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 2, GRID>), 2 * DQ_LDS)
+                 : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 1, GRID>)
+                                          : reinterpret_cast<const void*>(bwd_dq_kernel<4, HR, 1, GRID>), DQ_LDS);
+  }
+  const int dq_rows = big ? 256 : 128;
+  const dim3 grid_q(xcd_grid(d.heads / gq.group * parts.q, gq.b.side * gq.group * ((d.nq + dq_rows - 1) / dq_rows)));
+  const dim3 grid_kv(xcd_grid(d.heads / gq.group * parts.kv, gq.b.side * ((d.nkv + DK_KEYS - 1) / DK_KEYS)));
+#define A2D_DQ(WAVES, KL)                                                                                            \
+  A2D_LAUNCH((bwd_dq_kernel<WAVES, HR, KL, GRID>), grid_q, dim3(64 * WAVES), KL * DQ_LDS, s, d, gq, (const bf16_t*)Q, \
+             (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ)
+  if (big) A2D_DQ(8, 1);
+  else if (lanes) A2D_DQ(8, 2);
+  else A2D_DQ(4, 1);
+#undef A2D_DQ
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (parts.wide) return launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, nullptr, s);
+  A2D_LAUNCH((bwd_dkdv_kernel<HR, true, false, false, GRID>), grid_kv, dim3(DK_THREADS), DK_LDS, s, d, gk, (const bf16_t*)Q,
+             (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV, (bf16_t*)nullptr);
   return hipGetLastError();
 }
 
@@ -1169,8 +1270,7 @@ template <int HR>
 hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                          const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK,
                          float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
-  if (ds_ws && g.b.n) return bwd_launch_ds<HR, true>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
-  if (ds_ws) return bwd_launch_ds<HR, false>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+  if (ds_ws) return bwd_launch_ds<HR>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
   constexpr int DQ_LDS = dq_lds(padded_head(HR));
   const bool grouped = g.group > 1;
   // Q and dO in the plain layout: the variant with compile-time staging offsets
@@ -1188,21 +1288,21 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
                                         : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, false, false>));
     e = parts.wide ? launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, nullptr, s) : ensure_dynamic_lds(dkdv, DK_LDS);
     if (e != hipSuccess) return e;
-    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 2>), 2 * DQ_LDS)
-                 : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 1>)
-                                          : reinterpret_cast<const void*>(bwd_dq_kernel<4, HR, 1>), DQ_LDS);
+    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 2, 0>), 2 * DQ_LDS)
+                 : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 1, 0>)
+                                          : reinterpret_cast<const void*>(bwd_dq_kernel<4, HR, 1, 0>), DQ_LDS);
   }
   dim3 grid_kv(xcd_grid(d.heads / g.group * parts.kv, (d.nkv + DK_KEYS - 1) / DK_KEYS));
   const int dq_rows = big ? 256 : 128;
   dim3 grid_q(xcd_grid(d.heads / g.group * parts.q, g.group * ((d.nq + dq_rows - 1) / dq_rows)));
   if (big)
-    A2D_LAUNCH((bwd_dq_kernel<8, HR, 1>), grid_q, dim3(512), DQ_LDS, s, d, gq, (const bf16_t*)Q,
+    A2D_LAUNCH((bwd_dq_kernel<8, HR, 1, 0>), grid_q, dim3(512), DQ_LDS, s, d, gq, (const bf16_t*)Q,
                        (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ);
   else if (lanes)
-    A2D_LAUNCH((bwd_dq_kernel<8, HR, 2>), grid_q, dim3(512), 2 * DQ_LDS, s, d, gq, (const bf16_t*)Q,
+    A2D_LAUNCH((bwd_dq_kernel<8, HR, 2, 0>), grid_q, dim3(512), 2 * DQ_LDS, s, d, gq, (const bf16_t*)Q,
                        (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ);
   else
-    A2D_LAUNCH((bwd_dq_kernel<4, HR, 1>), grid_q, dim3(256), DQ_LDS, s, d, gq, (const bf16_t*)Q,
+    A2D_LAUNCH((bwd_dq_kernel<4, HR, 1, 0>), grid_q, dim3(256), DQ_LDS, s, d, gq, (const bf16_t*)Q,
                        (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1228,36 +1328,39 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q) {
   constexpr double kKvUs[3] = {0.75, 0.85, 1.0}, kWideUs[3] = {1.0, 1.2, 1.5};
   constexpr double kDqUs[3] = {1.6, 1.75, 2.1}, kDsqUs[3] = {0.7, 0.8, 0.85};
-  const int hx = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, kv_heads = d.heads / g.group, tiles = g.b.n ? g.b.n : 1;
-  const bool uneven = g.by_size || g.b.n;
+  const int hx = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, kv_heads = d.heads / g.group, side = g.b.side ? g.b.side : 1;
+  // (a grid's walks are `side` times as long; under the mask of every length down to a few steps)
+  const bool grid = g.b.side > 0, uneven = grid ? d.causal != 0 : g.by_size != 0;
+  const double tail = grid ? 0.1 : 0.5;
   double of_rows[8];                                   // keys that rows see
   const double seen = mean_visible_keys(d, g, of_rows);
-  const double* sorted = g.by_size && !g.b.n ? of_rows : nullptr;
+  const double* sorted = g.by_size && !grid ? of_rows : nullptr;
   BwdParts p;
-  const double rows = (double)g.group * ((d.nq + BQ - 1) / BQ);
-  const double kv_part_us = (double)tiles * kv_heads * d.nkv * d.hdim * 16 / 4.5e6, kv_merge_us = g.b.n ? 0.0 : 4.0;
-  const double kv_mean = uneven ? rows * seen / d.nkv + 1 : rows;
+  const double rows = (double)g.group * side * ((d.nq + BQ - 1) / BQ);
+  const double kv_part_us = (double)side * kv_heads * d.nkv * d.hdim * 16 / 4.5e6, kv_merge_us = 4.0;
+  const double kv_mean = !uneven ? rows : grid ? 0.5 * rows + side : rows * seen / d.nkv + 1;
   double kv_us[2];
   int kv_parts[2];
   for (int w = 0; w < 2; ++w) {                        // 128 keys per workgroup, 256
     const int keys = w ? 256 : DK_KEYS;
-    const WalkModel kv = {(int64_t)kv_heads * tiles * ((d.nkv + keys - 1) / keys), cus, kv_mean, rows,
-                          (w ? kWideUs : kKvUs)[hx], w ? 10.0 : 8.0, 0, 0, nullptr, 0};
+    const WalkModel kv = {(int64_t)kv_heads * side * ((d.nkv + keys - 1) / keys), cus, kv_mean, rows,
+                          (w ? kWideUs : kKvUs)[hx], w ? 10.0 : 8.0, 0, 0, nullptr, 0, tail};
     kv_parts[w] = best_parts(kv, cap_kv, kv_merge_us, kv_part_us, &kv_us[w]);
   }
   p.wide = kv_us[1] < kv_us[0] && d.scale > 1e-30f;    // (it takes lse / scale, which has to stay finite)
   p.kv = kv_parts[p.wide];
-  const double most = (double)visible_keys(d, g, d.nq - 1) / BKS + 0.2, mean = uneven ? seen / BKS + 0.2 : most;
+  const double most = grid ? (double)side * ((d.nkv + BKS - 1) / BKS) + 0.2 : (double)visible_keys(d, g, d.nq - 1) / BKS + 0.2;
+  const double mean = !uneven ? most : grid ? 0.5 * most + 0.5 * (g.b.cyclic ? side : 1) : seen / BKS + 0.2;
   const double step = ds ? kDsqUs[hx] : kDqUs[hx], fixed = 7.0;
-  const int64_t heads = (int64_t)d.heads * tiles, b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
+  const int64_t heads = (int64_t)d.heads * side, b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
   const double part_us = (double)heads * d.nq * d.hdim * 8 / 4.5e6;
-  const WalkModel q[3] = {{b256, cus, mean, most, step, fixed, 0, 0, sorted, 1.0 / BKS},
-                          {b128, cus, mean / 2, most / 2, step * 1.2, fixed + 0.5, 0, 0, sorted, 0.5 / BKS},
-                          {b128, cus, mean, most, step * 0.74, fixed, step, fixed + 0.5, nullptr, 0}};
+  const WalkModel q[3] = {{b256, cus, mean, most, step, fixed, 0, 0, sorted, 1.0 / BKS, tail},
+                          {b128, cus, mean / 2, most / 2, step * 1.2, fixed + 0.5, 0, 0, sorted, 0.5 / BKS, tail},
+                          {b128, cus, mean, most, step * 0.74, fixed, grid ? step * 1.05 : step, fixed + 0.5, nullptr, 0, tail}};
   double least = 0;
   for (int f = 0; f < 3; ++f) {
     double t;
-    const int z = best_parts(q[f], cap_q, g.b.n ? 0.0 : p.kv > 1 ? 1.0 : 4.0, part_us, &t);   // (one launch sums both)
+    const int z = best_parts(q[f], cap_q, p.kv > 1 ? 1.0 : 4.0, part_us, &t);   // (one launch sums both)
     if (f == 0 || t < (p.form == 0 ? 0.98 : 1.0) * least) { least = t; p.form = f; p.q = z; }
   }
   return p;
@@ -1273,6 +1376,19 @@ hipError_t launch_bwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, c
   if (d.hdim == 96) return bwd_launch_hd<96>(ph, d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
   if (d.hdim == 80) return bwd_launch_hd<80>(ph, d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
   return bwd_launch_hd<64>(ph, d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
+}
+
+hipError_t launch_bwd_grid(Phase ph, const a2d_tile_desc& d, const SegList& gq, const SegList& gk, const void* Q,
+                           const void* K, const void* V, const void* O, const void* dO, const float* lse, float* delta,
+                           void* dQ, void* dK, void* dV, const BwdParts& parts, hipStream_t s) {
+#define A2D_GRID(HR)                                                                                                 \
+  return gq.b.cyclic ? bwd_launch_grid<HR, 2>(ph, d, gq, gk, Q, K, V, O, dO, lse, delta, (float*)dQ, (float*)dK, (float*)dV, parts, s) \
+                     : bwd_launch_grid<HR, 1>(ph, d, gq, gk, Q, K, V, O, dO, lse, delta, (float*)dQ, (float*)dK, (float*)dV, parts, s)
+  if (d.hdim == 128) { A2D_GRID(128); }
+  if (d.hdim == 96) { A2D_GRID(96); }
+  if (d.hdim == 80) { A2D_GRID(80); }
+  A2D_GRID(64);
+#undef A2D_GRID
 }
 
 }  // namespace a2d

@@ -39,7 +39,10 @@ __device__ __forceinline__ int lane_again() {
   return l;
 }
 
-template <int HR, bool WRITE_DS, bool BATCH>
+// GRID: all key blocks of an emulated grid (g.b).  The workgroup walks the query rows of its whole grid column and
+// writes rows of dK and dV of the sequence (of a split walk: a partial, [part][column][head][key]).  Contiguous blocks
+// of queries are one run of rows; of cyclic ones, step s of every row block comes before step s + 1 of any.
+template <int HR, bool WRITE_DS, int GRID>
 __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
     const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO, const float* __restrict__ lse,
@@ -55,24 +58,31 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
   // that are used once a step are computed again in every step.
   constexpr bool TIGHT = HD == 128;
   const int kv_heads = d.heads / g.group;
-  const TilePos tp = tile_pos<BATCH>(d, g);
+  constexpr bool CYCLIC = GRID == 2;
+  const int nkb = (d.nkv + WK_KEYS - 1) / WK_KEYS;
   int unit, blk;
-  if (!xcd_map(kv_heads * g.parts, (d.nkv + WK_KEYS - 1) / WK_KEYS, tp.by_size != 0, unit, blk)) return;
+  if (!xcd_map(kv_heads * g.parts, (GRID ? g.b.side : 1) * nkb, (GRID ? d.causal : g.by_size) != 0, unit, blk)) return;
   const int head = unit / g.parts, part = unit - head * g.parts, qh0 = head * g.group;
-  {
-    const int64_t slot = (int64_t)part * g.b.slots + (BATCH ? row_slot(g.b, tp.r, tp.c) : 0);
+  const GridBlock gb = GRID ? grid_column(g.b, nkb, blk) : GridBlock{0, blk};
+  const int col = gb.r;                            // of the grid
+  blk = gb.blk;
+  if (!GRID || g.parts > 1) {
+    const int64_t slot = (int64_t)part * (GRID ? g.b.side : 1) + col;
     dK += slot * kv_heads * d.nkv * H;
     dV += slot * kv_heads * d.nkv * H;
   }
   const int k0 = blk * WK_KEYS;
+  const int side = CYCLIC ? __builtin_amdgcn_readfirstlane(g.b.side) : 1;      // row blocks that are walked in turn
+  const int nq = GRID == 1 ? g.b.side * d.nq : d.nq, head_rows = nq * side;    // rows of a run; of a query head
+  const int col_first = GRID == 1 && d.causal ? col * d.nkv : 0;               // the row that sees the column's first key
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31, half = lane >> 5;
-  Q += (int64_t)qh0 * d.lq.head + tp.r * g.b.q;
-  dO += (int64_t)qh0 * d.ldo.head + tp.r * g.b.g;
-  K += (int64_t)head * d.lk.head + tp.c * g.b.k;
-  V += (int64_t)head * d.lv.head + tp.c * g.b.v;
-  lse += ((int64_t)tp.r * d.heads + qh0) * d.nq;
-  delta += ((int64_t)tp.r * d.heads + qh0) * d.nq;
+  Q += (int64_t)qh0 * d.lq.head;
+  dO += (int64_t)qh0 * d.ldo.head;
+  K += (int64_t)head * d.lk.head + (GRID ? col * g.b.k : 0);
+  V += (int64_t)head * d.lv.head + (GRID ? col * g.b.v : 0);
+  lse += (int64_t)qh0 * head_rows;
+  delta += (int64_t)qh0 * head_rows;
   const float c = d.scale * kLog2e, inv_scale = 1.0f / d.scale;
 
   // ---- K^T and V^T fragments of the wavefront's 32 keys: lane = key.  Keys beyond nkv
@@ -93,12 +103,13 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
 
   // ---- which rows see which keys (as in bwd_dkdv_kernel)
   auto seg_first_row = [&](int sb, int r) -> int {
-    const int64_t f = (int64_t)(r - g.seg[sb].start) - g.seg[sb].rel - tp.rel;
+    const int64_t f = (int64_t)(r - g.seg[sb].start) - g.seg[sb].rel;
     return f <= 0 ? 0 : (f >= d.nq ? d.nq : (int)f);
   };
   auto first_row_range = [&](int a, int b, int& lo, int& hi) {
-    lo = d.nq; hi = 0;
+    lo = nq; hi = 0;
     if (!d.causal) { lo = 0; return; }
+    if (GRID) { lo = col_first + a; hi = col_first + b - 1; return; }
     for (int sb = 0; sb < g.n; ++sb) {
       const int x = max(a, g.seg[sb].start), y = min(b, g.seg[sb].start + g.seg[sb].rows);
       if (x >= y) continue;
@@ -109,29 +120,33 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
   int wg_lo, wg_hi;
   first_row_range(k0, min(k0 + WK_KEYS, d.nkv), wg_lo, wg_hi);
   const int i_start = (wg_lo / BQ) * BQ;
-  int nsteps = (d.nq - i_start + BQ - 1) / BQ;     // steps per query head
-  int total = nsteps * g.group, s0 = 0, h0 = 0;    // this part's steps, from step s0 of head h0 of the group on
+  int nsteps = (nq - i_start + BQ - 1) / BQ;       // steps per run of rows
+  // this part's steps: from step s0 of row block r0 of head h0 of the group on
+  int total = nsteps * side * g.group, s0 = 0, r0 = 0, h0 = 0;
   if (g.parts > 1) {
     const int all = total, first = (int)((int64_t)part * all / g.parts);
     total = (int)((int64_t)(part + 1) * all / g.parts) - first;
     if (nsteps > 0) {
-      h0 = first / nsteps;
-      s0 = first - h0 * nsteps;
+      h0 = first / (nsteps * side);
+      s0 = first - h0 * (nsteps * side);
+      if (CYCLIC) { r0 = s0 % side; s0 /= side; }
     }
   }
-  int my_first = d.nq;                             // first row that sees this lane's key; padding keys see nothing
+  int my_first = nq;                               // first row that sees this lane's key; padding keys see nothing
   if (key < d.nkv) {
-    my_first = 0;
-    if (d.causal) {
+    my_first = GRID && d.causal ? col_first + key : 0;
+    if (!GRID && d.causal) {
       for (int sb = 0; sb < g.n; ++sb)
         if (key >= g.seg[sb].start && key < g.seg[sb].start + g.seg[sb].rows) my_first = seg_first_row(sb, key);
     }
   }
-  int w_any = d.nq, w_all = d.nq;                  // rows below w_any see none of the wavefront's keys, from w_all on all
+  int w_any = nq, w_all = nq;                      // rows below w_any see none of the wavefront's keys, from w_all on all
   if (wk < d.nkv) {
     first_row_range(wk, min(wk + 32, d.nkv), w_any, w_all);
-    if (wk + 32 > d.nkv) w_all = d.nq;
+    if (wk + 32 > d.nkv) w_all = nq;
   }
+  // cyclic: the row blocks before the column see a key a row later than the others
+  const int late = CYCLIC && d.causal ? col : 0;
 
   // ---- staging: thread moves chunk (tid & 15) of row (tid >> 4) of both tiles.  Step
   // j + 2 is requested while step j is computed and written to LDS an iteration later; steps beyond the
@@ -141,24 +156,33 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
   const unsigned g_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.row * 2);
   const unsigned q_head_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lq.head * 2);
   const unsigned g_head_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.head * 2);
+  const unsigned q_blk_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.q * 2)) : 0;
+  const unsigned g_blk_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.g * 2)) : 0;
   u32x4 qreg, greg;
   float stat = 0.f;
   bool stat_ok = false;
-  int ld_s = s0, ld_row0 = h0 * d.nq, ld_left = total - 1;   // the step to be loaded next
+  int ld_s = s0, ld_r = r0, ld_row0 = h0 * head_rows, ld_left = total - 1;   // the step to be loaded next
   unsigned ld_qh = h0 * q_head_bytes, ld_gh = h0 * g_head_bytes;
   auto load_step = [&]() {
     const int tid = TIGHT ? wave * 64 + lane_again() : threadIdx.x;
     const int st_row = tid >> 4, ld_ch = min(tid & 15, H / 8 - 1);
     const int i0 = i_start + ld_s * BQ;
-    const unsigned r = (unsigned)min(i0 + st_row, d.nq - 1);
-    qreg = gload_b128(q_base, ld_qh + __umul24(r, q_row_bytes) + ld_ch * 16);
-    greg = gload_b128(g_base, ld_gh + __umul24(r, g_row_bytes) + ld_ch * 16);
-    const int i = ld_row0 + min(i0 + (tid & (BQ - 1)), d.nq - 1);
+    const unsigned r = (unsigned)min(i0 + st_row, nq - 1);
+    qreg = gload_b128(q_base, ld_qh + (CYCLIC ? ld_r * q_blk_bytes : 0u) + __umul24(r, q_row_bytes) + ld_ch * 16);
+    greg = gload_b128(g_base, ld_gh + (CYCLIC ? ld_r * g_blk_bytes : 0u) + __umul24(r, g_row_bytes) + ld_ch * 16);
+    const int ir = min(i0 + (tid & (BQ - 1)), nq - 1);
+    const int i = ld_row0 + (CYCLIC ? ir * side + ld_r : ir);
     stat = (tid & BQ) ? delta[i] : lse[i];
-    stat_ok = (i0 + (tid & (BQ - 1))) < d.nq;
-    const bool more = ld_left > 0, wrap = ld_s + 1 == nsteps;
+    stat_ok = (i0 + (tid & (BQ - 1))) < nq;
+    bool more = ld_left > 0;
     ld_left -= more ? 1 : 0;
-    ld_row0 += (more && wrap) ? d.nq : 0;
+    if constexpr (CYCLIC) {                        // the next row block, then the next step
+      const bool last = ld_r + 1 == side;
+      ld_r = more ? (last ? 0 : ld_r + 1) : ld_r;
+      more = more && last;
+    }
+    const bool wrap = ld_s + 1 == nsteps;
+    ld_row0 += (more && wrap) ? head_rows : 0;
     ld_qh += (more && wrap) ? q_head_bytes : 0u;
     ld_gh += (more && wrap) ? g_head_bytes : 0u;
     ld_s = more ? (wrap ? 0 : ld_s + 1) : ld_s;
@@ -201,8 +225,7 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
   const unsigned turn = lds_base + WK_TURN + wave * WK_TURN_BYTES;
   gwptr_t ds_base = nullptr;
   if constexpr (WRITE_DS)
-    ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) +
-                            ((BATCH ? (int64_t)blockIdx.y * d.heads : 0) + qh0) * ds_head_bytes(d.nq, d.nkv));
+    ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) + qh0 * ds_head_bytes(d.nq, d.nkv));
 
   DualAddr da;
   da.init(lane, lds_base);
@@ -210,7 +233,8 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
 
   // One step.  Fragments (A operands) in the order of their use: Q and dO rows, transposed dO, transposed
   // Q; each is requested RING fragments ahead.
-  auto compute = [&](int i0, unsigned ds_off, bool masked) {
+  // (i0: its first row, `rows` those of a run - both one less where the keys are seen a row later)
+  auto compute = [&](int i0, int rows, unsigned ds_off, bool masked) {
     constexpr int N1 = KS, N2 = 2 * KS, N3 = N2 + 2 * CT, N4 = N3 + 2 * CT, RING = TIGHT ? 2 : 4;
     bf16x8 a[RING], va[2];
     auto ld = [&](auto I) {
@@ -255,9 +279,10 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
     auto mask = [&]() {
       if (masked) {
         const int first = i0 + 4 * half - my_first;
+        const unsigned limit = CYCLIC ? max(rows - my_first, 0) : rows - my_first;   // (padding keys: none)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if ((unsigned)(first + 8 * (r >> 2) + (r & 3)) >= (unsigned)(d.nq - my_first)) s[r] = -INFINITY;
+          if ((unsigned)(first + 8 * (r >> 2) + (r & 3)) >= limit) s[r] = -INFINITY;
       }
     };
     auto prob = [&](int r) {
@@ -300,7 +325,7 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
     }
   };
 
-  int cs = s0;                                     // step inside its query head
+  int cs = s0, cr = r0;                            // step inside its run, row block
   int rt = h0 * ds_row_tiles(d.nq) + s0 + i_start / BQ;   // dS row tile, counted over the group's heads
   int buf = 0;
 #pragma nounroll
@@ -308,34 +333,45 @@ __global__ __launch_bounds__(WK_THREADS) void bwd_dkdv_wide_kernel(
     store_step(buf ^ 1);
     load_step();
     const int i0 = i_start + cs * BQ;
-    if (min(i0 + BQ - 1, d.nq - 1) >= w_any) {
+    const int sh = CYCLIC && cr < late ? 1 : 0;
+    if (min(i0 + BQ - 1, nq - 1) - sh >= w_any) {
       const unsigned off = (unsigned)rt * ds_row_stride + ds_wave_off;
-      compute(i0, off, i0 < w_all || i0 + BQ > d.nq);
+      compute(i0 - sh, nq - sh, off, i0 - sh < w_all || i0 + BQ > nq);
     }
-    const bool wrap = cs + 1 == nsteps;
-    rt += wrap ? 1 + i_start / BQ : 1;
-    cs = wrap ? 0 : cs + 1;
+    if (!CYCLIC || ++cr == side) {
+      const bool wrap = cs + 1 == nsteps;
+      rt += wrap ? 1 + i_start / BQ : 1;
+      cs = wrap ? 0 : cs + 1;
+      cr = 0;
+    }
     da.shift(buf ? -DK_BUF : DK_BUF);
     st_addr += buf ? -DK_STAT_BUF : DK_STAT_BUF;
     buf ^= 1;
     __syncthreads();
   }
 
-  if (key < d.nkv) {
+  if (GRID && g.parts == 1) {
+    if (key < d.nkv) {
+      bf16_t* const dkb = reinterpret_cast<bf16_t*>(dK) + head * g.b.out[0].head + col * g.b.out_step[0];
+      bf16_t* const dvb = reinterpret_cast<bf16_t*>(dV) + head * g.b.out[1].head + col * g.b.out_step[1];
+      store_acc_t<CT>(dvb + key * g.b.out[1].row, dv, half, 1.0f, H);
+      store_acc_t<CT>(dkb + key * g.b.out[0].row, dk, half, d.scale, H);
+    }
+  } else if (key < d.nkv) {
     const int64_t row = (int64_t)head * d.nkv + key;
     store_acc_t<CT>(dV + row * H, dv, half, 1.0f, H);
     store_acc_t<CT>(dK + row * H, dk, half, d.scale, H);
   }
 }
 
-template <int HR, bool WRITE_DS, bool BATCH>
+template <int HR, bool WRITE_DS, int GRID>
 hipError_t go(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
               const void* dO, const float* lse, const float* delta, float* dK, float* dV, void* dS, hipStream_t s) {
   constexpr int bytes = wk_lds(padded_head(HR));
   if (ph == PREPARE)
-    return ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dkdv_wide_kernel<HR, WRITE_DS, BATCH>), bytes);
-  const dim3 grid(xcd_grid(d.heads / g.group * g.parts, (d.nkv + WK_KEYS - 1) / WK_KEYS), g.b.n ? g.b.n : 1);
-  A2D_LAUNCH((bwd_dkdv_wide_kernel<HR, WRITE_DS, BATCH>), grid, dim3(WK_THREADS), bytes, s, d, g, (const bf16_t*)Q,
+    return ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dkdv_wide_kernel<HR, WRITE_DS, GRID>), bytes);
+  const dim3 grid(xcd_grid(d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * ((d.nkv + WK_KEYS - 1) / WK_KEYS)));
+  A2D_LAUNCH((bwd_dkdv_wide_kernel<HR, WRITE_DS, GRID>), grid, dim3(WK_THREADS), bytes, s, d, g, (const bf16_t*)Q,
              (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, lse, delta, dK, dV, (bf16_t*)dS);
   return hipGetLastError();
 }
@@ -343,9 +379,10 @@ hipError_t go(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q,
 template <int HR>
 hipError_t go_h(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                 const void* dO, const float* lse, const float* delta, float* dK, float* dV, void* dS, hipStream_t s) {
-  if (!dS) return go<HR, false, false>(ph, d, g, Q, K, V, dO, lse, delta, dK, dV, dS, s);
-  if (g.b.n) return go<HR, true, true>(ph, d, g, Q, K, V, dO, lse, delta, dK, dV, dS, s);
-  return go<HR, true, false>(ph, d, g, Q, K, V, dO, lse, delta, dK, dV, dS, s);
+  if (g.b.side) return g.b.cyclic ? go<HR, false, 2>(ph, d, g, Q, K, V, dO, lse, delta, dK, dV, dS, s)
+                                  : go<HR, false, 1>(ph, d, g, Q, K, V, dO, lse, delta, dK, dV, dS, s);
+  if (!dS) return go<HR, false, 0>(ph, d, g, Q, K, V, dO, lse, delta, dK, dV, dS, s);
+  return go<HR, true, 0>(ph, d, g, Q, K, V, dO, lse, delta, dK, dV, dS, s);
 }
 
 }  // namespace

@@ -50,13 +50,14 @@ template <> struct dtype_of<bf16_t> { static constexpr int value = A2D_BF16; };
 // A launch over a whole emulated side x side grid (side = 0: a plain call).  All blocks of the grid are
 // views of the same tensors: block b of Q starts b * q elements after block 0, and so on.  Tile (r, c) =
 // query block r against key block c; under the causal mask rel = q_off - kv_off is (r - c) * rows for
-// contiguous blocks, 0 / -1 (r >= c / r < c) for cyclic ones.  The forward walks whole grid rows.  The backward's
-// launches are over many tiles, one per grid.y (n = 0: a plain call); tri != 0: only the tiles c <= r exist.
-struct TileBatch {
-  int n, first;        // tiles of this launch, number of its first tile
-  int slots;           // tiles of the whole grid (1: a plain call); part z of a split walk is stored slots tiles on
-  int side, tri, cyclic;
+// contiguous blocks, 0 / -1 (r >= c / r < c) for cyclic ones.  A workgroup of the forward and dQ kernels walks the
+// tiles of a grid row, one of the dK/dV kernels those of a grid column.
+// The kernels' GRID parameter: 0 a plain call, 1 contiguous blocks, 2 cyclic ones.
+struct GridView {
+  int side, cyclic;
   int64_t q, k, v, g, o;  // elements between blocks of Q, K, V, dO, O
+  a2d_layout out[2];      // rows of a block of dQ, or of dK and dV, in the whole tensors
+  int64_t out_step[2];    // elements between their blocks
 };
 struct Segment {
   int start, rows;
@@ -68,51 +69,11 @@ struct SegList {
   int norm;
   int group;
   int by_size;
-  TileBatch b;
+  GridView b;
   int parts;      // workgroups that share the walk of one block, each leaving a partial result (>= 1)
   int form;       // which of its workgroup shapes a forward / dQ launch takes (plan_* below)
   Segment seg[A2D_MAX_SEGMENTS];
 };
-
-// The tile this workgroup belongs to (all zero for a plain call).
-// Partials of a batch are stored by slot: col_slot() puts the tiles of one grid column next to each
-// other (what the merge over a grid row reads as one array per column), row_slot() those of one row.
-struct TilePos {
-  int r, c, by_size;
-  int64_t rel;
-};
-template <bool BATCH>
-__device__ __forceinline__ TilePos tile_pos(const a2d_tile_desc& d, const SegList& g) {
-  TilePos p{0, 0, g.by_size, 0};
-  if (!BATCH || g.b.n == 0) return p;
-  int t = g.b.first + blockIdx.y;
-  if (g.b.tri) {                                 // whole tiles first, then those on the diagonal
-    const int whole = g.b.side * (g.b.side - 1) / 2;
-    if (t < whole) {
-      p.r = 1;
-      while (t >= p.r) { t -= p.r; ++p.r; }
-      p.c = t;
-    } else {
-      p.r = p.c = t - whole;
-    }
-  } else {
-    p.r = t / g.b.side;
-    p.c = t - p.r * g.b.side;
-  }
-  if (d.causal) {
-    p.rel = g.b.cyclic ? (p.r >= p.c ? 0 : -1) : (int64_t)(p.r - p.c) * d.nq;
-    p.by_size = g.b.cyclic || p.r == p.c;        // the mask crosses the tile
-  } else {
-    p.by_size = 0;
-  }
-  return p;
-}
-__host__ __device__ inline int col_slot(const TileBatch& b, int r, int c) {
-  return b.n == 0 ? 0 : b.tri ? c * b.side - c * (c - 1) / 2 + r - c : c * b.side + r;
-}
-__host__ __device__ inline int row_slot(const TileBatch& b, int r, int c) {
-  return b.n == 0 ? 0 : b.tri ? r * (r + 1) / 2 + c : r * b.side + c;
-}
 
 // Brings the kernel's arguments - the tile's descriptor, the list's head and first sub-block, and the
 // pointers behind them - into the scalar cache in one go.  A cold line costs about half a microsecond,
@@ -139,16 +100,18 @@ __device__ __forceinline__ void warm_arguments() {
 struct GridBlock {
   int r, blk;
 };
-__device__ __forceinline__ GridBlock grid_block(const TileBatch& b, int nblk, int t) {
+__device__ __forceinline__ GridBlock grid_block(const GridView& b, int nblk, int t) {
   const int per = b.cyclic ? b.side : nblk, x = t / per, y = t - x * per;
   // (cyclic: equal positions of all row blocks cost the same; contiguous: later row blocks cost more)
   return GridBlock{b.cyclic ? y : b.side - 1 - x, b.cyclic ? x : y};
 }
-__device__ __forceinline__ int grid_rel(const TileBatch& b, int rows, int r, int c) {
-  return b.cyclic ? (r >= c ? 0 : -1) : (r - c) * rows;
+// the same of the key blocks of a column: early keys are seen by more rows
+__device__ __forceinline__ GridBlock grid_column(const GridView& b, int nblk, int t) {
+  const int per = b.cyclic ? b.side : nblk, x = t / per, y = t - x * per;
+  return GridBlock{b.cyclic ? y : x, b.cyclic ? x : y};
 }
 // token of row i of row block r
-__device__ __forceinline__ int grid_token(const TileBatch& b, int rows, int r, int i) {
+__device__ __forceinline__ int grid_token(const GridView& b, int rows, int r, int i) {
   return b.cyclic ? i * b.side + r : r * rows + i;
 }
 
@@ -303,6 +266,12 @@ hipError_t launch_bwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, c
                            const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ,
                            float* dK, float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s);
 
+// A whole grid (g.b), recomputing the scores for dQ: gq, gk with the parts and output layouts of dQ and of dK, dV; lse and
+// delta [heads][seq].  (parts > 1: that output is the partial buffer)
+hipError_t launch_bwd_grid(Phase ph, const a2d_tile_desc& d, const SegList& gq, const SegList& gk, const void* Q,
+                           const void* K, const void* V, const void* O, const void* dO, const float* lse, float* delta,
+                           void* dQ, void* dK, void* dV, const BwdParts& parts, hipStream_t s);
+
 struct FixPtrs {
   const float* o[A2D_MAX_PARTS];
   const float* m[A2D_MAX_PARTS];
@@ -321,19 +290,9 @@ struct OutMap {
 };
 inline OutMap plain_out() { return OutMap{0, 0, 1, 1}; }
 // The merged output of a whole emulated grid: block b, head h, row i of the merge's input is token
-// i * side + b (cyclic) or b * rows + i of head h in a [heads][side * rows][H] tensor.  dir: which
-// of the `from` partials block b has - 0: all; 1: those x <= b (a grid row under the causal mask,
-// contiguous blocks); 2: those x >= b (a grid column).  Each is in `parts` parts: partial e of the
-// pointer lists is part e % parts of partial e / parts.
+// i * side + b (cyclic) or b * rows + i of head h in a [heads][side * rows][H] tensor.
 struct GridMap {
-  int side, rows, heads, cyclic, dir, parts, from;
-  // walks the pointer lists: does block b have the list's next entry?
-  struct Walk { int x = 0, z = 0; };
-  __host__ __device__ __forceinline__ bool next(Walk& w, int b) const {
-    const bool has = w.x < from && (dir == 0 || (dir == 1 ? w.x <= b : w.x >= b));
-    if (++w.z == parts) { w.z = 0; ++w.x; }
-    return has;
-  }
+  int side, rows, heads, cyclic, parts;
 };
 // O (layout lo), lse of a whole grid from its partial triples; sums of up to three sets of gradient partials
 hipError_t launch_fix_grid(const GridMap& gm, int hdim, int out_dtype, const FixPtrs& p, const a2d_layout& lo, void* O,
@@ -345,10 +304,6 @@ struct SumSet {
   a2d_layout lo;
 };
 hipError_t launch_sum_grid(int nsets, const SumSet* sets, int hdim, int out_dtype, hipStream_t s);
-// delta and lse of a whole [heads][side * rows] sequence, block by block: [side][heads][rows]
-hipError_t launch_delta_grid(const GridMap& gm, int hdim, const a2d_layout& lo, const a2d_layout& ldo, const bf16_t* O,
-                             const bf16_t* dO, const float* lse, float* delta_blk, float* lse_blk, hipStream_t s);
-
 // out[i] (+)= sum of k partials of n floats that follow one another, up to three sets in one launch
 struct PartSet {
   const float* p;

@@ -190,8 +190,8 @@ __global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_
   }
 }
 
-// ---- the merges of a whole emulated grid, one launch for all its blocks.  Same arithmetic and
-// order of sums as above; which partials a block has and where its rows go follows from GridMap.
+// ---- the merges of a whole emulated grid whose walks were split, one launch for all its blocks.  Same
+// arithmetic and order of sums as above; where a block's rows go follows from GridMap.
 // (Everything but the partials' addresses fits 32 bits: the launcher checks it.)
 struct GridRow {
   int b, h, i;                                     // block, head, row inside the block
@@ -214,10 +214,9 @@ __global__ __launch_bounds__(256) void fix_grid_kernel(FixPtrs p, GridMap g, int
   const GridRow gr(g, row);
   f32x4 n[KMAX];
   float mk[KMAX], lk[KMAX];
-  GridMap::Walk walk;
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    if (g.next(walk, gr.b)) {
+    if (x < g.parts) {
       n[x] = A2D_LD(reinterpret_cast<const f32x4*>(p.o[x]) + idx);
       mk[x] = p.m[x][row];
       lk[x] = p.l[x][row];
@@ -260,10 +259,9 @@ __global__ __launch_bounds__(256) void sum_grid_kernel(SumSets a, int hv) {
   if (row >= (unsigned)(g.side * g.heads * g.rows)) return;
   const GridRow gr(g, row);
   f32x4 v[KMAX];
-  GridMap::Walk walk;
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    if (g.next(walk, gr.b)) v[x] = A2D_LD(reinterpret_cast<const f32x4*>(s.p.p[x]) + idx);
+    if (x < g.parts) v[x] = A2D_LD(reinterpret_cast<const f32x4*>(s.p.p[x]) + idx);
     else v[x] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   f32x4 acc = v[0];
@@ -388,7 +386,7 @@ template <typename OutT>
 void fix_grid_dispatch(const GridMap& gm, int hv, const FixPtrs& p, const a2d_layout& lo, OutT* O, float* lse,
                        hipStream_t s) {
   const dim3 grid((unsigned)(((int64_t)gm.side * gm.heads * gm.rows * hv + 255) / 256)), block(256);
-  const int k = gm.from * gm.parts;
+  const int k = gm.parts;
 #define A2D_GO(KMAX) A2D_LAUNCH((fix_grid_kernel<OutT, KMAX>), grid, block, 0, s, p, gm, hv, lo, O, lse)
   if (k <= 2) A2D_GO(2);
   else if (k <= 4) A2D_GO(4);
@@ -401,7 +399,7 @@ template <typename OutT>
 void sum_grid_dispatch(int nsets, const SumSets& a, int hv, int64_t blocks, hipStream_t s) {
   const dim3 grid((unsigned)blocks, nsets), block(256);
   int k = 0;
-  for (int x = 0; x < nsets; ++x) k = a.s[x].gm.from * a.s[x].gm.parts > k ? a.s[x].gm.from * a.s[x].gm.parts : k;
+  for (int x = 0; x < nsets; ++x) k = a.s[x].gm.parts > k ? a.s[x].gm.parts : k;
 #define A2D_GO(KMAX) A2D_LAUNCH((sum_grid_kernel<OutT, KMAX>), grid, block, 0, s, a, hv)
   if (k <= 2) A2D_GO(2);
   else if (k <= 4) A2D_GO(4);

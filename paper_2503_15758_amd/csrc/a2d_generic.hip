@@ -429,36 +429,6 @@ __global__ __launch_bounds__(kThreads) void delta_kernel(int64_t rows, int nq, i
   if (row < rows && c == 0) delta[row] = acc;
 }
 
-// The same over a whole sequence of an emulated grid, written block by block ([side][heads][rows]) as the
-// tile kernels read it, with lse brought into the same order (one pass instead of one per tile).
-__global__ __launch_bounds__(kThreads) void delta_grid_kernel(GridMap g, int H, int lpr_log2, a2d_layout lo,
-                                                              a2d_layout ldo, const bf16_t* __restrict__ O,
-                                                              const bf16_t* __restrict__ dO,
-                                                              const float* __restrict__ lse,
-                                                              float* __restrict__ delta_blk,
-                                                              float* __restrict__ lse_blk) {
-  const unsigned idx = blockIdx.x * kThreads + threadIdx.x;
-  const unsigned row = idx >> lpr_log2, n = g.side * g.rows;
-  const int c = idx & ((1 << lpr_log2) - 1);
-  const unsigned h = row / n, j = row - h * n;
-  const bool ok = h < (unsigned)g.heads;
-  float acc = 0.f;
-  if (ok && c < H / 8) {
-    const bf16x8 o = *reinterpret_cast<const bf16x8*>(O + h * lo.head + j * lo.row + c * 8);
-    const bf16x8 w = *reinterpret_cast<const bf16x8*>(dO + h * ldo.head + j * ldo.row + c * 8);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc = fmaf(to_f32(o[e]), to_f32(w[e]), acc);
-  }
-  for (int o = 1; o < (1 << lpr_log2); o <<= 1) acc += __shfl_xor(acc, o, 64);
-  if (ok && c == 0) {
-    const unsigned q = j / (g.cyclic ? g.side : g.rows), r = j - q * (g.cyclic ? g.side : g.rows);
-    const unsigned b = g.cyclic ? r : q, i = g.cyclic ? q : r;
-    const int64_t to = ((int64_t)b * g.heads + h) * g.rows + i;
-    delta_blk[to] = acc;
-    lse_blk[to] = lse[row];
-  }
-}
-
 template <typename K>
 hipError_t set_lds(K kernel, size_t bytes) {
   return ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)bytes);
@@ -535,16 +505,6 @@ hipError_t launch_delta(const a2d_tile_desc& d, const void* O, const void* dO, f
   else
     A2D_LAUNCH((delta_kernel<float>), grid, block, 0, s, rows, d.nq, hdim, lpr, d.lo, d.ldo,
                        (const float*)O, (const float*)dO, delta);
-  return hipGetLastError();
-}
-
-hipError_t launch_delta_grid(const GridMap& gm, int hdim, const a2d_layout& lo, const a2d_layout& ldo, const bf16_t* O,
-                             const bf16_t* dO, const float* lse, float* delta_blk, float* lse_blk, hipStream_t s) {
-  int lg = 0;
-  while ((1 << lg) < hdim / 8) ++lg;
-  const int64_t threads = ((int64_t)gm.heads * gm.side * gm.rows) << lg;
-  A2D_LAUNCH(delta_grid_kernel, dim3((unsigned)((threads + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, gm, hdim, lg,
-             lo, ldo, O, dO, lse, delta_blk, lse_blk);
   return hipGetLastError();
 }
 

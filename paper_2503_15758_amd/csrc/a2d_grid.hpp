@@ -1,6 +1,6 @@
 // Alg. 1 and Alg. 3 over a whole emulated side x side grid in a handful of launches: the tile kernels, on all
-// grid rows (forward) or many tiles (backward) per launch (TileBatch), on the blocks where they lie in the
-// sequence (contiguous or cyclic: a stride, not a copy).
+// grid rows or columns per launch (GridView), on the blocks where they lie in the sequence (contiguous or
+// cyclic: a stride, not a copy).
 #pragma once
 #include <hip/hip_runtime_api.h>
 
@@ -26,9 +26,9 @@ struct GridProblem {
   a2d_layout dq, dk, dv;         // of the gradients
 };
 
-// Whether the batched path covers the problem (bf16; the kernels' 32-bit offsets, the dS hand-over)
+// Whether the batched path covers the problem (bf16; the kernels' 32-bit offsets)
 bool grid_supported(const GridProblem& p);
-// Workspace in bytes; dS of as many tiles as fit kGridDsBytes is kept at a time (at least one tile's)
+// Workspace in bytes: partial results of split walks, delta
 size_t grid_forward_bytes(const GridProblem& p);
 size_t grid_backward_bytes(const GridProblem& p);
 // O with the layout p.o, lse plain [heads][seq].  Both only enqueue on `s`.

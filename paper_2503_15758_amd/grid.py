@@ -3,8 +3,8 @@ sqrt(P) x sqrt(P) device grid on ONE GPU.
 
 Every "device" (r, c) of the paper is one tile of the library's tile kernels; the collectives become
 plain data movement on the one GPU.  Tiles are independent (Sec. 3.2).  For bf16 tensors a grid is a
-handful of launches, each over all its tiles, which read their blocks where they lie in the sequence
-(csrc/a2d_grid.hip).  Otherwise (fp32, merge="ring", ds_handover=False, strides the kernels do not
+handful of launches, whose workgroups read the blocks where they lie in the sequence, walk the tiles of
+a grid row (O, dQ) or column (dK, dV) and merge them in their registers (csrc/a2d_grid.hip).  Otherwise (fp32, merge="ring", ds_handover=False, strides the kernels do not
 take) every tile is a call of its own: the row / column all-gathers are index gathers of the blocks,
 the reduce-scatters the library's merge calls, and the calls go round-robin onto several HIP streams
 of default priority; `streams` says how many.  Either way the result does not depend on `streams`.
@@ -75,7 +75,7 @@ class _Streams:
 
 def forward(Q, K, V, grid, causal=True, layout="cyclic", scale=None, streams=4, merge="kway"):
     """Alg. 1: O [heads][n][H] in the input dtype and lse [heads][n] (what the forward saves).
-    merge: "kway" - the partials of a grid row in one a2d_fix pass; "ring" - folded pairwise by
+    merge: "kway" - the partials of a grid row at once (in registers, or by a2d_fix); "ring" - folded pairwise by
     a2d_attnfix, one hop per partial as a ring reduce-scatter with AttnFix as its operator does
     (Alg. 1 line 5), then the division of line 6 (a2d_fix of the one remaining partial)."""
     heads, n, H = Q.shape
@@ -120,8 +120,8 @@ def forward(Q, K, V, grid, causal=True, layout="cyclic", scale=None, streams=4, 
 def backward(Q, K, V, O, dO, lse, grid, causal=True, layout="cyclic", scale=None, streams=4,
              ds_handover=True):
     """Alg. 3: dQ, dK, dV [heads][n][H] in the input dtype from the saved O and lse.
-    ds_handover: keep dS for the dQ contraction instead of recomputing the scores (about 2 T^2 bytes per
-    head and tile more, for at most 2 GiB worth of tiles - or one tile - at a time)."""
+    ds_handover: a tile call may keep dS for the dQ contraction instead of recomputing the scores (about 2 T^2
+    bytes per head and stream more).  False: every tile is a call of its own that recomputes them."""
     heads, n, H = Q.shape
     scale = float(scale if scale is not None else 1.0 / math.sqrt(H))
     _check_blocks(n, grid, layout)

@@ -1,5 +1,6 @@
-"""The whole-grid launches, which walk all tiles of a grid row (forward) at once, against full attention in fp64 on the GPU:
-edges of the key blocks and workgroups in blocks of every kind, one-row blocks, split walks, every workgroup shape."""
+"""The whole-grid launches, which walk all tiles of a grid row (O, dQ) or column (dK, dV) at once, against full attention in
+fp64 on the GPU: edges of the blocks and workgroups in layouts of every kind, one-row blocks, split walks, every
+workgroup shape."""
 import math
 
 import pytest
@@ -51,3 +52,19 @@ def test_grid_rows(case, causal, layout):
     assert (got_lse.double() - lse).abs().max() < 1e-4
     again, again_lse = g2d.forward(Q, K, V, side, causal, layout, scale)
     assert torch.equal(got, again) and torch.equal(got_lse, again_lse)
+
+    dO, Os = make(heads), O.to(torch.bfloat16)
+    P = torch.exp(S - lse[..., None])
+    w = dO.double()
+    dS = P * (torch.bmm(w, v.transpose(1, 2).contiguous()) - (w * Os.double()).sum(2)[..., None])
+    fold = lambda x: x.view(kvh, heads // kvh, n, H).sum(1)
+    ref = (torch.bmm(dS, k) * scale, fold(torch.bmm(dS.transpose(1, 2).contiguous(), q)) * scale,
+           fold(torch.bmm(P.transpose(1, 2).contiguous(), w)))
+    args = (Q, K, V, Os, dO, lse.float())
+    assert a2d._ext().grid_backward(*args, side, causal, layout == "cyclic", scale) is not None
+    grads = g2d.backward(*args, side, causal, layout, scale)
+    again = g2d.backward(*args, side, causal, layout, scale)
+    for name, x, y, z in zip(("dQ", "dK", "dV"), grads, ref, again):
+        assert torch.equal(x, z), name
+        # P, dS and the results rounded to bf16 (a sequence of one or two tokens has a dQ and dK of almost nothing)
+        assert _rel(x, y) < 1e-2 or (x.double() - y).abs().max() < 2e-2, "%s: %.2e" % (name, _rel(x, y))
