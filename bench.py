@@ -51,6 +51,8 @@ def call_kernels(call, w, recompute):
     if call.startswith("partial_bwd"):
         if w.dtype != "bf16":
             return ["bwd_dq_f32_kernel", "bwd_dkdv_f32_kernel"]
+        if 2 * w.heads * (-(-w.tile // 256)) <= 6 * 256:      # at most six turns of 256 compute units: one launch
+            return ["delta_kernel", "bwd_one_kernel"]
         if recompute:
             return ["bwd_dq_kernel", "bwd_dkdv_kernel"]
         return ["delta_kernel", "bwd_dkdv_kernel", "bwd_dq_ds_kernel"]
@@ -229,10 +231,13 @@ def main():
             n = "partial_bwd_" + tag
             flops[n] = b
             ks = call_kernels(n, w, args.recompute_bwd)
-            k_kv, = [k for k in ks if k.startswith("bwd_dkdv")]
-            k_dq, = [k for k in ks if k.startswith("bwd_dq")]
             if "delta_kernel" in ks:
                 kbytes[(n, "delta_kernel")] = rows * (2 * H * esz + 4)
+            if "bwd_one_kernel" in ks:
+                kflops[(n, "bwd_one_kernel")] = b             # (recomputation of S and dP not counted)
+                continue
+            k_kv, = [k for k in ks if k.startswith("bwd_dkdv")]
+            k_dq, = [k for k in ks if k.startswith("bwd_dq")]
             kflops[(n, k_kv)] = 0.8 * b                       # four of the five counted contractions: S, dP, dV, dK
             if k_dq == "bwd_dq_ds_kernel":
                 # one contraction over the stored dS: dS (2 bytes per visible score) + K read, dQ written

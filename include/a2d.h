@@ -93,9 +93,10 @@ typedef struct {
 } a2d_layout;
 
 /*
- * desc->flags, backward calls: hand dS from the dK/dV kernel to the dQ kernel through the
- * workspace instead of computing it twice (see a2d_workspace_bytes).  The caller ASKS for this
- * path; the size of the workspace never selects it.
+ * desc->flags, backward calls: dS may be handed from the dK/dV kernel to the dQ kernel through the
+ * workspace instead of being computed twice (see a2d_workspace_bytes).  The caller ALLOWS this path;
+ * the size of the workspace never selects it.  The library takes it for the shapes that it makes
+ * faster (large tiles of H = 128) and recomputes for the others.
  */
 #define A2D_DESC_KEEP_DS 1
 
@@ -122,13 +123,13 @@ typedef struct {
  * Bytes of device workspace the given op needs for this tile (0 if none).
  * A2D_OP_PARTIAL_BWD: the minimum (the per-row sums delta = rowsum(dO o O)).
  * A2D_OP_PARTIAL_BWD_DS: the size the backward calls need when desc->flags has A2D_DESC_KEEP_DS:
- * they then ALSO keep dS (bf16, one value per score: about 2 nq nkv bytes per head) in the
+ * they may then ALSO keep dS (bf16, one value per score: about 2 nq nkv bytes per head) in the
  * workspace, so that dQ is one contraction over the stored dS instead of a second recomputation
  * of S and dP.  The hand-over exists for bf16 inputs, sub-blocks of a gathered tile that start at
  * multiples of 64 keys, and less than 4 GiB of dS per key/value head (all the query heads of its
  * group together); where it does not (this query then returns the minimum size for a plain tile)
  * the flag is accepted and the recomputing kernels run.  Same results up to fp32 summation
- * order; faster when the memory is there.
+ * order (dK and dV the same bits).
  * A2D_OP_PARTIAL_BWD_SPLIT: the size a2d_partial_bwd_gqa needs with A2D_TILE_SPLIT_GROUPS: that of
  * A2D_OP_PARTIAL_BWD_DS plus fp32 partial dK / dV buffers (at most 2 * heads * nkv * H floats);
  * `k` = the number of key/value heads.

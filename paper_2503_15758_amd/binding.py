@@ -263,7 +263,7 @@ def attnfix(O_parts, ms, ls, out=None):
 def partial_bwd(Q, K, V, O, dO, lse, q_off=0, kv_off=0, causal=False, scale=None, out=None,
                 workspace=None, segments=None, accumulate=False, ds_handover=False, split_groups=False):
     """a2d_partial_bwd. Returns (dQ_part, dK_part, dV_part), all fp32.  ds_handover=True sets
-    A2D_DESC_KEEP_DS in the descriptor: the library keeps dS for the dQ contraction instead of
+    A2D_DESC_KEEP_DS in the descriptor: the library may keep dS for the dQ contraction instead of
     recomputing it, and the workspace (allocated here when none is given) must then hold
     a2d_workspace_bytes(A2D_OP_PARTIAL_BWD_DS) bytes.  split_groups=True
     (grouped heads only) passes A2D_TILE_SPLIT_GROUPS: a key block may go to several workgroups,

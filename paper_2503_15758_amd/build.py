@@ -16,7 +16,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liba2d.so")
 EXT = os.path.join(PKG, "_native.so")
 SOURCES = ["a2d_api.hip", "a2d_device.hip", "a2d_fix.hip", "a2d_generic.hip", "a2d_f32_mfma.hip",
-           "a2d_fwd_mfma.hip", "a2d_bwd_mfma.hip", "a2d_bwd_wide.hip", "a2d_grid.hip", "a2d_static.hip",
+           "a2d_fwd_mfma.hip", "a2d_bwd_mfma.hip", "a2d_bwd_wide.hip", "a2d_bwd_one.hip", "a2d_grid.hip", "a2d_static.hip",
            "a2d_probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -56,7 +56,8 @@ def _ext_command():
 def build(force=False, verbose=True):
     os.makedirs(OBJ, exist_ok=True)
     headers = [os.path.join(CSRC, "a2d_common.hpp"), os.path.join(CSRC, "a2d_mfma.hpp"),
-               os.path.join(CSRC, "a2d_bwd.hpp"),
+               os.path.join(CSRC, "a2d_bwd.hpp"), os.path.join(CSRC, "a2d_bwd_dq.hpp"),
+               os.path.join(CSRC, "a2d_bwd_pairs.hpp"), os.path.join(CSRC, "a2d_bwd_wide.hpp"),
                os.path.join(CSRC, "a2d_grid.hpp"), os.path.join(ROOT, "include", "a2d.h")]
     jobs, objs = [], []
     for src in SOURCES:

@@ -284,6 +284,7 @@ a2d_status partial_bwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
       parts = plan(cap_ws, 1);
       kv_in_ws = parts.kv > 1;
     }
+    if (!parts.keep_ds) ds_ws = nullptr;                   // (faster without, see plan_bwd_mfma)
     float *dk = dK_part, *dv = dV_part, *dq = dQ_part;
     if (parts.kv > 1) {
       dk = kv_in_ws ? split_ws : more;

@@ -43,6 +43,12 @@ __device__ __forceinline__ void store_acc_t(float* __restrict__ out_row, const f
     }
 }
 
+// the value another lane holds (a DPP control word: quad_perm, row_half_mirror 0x141, row_mirror 0x140)
+template <int CTRL>
+__device__ __forceinline__ float lane_swap(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+
 __device__ __forceinline__ f32x4 lds_load_f32x4(unsigned addr) {
   return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>((uintptr_t)addr);
 }

@@ -56,8 +56,8 @@ template <> struct dtype_of<bf16_t> { static constexpr int value = A2D_BF16; };
 struct GridView {
   int side, cyclic;
   int64_t q, k, v, g, o;  // elements between blocks of Q, K, V, dO, O
-  a2d_layout out[2];      // rows of a block of dQ, or of dK and dV, in the whole tensors
-  int64_t out_step[2];    // elements between their blocks
+  a2d_layout out[3];      // rows of a block of dQ, dK, dV in the whole tensors
+  int64_t out_step[3];    // elements between their blocks
 };
 struct Segment {
   int start, rows;
@@ -227,7 +227,17 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap);
 // Parts of the two kernels of a backward tile, each at most its cap, and the dQ kernel's workgroup shape
 struct BwdParts {
   int kv, q, form, wide;     // wide: dK/dV in workgroups of 256 keys (launch_dkdv_wide)
+  int one, q_first;          // one launch (launch_bwd_one), its dQ workgroups first
+  int keep_ds;               // dS handed from dK/dV to dQ
 };
+// Walks of a tile's or grid's dK/dV workgroups (steps of 32 query rows) and dQ workgroups (64 keys): on average, the
+// longest; uneven: under a mask, longest first
+struct BwdWalks {
+  double kv_mean, kv_most, q_mean, q_most;
+  bool uneven;
+};
+double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w, int cus, int cap_kv, int cap_q,
+                    BwdParts* best);
 BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q);
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q);
 
@@ -261,16 +271,15 @@ size_t bwd_ds_bytes(const a2d_tile_desc& d, const SegList& g);
 hipError_t launch_dkdv_wide(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                             const void* V, const void* dO, const float* lse, const float* delta, float* dK, float* dV,
                             void* dS, hipStream_t s);
+// dQ (forms 0 and 1) and dK/dV workgroups in one launch, of a tile or of a whole grid (g.b: lse and delta [heads][seq], the
+// gradients in its layouts, of split walks the partial buffers); delta is written where parts.wide, else not used
+hipError_t launch_bwd_one(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
+                          const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ,
+                          float* dK, float* dV, const BwdParts& parts, hipStream_t s);
 // (parts > 1: the outputs are the partial buffers, [parts][heads][rows][H] each)
 hipError_t launch_bwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                            const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ,
                            float* dK, float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s);
-
-// A whole grid (g.b), recomputing the scores for dQ: gq, gk with the parts and output layouts of dQ and of dK, dV; lse and
-// delta [heads][seq].  (parts > 1: that output is the partial buffer)
-hipError_t launch_bwd_grid(Phase ph, const a2d_tile_desc& d, const SegList& gq, const SegList& gk, const void* Q,
-                           const void* K, const void* V, const void* O, const void* dO, const float* lse, float* delta,
-                           void* dQ, void* dK, void* dV, const BwdParts& parts, hipStream_t s);
 
 struct FixPtrs {
   const float* o[A2D_MAX_PARTS];

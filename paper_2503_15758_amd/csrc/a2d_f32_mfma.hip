@@ -291,7 +291,7 @@ __device__ __forceinline__ bool query_block(const a2d_tile_desc& d, const SegLis
                                             int& part) {
   const int nqb = (d.nq + rows - 1) / rows;
   int unit, blk;
-  if (!xcd_map(d.heads / g.group * g.parts, g.group * nqb, g.by_size != 0, unit, blk)) return false;
+  if (!xcd_map(blockIdx.x, d.heads / g.group * g.parts, g.group * nqb, g.by_size != 0, unit, blk)) return false;
   const int kvh = unit / g.parts;
   part = unit - kvh * g.parts;
   head = kvh * g.group + (g.by_size ? blk % g.group : blk / nqb);
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   warm_arguments<8 * 8>();
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int head, blk;                                      // key/value head
-  if (!xcd_map(d.heads / g.group * g.parts, (d.nkv + BLK - 1) / BLK, g.by_size != 0, head, blk)) return;
+  if (!xcd_map(blockIdx.x, d.heads / g.group * g.parts, (d.nkv + BLK - 1) / BLK, g.by_size != 0, head, blk)) return;
   const int unit = head, lanes = KL * g.parts;
   head = unit / g.parts;
   const int part = unit - head * g.parts;
@@ -722,7 +722,7 @@ void plan_fwd_f32(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
 BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q) {
   const int64_t bq = (int64_t)d.heads * ((d.nq + 15) / 16), bk = (int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16);
   const double sq = (double)visible_keys(d, g, d.nq - 1) / BLK + 1, sk = (double)g.group * ((d.nq + 15) / 16);
-  BwdParts p;
+  BwdParts p = {};
   p.form = p.wide = 0;
   p.kv = best_parts(f32_walk(bk, sk, 4, d.hdim, cus), cap_kv, 5.0,
                     (double)d.heads / g.group * d.nkv * d.hdim * 16 / 5e6, nullptr);

@@ -160,12 +160,9 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
   BwdParts bp;
   describe(p, &d, &g);
   if (!plan_backward(p, d, g, &bp)) return hipErrorInvalidDevice;
-  SegList gq = g, gk = g;
-  gq.parts = bp.q;
-  gk.parts = bp.kv;
-  output(p, p.dq, &gq, 0);
-  output(p, p.dk, &gk, 0);
-  output(p, p.dv, &gk, 1);
+  output(p, p.dq, &g, 0);
+  output(p, p.dk, &g, 1);
+  output(p, p.dv, &g, 2);
   float* delta = static_cast<float*>(ws);
   float* more = reinterpret_cast<float*>(static_cast<char*>(ws) + up256((size_t)p.heads * p.seq * sizeof(float)));
   // all lines of Alg. 3 in two launches, or the partials of split walks
@@ -189,10 +186,10 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
     k = split(bp.kv, p.kv_heads, nk, dK, p.dk);
     v = split(bp.kv, p.kv_heads, nk, dV, p.dv);
   }
-  hipError_t e = launch_bwd_grid(PREPARE, d, gq, gk, Q, K, V, O, dO, lse, delta, q, k, v, bp, s);
+  hipError_t e = launch_bwd_one(PREPARE, d, g, Q, K, V, O, dO, lse, delta, (float*)q, (float*)k, (float*)v, bp, s);
   if (e != hipSuccess) return e;
   trace_mark(s);
-  e = launch_bwd_grid(LAUNCH, d, gq, gk, Q, K, V, O, dO, lse, delta, q, k, v, bp, s);
+  e = launch_bwd_one(LAUNCH, d, g, Q, K, V, O, dO, lse, delta, (float*)q, (float*)k, (float*)v, bp, s);
   return e != hipSuccess || n == 0 ? e : launch_sum_grid(n, sets, p.hdim, A2D_BF16, s);
 }
 

@@ -162,8 +162,8 @@ __host__ __device__ inline int size_chunk(int whole, int nblocks, int turn) {
 __host__ __device__ inline int xcd_grid(int heads, int nblocks) {
   return kXcds * (heads / kXcds * nblocks + (heads % kXcds * nblocks + kXcds - 1) / kXcds);
 }
-__device__ __forceinline__ bool xcd_map(int heads, int nblocks, bool by_size, int& head, int& block, int turn = 0) {
-  const int id = blockIdx.x;
+// (id: the workgroup's number in the launch, or in its own part of one - which then starts at a multiple of kXcds)
+__device__ __forceinline__ bool xcd_map(int id, int heads, int nblocks, bool by_size, int& head, int& block, int turn = 0) {
   const int x = id % kXcds;
   int k = id / kXcds;
   const int whole = heads / kXcds, rest = heads % kXcds, spread = rest * nblocks;
