@@ -50,7 +50,7 @@ def call_kernels(call, w, recompute):
         return ["fwd_mfma_kernel" if w.dtype == "bf16" else "fwd_f32_kernel"]
     if call.startswith("partial_bwd"):
         if w.dtype != "bf16":
-            return ["bwd_dq_f32_kernel", "bwd_dkdv_f32_kernel"]
+            return ["bwd_f32_kernel"]
         if 2 * w.heads * (-(-w.tile // 256)) <= 6 * 256:      # at most six turns of 256 compute units: one launch
             return ["delta_kernel", "bwd_one_kernel"]
         if recompute:
@@ -233,8 +233,8 @@ def main():
             ks = call_kernels(n, w, args.recompute_bwd)
             if "delta_kernel" in ks:
                 kbytes[(n, "delta_kernel")] = rows * (2 * H * esz + 4)
-            if "bwd_one_kernel" in ks:
-                kflops[(n, "bwd_one_kernel")] = b             # (recomputation of S and dP not counted)
+            if ks[-1] in ("bwd_one_kernel", "bwd_f32_kernel"):
+                kflops[(n, ks[-1])] = b                       # (recomputation of S and dP not counted)
                 continue
             k_kv, = [k for k in ks if k.startswith("bwd_dkdv")]
             k_dq, = [k for k in ks if k.startswith("bwd_dq")]

@@ -69,13 +69,13 @@ struct SegList {
   int norm;
   int group;
   int by_size;
-  GridView b;
   int parts;      // workgroups that share the walk of one block, each leaving a partial result (>= 1)
   int form;       // which of its workgroup shapes a forward / dQ launch takes (plan_* below)
   Segment seg[A2D_MAX_SEGMENTS];
+  GridView b;     // (last: a tile's kernels do not read it)
 };
 
-// Brings the kernel's arguments - the tile's descriptor, the list's head and first sub-block, and the
+// Brings the kernel's arguments - the tile's descriptor, the list's head and first sub-block, the grid, and the
 // pointers behind them - into the scalar cache in one go.  A cold line costs about half a microsecond,
 // and read one after another as the prologue comes to them they were a good part of the time of small
 // tiles.
@@ -83,16 +83,18 @@ struct SegList {
 template <int MORE>
 __device__ __forceinline__ void warm_arguments() {
   constexpr int head = (int)(sizeof(a2d_tile_desc) + offsetof(SegList, seg) + sizeof(Segment) + 63) / 64;
-  constexpr int tail = (int)(sizeof(a2d_tile_desc) + sizeof(SegList)) / 64;
+  constexpr int grid = (int)(sizeof(a2d_tile_desc) + offsetof(SegList, b)) / 64;
   constexpr int last = (int)(sizeof(a2d_tile_desc) + sizeof(SegList) + MORE - 1) / 64;
-  static_assert(head <= 5 && last - tail <= 2, "lines to touch");
-  int v[8];
+  static_assert(head <= 4 && last - grid <= 4, "lines to touch");
+  constexpr auto line = [](int n) { return 64 * (n < last ? n : last); };
+  int v[9];
   asm volatile(
-      "s_load_dword %0, %8, 0x0\n\ts_load_dword %1, %8, 0x40\n\ts_load_dword %2, %8, 0x80\n\t"
-      "s_load_dword %3, %8, 0xc0\n\ts_load_dword %4, %8, 0x100\n\ts_load_dword %5, %8, %9\n\t"
-      "s_load_dword %6, %8, %10\n\ts_load_dword %7, %8, %11\n\ts_waitcnt lgkmcnt(0)"
-      : "=&s"(v[0]), "=&s"(v[1]), "=&s"(v[2]), "=&s"(v[3]), "=&s"(v[4]), "=&s"(v[5]), "=&s"(v[6]), "=&s"(v[7])
-      : "s"(__builtin_amdgcn_kernarg_segment_ptr()), "i"(64 * tail), "i"(64 * (tail + (last > tail))), "i"(64 * last));
+      "s_load_dword %0, %9, 0x0\n\ts_load_dword %1, %9, 0x40\n\ts_load_dword %2, %9, 0x80\n\t"
+      "s_load_dword %3, %9, 0xc0\n\ts_load_dword %4, %9, %10\n\ts_load_dword %5, %9, %11\n\t"
+      "s_load_dword %6, %9, %12\n\ts_load_dword %7, %9, %13\n\ts_load_dword %8, %9, %14\n\ts_waitcnt lgkmcnt(0)"
+      : "=&s"(v[0]), "=&s"(v[1]), "=&s"(v[2]), "=&s"(v[3]), "=&s"(v[4]), "=&s"(v[5]), "=&s"(v[6]), "=&s"(v[7]), "=&s"(v[8])
+      : "s"(__builtin_amdgcn_kernarg_segment_ptr()), "i"(line(grid)), "i"(line(grid + 1)), "i"(line(grid + 2)),
+        "i"(line(grid + 3)), "i"(line(last)));
 }
 
 // ---- a whole grid: block t (all of them cost-ordered, heaviest first) of the side x nblk blocks of rows that a
@@ -241,8 +243,7 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
 BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q);
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q);
 
-// fp32 tile kernels on the fp32 matrix units (H in {64, 80, 96, 128}); nothing to prepare.  The
-// backward also computes delta (into `delta`).
+// fp32 tile kernels on the fp32 matrix units (H in {64, 80, 96, 128}); nothing to prepare.
 hipError_t launch_fwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                           float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s);
 hipError_t launch_bwd_f32(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,

@@ -3,9 +3,12 @@
 // fp32 throughout: v_mfma_f32_16x16x4_f32 multiplies and accumulates in fp32 (2048 flop in 32 cycles
 // of a SIMD, 157 TFLOP/s over the chip - twice what unpacked vector FMAs reach).
 //
-// What bounds them: the fp32 MFMA rate where there are many rows; at 16 x 700 x 900 two ragged launches, one
-// behind the other, in which the matrix units work 42-44 % of the cycles.  A step of 16 keys (queries)
+// What bounds them: the fp32 MFMA rate where there are many rows (78 % of it at 16 x 4096 x 4096, H = 128); at 16 x 700 x
+// 900 prologues, merges and uneven walks of a few steps (55 %).  A step of 16 keys (queries)
 // against 16 rows is H / 4 MFMAs of 32 cycles per contraction, on 8 KiB of operands at H = 128.
+//   - The backward's dQ and dK/dV workgroups go out in one launch, so that the end of the one kind overlaps the start of
+//     the other (two launches, dQ leaving delta for dK/dV: 2 x 128 x 128, H = 64 13.4 -> 7.1 us; 8 x 256 x 900, H = 80
+//     39 -> 26; 16 x 700 x 900, H = 96, causal 109 -> 100).
 //   - Operands of a step come in by whole rows (16 lanes on 256 bytes), one step ahead, and pass through
 //     a tile in LDS that is the wavefront's own (no barriers): a contraction over H needs lane = row, and
 //     loading that from memory is 64 separate accesses per instruction, which kept the matrix units
@@ -29,10 +32,9 @@
 //     result (64 G + 16 g + 4 r + t), stored as four 16-byte pieces.  (H = 96 and 80 end in a group of
 //     32 or 16 columns with 8- or 4-byte pieces: Cols<H> below.)
 // Measured against the vector-ALU kernels of a2d_generic.hip: 16 heads x 700 x 900, H = 96, causal,
-// backward call 1034 -> 109 us (128 with the operands loaded lane = row; 52 us dQ, 69 us dK/dV by events around
-// them); 2 heads x 128 x 128, H = 64, forward 29 -> 5.2 us; 16 heads x 4096 x 4096, H = 128: forward 1.07 ms (129
-// TFLOP/s, 82 % of the fp32 matrix peak), dQ 1.73 ms (119 TFLOP/s executed), dK/dV 2.22 ms (124 TFLOP/s).
-#include "a2d_mfma.hpp"
+// backward call 1034 -> 100 us; 2 heads x 128 x 128, H = 64, forward 29 -> 5.2 us; 16 heads x 4096 x 4096, H = 128: forward
+// 1.07 ms (129 TFLOP/s, 82 % of the fp32 matrix peak), backward 3.87 ms (124 TFLOP/s executed).
+#include "a2d_bwd.hpp"
 
 namespace a2d {
 namespace {
@@ -83,6 +85,13 @@ struct Cols {
       b[0] = w[0]; b[1] = w[1];
     }
     if constexpr (REST == 16) b[0] = gload<float>(base, off + 256 * N4 + 4 * l15);
+  }
+  __device__ __forceinline__ float dot(const Cols& o) const {
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < H / 16; ++i)
+      t = fmaf(i < 4 * N4 ? a[i / 4][i % 4] : b[i - 4 * N4], i < 4 * N4 ? o.a[i / 4][i % 4] : o.b[i - 4 * N4], t);
+    return t;
   }
   template <int T>
   __device__ __forceinline__ float get() const {
@@ -287,13 +296,13 @@ struct Walk {
 
 // workgroup -> (head, first row, part of the walk): as in the bf16 kernels the row blocks of the query
 // heads that share a key/value head are placed together, late (heavy) blocks first
-__device__ __forceinline__ bool query_block(const a2d_tile_desc& d, const SegList& g, int rows, int& head, int& q0,
-                                            int& part) {
+__device__ __forceinline__ bool query_block(int id, const a2d_tile_desc& d, const SegList& g, int parts, int rows,
+                                            int& head, int& q0, int& part) {
   const int nqb = (d.nq + rows - 1) / rows;
   int unit, blk;
-  if (!xcd_map(blockIdx.x, d.heads / g.group * g.parts, g.group * nqb, g.by_size != 0, unit, blk)) return false;
-  const int kvh = unit / g.parts;
-  part = unit - kvh * g.parts;
+  if (!xcd_map(id, d.heads / g.group * parts, g.group * nqb, g.by_size != 0, unit, blk)) return false;
+  const int kvh = unit / parts;
+  part = unit - kvh * parts;
   head = kvh * g.group + (g.by_size ? blk % g.group : blk / nqb);
   q0 = (nqb - 1 - (g.by_size ? blk / g.group : blk % nqb)) * rows;
   return true;
@@ -315,6 +324,14 @@ __device__ __forceinline__ float row_sum(float v) {
   return v + __shfl_xor(v, 32, 64);
 }
 
+// sum over the 16 lanes of a group, left in all of them (see lane_swap)
+__device__ __forceinline__ float col_sum(float v) {
+  v += mfma::lane_swap<0xB1>(v);
+  v += mfma::lane_swap<0x4E>(v);
+  v += mfma::lane_swap<0x141>(v);
+  return v + mfma::lane_swap<0x140>(v);
+}
+
 // ------------------------------------------------------------------ forward
 // (O_part, m_out and l_out are not __restrict__: an accumulating call's `in` is the same memory)
 template <int H, int RT>
@@ -324,7 +341,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   warm_arguments<6 * 8 + sizeof(FwdInput)>();
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int head, q0, part;
-  if (!query_block(d, g, BLK * RT, head, q0, part)) return;
+  if (!query_block(blockIdx.x, d, g, g.parts, BLK * RT, head, q0, part)) return;
   const int lanes = KL * g.parts;
   const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l15 = lane & 15, g4 = lane >> 4;
@@ -455,17 +472,16 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
 
 // ---------------------------------------------------------------- backward: dQ (and delta)
 // Owns 16 query rows per workgroup.  Also computes delta = rowsum(dO o O) of its rows (every key lane
-// for itself) and leaves it for the dK/dV kernel, which runs after it: no separate pass over O and dO.
+// for itself): no separate pass over O and dO.
 template <int H>
-__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void bwd_dq_f32_kernel(
-    a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
-    const float* __restrict__ V, const float* __restrict__ O, const float* __restrict__ dO,
-    const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dQ) {
-  warm_arguments<8 * 8>();
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+__device__ __forceinline__ void dq_rows(int id, char* const smem, const a2d_tile_desc& d, const SegList& g,
+                                        const int parts, const float* __restrict__ Q, const float* __restrict__ K,
+                                        const float* __restrict__ V, const float* __restrict__ O,
+                                        const float* __restrict__ dO, const float* __restrict__ lse,
+                                        float* __restrict__ dQ) {
   int head, q0, part;
-  if (!query_block(d, g, BLK, head, q0, part)) return;
-  const int lanes = KL * g.parts;
+  if (!query_block(id, d, g, parts, BLK, head, q0, part)) return;
+  const int lanes = KL * parts;
   const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l15 = lane & 15, g4 = lane >> 4;
   const int kvh = head / g.group;
@@ -484,7 +500,6 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
     for (int e = 0; e < 4; ++e) del = fmaf(gf[0].v[y][e], of.v[y][e], del);
   del = row_sum(del);
-  if (kl == 0 && part == 0 && g4 == 0 && q_row < d.nq) delta[(int64_t)head * d.nq + q_row] = del;
 
   const int blk_last = min(q0 + BLK, d.nq) - 1;
   auto seg_blocks = [&](int s) { return (vis_count(d, g, blk_last, s) + BLK - 1) / BLK; };
@@ -538,28 +553,30 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
 
 // ---------------------------------------------------------------- backward: dK, dV
 // Owns 16 keys of a key/value head per workgroup and walks the query rows of all its group's query
-// heads, 16 at a time: S = Q K^T and dP = dO V^T leave a lane holding 4 queries of ONE key.
-template <int H>
-__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void bwd_dkdv_f32_kernel(
-    a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
-    const float* __restrict__ V, const float* __restrict__ dO, const float* __restrict__ lse,
-    const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV) {
-  warm_arguments<8 * 8>();
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+// heads, 16 at a time: S = Q K^T and dP = dO V^T leave a lane holding 4 queries of ONE key.  OWN_DELTA: delta of the step's
+// rows from those of O, which come in beside those of dO (lane: the same columns of the same rows); else it is read.
+template <int H, bool OWN_DELTA>
+__device__ __forceinline__ void dkdv_keys(int id, char* const smem, const a2d_tile_desc& d, const SegList& g,
+                                          const int parts, const float* __restrict__ Q, const float* __restrict__ K,
+                                          const float* __restrict__ V, const float* __restrict__ O,
+                                          const float* __restrict__ dO, const float* __restrict__ lse,
+                                          const float* __restrict__ delta, float* __restrict__ dK,
+                                          float* __restrict__ dV) {
   int head, blk;                                      // key/value head
-  if (!xcd_map(blockIdx.x, d.heads / g.group * g.parts, (d.nkv + BLK - 1) / BLK, g.by_size != 0, head, blk)) return;
-  const int unit = head, lanes = KL * g.parts;
-  head = unit / g.parts;
-  const int part = unit - head * g.parts;
+  if (!xcd_map(id, d.heads / g.group * parts, (d.nkv + BLK - 1) / BLK, g.by_size != 0, head, blk)) return;
+  const int unit = head, lanes = KL * parts;
+  head = unit / parts;
+  const int part = unit - head * parts;
   const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l15 = lane & 15, g4 = lane >> 4;
   const int k0 = blk * BLK, key = k0 + l15, k_ld = min(key, d.nkv - 1);
   const gptr_t qb = uniform_gptr(Q + (int64_t)head * g.group * d.lq.head);
   const gptr_t gb = uniform_gptr(dO + (int64_t)head * g.group * d.ldo.head);
   const float* lse_b = lse + (int64_t)head * g.group * d.nq;
-  const float* del_b = delta + (int64_t)head * g.group * d.nq;
-  const unsigned q_row = (unsigned)d.lq.row * 4, g_row = (unsigned)d.ldo.row * 4;
-  const unsigned q_head = (unsigned)d.lq.head * 4, g_head = (unsigned)d.ldo.head * 4;
+  const float* del_b = OWN_DELTA ? nullptr : delta + (int64_t)head * g.group * d.nq;
+  const gptr_t ob = uniform_gptr(O + (int64_t)head * g.group * d.lo.head);
+  const unsigned q_row = (unsigned)d.lq.row * 4, g_row = (unsigned)d.ldo.row * 4, o_row = (unsigned)d.lo.row * 4;
+  const unsigned q_head = (unsigned)d.lq.head * 4, g_head = (unsigned)d.ldo.head * 4, o_head = (unsigned)d.lo.head * 4;
 
   Nat<H> kf[1], vf[1];
   kf[0].load(uniform_gptr(K + (int64_t)head * d.lk.head), k_ld, (unsigned)d.lk.row * 4, g4);
@@ -589,7 +606,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   Tile<H> qt, gt;
   qt.init((lds_t)smem + 2 * kl * Tile<H>::BYTES, l15, g4);
   gt.init((lds_t)smem + (2 * kl + 1) * Tile<H>::BYTES, l15, g4);
-  Cols<H> qc[4], gc[4];                               // the rows of the step to come, and their statistics
+  Cols<H> qc[4], gc[4], oc[4];                        // the rows of the step to come, and their statistics
   float ln[4], dn[4];
   // position of walk step n: query head (inside the group) and first row
   const int n0 = part * KL + kl;
@@ -602,8 +619,9 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
       const unsigned row = min((b0 + rb) * BLK + 4 * g4 + r, d.nq - 1);
       qc[r].load(qb + qh * q_head, row, q_row, l15);
       gc[r].load(gb + qh * g_head, row, g_row, l15);
+      if constexpr (OWN_DELTA) oc[r].load(ob + qh * o_head, row, o_row, l15);
+      else dn[r] = del_b[qh * d.nq + row];
       ln[r] = lse_b[qh * d.nq + row];
-      dn[r] = del_b[qh * d.nq + row];
     }
   };
   if (n0 < total) load();
@@ -611,7 +629,11 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     const int i0 = (b0 + rb) * BLK;
     float ls[4], de[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) { ls[r] = ln[r]; de[r] = dn[r]; }
+    for (int r = 0; r < 4; ++r) {
+      ls[r] = ln[r];
+      if constexpr (OWN_DELTA) de[r] = col_sum(gc[r].dot(oc[r]));
+      else de[r] = dn[r];
+    }
     qt.store(qc, l15);
     gt.store(gc, l15);
     rb += lanes;
@@ -642,6 +664,21 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     dk.store(dK + row * H, g4, d.scale);
     dv.store(dV + row * H, g4, 1.0f);
   }
+}
+
+// The two kinds of workgroups in one launch, `first` of the kind with the longer walks before the others (see
+// a2d_bwd_one.hip; here always: fp32 tiles are small).
+template <int H, bool OWN_DELTA>
+__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void bwd_f32_kernel(
+    a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
+    const float* __restrict__ V, const float* __restrict__ O, const float* __restrict__ dO,
+    const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dQ, float* __restrict__ dK,
+    float* __restrict__ dV, int first, int q_first, int parts_q) {
+  warm_arguments<10 * 8 + 12>();
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int id = (int)blockIdx.x < first ? blockIdx.x : blockIdx.x - first;
+  if (((int)blockIdx.x < first) == (q_first != 0)) dq_rows<H>(id, smem, d, g, parts_q, Q, K, V, O, dO, lse, dQ);
+  else dkdv_keys<H, OWN_DELTA>(id, smem, d, g, g.parts, Q, K, V, O, dO, lse, delta, dK, dV);
 }
 
 // LDS of a workgroup: the wavefronts' tiles, over which their results are merged at the end
@@ -676,27 +713,39 @@ hipError_t fwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const 
                               : fwd_go<H, 1>(d, g, Q, K, V, O_part, m, l, in, s);
 }
 
+template <int H, bool OWN_DELTA>
+hipError_t bwd_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                  const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK, float* dV,
+                  const BwdParts& parts, hipStream_t s) {
+  SegList go = g;
+  if (parts.q > 1) go.acc = 0;                       // (the sum over the parts adds)
+  go.parts = parts.kv;
+  constexpr int lds = most(dq_lds<H>(), dkdv_lds<H>());
+  hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_f32_kernel<H, OWN_DELTA>), lds);
+  if (e == hipSuccess && !OWN_DELTA) e = launch_delta(d, O, dO, delta, s);
+  if (e != hipSuccess) return e;
+  const int n_q = xcd_grid(d.heads / g.group * parts.q, g.group * ((d.nq + BLK - 1) / BLK));
+  const int n_kv = xcd_grid(d.heads / g.group * parts.kv, (d.nkv + BLK - 1) / BLK);
+  A2D_LAUNCH((bwd_f32_kernel<H, OWN_DELTA>), dim3(n_q + n_kv), dim3(64 * KL), lds, s, d, go, (const float*)Q,
+             (const float*)K, (const float*)V, (const float*)O, (const float*)dO, lse, delta, dQ, dK, dV,
+             parts.q_first ? n_q : n_kv, parts.q_first, parts.q);
+  return hipGetLastError();
+}
+// delta: from O by the dK/dV workgroups themselves; by a launch in front where there are more than four turns of them,
+// two a compute unit, and at H = 128, where the rows of O do not fit the registers beside the others, more than two (H = 128:
+// 16 x 300 x 300 43 us against 54 with the launch, 16 x 1024 x 1024 293 / 274; H = 64, 16 x 1024 x 1024 causal 83 / 85,
+// 16 x 4096 x 4096 2015 / 1987).
 template <int H>
 hipError_t bwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                  const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK, float* dV,
                  const BwdParts& parts, hipStream_t s) {
-  SegList gq = g, gk = g;
-  gq.parts = parts.q;
-  if (parts.q > 1) gq.acc = 0;                       // (the sum over the parts adds)
-  gk.parts = parts.kv;
-  hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_f32_kernel<H>), dq_lds<H>());
-  if (e == hipSuccess) e = ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dkdv_f32_kernel<H>), dkdv_lds<H>());
+  int cus = 0;
+  const hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
-  const dim3 block(64 * KL);
-  A2D_LAUNCH((bwd_dq_f32_kernel<H>), dim3(xcd_grid(d.heads / g.group * gq.parts, g.group * ((d.nq + BLK - 1) / BLK))), block,
-             dq_lds<H>(), s, d, gq, (const float*)Q, (const float*)K, (const float*)V, (const float*)O, (const float*)dO,
-             lse, delta, dQ);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  A2D_LAUNCH((bwd_dkdv_f32_kernel<H>), dim3(xcd_grid(d.heads / g.group * gk.parts, (d.nkv + BLK - 1) / BLK)), block,
-             dkdv_lds<H>(), s, d, gk, (const float*)Q, (const float*)K, (const float*)V, (const float*)dO, lse, delta, dK,
-             dV);
-  return hipGetLastError();
+  const int64_t wgs = (int64_t)d.heads * parts.q * ((d.nq + BLK - 1) / BLK) +
+                      (int64_t)(d.heads / g.group) * parts.kv * ((d.nkv + BLK - 1) / BLK);
+  return wgs > (H == 128 ? 2 : 4) * 2 * (int64_t)cus ? bwd_go<H, false>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s)
+                                                     : bwd_go<H, true>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s);
 }
 
 // The walk of 16-row blocks as a model: a turn is one wavefront per SIMD, a step of `contractions`
@@ -723,11 +772,22 @@ BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap
   const int64_t bq = (int64_t)d.heads * ((d.nq + 15) / 16), bk = (int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16);
   const double sq = (double)visible_keys(d, g, d.nq - 1) / BLK + 1, sk = (double)g.group * ((d.nq + 15) / 16);
   BwdParts p = {};
-  p.form = p.wide = 0;
   p.kv = best_parts(f32_walk(bk, sk, 4, d.hdim, cus), cap_kv, 5.0,
                     (double)d.heads / g.group * d.nkv * d.hdim * 16 / 5e6, nullptr);
   p.q = best_parts(f32_walk(bq, sq, 3, d.hdim, cus), cap_q, p.kv > 1 ? 1.0 : 5.0,
                    (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
+  // the kind with the longer walks first; under a mask the longest and the shortest count alike, so that short ones come
+  // last (16 x 700 x 900: dQ first 100 us, dK/dV first 104; 16 x 1024 x 1024, H = 64, causal 90 / 83)
+  double lq = sq, lk = sk, of_rows[8];
+  if (g.by_size) {
+    mean_visible_keys(d, g, of_rows);
+    const double all = (double)visible_keys(d, g, d.nq - 1);
+    lq = (double)visible_keys(d, g, 0) / BLK;
+    lk = 0;                                          // rows that see the last keys
+    for (int i = 0; i < 8; ++i) lk += of_rows[i] >= all ? sk / 8 : 0;
+  }
+  p.q_first = 3 * (sq + lq) / p.q > 4 * (sk + lk) / p.kv;
+  p.one = 1;
   return p;
 }
 
