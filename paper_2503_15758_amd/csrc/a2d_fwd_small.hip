@@ -1,0 +1,336 @@
+// bf16 MFMA forward tile kernel for short calls: the contractions of a2d_fwd_mfma.hip, 32 query rows per workgroup.
+//
+// A call of few query rows leaves most of the chip without work when its blocks are 128 rows, and sharing their
+// walks between workgroups costs partial results in memory and a launch that merges them.  Here the eight
+// wavefronts of a workgroup hold the SAME 32 rows and take every eighth slab of 32 keys; their (N, m, l) are
+// merged through LDS at the end.  Nothing is shared during the walk, so there is no barrier in it: each wavefront
+// stages its slabs in a piece of LDS of its own.  (K read straight into the A operands, a lane a row, goes 32 lines at a
+// time through an L1 that eight wavefronts share: 13.5 us became 16.4 at 8 x 1024 x 1024, H = 128.)
+// What bounds it: launch, argument and first-load latencies below two rounds of slabs; then what a compute unit reads
+// from L2, 128 KiB a round at H = 128 (1.65 us; its MFMAs take 0.45), since every 32 rows read all keys they see.  For
+// short calls that is cheaper than partial results and a second launch, for long ones not (see plan_fwd_mfma).
+// Measured, against the best of the other forms: H = 128 2 x 512 x 512 causal 15.4 -> 9.6 us, 8 x 1024 x 1024 23.0 -> 13.6,
+// 4 x 2048 x 2048 26.5 -> 20.7; H = 64 64 x 128 x 128 6.8 -> 5.5, 8 x 1024 x 1024 16.6 -> 9.0.
+#include "a2d_mfma.hpp"
+
+namespace a2d {
+namespace {
+
+using namespace mfma;
+
+constexpr int SB = 32, LANES = 8;                  // keys of a slab, wavefronts
+// LDS: every wavefront's { K slab, V slab } (rows as in a2d_fwd_mfma.hip) | m, l of every wavefront's rows
+constexpr int KLD = 272, VLD = 320, V_AT = SB * KLD, SLAB_BYTES = SB * (KLD + VLD);
+constexpr int STAT = LANES * SLAB_BYTES;
+constexpr int LDS_BYTES = STAT + 2 * LANES * SB * 4;
+constexpr float kRescaleThreshold = 8.0f;          // log2 units
+static_assert(LANES * 8 * 1024 <= STAT, "the pieces of two column tiles must fit the slabs");
+
+// (template parameter, arguments and outputs as of fwd_mfma_kernel)
+template <int HR, int GRID>
+__global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
+    a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+    const bf16_t* __restrict__ V, float* O_part, float* m_out, float* l_out, FwdInput in) {
+  constexpr int HD = padded_head(HR), H = HR, KS = (HR + 15) / 16, CT = HD / 32;
+  constexpr bool PLAIN = GRID == 0, CYCLIC = GRID == 2;
+  warm_arguments<9 * 8>();
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int half = lane >> 5, l32 = lane & 31;
+
+  const int nqb = (d.nq + 31) / 32;
+  int unit, blk;
+  const int by_size = GRID ? d.causal : g.by_size;
+  if (!xcd_map(blockIdx.x, d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * nqb, by_size != 0, unit, blk,
+               kXcdCus)) return;
+  const int kvh = unit / g.parts, part = unit - kvh * g.parts;
+  const int head = kvh * g.group + (GRID || by_size ? blk % g.group : blk / nqb);
+  blk = GRID || by_size ? blk / g.group : blk % nqb;
+  const GridBlock gb = GRID ? grid_block(g.b, nqb, blk) : GridBlock{0, blk};
+  const int row_blk = gb.r;                        // of the grid
+  blk = gb.blk;
+  const int q0 = (nqb - 1 - blk) * 32;
+  Q += (int64_t)head * d.lq.head + (GRID ? row_blk * g.b.q : 0);
+  K += (int64_t)kvh * d.lk.head;
+  V += (int64_t)kvh * d.lv.head;
+  if (!GRID || !g.norm) {
+    const int64_t slot = ((int64_t)part * (GRID ? g.b.side : 1) + row_blk) * d.heads * d.nq;
+    O_part += slot * HR;
+    m_out += slot;
+    l_out += slot;
+  }
+
+  // ---- Q^T fragments; rows beyond nq re-read the last row
+  const int q_row = q0 + l32, q_ld = min(q_row, d.nq - 1);
+  bf16x8 qf[KS];
+  {
+    const bf16_t* qp = Q + (int64_t)q_ld * d.lq.row + 8 * half;
+#pragma unroll
+    for (int x = 0; x < KS; ++x) qf[x] = *reinterpret_cast<const bf16x8*>(qp + 16 * x);
+  }
+  const float c = d.scale * kLog2e;
+
+  // ---- visibility and the walk over (sub-block, slab), as in fwd_mfma_kernel
+  auto vis_count = [&](int i, int s) -> int {
+    if (GRID == 1) return d.causal ? row_blk * d.nq + i + 1 : g.b.side * d.nkv;
+    if (GRID == 2) return d.causal ? i + 1 : d.nkv;
+    if (!d.causal) return g.seg[s].rows;
+    const int64_t v = (int64_t)i + g.seg[s].rel + 1;
+    return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
+  };
+  const int last_row = min(q0 + 31, d.nq - 1);
+  const int segs = PLAIN ? g.n : CYCLIC ? g.b.side : 1, stride = LANES * g.parts;
+  const int grid_rows = GRID == 1 ? g.b.side * d.nkv : d.nkv;
+  const int shift_from = CYCLIC && d.causal ? row_blk : segs;
+  int nfull = 0, my_vis = 0;                       // of the current sub-block: keys all rows see, the lane's row
+  auto enter_segment = [&](int s) {
+    nfull = vis_count(q0, s);
+    my_vis = vis_count(q_ld, s);
+  };
+  auto open_segment = [&](int s, int& sb, int& n) {
+    n = 0;
+    while (s < segs && (n = (vis_count(last_row, s) + SB - 1) / SB) == 0) ++s;
+    sb = s;
+  };
+  auto advance = [&](int by, int& sb, int& j, int& n) {
+    if constexpr (CYCLIC) {
+      const int q = by / segs;
+      j += q;
+      sb += by - q * segs;
+      if (sb >= segs) { sb -= segs; ++j; }
+      if (j >= n) sb = segs;
+    } else {
+      j += by;
+      while (seldom(j >= n)) {
+        if (sb >= segs) break;
+        j -= n;
+        open_segment(sb + 1, sb, n);
+      }
+    }
+  };
+
+  // ---- staging: a lane moves one 16-byte chunk of ST_N rows (64 columns: eight lanes a row, else sixteen).  Rows
+  // beyond the sub-block re-read its last one.
+  constexpr int CHUNKS = HD == 64 ? 8 : 16, ST_ROWS = 64 / CHUNKS, ST_N = SB / ST_ROWS;
+  const unsigned k_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lk.row * 2);
+  const unsigned v_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lv.row * 2);
+  const unsigned k_col_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.k * 2)) : k_row_bytes;
+  const unsigned v_col_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.v * 2)) : v_row_bytes;
+  const int st_row = lane / CHUNKS, st_chunk = lane % CHUNKS;
+  int start = 0, rows = grid_rows;                 // of the sub-block to be loaded from (cyclic: the grid's column)
+  auto load_from = [&](int s) {
+    if (PLAIN) {
+      start = g.seg[s].start;
+      rows = g.seg[s].rows;
+    }
+  };
+  u32x4 kreg[ST_N], vreg[ST_N];
+#pragma unroll
+  for (int p = 0; p < ST_N; ++p) kreg[p] = vreg[p] = u32x4{0, 0, 0, 0};
+  auto load = [&](int s, int j) {
+    if (CYCLIC) start = s;
+    const gptr_t ka = uniform_gptr(reinterpret_cast<const char*>(K) + (start * k_col_bytes + (unsigned)(j * SB) * k_row_bytes));
+    const gptr_t va = uniform_gptr(reinterpret_cast<const char*>(V) + (start * v_col_bytes + (unsigned)(j * SB) * v_row_bytes));
+    if (st_chunk * 8 < H) {
+#pragma unroll
+      for (int p = 0; p < ST_N; ++p)
+        kreg[p] = gload_b128(ka, __umul24((unsigned)min(st_row + ST_ROWS * p, rows - 1 - j * SB), k_row_bytes) + 16 * st_chunk);
+#pragma unroll
+      for (int p = 0; p < ST_N; ++p)
+        vreg[p] = gload_b128(va, __umul24((unsigned)min(st_row + ST_ROWS * p, rows - 1 - j * SB), v_row_bytes) + 16 * st_chunk);
+    }
+  };
+  const unsigned slab = lds_base + kl * SLAB_BYTES;
+  const unsigned k_wr = slab + st_row * KLD + 16 * st_chunk, v_wr = slab + V_AT + st_row * VLD + 16 * st_chunk;
+  auto store = [&]() {
+    if (st_chunk * 8 < HD) {
+#pragma unroll
+      for (int p = 0; p < ST_N; ++p)
+        *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(k_wr + ST_ROWS * p * KLD)) = kreg[p];
+#pragma unroll
+      for (int p = 0; p < ST_N; ++p)
+        *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(v_wr + ST_ROWS * p * VLD)) = vreg[p];
+    }
+  };
+  const int g16 = lane >> 4, j16 = lane & 15;
+  const unsigned k_rd = slab + l32 * KLD + 16 * half;
+  const unsigned v_rd = slab + V_AT + (4 * (g16 >> 1) + (j16 >> 2)) * VLD + (16 * (g16 & 1) + 4 * (j16 & 3)) * 2;
+
+  int sb, j = 0, n;
+  open_segment(0, sb, n);
+  if (sb < segs) advance(part * LANES + kl, sb, j, n);
+  if (sb < segs) {
+    enter_segment(sb);
+    load_from(sb);
+    load(sb, j);
+  }
+
+  f32x16 o[CT];
+#pragma unroll
+  for (int t = 0; t < CT; ++t) o[t] = zero16();
+  float m_lane = -INFINITY, m_ref = -INFINITY, l_run = 0.f;
+  if (!GRID && g.acc && part == 0 && kl == 0) {
+    // the first wavefront continues the stored partial (rows past nq: the last row's, never stored)
+    const int64_t row = (int64_t)head * d.nq + q_ld;
+    m_lane = m_ref = in.m[row] / d.scale;
+    l_run = half == 0 ? in.l[row] : 0.f;
+    const float* np = in.N + row * H + 4 * half;
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (32 * t + 8 * q + 4 * half >= H) continue;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(np + 32 * t + 8 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[t][4 * q + e] = v[e];
+      }
+  }
+
+  while (sb < segs) {
+    int nsb = sb, nj = j, nn = n;
+    advance(stride, nsb, nj, nn);
+    store();
+    if (nsb < segs) {                              // the next slab
+      if (PLAIN && seldom(nsb != sb)) load_from(nsb);
+      load(nsb, nj);
+    }
+    const int k0 = j * SB + (CYCLIC && sb > shift_from);
+    f32x16 s = zero16();
+#pragma unroll
+    for (int x = 0; x < KS; ++x) s = mma(lds_load_b128(k_rd + 32 * x), qf[x], s);
+    if (k0 + SB > nfull) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (k0 + 8 * (r >> 2) + 4 * half + (r & 3) >= my_vis) s[r] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    m_lane = fmaxf(m_lane, mx);
+    if (__builtin_amdgcn_ballot_w64((m_lane - m_ref) * c > kRescaleThreshold) != 0) {
+      asm volatile("" ::: "memory");               // (a real branch, as in fwd_block)
+      const float m_row = fmaxf(m_lane, __shfl_xor(m_lane, 32, 64));
+      const float m_use = (m_row == -INFINITY) ? 0.f : m_row;
+      const float alpha = fast_exp2((m_ref - m_use) * c);
+      m_ref = m_row;
+      l_run *= alpha;
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
+    }
+    const float mc = (m_ref == -INFINITY) ? 0.f : m_ref * c;
+    float psum = 0.f;
+    bf16x8 pb[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float p = fast_exp2(fmaf(s[r], c, -mc));
+      psum += p;
+      pb[r >> 3][r & 7] = (bf16_t)p;
+    }
+    l_run += psum;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int t = 0; t < CT; ++t) {
+        const unsigned at = v_rd + 16 * u * VLD + 64 * t;
+        o[t] = mma(lds_load_tr(at, at + 8 * VLD), pb[u], o[t]);
+      }
+    if (!CYCLIC && nsb != sb && nsb < segs) enter_segment(nsb);
+    sb = nsb; j = nj; n = nn;
+  }
+
+  // ---- the wavefronts' (N, m, l) become one, as partials of one query block do (Alg. 2)
+  const float m_row = fmaxf(m_lane, __shfl_xor(m_lane, 32, 64));
+  const float f = (m_row == -INFINITY) ? 0.f : fast_exp2((m_ref - m_row) * c);
+  const float l_row = (l_run + __shfl_xor(l_run, 32, 64)) * f;
+  float* const xm = reinterpret_cast<float*>(lds + STAT) + l32;
+  float* const xl = xm + LANES * 32;
+  if (half == 0) {
+    xm[kl * 32] = m_row;
+    xl[kl * 32] = l_row;
+  }
+  __syncthreads();
+  float m_new = xm[0];
+#pragma unroll
+  for (int k = 1; k < LANES; ++k) m_new = fmaxf(m_new, xm[k * 32]);
+  float l_tot = 0.f;
+#pragma unroll
+  for (int k = 0; k < LANES; ++k)
+    l_tot += xm[k * 32] == -INFINITY ? 0.f : xl[k * 32] * fast_exp2((xm[k * 32] - m_new) * c);
+  const float a = (m_row == -INFINITY) ? 0.f : f * fast_exp2((m_row - m_new) * c);
+  const bool norm = g.norm != 0, ok = q_row < d.nq;
+  const int64_t row = GRID && norm ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, q_row)
+                                   : (int64_t)head * d.nq + q_row;
+  const int64_t o_at = GRID && norm ? head * d.lo.head + row_blk * g.b.o + q_row * d.lo.row : row * H;
+  if (kl == 0 && half == 0 && ok) {
+    if (norm) m_out[row] = l_tot > 0.f ? m_new * d.scale + logf(l_tot) : -INFINITY;
+    else {
+      m_out[row] = m_new * d.scale;                // -inf stays -inf (scale > 0)
+      l_out[row] = l_tot;
+    }
+  }
+  // Two column tiles at a time: every wavefront leaves its pieces of four columns, [wavefront][piece][lane], and
+  // adds up and stores one of the eight.
+  f32x4* const x = reinterpret_cast<f32x4*>(lds);
+  const float fn = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+#pragma unroll
+  for (int t0 = 0; t0 < CT; t0 += 2) {
+    if (t0 > 0) __syncthreads();
+#pragma unroll
+    for (int t = t0; t < t0 + 2 && t < CT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        x[(kl * 8 + (t - t0) * 4 + q) * 64 + lane] = f32x4{o[t][4 * q] * a, o[t][4 * q + 1] * a, o[t][4 * q + 2] * a, o[t][4 * q + 3] * a};
+    __syncthreads();
+    const int col = 32 * (t0 + (kl >> 2)) + 8 * (kl & 3) + 4 * half;
+    if (t0 + (kl >> 2) < CT && col < H && ok) {
+      f32x4 v = x[kl * 64 + lane];
+#pragma unroll
+      for (int k = 1; k < LANES; ++k) {
+        const f32x4 w = x[(k * 8 + kl) * 64 + lane];
+        v[0] += w[0]; v[1] += w[1]; v[2] += w[2]; v[3] += w[3];
+      }
+      if (norm) {
+        bf16x4 b;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b[e] = (bf16_t)(v[e] * fn);
+        *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(O_part) + o_at + col) = b;
+      } else {
+        *reinterpret_cast<f32x4*>(O_part + o_at + col) = v;
+      }
+    }
+  }
+}
+
+template <int HR, int GRID>
+hipError_t go(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+              float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
+  if (ph == PREPARE) return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_small_kernel<HR, GRID>), LDS_BYTES);
+  const dim3 grid(xcd_grid(d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * ((d.nq + 31) / 32)));
+  A2D_LAUNCH((fwd_small_kernel<HR, GRID>), grid, dim3(64 * LANES), LDS_BYTES, s, d, g, (const bf16_t*)Q,
+             (const bf16_t*)K, (const bf16_t*)V, O_part, m, l, in);
+  return hipGetLastError();
+}
+template <int GRID>
+hipError_t go_h(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
+                float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
+  switch (d.hdim) {
+    case 128: return go<128, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s);
+    case 96: return go<96, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s);
+    case 80: return go<80, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s);
+    default: return go<64, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s);
+  }
+}
+
+}  // namespace
+
+hipError_t launch_fwd_small(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
+                            const void* V, float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
+  return g.b.side == 0 ? go_h<0>(ph, d, g, Q, K, V, O_part, m, l, in, s)
+         : g.b.cyclic  ? go_h<2>(ph, d, g, Q, K, V, O_part, m, l, in, s)
+                       : go_h<1>(ph, d, g, Q, K, V, O_part, m, l, in, s);
+}
+
+}  // namespace a2d
