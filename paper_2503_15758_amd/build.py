@@ -16,7 +16,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liba2d.so")
 EXT = os.path.join(PKG, "_native.so")
 SOURCES = ["a2d_api.hip", "a2d_device.hip", "a2d_fix.hip", "a2d_generic.hip", "a2d_f32_mfma.hip",
-           "a2d_fwd_mfma.hip", "a2d_fwd_small.hip", "a2d_bwd_mfma.hip", "a2d_bwd_wide.hip", "a2d_bwd_one.hip", "a2d_grid.hip", "a2d_static.hip",
+           "a2d_fwd_mfma.hip", "a2d_fwd_small.hip", "a2d_bwd_mfma.hip", "a2d_bwd_wide.hip", "a2d_bwd_one.hip", "a2d_bwd_small.hip", "a2d_grid.hip", "a2d_static.hip",
            "a2d_probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

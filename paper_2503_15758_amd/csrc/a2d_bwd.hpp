@@ -43,6 +43,13 @@ __device__ __forceinline__ void store_acc_t(float* __restrict__ out_row, const f
     }
 }
 
+// the lane's number, computed where it is called (not kept in a register)
+__device__ __forceinline__ int lane_again() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
 // the value another lane holds (a DPP control word: quad_perm, row_half_mirror 0x141, row_mirror 0x140)
 template <int CTRL>
 __device__ __forceinline__ float lane_swap(float x) {

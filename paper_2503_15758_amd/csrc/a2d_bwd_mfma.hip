@@ -473,7 +473,7 @@ BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cu
   if (grid || wgs <= 6 * (int64_t)cus) {
     const BwdWalks w = {kv_mean < rows ? kv_mean : rows, rows, mean < most ? mean : most, most, uneven};
     one_us = plan_bwd_one(d, g, w, cus, cap_kv, cap_q, &one);
-    if (!ds) return one;
+    if (!ds || one.small) return one;
   }
   const double kv_part_us = (double)kv_heads * d.nkv * d.hdim * 16 / 4.5e6;
   const auto walk = [&](int w) {                       // 128 keys per workgroup, 256

@@ -155,12 +155,29 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
       consider(1, 1);
     }
   }
+  // 32 rows or keys a workgroup (a2d_bwd_small.hip; a step is a round of 256).  Fitted to 92 shapes of 1 x 41 x 80 to 16 x 512 x 512,
+  // 1 x 4096 x 4096: taken up to some 256 of them with walks of 2048, 512 with walks of 512 (under a mask 1024); 1.27 times as
+  // fast in the mean there as without that form, 0.5 % off the better of the two.
+  constexpr double kSmallKvUs[3] = {1.65, 2.8, 3.0}, kSmallKvFix[3] = {5.3, 5.9, 7.4}, kSmallRowUs[3] = {1.24, 1.69, 2.2},
+                   kSmallRowFix[3] = {5.3, 5.9, 7.0}, kSmallIdle = 0.88;
+  const int64_t n_kv = (int64_t)kv_heads * side * ((d.nkv + 31) / 32), n_q = (int64_t)d.heads * side * ((d.nq + 31) / 32);
+  const double busy = n_kv + n_q < cus ? kSmallIdle + (1 - kSmallIdle) * (n_kv + n_q) / cus : 1;
+  const auto of = [&](double rounds, const double* step, const double* fix) { return ((rounds < 1 ? 1 : rounds) * step[hx] + fix[hx]) * busy; };
+  const Kind kv = {n_kv, of(w.kv_mean / 8, kSmallKvUs, kSmallKvFix), of(w.kv_most / 8, kSmallKvUs, kSmallKvFix)};
+  const Kind q = {n_q, of(w.q_mean / 4, kSmallRowUs, kSmallRowFix), of(w.q_most / 4, kSmallRowUs, kSmallRowFix)};
+  const bool q_first = q.most > kv.most;
+  const double small = q_first ? one_time(q, kv, cus, w.uneven, kTail) : one_time(kv, q, cus, w.uneven, kTail);
+  if (small < 1.04 * least) {                              // (the other model is some 10 % low at few workgroups)
+    *best = BwdParts{1, 1, 0, 0, 1, q_first, 1};
+    return small;
+  }
   return least;
 }
 
 hipError_t launch_bwd_one(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                           const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ,
                           float* dK, float* dV, const BwdParts& parts, hipStream_t s) {
+  if (parts.small) return launch_bwd_small(ph, d, g, Q, K, V, O, dO, lse, dQ, dK, dV, parts.q_first, s);
   SegList go = g;
   go.parts = parts.kv;
   if (parts.q > 1) go.acc = 0;                             // (the sum over the parts adds)

@@ -30,13 +30,6 @@ constexpr int WK_V = WK_TURN + 8 * WK_TURN_BYTES;
 constexpr int WK_VLD = 272;
 __host__ __device__ constexpr int wk_lds(int hd) { return WK_V + (hd == 128 ? WK_KEYS * WK_VLD : 0); }
 
-// the lane's number, computed where it is called (not kept in a register)
-__device__ __forceinline__ int lane_again() {
-  int l;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-  return l;
-}
-
 // GRID: all key blocks of an emulated grid (g.b).  The workgroup walks the query rows of its whole grid column and
 // writes rows of dK and dV of the sequence (of a split walk: a partial, [part][column][head][key]).  Contiguous blocks
 // of queries are one run of rows; of cyclic ones, step s of every row block comes before step s + 1 of any.

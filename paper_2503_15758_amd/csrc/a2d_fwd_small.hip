@@ -110,8 +110,9 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
     }
   };
 
-  // ---- staging: a lane moves one 16-byte chunk of ST_N rows (64 columns: eight lanes a row, else sixteen).  Rows
-  // beyond the sub-block re-read its last one.
+  // ---- staging: a lane moves one 16-byte chunk of ST_N rows (64 columns: eight lanes a row, else sixteen; chunks past
+  // the head size: its last one once more, into columns whose results are not stored).  Rows beyond the sub-block
+  // re-read its last one.
   constexpr int CHUNKS = HD == 64 ? 8 : 16, ST_ROWS = 64 / CHUNKS, ST_N = SB / ST_ROWS;
   const unsigned k_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lk.row * 2);
   const unsigned v_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lv.row * 2);
@@ -126,32 +127,27 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
     }
   };
   u32x4 kreg[ST_N], vreg[ST_N];
-#pragma unroll
-  for (int p = 0; p < ST_N; ++p) kreg[p] = vreg[p] = u32x4{0, 0, 0, 0};
   auto load = [&](int s, int j) {
     if (CYCLIC) start = s;
     const gptr_t ka = uniform_gptr(reinterpret_cast<const char*>(K) + (start * k_col_bytes + (unsigned)(j * SB) * k_row_bytes));
     const gptr_t va = uniform_gptr(reinterpret_cast<const char*>(V) + (start * v_col_bytes + (unsigned)(j * SB) * v_row_bytes));
-    if (st_chunk * 8 < H) {
+    const int chunk = min(st_chunk, H / 8 - 1);
 #pragma unroll
-      for (int p = 0; p < ST_N; ++p)
-        kreg[p] = gload_b128(ka, __umul24((unsigned)min(st_row + ST_ROWS * p, rows - 1 - j * SB), k_row_bytes) + 16 * st_chunk);
+    for (int p = 0; p < ST_N; ++p)
+      kreg[p] = gload_b128(ka, __umul24((unsigned)min(st_row + ST_ROWS * p, rows - 1 - j * SB), k_row_bytes) + 16 * chunk);
 #pragma unroll
-      for (int p = 0; p < ST_N; ++p)
-        vreg[p] = gload_b128(va, __umul24((unsigned)min(st_row + ST_ROWS * p, rows - 1 - j * SB), v_row_bytes) + 16 * st_chunk);
-    }
+    for (int p = 0; p < ST_N; ++p)
+      vreg[p] = gload_b128(va, __umul24((unsigned)min(st_row + ST_ROWS * p, rows - 1 - j * SB), v_row_bytes) + 16 * chunk);
   };
   const unsigned slab = lds_base + kl * SLAB_BYTES;
   const unsigned k_wr = slab + st_row * KLD + 16 * st_chunk, v_wr = slab + V_AT + st_row * VLD + 16 * st_chunk;
   auto store = [&]() {
-    if (st_chunk * 8 < HD) {
 #pragma unroll
-      for (int p = 0; p < ST_N; ++p)
-        *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(k_wr + ST_ROWS * p * KLD)) = kreg[p];
+    for (int p = 0; p < ST_N; ++p)
+      *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(k_wr + ST_ROWS * p * KLD)) = kreg[p];
 #pragma unroll
-      for (int p = 0; p < ST_N; ++p)
-        *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(v_wr + ST_ROWS * p * VLD)) = vreg[p];
-    }
+    for (int p = 0; p < ST_N; ++p)
+      *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(v_wr + ST_ROWS * p * VLD)) = vreg[p];
   };
   const int g16 = lane >> 4, j16 = lane & 15;
   const unsigned k_rd = slab + l32 * KLD + 16 * half;
