@@ -68,31 +68,6 @@ hipError_t go_h(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* 
 
 }  // namespace
 
-namespace {
-// The time of `a.n` workgroups, the ones that walk longer, followed by `b.n` others over the slots of the chip
-struct Kind {
-  int64_t n;
-  double mean, most;         // us of a workgroup, on average and at most
-};
-double one_time(const Kind& a, const Kind& b, int slots, bool uneven, double tail) {
-  if (a.n + b.n <= slots) return a.most;
-  if (uneven) {                                            // longest first
-    const double even = (a.n * a.mean + b.n * b.mean) / slots + tail * b.mean;
-    return even > a.most ? even : a.most;
-  }
-  // whole turns of the first kind; then the slots it leaves free in its last turn, and the others, take the second
-  const int64_t rest = a.n % slots, free = slots - rest;
-  double u = (double)(a.n / slots) * a.most, v = rest ? u + a.most : u, end = v;
-  for (int64_t left = b.n; left > 0;) {
-    double& t = u <= v || !rest ? u : v;
-    left -= &t == &u ? free : rest;
-    t += b.most;
-    if (t > end) end = t;
-  }
-  return end;
-}
-}  // namespace
-
 // Workgroup shapes and parts of a tile or grid whose backward goes out in one launch: the ones with the least time in a
 // model of the launch, fitted to 60 shapes x up to 100 choices each (1 x 161 x 308 to 32 x 4096 x 4096, grids of 350
 // to 8192 tokens); its choice is 1 % off the best of them in the mean.  Parts of the two kinds are tried in step: of one from a

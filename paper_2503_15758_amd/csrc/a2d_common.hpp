@@ -207,6 +207,12 @@ inline double walk_time(const WalkModel& w, int parts) {
 // the best number of parts up to `cap` (ties: the smaller); a split costs merge_us, a launch behind the
 // tile kernel, and part_us per part to write and read back
 int best_parts(const WalkModel& w, int cap, double merge_us, double part_us, double* time);
+// The time of `a.n` workgroups, the ones that walk longer, followed by `b.n` others over the slots of the chip
+struct Kind {
+  int64_t n;
+  double mean, most;         // us of a workgroup, on average and at most
+};
+double one_time(const Kind& a, const Kind& b, int slots, bool uneven, double tail);
 // keys that query row i of the tile sees
 int64_t visible_keys(const a2d_tile_desc& d, const SegList& g, int64_t i);
 // of 8 rows spread over the tile, last rows first; returns the mean

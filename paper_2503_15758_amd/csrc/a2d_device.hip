@@ -116,6 +116,24 @@ int best_parts(const WalkModel& w, int cap, double merge_us, double part_us, dou
   return best;
 }
 
+double one_time(const Kind& a, const Kind& b, int slots, bool uneven, double tail) {
+  if (a.n + b.n <= slots) return a.most;
+  if (uneven) {                                            // longest first
+    const double even = (a.n * a.mean + b.n * b.mean) / slots + tail * b.mean;
+    return even > a.most ? even : a.most;
+  }
+  // whole turns of the first kind; then the slots it leaves free in its last turn, and the others, take the second
+  const int64_t rest = a.n % slots, free = slots - rest;
+  double u = (double)(a.n / slots) * a.most, v = rest ? u + a.most : u, end = v;
+  for (int64_t left = b.n; left > 0;) {
+    double& t = u <= v || !rest ? u : v;
+    left -= &t == &u ? free : rest;
+    t += b.most;
+    if (t > end) end = t;
+  }
+  return end;
+}
+
 double mean_visible_keys(const a2d_tile_desc& d, const SegList& g, double seen[8]) {
   double mean = 0;
   for (int i = 0; i < 8; ++i) {

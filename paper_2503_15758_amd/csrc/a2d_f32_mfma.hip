@@ -34,6 +34,8 @@
 // Measured against the vector-ALU kernels of a2d_generic.hip: 16 heads x 700 x 900, H = 96, causal,
 // backward call 1034 -> 100 us; 2 heads x 128 x 128, H = 64, forward 29 -> 5.2 us; 16 heads x 4096 x 4096, H = 128: forward
 // 1.07 ms (129 TFLOP/s, 82 % of the fp32 matrix peak), backward 3.87 ms (124 TFLOP/s executed).
+#include <cmath>
+
 #include "a2d_bwd.hpp"
 
 namespace a2d {
@@ -748,10 +750,17 @@ hipError_t bwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const 
                                                      : bwd_go<H, true>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s);
 }
 
-// The walk of 16-row blocks as a model: a turn is one wavefront per SIMD, a step of `contractions`
-// contractions over H takes 8 H cycles each (at about 2.1 GHz).
-WalkModel f32_walk(int64_t blocks, double steps, int contractions, int hdim, int cus) {
-  return WalkModel{blocks, cus, steps / KL, steps / KL, contractions * hdim * 8 / 2.1e3, 4.0, 0, 0, nullptr, 0};
+// Numbers of parts that are tried, and what they cost beside the walks: a launch behind the tile's
+constexpr int kParts[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+constexpr double kSumUs = 5.0, kPartUs = 0.2;
+// H = 64, 80, 96, 128
+int head_index(int hdim) { return hdim > 96 ? 3 : hdim > 80 ? 2 : hdim > 64 ? 1 : 0; }
+// A workgroup of KL wavefronts that walks `steps` steps in `parts` parts, whole steps at the most, some half a step more than
+// their share in the mean of an uneven walk
+Kind f32_kind(int64_t blocks, double mean, double most, int parts, bool uneven, double step, double fixed) {
+  const auto whole = [](double n) { return n <= 1 ? 1.0 : std::ceil(n - 1e-9); };
+  const double z = (double)KL * parts, m = uneven ? mean / z + 0.4 : whole(mean / z);
+  return Kind{blocks * parts, (m < 1 ? 1 : m) * step + fixed, whole(most / z) * step + fixed};
 }
 
 }  // namespace
@@ -763,19 +772,51 @@ void plan_fwd_f32(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   g->parts = 1;
   g->form = b32 >= 4 * (int64_t)cus ? F32_ROWS32 : F32_ROWS16;
   if (g->form == F32_ROWS32) return;
-  const double steps = (double)visible_keys(d, *g, d.nq - 1) / BLK + 1;
-  const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 5e6;
-  g->parts = best_parts(f32_walk(b16, steps, 2, d.hdim, cus), cap, 5.0, part_us, nullptr);
+  // (fitted, as plan_bwd_f32, to 39 shapes of 1 x 64 x 64 to 16 x 1024 x 1024 x up to 6 (36) numbers of parts: 2 % (6 %) off the best of
+  // them in the mean, where steps as long as their matrix instructions were 5 % (12 %) off - a step of a chip that is
+  // not full waits for its loads.  2 x 300 x 900, H = 64 15.0 -> 10.7 us)
+  constexpr double kStep[4] = {0.93, 1.11, 1.49, 1.99}, kFixed = 2.4;
+  double of_rows[8];
+  const double most = (double)visible_keys(d, *g, d.nq - 1) / BLK;
+  const double mean = g->by_size ? mean_visible_keys(d, *g, of_rows) / BLK : most;
+  const double part_us = (double)d.heads * d.nq * (d.hdim + 2) * 8 / 4.6e6;
+  double whole = 0, least = 0;
+  for (int z : kParts) {
+    if (z > 1 && (z > cap || z > most + 1)) break;
+    const Kind k = f32_kind(b16, mean, most, z, g->by_size != 0, kStep[head_index(d.hdim)], kFixed);
+    const double t = one_time(k, Kind{0, 0, 0}, 2 * cus, g->by_size != 0, 0.5) + (z > 1 ? kSumUs + z * (part_us + 1.5 * kPartUs) : 0);
+    if (z == 1) whole = least = t;
+    else if (t < 0.85 * whole && t < least) { least = t; g->parts = z; }      // (a split has to be clearly better)
+  }
 }
 
 BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q) {
   const int64_t bq = (int64_t)d.heads * ((d.nq + 15) / 16), bk = (int64_t)(d.heads / g.group) * ((d.nkv + 15) / 16);
   const double sq = (double)visible_keys(d, g, d.nq - 1) / BLK + 1, sk = (double)g.group * ((d.nq + 15) / 16);
+  constexpr double kRow[4] = {0.95, 1.21, 1.87, 2.88}, kRowFixed = 3.6, kKey[4] = {1.69, 2.06, 3.05, 4.28}, kKeyFixed = 1.7;
+  const int hx = head_index(d.hdim);
+  const bool uneven = g.by_size != 0;
+  double seen[8];
+  const double q_most = (double)visible_keys(d, g, d.nq - 1) / BLK;
+  const double mean = uneven ? mean_visible_keys(d, g, seen) : q_most * BLK;
+  const double part_kv = (double)d.heads / g.group * d.nkv * d.hdim * 16 / 4.9e6, part_q = (double)d.heads * d.nq * d.hdim * 8 / 4.9e6;
   BwdParts p = {};
-  p.kv = best_parts(f32_walk(bk, sk, 4, d.hdim, cus), cap_kv, 5.0,
-                    (double)d.heads / g.group * d.nkv * d.hdim * 16 / 5e6, nullptr);
-  p.q = best_parts(f32_walk(bq, sq, 3, d.hdim, cus), cap_q, p.kv > 1 ? 1.0 : 5.0,
-                   (double)d.heads * d.nq * d.hdim * 8 / 5e6, nullptr);
+  p.kv = p.q = 1;
+  double whole = 0, least = 0;
+  for (int zk : kParts) {
+    if (bq + bk > 16 * (int64_t)cus) break;          // (a chip that is full for many turns)
+    if (zk > 1 && (zk > cap_kv || zk > sk)) break;
+    for (int zq : kParts) {
+      if (zq > 1 && (zq > cap_q || zq > sq)) break;
+      const double share = (double)(bq * zq + bk * zk) / cus, busy = share > 2 ? 1.14 : share > 1.75 ? 0.57 * share : 1;
+      const Kind q = f32_kind(bq, mean / BLK, q_most, zq, uneven, kRow[hx] * busy, kRowFixed);
+      const Kind k = f32_kind(bk, uneven ? sk * mean / d.nkv : sk, sk, zk, uneven, kKey[hx] * busy, kKeyFixed);
+      const double t = (q.most > k.most ? one_time(q, k, 2 * cus, uneven, 0.86) : one_time(k, q, 2 * cus, uneven, 0.86)) +
+                       (zk > 1 || zq > 1 ? kSumUs : 0) + (zk > 1 ? zk * (part_kv + kPartUs) : 0) + (zq > 1 ? zq * (part_q + kPartUs) : 0);
+      if (zk == 1 && zq == 1) whole = least = t;
+      else if (t < 0.87 * whole && t < least) { least = t; p.kv = zk; p.q = zq; }
+    }
+  }
   // the kind with the longer walks first; under a mask the longest and the shortest count alike, so that short ones come
   // last (16 x 700 x 900: dQ first 100 us, dK/dV first 104; 16 x 1024 x 1024, H = 64, causal 90 / 83)
   double lq = sq, lk = sk, of_rows[8];
