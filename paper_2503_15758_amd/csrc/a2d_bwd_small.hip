@@ -54,11 +54,14 @@ __device__ __forceinline__ void small_rows(
   const int nb = ((KV ? d.nkv : d.nq) + 31) / 32, group = g.group;
   int kvh, blk, head;
   if (!xcd_map(id, d.heads / group, sides * (KV ? 1 : group) * nb, by_size != 0, kvh, blk, KV ? 0 : kXcdCus)) return;
-  if constexpr (KV) {
+  head = kvh;                                      // (no divisions by one: they delay the first loads)
+  if (group > 1) {
     head = kvh * group;
-  } else {
-    head = kvh * group + (GRID || by_size ? blk % group : blk / nb);
-    blk = GRID || by_size ? blk / group : blk % nb;
+    if constexpr (!KV) {
+      const int by = GRID || by_size ? group : nb, q = blk / by, r = blk - q * by;
+      head += GRID || by_size ? r : q;
+      blk = GRID || by_size ? q : r;
+    }
   }
   int place = 0;
   if constexpr (GRID != 0) {
@@ -115,23 +118,31 @@ __device__ __forceinline__ void small_rows(
   // ---- the walk: entry e, e + LANES, .. of (sub-block, slab) as in fwd_small_kernel (dQ), or of (query head, slab, row block)
   const int nq = GRID == 1 ? sides * d.nq : d.nq, head_rows = nq * side;
   const int key_rows = GRID == 1 ? sides * d.nkv : d.nkv;
-  int sb = 0, j = 0, n = 0, start = 0, rows = key_rows, nfull = 0, my_vis = 0;      // dQ
+  int sb = 0, j = 0, n = 0, start = 0, rows = key_rows, nfull = 0, my_vis = 0;      // dQ: as in fwd_small_kernel
+  int64_t rel = 0;
   const int segs = PLAIN ? g.n : side, shift_from = CYCLIC && d.causal ? place : segs;
   const int last_row = min(r0 + 31, d.nq - 1);
-  auto vis_count = [&](int i, int s) -> int {
-    if (GRID == 1) return d.causal ? place * d.nq + i + 1 : key_rows;
-    if (GRID == 2) return d.causal ? i + 1 : d.nkv;
-    if (!d.causal) return g.seg[s].rows;
-    const int64_t v = (int64_t)i + g.seg[s].rel + 1;
-    return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
+  auto vis_count = [&](int i) -> int {
+    if (GRID == 1) return d.causal ? place * d.nq + i + 1 : rows;
+    if (GRID == 2) return d.causal ? i + 1 : rows;
+    if (!d.causal) return rows;
+    const int64_t v = (int64_t)i + rel + 1;
+    return v <= 0 ? 0 : (v < rows ? (int)v : rows);
   };
-  auto enter_segment = [&](int s) {
-    nfull = vis_count(r0, s);
-    my_vis = vis_count(row_ld, s);
+  auto enter_segment = [&]() {
+    nfull = vis_count(r0);
+    my_vis = vis_count(row_ld);
   };
   auto open_segment = [&](int s) {
-    n = 0;
-    while (s < segs && (n = (vis_count(last_row, s) + 31) / 32) == 0) ++s;
+    for (n = 0; s < segs; ++s) {
+      if (PLAIN) {
+        start = g.seg[s].start;
+        rows = g.seg[s].rows;
+        rel = g.seg[s].rel;
+      }
+      n = (vis_count(last_row) + 31) / 32;
+      if (n > 0) break;
+    }
     sb = s;
   };
   auto advance = [&](int by) {
@@ -166,8 +177,8 @@ __device__ __forceinline__ void small_rows(
   int i_start = 0, w_all = 0, nsteps = 0, total = 0, my_first = nq;
   int e = kl, eh = 0, es = 0, er = 0;              // this entry, its query head of the group, slab, row block
   auto locate = [&]() {
-    eh = e / (nsteps * side);
-    es = e - eh * (nsteps * side);
+    eh = group > 1 ? e / (nsteps * side) : 0;
+    es = group > 1 ? e - eh * (nsteps * side) : e;
     if constexpr (CYCLIC) {
       er = es % side;
       es /= side;
@@ -202,7 +213,7 @@ __device__ __forceinline__ void small_rows(
   } else {
     open_segment(0);
     if (sb < segs) advance(kl);
-    if (sb < segs) enter_segment(sb);
+    if (sb < segs) enter_segment();
   }
   float stat = 0.f;                                // lse of query l32 of the slab (dK / dV)
   const float* lse_at = lse + (int64_t)head * (GRID ? sides : 1) * d.nq;
@@ -214,12 +225,7 @@ __device__ __forceinline__ void small_rows(
       const int i = min(i0 + l32, nq - 1);
       stat = lse_at[eh * head_rows + (CYCLIC ? i * side + er : i)];
     } else {
-      if (PLAIN) {
-        start = g.seg[sb].start;
-        rows = g.seg[sb].rows;
-      } else if (CYCLIC) {
-        start = sb;
-      }
+      if (CYCLIC) start = sb;
       load(xr, x_base, start * x_blk, x_row, 32 * j, rows - 1);
     }
   };
@@ -382,7 +388,7 @@ __device__ __forceinline__ void small_rows(
       ld(std::integral_constant<int, i + 2>{});
       __builtin_amdgcn_sched_barrier(0);
     });
-    if (!KV && !CYCLIC && sb != sb_now && sb < segs) enter_segment(sb);
+    if (!KV && !CYCLIC && sb != sb_now && sb < segs) enter_segment();
   }
 
   // ---- the wavefronts' sums: pieces of four columns, [wavefront][piece][lane]; each adds up and stores two of the sixteen

@@ -24,7 +24,7 @@ constexpr int KLD = 272, VLD = 320, V_AT = SB * KLD, SLAB_BYTES = SB * (KLD + VL
 constexpr int STAT = LANES * SLAB_BYTES;
 constexpr int LDS_BYTES = STAT + 2 * LANES * SB * 4;
 constexpr float kRescaleThreshold = 8.0f;          // log2 units
-static_assert(LANES * 8 * 1024 <= STAT, "the pieces of two column tiles must fit the slabs");
+static_assert(LANES * 16 * 1024 <= STAT, "the pieces of four column tiles must fit the slabs");
 
 // (template parameter, arguments and outputs as of fwd_mfma_kernel)
 template <int HR, int GRID>
@@ -44,9 +44,18 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
   const int by_size = GRID ? d.causal : g.by_size;
   if (!xcd_map(blockIdx.x, d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * nqb, by_size != 0, unit, blk,
                kXcdCus)) return;
-  const int kvh = unit / g.parts, part = unit - kvh * g.parts;
-  const int head = kvh * g.group + (GRID || by_size ? blk % g.group : blk / nqb);
-  blk = GRID || by_size ? blk / g.group : blk % nqb;
+  // (divisions are a good part of the way to the first load: none by one)
+  int kvh = unit, part = 0, head = unit;
+  if (g.parts > 1) {
+    kvh = unit / g.parts;
+    part = unit - kvh * g.parts;
+    head = kvh;
+  }
+  if (g.group > 1) {
+    const int by = GRID || by_size ? g.group : nqb, q = blk / by, r = blk - q * by;
+    head = kvh * g.group + (GRID || by_size ? r : q);
+    blk = GRID || by_size ? q : r;
+  }
   const GridBlock gb = GRID ? grid_block(g.b, nqb, blk) : GridBlock{0, blk};
   const int row_blk = gb.r;                        // of the grid
   blk = gb.blk;
@@ -72,25 +81,34 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
   const float c = d.scale * kLog2e;
 
   // ---- visibility and the walk over (sub-block, slab), as in fwd_mfma_kernel
-  auto vis_count = [&](int i, int s) -> int {
-    if (GRID == 1) return d.causal ? row_blk * d.nq + i + 1 : g.b.side * d.nkv;
-    if (GRID == 2) return d.causal ? i + 1 : d.nkv;
-    if (!d.causal) return g.seg[s].rows;
-    const int64_t v = (int64_t)i + g.seg[s].rel + 1;
-    return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
-  };
   const int last_row = min(q0 + 31, d.nq - 1);
   const int segs = PLAIN ? g.n : CYCLIC ? g.b.side : 1, stride = LANES * g.parts;
-  const int grid_rows = GRID == 1 ? g.b.side * d.nkv : d.nkv;
   const int shift_from = CYCLIC && d.causal ? row_blk : segs;
-  int nfull = 0, my_vis = 0;                       // of the current sub-block: keys all rows see, the lane's row
-  auto enter_segment = [&](int s) {
-    nfull = vis_count(q0, s);
-    my_vis = vis_count(q_ld, s);
+  // the sub-block to be loaded from (cyclic: start is the grid's column); the keys of it that row i sees
+  int start = 0, rows = GRID == 1 ? g.b.side * d.nkv : d.nkv;
+  int64_t rel = 0;
+  auto vis_count = [&](int i) -> int {
+    if (GRID == 1) return d.causal ? row_blk * d.nq + i + 1 : rows;
+    if (GRID == 2) return d.causal ? i + 1 : rows;
+    if (!d.causal) return rows;
+    const int64_t v = (int64_t)i + rel + 1;
+    return v <= 0 ? 0 : (v < rows ? (int)v : rows);
+  };
+  int nfull = 0, my_vis = 0;                       // keys of the current sub-block that all rows see, the lane's row
+  auto enter_segment = [&]() {
+    nfull = vis_count(q0);
+    my_vis = vis_count(q_ld);
   };
   auto open_segment = [&](int s, int& sb, int& n) {
-    n = 0;
-    while (s < segs && (n = (vis_count(last_row, s) + SB - 1) / SB) == 0) ++s;
+    for (n = 0; s < segs; ++s) {
+      if (PLAIN) {
+        start = g.seg[s].start;
+        rows = g.seg[s].rows;
+        rel = g.seg[s].rel;
+      }
+      n = (vis_count(last_row) + SB - 1) / SB;
+      if (n > 0) break;
+    }
     sb = s;
   };
   auto advance = [&](int by, int& sb, int& j, int& n) {
@@ -119,13 +137,6 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
   const unsigned k_col_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.k * 2)) : k_row_bytes;
   const unsigned v_col_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.v * 2)) : v_row_bytes;
   const int st_row = lane / CHUNKS, st_chunk = lane % CHUNKS;
-  int start = 0, rows = grid_rows;                 // of the sub-block to be loaded from (cyclic: the grid's column)
-  auto load_from = [&](int s) {
-    if (PLAIN) {
-      start = g.seg[s].start;
-      rows = g.seg[s].rows;
-    }
-  };
   u32x4 kreg[ST_N], vreg[ST_N];
   auto load = [&](int s, int j) {
     if (CYCLIC) start = s;
@@ -157,9 +168,8 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
   open_segment(0, sb, n);
   if (sb < segs) advance(part * LANES + kl, sb, j, n);
   if (sb < segs) {
-    enter_segment(sb);
-    load_from(sb);
     load(sb, j);
+    enter_segment();
   }
 
   f32x16 o[CT];
@@ -187,10 +197,7 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
     int nsb = sb, nj = j, nn = n;
     advance(stride, nsb, nj, nn);
     store();
-    if (nsb < segs) {                              // the next slab
-      if (PLAIN && seldom(nsb != sb)) load_from(nsb);
-      load(nsb, nj);
-    }
+    if (nsb < segs) load(nsb, nj);                 // the next slab
     const int k0 = j * SB + (CYCLIC && sb > shift_from);
     f32x16 s = zero16();
 #pragma unroll
@@ -233,7 +240,7 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
         const unsigned at = v_rd + 16 * u * VLD + 64 * t;
         o[t] = mma(lds_load_tr(at, at + 8 * VLD), pb[u], o[t]);
       }
-    if (!CYCLIC && nsb != sb && nsb < segs) enter_segment(nsb);
+    if (!CYCLIC && nsb != sb && nsb < segs) enter_segment();
     sb = nsb; j = nj; n = nn;
   }
 
@@ -248,14 +255,18 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
     xl[kl * 32] = l_row;
   }
   __syncthreads();
-  float m_new = xm[0];
+  float mk[LANES], lk[LANES], m_new = -INFINITY;
 #pragma unroll
-  for (int k = 1; k < LANES; ++k) m_new = fmaxf(m_new, xm[k * 32]);
+  for (int k = 0; k < LANES; ++k) {
+    mk[k] = xm[k * 32];
+    lk[k] = xl[k * 32];
+    m_new = fmaxf(m_new, mk[k]);
+  }
+  const float m_use = m_new == -INFINITY ? 0.f : m_new;      // (2^-inf = 0 for the wavefronts that saw nothing)
   float l_tot = 0.f;
 #pragma unroll
-  for (int k = 0; k < LANES; ++k)
-    l_tot += xm[k * 32] == -INFINITY ? 0.f : xl[k * 32] * fast_exp2((xm[k * 32] - m_new) * c);
-  const float a = (m_row == -INFINITY) ? 0.f : f * fast_exp2((m_row - m_new) * c);
+  for (int k = 0; k < LANES; ++k) l_tot += lk[k] * fast_exp2((mk[k] - m_use) * c);
+  const float a = f * fast_exp2((m_row - m_use) * c);
   const bool norm = g.norm != 0, ok = q_row < d.nq;
   const int64_t row = GRID && norm ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, q_row)
                                    : (int64_t)head * d.nq + q_row;
@@ -267,35 +278,32 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
       l_out[row] = l_tot;
     }
   }
-  // Two column tiles at a time: every wavefront leaves its pieces of four columns, [wavefront][piece][lane], and
-  // adds up and stores one of the eight.
+  // Every wavefront leaves its pieces of four columns, [wavefront][piece][lane], and adds up and stores two of them.
   f32x4* const x = reinterpret_cast<f32x4*>(lds);
   const float fn = l_tot > 0.f ? 1.0f / l_tot : 0.f;
 #pragma unroll
-  for (int t0 = 0; t0 < CT; t0 += 2) {
-    if (t0 > 0) __syncthreads();
+  for (int t = 0; t < CT; ++t)
 #pragma unroll
-    for (int t = t0; t < t0 + 2 && t < CT; ++t)
+    for (int q = 0; q < 4; ++q)
+      x[(kl * 16 + t * 4 + q) * 64 + lane] = f32x4{o[t][4 * q] * a, o[t][4 * q + 1] * a, o[t][4 * q + 2] * a, o[t][4 * q + 3] * a};
+  __syncthreads();
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        x[(kl * 8 + (t - t0) * 4 + q) * 64 + lane] = f32x4{o[t][4 * q] * a, o[t][4 * q + 1] * a, o[t][4 * q + 2] * a, o[t][4 * q + 3] * a};
-    __syncthreads();
-    const int col = 32 * (t0 + (kl >> 2)) + 8 * (kl & 3) + 4 * half;
-    if (t0 + (kl >> 2) < CT && col < H && ok) {
-      f32x4 v = x[kl * 64 + lane];
+  for (int i = 0; i < 2; ++i) {
+    const int piece = kl + 8 * i, col = 32 * (piece >> 2) + 8 * (piece & 3) + 4 * half;
+    if (piece >= 4 * CT || col >= H || !ok) continue;
+    f32x4 v = x[piece * 64 + lane];
 #pragma unroll
-      for (int k = 1; k < LANES; ++k) {
-        const f32x4 w = x[(k * 8 + kl) * 64 + lane];
-        v[0] += w[0]; v[1] += w[1]; v[2] += w[2]; v[3] += w[3];
-      }
-      if (norm) {
-        bf16x4 b;
+    for (int k = 1; k < LANES; ++k) {
+      const f32x4 w = x[(k * 16 + piece) * 64 + lane];
+      v[0] += w[0]; v[1] += w[1]; v[2] += w[2]; v[3] += w[3];
+    }
+    if (norm) {
+      bf16x4 b;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) b[e] = (bf16_t)(v[e] * fn);
-        *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(O_part) + o_at + col) = b;
-      } else {
-        *reinterpret_cast<f32x4*>(O_part + o_at + col) = v;
-      }
+      for (int e = 0; e < 4; ++e) b[e] = (bf16_t)(v[e] * fn);
+      *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(O_part) + o_at + col) = b;
+    } else {
+      *reinterpret_cast<f32x4*>(O_part + o_at + col) = v;
     }
   }
 }
