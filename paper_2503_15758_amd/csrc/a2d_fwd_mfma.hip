@@ -44,7 +44,7 @@ __host__ __device__ constexpr int buf_bytes(int hd) { return BN * kld(hd) + BN *
 __host__ __device__ constexpr int lds_bytes(int hd) { return 2 * buf_bytes(hd); }
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
 constexpr double kStepUs[3] = {1.25, 1.45, 1.66};   // a 64-key step of a 256-row workgroup, H = 64 / 96 / 128
-constexpr double kSmallRoundUs[3] = {0.95, 1.42, 1.65}, kSmallFixedUs[3] = {3.4, 3.7, 3.2};   // 256 keys of 32 rows
+constexpr double kSmallRoundUs[3] = {0.95, 1.42, 1.65}, kSmallFixedUs[3] = {3.1, 3.5, 3.2};   // 256 keys of 32 rows
 
 template <int HD>
 struct FwdState {
@@ -537,8 +537,8 @@ hipError_t fwd_form(Phase ph, const a2d_tile_desc& d, const SegList& g, const vo
 // keys).  By model, with parts > 1 where the blocks leave compute units idle and the walk is long.  The
 // constants are a fit to 95 shapes x three forms x up to five numbers of parts (1 x 128 x 128 to 96 x 1024 x
 // 2048, H = 64 and 128), of the 32-row form to 101 shapes of few rows, H = 64 to 128: it is taken up to about 256 blocks of
-// 32 rows, 16 rounds each, and under a causal mask for up to 512; there the choice is 0.4 % slower than the best of 13 forms
-// and parts, and 1.19 times as fast in the mean as without that form.
+// 32 rows, 16 rounds each, and under a causal mask for up to 512; there the choice is 0.6 % slower than the best of 13 forms
+// and parts, and 1.24 times as fast in the mean as without that form.
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t heads = (int64_t)d.heads * (g->b.side ? g->b.side : 1);
   double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2, mean = most;
@@ -556,9 +556,15 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const double tail = g->b.side ? 0.1 : 0.5, big = g->b.side ? fixed + 1.5 : fixed;
   const int h = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0;
   const double round = kSmallRoundUs[h], small = kSmallFixedUs[h];
-  const WalkModel m[4] = {{b256, cus, mean, most, step, big, 0, 0, nullptr, 0, tail},
-                          {b128, cus, mean / 2, most / 2, step * 1.13, fixed + 0.8, 0, 0, nullptr, 0, tail},
-                          {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, fixed + 0.5, nullptr, 0, tail},
+  // (plain calls write fp32 partials, 128 KiB a workgroup of 256 rows at H = 128: those that start and end together store
+  // at the rate of the memory, two side by side on a compute unit one under the other's walk.  29 x 4679 x 359, H = 96: 49 us
+  // in 256-row workgroups, 42 in pairs)
+  const double store = g->b.side ? 0 : d.hdim / 128.0;
+  const double big_fix = big + (b256 > cus ? 4.0 * store : 0), lanes_fix = fixed + 0.8 + (b128 > cus ? 2.0 * store : 0);
+  const double pair_fix = store > 0 && b128 > 2 * cus ? 2.4 + 6.1 * store : fixed + 0.5;
+  const WalkModel m[4] = {{b256, cus, mean, most, step, big_fix, 0, 0, nullptr, 0, tail},
+                          {b128, cus, mean / 2, most / 2, step * 1.13, lanes_fix, 0, 0, nullptr, 0, tail},
+                          {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, pair_fix, nullptr, 0, tail},
                           {b32, cus, mean / 4, most / 4, round, small, 0, 0, nullptr, 0, tail, true}};
   double least = 0;
   for (int f = 0; f < 4; ++f) {
