@@ -279,8 +279,7 @@ __device__ __forceinline__ void dq_rows(
     for (int x = 0; x < 8; ++x) {
       t[x] = 0.f;
       if (x >= KS) continue;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) t[x] = fmaf((float)of[x][e], (float)cx.gf[x][e], t[x]);
+      t[x] = dot8(__builtin_bit_cast(u32x4, of[x]), __builtin_bit_cast(u32x4, cx.gf[x]), 0.f);
       t[x] += __shfl_xor(t[x], 32, 64);
     }
     cx.del = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));

@@ -4,7 +4,7 @@
 // In launches one behind the other each ends with compute units that wait for its longest walks, and a small tile pays
 // a launch and a kernel's first loads twice.  Neither kind of workgroup needs the other's result but for delta: dQ
 // workgroups compute it of their rows anyway, dK/dV workgroups in pairs of the rows they stage (OWN_DELTA: an
-// eighth more loads in a step, 30 vector instructions; a launch of delta_kernel in front costs a small tile more).
+// eighth more loads in a step, a dozen vector instructions; a launch of delta_kernel in front costs a small tile more).
 // Those of 256 keys have no registers for it at H = 128 and serve tiles where that launch costs 3 %: they read it.
 // The kind with the longer walks goes first (plan_bwd_mfma).
 #include "a2d_bwd_dq.hpp"

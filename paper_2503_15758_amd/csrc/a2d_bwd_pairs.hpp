@@ -388,10 +388,7 @@ __device__ __forceinline__ void dkdv_pairs(
     if constexpr (OWN_DELTA) {
       // this thread's 16-byte chunk of the row, then the chunks 1, 2, 4, 8 apart (16 lanes hold a row; every lane of
       // a quad, then of half a row has its sum, so that mirroring stands for the exchange 4 and 8 apart)
-      const bf16x8 ov = __builtin_bit_cast(bf16x8, oreg[SET]), gv = __builtin_bit_cast(bf16x8, greg[SET]);
-      float t = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) t = fmaf((float)ov[e], (float)gv[e], t);
+      float t = dot8(oreg[SET], greg[SET], 0.f);
       if (HD != HR || HR != 128) t = ch_data ? t : 0.f;
       t += lane_swap<0xB1>(t);                                 // quad_perm 1, 0, 3, 2
       t += lane_swap<0x4E>(t);                                 // quad_perm 2, 3, 0, 1

@@ -8,11 +8,11 @@
 // dK / dV workgroups compute delta of the rows they stage, from O.
 //
 // What bounds it: launch, argument and first-load latencies below two rounds of slabs; then the 16-byte loads of the
-// staging, which every 32 rows or keys do for all they meet (24 a lane and round for dK / dV; 3.0 us a round at H = 128,
-// its MFMAs take 0.9).  Registers: dK, dV and one slab of loads fill the 256 of a wavefront at H = 128, so the second slab
+// staging, which every 32 rows or keys do for all they meet (24 a lane and round for dK / dV; 2.7 us a round at H = 128,
+// its MFMAs take 0.9; delta from unpacked products was a third of its vector instructions, 3.0 us).  Registers: dK, dV and one slab of loads fill the 256 of a wavefront at H = 128, so the second slab
 // is loaded under the first contraction only, and the keys' operands are read from LDS.
-// Measured, against workgroups of 128 and more rows with their walks in parts: H = 64 8 x 512 x 512 19.1 -> 9.1 us, 4 x 1024 x
-// 1024 22.6 -> 12.1, 1 x 128 x 128 10.1 -> 6.3; H = 128 26.9 -> 13.9, 28.5 -> 19.2, 13.4 -> 9.3, 2 x 2048 x 2048 36.6 -> 31.6.
+// Measured, against workgroups of 128 and more rows with their walks in parts: H = 64 8 x 512 x 512 19.1 -> 8.9 us, 4 x 1024 x
+// 1024 22.6 -> 11.8, 1 x 128 x 128 10.1 -> 6.1; H = 128 26.9 -> 13.7, 28.5 -> 18.9, 13.4 -> 9.0, 2 x 2048 x 2048 36.6 -> 29.2.
 #include "a2d_bwd.hpp"
 
 namespace a2d {
@@ -255,9 +255,7 @@ __device__ __forceinline__ void small_rows(
     }
     lse2 = l == -INFINITY ? INFINITY : l * kLog2e;           // +inf: exp2(s - lse2) = 0
 #pragma unroll
-    for (int x = 0; x < KS; ++x)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) del = fmaf((float)of[x][i], (float)f2[x][i], del);
+    for (int x = 0; x < KS; ++x) del = dot8(__builtin_bit_cast(u32x4, of[x]), __builtin_bit_cast(u32x4, f2[x]), del);
     del += __shfl_xor(del, 32, 64);
   }
 
@@ -311,10 +309,7 @@ __device__ __forceinline__ void small_rows(
       const int ln = lane_again();                 // -delta = -rowsum(dO o O), CHUNKS lanes a row
 #pragma unroll
       for (int p = 0; p < ST_N; ++p) {
-        const bf16x8 ov = __builtin_bit_cast(bf16x8, zr[p]), gv = __builtin_bit_cast(bf16x8, xr[p]);
-        float t = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t = fmaf((float)ov[i], (float)gv[i], t);
+        float t = dot8(zr[p], xr[p], 0.f);
         if (8 * CHUNKS != H) t = ln % CHUNKS * 8 < H ? t : 0.f;
         t += lane_swap<0xB1>(t);
         t += lane_swap<0x4E>(t);

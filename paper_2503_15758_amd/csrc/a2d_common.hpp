@@ -31,6 +31,18 @@ __device__ __forceinline__ float to_f32(bf16_t x) { return (float)x; }
 // 2^x on the hardware transcendental unit (about 1 ulp).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// c + the sum of eight products of bf16 pairs (two at a time: half the instructions of unpacked multiply-adds, and of
+// rows of 128 N(0,1) pairs 9.5e-9 off in the mean of the magnitudes' sum against 9.9e-9)
+__device__ __forceinline__ float dot8(u32x4 a, u32x4 b, float c) {
+  typedef __bf16 pair_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const unsigned x = a[i], y = b[i];               // (a bit cast of a[i] itself takes a[0])
+    c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(pair_t, x), __builtin_bit_cast(pair_t, y), c, false);
+  }
+  return c;
+}
+
 template <typename T> struct dtype_of;
 template <> struct dtype_of<float> { static constexpr int value = A2D_F32; };
 template <> struct dtype_of<bf16_t> { static constexpr int value = A2D_BF16; };

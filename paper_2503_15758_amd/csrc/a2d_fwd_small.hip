@@ -9,8 +9,8 @@
 // What bounds it: launch, argument and first-load latencies below two rounds of slabs; then what a compute unit reads
 // from L2, 128 KiB a round at H = 128 (1.65 us; its MFMAs take 0.45), since every 32 rows read all keys they see.  For
 // short calls that is cheaper than partial results and a second launch, for long ones not (see plan_fwd_mfma).
-// Measured, against the best of the other forms: H = 128 2 x 512 x 512 causal 15.4 -> 9.6 us, 8 x 1024 x 1024 23.0 -> 13.6,
-// 4 x 2048 x 2048 26.5 -> 20.7; H = 64 64 x 128 x 128 6.8 -> 5.5, 8 x 1024 x 1024 16.6 -> 9.0.
+// Measured, against the best of the other forms: H = 128 2 x 512 x 512 causal 15.4 -> 9.3 us, 8 x 1024 x 1024 23.0 -> 12.8,
+// 4 x 2048 x 2048 26.5 -> 20; H = 64 2 x 512 x 512 10.8 -> 6.3, 8 x 1024 x 1024 16.6 -> 8.6.
 #include "a2d_mfma.hpp"
 
 namespace a2d {

@@ -420,10 +420,14 @@ __global__ __launch_bounds__(kThreads) void delta_kernel(int64_t rows, int nq, i
     const T* g = dO + head * ldo.head + r * ldo.row + c * EPL;
     const u32x4 ow = *reinterpret_cast<const u32x4*>(o);
     const u32x4 gw = *reinterpret_cast<const u32x4*>(g);
-    const T* ov = reinterpret_cast<const T*>(&ow);
-    const T* gv = reinterpret_cast<const T*>(&gw);
+    if constexpr (sizeof(T) == 2) {
+      acc = dot8(ow, gw, acc);
+    } else {
+      const T* ov = reinterpret_cast<const T*>(&ow);
+      const T* gv = reinterpret_cast<const T*>(&gw);
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc = fmaf(to_f32(ov[e]), to_f32(gv[e]), acc);
+      for (int e = 0; e < EPL; ++e) acc = fmaf(ov[e], gv[e], acc);
+    }
   }
   for (int o = 1; o < lpr; o <<= 1) acc += __shfl_xor(acc, o, 64);
   if (row < rows && c == 0) delta[row] = acc;
