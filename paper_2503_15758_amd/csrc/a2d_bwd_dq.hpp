@@ -110,9 +110,11 @@ __device__ __forceinline__ void dq_rows(
                kXcdCus * 8 / WAVES)) return;
   // (unit = part `part` of the walks over one key/value head; blocks numbered by size first when the
   // workgroups are ordered by size)
-  const int kvh = unit / parts, part = unit - kvh * parts;
-  const int head = kvh * g.group + (GRID || by_size ? blk % g.group : blk / nqb);
-  blk = GRID || by_size ? blk / g.group : blk % nqb;
+  const Split up = split_by(unit, parts);
+  const int kvh = up.q, part = up.r;
+  const Split in_group = query_head(blk, g.group, nqb, GRID || by_size);
+  const int head = kvh * g.group + in_group.r;
+  blk = in_group.q;
   const GridBlock gb = GRID ? grid_block(g.b, nqb, blk) : GridBlock{0, blk};
   const int row_blk = gb.r;                            // of the grid
   blk = gb.blk;

@@ -179,8 +179,9 @@ __device__ __forceinline__ void dkdv_pairs(
   const int nkb = (d.nkv + DK_KEYS - 1) / DK_KEYS;
   int unit;
   if (!xcd_map(id, kv_heads * parts, (GRID ? g.b.side : 1) * nkb, (GRID ? d.causal : g.by_size) != 0, unit, blk)) return;
-  head = unit / parts;
-  const int part = unit - head * parts;
+  const Split up = split_by(unit, parts);
+  head = up.q;
+  const int part = up.r;
   const int qh0 = GROUPED ? head * g.group : head;           // the first query head, as a head of Q
   const GridBlock gb = GRID ? grid_column(g.b, nkb, blk) : GridBlock{0, blk};
   const int col = gb.r;                                      // of the grid

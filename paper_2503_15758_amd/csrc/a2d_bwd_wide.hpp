@@ -52,7 +52,8 @@ __device__ __forceinline__ void dkdv_wide(
   const int nkb = (d.nkv + WK_KEYS - 1) / WK_KEYS;
   int unit, blk;
   if (!xcd_map(id, kv_heads * parts, (GRID ? g.b.side : 1) * nkb, (GRID ? d.causal : g.by_size) != 0, unit, blk)) return;
-  const int head = unit / parts, part = unit - head * parts, qh0 = head * g.group;
+  const Split up = split_by(unit, parts);
+  const int head = up.q, part = up.r, qh0 = head * g.group;
   const GridBlock gb = GRID ? grid_column(g.b, nkb, blk) : GridBlock{0, blk};
   const int col = gb.r;                            // of the grid
   blk = gb.blk;

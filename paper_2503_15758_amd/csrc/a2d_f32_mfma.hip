@@ -303,10 +303,10 @@ __device__ __forceinline__ bool query_block(int id, const a2d_tile_desc& d, cons
   const int nqb = (d.nq + rows - 1) / rows;
   int unit, blk;
   if (!xcd_map(id, d.heads / g.group * parts, g.group * nqb, g.by_size != 0, unit, blk)) return false;
-  const int kvh = unit / parts;
-  part = unit - kvh * parts;
-  head = kvh * g.group + (g.by_size ? blk % g.group : blk / nqb);
-  q0 = (nqb - 1 - (g.by_size ? blk / g.group : blk % nqb)) * rows;
+  const mfma::Split up = mfma::split_by(unit, parts), in_group = mfma::query_head(blk, g.group, nqb, g.by_size != 0);
+  part = up.r;
+  head = up.q * g.group + in_group.r;
+  q0 = (nqb - 1 - in_group.q) * rows;
   return true;
 }
 
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int lanes = KL * g.parts;
   const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l15 = lane & 15, g4 = lane >> 4;
-  const int kvh = head / g.group;
+  const int kvh = mfma::split_by(head, g.group).q;
   const gptr_t kb = uniform_gptr(K + (int64_t)kvh * d.lk.head), vb = uniform_gptr(V + (int64_t)kvh * d.lv.head);
   const gptr_t qb = uniform_gptr(Q + (int64_t)head * d.lq.head);
   const unsigned k_row = (unsigned)d.lk.row * 4, v_row = (unsigned)d.lv.row * 4;
@@ -486,7 +486,7 @@ __device__ __forceinline__ void dq_rows(int id, char* const smem, const a2d_tile
   const int lanes = KL * parts;
   const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l15 = lane & 15, g4 = lane >> 4;
-  const int kvh = head / g.group;
+  const int kvh = mfma::split_by(head, g.group).q;
   const gptr_t kb = uniform_gptr(K + (int64_t)kvh * d.lk.head), vb = uniform_gptr(V + (int64_t)kvh * d.lv.head);
   const unsigned k_row = (unsigned)d.lk.row * 4, v_row = (unsigned)d.lv.row * 4;
   const int q_row = q0 + l15, q_ld = min(q_row, d.nq - 1);
@@ -566,9 +566,10 @@ __device__ __forceinline__ void dkdv_keys(int id, char* const smem, const a2d_ti
                                           float* __restrict__ dV) {
   int head, blk;                                      // key/value head
   if (!xcd_map(id, d.heads / g.group * parts, (d.nkv + BLK - 1) / BLK, g.by_size != 0, head, blk)) return;
-  const int unit = head, lanes = KL * parts;
-  head = unit / parts;
-  const int part = unit - head * parts;
+  const int lanes = KL * parts;
+  const mfma::Split up = mfma::split_by(head, parts);
+  head = up.q;
+  const int part = up.r;
   const int kl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l15 = lane & 15, g4 = lane >> 4;
   const int k0 = blk * BLK, key = k0 + l15, k_ld = min(key, d.nkv - 1);

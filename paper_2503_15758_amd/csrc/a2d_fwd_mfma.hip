@@ -185,9 +185,11 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
                kXcdCus * 8 / WAVES)) return;
   // (unit = part `part` of the walks over one key/value head; blocks numbered by size first when the
   // workgroups are ordered by size)
-  const int kvh = unit / g.parts, part = unit - kvh * g.parts;
-  const int head = kvh * g.group + (GRID || by_size ? blk % g.group : blk / nqb);
-  blk = GRID || by_size ? blk / g.group : blk % nqb;
+  const Split up = split_by(unit, g.parts);
+  const int kvh = up.q, part = up.r;
+  const Split in_group = query_head(blk, g.group, nqb, GRID || by_size);
+  const int head = kvh * g.group + in_group.r;
+  blk = in_group.q;
   const GridBlock gb = GRID ? grid_block(g.b, nqb, blk) : GridBlock{0, blk};
   const int row_blk = gb.r;                             // of the grid
   blk = gb.blk;

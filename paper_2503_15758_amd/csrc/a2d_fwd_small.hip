@@ -44,18 +44,11 @@ __global__ __launch_bounds__(64 * LANES, 1) void fwd_small_kernel(
   const int by_size = GRID ? d.causal : g.by_size;
   if (!xcd_map(blockIdx.x, d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * nqb, by_size != 0, unit, blk,
                kXcdCus)) return;
-  // (divisions are a good part of the way to the first load: none by one)
-  int kvh = unit, part = 0, head = unit;
-  if (g.parts > 1) {
-    kvh = unit / g.parts;
-    part = unit - kvh * g.parts;
-    head = kvh;
-  }
-  if (g.group > 1) {
-    const int by = GRID || by_size ? g.group : nqb, q = blk / by, r = blk - q * by;
-    head = kvh * g.group + (GRID || by_size ? r : q);
-    blk = GRID || by_size ? q : r;
-  }
+  const Split up = split_by(unit, g.parts);
+  const int kvh = up.q, part = up.r;
+  const Split in_group = query_head(blk, g.group, nqb, GRID || by_size);
+  const int head = kvh * g.group + in_group.r;
+  blk = in_group.q;
   const GridBlock gb = GRID ? grid_block(g.b, nqb, blk) : GridBlock{0, blk};
   const int row_blk = gb.r;                        // of the grid
   blk = gb.blk;

@@ -59,6 +59,31 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& s, int base) {
 // cost 1 % at H = 128, 2 % at H = 80, 3 % at 16 x 2048 x 2048).
 __device__ __forceinline__ bool seldom(bool x) { return __builtin_expect(x, 0); }
 
+// a / b and the rest, without a division by one: unsplit walks, heads that are not grouped (a division is some 35 dependent
+// instructions on the way to a workgroup's first loads)
+struct Split {
+  int q, r;
+};
+__device__ __forceinline__ Split split_by(int a, int b) {
+  Split s = {a, 0};
+  if (seldom(b != 1)) {
+    s.q = a / b;
+    s.r = a - s.q * b;
+  }
+  return s;
+}
+
+// of block t of the group x nblocks of a key/value head: its number within its query head (q) and that head (r)
+__device__ __forceinline__ Split query_head(int t, int group, int nblocks, bool by_size) {
+  Split s = {t, 0};
+  if (seldom(group != 1)) {
+    const int by = by_size ? group : nblocks, q = t / by, r = t - q * by;
+    s.q = by_size ? q : r;
+    s.r = by_size ? r : q;
+  }
+  return s;
+}
+
 // s_waitcnt vmcnt(0) only (gfx9 encoding: lgkmcnt and expcnt fields left at their maxima).
 // Placed after a prologue's one-off global loads it tells the compiler's wait-count insertion that
 // those registers are complete, so that uses inside the main loop do not have to be guarded by
