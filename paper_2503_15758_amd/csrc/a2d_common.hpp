@@ -190,7 +190,8 @@ struct WalkModel {
   const double* sorted;    // the steps at 8 places, longest first, as multiples of 1 / `per` (NULL: not known)
   double per;
   double tail = 0.5;       // of a workgroup, while the last turn of uneven walks ends
-  bool short_walks = false;   // a workgroup's fixed time counts as much as its walk: never less than whole turns
+  bool short_walks = false;   // the chip is not busy enough for its clock to fall
+  bool capped = false;        // no more than whole turns of mean walks
 };
 inline double walk_time(const WalkModel& w, int parts) {
   const auto len = [&](double steps, double step, double fixed) {
@@ -206,8 +207,9 @@ inline double walk_time(const WalkModel& w, int parts) {
     return pairs ? turns / 2 * len(w.most, w.pair_step, w.pair_fixed) + turns % 2 * len(w.most, w.step, w.fixed)
                  : turns * len(w.most, w.step, w.fixed);
   const double each = pairs ? 0.5 * len(w.mean, w.pair_step, w.pair_fixed) : len(w.mean, w.step, w.fixed);
-  const double part_turns = (double)wgs / w.slots + w.tail;
-  const double even = (w.short_walks && part_turns < turns ? (double)turns : part_turns) * each;   // longest first
+  double n = (double)wgs / w.slots + w.tail;                              // longest first
+  if (w.capped && n > turns) n = (double)turns;
+  const double even = n * each;
   double longest = len(w.most, pairs ? w.pair_step : w.step, w.fixed);
   if (w.sorted && !pairs) {
     // the first walk of the last turn: every slot then holds walks no shorter
@@ -285,8 +287,8 @@ hipError_t launch_delta(const a2d_tile_desc& d, const void* O, const void* dO, f
 // bf16 MFMA tile kernels (H in {64, 80, 96, 128}).  `supported` tells whether the shape is covered.
 hipError_t launch_fwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                            const void* V, float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s);
-// the form of 32-row workgroups (a2d_fwd_small.hip); arguments as of launch_fwd_mfma
-hipError_t launch_fwd_small(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
+// the forms of 32- and 64-row workgroups (a2d_fwd_small.hip); arguments as of launch_fwd_mfma
+hipError_t launch_fwd_small(Phase ph, int rows, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                             const void* V, float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s);
 bool bwd_mfma_supported(const a2d_tile_desc& d);
 // ds_ws: NULL, or a workspace of bwd_ds_bytes(d, g) (> 0) bytes through which the dK/dV kernel

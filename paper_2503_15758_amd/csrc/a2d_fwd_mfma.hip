@@ -45,6 +45,7 @@ __host__ __device__ constexpr int lds_bytes(int hd) { return 2 * buf_bytes(hd); 
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
 constexpr double kStepUs[3] = {1.25, 1.45, 1.66};   // a 64-key step of a 256-row workgroup, H = 64 / 96 / 128
 constexpr double kSmallRoundUs[3] = {0.95, 1.42, 1.65}, kSmallFixedUs[3] = {3.1, 3.5, 3.2};   // 256 keys of 32 rows
+constexpr double kPairRoundUs[3] = {0.95, 1.25, 1.37}, kPairFixedUs[3] = {4.1, 4.3, 4.4};     // 128 keys of 64 rows
 
 template <int HD>
 struct FwdState {
@@ -513,7 +514,7 @@ hipError_t fwd_launch(Phase ph, const a2d_tile_desc& d, const SegList& g, const 
                      (const bf16_t*)K, (const bf16_t*)V, O_part, m, l, in);
   return hipGetLastError();
 }
-enum { FWD_BIG = 0, FWD_LANES = 1, FWD_PAIRS = 2, FWD_SMALL = 3 };   // <8, HR, 1>, <8, HR, 2>, <4, HR, 1>, fwd_small_kernel
+enum { FWD_BIG = 0, FWD_LANES = 1, FWD_PAIRS = 2, FWD_32 = 3, FWD_64 = 4 };   // <8, HR, 1>, <8, HR, 2>, <4, HR, 1>; fwd_small_kernel
 }  // namespace
 
 namespace {
@@ -532,15 +533,15 @@ hipError_t fwd_form(Phase ph, const a2d_tile_desc& d, const SegList& g, const vo
 }
 }  // namespace
 
-// Shape and parts.  Four shapes: 256-row workgroups, one per compute unit; 128-row workgroups whose two
+// Shape and parts.  Five shapes: 256-row workgroups, one per compute unit; 128-row workgroups whose two
 // key lanes walk alternate key blocks, one per compute unit; 128-row workgroups of four wavefronts, two
 // per compute unit (each K / V tile is staged twice, but there is no merge of lanes and the last turn
-// is finer); 32-row workgroups whose eight wavefronts share the walk (a2d_fwd_small.hip; a step is a round of 256
-// keys).  By model, with parts > 1 where the blocks leave compute units idle and the walk is long.  The
+// is finer); 64- and 32-row workgroups whose four or eight key lanes share the walk (a2d_fwd_small.hip; a step is a round
+// of 128 or 256 keys).  By model, with parts > 1 where the blocks leave compute units idle and the walk is long.  The
 // constants are a fit to 95 shapes x three forms x up to five numbers of parts (1 x 128 x 128 to 96 x 1024 x
-// 2048, H = 64 and 128), of the 32-row form to 101 shapes of few rows, H = 64 to 128: it is taken up to about 256 blocks of
-// 32 rows, 16 rounds each, and under a causal mask for up to 512; there the choice is 0.6 % slower than the best of 13 forms
-// and parts, and 1.24 times as fast in the mean as without that form.
+// 2048, H = 64 and 128), to 149 shapes of few rows, H = 64 to 128 - 32 rows are taken up to about 256 such blocks, 64 rows up to
+// 256 of theirs, under a causal mask up to 512, with walks of 16 rounds at the most; there the choice is 0.3 % slower than the best
+// of 12 forms and parts, and 1.25 times as fast in the mean as without the two forms - and 73 of any size (worst miss 11 %).
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t heads = (int64_t)d.heads * (g->b.side ? g->b.side : 1);
   double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2, mean = most;
@@ -548,12 +549,14 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   if (g->b.side) {                                             // (the rows of a whole sequence see half of it in the mean)
     most = (double)g->b.side * ((d.nkv + BN - 1) / BN) + 0.2;
     mean = d.causal ? 0.5 * most + 0.5 * (g->b.cyclic ? g->b.side : 1) : most;
+    for (int i = 0; i < 8; ++i) seen[i] = (d.causal ? (15 - 2 * i) / 16.0 : 1.0) * most * BN;
   } else if (g->by_size) {
     mean = mean_visible_keys(d, *g, seen) / BN + 0.2;
   }
+  const double* const sorted = mean < most ? seen : nullptr;
   const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 3.7;
   const double part_us = (double)heads * d.nq * (d.hdim + 2) * 8 / 4.5e6;      // written and read back at 4.5 TB/s
-  const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128), b32 = heads * ((d.nq + 31) / 32);
+  const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128), b64 = heads * ((d.nq + 63) / 64), b32 = heads * ((d.nq + 31) / 32);
   // (the walks of a causal grid are of every length down to a few steps, so that the last ones end nearly together)
   const double tail = g->b.side ? 0.1 : 0.5, big = g->b.side ? fixed + 1.5 : fixed;
   const int h = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0;
@@ -564,21 +567,22 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const double store = g->b.side ? 0 : d.hdim / 128.0;
   const double big_fix = big + (b256 > cus ? 4.0 * store : 0), lanes_fix = fixed + 0.8 + (b128 > cus ? 2.0 * store : 0);
   const double pair_fix = store > 0 && b128 > 2 * cus ? 2.4 + 6.1 * store : fixed + 0.5;
-  const WalkModel m[4] = {{b256, cus, mean, most, step, big_fix, 0, 0, nullptr, 0, tail},
+  const WalkModel m[5] = {{b256, cus, mean, most, step, big_fix, 0, 0, nullptr, 0, tail},
                           {b128, cus, mean / 2, most / 2, step * 1.13, lanes_fix, 0, 0, nullptr, 0, tail},
                           {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, pair_fix, nullptr, 0, tail},
-                          {b32, cus, mean / 4, most / 4, round, small, 0, 0, nullptr, 0, tail, true}};
+                          {b32, cus, mean / 4, most / 4, round, small, 0, 0, sorted, 0.25 / BN, tail, true},
+                          {b64, cus, mean / 2, most / 2, kPairRoundUs[h], kPairFixedUs[h], 0, 0, sorted, 0.5 / BN, tail, true, true}};
   double least = 0;
-  for (int f = 0; f < 4; ++f) {
+  for (int f = 0; f < 5; ++f) {
     double t;
-    const int z = best_parts(m[f], cap, f == FWD_SMALL ? 4.5 : 3.2, part_us, &t);
+    const int z = best_parts(m[f], cap, f >= FWD_32 ? 4.5 : 3.2, part_us, &t);
     if (f == 0 || t < (g->form == 0 ? 0.98 : 1.0) * least) { least = t; g->form = f; g->parts = z; }
   }
 }
 
 hipError_t launch_fwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                            const void* V, float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
-  if (g.form == FWD_SMALL) return launch_fwd_small(ph, d, g, Q, K, V, O_part, m, l, in, s);
+  if (g.form >= FWD_32) return launch_fwd_small(ph, g.form == FWD_64 ? 64 : 32, d, g, Q, K, V, O_part, m, l, in, s);
   return g.b.side == 0 ? fwd_form<0>(ph, d, g, Q, K, V, O_part, m, l, in, s)
          : g.b.cyclic  ? fwd_form<2>(ph, d, g, Q, K, V, O_part, m, l, in, s)
                        : fwd_form<1>(ph, d, g, Q, K, V, O_part, m, l, in, s);

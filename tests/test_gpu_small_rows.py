@@ -1,5 +1,5 @@
-"""Forward tiles of few rows: 32 query rows a workgroup, whose eight wavefronts share the walk by slabs of 32 keys and merge
-their (N, m, l) inside the kernel.  At the edges of rows, slabs and sub-blocks, against fp64 on the GPU; the three forms of
+"""Forward tiles of few rows: 32 (64) query rows a workgroup, whose eight (four) key lanes share the walk by slabs of 32 keys and
+merge their (N, m, l) inside the kernel.  At the edges of rows, slabs and sub-blocks, against fp64 on the GPU; the three forms of
 the call: plain, accumulating, normalised."""
 import math
 
@@ -24,6 +24,11 @@ CASES = [
     (17, 17, 480, 545, 128, False, 0, None, False, 8),
     (30, 10, 250, 1030, 96, True, 780, None, True, 1),
     (1, 1, 40, 9000, 128, False, 0, None, False, 2),         # a walk worth sharing between workgroups too
+    (40, 40, 300, 300, 128, False, 0, None, False, 2),       # from here on 64 rows a workgroup
+    (40, 20, 290, 333, 80, True, 60, None, True, 1),
+    (26, 13, 610, 129, 64, True, -30, None, False, 3),       # rows that see nothing; one key in the second round
+    (44, 11, 250, 500, 96, True, 300, [(0, 31), (40, 1), (90, 300), (420, 168)], True, 1),
+    (70, 70, 225, 31, 128, False, 0, None, True, 1),         # three of the four lanes have no keys
 ]
 
 
