@@ -557,7 +557,8 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 3.7;
   const double part_us = (double)heads * d.nq * (d.hdim + 2) * 8 / 4.5e6;      // written and read back at 4.5 TB/s
   const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128), b64 = heads * ((d.nq + 63) / 64), b32 = heads * ((d.nq + 31) / 32);
-  // (the walks of a causal grid are of every length down to a few steps, so that the last ones end nearly together)
+  // (the walks of a causal grid are of every length down to a few steps, so that the last ones end nearly together; those of 32
+  // and 64 rows wait for each other's loads all the same: 7 heads, 5166 tokens on 3 x 3, H = 128, cyclic 101 us with 0.1, 82 in pairs)
   const double tail = g->b.side ? 0.1 : 0.5, big = g->b.side ? fixed + 1.5 : fixed;
   const int h = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0;
   const double round = kSmallRoundUs[h], small = kSmallFixedUs[h];
@@ -570,8 +571,8 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const WalkModel m[5] = {{b256, cus, mean, most, step, big_fix, 0, 0, nullptr, 0, tail},
                           {b128, cus, mean / 2, most / 2, step * 1.13, lanes_fix, 0, 0, nullptr, 0, tail},
                           {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, pair_fix, nullptr, 0, tail},
-                          {b32, cus, mean / 4, most / 4, round, small, 0, 0, sorted, 0.25 / BN, tail, true},
-                          {b64, cus, mean / 2, most / 2, kPairRoundUs[h], kPairFixedUs[h], 0, 0, sorted, 0.5 / BN, tail, true, true}};
+                          {b32, cus, mean / 4, most / 4, round, small, 0, 0, sorted, 0.25 / BN, 0.5, true},
+                          {b64, cus, mean / 2, most / 2, kPairRoundUs[h], kPairFixedUs[h], 0, 0, sorted, 0.5 / BN, 0.5, true, true}};
   double least = 0;
   for (int f = 0; f < 5; ++f) {
     double t;
