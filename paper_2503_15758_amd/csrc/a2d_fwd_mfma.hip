@@ -416,13 +416,13 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     const bool more = nsb < segs;
     if (CYCLIC) nx_start = nsb;
     else if (seldom(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
-    if (more) load_tile(nx_start, nx_rows, nj);
+    if (often(more)) load_tile(nx_start, nx_rows, nj);
     const int k0 = j * BN + (CYCLIC && sb > shift_from);       // local to the sub-block
     if ((KL == 1 || sb < segs) && k0 < nvis_wave) {
       if (k0 + BN > nfull_wave) fwd_block<HD, true, KSR>(st, qf, k_rd0 + boff, v_rd0 + boff, k0, my_vis, half, c);
       else fwd_block<HD, false, KSR>(st, qf, k_rd0 + boff, v_rd0 + boff, k0, my_vis, half, c);
     }
-    if (more) store_tile(BUF_BYTES - boff);
+    if (often(more)) store_tile(BUF_BYTES - boff);
     __syncthreads();
     if (!CYCLIC && seldom(more && nsb != sb)) enter_segment(nsb);
     if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);

@@ -56,8 +56,10 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& s, int base) {
 
 // A branch of a main loop that is seldom taken: its code is laid out behind the loop, so that the loop
 // itself stays in one run of instruction lines (the walk's move to another sub-block inside the forward loop
-// cost 1 % at H = 128, 2 % at H = 80, 3 % at 16 x 2048 x 2048).
-__device__ __forceinline__ bool seldom(bool x) { return __builtin_expect(x, 0); }
+// cost 1 % at H = 128, 2 % at H = 80, 3 % at 16 x 2048 x 2048).  And one that is taken in every turn but the last: its
+// code stays where it stands.  (Macros: of an inlined function the compiler has dropped the hint by the time it is inlined.)
+#define seldom(x) __builtin_expect((bool)(x), 0)
+#define often(x) __builtin_expect((bool)(x), 1)
 
 // a / b and the rest, without a division by one: unsplit walks, heads that are not grouped (a division is some 35 dependent
 // instructions on the way to a workgroup's first loads)
