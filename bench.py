@@ -21,6 +21,7 @@ All inputs are resident in HBM before the timed region.  Prints ONE JSON line.
                      and the shader clock during each; context for the roofline fraction, not its peak
 """
 import argparse
+import functools
 import json
 import math
 import os
@@ -43,19 +44,15 @@ def tile_flops(w, nq, nkv, causal_diag):
     return 4.0 * base, 10.0 * base
 
 
+@functools.lru_cache(None)
 def call_kernels(call, w, recompute):
-    """The library kernels one call of the step launches, in launch order (bwd_dkdv_kernel: whichever form of it the
-    call takes, 128 or 256 keys per workgroup; the profiles name the one that ran)."""
-    if call.startswith("partial_fwd"):
-        return ["fwd_mfma_kernel" if w.dtype == "bf16" else "fwd_f32_kernel"]
-    if call.startswith("partial_bwd"):
-        if w.dtype != "bf16":
-            return ["bwd_f32_kernel"]
-        if 2 * w.heads * (-(-w.tile // 256)) <= 6 * 256:      # at most six turns of 256 compute units: one launch
-            return ["delta_kernel", "bwd_one_kernel"]
-        if recompute:
-            return ["bwd_dq_kernel", "bwd_dkdv_kernel"]
-        return ["delta_kernel", "bwd_dkdv_kernel", "bwd_dq_ds_kernel"]
+    """The library kernels one call of the step launches, in launch order (tile calls: by the library's own plans)."""
+    if call.startswith("partial_"):
+        from paper_2503_15758_amd import binding as a2d, synth
+        route = a2d.tile_route(w.heads, w.tile, w.tile, w.hdim, synth.torch_dtype(w.dtype), causal=w.causal,
+                               q_off=0 if call.endswith("diag") else w.tile, backward=call.startswith("partial_bwd"),
+                               ds_handover=not recompute)
+        return list(route["kernels"])
     if call == "fix":
         return ["fix_kernel"]
     if call.startswith("fix_bwd"):
@@ -233,8 +230,9 @@ def main():
             ks = call_kernels(n, w, args.recompute_bwd)
             if "delta_kernel" in ks:
                 kbytes[(n, "delta_kernel")] = rows * (2 * H * esz + 4)
-            if ks[-1] in ("bwd_one_kernel", "bwd_f32_kernel"):
-                kflops[(n, ks[-1])] = b                       # (recomputation of S and dP not counted)
+            both = [k for k in ks if k in ("bwd_one_kernel", "bwd_small_kernel", "bwd_f32_kernel")]
+            if both:
+                kflops[(n, both[0])] = b                      # (recomputation of S and dP not counted)
                 continue
             k_kv, = [k for k in ks if k.startswith("bwd_dkdv")]
             k_dq, = [k for k in ks if k.startswith("bwd_dq")]
@@ -259,6 +257,8 @@ def main():
     src_sha = rocprof_summary.source_hash()
 
     def entry(ms, fl=None, by=None, note=None):
+        if by is None and fl is None:                         # (merges of split walks: no work of the method's own)
+            return {"avg_ms": round(ms, 4)}
         if by is not None and (fl is None or note):           # HBM-bound
             ach = by / (ms * 1e-3) / 1e9
             e = {"avg_ms": round(ms, 4), "bound": "hbm", "achieved": round(ach, 1), "unit": "GB/s",
@@ -282,12 +282,12 @@ def main():
     for n in names:
         kernels[n]["traffic"] = traffic.get(n)
     # the dominant kernel: the longest single launch of the step
-    dom = max(kern_ms, key=lambda nk: kern_ms[nk])
+    dom = max((nk for nk in kern_ms if nk in kflops or nk in kbytes), key=lambda nk: kern_ms[nk])
     de = per_kernel["%s/%s" % dom]
     roofline = {"kernel": dom[1], "call": dom[0], "bound": de["bound"], "achieved": de["achieved"], "peak": de["peak"],
                 "unit": de["unit"], "frac": de["frac"], "avg_ms": de["avg_ms"], "traffic": de["traffic"],
                 "algorithmic": ("4 of the call's 5 counted contractions (S, dP, dV, dK): 8 Nq Nkv H per head"
-                                if dom[1] == "bwd_dkdv_kernel" else "the call's counted work"),
+                                if dom[1].startswith("bwd_dkdv") else "the call's counted work"),
                 "traffic_source": {"file": "profiles/%s_hbm_traffic.txt" % traffic_name if traffic else None,
                                    "measured_on_sources": traffic_sha, "current_sources": src_sha,
                                    "current": bool(traffic) and traffic_sha == src_sha}}

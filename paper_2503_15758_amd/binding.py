@@ -335,6 +335,17 @@ def lds_read_ceiling(iters=20000, transposing=False):
     return tb.value, mhz.value
 
 
+def tile_route(heads, nq, nkv, hdim, dtype=torch.bfloat16, kv_heads=None, q_off=0, kv_off=0, causal=False, segments=None,
+               backward=False, ds_handover=False, split_groups=False, scratch=True, compute_units=0):
+    """Diagnostic: how a tile call of these sizes goes out, by the library's own plans and without a device (compute_units
+    0: those of the current one).  A dict: "kernels" in launch order, "rows" and "lanes" (key lanes) of a forward or dQ
+    workgroup, "keys" of a dK/dV workgroup, "parts_q" and "parts_kv" (workgroups that share a walk).  scratch: whether
+    there is memory for partial results (this module's calls; not those of the C boundary)."""
+    flags = 1 * bool(backward) | 2 * bool(ds_handover) | 4 * bool(split_groups) | 8 * bool(scratch)
+    return _ext().tile_route(heads, kv_heads or heads, nq, nkv, hdim, dtype, q_off, kv_off, causal, segments, flags,
+                             compute_units)
+
+
 def force_generic(on):
     """a2d_debug_force_generic: route every tile call to the vector-ALU kernels (debugging aid)."""
     lib().a2d_debug_force_generic(int(bool(on)))

@@ -165,6 +165,24 @@ int cap_of(int64_t floats) {
   return n < 1 ? 1 : n > A2D_MAX_PARTS ? A2D_MAX_PARTS : (int)n;
 }
 
+// Route of a backward call, and the floats of partial sums it puts into scratch memory.  Those of dK, dV go into the
+// caller's split area (room for cap_ws of them) where they fit, the others into scratch memory where it is offered.
+struct BwdPlan {
+  a2d::BwdParts parts;
+  bool kv_in_ws;
+  int64_t scratch;
+};
+BwdPlan plan_bwd(const a2d_tile_desc& d, const a2d::SegList& g, bool ds, int cus, bool offered, int cap_ws) {
+  const int64_t nq = (int64_t)d.heads * d.nq * d.hdim, nk = (int64_t)(d.heads / g.group) * d.nkv * d.hdim;
+  const int cap_sc = offered ? cap_of(2 * nk) : 1, cap_kv = cap_sc > cap_ws ? cap_sc : cap_ws, cap_q = offered ? cap_of(nq) : 1;
+  BwdPlan p;
+  p.parts = d.dtype == A2D_F32 ? a2d::plan_bwd_f32(d, g, cus, cap_kv, cap_q) : a2d::plan_bwd_mfma(d, g, ds, cus, cap_kv, cap_q);
+  p.kv_in_ws = p.parts.kv > 1 && p.parts.kv <= cap_ws;
+  p.scratch = (p.parts.kv > 1 && !p.kv_in_ws ? 2 * p.parts.kv * nk : 0) + (p.parts.q > 1 ? p.parts.q * nq : 0);
+  return p;
+}
+int split_cap(int group) { return group < A2D_MAX_PARTS ? group : A2D_MAX_PARTS; }
+
 a2d_status partial_fwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, const void* Q, const void* K,
                             const void* V, float* O_part, float* m, float* l, void* stream,
                             const char* who) {
@@ -183,7 +201,9 @@ a2d_status partial_fwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
     // N, m, l: where the tile kernel leaves its result - the outputs, or the partials of a split walk
     const int64_t rows = (int64_t)dd.heads * dd.nq, H = dd.hdim;
     float *N = O_part, *tm = m, *tl = l;
-    A2D_TRY(hip_result(a2d::plan_fwd(dd, &go, a2d::scratch_offered()), who));
+    int cus = 0;
+    A2D_TRY(hip_result(a2d::device_cus(&cus), who));
+    a2d::plan_fwd(dd, &go, a2d::scratch_offered(), cus);
     if (go.parts > 1) {
       N = static_cast<float*>(a2d::scratch_get((size_t)go.parts * rows * (H + 2) * sizeof(float)));
       if (N) {
@@ -192,7 +212,7 @@ a2d_status partial_fwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
         go.norm = 0;
       } else {
         N = O_part;
-        A2D_TRY(hip_result(a2d::plan_fwd(dd, &go, false), who));
+        a2d::plan_fwd(dd, &go, false, cus);
       }
     }
     const a2d::FwdInput in{O_part, m, l};
@@ -264,32 +284,21 @@ a2d_status partial_bwd_impl(const a2d_tile_desc* desc, const a2d::SegList& g, co
     const size_t ds_bytes = keep_ds && dd.dtype == A2D_BF16 ? a2d::bwd_ds_bytes(dd, g) : 0;
     void* ds_ws = (ds_bytes > 0 && workspace_bytes >= delta_bytes + ds_bytes) ? static_cast<char*>(workspace) + delta_bytes
                                                                               : nullptr;
-    // Partial sums of split walks: in offered scratch memory, those of dK, dV otherwise in the
-    // caller's split area
     const int64_t nq = (int64_t)dd.heads * dd.nq * dd.hdim, nk = (int64_t)(dd.heads / g.group) * dd.nkv * dd.hdim;
-    const bool offered = a2d::scratch_offered();
-    const int cap_kv = offered ? cap_of(2 * nk) : 1, cap_q = offered ? cap_of(nq) : 1;
-    const int cap_ws = split_ws ? (g.group < A2D_MAX_PARTS ? g.group : A2D_MAX_PARTS) : 1;
+    const int cap_ws = split_ws ? split_cap(g.group) : 1;
     int cus = 0;
     A2D_TRY(hip_result(a2d::device_cus(&cus), who));
-    const auto plan = [&](int ckv, int cq) {
-      return dd.dtype == A2D_F32 ? a2d::plan_bwd_f32(dd, go, cus, ckv, cq)
-                                 : a2d::plan_bwd_mfma(dd, go, ds_ws != nullptr, cus, ckv, cq);
-    };
-    a2d::BwdParts parts = plan(cap_kv > cap_ws ? cap_kv : cap_ws, cap_q);
-    bool kv_in_ws = parts.kv > 1 && parts.kv <= cap_ws;
-    const auto scratch_floats = [&] { return (parts.kv > 1 && !kv_in_ws ? 2 * parts.kv * nk : 0) + (parts.q > 1 ? parts.q * nq : 0); };
+    BwdPlan plan = plan_bwd(dd, go, ds_ws != nullptr, cus, a2d::scratch_offered(), cap_ws);
     float* more = nullptr;
-    if (scratch_floats() > 0 && !(more = static_cast<float*>(a2d::scratch_get(scratch_floats() * sizeof(float))))) {
-      parts = plan(cap_ws, 1);
-      kv_in_ws = parts.kv > 1;
-    }
+    if (plan.scratch > 0 && !(more = static_cast<float*>(a2d::scratch_get(plan.scratch * sizeof(float)))))
+      plan = plan_bwd(dd, go, ds_ws != nullptr, cus, false, cap_ws);
+    const a2d::BwdParts& parts = plan.parts;
     if (!parts.keep_ds) ds_ws = nullptr;                   // (faster without, see plan_bwd_mfma)
     float *dk = dK_part, *dv = dV_part, *dq = dQ_part;
     if (parts.kv > 1) {
-      dk = kv_in_ws ? split_ws : more;
+      dk = plan.kv_in_ws ? split_ws : more;
       dv = dk + parts.kv * nk;
-      if (!kv_in_ws) more += 2 * parts.kv * nk;
+      if (!plan.kv_in_ws) more += 2 * parts.kv * nk;
     }
     if (parts.q > 1) dq = more;
     if (dd.dtype == A2D_F32) {
@@ -796,3 +805,30 @@ const char* a2d_last_error(void) { return g_err; }
 const char* a2d_version(void) { return "0.1"; }
 
 }  // extern "C"
+
+namespace a2d {
+
+a2d_status tile_route(const a2d_tile_desc& desc, int kv_heads, int nseg, const a2d_kv_segment* segs, int flags, int cus,
+                      Route* out) {
+  const char* who = "tile_route";
+  A2D_TRY(check_desc(&desc, who));
+  SegList g = one_segment(&desc);
+  if (nseg != 0) A2D_TRY(make_segments(&desc, nseg, segs, who, &g));
+  A2D_TRY(group_of(&desc, kv_heads, who, &g));
+  if (cus == 0) A2D_TRY(hip_result(device_cus(&cus), who));
+  g.by_size = blocks_differ(&desc, g);
+  const bool scratch = (flags & ROUTE_SCRATCH) != 0;
+  if ((flags & ROUTE_BACKWARD) == 0) {
+    plan_fwd(desc, &g, scratch, cus);
+    route_fwd(desc, g, out);
+    if (g.parts > 1) out->kernel[out->kernels++] = "fix_kernel";
+    return A2D_OK;
+  }
+  const bool ds = (flags & ROUTE_KEEP_DS) != 0 && desc.dtype == A2D_BF16 && bwd_ds_bytes(desc, g) > 0;
+  const BwdPlan p = plan_bwd(desc, g, ds, cus, scratch, (flags & ROUTE_SPLIT_GROUPS) != 0 ? split_cap(g.group) : 1);
+  route_bwd(desc, p.parts, out);
+  if (p.parts.kv > 1 || p.parts.q > 1) out->kernel[out->kernels++] = "sum_parts_kernel";
+  return A2D_OK;
+}
+
+}  // namespace a2d

@@ -245,7 +245,7 @@ struct FwdInput {
 };
 // Workgroup shape and parts of a forward tile (sets g->form, g->parts); may_split: partial results
 // of parts > 1 workgroups per block ([parts][heads][nq] each of N, m, l) can be stored and merged.
-hipError_t plan_fwd(const a2d_tile_desc& d, SegList* g, bool may_split);
+void plan_fwd(const a2d_tile_desc& d, SegList* g, bool may_split, int cus);
 void plan_fwd_f32(const a2d_tile_desc& d, SegList* g, int cus, int cap);
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap);
 // Parts of the two kernels of a backward tile, each at most its cap, and the dQ kernel's workgroup shape
@@ -254,7 +254,11 @@ struct BwdParts {
   int one, q_first;          // one launch (launch_bwd_one), its dQ workgroups first
   int small;                 // that of launch_bwd_small
   int keep_ds;               // dS handed from dK/dV to dQ
+  int delta;                 // fp32: delta by a launch of its own
 };
+// the kernels of a planned forward or backward, without the launches that merge or sum its parts
+void route_fwd(const a2d_tile_desc& d, const SegList& g, Route* r);
+void route_bwd(const a2d_tile_desc& d, const BwdParts& p, Route* r);
 // Walks of a tile's or grid's dK/dV workgroups (steps of 32 query rows) and dQ workgroups (64 keys): on average, the
 // longest; uneven: under a mask, longest first
 struct BwdWalks {

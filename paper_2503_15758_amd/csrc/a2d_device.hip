@@ -143,15 +143,58 @@ double mean_visible_keys(const a2d_tile_desc& d, const SegList& g, double seen[8
   return mean;
 }
 
-hipError_t plan_fwd(const a2d_tile_desc& d, SegList* g, bool may_split) {
-  int cus = 0;
-  const hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
+void plan_fwd(const a2d_tile_desc& d, SegList* g, bool may_split, int cus) {
   const int64_t part = (int64_t)d.heads * d.nq * (d.hdim + 2) * sizeof(float);
   const int64_t cap = may_split ? (int64_t)kSplitBytes / part : 1;
   if (d.dtype == A2D_F32) plan_fwd_f32(d, g, cus, cap < 1 ? 1 : (int)cap);
   else plan_fwd_mfma(d, g, cus, cap < 1 ? 1 : (int)cap);
-  return hipSuccess;
+}
+
+namespace {
+void add(Route* r, const char* kernel) { r->kernel[r->kernels++] = kernel; }
+}  // namespace
+
+void route_fwd(const a2d_tile_desc& d, const SegList& g, Route* r) {
+  *r = Route{};
+  const bool f32 = d.dtype == A2D_F32, small = !f32 && g.form >= 3;
+  static const int kRows[2][5] = {{256, 128, 128, 32, 64}, {16, 32, 0, 0, 0}};     // of the forms
+  static const int kLanes[2][5] = {{1, 2, 1, 8, 4}, {4, 4, 0, 0, 0}};
+  add(r, f32 ? "fwd_f32_kernel" : small ? "fwd_small_kernel" : "fwd_mfma_kernel");
+  r->rows = kRows[f32][g.form];
+  r->lanes = kLanes[f32][g.form];
+  r->parts_q = g.parts;
+  r->parts_kv = 1;
+}
+
+void route_bwd(const a2d_tile_desc& d, const BwdParts& p, Route* r) {
+  *r = Route{};
+  r->parts_q = p.q;
+  r->parts_kv = p.kv;
+  if (d.dtype == A2D_F32) {
+    if (p.delta) add(r, "delta_kernel");
+    add(r, "bwd_f32_kernel");
+    r->rows = r->keys = 16;
+    r->lanes = 4;
+    return;
+  }
+  if (p.small) {
+    add(r, "bwd_small_kernel");
+    r->rows = r->keys = 32;
+    r->lanes = 8;
+    return;
+  }
+  const char* const kv = p.wide ? "bwd_dkdv_wide_kernel" : "bwd_dkdv_kernel";
+  if (p.one || p.keep_ds) {
+    if (p.wide || p.keep_ds) add(r, "delta_kernel");
+    add(r, p.one ? "bwd_one_kernel" : kv);
+    if (!p.one) add(r, "bwd_dq_ds_kernel");
+  } else {
+    add(r, "bwd_dq_kernel");
+    add(r, kv);
+  }
+  r->rows = p.form == 0 ? 256 : 128;
+  r->lanes = p.form == 1 ? 2 : 1;
+  r->keys = p.wide ? 256 : 128;
 }
 
 int64_t visible_keys(const a2d_tile_desc& d, const SegList& g, int64_t i) {

@@ -738,17 +738,17 @@ hipError_t bwd_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const
 // two a compute unit, and at H = 128, where the rows of O do not fit the registers beside the others, more than two (H = 128:
 // 16 x 300 x 300 43 us against 54 with the launch, 16 x 1024 x 1024 293 / 274; H = 64, 16 x 1024 x 1024 causal 83 / 85,
 // 16 x 4096 x 4096 2015 / 1987).
+bool delta_first(const a2d_tile_desc& d, const SegList& g, const BwdParts& parts, int cus) {
+  const int64_t wgs = (int64_t)d.heads * parts.q * ((d.nq + BLK - 1) / BLK) +
+                      (int64_t)(d.heads / g.group) * parts.kv * ((d.nkv + BLK - 1) / BLK);
+  return wgs > (d.hdim == 128 ? 2 : 4) * 2 * (int64_t)cus;
+}
 template <int H>
 hipError_t bwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                  const void* O, const void* dO, const float* lse, float* delta, float* dQ, float* dK, float* dV,
                  const BwdParts& parts, hipStream_t s) {
-  int cus = 0;
-  const hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
-  const int64_t wgs = (int64_t)d.heads * parts.q * ((d.nq + BLK - 1) / BLK) +
-                      (int64_t)(d.heads / g.group) * parts.kv * ((d.nkv + BLK - 1) / BLK);
-  return wgs > (H == 128 ? 2 : 4) * 2 * (int64_t)cus ? bwd_go<H, false>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s)
-                                                     : bwd_go<H, true>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s);
+  return parts.delta ? bwd_go<H, false>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s)
+                     : bwd_go<H, true>(d, g, Q, K, V, O, dO, lse, delta, dQ, dK, dV, parts, s);
 }
 
 // Numbers of parts that are tried, and what they cost beside the walks: a launch behind the tile's
@@ -830,6 +830,7 @@ BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap
   }
   p.q_first = 3 * (sq + lq) / p.q > 4 * (sk + lk) / p.kv;
   p.one = 1;
+  p.delta = delta_first(d, g, p, cus);
   return p;
 }
 

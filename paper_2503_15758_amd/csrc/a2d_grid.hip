@@ -64,16 +64,15 @@ int cap_of(size_t floats) {
 }
 size_t out_floats(const GridProblem& p, int heads) { return (size_t)heads * p.seq * p.hdim; }
 
-// The forward's shape and parts, the backward's parts, from the problem alone.  false: no device
-bool plan_forward(const GridProblem& p, const a2d_tile_desc& d, SegList* g) {
-  int cus = 0;
-  if (device_cus(&cus) != hipSuccess) return false;
+// The forward's shape and parts, the backward's parts, from the problem and the compute units (0: of the device).
+// false: no device
+bool plan_forward(const GridProblem& p, const a2d_tile_desc& d, SegList* g, int cus = 0) {
+  if (cus == 0 && device_cus(&cus) != hipSuccess) return false;
   plan_fwd_mfma(d, g, cus, cap_of((size_t)p.heads * p.seq * (p.hdim + 2)));
   return true;
 }
-bool plan_backward(const GridProblem& p, const a2d_tile_desc& d, const SegList& g, BwdParts* b) {
-  int cus = 0;
-  if (device_cus(&cus) != hipSuccess) return false;
+bool plan_backward(const GridProblem& p, const a2d_tile_desc& d, const SegList& g, BwdParts* b, int cus = 0) {
+  if (cus == 0 && device_cus(&cus) != hipSuccess) return false;
   *b = plan_bwd_mfma(d, g, false, cus, cap_of(2 * out_floats(p, p.kv_heads)), cap_of(out_floats(p, p.heads)));
   return true;
 }
@@ -191,6 +190,24 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
   trace_mark(s);
   e = launch_bwd_one(LAUNCH, d, g, Q, K, V, O, dO, lse, delta, (float*)q, (float*)k, (float*)v, bp, s);
   return e != hipSuccess || n == 0 ? e : launch_sum_grid(n, sets, p.hdim, A2D_BF16, s);
+}
+
+bool grid_route(const GridProblem& p, bool backward, int cus, Route* out) {
+  if (!grid_supported(p)) return false;
+  a2d_tile_desc d;
+  SegList g;
+  describe(p, &d, &g);
+  if (!backward) {
+    if (!plan_forward(p, d, &g, cus)) return false;
+    route_fwd(d, g, out);
+    if (g.parts > 1) out->kernel[out->kernels++] = "fix_grid_kernel";
+    return true;
+  }
+  BwdParts b;
+  if (!plan_backward(p, d, g, &b, cus)) return false;
+  route_bwd(d, b, out);
+  if (b.kv > 1 || b.q > 1) out->kernel[out->kernels++] = "sum_grid_kernel";
+  return true;
 }
 
 }  // namespace a2d

@@ -19,6 +19,20 @@ void scratch_offer(const ScratchSource* src);
 // `bytes` of a device array of the library's own, the same at every call (a2d_static.hip); NULL: not to be had
 void* static_partial_sums(size_t bytes);
 
+// How a call goes out: the kernels it launches, in order, and how they share the work.  From host arithmetic alone
+// (diagnostic: no device is needed, nothing is enqueued), by the same plans as the calls.
+struct Route {
+  const char* kernel[4];
+  int kernels;
+  int rows, lanes;               // query rows of a forward or dQ workgroup; its key lanes, which share the walk
+  int keys;                      // of a dK/dV workgroup (0: a forward)
+  int parts_q, parts_kv;         // workgroups that share a walk of the one kind (forward and dQ) and the other
+};
+enum RouteFlags { ROUTE_BACKWARD = 1, ROUTE_KEEP_DS = 2, ROUTE_SPLIT_GROUPS = 4, ROUTE_SCRATCH = 8 };
+// a tile call on a chip of `cus` compute units (0: the current device); ROUTE_SCRATCH: with scratch memory on offer
+a2d_status tile_route(const a2d_tile_desc& desc, int kv_heads, int nseg, const a2d_kv_segment* segs, int flags, int cus,
+                      Route* out);
+
 struct GridProblem {
   int heads, kv_heads, seq, side, hdim, causal, cyclic;
   float scale;
@@ -37,5 +51,8 @@ hipError_t grid_forward(const GridProblem& p, const void* Q, const void* K, cons
 // O, dO and the gradients with the problem's layouts; lse plain
 hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, const void* V, const void* O,
                          const void* dO, const float* lse, void* dQ, void* dK, void* dV, void* ws, hipStream_t s);
+
+// false: not covered, or no device to ask
+bool grid_route(const GridProblem& p, bool backward, int cus, Route* out);
 
 }  // namespace a2d

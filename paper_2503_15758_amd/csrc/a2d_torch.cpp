@@ -698,6 +698,53 @@ PyObject* grid_backward(Args a) {
   return o.give();
 }
 
+// ---- diagnostics: a call's route, from numbers alone
+PyObject* route_dict(const a2d::Route& r) {
+  PyObject* k = PyTuple_New(r.kernels);
+  if (!k) throw PythonError();
+  for (int i = 0; i < r.kernels; ++i) {
+    PyObject* name = PyUnicode_FromString(r.kernel[i]);
+    if (!name) {
+      Py_DECREF(k);
+      throw PythonError();
+    }
+    PyTuple_SET_ITEM(k, i, name);
+  }
+  PyObject* d = Py_BuildValue("{s:N,s:i,s:i,s:i,s:i,s:i}", "kernels", k, "rows", r.rows, "lanes", r.lanes, "keys", r.keys,
+                              "parts_q", r.parts_q, "parts_kv", r.parts_kv);
+  if (!d) throw PythonError();
+  return d;
+}
+
+// heads, kv_heads, nq, nkv, hdim, dtype, q_off, kv_off, causal, segments, flags, compute_units
+PyObject* tile_route(Args a) {
+  a2d_tile_desc d{};
+  d.heads = (int32_t)integer(a[0]);
+  d.nq = (int32_t)integer(a[2]);
+  d.nkv = (int32_t)integer(a[3]);
+  d.hdim = (int32_t)integer(a[4]);
+  d.dtype = dtype_code(dtype_arg(a[5]));
+  d.q_off = integer(a[6]);
+  d.kv_off = integer(a[7]);
+  d.causal = truth(a[8]);
+  d.scale = scale_of(Py_None, d.hdim);
+  const Segments segs(a[9]);
+  a2d::Route r;
+  check(a2d::tile_route(d, (int)integer(a[1]), segs.n(), segs.ptr(), (int)integer(a[10]), (int)integer(a[11]), &r));
+  return route_dict(r);
+}
+
+// heads, kv_heads, seq, side, hdim, causal, cyclic, backward, compute_units
+PyObject* grid_route(Args a) {
+  const int64_t heads = integer(a[0]), kv_heads = integer(a[1]), seq = integer(a[2]), hdim = integer(a[4]);
+  const a2d_layout plain{seq * hdim, hdim};
+  const a2d::GridProblem p{(int)heads, (int)kv_heads, (int)seq, (int)integer(a[3]), (int)hdim, truth(a[5]), truth(a[6]),
+                           scale_of(Py_None, hdim), plain, plain, plain, plain, plain, plain, plain, plain};
+  a2d::Route r;
+  if (!a2d::grid_route(p, truth(a[7]), (int)integer(a[8]), &r)) Py_RETURN_NONE;
+  return route_dict(r);
+}
+
 template <PyObject* (*F)(Args), int N>
 PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   HANDLE_TH_ERRORS
@@ -732,7 +779,7 @@ PyMethodDef g_methods[] = {
     A2D_ENTRY(partial_fwd, 10),    A2D_ENTRY(partial_fwd_norm, 9), A2D_ENTRY(partial_bwd, 16),
     A2D_ENTRY(partial_bwd_static, 11), A2D_ENTRY(fix, 5),          A2D_ENTRY(fix_norm, 4),
     A2D_ENTRY(attnfix, 4),         A2D_ENTRY(fix_bwd, 3),          A2D_ENTRY(grid_forward, 7),
-    A2D_ENTRY(grid_backward, 10),
+    A2D_ENTRY(grid_backward, 10),  A2D_ENTRY(tile_route, 12),      A2D_ENTRY(grid_route, 9),
     {"set_error_class", set_error_class, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};

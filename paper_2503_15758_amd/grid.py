@@ -155,3 +155,11 @@ def backward(Q, K, V, O, dO, lse, grid, causal=True, layout="cyclic", scale=None
         dK.index_copy_(1, idx[b], a2d.fix_bwd([parts[t][1] for t in tiles if t[1] == b], Q.dtype))
         dV.index_copy_(1, idx[b], a2d.fix_bwd([parts[t][2] for t in tiles if t[1] == b], Q.dtype))
     return dQ, dK, dV
+
+
+def route(heads, n, hdim, grid, kv_heads=None, causal=True, layout="cyclic", backward=False, compute_units=0):
+    """Diagnostic: how the launches of a whole bf16 grid in plain tensors go out (see binding.tile_route); None where the
+    tiles are calls of their own."""
+    _check_blocks(n, grid, layout)
+    return a2d._ext().grid_route(heads, kv_heads or heads, n, grid, hdim, causal, layout == "cyclic", backward,
+                                 compute_units)

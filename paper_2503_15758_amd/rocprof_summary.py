@@ -108,12 +108,6 @@ def short_name(k):
     return m.group(1) if m else None
 
 
-def family(k):
-    """The launch log's name of a kernel: bench.py cannot see which form of the dK/dV kernel a call took (128 or
-    256 keys per workgroup) and logs both as one.  The tables name the form that ran."""
-    return k.replace("bwd_dkdv_wide_", "bwd_dkdv_")
-
-
 def _find(out_dir, pattern):
     hits = glob.glob(os.path.join(out_dir, "**", pattern), recursive=True)
     if not hits:
@@ -140,7 +134,7 @@ def kernel_rows(out_dir):
     out = []
     for r, e in zip(rows, log):
         k = short_name(r["Kernel_Name"])
-        if family(k) != e["kernel"]:
+        if k != e["kernel"]:
             sys.exit("%s: trace has %s where the launch log has %s" % (out_dir, k, e["kernel"]))
         out.append((k, e["call"], e["phase"], (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3,
                     r.get("Grid_Size_X", r.get("Grid_Size", "")), r.get("Workgroup_Size_X", r.get("Workgroup_Size", ""))))
@@ -165,7 +159,7 @@ def counter_rows(out_dir):
         vals = list(by_dispatch.values())
         if len(vals) != len(log):
             sys.exit("%s: %d dispatches carry %s, the launch log has %d" % (out_dir, len(vals), ctr, len(log)))
-        out[ctr] = [(k, e["call"], e["phase"], v) for (k, v), e in zip(vals, log) if family(k) == e["kernel"]]
+        out[ctr] = [(k, e["call"], e["phase"], v) for (k, v), e in zip(vals, log) if k == e["kernel"]]
         if len(out[ctr]) != len(log):
             sys.exit("%s: kernel names of %s do not follow the launch log" % (out_dir, ctr))
     return out
@@ -303,7 +297,7 @@ def tables(args):
 
 def read_traffic(workload, profiles_dir=None):
     """(dict name -> bytes, source hash the table was measured on) from profiles/<workload>_hbm_traffic.txt,
-    or ({}, None) when there is no such file.  Kernels by the launch log's names (family())."""
+    or ({}, None) when there is no such file."""
     path = os.path.join(profiles_dir or os.path.join(ROOT, "profiles"), "%s_hbm_traffic.txt" % workload)
     if not os.path.exists(path):
         return {}, None
@@ -311,7 +305,7 @@ def read_traffic(workload, profiles_dir=None):
     for line in open(path):
         p = line.split()
         if len(p) == 3 and p[0] == "traffic_bytes":
-            table[family(p[1])] = int(p[2])
+            table[p[1]] = int(p[2])
         elif len(p) == 2 and p[0] == "source_sha256":
             sha = p[1]
     return table, sha

@@ -1,0 +1,73 @@
+"""How calls go out (binding.tile_route, grid.route: the library's own plans, on the CPU): the rules that were measured, and that
+the GPU tests' cases take the kernels they are there for.  256 compute units, as on MI355X."""
+import random
+
+import pytest
+import torch
+
+CUS = 256
+
+
+@pytest.fixture(scope="module")
+def a2d():
+    from paper_2503_15758_amd import binding
+    binding._ext()
+    return binding
+
+
+def tile(a2d, heads, nq, nkv, H, **more):
+    return a2d.tile_route(heads, nq, nkv, H, compute_units=CUS, **more)
+
+
+def test_keeping_ds_does_not_change_dk_dv(a2d):
+    """The choice for dK and dV is the same with A2D_DESC_KEEP_DS as without: their bits are part of the contract."""
+    rng, kept = random.Random(5), 0
+    for _ in range(400):
+        kv = int(2 ** rng.uniform(0, 7))
+        heads = kv * rng.choice([1, 1, 2, 4])
+        nq, nkv = (int(2 ** rng.uniform(5, 13)) for _ in range(2))
+        more = dict(kv_heads=kv, causal=rng.random() < 0.5, q_off=rng.randint(0, nkv), backward=True, scratch=rng.random() < 0.7)
+        plain, keep = (tile(a2d, heads, nq, nkv, 128, ds_handover=k, **more) for k in (False, True))
+        case = (heads, nq, nkv, more)
+        assert ("bwd_small_kernel" in plain["kernels"]) == ("bwd_small_kernel" in keep["kernels"]), case
+        assert (plain["keys"], plain["parts_kv"]) == (keep["keys"], keep["parts_kv"]), case
+        kept += "bwd_dq_ds_kernel" in keep["kernels"]
+    assert kept > 50
+
+
+def test_route_refuses_what_the_calls_refuse(a2d):
+    with pytest.raises(a2d.A2DError):
+        tile(a2d, 4, 100, 100, 72)
+    with pytest.raises(a2d.A2DError):
+        tile(a2d, 4, 100, 100, 64, kv_heads=3)
+    with pytest.raises(a2d.A2DError):
+        tile(a2d, 4, 100, 100, 64, segments=[(0, 99)])
+    from paper_2503_15758_amd import grid as g2d
+    assert g2d.route(4, 128, 72, 2, compute_units=CUS) is None
+
+
+def test_parts_need_scratch_memory(a2d):
+    for dtype in (torch.bfloat16, torch.float32):
+        for backward in (False, True):
+            shared, alone = (tile(a2d, 1, 60, 20000, 128, dtype=dtype, backward=backward, scratch=s) for s in (True, False))
+            assert shared["parts_q"] > 1 and alone["parts_q"] == alone["parts_kv"] == 1
+            assert shared["kernels"][-1] == ("sum_parts_kernel" if backward else "fix_kernel")
+            assert "sum_parts_kernel" not in alone["kernels"] and "fix_kernel" not in alone["kernels"]
+
+
+@pytest.mark.parametrize("workload", ["c2", "c3", "c4", "c5"])
+def test_bench_names_the_kernels_of_the_library(a2d, workload, monkeypatch):
+    """What bench.py logs for a call, and reports times of, is what the library launches: the form of the dK/dV kernel too."""
+    import bench
+    from paper_2503_15758_amd import synth
+    route = a2d.tile_route
+    monkeypatch.setattr(a2d, "tile_route", lambda *x, **more: route(*x, **dict(more, compute_units=CUS)))
+    w = synth.WORKLOADS[workload]
+    for recompute in (False, True):
+        got = [bench.call_kernels.__wrapped__("partial_bwd_" + tag, w, recompute) for tag in ("full", "diag")]
+        want = ["delta_kernel", "bwd_one_kernel"] if workload == "c2" else \
+            ["bwd_dq_kernel", "bwd_dkdv_wide_kernel"] if recompute else \
+            ["delta_kernel", "bwd_dkdv_wide_kernel", "bwd_dq_ds_kernel"]
+        if w.backward:
+            assert got == [want, want]
+        assert bench.call_kernels.__wrapped__("partial_fwd_full", w, recompute) == ["fwd_mfma_kernel"]
