@@ -441,10 +441,16 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 }  // namespace
 
 // How a backward goes out (steps in microseconds; H = 64, 96, 128):
-//   - in one launch, recomputing (a2d_bwd_one.hip), where its workgroups come to at most six turns of the chip and for whole
-//     grids: against dQ and dK/dV one after the other 0.6 of the time at a few workgroups, 0.8-0.95 at one to three turns,
-//     the same at four (1 x 161 x 308 20 -> 11 us, 16 x 1024 x 1024 74 -> 50, 16 x 2048 x 2048 144 -> 130; from some ten
-//     turns on 1 % slower).
+//   - in one launch, recomputing (a2d_bwd_one.hip), for whole grids, and where its workgroups come to at most six turns of the
+//     chip and no engine's share comes out badly: against dQ and dK/dV one after the other 0.6 of the time at a few
+//     workgroups, 0.8-0.95 at one to three turns, the same at four (1 x 161 x 308 20 -> 11 us, 16 x 1024 x 1024 74 -> 50,
+//     16 x 2048 x 2048 144 -> 130; from some ten turns on 1 % slower).  The second kind does not fill what the first leaves of
+//     its last turn where the shader engines are dealt unlike numbers of the long walks (dealt_time): 72/18 heads x 651 x 861,
+//     H = 64 88 us in one launch, 77 in two; 6 x 9048 x 1290, H = 128 197 / 174; 51 x 2015 x 438, H = 64 96 / 88; 9 x 563 x
+//     2404, H = 80 50 / 43.  kOneUs is fitted to 770 drawn shapes of up to six turns, on the
+//     side of one launch: where the walks are even the choice is 0.1 % off the better one in the mean (one launch always: 0.4 %,
+//     23 % at worst).  Of uneven walks 3 % of the shapes would be 3-9 % faster in two and neither model tells which (84 x
+//     1117 x 2587, H = 96, causal 167 / 154): 0.3 % in the mean.
 //   - with dS kept, where the caller allows it and the model says so: at H = 128 only.  Below, recomputing S and dP costs
 //     less than writing and reading dS at every size (64 x 4096 x 4096 H = 64 1044 against 1157 us, H = 80 1268 / 1320,
 //     16 x 2048 x 2048 H = 64 79 / 103).  At H = 128 it gains 5-9 % from two turns of unmasked tiles on (16 x 4096 x 4096 414
@@ -457,6 +463,7 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q) {
   constexpr double kKvUs[3] = {0.75, 0.85, 1.0}, kWideUs[3] = {1.0, 1.2, 1.5};
   constexpr double kDqUs[3] = {1.6, 1.75, 2.1};
+  constexpr double kOneUs[3] = {1.03, 1.0, 0.85};      // the model of two launches on the scale of the one of one
   const int hx = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, kv_heads = d.heads / g.group, side = g.b.side ? g.b.side : 1;
   // (a grid's walks are `side` times as long; under the mask of every length down to a few steps)
   const bool grid = g.b.side > 0, uneven = grid ? d.causal != 0 : g.by_size != 0;
@@ -466,57 +473,68 @@ BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cu
   const double kv_mean = !uneven ? rows : grid ? 0.5 * rows + side : rows * seen / d.nkv + 1;
   const double most = grid ? (double)side * ((d.nkv + BKS - 1) / BKS) + 0.2 : (double)visible_keys(d, g, d.nq - 1) / BKS + 0.2;
   const double mean = !uneven ? most : grid ? 0.5 * most + 0.5 * (g.b.cyclic ? side : 1) : seen / BKS + 0.2;
-  ds = ds && d.hdim == 128;
-  BwdParts p = {}, one = {};
-  double one_us = 0;
-  const int64_t wgs = (int64_t)side * (kv_heads * (int64_t)((d.nkv + 255) / 256) + d.heads * (int64_t)((d.nq + 255) / 256));
-  if (grid || wgs <= 6 * (int64_t)cus) {
-    const BwdWalks w = {kv_mean < rows ? kv_mean : rows, rows, mean < most ? mean : most, most, uneven};
-    one_us = plan_bwd_one(d, g, w, cus, cap_kv, cap_q, &one);
-    if (!ds || one.small) return one;
-  }
   const double kv_part_us = (double)kv_heads * d.nkv * d.hdim * 16 / 4.5e6;
   const auto walk = [&](int w) {                       // 128 keys per workgroup, 256
     const int keys = w ? 256 : DK_KEYS;
     return WalkModel{(int64_t)kv_heads * ((d.nkv + keys - 1) / keys), cus, kv_mean, rows, (w ? kWideUs : kKvUs)[hx],
                      w ? 10.0 : 8.0, 0, 0, nullptr, 0};
   };
-  double kv_us[2];
-  if (one.one) {
-    p.wide = one.wide;
-    p.kv = one.kv;
-  } else {
-    int kv_parts[2];
-    for (int w = 0; w < 2; ++w) kv_parts[w] = best_parts(walk(w), cap_kv, 4.0, kv_part_us, &kv_us[w]);
-    p.wide = kv_us[1] < kv_us[0] && d.scale > 1e-30f;  // (it takes lse / scale, which has to stay finite)
-    p.kv = kv_parts[p.wide];
-  }
-  p.keep_ds = ds;
   const double* sorted = g.by_size ? of_rows : nullptr;
   const double fixed = 7.0;
   const int64_t heads = d.heads, b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128);
   const double part_us = (double)heads * d.nq * d.hdim * 8 / 4.5e6;
   // (dS comes at the rate of the memory: a full chip's steps take longer)
   const auto full = [&](int64_t n) { return n < cus ? (double)n / cus : 1.0; };
-  const double step = ds ? 0.7 + 0.9 * full(b256) : kDqUs[hx];
-  const WalkModel q[3] = {{b256, cus, mean, most, step, fixed, 0, 0, sorted, 1.0 / BKS},
-                          {b128, cus, mean / 2, most / 2, step * 1.2, fixed + 0.5, 0, 0, sorted, 0.5 / BKS},
-                          {b128, cus, mean, most, step * 0.74, fixed, step, fixed + 0.5, nullptr, 0}};
-  double least = 0;
-  for (int f = 0; f < 3; ++f) {
-    double t;
-    const int z = best_parts(q[f], cap_q, p.kv > 1 ? 1.0 : 4.0, part_us, &t);   // (one launch sums both)
-    if (f == 0 || t < (p.form == 0 ? 0.98 : 1.0) * least) { least = t; p.form = f; p.q = z; }
+  const auto rows_of = [&](bool from_ds, BwdParts* p) {    // shape and parts of the dQ launch; its time
+    const double step = from_ds ? 0.7 + 0.9 * full(b256) : kDqUs[hx];
+    const WalkModel q[3] = {{b256, cus, mean, most, step, fixed, 0, 0, sorted, 1.0 / BKS},
+                            {b128, cus, mean / 2, most / 2, step * 1.2, fixed + 0.5, 0, 0, sorted, 0.5 / BKS},
+                            {b128, cus, mean, most, step * 0.74, fixed, step, fixed + 0.5, nullptr, 0}};
+    double least = 0;
+    for (int f = 0; f < 3; ++f) {
+      double t;
+      const int z = best_parts(q[f], cap_q, p->kv > 1 ? 1.0 : 4.0, part_us, &t);   // (one launch sums both)
+      if (f == 0 || t < (p->form == 0 ? 0.98 : 1.0) * least) { least = t; p->form = f; p->q = z; }
+    }
+    return least;
+  };
+
+  BwdParts plan = {};                                  // recomputing: dQ, then dK/dV ...
+  double plan_us = 0;
+  if (!grid) {
+    double kv_us[2];
+    int kv_parts[2];
+    for (int w = 0; w < 2; ++w) kv_parts[w] = best_parts(walk(w), cap_kv, 4.0, kv_part_us, &kv_us[w]);
+    plan.wide = kv_us[1] < kv_us[0] && d.scale > 1e-30f;   // (it takes lse / scale, which has to stay finite)
+    plan.kv = kv_parts[plan.wide];
+    plan_us = kv_us[plan.wide];
+    plan_us += rows_of(false, &plan);
   }
-  if (one.one) {                                       // (a full chip clocks lower, most so beside the dS stores)
-    WalkModel kv = walk(p.wide);
-    const double f = full(kv.blocks * p.kv);
-    kv.step = p.wide ? 1.3 + 0.8 * f * f : 1.1;
-    kv.tail = 0.3;
-    const double kept = 8.0 + walk_time(kv, p.kv) + (p.kv > 1 ? 4.0 + p.kv * kv_part_us : 0) + least;
-    if (one_us * (wgs >= cus ? 1.08 : 1.0) <= kept) return one;
+  const int64_t wgs = (int64_t)side * (kv_heads * (int64_t)((d.nkv + 255) / 256) + d.heads * (int64_t)((d.nq + 255) / 256));
+  if (grid || wgs <= 6 * (int64_t)cus) {               // ... or both in one launch
+    const BwdWalks w = {kv_mean < rows ? kv_mean : rows, rows, mean < most ? mean : most, most, uneven};
+    BwdParts one = {};
+    double dealt_us = 0;
+    const double one_us = plan_bwd_one(d, g, w, cus, cap_kv, cap_q, &one, &dealt_us);
+    plan_us /= kOneUs[hx];
+    if (grid || one.small || dealt_us <= plan_us) {
+      plan = one;
+      plan_us = one_us;
+    }
   }
-  return p;
+  if (!ds || d.hdim != 128 || plan.small) return plan;
+  BwdParts kept = {};
+  kept.wide = plan.wide;
+  kept.kv = plan.kv;
+  kept.keep_ds = 1;
+  const double dq_us = rows_of(true, &kept);
+  if (wgs > 6 * (int64_t)cus) return kept;
+  WalkModel kv = walk(kept.wide);                      // (a full chip clocks lower, most so beside the dS stores)
+  const double f = full(kv.blocks * kept.kv);
+  kv.step = kept.wide ? 1.3 + 0.8 * f * f : 1.1;
+  kv.tail = 0.3;
+  const double kept_us = 8.0 + walk_time(kv, kept.kv) + (kept.kv > 1 ? 4.0 + kept.kv * kv_part_us : 0) + dq_us;
+  return plan_us * (wgs >= cus ? 1.08 : 1.0) <= kept_us ? plan : kept;
 }
 
 // ds_ws != NULL: a workspace of bwd_ds_bytes(d, g) bytes; the dK/dV kernel leaves dS there and the

@@ -72,8 +72,9 @@ hipError_t go_h(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* 
 // model of the launch, fitted to 60 shapes x up to 100 choices each (1 x 161 x 308 to 32 x 4096 x 4096, grids of 350
 // to 8192 tokens); its choice is 1 % off the best of them in the mean.  Parts of the two kinds are tried in step: of one from a
 // list, of the other the fewest that make its walks no longer.
+// dealt: the time of the chosen one with its workgroups dealt to the chip's shader engines (see dealt_time); NULL: not asked.
 double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w, int cus, int cap_kv, int cap_q,
-                    BwdParts* best) {
+                    BwdParts* best, double* dealt) {
   constexpr double kPairUs[3] = {0.81, 0.94, 1.34}, kWideUs[3] = {0.95, 1.05, 1.61}, kRowUs[3] = {1.57, 1.67, 2.68};
   constexpr double kPairFix = 7, kWideFix = 6.1, kRowFix = 5.5, kLane = 1.2, kLaneFix = 0.45, kTail = 0.26, kMerge = 3.7,
                    kDelta = 2.9, kIdle = 0.93;
@@ -81,7 +82,8 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
   const int hx = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, kv_heads = d.heads / g.group, side = g.b.side ? g.b.side : 1;
   const double part_kv = (double)side * kv_heads * d.nkv * d.hdim * 16 / 4.5e6;     // written and read back at 4.5 TB/s
   const double part_q = (double)side * d.heads * d.nq * d.hdim * 8 / 4.5e6;
-  double least = 0;
+  double least = 0, rest = 0;
+  Kind first = {}, second = {};
   *best = BwdParts{};
   for (int wide = 0; wide < 2; ++wide) {
     if (wide && !(d.scale > 1e-30f)) continue;             // (it takes lse / scale, which has to stay finite)
@@ -109,10 +111,15 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
         const Kind kv = {n_kv * zk, len(w.kv_mean, zk, kv_step * busy, kv_fix, 1), len(w.kv_most, zk, kv_step * busy, kv_fix, 1)};
         const Kind q = {n_q * zq, len(w.q_mean, zq, q_step * busy, q_fix, q_least), len(w.q_most, zq, q_step * busy, q_fix, q_least)};
         const bool q_first = q.most > kv.most;
-        const double t = before + (zk > 1 || zq > 1 ? kMerge : 0) + (zk > 1 ? zk * part_kv : 0) + (zq > 1 ? zq * part_q : 0) +
-                         (q_first ? one_time(q, kv, cus, w.uneven, kTail) : one_time(kv, q, cus, w.uneven, kTail));
+        const double more = before + (zk > 1 || zq > 1 ? kMerge : 0) + (zk > 1 ? zk * part_kv : 0) + (zq > 1 ? zq * part_q : 0);
+        const double t = more + (q_first ? one_time(q, kv, cus, w.uneven, kTail) : one_time(kv, q, cus, w.uneven, kTail));
         if (best->one && t >= least) return;
         least = t;
+        rest = more;
+        const Kind kv_ids = {xcd_grid(kv_heads * zk, side * ((d.nkv + keys - 1) / keys)), kv.mean, kv.most};
+        const Kind q_ids = {xcd_grid(kv_heads * zq, side * g.group * ((d.nq + rows - 1) / rows)), q.mean, q.most};
+        first = q_first ? q_ids : kv_ids;
+        second = q_first ? kv_ids : q_ids;
         *best = BwdParts{zk, zq, form, wide, 1, q_first};
       };
       for (int z : kParts) {
@@ -130,6 +137,7 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
       consider(1, 1);
     }
   }
+  if (dealt) *dealt = rest + dealt_time(first, second, cus, w.uneven, kTail);
   // 32 rows or keys a workgroup (a2d_bwd_small.hip; a step is a round of 256).  Fitted to 92 shapes of 1 x 41 x 80 to 16 x 512 x 512,
   // 1 x 4096 x 4096: taken up to some 256 of them with walks of 2048, 512 with walks of 512 (under a mask 1024); 1.27 times as
   // fast in the mean there as without that form, 0.5 % off the better of the two.

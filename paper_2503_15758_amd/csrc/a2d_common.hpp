@@ -227,6 +227,10 @@ struct Kind {
   double mean, most;         // us of a workgroup, on average and at most
 };
 double one_time(const Kind& a, const Kind& b, int slots, bool uneven, double tail);
+// The same of a chip that deals its workgroups (the idle ones of the kernels' placement among them) in turn to shader engines
+// of kEngineSlots compute units, whatever these still have to do: the time of the engine that comes out worst.
+constexpr int kEngineSlots = 8;
+double dealt_time(const Kind& a, const Kind& b, int slots, bool uneven, double tail);
 // keys that query row i of the tile sees
 int64_t visible_keys(const a2d_tile_desc& d, const SegList& g, int64_t i);
 // of 8 rows spread over the tile, last rows first; returns the mean
@@ -266,7 +270,7 @@ struct BwdWalks {
   bool uneven;
 };
 double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w, int cus, int cap_kv, int cap_q,
-                    BwdParts* best);
+                    BwdParts* best, double* dealt);
 BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap_kv, int cap_q);
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q);
 

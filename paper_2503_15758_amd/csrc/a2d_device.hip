@@ -134,6 +134,18 @@ double one_time(const Kind& a, const Kind& b, int slots, bool uneven, double tai
   return end;
 }
 
+double dealt_time(const Kind& a, const Kind& b, int slots, bool uneven, double tail) {
+  if (a.n + b.n <= slots) return a.most;
+  const int engines = slots < kEngineSlots ? 1 : slots / kEngineSlots, each = slots / engines;
+  double worst = 0;
+  for (int i = 0; i < engines; ++i) {                      // workgroups i, i + engines, ..
+    const int64_t na = (a.n - i + engines - 1) / engines, nb = (a.n + b.n - i + engines - 1) / engines - na;
+    const double t = one_time(Kind{na, a.mean, a.most}, Kind{nb, b.mean, b.most}, each, uneven, tail);
+    if (t > worst) worst = t;
+  }
+  return worst;
+}
+
 double mean_visible_keys(const a2d_tile_desc& d, const SegList& g, double seen[8]) {
   double mean = 0;
   for (int i = 0; i < 8; ++i) {

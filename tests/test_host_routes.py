@@ -35,6 +35,42 @@ def test_keeping_ds_does_not_change_dk_dv(a2d):
     assert kept > 50
 
 
+# heads, kv_heads, nq, nkv, H, causal, q_off; us on MI355X in one launch and in two (dQ, then dK/dV)
+MEASURED = [
+    (51, 51, 2015, 438, 64, False, 0, 95.9, 87.8),
+    (51, 51, 3000, 1185, 64, False, 0, 226.0, 215.1),
+    (16, 16, 4096, 4096, 64, False, 0, 265.3, 261.7),
+    (72, 18, 651, 861, 64, False, 0, 87.7, 76.6),
+    (6, 6, 9048, 1290, 128, False, 0, 196.6, 173.6),
+    (8, 1, 11144, 5593, 64, False, 0, 603.1, 557.3),
+    (18, 9, 1125, 1107, 80, False, 0, 80.7, 60.6),
+    (72, 72, 575, 304, 64, True, 246, 44.6, 35.6),
+    (46, 23, 541, 1027, 128, False, 0, 94.3, 77.2),
+    (9, 9, 563, 2404, 80, False, 0, 50.2, 42.9),
+    (7, 7, 7700, 1656, 64, False, 0, 149.2, 121.7),
+    (14, 14, 4494, 358, 64, True, 0, 54.8, 48.7),
+    (16, 16, 1024, 1024, 128, False, 0, 50.3, 71.1),
+    (16, 16, 2048, 2048, 128, False, 0, 129.3, 136.7),
+    (32, 32, 1999, 2777, 80, True, 778, 171.8, 174.6),
+    (7, 7, 780, 426, 80, False, 0, 15.2, 27.3),
+    (31, 31, 1897, 1815, 80, True, 0, 103.4, 120.5),
+    (6, 3, 4206, 2488, 64, False, 0, 85.4, 98.9),
+    (48, 6, 1282, 2778, 128, False, 0, 389.0, 516.0),
+    (84, 84, 4318, 80, 80, False, 0, 118.5, 128.3),
+    (2, 2, 146, 5176, 128, False, 0, 24.0, 35.0),
+]
+
+
+@pytest.mark.parametrize("case", MEASURED, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))
+def test_one_launch_only_where_it_is_not_slower(a2d, case):
+    heads, kvh, nq, nkv, H, causal, q_off, one, two = case
+    for scratch in (True, False):                  # (without scratch memory the walks are whole: the rule holds, the times do not)
+        kernels = tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, q_off=q_off, backward=True, scratch=scratch)["kernels"]
+        assert ("bwd_dq_kernel" in kernels) == (not {"bwd_one_kernel", "bwd_small_kernel"} & set(kernels))
+        if scratch:
+            assert ("bwd_dq_kernel" in kernels) == (two < one), kernels
+
+
 def test_route_refuses_what_the_calls_refuse(a2d):
     with pytest.raises(a2d.A2DError):
         tile(a2d, 4, 100, 100, 72)
