@@ -254,9 +254,15 @@ __device__ __forceinline__ void small_rows(
       of[x] = *reinterpret_cast<const bf16x8*>(op + 16 * x);
     }
     lse2 = l == -INFINITY ? INFINITY : l * kLog2e;           // +inf: exp2(s - lse2) = 0
+    float t[8];                                    // (the order of sums of dK / dV, see dq_rows: one delta for both)
 #pragma unroll
-    for (int x = 0; x < KS; ++x) del = dot8(__builtin_bit_cast(u32x4, of[x]), __builtin_bit_cast(u32x4, f2[x]), del);
-    del += __shfl_xor(del, 32, 64);
+    for (int x = 0; x < 8; ++x) {
+      t[x] = 0.f;
+      if (x >= KS) continue;
+      t[x] = dot8(__builtin_bit_cast(u32x4, of[x]), __builtin_bit_cast(u32x4, f2[x]), 0.f);
+      t[x] += __shfl_xor(t[x], 32, 64);
+    }
+    del = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
   }
 
   f32x16 acc[CT], acc2[KV ? CT : 1];               // dQ, or dK; dV

@@ -85,3 +85,40 @@ def test_routes(case):
     recomputed, kept = _check(case, False), _check(case, True)
     assert torch.equal(recomputed[1], kept[1]) and torch.equal(recomputed[2], kept[2])
     assert _rel(kept[0], recomputed[0].double()) < 1e-2 or (kept[0] - recomputed[0]).abs().max() < 2e-2
+
+
+# heads, nq, nkv: few rows; in one launch of 128 and of 256 keys a workgroup; dQ, then dK / dV, or with dS kept
+DELTA = [(8, 40, 33), (6, 300, 500), (60, 700, 129), (90, 256, 700), (800, 33, 129)]
+
+
+@pytest.mark.parametrize("H", [64, 80, 96, 128])
+@pytest.mark.parametrize("case", DELTA, ids=lambda c: "%dx%dx%d" % c)
+def test_one_delta_for_all_gradients(case, H):
+    """dQ and dK use the same bits of delta = rowsum(dO o O), shown by products that cancel, so that its value is that of the
+    order of its sums.  Row 0 sees key 0 alone, with probability 1 (q.k scale = lse = 4, a power of two: no rounding); the other
+    rows' probabilities and V are zero, so that in 64 columns dQ of row 0 and dK of key 0 are both -scale bf16(delta)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_15758_amd import binding as a2d
+    heads, nq, nkv = case
+    scale, gen, some = 2.0 ** -4, torch.Generator(device="cuda"), 0
+    print("delta case", case, H, flush=True)
+    make = lambda n: torch.randn(heads, n, H, generator=gen, device="cuda")
+    Q, K = torch.ones(heads, nq, H, device="cuda", dtype=BF), torch.ones(heads, nkv, H, device="cuda", dtype=BF)
+    Q[..., 64:] = 0
+    V = torch.zeros_like(K)
+    lse = torch.full((heads, nq), 1e30, device="cuda")
+    lse[:, 0] = 64 * scale
+    for seed in range(4):
+        gen.manual_seed(seed)
+        dO, O = make(nq).to(BF), (make(nq) * 2.0 ** torch.randint(-20, 20, (heads, nq, H), generator=gen, device="cuda")).to(BF)
+        O[..., H // 2:] = -O[..., :H // 2]                       # exact sum: zero
+        dO[..., H // 2:] = dO[..., :H // 2]
+        order = torch.randperm(H, generator=gen, device="cuda")
+        O, dO = O[..., order].contiguous(), dO[..., order].contiguous()
+        for keep in (False, True):
+            dQ, dK, _ = a2d.partial_bwd(Q, K, V, O, dO, lse, 0, 0, True, scale, ds_handover=keep)
+            some += int((dQ[:, 0, 0] != 0).sum())
+            assert not dQ[:, 1:].any()
+            assert torch.equal(dQ[:, 0, :64], dK[:, 0, :64]), "dQ %s, dK %s" % (dQ[:4, 0, 0], dK[:4, 0, 0])
+    assert some > 0
