@@ -129,7 +129,8 @@ typedef struct {
  * multiples of 64 keys, and less than 4 GiB of dS per key/value head (all the query heads of its
  * group together); where it does not (this query then returns the minimum size for a plain tile)
  * the flag is accepted and the recomputing kernels run.  Same results up to fp32 summation
- * order (dK and dV the same bits).
+ * order (dK and dV the same bits).  At present it is taken for tiles of H = 128 only; the size is that
+ * of the hand-over for every head size, and a caller with H < 128 saves the memory by leaving the flag out.
  * A2D_OP_PARTIAL_BWD_SPLIT: the size a2d_partial_bwd_gqa needs with A2D_TILE_SPLIT_GROUPS: that of
  * A2D_OP_PARTIAL_BWD_DS plus fp32 partial dK / dV buffers (at most 2 * heads * nkv * H floats);
  * `k` = the number of key/value heads.

@@ -215,9 +215,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 
   // ---- K staging: thread moves chunk (tid & 15) of rows (tid >> 4) + ST_ROWS p of the 64-row tile
   constexpr int ST_ROWS = DQ_THREADS / 16, ST_N = BKS / ST_ROWS;
+  static_assert(H == 128, "a thread's chunk is one of sixteen of the row");
   const int st_row = tid >> 4, st_ch = tid & 15;
-  const int ld_ch = min(st_ch, H / 8 - 1);
-  const bool ch_data = st_ch * 8 < H, ch_tile = st_ch * 8 < HD;
   const gptr_t k_base = uniform_gptr(K);
   const unsigned k_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lk.row * 2);
   u32x4 kreg[ST_N];
@@ -225,17 +224,13 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 #pragma unroll
     for (int p = 0; p < ST_N; ++p) {
       const int row = min(id * BKS + st_row + ST_ROWS * p, d.nkv - 1);   // rows past the end re-read the last key
-      kreg[p] = gload_b128(k_base, __umul24((unsigned)row, k_row_bytes) + ld_ch * 16);
+      kreg[p] = gload_b128(k_base, __umul24((unsigned)row, k_row_bytes) + st_ch * 16);
     }
   };
   auto store_k = [&](int buf) {
     char* b = lds + buf * DUAL64_BYTES;
-    if (HD == 128 || ch_tile) {
-      const u32x4 zero = {0, 0, 0, 0};
 #pragma unroll
-      for (int p = 0; p < ST_N; ++p)
-        *reinterpret_cast<u32x4*>(b + dual_store_off(st_row + ST_ROWS * p, st_ch)) = (HD == 128 || ch_data) ? kreg[p] : zero;
-    }
+    for (int p = 0; p < ST_N; ++p) *reinterpret_cast<u32x4*>(b + dual_store_off(st_row + ST_ROWS * p, st_ch)) = kreg[p];
   };
   u32x4 ds[DSQ_SETS][4];
   auto load_ds = [&](int id, auto set_tag) {
@@ -325,7 +320,8 @@ bool bwd_mfma_supported(const a2d_tile_desc& d) {
 }
 
 // Bytes of the dS workspace of a tile (0 when the hand-over does not apply: a sub-block that does
-// not start at a multiple of 64 keys, or 4 GiB or more per key/value head)
+// not start at a multiple of 64 keys, or 4 GiB or more per key/value head).  Below H = 128 it is not used
+// (plan_bwd_mfma); its size is part of the interface, so that callers' sizes hold whatever the plan does.
 size_t bwd_ds_bytes(const a2d_tile_desc& d, const SegList& g) {
   if (!bwd_mfma_supported(d)) return 0;
   for (int s = 0; s < g.n; ++s)

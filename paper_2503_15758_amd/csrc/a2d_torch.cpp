@@ -436,7 +436,8 @@ void gradients(Outputs* o, const Saved& x, PyObject* out) {
 PyObject* partial_bwd(Args a) {
   const Saved x(a);
   if (!x.match()) fail(A2D_ERR_INVALID_ARG, "O, dO, lse do not match Q (lse: plain fp32 [heads][nq])");
-  const bool keep_ds = truth(a[14]), acc = truth(a[13]);
+  // (the library keeps dS at H = 128 only: below, no memory is taken for it)
+  const bool keep_ds = truth(a[14]) && (a[11] != Py_None || x.Q.size(2) == 128), acc = truth(a[13]);
   a2d_tile_desc d = descriptor(x.Q, x.K, x.V, a + 6, keep_ds ? A2D_DESC_KEEP_DS : 0);
   d.lo = layout(x.O);
   d.ldo = layout(x.dO);

@@ -120,8 +120,8 @@ def forward(Q, K, V, grid, causal=True, layout="cyclic", scale=None, streams=4, 
 def backward(Q, K, V, O, dO, lse, grid, causal=True, layout="cyclic", scale=None, streams=4,
              ds_handover=True):
     """Alg. 3: dQ, dK, dV [heads][n][H] in the input dtype from the saved O and lse.
-    ds_handover: a tile call may keep dS for the dQ contraction instead of recomputing the scores (about 2 T^2
-    bytes per head and stream more).  False: every tile is a call of its own that recomputes them."""
+    ds_handover: a tile call may keep dS for the dQ contraction instead of recomputing the scores (at H = 128: about
+    2 T^2 bytes per head and stream more).  False: every tile is a call of its own that recomputes them."""
     heads, n, H = Q.shape
     scale = float(scale if scale is not None else 1.0 / math.sqrt(H))
     _check_blocks(n, grid, layout)
@@ -140,6 +140,7 @@ def backward(Q, K, V, O, dO, lse, grid, causal=True, layout="cyclic", scale=None
              for t in tiles}
     st = _Streams(streams)
     # one workspace per stream: calls that share a workspace must be ordered on one stream
+    ds_handover = ds_handover and H == 128             # (the library keeps dS there only)
     need = a2d.workspace_bytes(a2d.tile_desc(Qb[0], Kb[0], 0, 0, causal, scale),
                                a2d.OP_PARTIAL_BWD_DS if ds_handover else a2d.OP_PARTIAL_BWD)
     ws = [torch.empty(need, dtype=torch.uint8, device=Q.device) for _ in st.side]

@@ -122,3 +122,24 @@ def test_one_delta_for_all_gradients(case, H):
             assert not dQ[:, 1:].any()
             assert torch.equal(dQ[:, 0, :64], dK[:, 0, :64]), "dQ %s, dK %s" % (dQ[:4, 0, 0], dK[:4, 0, 0])
     assert some > 0
+
+
+@pytest.mark.parametrize("H", [64, 80, 96, 128])
+def test_no_memory_for_a_ds_that_is_not_kept(H):
+    """ds_handover without a workspace: memory for dS (64 MiB here) is taken where it may be kept, at H = 128."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_15758_amd import binding as a2d
+    heads, n = 8, 2048
+    make = lambda: torch.randn(heads, n, H, device="cuda").to(BF)
+    Q, K, V, O, dO = (make() for _ in range(5))
+    lse = torch.full((heads, n), 8.0, device="cuda")
+    took = {}
+    for keep in (False, True):
+        a2d.partial_bwd(Q, K, V, O, dO, lse, ds_handover=keep)
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        a2d.partial_bwd(Q, K, V, O, dO, lse, ds_handover=keep)
+        took[keep] = torch.cuda.max_memory_allocated() - before
+    assert (took[True] - took[False] >= 2 * heads * n * n) == (H == 128) and (H == 128 or took[True] == took[False]), took
