@@ -1,6 +1,6 @@
 """The whole-grid launches (many tiles per launch, blocks read in place) against the per-tile calls of the same
 grid, which test_gpu_parity.py checks against the oracle: ragged blocks, grouped heads, strided inputs, every
-kind of grid, and a grid whose dS does not fit one pass of the workspace."""
+kind of grid."""
 import math
 
 import pytest
@@ -18,10 +18,10 @@ CASES = [
     (2, 1, 200, 3, 80, False, "contiguous", True),    # all tiles, packed inputs
     (8, 2, 65, 7, 64, True, "cyclic", True),
     (5, 5, 300, 1, 128, True, "contiguous", False),   # a grid of one tile
-    (64, 64, 2048, 2, 64, False, "cyclic", False),    # dS of three of the four tiles fits the workspace
-    (2, 2, 700, 2, 128, True, "contiguous", False),   # few tiles: the walks are split
-    (8, 1, 90, 4, 96, True, "cyclic", False),         # ... over the heads of a group
-    (30, 30, 300, 3, 128, True, "contiguous", False),  # dK / dV in workgroups of 256 keys
+    (64, 64, 2048, 2, 64, False, "cyclic", False),    # long rows, many heads
+    (2, 2, 700, 2, 128, True, "contiguous", False),   # few tiles
+    (8, 1, 90, 4, 96, True, "cyclic", False),         # ... the heads of a group
+    (30, 30, 300, 3, 128, True, "contiguous", False),
     (60, 30, 270, 2, 80, True, "cyclic", True),
 ]
 

@@ -18,10 +18,30 @@ CASES = [
     (2, 1, 64, 3, 80),
     (4, 4, 65, 8, 96),             # more columns than the parts of a split walk step over
     (1, 1, 129, 5, 128),
-    (40, 40, 257, 2, 64),          # a workgroup shape each: 128-row pairs ...
-    (48, 24, 255, 4, 128),         # ... and 256 rows
+    (40, 40, 257, 2, 64),
+    (48, 24, 255, 4, 128),
     (16, 8, 513, 3, 96),
-    (2, 2, 2000, 1, 128),          # a grid of one tile, in two key lanes and parts
+    (2, 2, 2000, 1, 128),          # a grid of one tile
+    # every workgroup shape of both kernels, whole walks and shared ones, in each layout and head size (tests/test_host_routes.py)
+    (8, 1, 17, 3, 80),
+    (8, 1, 132, 7, 64),
+    (88, 11, 16, 3, 96),
+    (1, 1, 641, 5, 96),
+    (1, 1, 16, 1, 128),
+    (1, 1, 131, 7, 80),
+    (27, 27, 278, 2, 80),
+    (61, 61, 140, 4, 64),
+    (1, 1, 205, 5, 80),
+    (16, 2, 144, 5, 96),
+    (272, 34, 16, 1, 128),
+    (52, 26, 150, 3, 128),
+    (3, 3, 678, 5, 64),
+    (1, 1, 585, 5, 128),
+    (80, 80, 212, 4, 80),
+    (66, 33, 35, 2, 128),
+    (3, 3, 1953, 4, 64),
+    (40, 5, 140, 4, 96),
+    (64, 8, 802, 4, 128),
 ]
 
 
@@ -68,3 +88,44 @@ def test_grid_rows(case, causal, layout):
         assert torch.equal(x, z), name
         # P, dS and the results rounded to bf16 (a sequence of one or two tokens has a dQ and dK of almost nothing)
         assert _rel(x, y) < 1e-2 or (x.double() - y).abs().max() < 2e-2, "%s: %.2e" % (name, _rel(x, y))
+
+
+@pytest.mark.parametrize("layout", ["cyclic", "contiguous"])
+@pytest.mark.parametrize("causal", [True, False], ids=["causal", "full"])
+def test_long_blocks(causal, layout):
+    """Blocks of 46400 rows, whose tiles have more than 2^31 scores (dS of one would be more than 4 GiB): some rows and some
+    keys, at the edges of the blocks and inside, against fp64."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_15758_amd import binding as a2d, grid as g2d
+    T, side, H = 46400, 2, 64
+    n, scale, gen = T * side, 0.125, torch.Generator(device="cuda")
+    gen.manual_seed(37)
+    print("long blocks", causal, layout, flush=True)
+    Q, K, V, dO = (torch.randn(1, n, H, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    assert a2d._ext().grid_forward(Q, K, V, side, causal, layout == "cyclic", scale) is not None
+    O, lse = g2d.forward(Q, K, V, side, causal, layout, scale)
+    args = (Q, K, V, O, dO, lse, side, causal, layout == "cyclic", scale)
+    assert a2d._ext().grid_backward(*args) is not None
+    dQ, dK, dV = (x[0] for x in g2d.backward(Q, K, V, O, dO, lse, side, causal, layout, scale))
+    q, k, v, g, o = (x[0].double() for x in (Q, K, V, dO, O))
+    at = torch.tensor([0, 1, 31, 255, 256, 46339, 46340, 46341, T - 1, T, T + 1, 60001, n - 257, n - 2, n - 1], device="cuda")
+    token = torch.arange(n, device="cuda")
+    delta, ls = (g * o).sum(1), lse[0].double()
+    S = q[at] @ k.t().contiguous() * scale                       # rows `at`
+    if causal:
+        S.masked_fill_(token[None, :] > at[:, None], -math.inf)
+    assert (torch.logsumexp(S, 1) - ls[at]).abs().max() < 1e-4
+    P = torch.exp(S - ls[at, None])
+    assert _rel(O[0, at], P @ v) < 5e-3
+    dS = P * (g[at] @ v.t().contiguous() - delta[at, None])
+    # (the first row sees itself alone: its dQ is rounding noise)
+    first = 1 if causal else 0
+    assert _rel(dQ[at][first:], ((dS @ k) * scale)[first:]) < 1e-2
+    S = k[at] @ q.t().contiguous() * scale                       # keys `at`
+    if causal:
+        S.masked_fill_(token[None, :] < at[:, None], -math.inf)
+    P = torch.exp(S - ls[None, :])
+    assert _rel(dV[at], P @ g) < 1e-2
+    dS = P * (v[at] @ g.t().contiguous() - delta[None, :])
+    assert _rel(dK[at], (dS @ q) * scale) < 1e-2

@@ -10,8 +10,11 @@ from test_gpu_split_walks import _rel
 
 pytestmark = pytest.mark.gpu
 
-# dtype, heads, H: tiles of 100 x 300, of which few heads take 128 keys per workgroup and many take 256
-CASES = [("bf16", 4, 128), ("bf16", 90, 128), ("bf16", 90, 80), ("f32", 4, 64)]
+# dtype, heads, H: tiles of 100 x 300, which take, from few heads to many, 32 keys per workgroup, 128 and 256 in one launch with
+# dQ, 128 in a launch of their own, 256 in one (at H = 128 with dS kept where allowed)
+CASES = [("bf16", 4, 128), ("bf16", 90, 128), ("bf16", 90, 80), ("f32", 4, 64),
+         ("bf16", 150, 128), ("bf16", 150, 96), ("bf16", 150, 80), ("bf16", 150, 64), ("bf16", 170, 64),
+         ("bf16", 600, 128), ("bf16", 600, 96), ("bf16", 600, 80), ("bf16", 600, 64)]
 NQ, NKV, OFF = 100, 300, 192                       # row i sees the keys up to i + OFF
 BIG = 1e20
 

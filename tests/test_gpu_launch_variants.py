@@ -1,18 +1,16 @@
 """GPU parity at every launch shape of the tile kernels, on sizes the oracle still finishes.
 
-The forward, dQ and dQ-from-dS kernels exist in several instantiations, chosen from the number of
-query blocks against the number of compute units (256 on MI355X):
-  * workgroups of eight wavefronts (256 query rows) once heads * ceil(nq / 256) reaches the number
-    of compute units - the one every paper-sized workload runs;
-  * workgroups of four wavefronts (128 rows) below that;
-  * when even heads * ceil(nq / 128) is at most the number of compute units, 128-row workgroups of
-    eight wavefronts in two key lanes whose partials (forward) or sums (dQ) are merged inside the
-    kernel (the small cases of test_gpu_parity.py all take this one).
-The cases here have many heads and short, RAGGED tiles, so that each regime is reached (with the
-by-size workgroup order under a causal mask, and head counts that leave a partial last chunk of
-heads per XCD) for every head size, in every form of the calls: plain, accumulating, normalised,
-gathered, grouped heads, both backward paths.  The oracle checks whole heads: the first, the last,
-and heads whose index is 1..6 modulo the 8 XCDs.
+The forward, dQ and dQ-from-dS kernels exist in several instantiations, chosen by models of their times:
+  * workgroups of eight wavefronts (256 query rows) - the one most paper-sized workloads run;
+  * 128-row workgroups of eight wavefronts in two key lanes whose partials (forward) or sums (dQ) are merged
+    inside the kernel;
+  * workgroups of four wavefronts (128 rows), two per compute unit.
+ROUTES has tiles whose forward, and whose backward in launches of its own (recomputing, and with dS kept), take each
+of them for every head size, ragged, grouped and not, with rows that see nothing; `tests/test_host_routes.py` holds
+them to it.  The other cases have many heads and short, RAGGED tiles (with the by-size workgroup order under a causal
+mask, and head counts that leave a partial last chunk of heads per XCD), or few.  Every form of the calls: plain,
+accumulating, normalised, gathered, grouped heads, both backward paths.  The oracle checks whole heads: the first, the
+last, and heads whose index is 1..6 modulo the 8 XCDs.
 """
 import math
 
@@ -27,7 +25,6 @@ from helpers import assert_close, np64
 pytestmark = pytest.mark.gpu
 
 BF = torch.bfloat16
-CUS = 256     # compute units of MI355X: the launchers' threshold for the eight-wavefront kernels
 
 
 @pytest.fixture(scope="module")
@@ -44,6 +41,30 @@ def dev(t):
 
 
 # heads, kv_heads, nq, nkv, H, causal, q_off, kv_off
+ROUTES = [
+    (297, 99, 98, 138, 128, True, 124, 0),
+    (204, 102, 115, 311, 128, True, 282, 0),
+    (169, 169, 102, 174, 96, False, 0, 0),
+    (98, 98, 313, 227, 128, False, 0, 0),
+    (201, 201, 287, 137, 64, False, 0, 0),
+    (54, 27, 603, 162, 64, True, 120, 0),       # a long walk of dK / dV in parts
+    (170, 85, 94, 178, 80, True, 110, 0),
+    (386, 193, 91, 154, 80, False, 0, 0),
+    (160, 160, 366, 289, 96, False, 0, 0),
+    (238, 238, 244, 165, 80, False, 0, 0),
+    (158, 158, 286, 171, 128, False, 0, 0),
+    (462, 231, 166, 187, 96, False, 0, 0),
+    (70, 70, 327, 297, 128, True, 213, 0),
+    (214, 107, 253, 275, 128, True, 169, 0),
+    (213, 71, 108, 278, 64, True, 249, 0),
+    (4, 4, 177, 140, 96, True, 0, 151),         # most rows see nothing
+    (199, 199, 136, 145, 64, True, 0, 133),     # all but three rows see nothing
+    (15, 5, 815, 1852, 128, False, 0, 0),       # dQ in two key lanes and parts ...
+    (68, 68, 232, 185, 128, True, 6, 13),
+    (34, 17, 142, 1108, 64, False, 0, 0),       # ... in 256 rows ...
+    (17, 17, 205, 1287, 96, False, 0, 0),       # ... in four wavefronts
+    (11, 11, 578, 1738, 128, True, 1393, 0),
+]
 CASES = [
     (64, 64, 1100, 700, 96, True, 200, 0),      # diagonal through the tile, ragged rows and keys
     (40, 40, 1700, 700, 80, True, 0, 300),      # 5 heads per XCD: last by-size chunk holds one; first rows see no key
@@ -84,7 +105,7 @@ def _fwd_close(got, ref, what):
         assert_close(Ng[ok], Nr[ok], BF, what + " N (per-row scaled)", rel=False, scale_rows=True)
 
 
-# between the two thresholds: 128-row workgroups of four wavefronts, two per compute unit
+# some 128 to 256 blocks of 256 rows
 CASES_FOUR = [
     (30, 30, 1100, 700, 96, True, 200, 0),      # 150 blocks of 256 rows, 270 of 128
     (36, 36, 1000, 400, 64, True, 300, 0),
@@ -92,7 +113,7 @@ CASES_FOUR = [
     (24, 6, 1400, 600, 80, False, 0, 0),        # grouped heads, no mask
 ]
 
-# at most one 128-row block per compute unit: the forward and dQ kernels walk the keys in two lanes
+# at most one 128-row block per compute unit
 CASES_LANES = [
     (8, 8, 700, 900, 128, True, 400, 0),        # diagonal through the tile: the lanes' shares differ
     (12, 12, 300, 1000, 80, True, 900, 0),      # an odd number of visible key blocks for most workgroups
@@ -102,23 +123,24 @@ CASES_LANES = [
 ]
 
 
+@pytest.mark.parametrize("case", ROUTES, ids=_ids)
+def test_every_kernel_every_call_form(a2d, case):
+    _every_call_form(a2d, case, "routes")
+
+
 @pytest.mark.parametrize("case", CASES, ids=_ids)
-def test_eight_wavefront_kernels_every_call_form(a2d, case):
-    assert case[0] * ((case[2] + 255) // 256) >= CUS, "the case must take the eight-wavefront kernels"
-    _every_call_form(a2d, case, "8w")
+def test_many_heads_every_call_form(a2d, case):
+    _every_call_form(a2d, case, "many heads")
 
 
 @pytest.mark.parametrize("case", CASES_FOUR, ids=_ids)
-def test_four_wavefront_kernels_every_call_form(a2d, case):
-    assert case[0] * ((case[2] + 255) // 256) < CUS < case[0] * ((case[2] + 127) // 128), \
-        "the case must take the four-wavefront kernels with one key lane"
-    _every_call_form(a2d, case, "4w")
+def test_some_blocks_every_call_form(a2d, case):
+    _every_call_form(a2d, case, "some blocks")
 
 
 @pytest.mark.parametrize("case", CASES_LANES, ids=_ids)
-def test_two_key_lane_kernels_every_call_form(a2d, case):
-    assert case[0] * ((case[2] + 127) // 128) <= CUS, "the case must take the kernels with two key lanes"
-    _every_call_form(a2d, case, "2 lanes")
+def test_few_blocks_every_call_form(a2d, case):
+    _every_call_form(a2d, case, "few blocks")
 
 
 def _every_call_form(a2d, case, regime):
@@ -234,10 +256,10 @@ def _every_call_form(a2d, case, regime):
                 assert_close(np64(dV[kv]), rv.sum(axis=0), BF, w2 + " dV")
 
 
-def test_strided_inputs_eight_wavefront_kernels(a2d):
-    """Q, K, V, O, dO as views of a packed [rows][..][heads][H] buffer at a launch shape of the
-    eight-wavefront kernels: bit for bit the results on plain copies."""
-    heads, n, H = 72, 900, 96
+@pytest.mark.parametrize("n", [700, 900])            # 256-row workgroups, 128-row ones of four wavefronts
+def test_strided_inputs_many_heads(a2d, n):
+    """Q, K, V, O, dO as views of a packed [rows][..][heads][H] buffer: bit for bit the results on plain copies."""
+    heads, H = 72, 96
     scale = 1.0 / math.sqrt(H)
     packed = dev(synth.normal((n, 3, heads, H), 98, 0, 1.0, "bf16"))
     Qv, Kv, Vv = (packed[:, i].permute(1, 0, 2) for i in range(3))

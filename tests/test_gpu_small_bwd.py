@@ -8,9 +8,10 @@ pytestmark = pytest.mark.gpu
 
 # heads, kv_heads, nq, nkv, H, causal, q_off, sub-blocks (None: one), packed
 CASES = [
-    (2, 2, 32, 32, 128, False, 0, None, False),
+    (2, 2, 32, 96, 128, False, 0, None, False),
+    (2, 2, 64, 64, 128, True, 0, None, False),
     (1, 1, 33, 31, 64, True, 0, None, True),
-    (3, 1, 255, 33, 80, True, -20, None, True),              # rows that see nothing, grouped heads
+    (6, 2, 255, 65, 80, True, -20, None, True),              # rows that see nothing, grouped heads
     (2, 2, 257, 256, 96, False, 0, None, False),             # one row beyond the first round
     (4, 2, 300, 289, 128, True, 30, None, True),
     (2, 1, 70, 600, 64, True, 560, [(2, 31), (40, 1), (60, 200), (300, 368)], False),
@@ -18,8 +19,13 @@ CASES = [
     (8, 8, 500, 530, 80, False, 0, None, True),
     (5, 5, 40, 1100, 96, True, 1061, None, False),
 ]
+# one block of keys: the paired workgroups
+PAIRS = [
+    (2, 2, 32, 32, 128, False, 0, None, False),
+    (3, 1, 255, 33, 80, True, -20, None, True),
+]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))
+@pytest.mark.parametrize("case", CASES + PAIRS, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))
 def test_small_bwd(case):
     _check(case, False)

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 BF = torch.bfloat16
 
 # heads, kv_heads, nq, nkv, H, causal, q_off, sub-blocks (None: one), packed, sigma
-CASES = [
+# 32 rows a workgroup
+ROWS32 = [
     (1, 1, 1, 1, 128, False, 0, None, False, 1),
     (3, 3, 31, 33, 64, False, 0, None, True, 1),             # two of the eight wavefronts have keys
     (2, 1, 32, 255, 80, True, 230, None, False, 1),
@@ -24,12 +25,26 @@ CASES = [
     (17, 17, 480, 545, 128, False, 0, None, False, 8),
     (30, 10, 250, 1030, 96, True, 780, None, True, 1),
     (1, 1, 40, 9000, 128, False, 0, None, False, 2),         # a walk worth sharing between workgroups too
-    (40, 40, 300, 300, 128, False, 0, None, False, 2),       # from here on 64 rows a workgroup
-    (40, 20, 290, 333, 80, True, 60, None, True, 1),
-    (26, 13, 610, 129, 64, True, -30, None, False, 3),       # rows that see nothing; one key in the second round
-    (44, 11, 250, 500, 96, True, 300, [(0, 31), (40, 1), (90, 300), (420, 168)], True, 1),
-    (70, 70, 225, 31, 128, False, 0, None, True, 1),         # three of the four lanes have no keys
 ]
+# 64 rows
+ROWS64 = [
+    (40, 40, 300, 300, 128, False, 0, None, False, 2),
+    (40, 20, 290, 333, 80, True, 60, None, True, 1),
+    (20, 10, 610, 129, 64, True, -30, None, False, 3),       # rows that see nothing; one key in the second round
+    (24, 6, 610, 129, 80, True, -30, None, True, 1),
+    (44, 11, 250, 500, 96, True, 300, [(0, 31), (40, 1), (90, 300), (420, 168)], True, 1),
+    (44, 11, 305, 82, 128, True, -101, None, False, 2),      # a block whose rows all see nothing; lanes without keys
+    (9, 9, 1375, 83, 64, True, -288, None, True, 1),
+    (50, 50, 284, 80, 64, False, 0, None, False, 1),         # a lane without keys, one with half a slab
+    (8, 2, 1192, 93, 128, False, 0, None, True, 4),
+    (148, 74, 36, 96, 96, False, 0, None, False, 1),         # rows in the second of the two row groups: four
+]
+# fewer keys than two rounds: 128 rows, in pairs of workgroups
+PAIRS = [
+    (26, 13, 610, 129, 64, True, -30, None, False, 3),
+    (70, 70, 225, 31, 128, False, 0, None, True, 1),
+]
+CASES = ROWS32 + ROWS64 + PAIRS
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))

@@ -11,17 +11,32 @@ from test_gpu_split_walks import _rel
 pytestmark = pytest.mark.gpu
 
 # heads, kv_heads, nq, nkv, H, causal, q_off, segments (kv_off, rows)
+# 256 keys a workgroup, in one launch with dQ ...
 CASES = [
+    (150, 150, 100, 300, 128, False, 0, [(0, 300)]),
+    (120, 120, 333, 257, 96, True, 0, [(0, 257)]),
+    (340, 170, 65, 289, 80, True, 200, [(0, 64), (100, 225)]),
+    (120, 120, 1, 301, 64, False, 0, [(0, 301)]),
+    (176, 88, 70, 512, 64, True, 450, [(30, 512)]),           # the last keys are seen by no row
+    (45, 45, 90, 641, 128, True, 300, [(300, 128), (0, 513)]),  # first rows see nothing of the first sub-block
+    # ... and in a launch of their own, at H = 128 with dS kept too
+    (600, 600, 100, 300, 128, False, 0, [(0, 300)]),
+    (600, 600, 1, 301, 128, False, 0, [(0, 301)]),
+    (400, 400, 333, 257, 96, True, 0, [(0, 257)]),
+    (500, 250, 65, 289, 80, True, 200, [(0, 64), (100, 225)]),
+    (600, 600, 1, 301, 64, False, 0, [(0, 301)]),
+    (500, 250, 90, 321, 128, True, 150, [(200, 128), (0, 193)]),
+]
+# 128 keys a workgroup
+NARROW = [
     (90, 90, 100, 300, 128, False, 0, [(0, 300)]),
     (90, 90, 333, 257, 96, True, 0, [(0, 257)]),
     (180, 90, 65, 289, 80, True, 200, [(0, 64), (100, 225)]),
     (90, 90, 1, 301, 64, False, 0, [(0, 301)]),
-    (176, 88, 70, 512, 64, True, 450, [(30, 512)]),           # the last keys are seen by no row
-    (45, 45, 90, 641, 128, True, 300, [(300, 128), (0, 513)]),  # first rows see nothing of the first sub-block
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))
+@pytest.mark.parametrize("case", CASES + NARROW, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))
 def test_wide_key_blocks(case):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -1,5 +1,6 @@
 """How calls go out (binding.tile_route, grid.route: the library's own plans, on the CPU): the rules that were measured, and that
 the GPU tests' cases take the kernels they are there for.  256 compute units, as on MI355X."""
+import itertools
 import random
 
 import pytest
@@ -107,3 +108,128 @@ def test_bench_names_the_kernels_of_the_library(a2d, workload, monkeypatch):
         if w.backward:
             assert got == [want, want]
         assert bench.call_kernels.__wrapped__("partial_fwd_full", w, recompute) == ["fwd_mfma_kernel"]
+
+
+# ---- the GPU tests' cases take the kernels that they are there for
+FORMS = [(256, 1), (128, 2), (128, 1)]             # rows, key lanes of the forward and dQ kernels of large tiles
+SIZES = (64, 80, 96, 128)
+
+
+def every(*axes):
+    return set(itertools.product(*axes))
+
+
+def test_launch_variant_cases(a2d):
+    import test_gpu_launch_variants as t
+    fwd, masked, dq, shared, dkdv, kept, grouped = (set() for _ in range(7))
+    for heads, kvh, nq, nkv, H, causal, q_off, kv_off in t.ROUTES:
+        route = lambda **more: tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, q_off=q_off, kv_off=kv_off, **more)
+        f, b, d = route(), route(backward=True), route(backward=True, ds_handover=True)
+        if f["kernels"] == ("fwd_mfma_kernel",):
+            form = (f["rows"], f["lanes"])
+            fwd.add((form, H))
+            masked.add(("forward", form, causal))
+            grouped.add(("forward", form, heads > kvh))
+        if "bwd_dq_kernel" in b["kernels"]:
+            form = (b["rows"], b["lanes"])
+            dq.add((form, H))
+            dkdv.add((b["kernels"][1], H))
+            masked.add(("dQ", form, causal))
+            grouped.add(("dQ", form, heads > kvh))
+            if b["parts_q"] > 1:
+                shared.add(form)
+        if "bwd_dq_ds_kernel" in d["kernels"]:
+            form = (d["rows"], d["lanes"])
+            kept.add((form, d["keys"]))
+            masked.add(("dQ from dS", form, causal))
+            grouped.add(("dQ from dS", form, heads > kvh))
+    kinds = ("forward", "dQ", "dQ from dS")
+    assert fwd == dq == every(FORMS, SIZES) and shared == set(FORMS)
+    assert dkdv == every(("bwd_dkdv_kernel", "bwd_dkdv_wide_kernel"), SIZES) and kept == every(FORMS, (128, 256))
+    assert masked == grouped == every(kinds, FORMS, (False, True))
+    strided = [tile(a2d, 72, n, n, 96, causal=True) for n in (700, 900)]
+    assert [(r["rows"], r["lanes"]) for r in strided] == [(256, 1), (128, 1)]
+
+
+def test_hidden_score_cases(a2d):
+    import test_gpu_hidden_scores as t
+    took = set()
+    for dtype, heads, H in t.CASES:
+        for keep in (False, True) if dtype == "bf16" else ():
+            r = tile(a2d, heads, t.NQ, t.NKV, H, causal=True, q_off=t.OFF, backward=True, ds_handover=keep)
+            took |= {(k, r["keys"], H) for k in r["kernels"]}
+    assert {("bwd_small_kernel", 32, 128), ("bwd_one_kernel", 128, 80), ("bwd_one_kernel", 128, 128),
+            ("bwd_dkdv_kernel", 128, 64), ("bwd_dq_ds_kernel", 256, 128)} <= took
+    assert {("bwd_one_kernel", 256, H) for H in SIZES} | {("bwd_dkdv_wide_kernel", 256, H) for H in SIZES} <= took
+
+
+def test_wide_key_cases(a2d):
+    import test_gpu_wide_keys as t
+    took = set()
+    for cases, keys in ((t.CASES, 256), (t.NARROW, 128)):
+        for heads, kvh, nq, nkv, H, causal, q_off, segs in cases:
+            for keep in (False, True):
+                r = tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, q_off=q_off, segments=segs, backward=True,
+                         ds_handover=keep)
+                assert r["keys"] == keys, (heads, nq, nkv, H)
+                took |= {(k, H) for k in r["kernels"]}
+    assert {("bwd_one_kernel", H) for H in SIZES} | {("bwd_dkdv_wide_kernel", H) for H in SIZES} <= took
+    assert ("bwd_dq_ds_kernel", 128) in took
+
+
+def test_few_row_cases(a2d):
+    import test_gpu_small_bwd as b
+    import test_gpu_small_rows as f
+    rows64 = set()
+    for cases, form in ((f.ROWS32, (32, 8)), (f.ROWS64, (64, 4)), (f.PAIRS, (128, 1))):
+        for heads, kvh, nq, nkv, H, causal, q_off, segs, *_ in cases:
+            r = tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, q_off=q_off, segments=segs)
+            assert (r["rows"], r["lanes"]) == form, (heads, nq, nkv, H)
+            if form == (64, 4):
+                rows64.add((H, causal and q_off < 0 or segs is not None))
+    assert {H for H, _ in rows64} == set(SIZES) and {(64, True), (80, True), (96, True), (128, True)} <= rows64
+    for cases, small in ((b.CASES, True), (b.PAIRS, False)):
+        for heads, kvh, nq, nkv, H, causal, q_off, segs, _ in cases:
+            r = tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, q_off=q_off, segments=segs, backward=True)
+            assert ("bwd_small_kernel" in r["kernels"]) == small, (heads, nq, nkv, H)
+    assert {c[4] for c in b.CASES} == set(SIZES)
+
+
+def test_backward_route_cases(a2d):
+    import test_gpu_bwd_routes as t
+    for cases, one in ((t.ONE, True), (t.MANY, False)):
+        for heads, kvh, nq, nkv, H, causal, q_off, segs, _ in cases:
+            r = tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, q_off=q_off, segments=segs, backward=True,
+                     ds_handover=H == 128)
+            assert bool({"bwd_one_kernel", "bwd_small_kernel"} & set(r["kernels"])) == one, (heads, nq, nkv, H)
+            assert ("bwd_dq_ds_kernel" in r["kernels"]) == (not one and H == 128)
+    took = {tile(a2d, *c, H, causal=True, backward=True, ds_handover=k)["kernels"] for c in t.DELTA for H in SIZES for k in (False, True)}
+    assert {("bwd_small_kernel",), ("bwd_one_kernel",), ("delta_kernel", "bwd_one_kernel"),
+            ("bwd_dq_kernel", "bwd_dkdv_wide_kernel"), ("delta_kernel", "bwd_dkdv_wide_kernel", "bwd_dq_ds_kernel")} <= took
+
+
+def test_grid_row_cases(a2d):
+    import test_gpu_grid_rows as t
+    from paper_2503_15758_amd import grid as g2d
+    layouts = ("cyclic", "contiguous")
+    fwd, shared, sizes, bwd, heads_of = (set() for _ in range(5))
+    for heads, kvh, rows, side, H in t.CASES:
+        for causal, layout in every((False, True), layouts):
+            route = lambda backward: g2d.route(heads, rows * side, H, side, kvh, causal, layout, backward, CUS)
+            f, b = route(False), route(True)
+            form = (f["rows"], f["lanes"])
+            (shared if f["parts_q"] > 1 else fwd).add((form, layout, causal))
+            if f["parts_q"] == 1:
+                sizes.add((form, H))
+                heads_of.add((form, heads > kvh))
+            kind = (b["keys"], b["rows"], b["lanes"])
+            bwd.add((kind, layout, causal))
+            sizes.add((b["keys"], H))
+            heads_of.add((b["keys"], heads > kvh))
+    forms = FORMS + [(64, 4), (32, 8)]
+    kinds = [(32, 32, 8)] + [(keys, *form) for keys in (128, 256) for form in FORMS[:2]]
+    assert fwd == every(forms, layouts, (False, True)) and sizes == every(forms + [32, 128, 256], SIZES)
+    # (the 64-row form shares unmasked walks only)
+    assert shared == every(forms, layouts, (False, True)) - every([(64, 4)], layouts, [True])
+    assert bwd == every(kinds, layouts, (False, True))
+    assert heads_of == every(forms + [32, 128, 256], (False, True))
