@@ -351,8 +351,8 @@ a2d_status a2d_partial_bwd_static(const a2d_tile_desc* desc, const void* Q, cons
   if (rows > (int64_t)A2D_STATIC_MAX_ROWS)
     return fail(A2D_ERR_WORKSPACE, "%s: heads * nq = %lld rows exceed the static scratch of %d rows (use a2d_partial_bwd)",
                 who, (long long)rows, A2D_STATIC_MAX_ROWS);
-  // delta is written in full by the call's first kernel before the others read it: nothing in
-  // the array has to start at zero
+  // where kernels of the call read delta, one before them has written it in full: nothing in the array has to
+  // start at zero
   void* ptr = nullptr;
   A2D_TRY(hip_result(a2d::symbol_address(HIP_SYMBOL(scratch), &g_scratch, &ptr), who));
   return partial_bwd_impl(desc, one_segment(desc), Q, K, V, O, dO, lse, dQ_part, dK_part, dV_part, ptr,

@@ -1,4 +1,4 @@
-// Shared by the bf16 backward kernels (a2d_bwd_mfma.hip, a2d_bwd_wide.hip).
+// Shared by the bf16 backward kernels (a2d_bwd_*).
 #pragma once
 #include "a2d_mfma.hpp"
 
@@ -41,19 +41,6 @@ __device__ __forceinline__ void store_acc_t(float* __restrict__ out_row, const f
       }
       *p = v;
     }
-}
-
-// the lane's number, computed where it is called (not kept in a register)
-__device__ __forceinline__ int lane_again() {
-  int l;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-  return l;
-}
-
-// the value another lane holds (a DPP control word: quad_perm, row_half_mirror 0x141, row_mirror 0x140)
-template <int CTRL>
-__device__ __forceinline__ float lane_swap(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
 }
 
 __device__ __forceinline__ f32x4 lds_load_f32x4(unsigned addr) {

@@ -299,23 +299,23 @@ __device__ __forceinline__ void dq_rows(
     advance(stride, nsb, nj, nnblk);
     const bool more = nsb < segs;
     if (CYCLIC) nx_start = nsb;
-    else if (seldom(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
+    else if (A2D_SELDOM(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
     const bool here = KL == 1 || sb < segs;         // this lane has a block in this round
     const int k0 = j * BKS + (CYCLIC && sb > shift_from);      // local to the sub-block
-    if (often(more)) load_half(nx_start, nx_rows, nj, 0);
+    if (A2D_OFTEN(more)) load_half(nx_start, nx_rows, nj, 0);
     if (here && k0 < nvis_wave) {
       if (k0 + 32 > nfull_wave) dq_piece<0, true, HD, KSR>(cx, k0); else dq_piece<0, false, HD, KSR>(cx, k0);
     }
-    if (often(more)) { store_half(buf ^ 1, 0); load_half(nx_start, nx_rows, nj, 1); }
+    if (A2D_OFTEN(more)) { store_half(buf ^ 1, 0); load_half(nx_start, nx_rows, nj, 1); }
     if (here && k0 + 32 < nvis_wave) {
       if (k0 + 64 > nfull_wave) dq_piece<1, true, HD, KSR>(cx, k0 + 32); else dq_piece<1, false, HD, KSR>(cx, k0 + 32);
     }
-    if (often(more)) store_half(buf ^ 1, 1);
+    if (A2D_OFTEN(more)) store_half(buf ^ 1, 1);
     const int tog = buf ? -DQ_BUF : DQ_BUF;
     cx.ka.shift(tog);
     cx.vnat += tog;
     __syncthreads();
-    if (!CYCLIC && seldom(more && nsb != sb)) enter_segment(nsb);
+    if (!CYCLIC && A2D_SELDOM(more && nsb != sb)) enter_segment(nsb);
     if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
     sb = nsb; j = nj; nblk = nnblk;
     buf ^= 1;

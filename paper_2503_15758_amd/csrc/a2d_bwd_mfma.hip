@@ -448,8 +448,9 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 //     23 % at worst).  Of uneven walks 3 % of the shapes would be 3-9 % faster in two and neither model tells which (84 x
 //     1117 x 2587, H = 96, causal 167 / 154): 0.3 % in the mean.
 //   - with dS kept, where the caller allows it and the model says so: at H = 128 only.  Below, recomputing S and dP costs
-//     less than writing and reading dS at every size (64 x 4096 x 4096 H = 64 1044 against 1157 us, H = 80 1268 / 1320,
-//     16 x 2048 x 2048 H = 64 79 / 103).  At H = 128 it gains 5-9 % from two turns of unmasked tiles on (16 x 4096 x 4096 414
+//     less than writing and reading dS (64 x 4096 x 4096 H = 64 1044 against 1157 us, H = 80 1268 / 1320, 16 x 2048 x 2048
+//     H = 64 79 / 103; of 262 drawn shapes of H = 64 to 96 15 % in the mean, 14 of them 2-11 % slower: 36 x 1413 x 2468, H = 96
+//     221 / 199).  At H = 128 it gains 5-9 % from two turns of unmasked tiles on (16 x 4096 x 4096 414
 //     against 445 us; 16 x 2048 x 2048, one turn, 138 / 130).
 //   - else dQ, recomputing, then dK/dV.
 // Parts of the dK/dV and dQ walks where their row blocks leave compute units idle, and the dQ kernels' workgroup

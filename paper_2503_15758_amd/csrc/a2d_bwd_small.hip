@@ -154,7 +154,7 @@ __device__ __forceinline__ void small_rows(
       if (j >= n) sb = segs;
     } else {
       j += by;
-      while (seldom(j >= n)) {
+      while (A2D_SELDOM(j >= n)) {
         if (sb >= segs) break;
         j -= n;
         open_segment(sb + 1);

@@ -31,8 +31,8 @@ __device__ __forceinline__ float to_f32(bf16_t x) { return (float)x; }
 // 2^x on the hardware transcendental unit (about 1 ulp).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// c + the sum of eight products of bf16 pairs (two at a time: half the instructions of unpacked multiply-adds, and of
-// rows of 128 N(0,1) pairs 9.5e-9 off in the mean of the magnitudes' sum against 9.9e-9)
+// c + the sum of eight products of bf16 pairs, two at a time: half the instructions of unpacked multiply-adds.  (Its error
+// against 64 bits, in the sums of whole rows: tests/test_gpu_bwd_routes.py, no larger than that of such multiply-adds.)
 __device__ __forceinline__ float dot8(u32x4 a, u32x4 b, float c) {
   typedef __bf16 pair_t __attribute__((ext_vector_type(2)));
 #pragma unroll

@@ -4,7 +4,7 @@
 // of a SIMD, 157 TFLOP/s over the chip - twice what unpacked vector FMAs reach).
 //
 // What bounds them: the fp32 MFMA rate where there are many rows (78 % of it at 16 x 4096 x 4096, H = 128); at 16 x 700 x
-// 900 prologues, merges and uneven walks of a few steps (55 %).  A step of 16 keys (queries)
+// 900 prologues, merges, uneven walks of a few steps and bank conflicts (50 % of the cycles in the matrix units).  A step of 16 keys (queries)
 // against 16 rows is H / 4 MFMAs of 32 cycles per contraction, on 8 KiB of operands at H = 128.
 //   - The backward's dQ and dK/dV workgroups go out in one launch, so that the end of the one kind overlaps the start of
 //     the other (two launches, dQ leaving delta for dK/dV: 2 x 128 x 128, H = 64 13.4 -> 7.1 us; 8 x 256 x 900, H = 80
@@ -25,7 +25,7 @@
 //   - Contractions over H read rows "naturally": lane (row l15, group g) reads the 16 bytes
 //     16 y + 4 g .. + 3 of its row, which serve four MFMAs (the contraction index may be permuted as
 //     long as both operands use the same permutation).  Tile rows are padded by 16 bytes (the backward kernels'
-//     LDS cycles are 27-29 % bank conflicts all the same, at 18 % of the time in LDS and 42-44 % MFMA busy).
+//     LDS cycles are 28 % bank conflicts all the same, at 21 % of the time in LDS).
 //   - Contractions over rows need the transposed operand (lane = column): lane l15 loads 16 bytes of
 //     row 4 g + r, columns 64 G + 4 l15 + t, and MFMA t of the group takes one of the four, i.e. row
 //     i of its result is column 64 G + 4 i + t.  A lane then holds 16 consecutive columns of the
@@ -36,7 +36,7 @@
 // 1.07 ms (129 TFLOP/s, 82 % of the fp32 matrix peak), backward 3.87 ms (124 TFLOP/s executed).
 #include <cmath>
 
-#include "a2d_bwd.hpp"
+#include "a2d_mfma.hpp"
 
 namespace a2d {
 namespace {

@@ -382,7 +382,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
       if (j >= nblk) sb = segs;
     } else {
       j += by;
-      while (seldom(j >= nblk)) {
+      while (A2D_SELDOM(j >= nblk)) {
         if (sb >= segs) break;
         j -= nblk;
         open_segment(sb + 1, sb, nblk);
@@ -415,16 +415,16 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     advance(stride, nsb, nj, nnblk);
     const bool more = nsb < segs;
     if (CYCLIC) nx_start = nsb;
-    else if (seldom(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
-    if (often(more)) load_tile(nx_start, nx_rows, nj);
+    else if (A2D_SELDOM(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
+    if (A2D_OFTEN(more)) load_tile(nx_start, nx_rows, nj);
     const int k0 = j * BN + (CYCLIC && sb > shift_from);       // local to the sub-block
     if ((KL == 1 || sb < segs) && k0 < nvis_wave) {
       if (k0 + BN > nfull_wave) fwd_block<HD, true, KSR>(st, qf, k_rd0 + boff, v_rd0 + boff, k0, my_vis, half, c);
       else fwd_block<HD, false, KSR>(st, qf, k_rd0 + boff, v_rd0 + boff, k0, my_vis, half, c);
     }
-    if (often(more)) store_tile(BUF_BYTES - boff);
+    if (A2D_OFTEN(more)) store_tile(BUF_BYTES - boff);
     __syncthreads();
-    if (!CYCLIC && seldom(more && nsb != sb)) enter_segment(nsb);
+    if (!CYCLIC && A2D_SELDOM(more && nsb != sb)) enter_segment(nsb);
     if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
     sb = nsb; j = nj; nblk = nnblk;
     boff = BUF_BYTES - boff;

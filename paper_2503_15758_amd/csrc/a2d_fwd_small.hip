@@ -121,7 +121,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
       if (j >= n) sb = segs;
     } else {
       j += by;
-      while (seldom(j >= n)) {
+      while (A2D_SELDOM(j >= n)) {
         if (sb >= segs) break;
         j -= n;
         open_segment(sb + 1, sb, n);

@@ -164,7 +164,7 @@ hipError_t grid_backward(const GridProblem& p, const void* Q, const void* K, con
   output(p, p.dv, &g, 2);
   float* delta = static_cast<float*>(ws);
   float* more = reinterpret_cast<float*>(static_cast<char*>(ws) + up256((size_t)p.heads * p.seq * sizeof(float)));
-  // all lines of Alg. 3 in two launches, or the partials of split walks
+  // all lines of Alg. 3 in one launch, delta's in front where the plan has it read, or the partials of split walks and their sums
   const size_t nq = out_floats(p, p.heads), nk = out_floats(p, p.kv_heads);
   void *q = dQ, *k = dK, *v = dV;
   SumSet sets[3];

@@ -54,12 +54,25 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& s, int base) {
   return r;
 }
 
+// the lane's number, computed where it is called (not kept in a register)
+__device__ __forceinline__ int lane_again() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
+// the value another lane holds (a DPP control word: quad_perm, row_half_mirror 0x141, row_mirror 0x140)
+template <int CTRL>
+__device__ __forceinline__ float lane_swap(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+
 // A branch of a main loop that is seldom taken: its code is laid out behind the loop, so that the loop
 // itself stays in one run of instruction lines (the walk's move to another sub-block inside the forward loop
 // cost 1 % at H = 128, 2 % at H = 80, 3 % at 16 x 2048 x 2048).  And one that is taken in every turn but the last: its
 // code stays where it stands.  (Macros: of an inlined function the compiler has dropped the hint by the time it is inlined.)
-#define seldom(x) __builtin_expect((bool)(x), 0)
-#define often(x) __builtin_expect((bool)(x), 1)
+#define A2D_SELDOM(x) __builtin_expect((bool)(x), 0)
+#define A2D_OFTEN(x) __builtin_expect((bool)(x), 1)
 
 // a / b and the rest, without a division by one: unsplit walks, heads that are not grouped (a division is some 35 dependent
 // instructions on the way to a workgroup's first loads)
@@ -68,7 +81,7 @@ struct Split {
 };
 __device__ __forceinline__ Split split_by(int a, int b) {
   Split s = {a, 0};
-  if (seldom(b != 1)) {
+  if (A2D_SELDOM(b != 1)) {
     s.q = a / b;
     s.r = a - s.q * b;
   }
@@ -78,7 +91,7 @@ __device__ __forceinline__ Split split_by(int a, int b) {
 // of block t of the group x nblocks of a key/value head: its number within its query head (q) and that head (r)
 __device__ __forceinline__ Split query_head(int t, int group, int nblocks, bool by_size) {
   Split s = {t, 0};
-  if (seldom(group != 1)) {
+  if (A2D_SELDOM(group != 1)) {
     const int by = by_size ? group : nblocks, q = t / by, r = t - q * by;
     s.q = by_size ? q : r;
     s.r = by_size ? r : q;

@@ -143,3 +143,36 @@ def test_no_memory_for_a_ds_that_is_not_kept(H):
         a2d.partial_bwd(Q, K, V, O, dO, lse, ds_handover=keep)
         took[keep] = torch.cuda.max_memory_allocated() - before
     assert (took[True] - took[False] >= 2 * heads * n * n) == (H == 128) and (H == 128 or took[True] == took[False]), took
+
+
+@pytest.mark.parametrize("H", [64, 80, 96, 128])
+def test_delta_against_64_bits(H):
+    """delta of whole rows as delta_kernel leaves it in the workspace, from products of bf16 pairs: against 64 bits, and against
+    unpacked fp32 multiply-adds in the same order."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_15758_amd import binding as a2d
+    heads, nq, nkv = 90, 256, 700
+    assert a2d.tile_route(heads, nq, nkv, H, causal=True, q_off=444, backward=True)["kernels"][0] == "delta_kernel"
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(41)
+    make = lambda n: torch.randn(heads, n, H, generator=gen, device="cuda").to(BF)
+    Q, K, V, O, dO = make(nq), make(nkv), make(nkv), make(nq), make(nq)
+    lse = torch.full((heads, nq), 7.0, device="cuda")
+    ws = torch.empty(a2d.workspace_bytes(a2d.tile_desc(Q, K, 444, 0, True, None), a2d.OP_PARTIAL_BWD), dtype=torch.uint8,
+                     device="cuda")
+    a2d.partial_bwd(Q, K, V, O, dO, lse, 444, 0, True, workspace=ws)
+    got = ws[:4 * heads * nq].view(torch.float32).view(heads, nq).double()
+    prod = O.double() * dO.double()                              # (exact; in fp32 too: 16 bits of mantissa)
+    exact, size = prod.sum(2), prod.abs().sum(2)
+    chunks = prod.float().view(heads, nq, H // 8, 8)
+    t = torch.zeros(heads, nq, 16, device="cuda")
+    for e in range(8):
+        t[..., :H // 8] += chunks[..., e]
+    for o in (1, 2, 4, 8):
+        t = t + t[..., torch.arange(16, device="cuda") ^ o]
+    plain = t[..., 0].double()
+    off, plain_off = ((x - exact).abs() / size for x in (got, plain))
+    print("H %d: mean error of the magnitudes' sum %.2e, unpacked %.2e" % (H, off.mean(), plain_off.mean()), flush=True)
+    # eight products and four exchanges: at most twelve roundings of a partial sum
+    assert off.max() < 12 * 2.0 ** -24 and off.mean() <= 1.05 * plain_off.mean()
