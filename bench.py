@@ -62,6 +62,11 @@ def call_kernels(call, w, recompute):
     raise KeyError(call)
 
 
+def bwd_path(calls, w, recompute):
+    """How the step's backward calls get dQ: where dS may be kept, the library keeps it for the shapes that it makes faster."""
+    return "dS hand-over" if all("bwd_dq_ds_kernel" in call_kernels(n, w, recompute) for n in calls) else "recompute"
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -292,7 +297,7 @@ def main():
                                    "measured_on_sources": traffic_sha, "current_sources": src_sha,
                                    "current": bool(traffic) and traffic_sha == src_sha}}
     if w.backward:
-        roofline["bwd_path"] = "recompute" if args.recompute_bwd else "dS hand-over"
+        roofline["bwd_path"] = bwd_path([n for n in names if n.startswith("partial_bwd")], w, args.recompute_bwd)
         # the call's inputs and outputs read / written once (Q, K, V, O, dO in the model's dtype, three fp32
         # gradient partials, lse): what the call's `traffic` is to be held against.  The dS hand-over adds 2
         # bytes per visible score written and read back (an intermediate traded for two contractions).

@@ -99,15 +99,19 @@ def test_bench_names_the_kernels_of_the_library(a2d, workload, monkeypatch):
     from paper_2503_15758_amd import synth
     route = a2d.tile_route
     monkeypatch.setattr(a2d, "tile_route", lambda *x, **more: route(*x, **dict(more, compute_units=CUS)))
+    kernels = bench.call_kernels.__wrapped__
+    monkeypatch.setattr(bench, "call_kernels", kernels)
     w = synth.WORKLOADS[workload]
     for recompute in (False, True):
-        got = [bench.call_kernels.__wrapped__("partial_bwd_" + tag, w, recompute) for tag in ("full", "diag")]
+        got = [kernels("partial_bwd_" + tag, w, recompute) for tag in ("full", "diag")]
         want = ["delta_kernel", "bwd_one_kernel"] if workload == "c2" else \
             ["bwd_dq_kernel", "bwd_dkdv_wide_kernel"] if recompute else \
             ["delta_kernel", "bwd_dkdv_wide_kernel", "bwd_dq_ds_kernel"]
         if w.backward:
             assert got == [want, want]
-        assert bench.call_kernels.__wrapped__("partial_fwd_full", w, recompute) == ["fwd_mfma_kernel"]
+            assert bench.bwd_path(["partial_bwd_full"], w, recompute) == \
+                ("recompute" if recompute or workload == "c2" else "dS hand-over")
+        assert kernels("partial_fwd_full", w, recompute) == ["fwd_mfma_kernel"]
 
 
 # ---- the GPU tests' cases take the kernels that they are there for
