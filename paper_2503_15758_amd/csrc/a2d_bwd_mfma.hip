@@ -496,36 +496,33 @@ BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cu
     return least;
   };
 
-  BwdParts plan = {};                                  // recomputing: dQ, then dK/dV ...
-  double plan_us = 0;
-  if (!grid) {
-    double kv_us[2];
-    int kv_parts[2];
-    for (int w = 0; w < 2; ++w) kv_parts[w] = best_parts(walk(w), cap_kv, 4.0, kv_part_us, &kv_us[w]);
-    plan.wide = kv_us[1] < kv_us[0] && d.scale > 1e-30f;   // (it takes lse / scale, which has to stay finite)
-    plan.kv = kv_parts[plan.wide];
-    plan_us = kv_us[plan.wide];
-    plan_us += rows_of(false, &plan);
-  }
   const int64_t wgs = (int64_t)side * (kv_heads * (int64_t)((d.nkv + 255) / 256) + d.heads * (int64_t)((d.nq + 255) / 256));
-  if (grid || wgs <= 6 * (int64_t)cus) {               // ... or both in one launch
+  const bool few = wgs <= 6 * (int64_t)cus;
+  BwdParts one = {}, plan = {};                        // recomputing, in one launch ...
+  double one_us = 0, dealt_us = 0;
+  if (grid || few) {
     const BwdWalks w = {kv_mean < rows ? kv_mean : rows, rows, mean < most ? mean : most, most, uneven};
-    BwdParts one = {};
-    double dealt_us = 0;
-    const double one_us = plan_bwd_one(d, g, w, cus, cap_kv, cap_q, &one, &dealt_us);
-    plan_us /= kOneUs[hx];
-    if (grid || one.small || dealt_us <= plan_us) {
-      plan = one;
-      plan_us = one_us;
-    }
+    one_us = plan_bwd_one(d, g, w, cus, cap_kv, cap_q, &one, &dealt_us);
+    if (grid || one.small) return one;
   }
-  if (!ds || d.hdim != 128 || plan.small) return plan;
+  double kv_us[2];                                     // ... or dQ, then dK/dV
+  int kv_parts[2];
+  for (int w = 0; w < 2; ++w) kv_parts[w] = best_parts(walk(w), cap_kv, 4.0, kv_part_us, &kv_us[w]);
+  plan.wide = kv_us[1] < kv_us[0] && d.scale > 1e-30f;     // (it takes lse / scale, which has to stay finite)
+  plan.kv = kv_parts[plan.wide];
+  double plan_us = kv_us[plan.wide];
+  plan_us = (plan_us + rows_of(false, &plan)) / kOneUs[hx];
+  if (few && dealt_us <= plan_us) {
+    plan = one;
+    plan_us = one_us;
+  }
+  if (!ds || d.hdim != 128) return plan;
   BwdParts kept = {};
   kept.wide = plan.wide;
   kept.kv = plan.kv;
   kept.keep_ds = 1;
   const double dq_us = rows_of(true, &kept);
-  if (wgs > 6 * (int64_t)cus) return kept;
+  if (!few) return kept;
   WalkModel kv = walk(kept.wide);                      // (a full chip clocks lower, most so beside the dS stores)
   const double f = full(kv.blocks * kept.kv);
   kv.step = kept.wide ? 1.3 + 0.8 * f * f : 1.1;

@@ -72,7 +72,8 @@ hipError_t go_h(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* 
 // model of the launch, fitted to 60 shapes x up to 100 choices each (1 x 161 x 308 to 32 x 4096 x 4096, grids of 350
 // to 8192 tokens); its choice is 1 % off the best of them in the mean.  Parts of the two kinds are tried in step: of one from a
 // list, of the other the fewest that make its walks no longer.
-// dealt: the time of the chosen one with its workgroups dealt to the chip's shader engines (see dealt_time); NULL: not asked.
+// dealt: the time of the chosen one, unless it is that of few rows, with its workgroups dealt to the chip's shader engines
+// (see dealt_time).
 double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w, int cus, int cap_kv, int cap_q,
                     BwdParts* best, double* dealt) {
   constexpr double kPairUs[3] = {0.81, 0.94, 1.34}, kWideUs[3] = {0.95, 1.05, 1.61}, kRowUs[3] = {1.57, 1.67, 2.68};
@@ -83,7 +84,7 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
   const double part_kv = (double)side * kv_heads * d.nkv * d.hdim * 16 / 4.5e6;     // written and read back at 4.5 TB/s
   const double part_q = (double)side * d.heads * d.nq * d.hdim * 8 / 4.5e6;
   double least = 0, rest = 0;
-  Kind first = {}, second = {};
+  Kind best_kv = {}, best_q = {};
   *best = BwdParts{};
   for (int wide = 0; wide < 2; ++wide) {
     if (wide && !(d.scale > 1e-30f)) continue;             // (it takes lse / scale, which has to stay finite)
@@ -116,10 +117,8 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
         if (best->one && t >= least) return;
         least = t;
         rest = more;
-        const Kind kv_ids = {xcd_grid(kv_heads * zk, side * ((d.nkv + keys - 1) / keys)), kv.mean, kv.most};
-        const Kind q_ids = {xcd_grid(kv_heads * zq, side * g.group * ((d.nq + rows - 1) / rows)), q.mean, q.most};
-        first = q_first ? q_ids : kv_ids;
-        second = q_first ? kv_ids : q_ids;
+        best_kv = kv;
+        best_q = q;
         *best = BwdParts{zk, zq, form, wide, 1, q_first};
       };
       for (int z : kParts) {
@@ -137,7 +136,6 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
       consider(1, 1);
     }
   }
-  if (dealt) *dealt = rest + dealt_time(first, second, cus, w.uneven, kTail);
   // 32 rows or keys a workgroup (a2d_bwd_small.hip; a step is a round of 256).  Fitted to 92 shapes of 1 x 41 x 80 to 16 x 512 x 512,
   // 1 x 4096 x 4096: taken up to some 256 of them with walks of 2048, 512 with walks of 512 (under a mask 1024); 1.27 times as
   // fast in the mean there as without that form, 0.5 % off the better of the two.
@@ -157,6 +155,10 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
     *best = BwdParts{1, 1, 0, 0, 1, q_first, 1};
     return small;
   }
+  const int keys = best->wide ? WK_KEYS : DK_KEYS, rows = best->form ? 128 : 256;
+  best_kv.n = xcd_grid(kv_heads * best->kv, side * ((d.nkv + keys - 1) / keys));
+  best_q.n = xcd_grid(kv_heads * best->q, side * g.group * ((d.nq + rows - 1) / rows));
+  *dealt = rest + (best->q_first ? dealt_time(best_q, best_kv, cus, w.uneven, kTail) : dealt_time(best_kv, best_q, cus, w.uneven, kTail));
   return least;
 }
 
