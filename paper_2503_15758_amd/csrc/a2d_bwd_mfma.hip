@@ -443,10 +443,10 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 //     16 x 2048 x 2048 144 -> 130; from some ten turns on 1 % slower).  The second kind does not fill what the first leaves of
 //     its last turn where the shader engines are dealt unlike numbers of the long walks (dealt_time): 72/18 heads x 651 x 861,
 //     H = 64 88 us in one launch, 77 in two; 6 x 9048 x 1290, H = 128 197 / 174; 51 x 2015 x 438, H = 64 96 / 88; 9 x 563 x
-//     2404, H = 80 50 / 43.  kOneUs is fitted to 770 drawn shapes of up to six turns, on the
-//     side of one launch: where the walks are even the choice is 0.1 % off the better one in the mean (one launch always: 0.4 %,
-//     23 % at worst).  Of uneven walks 3 % of the shapes would be 3-9 % faster in two and neither model tells which (84 x
-//     1117 x 2587, H = 96, causal 167 / 154): 0.3 % in the mean.
+//     2404, H = 80 50 / 43.  kOneUs is fitted to 770 drawn shapes of up to six turns, and favours one launch a little: where the
+//     walks are even the choice is 0.1 % off the better one in the mean (one launch always: 0.4 %, 23 % at worst).  Of uneven
+//     walks 3 % of the shapes would be 3-9 % faster in two and neither model tells which (84 x 1117 x 2587, H = 96, causal
+//     167 / 154): 0.3 % in the mean.
 //   - with dS kept, where the caller allows it and the model says so: at H = 128 only.  Below, recomputing S and dP costs
 //     less than writing and reading dS (64 x 4096 x 4096 H = 64 1044 against 1157 us, H = 80 1268 / 1320, 16 x 2048 x 2048
 //     H = 64 79 / 103; of 262 drawn shapes of H = 64 to 96 15 % in the mean, 14 of them 2-11 % slower: 36 x 1413 x 2468, H = 96
@@ -460,7 +460,7 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 BwdParts plan_bwd_mfma(const a2d_tile_desc& d, const SegList& g, bool ds, int cus, int cap_kv, int cap_q) {
   constexpr double kKvUs[3] = {0.75, 0.85, 1.0}, kWideUs[3] = {1.0, 1.2, 1.5};
   constexpr double kDqUs[3] = {1.6, 1.75, 2.1};
-  constexpr double kOneUs[3] = {1.03, 1.0, 0.85};      // the model of two launches on the scale of the one of one
+  constexpr double kOneUs[3] = {1.03, 1.0, 0.85};      // two launches' modelled time over that of one which takes as long
   const int hx = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, kv_heads = d.heads / g.group, side = g.b.side ? g.b.side : 1;
   // (a grid's walks are `side` times as long; under the mask of every length down to a few steps)
   const bool grid = g.b.side > 0, uneven = grid ? d.causal != 0 : g.by_size != 0;
