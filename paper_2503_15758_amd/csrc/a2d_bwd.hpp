@@ -43,6 +43,35 @@ __device__ __forceinline__ void store_acc_t(float* __restrict__ out_row, const f
     }
 }
 
+// the same of 16 x 16 tiles: HT column tiles, the lane's row of tile kt, columns 16 ht + 4 g + 0..3 of lane group g
+template <int HT, int NT>
+__device__ __forceinline__ void store_acc16(bf16_t* __restrict__ out_row, const f32x4 (&acc)[HT][NT], int kt, int g, float mul) {
+#pragma unroll
+  for (int ht = 0; ht < HT; ++ht) {
+    bf16x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (bf16_t)(acc[ht][kt][e] * mul);
+    *reinterpret_cast<bf16x4*>(out_row + 16 * ht + 4 * g) = v;
+  }
+}
+template <int HT, int NT>
+__device__ __forceinline__ void store_acc16(float* __restrict__ out_row, const f32x4 (&acc)[HT][NT], int kt, int g, float mul,
+                                            bool add = false) {
+#pragma unroll
+  for (int ht = 0; ht < HT; ++ht) {
+    f32x4* p = reinterpret_cast<f32x4*>(out_row + 16 * ht + 4 * g);
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = acc[ht][kt][e] * mul;
+    if (add) {
+      const f32x4 o = *p;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += o[e];
+    }
+    *p = v;
+  }
+}
+
 __device__ __forceinline__ f32x4 lds_load_f32x4(unsigned addr) {
   return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>((uintptr_t)addr);
 }
@@ -63,9 +92,9 @@ constexpr int DK_STAT_BUF = 2 * BQ * 4;
 // ---- dS hand-over to the dQ kernel (optional).  The dK/dV kernel can leave dS (bf16, already
 // multiplied out: P o (dP - delta)) in a workspace, so that the dQ kernel is a plain contraction
 // dQ = scale dS K instead of recomputing S and dP.  Workspace layout: per head, per 32-row tile rt,
-// per 64-key block kb one 4 KiB tile [piece T = 0, 1 (32 keys each)][u = 0, 1 (16 keys each)]
-// [lane 0..63][8 bf16]: lane (row = lane & 31, half = lane >> 5) holds, for the 16 keys
-// 64 kb + 32 T + 16 u + .., the keys 4 half + {0..3} and 8 + 4 half + {0..3} - exactly the B
+// per 64-key block kb one 4 KiB tile [piece T = 0, 1 (32 keys each)][u = 0, 1 (16 rows each)]
+// [lane 0..63][8 bf16]: lane (row = 16 u + (lane & 15), g = lane >> 4) holds, of the 32 keys
+// 64 kb + 32 T + .., the keys 4 g + {0..3} and 16 + 4 g + {0..3} - exactly the B
 // fragment of the dQ kernel's MFMA, so the consumer reads it with one coalesced 16-byte load per
 // lane and the producer writes it with one coalesced 16-byte store per lane.
 constexpr int DS_TILE_BYTES = 4096;
@@ -87,27 +116,40 @@ __device__ __forceinline__ void gstore_b128(gwptr_t base, unsigned byte_off, bf1
   __builtin_nontemporal_store(v, reinterpret_cast<__attribute__((address_space(1))) bf16x8*>(base + byte_off));
 }
 
-// The gradient wave holds dS with lane = key and registers = query rows; the dQ kernel needs
-// lane = query row and registers = keys.  The wave turns its 32 x 32 piece around through LDS (its
-// own mailbox piece, free once the probabilities have been read): each lane writes its four
-// 4-row groups as 8-byte pieces of a [key][row] tile (rows of 72 bytes: conflict-free), and the
-// transposing read returns, per lane, four keys of one row.
-constexpr int DS_TR_LD = 72;
+// The dK/dV wavefronts hold dS with lane = key and registers = query rows; the dQ kernel needs
+// lane = query row and registers = keys.  A wavefront turns its 32 x 32 piece around through LDS: each lane
+// writes its 4-row groups as 8-byte pieces of a [key][row] tile, and the transposing read returns, per lane,
+// four keys of one row.  Rows of 96 bytes (8 banks times an odd number, as row_ld), the two 16-byte chunks of a
+// pair swapped in every other eight keys: neither access has bank conflicts (rows of 80 bytes: twice the cycles).
+constexpr int DS_TR_LD = 96;
+// (rows: the first of four consecutive ones)
+__device__ __forceinline__ unsigned ds_turn_at(unsigned piece, int key, int rows) {
+  return piece + key * DS_TR_LD + ((2 * rows) ^ (16 * ((key >> 3) & 1)));
+}
+// 32 x 32 tiles: lane = key, register group q of the two fragments = rows 8 q + 4 half + 0..3
 __device__ __forceinline__ void ds_turn_write(unsigned piece, int l32, int half, const bf16x8 (&bf)[2]) {
-  const unsigned a = piece + l32 * DS_TR_LD + 8 * half;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const u32x4 w = __builtin_bit_cast(u32x4, bf[u]);
-    // register group g = 2u (w.x, w.y) and g = 2u + 1 (w.z, w.w): rows 8g + 4 half + 0..3
-    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * (2 * u))) = u32x2{w[0], w[1]};
-    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * (2 * u + 1))) = u32x2{w[2], w[3]};
+    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)ds_turn_at(piece, l32, 16 * u + 4 * half)) = u32x2{w[0], w[1]};
+    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)ds_turn_at(piece, l32, 16 * u + 8 + 4 * half)) = u32x2{w[2], w[3]};
+  }
+}
+// 16 x 16 tiles: fragment kt holds key 16 kt + (lane & 15), rows 4 g + 0..3 and 16 + 4 g + 0..3
+__device__ __forceinline__ void ds_turn_write16(unsigned piece, int lane, const bf16x8 (&bf)[2]) {
+  const unsigned a = ds_turn_at(piece, lane & 15, 4 * (lane >> 4));
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) {
+    const u32x4 w = __builtin_bit_cast(u32x4, bf[kt]);
+    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * kt * DS_TR_LD)) = u32x2{w[0], w[1]};
+    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * kt * DS_TR_LD + 32)) = u32x2{w[2], w[3]};
   }
 }
 __device__ __forceinline__ void ds_turn_read(unsigned piece, int lane, bf16x8 (&out)[2]) {
-  const int g16 = lane >> 4, j16 = lane & 15;
-  const unsigned a = piece + (4 * (g16 >> 1) + (j16 >> 2)) * DS_TR_LD + (16 * (g16 & 1) + 4 * (j16 & 3)) * 2;
+  const int g = lane >> 4, j = lane & 15;
+  const unsigned a = ds_turn_at(piece, 4 * g + (j >> 2), 4 * (j & 3));
 #pragma unroll
-  for (int u = 0; u < 2; ++u) out[u] = lds_load_tr(a + 16 * u * DS_TR_LD, a + (16 * u + 8) * DS_TR_LD);
+  for (int u = 0; u < 2; ++u) out[u] = lds_load_tr(a + 32 * u, a + 32 * u + 16 * DS_TR_LD);
 }
 
 }  // namespace mfma

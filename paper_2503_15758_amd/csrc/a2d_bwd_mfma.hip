@@ -76,45 +76,45 @@ constexpr int DSQ_RING = 4;
 constexpr int DSQ_SETS = 3;  // register sets of dS fragments: requests run DSQ_SETS - 1 steps ahead
 template <int HD>
 struct DsqCtx {
-  f32x16 dq[HD / 32];
-  DualAddr ka;          // K tile of the current buffer
-  int my_vis;           // number of leading keys of the current sub-block this lane's query row sees
-  int half;
+  f32x4 dq[HD / 16][2]; // column tiles x the wavefront's two tiles of 16 query rows
+  unsigned kt;          // transposed fragments of the K tile of the current buffer
+  int my_vis[2];        // number of leading keys of the current sub-block this lane's query rows see
+  int grp;
 };
 
-// one 32-key piece (T = 0, 1) of the step: ds[2T], ds[2T + 1] are the two 16-key B fragments;
+// one 32-key piece (T = 0, 1) of the step: ds[2T], ds[2T + 1] are its B fragments of the two row tiles;
 // key0 = the piece's first key, local to its sub-block
 template <int T, bool MASK, int HD>
 __device__ __forceinline__ void dsq_piece(DsqCtx<HD>& cx, const u32x4 (&ds)[4], int key0) {
-  constexpr int CT = HD / 32;
-  constexpr int RB = T * 32 * DUAL_LD;
+  constexpr int HT = HD / 16, LD = row_ld(HD);
   bf16x8 kt[DSQ_RING];
   auto ld = [&](auto I) {
     constexpr int i = decltype(I)::value;
-    kt[i % DSQ_RING] = lds_load_tr(cx.ka.tr_lo + RB + (i / CT) * 16 * DUAL_LD + 64 * (i % CT),
-                                   cx.ka.tr_hi + RB + (i / CT) * 16 * DUAL_LD + 64 * (i % CT));
+    const unsigned at = cx.kt + T * 32 * LD + 32 * i;
+    kt[i % DSQ_RING] = lds_load_tr(at, at + 16 * LD);
     __builtin_amdgcn_sched_barrier(0);
   };
-  static_for<0, (DSQ_RING < 2 * CT ? DSQ_RING : 2 * CT)>(ld);
+  static_for<0, (DSQ_RING < HT ? DSQ_RING : HT)>(ld);
   bf16x8 dsb[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     u32x4 w = ds[2 * T + u];
     if (MASK) {
-      // element e of the fragment <-> key key0 + 16u + 8 (e >> 2) + 4 half + (e & 3); two per word
+      // element e of the fragment <-> key key0 + 16 (e >> 2) + 4 grp + (e & 3); two per word
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        const int k = key0 + 16 * u + 8 * (x >> 1) + 4 * cx.half + 2 * (x & 1);
-        const unsigned keep = (k < cx.my_vis ? 0x0000FFFFu : 0u) | (k + 1 < cx.my_vis ? 0xFFFF0000u : 0u);
+        const int k = key0 + 16 * (x >> 1) + 4 * cx.grp + 2 * (x & 1);
+        const unsigned keep = (k < cx.my_vis[u] ? 0x0000FFFFu : 0u) | (k + 1 < cx.my_vis[u] ? 0xFFFF0000u : 0u);
         w[x] &= keep;
       }
     }
     dsb[u] = __builtin_bit_cast(bf16x8, w);
   }
-  static_for<0, 2 * CT>([&](auto I) {
+  static_for<0, HT>([&](auto I) {
     constexpr int i = decltype(I)::value;
-    cx.dq[i % CT] = mma(kt[i % DSQ_RING], dsb[i / CT], cx.dq[i % CT]);
-    if constexpr (i + DSQ_RING < 2 * CT) ld(std::integral_constant<int, i + DSQ_RING>{});
+#pragma unroll
+    for (int u = 0; u < 2; ++u) cx.dq[i][u] = mma16(kt[i % DSQ_RING], dsb[u], cx.dq[i][u]);
+    if constexpr (i + DSQ_RING < HT) ld(std::integral_constant<int, i + DSQ_RING>{});
   });
 }
 
@@ -131,9 +131,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   constexpr int RW = WAVES / KL;                       // wavefronts of one key lane
   constexpr int DQ_ROWS = 32 * RW, DQ_THREADS = 64 * RW;   // rows of the workgroup, threads of one key lane
   const int kl = KL == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / DQ_THREADS);
-  char* const lds = lds_all + kl * (2 * DUAL64_BYTES);
+  constexpr int HD = padded_head(HR), H = HR, HT = HD / 16, LD = row_ld(HD), TILE = BKS * LD;
+  char* const lds = lds_all + kl * (2 * TILE);
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-  constexpr int HD = padded_head(HR), H = HR, CT = HD / 32;
   const int nqb = (d.nq + DQ_ROWS - 1) / DQ_ROWS;
   // placement as in bwd_dq_kernel (grouped heads: the query heads of a key/value head share an XCD)
   int unit, blk;
@@ -144,17 +144,16 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   const int q0 = (nqb - 1 - blk) * DQ_ROWS;            // heavy blocks first under a causal mask
   const int tid = (int)threadIdx.x - kl * DQ_THREADS;  // within the key lane
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int l32 = lane & 31;
   K += (int64_t)kvh * d.lk.head;
 
   DsqCtx<HD> cx;
-  cx.half = lane >> 5;
-  const int q_row = q0 + wave * 32 + l32;
-  const bool q_ok = q_row < d.nq;
-  const int q_ld = min(q_row, d.nq - 1);
+  cx.grp = lane >> 4;
+  const int q_row = q0 + wave * 32 + (lane & 15);      // of the first row tile
 #pragma unroll
-  for (int t = 0; t < CT; ++t) cx.dq[t] = zero16();
-  cx.ka.init(lane, lds_base);
+  for (int t = 0; t < HT; ++t) cx.dq[t][0] = cx.dq[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Rows16 at;
+  at.init(lane, lds_base, LD);
+  cx.kt = at.tr;
 
   // this wavefront's row tile of dS (a wavefront past the last row reads the last tile; its
   // results are never stored)
@@ -209,7 +208,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
       }
       nvis_wave = vis_count(w_last, c_sb);
       nfull_wave = vis_count(w_first, c_sb);
-      cx.my_vis = vis_count(q_ld, c_sb);
+      for (int u = 0; u < 2; ++u) cx.my_vis[u] = vis_count(min(q_row + 16 * u, d.nq - 1), c_sb);
     }
   };
 
@@ -228,9 +227,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     }
   };
   auto store_k = [&](int buf) {
-    char* b = lds + buf * DUAL64_BYTES;
+    char* b = lds + buf * TILE;
 #pragma unroll
-    for (int p = 0; p < ST_N; ++p) *reinterpret_cast<u32x4*>(b + dual_store_off(st_row + ST_ROWS * p, st_ch)) = kreg[p];
+    for (int p = 0; p < ST_N; ++p) *reinterpret_cast<u32x4*>(b + (st_row + ST_ROWS * p) * LD + st_ch * 16) = kreg[p];
   };
   u32x4 ds[DSQ_SETS][4];
   auto load_ds = [&](int id, auto set_tag) {
@@ -244,9 +243,15 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     }
   };
 
+  auto store_rows = [&](float mul, bool add) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (q_row + 16 * u < d.nq)
+        store_acc16(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row + 16 * u) * H, cx.dq, u, cx.grp, mul, add);
+  };
   count = count > part * KL ? count - part * KL : 0;           // from this part's first block on
   if (count == 0) {                                // no visible key: dQ share is zero
-    if (q_ok && !g.acc && kl == 0) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, 0.f, H, false);
+    if (!g.acc && kl == 0) store_rows(0.f, false);
     return;
   }
   // (the first block is block 0; a lane without one re-reads the last block it passed)
@@ -285,7 +290,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 #pragma unroll
     for (int x = 0; x + 1 < DSQ_SETS - 2; ++x) idq[x] = idq[x + 1];
     idq[DSQ_SETS - 3] = f_id;
-    cx.ka.shift(buf ? -DUAL64_BYTES : DUAL64_BYTES);
+    cx.kt += buf ? -TILE : TILE;
     buf ^= 1;
     compute_by(stride);
     __syncthreads();
@@ -295,22 +300,22 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   if constexpr (KL == 2) {
     // lane 1 hands its sums to lane 0 through LDS (the K tiles are no longer read: every wavefront
     // has passed the walk's last barrier); layout [row wavefront][value][lane]: conflict free
-    static_assert(RW * CT * 16 * 256 <= KL * 2 * DUAL64_BYTES, "the exchange area must fit the K buffers");
-    float* xch = reinterpret_cast<float*>(lds_all) + wave * (CT * 16 * 64) + lane;
+    static_assert(RW * HT * 8 * 256 <= KL * 2 * TILE, "the exchange area must fit the K buffers");
+    float* xch = reinterpret_cast<float*>(lds_all) + wave * (HT * 8 * 64) + lane;
     if (kl == 1) {
 #pragma unroll
-      for (int t = 0; t < CT; ++t)
+      for (int t = 0; t < HT; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) xch[(16 * t + r) * 64] = cx.dq[t][r];
+        for (int r = 0; r < 8; ++r) xch[(8 * t + r) * 64] = cx.dq[t][r >> 2][r & 3];
     }
     __syncthreads();
     if (kl == 1) return;
 #pragma unroll
-    for (int t = 0; t < CT; ++t)
+    for (int t = 0; t < HT; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) cx.dq[t][r] += xch[(16 * t + r) * 64];
+      for (int r = 0; r < 8; ++r) cx.dq[t][r >> 2][r & 3] += xch[(8 * t + r) * 64];
   }
-  if (q_ok) store_acc_t<CT>(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, g.acc != 0);
+  store_rows(d.scale, g.acc != 0);
 }
 
 }  // namespace
@@ -338,7 +343,7 @@ template <int HR>
 hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                          const void* V, const void* dO, const float* lse, const float* delta, float* dQ, float* dK,
                          float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
-  constexpr int DSQ_LDS = 2 * DUAL64_BYTES;
+  constexpr int DSQ_LDS = 2 * BKS * row_ld(padded_head(HR));
   const bool grouped = g.group > 1;
   hipError_t e = hipSuccess;
   SegList gk = g, gq = g;

@@ -14,21 +14,25 @@ namespace mfma {
 // its staging, its LDS latencies - holds twice the MFMAs.  In program order the exponentials stand
 // under the dP MFMAs and the products dS under the dV MFMAs.  The scores start from -lse / scale
 // and dP from -delta, so that p = exp2(c s) and dS = p dP need no further operand.
-// Measured per 32 rows x 256 keys, H = 128 / 96 / 80 / 64: 1.51 / 1.22 / 1.17 / 0.99 us against 2.26 / 1.92 /
-// 1.86 / 1.58 us in pairs; the call at 96 x 4096 x 4096 H = 128 2.80 -> 2.60 ms (dS kept: 2.60 -> 2.43 ms), at
+// Against the pairs: the call at 96 x 4096 x 4096 H = 128 2.80 -> 2.60 ms (dS kept: 2.60 -> 2.43 ms), at
 // 32 x 1999 x 2777 H = 80 causal 217 -> 190 us.
+// Bound by the chip's power at 1.8-1.9 GHz with the matrix units 55 % busy, so the contractions run on
+// v_mfma_f32_16x16x32_bf16: an MFMA of 16 x 16 x 32 reads and writes half the accumulators per flop of one of 32 x 32 x 16
+// (MFMAs alone on normal operands sustain 1.94-1.99 PFLOP/s against 1.72-1.76), and H = 80 fills five column tiles of 16
+// instead of three of 32.  64 x 4096 x 4096, H = 128 / 96 / 80 / 64: 1065 / 749 / 697 / 571 -> 1010 / 727 / 669 / 543 us, 1199 ->
+// 1183 with dS.  Each fragment still serves two MFMAs (the 32 keys of a wavefront), so the LDS reads are the same.
 // (One wavefront per SIMD with two tiles of 32 keys, which halves the LDS reads again, issues too
 // slowly: 2.8 us at H = 128.)
 // Not for tiles with few keys, whose workgroups it halves (see plan_bwd_mfma).
 constexpr int WK_KEYS = 256, WK_THREADS = 512;
 // LDS: two buffers { Q tile, dO tile } | two of { -lse / scale [32], -delta [32] } | a wavefront's piece
 // for turning dS | V (H = 128; rows of 272 bytes)
-constexpr int WK_STAT = 2 * DK_BUF;
-constexpr int WK_TURN = WK_STAT + 2 * DK_STAT_BUF;
+__host__ __device__ constexpr int wk_tile(int hd) { return BQ * row_ld(hd); }
+__host__ __device__ constexpr int wk_stat(int hd) { return 4 * wk_tile(hd); }
+__host__ __device__ constexpr int wk_turn(int hd) { return wk_stat(hd) + 2 * DK_STAT_BUF; }
 constexpr int WK_TURN_BYTES = 32 * DS_TR_LD;
-constexpr int WK_V = WK_TURN + 8 * WK_TURN_BYTES;
-constexpr int WK_VLD = 272;
-__host__ __device__ constexpr int wk_lds(int hd) { return WK_V + (hd == 128 ? WK_KEYS * WK_VLD : 0); }
+__host__ __device__ constexpr int wk_v(int hd) { return wk_turn(hd) + 8 * WK_TURN_BYTES; }
+__host__ __device__ constexpr int wk_lds(int hd) { return wk_v(hd) + (hd == 128 ? WK_KEYS * row_ld(hd) : 0); }
 
 // GRID: all key blocks of an emulated grid (g.b).  The workgroup walks the query rows of its whole grid column and
 // writes rows of dK and dV of the sequence (of a split walk: a partial, [part][column][head][key]).  Contiguous blocks
@@ -41,8 +45,8 @@ __device__ __forceinline__ void dkdv_wide(
     const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV,
     bf16_t* __restrict__ dS) {
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-  constexpr int HD = padded_head(HR), H = HR, CT = HD / 32;
-  constexpr int KS = (HR + 15) / 16;               // slices of H that hold data
+  constexpr int HD = padded_head(HR), H = HR, LD = row_ld(HD), TILE = wk_tile(HD), BUF = 2 * TILE;
+  constexpr int KS = HD / 32, HT = HR / 16;        // slices of H in the first two contractions, column tiles of the others
   constexpr bool V_LDS = HD == 128;
   // At H = 128 the accumulators and K^T leave 96 registers: shorter fragment rings, and per-lane addresses
   // that are used once a step are computed again in every step.
@@ -67,7 +71,7 @@ __device__ __forceinline__ void dkdv_wide(
   const int nq = GRID == 1 ? g.b.side * d.nq : d.nq, head_rows = nq * side;    // rows of a run; of a query head
   const int col_first = GRID == 1 && d.causal ? col * d.nkv : 0;               // the row that sees the column's first key
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int l32 = lane & 31, half = lane >> 5;
+  const int l16 = lane & 15, grp = lane >> 4;
   Q += (int64_t)qh0 * d.lq.head;
   dO += (int64_t)qh0 * d.ldo.head;
   K += (int64_t)head * d.lk.head + (GRID ? col * g.b.k : 0);
@@ -76,21 +80,26 @@ __device__ __forceinline__ void dkdv_wide(
   delta += (int64_t)qh0 * head_rows;
   const float c = d.scale * kLog2e, inv_scale = 1.0f / d.scale;
 
-  // ---- K^T and V^T fragments of the wavefront's 32 keys: lane = key.  Keys beyond nkv
-  // re-read the last key; the mask zeroes their probabilities.
-  const int wk = k0 + wave * 32, key = wk + l32;
-  bf16x8 kf[KS], vf[KS];
-  {
-    const int64_t r = min(key, d.nkv - 1);
+  // ---- K^T and V^T fragments of the wavefront's 32 keys, two tiles of 16: lane = key.  Keys beyond nkv
+  // re-read the last key; the mask zeroes their probabilities.  (Columns past the head size are zero.)
+  const int wk = k0 + wave * 32, key = wk + l16;   // (of tile 0)
+  bf16x8 kf[KS][2], vf[KS][2];
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) {
+    const int64_t r = min(key + 16 * kt, d.nkv - 1);
 #pragma unroll
     for (int x = 0; x < KS; ++x) {
-      kf[x] = *reinterpret_cast<const bf16x8*>(K + r * d.lk.row + 16 * x + 8 * half);
-      vf[x] = *reinterpret_cast<const bf16x8*>(V + r * d.lv.row + 16 * x + 8 * half);
+      const int at = 32 * x + 8 * grp, ld = min(at, H - 8);
+      kf[x][kt] = *reinterpret_cast<const bf16x8*>(K + r * d.lk.row + ld);
+      vf[x][kt] = *reinterpret_cast<const bf16x8*>(V + r * d.lv.row + ld);
+      if (32 * x + 32 > H && at >= H) kf[x][kt] = vf[x][kt] = bf16x8{};
     }
   }
-  f32x16 dk[CT], dv[CT];
+  f32x4 dk[HT][2], dv[HT][2];
 #pragma unroll
-  for (int x = 0; x < CT; ++x) { dk[x] = zero16(); dv[x] = zero16(); }
+  for (int x = 0; x < HT; ++x)
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) dk[x][kt] = dv[x][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // ---- which rows see which keys (as in bwd_dkdv_kernel)
   auto seg_first_row = [&](int sb, int r) -> int {
@@ -123,12 +132,15 @@ __device__ __forceinline__ void dkdv_wide(
       if (CYCLIC) { r0 = s0 % side; s0 /= side; }
     }
   }
-  int my_first = nq;                               // first row that sees this lane's key; padding keys see nothing
-  if (key < d.nkv) {
-    my_first = GRID && d.causal ? col_first + key : 0;
+  int my_first[2] = {nq, nq};                      // first row that sees this lane's keys; padding keys see nothing
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) {
+    const int k = key + 16 * kt;
+    if (k >= d.nkv) continue;
+    my_first[kt] = GRID && d.causal ? col_first + k : 0;
     if (!GRID && d.causal) {
       for (int sb = 0; sb < g.n; ++sb)
-        if (key >= g.seg[sb].start && key < g.seg[sb].start + g.seg[sb].rows) my_first = seg_first_row(sb, key);
+        if (k >= g.seg[sb].start && k < g.seg[sb].start + g.seg[sb].rows) my_first[kt] = seg_first_row(sb, k);
     }
   }
   int w_any = nq, w_all = nq;                      // rows below w_any see none of the wavefront's keys, from w_all on all
@@ -182,18 +194,18 @@ __device__ __forceinline__ void dkdv_wide(
     const int tid = TIGHT ? wave * 64 + lane_again() : threadIdx.x;
     const int st_row = tid >> 4, st_ch = tid & 15;
     const bool ch_data = st_ch * 8 < H, ch_tile = st_ch * 8 < HD;
-    char* b = lds + buf * DK_BUF;
+    char* b = lds + buf * BUF;
     if (HD == 128 || ch_tile) {
       const u32x4 zero = {0, 0, 0, 0};
-      const int off = dual_store_off(st_row, st_ch);
+      const int off = st_row * LD + st_ch * 16;
       *reinterpret_cast<u32x4*>(b + off) = (HD == 128 || ch_data) ? qreg : zero;
-      *reinterpret_cast<u32x4*>(b + DK_TILE + off) = (HD == 128 || ch_data) ? greg : zero;
+      *reinterpret_cast<u32x4*>(b + TILE + off) = (HD == 128 || ch_data) ? greg : zero;
     }
     if (tid < 2 * BQ) {
       float v = -stat;
       if (tid < BQ) v = (!stat_ok || v == INFINITY) ? -INFINITY : v * inv_scale;
       else v = stat_ok ? v : 0.f;
-      reinterpret_cast<float*>(lds + WK_STAT + buf * DK_STAT_BUF)[tid] = v;
+      reinterpret_cast<float*>(lds + wk_stat(HD) + buf * DK_STAT_BUF)[tid] = v;
     }
   };
   if (total > 0) load_step();
@@ -202,114 +214,116 @@ __device__ __forceinline__ void dkdv_wide(
     store_step(0);
     load_step();
   }
-  const unsigned v_nat = lds_base + WK_V + (wave * 32 + l32) * WK_VLD + 16 * half;
+  const unsigned v_nat = lds_base + wk_v(HD) + (wave * 32 + l16) * LD + 16 * grp;
   if constexpr (V_LDS) {
 #pragma unroll
     for (int x = 0; x < KS; ++x)
-      *reinterpret_cast<__attribute__((address_space(3))) bf16x8*>((uintptr_t)(v_nat + 32 * x)) = vf[x];
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+        *reinterpret_cast<__attribute__((address_space(3))) bf16x8*>((uintptr_t)(v_nat + 64 * x + 16 * kt * LD)) = vf[x][kt];
   }
   __syncthreads();
 
   // dS hand-over: the wavefront's 32 keys are piece wave & 1 of key block 4 blk + wave / 2
   const unsigned ds_row_stride = (unsigned)ds_key_blocks(d.nkv) * DS_TILE_BYTES;
   const unsigned ds_wave_off = (unsigned)(8 * blk + wave) * (DS_TILE_BYTES / 2);
-  const unsigned turn = lds_base + WK_TURN + wave * WK_TURN_BYTES;
+  const unsigned turn = lds_base + wk_turn(HD) + wave * WK_TURN_BYTES;
   gwptr_t ds_base = nullptr;
   if constexpr (WRITE_DS)
     ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) + qh0 * ds_head_bytes(d.nq, d.nkv));
 
-  DualAddr da;
-  da.init(lane, lds_base);
-  unsigned st_addr = lds_base + WK_STAT + 16 * half;
+  Rows16 da;
+  da.init(lane, lds_base, LD);
+  unsigned st_addr = lds_base + wk_stat(HD) + 16 * grp;
 
-  // One step.  Fragments (A operands) in the order of their use: Q and dO rows, transposed dO, transposed
-  // Q; each is requested RING fragments ahead.
+  // One step: S and dP of the 32 rows in tiles of 16 rows (t) x 16 keys (kt), lane = key, registers = rows 16 t + 4 grp + 0..3.
+  // The two row tiles' registers are the eight contraction indices of a lane in dV^T += dO^T P and dK^T += Q^T dS.  An A
+  // fragment serves both key tiles.  Fragments in the order of their use: Q and dO rows (slice i >> 1, row tile i & 1),
+  // transposed dO, transposed Q; each is requested RING fragments ahead.
   // (i0: its first row, `rows` those of a run - both one less where the keys are seen a row later)
   auto compute = [&](int i0, int rows, unsigned ds_off, bool masked) {
-    constexpr int N1 = KS, N2 = 2 * KS, N3 = N2 + 2 * CT, N4 = N3 + 2 * CT, RING = TIGHT ? 2 : 4;
-    bf16x8 a[RING], va[2];
+    constexpr int N1 = 2 * KS, N2 = 4 * KS, N3 = N2 + HT, N4 = N3 + HT, RING = TIGHT ? 2 : 4;
+    bf16x8 a[RING], va[4];
     auto ld = [&](auto I) {
       constexpr int i = decltype(I)::value;
-      if constexpr (i < N1) a[i % RING] = dual_nat<i>(da, 0);
-      else if constexpr (i < N2) a[i % RING] = dual_nat<i - N1>(da, DK_TILE);
+      if constexpr (i < N2) a[i % RING] = lds_load_b128(da.nat + (i < N1 ? 0 : TILE) + 64 * (i % N1 >> 1) + 16 * LD * (i & 1));
       else if constexpr (i < N4) {
-        constexpr int y = i < N3 ? i - N2 : i - N3;
-        constexpr int at = (i < N3 ? DK_TILE : 0) + (y / CT) * 16 * DUAL_LD + 64 * (y % CT);
-        a[i % RING] = lds_load_tr(da.tr_lo + at, da.tr_hi + at);
+        const unsigned at = da.tr + (i < N3 ? TILE + 32 * (i - N2) : 32 * (i - N3));
+        a[i % RING] = lds_load_tr(at, at + 16 * LD);
       }
     };
-    auto ldv = [&](auto X) {
+    auto ldv = [&](auto X) {                       // V^T fragment of slice x >> 1, key tile x & 1
       constexpr int x = decltype(X)::value;
-      if constexpr (V_LDS && x < KS) va[x & 1] = lds_load_b128(v_nat + 32 * x);
+      if constexpr (V_LDS && x < N1) va[x & 3] = lds_load_b128(v_nat + 64 * (x >> 1) + 16 * LD * (x & 1));
     };
     static_for<0, RING>(ld);
-    f32x16 s, dp;
+    f32x4 s[2][2], dp[2][2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 v = lds_load_f32x4(st_addr + 32 * q);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[4 * q + e] = v[e];
-    }
+    for (int t = 0; t < 2; ++t) s[t][0] = s[t][1] = lds_load_f32x4(st_addr + 64 * t);
     __builtin_amdgcn_sched_barrier(0);
-    static_for<0, KS>([&](auto X) {
-      constexpr int x = decltype(X)::value;
-      s = mma(a[x % RING], kf[x], s);
-      ld(std::integral_constant<int, x + RING>{});
-      if constexpr (x + 2 >= KS) ldv(std::integral_constant<int, x + 2 - KS>{});
+    static_for<0, N1>([&](auto I) {
+      constexpr int i = decltype(I)::value, x = i >> 1, t = i & 1;
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) s[t][kt] = mma16(a[i % RING], kf[x][kt], s[t][kt]);
+      ld(std::integral_constant<int, i + RING>{});
+      if constexpr (i + 2 >= N1) ldv(std::integral_constant<int, i + 2 - N1>{});
       __builtin_amdgcn_sched_barrier(0);
     });
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 v = lds_load_f32x4(st_addr + BQ * 4 + 32 * q);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dp[4 * q + e] = v[e];
-    }
+    for (int t = 0; t < 2; ++t) dp[t][0] = dp[t][1] = lds_load_f32x4(st_addr + BQ * 4 + 64 * t);
     bf16x8 pb[2], sb[2];
-    // Register r of a tile <-> row i0 + 8 (r >> 2) + 4 half + (r & 3).  Hidden pairs, and rows past the end, are
-    // taken out of the finished scores, not by where these start from: q.k may have overflowed there.
+    // Hidden pairs, and rows past the end, are taken out of the finished scores, not by where these start from: q.k may
+    // have overflowed there.
     auto mask = [&]() {
       if (masked) {
-        const int first = i0 + 4 * half - my_first;
-        const unsigned limit = CYCLIC ? max(rows - my_first, 0) : rows - my_first;   // (padding keys: none)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if ((unsigned)(first + 8 * (r >> 2) + (r & 3)) >= limit) s[r] = -INFINITY;
+        for (int kt = 0; kt < 2; ++kt) {
+          const int first = i0 + 4 * grp - my_first[kt];
+          const unsigned limit = CYCLIC ? max(rows - my_first[kt], 0) : rows - my_first[kt];   // (padding keys: none)
+#pragma unroll
+          for (int r = 0; r < 8; ++r)
+            if ((unsigned)(first + 16 * (r >> 2) + (r & 3)) >= limit) s[r >> 2][kt][r & 3] = -INFINITY;
+        }
       }
     };
+    // score r of the lane's 16: key tile r >> 3, element r & 7 of its fragment
     auto prob = [&](int r) {
-      const float p = fast_exp2(s[r] * c);
-      s[r] = p;
+      const float p = fast_exp2(s[(r >> 2) & 1][r >> 3][r & 3] * c);
+      s[(r >> 2) & 1][r >> 3][r & 3] = p;
       pb[r >> 3][r & 7] = (bf16_t)p;
     };
-    auto dscore = [&](int r) { sb[r >> 3][r & 7] = (bf16_t)(s[r] * dp[r]); };
-    static_for<0, KS>([&](auto X) {
-      constexpr int x = decltype(X)::value;
-      dp = mma(a[(N1 + x) % RING], V_LDS ? va[x & 1] : vf[x], dp);
-      if constexpr (x == 0) mask();
+    auto dscore = [&](int r) { sb[r >> 3][r & 7] = (bf16_t)(s[(r >> 2) & 1][r >> 3][r & 3] * dp[(r >> 2) & 1][r >> 3][r & 3]); };
+    static_for<0, N1>([&](auto I) {
+      constexpr int i = decltype(I)::value, x = i >> 1, t = i & 1;
 #pragma unroll
-      for (int r = 16 * x / KS; r < 16 * (x + 1) / KS; ++r) prob(r);
-      ld(std::integral_constant<int, N1 + x + RING>{});
-      ldv(std::integral_constant<int, x + 2>{});
+      for (int kt = 0; kt < 2; ++kt) dp[t][kt] = mma16(a[(N1 + i) % RING], V_LDS ? va[(2 * x + kt) & 3] : vf[x][kt], dp[t][kt]);
+      if constexpr (i == 0) mask();
+#pragma unroll
+      for (int r = 16 * i / N1; r < 16 * (i + 1) / N1; ++r) prob(r);
+      ld(std::integral_constant<int, N1 + i + RING>{});
+      ldv(std::integral_constant<int, i + 2>{});
       __builtin_amdgcn_sched_barrier(0);
     });
-    static_for<0, 2 * CT>([&](auto Y) {
+    static_for<0, HT>([&](auto Y) {
       constexpr int y = decltype(Y)::value;
-      dv[y % CT] = mma(a[(N2 + y) % RING], pb[y / CT], dv[y % CT]);
 #pragma unroll
-      for (int r = 16 * y / (2 * CT); r < 16 * (y + 1) / (2 * CT); ++r) dscore(r);
+      for (int kt = 0; kt < 2; ++kt) dv[y][kt] = mma16(a[(N2 + y) % RING], pb[kt], dv[y][kt]);
+#pragma unroll
+      for (int r = 16 * y / HT; r < 16 * (y + 1) / HT; ++r) dscore(r);
       ld(std::integral_constant<int, N2 + y + RING>{});
       __builtin_amdgcn_sched_barrier(0);
     });
-    static_for<0, 2 * CT>([&](auto Y) {
+    static_for<0, HT>([&](auto Y) {
       constexpr int y = decltype(Y)::value;
-      dk[y % CT] = mma(a[(N3 + y) % RING], sb[y / CT], dk[y % CT]);
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) dk[y][kt] = mma16(a[(N3 + y) % RING], sb[kt], dk[y][kt]);
       ld(std::integral_constant<int, N3 + y + RING>{});
       __builtin_amdgcn_sched_barrier(0);
     });
     if constexpr (WRITE_DS) {
       const int ln = TIGHT ? lane_again() : lane;
       bf16x8 out[2];
-      ds_turn_write(turn, ln & 31, ln >> 5, sb);
+      ds_turn_write16(turn, ln, sb);
       ds_turn_read(turn, ln, out);
       gstore_b128(ds_base, ds_off + 16 * ln, out[0]);
       gstore_b128(ds_base, ds_off + 16 * ln + 1024, out[1]);
@@ -335,23 +349,26 @@ __device__ __forceinline__ void dkdv_wide(
       cs = wrap ? 0 : cs + 1;
       cr = 0;
     }
-    da.shift(buf ? -DK_BUF : DK_BUF);
+    da.shift(buf ? -BUF : BUF);
     st_addr += buf ? -DK_STAT_BUF : DK_STAT_BUF;
     buf ^= 1;
     __syncthreads();
   }
 
-  if (GRID && parts == 1) {
-    if (key < d.nkv) {
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) {
+    const int k = key + 16 * kt;
+    if (k >= d.nkv) continue;
+    if (GRID && parts == 1) {
       bf16_t* const dkb = reinterpret_cast<bf16_t*>(dK) + head * g.b.out[1].head + col * g.b.out_step[1];
       bf16_t* const dvb = reinterpret_cast<bf16_t*>(dV) + head * g.b.out[2].head + col * g.b.out_step[2];
-      store_acc_t<CT>(dvb + key * g.b.out[2].row, dv, half, 1.0f, H);
-      store_acc_t<CT>(dkb + key * g.b.out[1].row, dk, half, d.scale, H);
+      store_acc16(dvb + k * g.b.out[2].row, dv, kt, grp, 1.0f);
+      store_acc16(dkb + k * g.b.out[1].row, dk, kt, grp, d.scale);
+    } else {
+      const int64_t row = (int64_t)head * d.nkv + k;
+      store_acc16(dV + row * H, dv, kt, grp, 1.0f);
+      store_acc16(dK + row * H, dk, kt, grp, d.scale);
     }
-  } else if (key < d.nkv) {
-    const int64_t row = (int64_t)head * d.nkv + key;
-    store_acc_t<CT>(dV + row * H, dv, half, 1.0f, H);
-    store_acc_t<CT>(dK + row * H, dk, half, d.scale, H);
   }
 }
 

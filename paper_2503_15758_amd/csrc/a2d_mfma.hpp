@@ -2,10 +2,14 @@
 // fragment layouts, LDS fragment reads, the "dual" LDS tile layout, scalar-base global loads and
 // the XCD-aware work mapping.
 //
-// MFMA used everywhere: v_mfma_f32_32x32x16_bf16, D(32x32) += A(32x16) * B(16x32).
+// v_mfma_f32_32x32x16_bf16, D(32x32) += A(32x16) * B(16x32):
 //   A fragment: lane holds row (lane & 31), contraction indices 8*(lane>>5) + 0..7
 //   B fragment: lane holds column (lane & 31), contraction indices 8*(lane>>5) + 0..7
 //   D: lane holds column (lane & 31); register r is row 8*(r>>2) + 4*(lane>>5) + (r&3)
+// v_mfma_f32_16x16x32_bf16, D(16x16) += A(16x32) * B(32x16):
+//   A, B fragments: lane holds row / column (lane & 15), contraction indices 8*(lane>>4) + 0..7
+//   D: lane holds column (lane & 15); register r is row 4*(lane>>4) + r
+// The large tiles' backward runs on the latter, which costs less power per flop (see a2d_bwd_wide.hpp).
 // Two kinds of fragment reads from a row-major LDS tile (rows x padded head size, bf16):
 //   - "natural" fragments (contraction along H): one 128-bit read per lane;
 //   - "transposed" fragments (contraction along the row index): two ds_read_b64_tr_b16, where a
@@ -44,6 +48,10 @@ __device__ __forceinline__ f32x16 zero16() {
 
 __device__ __forceinline__ f32x16 mma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 // eight consecutive D registers -> one bf16 B/A fragment (round to nearest even)
@@ -163,6 +171,23 @@ struct DualAddr {
 };
 // byte offset inside a dual tile at which the 16-byte chunk `c` of row `r` is stored
 __device__ __forceinline__ int dual_store_off(int r, int c) { return r * DUAL_LD + ((c ^ ((r >> 2) & 3)) << 4); }
+
+// Tiles of the 16 x 16 x 32 kernels: rows of the padded head's bytes + 32, no swizzle.  The row stride is an odd multiple
+// of 8 banks (288, 224, 160 bytes), which makes both kinds of fragment reads conflict free:
+//   - natural fragment of rows RB + (lane & 15), slice sl of 32 columns: nat + 64 sl + RB ld;
+//   - transposed fragment of column tile ht (16 columns), rows RB + 4 g + 0..3 and RB + 16 + 4 g + 0..3 of lane group
+//     g = lane >> 4: tr + 32 ht + RB ld and 16 ld further on.
+// (272 bytes or a swizzle of the chunks cost the natural reads 1.55 times the cycles, the former the transposing ones too.)
+__host__ __device__ constexpr int row_ld(int hd) { return 2 * hd + 32; }
+struct Rows16 {
+  unsigned nat, tr;
+  __device__ __forceinline__ void init(int lane, unsigned tile_base, int ld) {
+    const int g = lane >> 4, j = lane & 15;
+    nat = tile_base + j * ld + 16 * g;
+    tr = tile_base + (4 * g + (j >> 2)) * ld + 8 * (j & 3);
+  }
+  __device__ __forceinline__ void shift(int delta) { nat += delta; tr += delta; }
+};
 
 // XCD-aware work mapping.  MI355X has 8 XCDs, each with its own L2, and hands consecutive
 // workgroup ids to consecutive XCDs (id % 8).  All blocks of one head read the same K / V (or

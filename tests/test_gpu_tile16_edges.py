@@ -1,0 +1,24 @@
+"""The 16 x 16 tiles inside a wavefront's 32 rows and keys, at their edges: sizes one off multiples of 16, diagonals at every
+offset within a tile, against fp64 on the GPU."""
+import pytest
+
+from test_gpu_bwd_routes import _check
+
+pytestmark = pytest.mark.gpu
+
+# heads, kv_heads, nq, nkv, H, causal, q_off, sub-blocks, packed; dK/dV in 256 keys a workgroup, dS kept where H = 128
+BACKWARD = [(600, 600, nq, nkv, H, causal, q_off, None, False)
+            for nq, nkv, H, causal, q_off in [
+                (15, 257, 128, False, 0), (17, 271, 128, True, 240), (33, 273, 128, True, 243), (47, 289, 128, True, 257),
+                (49, 303, 96, True, 271), (16, 272, 80, True, 259), (31, 305, 80, False, 0), (65, 287, 64, True, 239)]]
+
+
+@pytest.mark.parametrize("keep", [False, True])
+@pytest.mark.parametrize("case", BACKWARD, ids=lambda c: "%dx%dH%d_%d" % (c[2], c[3], c[4], c[6]))
+def test_backward_tile_edges(case, keep):
+    from paper_2503_15758_amd import binding as a2d
+    heads, kvh, nq, nkv, H, causal, q_off = case[:7]
+    route = a2d.tile_route(heads, nq, nkv, H, causal=causal, q_off=q_off, backward=True, ds_handover=keep)
+    assert route["keys"] == 256, route
+    assert ("bwd_dq_ds_kernel" in route["kernels"]) == (keep and H == 128), route
+    _check(case, keep)
