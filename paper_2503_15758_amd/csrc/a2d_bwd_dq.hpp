@@ -8,72 +8,79 @@ namespace a2d {
 namespace mfma {
 
 constexpr int BKS = 64;           // keys per step
-// LDS: [buf]{ K tile (dual layout), V tile (natural reads only: rows of the head's bytes + 16) }
-__host__ __device__ constexpr int vt_ld(int hd) { return hd * 2 + 16; }
-constexpr int DQ_VT = DUAL64_BYTES;
-__host__ __device__ constexpr int dq_buf(int hd) { return DUAL64_BYTES + BKS * vt_ld(hd); }
+// LDS: [buf]{ K tile, V tile }
+__host__ __device__ constexpr int dq_buf(int hd) { return 2 * BKS * row_ld(hd); }
 __host__ __device__ constexpr int dq_lds(int hd) { return 2 * dq_buf(hd); }
 // fragment ring depth (registers are tight above H = 64: 256 per wavefront)
 __host__ __device__ constexpr int dq_ring(int hd) { return hd == 64 ? 4 : 2; }
 
-template <int HD>
+template <int HR>
 struct DqCtx {
-  f32x16 dq[HD / 32];
-  bf16x8 qf[HD / 16], gf[HD / 16];
-  DualAddr ka;          // K tile of the current buffer
-  unsigned vnat;        // natural-fragment base in the V tile of the current buffer
-  float c, lse2, del;
-  int my_vis;           // number of leading local keys this lane's query row sees
-  int half;
+  static constexpr int KS = padded_head(HR) / 32, HT = HR / 16;
+  f32x4 dq[HT][2];              // column tiles x the wavefront's two tiles of 16 query rows
+  bf16x8 qf[KS][2], gf[KS][2];  // slices of H x row tiles
+  f32x4 start[2];               // -delta: what dP starts from, so that the contraction yields dP - delta
+  Rows16 ka;                    // K tile of the current buffer (the V tile stands dq_buf / 2 behind it)
+  float c, lse2[2];
+  int my_vis[2];                // number of leading local keys this lane's query rows see
+  int grp;
 };
 
-// one 32-key x 32-query piece: T selects the half of the 64-key step.  HD / 16 slices of H in the
-// two first contractions (S^T and dP^T, alternating), 2 * HD / 32 MFMAs in dQ^T += K^T dS^T
-// (step I: 16-key group I / CT, column tile I % CT); fragments run two steps ahead of their use.
-// (KS: the slices that hold data - a head size of 80 fills five of the padded six)
-template <int T, bool MASK, int HD, int KS = HD / 16>
-__device__ __forceinline__ void dq_piece(DqCtx<HD>& cx, int key0) {
-  constexpr int CT = HD / 32, VT_LD = vt_ld(HD), DQ_RING = dq_ring(HD);
-  constexpr int RB = T * 32 * DUAL_LD;
-  constexpr int VB = T * 32 * VT_LD;
+// one 32-key x 32-query piece: T selects the half of the 64-key step.  S^T and dP^T in tiles of 16 keys (kt) x 16 queries
+// (qt), lane = query, registers = keys 16 kt + 4 grp + 0..3; the two key tiles' registers are the eight contraction
+// indices of a lane in dQ^T += K^T dS^T.  An A fragment serves both query tiles (slot i of the first contractions: slice
+// i >> 1 of H, key tile i & 1); fragments run DQ_RING slots ahead of their use.
+template <int T, bool MASK, int HR>
+__device__ __forceinline__ void dq_piece(DqCtx<HR>& cx, int key0) {
+  constexpr int HD = padded_head(HR), LD = row_ld(HD), DQ_RING = dq_ring(HD);
+  constexpr int KS = DqCtx<HR>::KS, HT = DqCtx<HR>::HT, N = 2 * KS;
+  constexpr int RB = T * 32 * LD, VT = BKS * LD;
   bf16x8 kr[DQ_RING], vr[DQ_RING], kt[DQ_RING];
   auto ld1 = [&](auto X) {
     constexpr int x = decltype(X)::value;
-    kr[x % DQ_RING] = dual_nat<x>(cx.ka, RB);
-    vr[x % DQ_RING] = lds_load_b128(cx.vnat + VB + 32 * x);
+    const unsigned at = cx.ka.nat + RB + 64 * (x >> 1) + 16 * LD * (x & 1);
+    kr[x % DQ_RING] = lds_load_b128(at);
+    vr[x % DQ_RING] = lds_load_b128(at + VT);
     __builtin_amdgcn_sched_barrier(0);
   };
   // K^T fragments; the first ones are on their way during the exponentials
   auto ld2 = [&](auto I) {
     constexpr int i = decltype(I)::value;
-    kt[i % DQ_RING] = lds_load_tr(cx.ka.tr_lo + RB + (i / CT) * 16 * DUAL_LD + 64 * (i % CT),
-                                  cx.ka.tr_hi + RB + (i / CT) * 16 * DUAL_LD + 64 * (i % CT));
+    const unsigned at = cx.ka.tr + RB + 32 * i;
+    kt[i % DQ_RING] = lds_load_tr(at, at + 16 * LD);
     __builtin_amdgcn_sched_barrier(0);
   };
   static_for<0, DQ_RING>(ld1);
-  f32x16 s = zero16(), dp = zero16();
-  static_for<0, KS>([&](auto X) {
-    constexpr int x = decltype(X)::value;
-    s = mma(kr[x % DQ_RING], cx.qf[x], s);
-    dp = mma(vr[x % DQ_RING], cx.gf[x], dp);
-    if constexpr (x + DQ_RING < KS) ld1(std::integral_constant<int, x + DQ_RING>{});
-    else ld2(std::integral_constant<int, x + DQ_RING - KS>{});
-  });
-  // register r <-> key key0 + 8*(r>>2) + 4*half + (r&3); lane <-> query
+  f32x4 s[2][2], dp[2][2];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    float p = fast_exp2(fmaf(s[r], cx.c, -cx.lse2));
-    if (MASK && (key0 + 8 * (r >> 2) + 4 * cx.half + (r & 3) >= cx.my_vis)) p = 0.f;
-    dp[r] = p * (dp[r] - cx.del);
-  }
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) { s[k][q] = f32x4{0.f, 0.f, 0.f, 0.f}; dp[k][q] = cx.start[q]; }
+  static_for<0, N>([&](auto X) {
+    constexpr int x = decltype(X)::value, k = x & 1;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      s[k][q] = mma16(kr[x % DQ_RING], cx.qf[x >> 1][q], s[k][q]);
+      dp[k][q] = mma16(vr[x % DQ_RING], cx.gf[x >> 1][q], dp[k][q]);
+    }
+    if constexpr (x + DQ_RING < N) ld1(std::integral_constant<int, x + DQ_RING>{});
+    else ld2(std::integral_constant<int, x + DQ_RING - N>{});
+  });
   bf16x8 dsb[2];
-  dsb[0] = pack8(dp, 0);
-  dsb[1] = pack8(dp, 8);
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float p = fast_exp2(fmaf(s[e >> 2][q][e & 3], cx.c, -cx.lse2[q]));
+      if (MASK && (key0 + 16 * (e >> 2) + 4 * cx.grp + (e & 3) >= cx.my_vis[q])) p = 0.f;
+      dsb[q][e] = (bf16_t)(p * dp[e >> 2][q][e & 3]);
+    }
   __builtin_amdgcn_sched_barrier(0);
-  static_for<0, 2 * CT>([&](auto I) {
+  static_for<0, HT>([&](auto I) {
     constexpr int i = decltype(I)::value;
-    cx.dq[i % CT] = mma(kt[i % DQ_RING], dsb[i / CT], cx.dq[i % CT]);
-    if constexpr (i + DQ_RING < 2 * CT) ld2(std::integral_constant<int, i + DQ_RING>{});
+#pragma unroll
+    for (int q = 0; q < 2; ++q) cx.dq[i][q] = mma16(kt[i % DQ_RING], dsb[q], cx.dq[i][q]);
+    if constexpr (i + DQ_RING < HT) ld2(std::integral_constant<int, i + DQ_RING>{});
   });
 }
 
@@ -97,8 +104,7 @@ __device__ __forceinline__ void dq_rows(
   constexpr int DQ_ROWS = 32 * RW;         // query rows per workgroup
   constexpr int DQ_THREADS = 64 * RW;      // threads of one key lane (they stage its tiles)
   constexpr int HD = padded_head(HR), H = HR;
-  constexpr int KS = HD / 16, CT = HD / 32, VT_LD = vt_ld(HD), DQ_BUF = dq_buf(HD);
-  constexpr int KSR = (HR + 15) / 16;      // slices of H that hold data
+  constexpr int KS = DqCtx<HR>::KS, HT = DqCtx<HR>::HT, LD = row_ld(HD), DQ_BUF = dq_buf(HD), DQ_VT = DQ_BUF / 2;
   const int kl = KL == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / DQ_THREADS);
   char* const lds = lds_all + kl * (2 * DQ_BUF);
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
@@ -121,42 +127,33 @@ __device__ __forceinline__ void dq_rows(
   const int q0 = (nqb - 1 - blk) * DQ_ROWS;            // heavy blocks first under a causal mask
   const int tid = (int)threadIdx.x - kl * DQ_THREADS;  // within the key lane
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int l32 = lane & 31;
   Q += (int64_t)head * d.lq.head + (GRID ? row_blk * g.b.q : 0);
   O += (int64_t)head * d.lo.head + (GRID ? row_blk * g.b.o : 0);
   dO += (int64_t)head * d.ldo.head + (GRID ? row_blk * g.b.g : 0);
   K += (int64_t)kvh * d.lk.head;
   V += (int64_t)kvh * d.lv.head;
 
-  DqCtx<HD> cx;
-  cx.half = lane >> 5;
+  DqCtx<HR> cx;
+  cx.grp = lane >> 4;
   cx.c = d.scale * kLog2e;
-  const int q_row = q0 + wave * 32 + l32;
-  const bool q_ok = q_row < d.nq;
-  const int q_ld = min(q_row, d.nq - 1);         // rows beyond nq re-read the last row, lse2 = +inf
-  {
-    const int64_t off = (int64_t)q_ld * d.lq.row + 8 * cx.half, goff = (int64_t)q_ld * d.ldo.row + 8 * cx.half;
+  const int q_row = q0 + wave * 32 + (lane & 15);      // of the first row tile
+  // rows beyond nq re-read the last row, lse2 = +inf; columns past the head size are zero
+  int64_t stat_at[2];                                  // (lse and delta: of the tile, or of the whole sequence)
+  float lse_i[2];
+  bf16x8 of[KS][2];                                    // delta = rowsum(dO o O)
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int r = min(q_row + 16 * q, d.nq - 1);
 #pragma unroll
     for (int x = 0; x < KS; ++x) {
-      if (16 * x < H) {
-        cx.qf[x] = *reinterpret_cast<const bf16x8*>(Q + off + 16 * x);
-        cx.gf[x] = *reinterpret_cast<const bf16x8*>(dO + goff + 16 * x);
-      } else {                                                 // columns past the head size are zero
-        cx.qf[x] = bf16x8{};
-        cx.gf[x] = bf16x8{};
-      }
+      const int at = 32 * x + 8 * cx.grp, ld = min(at, H - 8);
+      cx.qf[x][q] = *reinterpret_cast<const bf16x8*>(Q + (int64_t)r * d.lq.row + ld);
+      cx.gf[x][q] = *reinterpret_cast<const bf16x8*>(dO + (int64_t)r * d.ldo.row + ld);
+      of[x][q] = *reinterpret_cast<const bf16x8*>(O + (int64_t)r * d.lo.row + ld);
+      if (32 * x + 32 > H && at >= H) cx.qf[x][q] = cx.gf[x][q] = of[x][q] = bf16x8{};
     }
-  }
-  // (lse and delta: of the tile, or of the whole sequence)
-  const int64_t stat_at = GRID ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, q_ld)
-                               : (int64_t)head * d.nq + q_ld;
-  const float lse_i = lse[stat_at];
-  // delta = rowsum(dO o O) of the wavefront's rows, left for the dK/dV kernel where that runs after this one
-  bf16x8 of[KS];
-#pragma unroll
-  for (int x = 0; x < KS; ++x) {
-    if (16 * x < H) of[x] = *reinterpret_cast<const bf16x8*>(O + (int64_t)q_ld * d.lo.row + 8 * cx.half + 16 * x);
-    else of[x] = bf16x8{};
+    stat_at[q] = GRID ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, r) : (int64_t)head * d.nq + r;
+    lse_i[q] = lse[stat_at[q]];
   }
 
   // visibility per key/value sub-block s: query i sees the first vis_count(i, s) keys of it
@@ -176,13 +173,13 @@ __device__ __forceinline__ void dq_rows(
   auto enter_segment = [&](int s) {
     nvis_wave = vis_count(w_last, s);
     nfull_wave = vis_count(w_first, s);
-    cx.my_vis = vis_count(q_ld, s);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) cx.my_vis[q] = vis_count(min(q_row + 16 * q, d.nq - 1), s);
   };
 #pragma unroll
-  for (int t = 0; t < CT; ++t) cx.dq[t] = zero16();
+  for (int t = 0; t < HT; ++t) cx.dq[t][0] = cx.dq[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  cx.ka.init(lane, lds_base);
-  cx.vnat = lds_base + DQ_VT + l32 * VT_LD + 16 * cx.half;
+  cx.ka.init(lane, lds_base, LD);
 
   // ---- staging, in two halves of 32 key rows: thread moves chunk (tid & 15) of rows
   // (tid >> 4) + ST_ROWS p of a half.  Rows beyond nkv re-read the last row (finite values,
@@ -221,8 +218,8 @@ __device__ __forceinline__ void dq_rows(
 #pragma unroll
       for (int p = 0; p < ST_N; ++p) {
         const int row = 32 * hf + st_row + ST_ROWS * p;
-        *reinterpret_cast<u32x4*>(b + dual_store_off(row, st_ch)) = (HD == 128 || ch_data) ? kreg[p] : zero;
-        *reinterpret_cast<u32x4*>(b + DQ_VT + row * VT_LD + st_ch * 16) = (HD == 128 || ch_data) ? vreg[p] : zero;
+        *reinterpret_cast<u32x4*>(b + row * LD + st_ch * 16) = (HD == 128 || ch_data) ? kreg[p] : zero;
+        *reinterpret_cast<u32x4*>(b + DQ_VT + row * LD + st_ch * 16) = (HD == 128 || ch_data) ? vreg[p] : zero;
       }
     }
   };
@@ -272,21 +269,25 @@ __device__ __forceinline__ void dq_rows(
     load_half(nx_start, nx_rows, j, 0);
   }
   wait_vmem_all();                                 // (the rows of Q, dO, O and the first half together)
-  cx.lse2 = (!q_ok || lse_i == -INFINITY) ? INFINITY : lse_i * kLog2e;      // +inf: exp2(s - lse2) = 0
-  {
-    // (the order of sums of delta_kernel, so that both dQ paths give the same dK, dV: 16-byte chunks,
-    // then chunks 1, 2, 4, 8 apart; this lane holds the chunks 2 x + half)
-    float t[8];
 #pragma unroll
-    for (int x = 0; x < 8; ++x) {
+  for (int q = 0; q < 2; ++q) {
+    const bool ok = q_row + 16 * q < d.nq;
+    cx.lse2[q] = (!ok || lse_i[q] == -INFINITY) ? INFINITY : lse_i[q] * kLog2e;      // +inf: exp2(s - lse2) = 0
+    // (the order of sums of delta_kernel, so that both dQ paths give the same dK, dV: 16-byte chunks,
+    // then chunks 1, 2, 4, 8 apart; this lane holds the chunks 4 x + grp)
+    float t[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
       t[x] = 0.f;
       if (x >= KS) continue;
-      t[x] = dot8(__builtin_bit_cast(u32x4, of[x]), __builtin_bit_cast(u32x4, cx.gf[x]), 0.f);
+      t[x] = dot8(__builtin_bit_cast(u32x4, of[x][q]), __builtin_bit_cast(u32x4, cx.gf[x][q]), 0.f);
+      t[x] += __shfl_xor(t[x], 16, 64);
       t[x] += __shfl_xor(t[x], 32, 64);
     }
-    cx.del = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    const float del = (t[0] + t[1]) + (t[2] + t[3]);
+    cx.start[q] = f32x4{-del, -del, -del, -del};
+    if (delta && part == 0 && kl == 0 && cx.grp == 0 && ok) delta[stat_at[q]] = del;
   }
-  if (delta && part == 0 && kl == 0 && cx.half == 0 && q_ok) delta[stat_at] = cx.del;
   if (sb < segs) {
     store_half(0, 0);
     load_half(nx_start, nx_rows, j, 1); store_half(0, 1);
@@ -304,16 +305,15 @@ __device__ __forceinline__ void dq_rows(
     const int k0 = j * BKS + (CYCLIC && sb > shift_from);      // local to the sub-block
     if (A2D_OFTEN(more)) load_half(nx_start, nx_rows, nj, 0);
     if (here && k0 < nvis_wave) {
-      if (k0 + 32 > nfull_wave) dq_piece<0, true, HD, KSR>(cx, k0); else dq_piece<0, false, HD, KSR>(cx, k0);
+      if (k0 + 32 > nfull_wave) dq_piece<0, true, HR>(cx, k0); else dq_piece<0, false, HR>(cx, k0);
     }
     if (A2D_OFTEN(more)) { store_half(buf ^ 1, 0); load_half(nx_start, nx_rows, nj, 1); }
     if (here && k0 + 32 < nvis_wave) {
-      if (k0 + 64 > nfull_wave) dq_piece<1, true, HD, KSR>(cx, k0 + 32); else dq_piece<1, false, HD, KSR>(cx, k0 + 32);
+      if (k0 + 64 > nfull_wave) dq_piece<1, true, HR>(cx, k0 + 32); else dq_piece<1, false, HR>(cx, k0 + 32);
     }
     if (A2D_OFTEN(more)) store_half(buf ^ 1, 1);
     const int tog = buf ? -DQ_BUF : DQ_BUF;
     cx.ka.shift(tog);
-    cx.vnat += tog;
     __syncthreads();
     if (!CYCLIC && A2D_SELDOM(more && nsb != sb)) enter_segment(nsb);
     if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
@@ -323,27 +323,32 @@ __device__ __forceinline__ void dq_rows(
   if constexpr (KL == 2) {
     // lane 1 hands its sums to lane 0 through LDS (the tiles are no longer read: every wavefront
     // has passed the walk's last barrier); layout [row wavefront][value][lane]: conflict free
-    static_assert(RW * CT * 16 * 256 <= KL * 2 * DQ_BUF, "the exchange area must fit the tile buffers");
-    float* xch = reinterpret_cast<float*>(lds_all) + wave * (CT * 16 * 64) + lane;
+    static_assert(RW * HT * 8 * 256 <= KL * 2 * DQ_BUF, "the exchange area must fit the tile buffers");
+    float* xch = reinterpret_cast<float*>(lds_all) + wave * (HT * 8 * 64) + lane;
     if (kl == 1) {
 #pragma unroll
-      for (int t = 0; t < CT; ++t)
+      for (int t = 0; t < HT; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) xch[(16 * t + r) * 64] = cx.dq[t][r];
+        for (int r = 0; r < 8; ++r) xch[(8 * t + r) * 64] = cx.dq[t][r >> 2][r & 3];
     }
     __syncthreads();
     if (kl == 1) return;
 #pragma unroll
-    for (int t = 0; t < CT; ++t)
+    for (int t = 0; t < HT; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) cx.dq[t][r] += xch[(16 * t + r) * 64];
+      for (int r = 0; r < 8; ++r) cx.dq[t][r >> 2][r & 3] += xch[(8 * t + r) * 64];
   }
-  if (GRID && parts == 1) {
-    bf16_t* const out = reinterpret_cast<bf16_t*>(dQ) + head * g.b.out[0].head + row_blk * g.b.out_step[0];
-    if (q_ok) store_acc_t<CT>(out + q_row * g.b.out[0].row, cx.dq, cx.half, d.scale, H);
-  } else if (q_ok) {
-    const int64_t slot = (int64_t)part * (GRID ? g.b.side : 1) + row_blk;
-    store_acc_t<CT>(dQ + ((slot * d.heads + head) * d.nq + q_row) * H, cx.dq, cx.half, d.scale, H, !GRID && g.acc != 0);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int r = q_row + 16 * q;
+    if (r >= d.nq) continue;
+    if (GRID && parts == 1) {
+      bf16_t* const out = reinterpret_cast<bf16_t*>(dQ) + head * g.b.out[0].head + row_blk * g.b.out_step[0];
+      store_acc16(out + r * g.b.out[0].row, cx.dq, q, cx.grp, d.scale);
+    } else {
+      const int64_t slot = (int64_t)part * (GRID ? g.b.side : 1) + row_blk;
+      store_acc16(dQ + ((slot * d.heads + head) * d.nq + r) * H, cx.dq, q, cx.grp, d.scale, !GRID && g.acc != 0);
+    }
   }
 }
 
