@@ -43,35 +43,6 @@ __device__ __forceinline__ void store_acc_t(float* __restrict__ out_row, const f
     }
 }
 
-// the same of 16 x 16 tiles: HT column tiles, the lane's row of tile kt, columns 16 ht + 4 g + 0..3 of lane group g
-template <int HT, int NT>
-__device__ __forceinline__ void store_acc16(bf16_t* __restrict__ out_row, const f32x4 (&acc)[HT][NT], int kt, int g, float mul) {
-#pragma unroll
-  for (int ht = 0; ht < HT; ++ht) {
-    bf16x4 v;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (bf16_t)(acc[ht][kt][e] * mul);
-    *reinterpret_cast<bf16x4*>(out_row + 16 * ht + 4 * g) = v;
-  }
-}
-template <int HT, int NT>
-__device__ __forceinline__ void store_acc16(float* __restrict__ out_row, const f32x4 (&acc)[HT][NT], int kt, int g, float mul,
-                                            bool add = false) {
-#pragma unroll
-  for (int ht = 0; ht < HT; ++ht) {
-    f32x4* p = reinterpret_cast<f32x4*>(out_row + 16 * ht + 4 * g);
-    f32x4 v;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = acc[ht][kt][e] * mul;
-    if (add) {
-      const f32x4 o = *p;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] += o[e];
-    }
-    *p = v;
-  }
-}
-
 __device__ __forceinline__ f32x4 lds_load_f32x4(unsigned addr) {
   return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>((uintptr_t)addr);
 }

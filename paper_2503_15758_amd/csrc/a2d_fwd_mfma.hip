@@ -7,26 +7,30 @@
 // query blocks for that take 128-row workgroups: see the kernel's template parameters.)
 //
 // Both contractions are issued TRANSPOSED so that no cross-lane data movement is
-// needed between them (v_mfma_f32_32x32x16_bf16, D = A * B, A: 32 x 16, B: 16 x 32):
+// needed between them (v_mfma_f32_16x16x32_bf16, D = A * B, A: 16 x 32, B: 32 x 16):
 //   S^T = K * Q^T : A = K fragment (LDS, 128-bit reads), B = Q^T fragment (registers,
-//                   loaded once).  In D a lane holds 16 keys of ONE query column, so
-//                   row max / row sum are in-lane reductions; the two lanes of a row
-//                   (lane, lane ^ 32) are combined only when needed.
-//   O^T += V^T * P^T : B = P^T is exactly the D layout of S^T (the contraction index
+//                   loaded once).  In D a lane holds 4 keys of ONE query column per tile, so
+//                   row max / row sum are in-lane reductions; the four lanes of a row
+//                   (16 apart) are combined only when needed.
+//   O^T += V^T * P^T : B = P^T is the D layout of two tiles of S^T (the contraction index
 //                   may be permuted freely as long as A uses the same permutation),
 //                   A = V^T fragment read from the row-major V tile with the LDS
 //                   transpose read ds_read_b64_tr_b16.
-// LDS: K and V tiles double-buffered, rows padded (K: 272 B, V: 320 B) so that the
-// 128-bit K reads and the transposing V reads are bank-conflict free and every
-// fragment address is one per-lane base register plus an immediate.  One workgroup
-// fills a compute unit with two wavefronts per SIMD, so one's MFMAs overlap the other's
-// softmax arithmetic, and every staged K / V tile serves all eight (two workgroups of four
-// would stage each tile twice: measured 6 % slower).
+// Large tiles are held by the chip's power (1.4 kW at 1.8-1.9 GHz), so it is the energy of a flop that counts: an MFMA of
+// 16 x 16 x 32 moves half the accumulators per flop of one of 32 x 32 x 16 (787 -> 763 us at 96 x 4096 x 4096, H = 128).
+// LDS: K and V tiles double-buffered, loaded straight into LDS (dma_b128) in blocks whose chunks are placed so that the
+// 128-bit K reads and the transposing V reads are bank-conflict free (Blocks16).  Through registers, written to
+// LDS by all wavefronts in front of a step's barrier, tiles cost a step 5-10 %.  The two together, H = 128: 96 x 4096 x 4096
+// 780 -> 725 us (1137 TFLOP/s), causal 444 -> 410, 8 x 16384 x 16384 1034 -> 940, 16 x 2048 x 2048 41.9 -> 39.5; 64 x 4096 x 4096, H =
+// 96 / 80 / 64 425 / 398 / 343 -> 389 / 370 / 312.  One workgroup of eight wavefronts has a compute unit with two wavefronts
+// per SIMD, so one's MFMAs overlap the other's softmax arithmetic, and every staged K / V tile serves all eight (two
+// workgroups of four would stage each tile twice).  The mask is a branch around its selects inside the one copy of the
+// block: with a copy of its own per kind of block the compiler moved the accumulators between registers.
 //
 // Rescaling is lazy: a row's exponent reference m_ref follows its running maximum
 // only when a score exceeds it by more than 2^8 (in the exponent's units) - a rare,
-// wave-uniform branch, and the only place where the two lanes of a row talk to each
-// other.  Each lane tracks the true maximum of its own scores; at the end the halves
+// wave-uniform branch, and the only place where the lanes of a row talk to each
+// other.  Each lane tracks the true maximum of its own scores; at the end they
 // are combined and N, l are brought to the true row maximum, so (N, m, l) leave the
 // kernel exactly as Eq. (3) defines them.
 #include "a2d_mfma.hpp"
@@ -37,108 +41,129 @@ namespace {
 using namespace mfma;
 
 constexpr int BN = 64;             // keys per step
-constexpr int VLD = 320;           // V tile row stride, bytes (256 of data at most + a pad that shifts rows by 16 banks)
-// K tile row stride: the row's bytes + 16, which shifts consecutive rows by one 128-bit bank group
-__host__ __device__ constexpr int kld(int hd) { return hd * 2 + 16; }
-__host__ __device__ constexpr int buf_bytes(int hd) { return BN * kld(hd) + BN * VLD; }
-__host__ __device__ constexpr int lds_bytes(int hd) { return 2 * buf_bytes(hd); }
+__host__ __device__ constexpr int buf_bytes(int hd) { return 2 * BN * 2 * hd; }   // { K tile, V tile }, in blocks
+__host__ __device__ constexpr int lds_bytes(int hd) { return 2 * buf_bytes(hd); }          // of a key lane
+// of a launch: an accumulating call brings 16 rows of every wavefront in at a time
+__host__ __device__ constexpr int fwd_lds(int waves, int hd, int kl) {
+  const int tiles = kl * lds_bytes(hd), rows = waves / kl * 16 * (4 * hd + 16);
+  return tiles > rows ? tiles : rows;
+}
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
 constexpr double kStepUs[3] = {1.25, 1.45, 1.66};   // a 64-key step of a 256-row workgroup, H = 64 / 96 / 128
 constexpr double kSmallRoundUs[3] = {0.95, 1.42, 1.65}, kSmallFixedUs[3] = {3.1, 3.5, 3.2};   // 256 keys of 32 rows
 constexpr double kPairRoundUs[3] = {0.95, 1.25, 1.37}, kPairFixedUs[3] = {4.1, 4.3, 4.4};     // 128 keys of 64 rows
 
-template <int HD>
+template <int HR>
 struct FwdState {
-  f32x16 o[HD / 32];
-  float m_lane;   // true running max of this lane's raw dot products
-  float m_ref;    // reference the exponentials are taken against (raw units, same in both lanes of a row)
-  float l_run;    // this lane's share of the row sum, relative to m_ref
+  f32x4 o[HR / 16][2];   // column tiles x the wavefront's two tiles of 16 query rows
+  // of the lane's row in each tile:
+  float m_lane[2];       // true running max of this lane's raw dot products
+  float m_ref[2];        // reference the exponentials are taken against (raw units, same in the four lanes of a row)
+  float l_run[2];        // this lane's share of the row sum, relative to m_ref
 };
 
-// One 64-key block for one wavefront.  k_rd / v_rd: per-lane LDS byte addresses of the
-// natural K fragment (t = 0, st = 0) and of the transposing V read (u = 0, ht = 0, low rows).
-// KS slices of H in the score contraction (those that hold data: a head size of 80 fills five of
-// the padded six), HD / 32 column tiles in the output contraction.
-template <int HD, bool MASK, int KS = HD / 16>
-__device__ __forceinline__ void fwd_block(FwdState<HD>& st, const bf16x8 (&qf)[HD / 16], unsigned k_rd, unsigned v_rd,
-                                          int k0, int my_vis, int half, float c) {
-  constexpr int CT = HD / 32, KLD = kld(HD);
-  // K fragments go through a ring four deep: each is requested four MFMAs before its use (the
+// maximum, sum over the four lanes of a row
+__device__ __forceinline__ float row_max(float x) {
+  x = fmaxf(x, __shfl_xor(x, 16, 64));
+  return fmaxf(x, __shfl_xor(x, 32, 64));
+}
+__device__ __forceinline__ float row_sum(float x) {
+  x += __shfl_xor(x, 16, 64);
+  return x + __shfl_xor(x, 32, 64);
+}
+
+// One 64-key block for one wavefront; at: its buffer's offset from the addresses in rd.  S^T in tiles of 16 keys (k) x 16 queries (q): lane = query, registers = keys 16 k + 4 grp +
+// 0..3; the registers of two key tiles are the eight contraction indices of a lane in O^T += V^T P^T.
+// masked: some of the wavefront's rows do not see all of its keys.
+template <int HR>
+__device__ __forceinline__ void fwd_block(FwdState<HR>& st, const bf16x8 (&qf)[padded_head(HR) / 32][2],
+                                          const Blocks16& rd, unsigned at, bool masked, int k0, const int (&my_vis)[2], int grp, float c) {
+  constexpr int KS = padded_head(HR) / 32, HT = HR / 16, K_BYTES = buf_bytes(padded_head(HR)) / 2;
+  const unsigned k_rd = rd.nat + at, v_rd[2] = {rd.tr_e + at, rd.tr_o + at};
+  // K fragments go through a ring four deep: each is requested four slots of two MFMAs before its use (the
   // scheduling fences keep the compiler from sinking the requests back to their uses)
-  f32x16 s[2];
-  s[0] = zero16();
-  s[1] = zero16();
+  f32x4 s[4][2];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) s[k][0] = s[k][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   bf16x8 kr[4];
-  // step I works on key tile I & 1, slice I >> 1 of H: the two accumulators alternate, so that no
-  // MFMA accumulates onto the result of the one issued just before it
+  // slot I: key tile I & 3, slice I >> 2 of H, both query tiles
   auto ldk = [&](auto I) {
     constexpr int i = decltype(I)::value;
-    kr[i & 3] = lds_load_b128(k_rd + (i & 1) * 32 * KLD + (i >> 1) * 32);
+    kr[i & 3] = lds_load_b128(k_rd + ((i & 3) * KS + (i >> 2)) * BLOCK);
   };
   static_for<0, 4>(ldk);
   __builtin_amdgcn_sched_barrier(0);
-  static_for<0, 2 * KS>([&](auto I) {
+  static_for<0, 4 * KS>([&](auto I) {
     constexpr int i = decltype(I)::value;
-    s[i & 1] = mma(kr[i & 3], qf[i >> 1], s[i & 1]);
-    if constexpr (i + 4 < 2 * KS) ldk(std::integral_constant<int, i + 4>{});
+#pragma unroll
+    for (int q = 0; q < 2; ++q) s[i & 3][q] = mma16(kr[i & 3], qf[i >> 2][q], s[i & 3][q]);
+    if constexpr (i + 4 < 4 * KS) ldk(std::integral_constant<int, i + 4>{});
     __builtin_amdgcn_sched_barrier(0);
   });
-  if (MASK) {
+  if (A2D_SELDOM(masked)) {
+    asm volatile("" ::: "memory");   // keep this a branch
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int key = k0 + 32 * t + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (key >= my_vis) s[t][r] = -INFINITY;
+        const int key = k0 + 16 * (r >> 2) + 4 * grp + (r & 3);
+        if (key >= my_vis[q]) s[r >> 2][q][r & 3] = -INFINITY;
       }
   }
-  float mx = s[0][0];
+  bool grow = false;
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int q = 0; q < 2; ++q) {
+    float mx = st.m_lane[q];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
-  st.m_lane = fmaxf(st.m_lane, mx);
-  // (m_lane - m_ref) is +inf on the first visible block, NaN (-> false) while nothing is visible
-  const bool grow = (st.m_lane - st.m_ref) * c > kRescaleThreshold;
-  if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-    asm volatile("" ::: "memory");   // keep this a real (rarely taken) branch: no if-conversion
-    const float m_row = fmaxf(st.m_lane, __shfl_xor(st.m_lane, 32, 64));
-    const float m_use = (m_row == -INFINITY) ? 0.f : m_row;
-    const float alpha = fast_exp2((st.m_ref - m_use) * c);    // m_ref = -inf gives 0
-    st.m_ref = m_row;
-    st.l_run *= alpha;
-#pragma unroll
-    for (int t = 0; t < CT; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) st.o[t][r] *= alpha;
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r >> 2][q][r & 3]);
+    st.m_lane[q] = mx;
+    // (m_lane - m_ref) is +inf on the first visible block, NaN (-> false) while nothing is visible
+    grow |= (mx - st.m_ref[q]) * c > kRescaleThreshold;
   }
-  const float mc = (st.m_ref == -INFINITY) ? 0.f : st.m_ref * c;
-  // V^T fragments (step I: 16-key group I / CT, column tile I % CT) go through a ring four deep
+  if (A2D_SELDOM(__builtin_amdgcn_ballot_w64(grow) != 0)) {
+    asm volatile("" ::: "memory");   // keep this a real (rarely taken) branch: no if-conversion
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float m_row = row_max(st.m_lane[q]);
+      const float m_use = (m_row == -INFINITY) ? 0.f : m_row;
+      const float alpha = fast_exp2((st.m_ref[q] - m_use) * c);    // m_ref = -inf gives 0
+      st.m_ref[q] = m_row;
+      st.l_run[q] *= alpha;
+#pragma unroll
+      for (int t = 0; t < HT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) st.o[t][q][r] *= alpha;
+    }
+  }
+  // V^T fragments (step I: 32-key group I / HT, column tile I % HT) go through a ring four deep
   // as well; the first four are requested before the exponentials
   bf16x8 vr[4];
   auto ldv = [&](auto I) {
     constexpr int i = decltype(I)::value;
-    const unsigned a = v_rd + (i / CT) * 16 * VLD + (i % CT) * 64;
-    vr[i & 3] = lds_load_tr(a, a + 8 * VLD);
+    const unsigned a = v_rd[i % HT & 1] + K_BYTES + ((i / HT) * 2 * KS + (i % HT >> 1)) * BLOCK;
+    vr[i & 3] = lds_load_tr(a, a + KS * BLOCK);
   };
   static_for<0, 4>(ldv);
   __builtin_amdgcn_sched_barrier(0);
-  float psum = 0.f;
-  bf16x8 pb[4];
+  bf16x8 pb[2][2];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int q = 0; q < 2; ++q) {
+    const float mc = (st.m_ref[q] == -INFINITY) ? 0.f : st.m_ref[q] * c;
+    float psum = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float p = fast_exp2(fmaf(s[u >> 1][8 * (u & 1) + e], c, -mc));
+    for (int r = 0; r < 16; ++r) {
+      const float p = fast_exp2(fmaf(s[r >> 2][q][r & 3], c, -mc));
       psum += p;
-      pb[u][e] = (bf16_t)p;
+      pb[r >> 3][q][r & 7] = (bf16_t)p;
     }
-  st.l_run += psum;
+    st.l_run[q] += psum;
+  }
   __builtin_amdgcn_sched_barrier(0);
-  static_for<0, 4 * CT>([&](auto I) {
+  static_for<0, 2 * HT>([&](auto I) {
     constexpr int i = decltype(I)::value;
-    st.o[i % CT] = mma(vr[i & 3], pb[i / CT], st.o[i % CT]);
-    if constexpr (i + 4 < 4 * CT) ldv(std::integral_constant<int, i + 4>{});
+#pragma unroll
+    for (int q = 0; q < 2; ++q) st.o[i % HT][q] = mma16(vr[i & 3], pb[i / HT][q], st.o[i % HT][q]);
+    if constexpr (i + 4 < 2 * HT) ldv(std::integral_constant<int, i + 4>{});
     __builtin_amdgcn_sched_barrier(0);
   });
 }
@@ -168,12 +193,11 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   constexpr int BM = 32 * RW;             // query rows per workgroup
   constexpr int kThreads = 64 * RW;       // threads of one key lane (they stage its tiles)
   constexpr int HD = padded_head(HR), H = HR;
-  constexpr int KS = HD / 16, CT = HD / 32, KLD = kld(HD), K_BYTES = BN * KLD, BUF_BYTES = buf_bytes(HD);
-  constexpr int KSR = (HR + 15) / 16;     // slices of H that hold data
+  constexpr int KS = HD / 32, HT = HR / 16, BUF_BYTES = buf_bytes(HD);
   constexpr int kLdsBytes = lds_bytes(HD);
   if constexpr (GRID) warm_arguments<9 * 8>();
   extern __shared__ __attribute__((aligned(16))) char lds_all[];
-  // per key lane: [buf]{ K tile (BN x KLD), V tile (BN x VLD) }
+  // per key lane: [buf]{ K tile, V tile }
   const int kl = KL == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);   // key lane of this wavefront
   char* const lds = lds_all + kl * kLdsBytes;
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
@@ -197,8 +221,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // heavy (late) query blocks first: under a causal mask they walk more key blocks
   const int q0 = (nqb - 1 - blk) * BM;
   const int tid = (int)threadIdx.x - kl * kThreads;     // within the key lane
-  const int wave = tid >> 6, lane = tid & 63;
-  const int half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int grp = lane >> 4;
   Q += (int64_t)head * d.lq.head + (GRID ? row_blk * g.b.q : 0);
   K += (int64_t)kvh * d.lk.head;
   V += (int64_t)kvh * d.lv.head;
@@ -209,33 +233,35 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     l_out += slot;
   }
 
-  // ---- Q^T fragments: lane holds query row (l32), h = 16*step + 8*half + 0..7.
-  // Rows beyond nq re-read the last row (their results are never stored).
-  const int q_row = q0 + wave * 32 + l32;
-  bf16x8 qf[KS];
-  {
-    const bf16_t* qp = Q + (int64_t)min(q_row, d.nq - 1) * d.lq.row + 8 * half;
+  // ---- Q^T fragments: lane holds query row (lane & 15) of two tiles, h = 32*step + 8*grp + 0..7.
+  // Rows beyond nq re-read the last row (their results are never stored); columns past the head size are zero.
+  const int q_row = q0 + wave * 32 + (lane & 15);       // of the first tile
+  bf16x8 qf[KS][2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const bf16_t* qp = Q + (int64_t)min(q_row + 16 * q, d.nq - 1) * d.lq.row;
 #pragma unroll
     for (int x = 0; x < KS; ++x) {
-      if (16 * x < H) qf[x] = *reinterpret_cast<const bf16x8*>(qp + 16 * x);
-      else qf[x] = bf16x8{};                                  // columns past the head size are zero
+      const int at = 32 * x + 8 * grp;
+      qf[x][q] = *reinterpret_cast<const bf16x8*>(qp + min(at, H - 8));
+      if (32 * x + 32 > H && at >= H) qf[x][q] = bf16x8{};
     }
   }
-  FwdState<HD> st;
+  FwdState<HR> st;
 #pragma unroll
-  for (int t = 0; t < CT; ++t) st.o[t] = zero16();
-  st.l_run = 0.f;
+  for (int t = 0; t < HT; ++t) st.o[t][0] = st.o[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  st.l_run[0] = st.l_run[1] = 0.f;
   const float c = d.scale * kLog2e;
-  float m_in = -INFINITY;
+  float m_in[2] = {-INFINITY, -INFINITY};
   if (!GRID && g.acc && part == 0) {
     // (key lane 0 of the first part continues the stored partial; the barriers are the whole workgroup's)
     // Continue from the (N, m, l) of `in`: N into the accumulators (same
-    // element mapping as the epilogue's stores), m as the exponent reference, l into one of the two
-    // lanes of the row.  A lane's share of N is 16 scattered 16-byte pieces of its row, so the
+    // element mapping as the epilogue's stores), m as the exponent reference, l into one of the four
+    // lanes of the row.  A lane's share of N is scattered 16-byte pieces of its rows, so the
     // rows come in through LDS: each wavefront reads 16 of its rows at a time with whole-row
-    // coalesced loads into a private, padded LDS area and the owning lanes pick their pieces.
+    // coalesced loads into a private, padded LDS area and the lanes pick their pieces.
     constexpr int ALD = HD * 4 + 16;                          // padded row stride, bytes
-    static_assert(16 * ALD * (kThreads / 64) <= kLdsBytes, "accumulator staging must fit the tile buffers");
+    static_assert(16 * ALD * RW <= fwd_lds(WAVES, HD, KL), "accumulator staging must fit the launch's LDS");
     char* area = lds_all + wave * 16 * ALD;
     const int64_t wrow0 = (int64_t)head * d.nq + q0 + wave * 32;   // first row of the wavefront
     const int64_t last_row = (int64_t)head * d.nq + d.nq - 1;
@@ -257,27 +283,25 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
         }
       }
       __syncthreads();
-      if ((l32 >> 4) == pass && kl == 0) {
-        const char* mine = area + (l32 & 15) * ALD + 16 * half;
+      if (kl == 0) {
+        const char* mine = area + (lane & 15) * ALD + 16 * grp;
 #pragma unroll
-        for (int ht = 0; ht < CT; ++ht)
-#pragma unroll
-          for (int gq = 0; gq < 4; ++gq) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(mine + (32 * ht + 8 * gq) * 4);
-            st.o[ht][4 * gq] = v[0]; st.o[ht][4 * gq + 1] = v[1]; st.o[ht][4 * gq + 2] = v[2]; st.o[ht][4 * gq + 3] = v[3];
-          }
+        for (int ht = 0; ht < HT; ++ht) st.o[ht][pass] = *reinterpret_cast<const f32x4*>(mine + 16 * ht * 4);
       }
       __syncthreads();
     }
-    if (kl != 0) {
-      // the other key lane starts from nothing
-    } else if (q_row < d.nq) {
-      const int64_t row = (int64_t)head * d.nq + q_row;
-      m_in = in.m[row];
-      st.l_run = half == 0 ? in.l[row] : 0.f;
-    } else {
 #pragma unroll
-      for (int t = 0; t < CT; ++t) st.o[t] = zero16();       // rows beyond nq: nothing to continue
+    for (int q = 0; q < 2; ++q) {
+      if (kl != 0) {
+        // the other key lane starts from nothing
+      } else if (q_row + 16 * q < d.nq) {
+        const int64_t row = (int64_t)head * d.nq + q_row + 16 * q;
+        m_in[q] = in.m[row];
+        st.l_run[q] = grp == 0 ? in.l[row] : 0.f;
+      } else {
+#pragma unroll
+        for (int t = 0; t < HT; ++t) st.o[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};     // rows beyond nq: nothing to continue
+      }
     }
   }
 
@@ -296,27 +320,18 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   const int w_last = min(q0 + wave * 32 + 31, d.nq - 1);
   // key blocks of sub-block s that some row of the workgroup sees; the walk over (sub-block, block)
   auto seg_blocks = [&](int s) { return (vis_count(blk_last, s) + BN - 1) / BN; };
-  int nvis_wave = 0, nfull_wave = 0, my_vis = 0;   // of the current sub-block
+  int nvis_wave = 0, nfull_wave = 0, my_vis[2] = {0, 0};   // of the current sub-block
   auto enter_segment = [&](int s) {
     nvis_wave = vis_count(w_last, s);        // keys any row of the wave sees
     nfull_wave = vis_count(w_first, s);      // keys every row of the wave sees
-    my_vis = vis_count(min(q_row, d.nq - 1), s);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) my_vis[q] = vis_count(min(q_row + 16 * q, d.nq - 1), s);
   };
 
 
-  // ---- staging: thread moves the 16-byte chunk (tid & 15) of rows (tid >> 4) + 32 p.
-  // Rows beyond nkv re-read the last row: finite values, masked out of the scores.
-  const int ld_row = tid >> 4, ld_chunk = tid & 15;
-  const bool ld_ok = ld_chunk * 8 < H;          // the chunk exists in memory (else it is a zero pad column group)
-  const bool st_ok = ld_chunk * 8 < HD;         // the chunk exists in the LDS tile
-  const int k_wr = ld_row * KLD + ld_chunk * 16;
-  const int v_wr = K_BYTES + ld_row * VLD + ld_chunk * 16;
-  constexpr int ST_ROWS = kThreads / 16, ST_N = BN / ST_ROWS;   // rows per pass, passes per tile
-  u32x4 kreg[ST_N], vreg[ST_N];
-#pragma unroll
-  for (int p = 0; p < ST_N; ++p) { kreg[p] = u32x4{0, 0, 0, 0}; vreg[p] = u32x4{0, 0, 0, 0}; }
-  // block j of the sub-block of seg_rows keys that starts at local key seg_start; rows beyond its
-  // end re-read its last row
+  // ---- staging, straight into LDS: wavefront w of a key lane loads the blocks w, w + RW, ... of { K tile, V tile }.
+  // Block j of the sub-block of seg_rows keys that starts at local key seg_start; rows beyond its end re-read its last
+  // row: finite values, masked out of the scores.
   // (row strides in bytes, pinned in registers: read from the kernel arguments inside the loop they
   // would be scalar loads, which share a wait counter with the LDS reads in flight.  A head's rows
   // span less than 4 GiB - the API layer checks it - so row index times stride fits 32 bits.)
@@ -325,35 +340,31 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // (cyclic: seg_start is the number of the grid's column, whose first row that is in the sequence)
   const unsigned k_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.k * 2)) : k_row_bytes;
   const unsigned v_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.v * 2)) : v_row_bytes;
-  auto load_tile = [&](int seg_start, int seg_rows, int j) {
+  const int ld_row = lane >> 2, ld_chunk = (lane & 3) ^ block_swap(lane >> 4);
+  auto load_tile = [&](int seg_start, int seg_rows, int j, int boff) {
     const unsigned k_at = seg_start * k_col_bytes + (unsigned)(j * BN) * k_row_bytes;
     const unsigned v_at = seg_start * v_col_bytes + (unsigned)(j * BN) * v_row_bytes;
     const gptr_t kb = uniform_gptr(reinterpret_cast<const char*>(K) + k_at);   // scalar bases
     const gptr_t vb = uniform_gptr(reinterpret_cast<const char*>(V) + v_at);
     const int last = seg_rows - 1 - j * BN;
-    if (ld_ok) {
 #pragma unroll
-      for (int p = 0; p < ST_N; ++p) {
-        const unsigned r = (unsigned)min(ld_row + ST_ROWS * p, last);
-        kreg[p] = gload_b128(kb, __umul24(r, k_row_bytes) + ld_chunk * 16);
-        vreg[p] = gload_b128(vb, __umul24(r, v_row_bytes) + ld_chunk * 16);
-      }
+    for (int p = 0; p < 8 * KS / RW; ++p) {
+      const int b = wave + RW * p, is_v = b >= 4 * KS, t = (is_v ? b - 4 * KS : b) / KS, sl = (is_v ? b - 4 * KS : b) - t * KS;
+      const unsigned r = (unsigned)min(16 * t + ld_row, last);
+      const unsigned off = __umul24(r, is_v ? v_row_bytes : k_row_bytes) + 64 * sl + 16 * ld_chunk;
+      if (H == HD || 32 * sl + 8 * ld_chunk < H) dma_b128(lds_base + boff + b * BLOCK, is_v ? vb : kb, off);
     }
   };
-  auto store_tile = [&](int boff) {
-    if (st_ok) {
-#pragma unroll
-      for (int p = 0; p < ST_N; ++p) {
-        *reinterpret_cast<u32x4*>(lds + boff + k_wr + p * ST_ROWS * KLD) = kreg[p];
-        *reinterpret_cast<u32x4*>(lds + boff + v_wr + p * ST_ROWS * VLD) = vreg[p];
-      }
+  if constexpr (H != HD) {
+    // the K tiles' columns past the head size are zero for good (those of V are not read)
+    for (int i = tid; i < 2 * BN * (HD - H) / 8; i += kThreads) {
+      const int row = i % BN, x = i / BN, buf = x / ((HD - H) / 8), ch = H % 32 / 8 + x % ((HD - H) / 8);
+      *reinterpret_cast<u32x4*>(lds + buf * BUF_BYTES + ((row >> 4) * KS + H / 32) * BLOCK + (row & 15) * 64 +
+                                16 * (ch ^ block_swap((row & 15) >> 2))) = u32x4{0, 0, 0, 0};
     }
-  };
-  // fragment read bases (buffer 0)
-  const unsigned k_rd0 = lds_base + l32 * KLD + half * 16;
-  const int g16 = lane >> 4, j16 = lane & 15;
-  const unsigned v_rd0 =
-      lds_base + K_BYTES + (4 * (g16 >> 1) + (j16 >> 2)) * VLD + (16 * (g16 & 1) + 4 * (j16 & 3)) * 2;
+  }
+  Blocks16 rd;                                    // fragment reads, buffer 0
+  rd.init(lane, lds_base);
 
   // Walk over the entries (sub-block, key block): lane part * KL + kl of parts * KL takes every
   // (parts * KL)-th entry.  The sub-block table lives in kernel-argument memory, and scalar loads
@@ -401,12 +412,12 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   if (sb < segs) {
     enter_segment(sb);
     nx_start = seg_start(sb); nx_rows = seg_rows(sb);
-    load_tile(nx_start, nx_rows, j);
+    load_tile(nx_start, nx_rows, j, 0);
   }
   // (one wait for the Q rows and the first tile: the two latencies overlap)
   wait_vmem_all();
-  st.m_lane = st.m_ref = m_in / d.scale;               // -inf stays -inf
-  if (sb < segs) store_tile(0);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) st.m_lane[q] = st.m_ref[q] = m_in[q] / d.scale;      // -inf stays -inf
   __syncthreads();
 
   int boff = 0;
@@ -416,13 +427,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     const bool more = nsb < segs;
     if (CYCLIC) nx_start = nsb;
     else if (A2D_SELDOM(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
-    if (A2D_OFTEN(more)) load_tile(nx_start, nx_rows, nj);
+    if (A2D_OFTEN(more)) load_tile(nx_start, nx_rows, nj, BUF_BYTES - boff);
     const int k0 = j * BN + (CYCLIC && sb > shift_from);       // local to the sub-block
-    if ((KL == 1 || sb < segs) && k0 < nvis_wave) {
-      if (k0 + BN > nfull_wave) fwd_block<HD, true, KSR>(st, qf, k_rd0 + boff, v_rd0 + boff, k0, my_vis, half, c);
-      else fwd_block<HD, false, KSR>(st, qf, k_rd0 + boff, v_rd0 + boff, k0, my_vis, half, c);
-    }
-    if (A2D_OFTEN(more)) store_tile(BUF_BYTES - boff);
+    if ((KL == 1 || sb < segs) && k0 < nvis_wave) fwd_block<HR>(st, qf, rd, boff, k0 + BN > nfull_wave, k0, my_vis, grp, c);
+    wait_vmem_all();
     __syncthreads();
     if (!CYCLIC && A2D_SELDOM(more && nsb != sb)) enter_segment(nsb);
     if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
@@ -431,71 +439,68 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   }
 
   // ---- epilogue: bring N and l to the true row maximum, store N, m (scaled units), l
-  float m_row = fmaxf(st.m_lane, __shfl_xor(st.m_lane, 32, 64));
-  float f = (m_row == -INFINITY) ? 0.f : fast_exp2((st.m_ref - m_row) * c);
-  float l_tot = (st.l_run + __shfl_xor(st.l_run, 32, 64)) * f;
+  float m_row[2], f[2], l_tot[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    m_row[q] = row_max(st.m_lane[q]);
+    f[q] = (m_row[q] == -INFINITY) ? 0.f : fast_exp2((st.m_ref[q] - m_row[q]) * c);
+    l_tot[q] = row_sum(st.l_run[q]) * f[q];
+  }
   if constexpr (KL == 2) {
     // Key lane 1 hands its (N, m, l) to lane 0 through LDS (the tiles are no longer read: every
     // wavefront has passed the walk's last barrier), which merges the two as Alg. 2 does.
     // Layout: [row wavefront][value index][lane], one float each, so every access is conflict free.
-    constexpr int NV = CT * 16 + 2;
+    constexpr int NV = HT * 8 + 4;
     static_assert(RW * NV * 256 <= KL * kLdsBytes, "the exchange area must fit the tile buffers");
     float* xch = reinterpret_cast<float*>(lds_all) + wave * NV * 64 + lane;
     if (kl == 1) {
 #pragma unroll
-      for (int t = 0; t < CT; ++t)
+      for (int q = 0; q < 2; ++q) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) xch[(16 * t + r) * 64] = st.o[t][r] * f;
-      xch[(CT * 16) * 64] = m_row;
-      xch[(CT * 16 + 1) * 64] = l_tot;
+        for (int t = 0; t < HT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) xch[(8 * t + 4 * q + r) * 64] = st.o[t][q][r] * f[q];
+        xch[(HT * 8 + 2 * q) * 64] = m_row[q];
+        xch[(HT * 8 + 2 * q + 1) * 64] = l_tot[q];
+      }
     }
     __syncthreads();
     if (kl == 1) return;
-    const float m1 = xch[(CT * 16) * 64], l1 = xch[(CT * 16 + 1) * 64];
-    const float m_new = fmaxf(m_row, m1);
-    const float a0 = (m_row == -INFINITY) ? 0.f : f * fast_exp2((m_row - m_new) * c);
-    const float a1 = (m1 == -INFINITY) ? 0.f : fast_exp2((m1 - m_new) * c);
 #pragma unroll
-    for (int t = 0; t < CT; ++t)
+    for (int q = 0; q < 2; ++q) {
+      const float m1 = xch[(HT * 8 + 2 * q) * 64], l1 = xch[(HT * 8 + 2 * q + 1) * 64];
+      const float m_new = fmaxf(m_row[q], m1);
+      const float a0 = (m_row[q] == -INFINITY) ? 0.f : f[q] * fast_exp2((m_row[q] - m_new) * c);
+      const float a1 = (m1 == -INFINITY) ? 0.f : fast_exp2((m1 - m_new) * c);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) st.o[t][r] = st.o[t][r] * a0 + xch[(16 * t + r) * 64] * a1;
-    l_tot = (m_row == -INFINITY ? 0.f : l_tot * fast_exp2((m_row - m_new) * c)) + l1 * a1;
-    m_row = m_new;
-    f = 1.f;
+      for (int t = 0; t < HT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) st.o[t][q][r] = st.o[t][q][r] * a0 + xch[(8 * t + 4 * q + r) * 64] * a1;
+      l_tot[q] = (m_row[q] == -INFINITY ? 0.f : l_tot[q] * fast_exp2((m_row[q] - m_new) * c)) + l1 * a1;
+      m_row[q] = m_new;
+      f[q] = 1.f;
+    }
   }
-  // a lane's piece (column tile ht, group gq) covers columns 32 ht + 8 gq + 4 half + 0..3
-  if (q_row < d.nq && g.norm) {
-    // normalised partial: O' = N / l rounded to bf16, lse' = m + ln l (Sec. 3.2, footnote)
-    // (GRID: the row of O and lse itself)
-    const int64_t row = GRID ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, q_row)
-                             : (int64_t)head * d.nq + q_row;
-    const int64_t o_at = GRID ? head * d.lo.head + row_blk * g.b.o + q_row * d.lo.row : row * H;
-    const float fn = l_tot > 0.f ? f / l_tot : 0.f;
-    bf16_t* op = reinterpret_cast<bf16_t*>(O_part) + o_at + 4 * half;
+  // a lane's pieces of a row: columns 16 ht + 4 grp + 0..3
 #pragma unroll
-    for (int ht = 0; ht < CT; ++ht)
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        bf16x4 v;
-        v[0] = (bf16_t)(st.o[ht][4 * gq] * fn); v[1] = (bf16_t)(st.o[ht][4 * gq + 1] * fn);
-        v[2] = (bf16_t)(st.o[ht][4 * gq + 2] * fn); v[3] = (bf16_t)(st.o[ht][4 * gq + 3] * fn);
-        if (32 * ht + 8 * gq + 4 * half < H) *reinterpret_cast<bf16x4*>(op + 32 * ht + 8 * gq) = v;
+  for (int q = 0; q < 2; ++q) {
+    const int r = q_row + 16 * q;
+    if (r >= d.nq) continue;
+    if (g.norm) {
+      // normalised partial: O' = N / l rounded to bf16, lse' = m + ln l (Sec. 3.2, footnote)
+      // (GRID: the row of O and lse itself)
+      const int64_t row = GRID ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, r) : (int64_t)head * d.nq + r;
+      const int64_t o_at = GRID ? head * d.lo.head + row_blk * g.b.o + r * d.lo.row : row * H;
+      const float fn = l_tot[q] > 0.f ? f[q] / l_tot[q] : 0.f;
+      store_acc16(reinterpret_cast<bf16_t*>(O_part) + o_at, st.o, q, grp, fn);
+      if (grp == 0) m_out[row] = l_tot[q] > 0.f ? m_row[q] * d.scale + logf(l_tot[q]) : -INFINITY;
+    } else {
+      const int64_t row = (int64_t)head * d.nq + r;
+      store_acc16(O_part + row * H, st.o, q, grp, f[q]);
+      if (grp == 0) {
+        m_out[row] = m_row[q] * d.scale;      // -inf stays -inf (scale > 0)
+        l_out[row] = l_tot[q];
       }
-    if (half == 0) m_out[row] = l_tot > 0.f ? m_row * d.scale + logf(l_tot) : -INFINITY;
-  } else if (q_row < d.nq) {
-    const int64_t row = (int64_t)head * d.nq + q_row;
-    float* op = O_part + row * H + 4 * half;
-#pragma unroll
-    for (int ht = 0; ht < CT; ++ht)
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        f32x4 v = {st.o[ht][4 * gq] * f, st.o[ht][4 * gq + 1] * f, st.o[ht][4 * gq + 2] * f,
-                   st.o[ht][4 * gq + 3] * f};
-        if (32 * ht + 8 * gq + 4 * half < H) *reinterpret_cast<f32x4*>(op + 32 * ht + 8 * gq) = v;
-      }
-    if (half == 0) {
-      m_out[row] = m_row * d.scale;      // -inf stays -inf (scale > 0)
-      l_out[row] = l_tot;
     }
   }
 }
@@ -506,7 +511,7 @@ namespace {
 template <int WAVES, int HR, int KL, int GRID>
 hipError_t fwd_launch(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                       float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
-  constexpr int bytes = KL * lds_bytes(padded_head(HR)), BM = 32 * WAVES / KL;
+  constexpr int bytes = fwd_lds(WAVES, padded_head(HR), KL), BM = 32 * WAVES / KL;
   if (ph == PREPARE)
     return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_mfma_kernel<WAVES, HR, KL, GRID>), bytes);
   dim3 grid(xcd_grid(d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * ((d.nq + BM - 1) / BM))), block(64 * WAVES);

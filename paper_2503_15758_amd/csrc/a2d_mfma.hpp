@@ -189,6 +189,59 @@ struct Rows16 {
   __device__ __forceinline__ void shift(int delta) { nat += delta; tr += delta; }
 };
 
+// Tiles that are loaded straight into LDS (dma_b128: lane i of a wavefront writes the 16 bytes at i from a common address on,
+// so rows cannot be padded).  A tile is made of blocks of 16 rows x 32 columns, 1 KiB each, one wavefront's load: row r at 64 r,
+// its four 16-byte chunks c at c ^ block_swap(r >> 2).  With that both kinds of fragment reads are conflict free:
+//   - natural fragment of row tile t, slice sl: nat + block(t, sl);
+//   - transposed fragment of column tile ht, row tiles t and t + 1: (ht & 1 ? tr_o : tr_e) + block(t, ht >> 1) and block(t + 1, ht >> 1).
+constexpr int BLOCK = 1024;
+__device__ __forceinline__ int block_swap(int q) { return 2 * ((q ^ (q >> 1)) & 1) | (q >> 1); }
+struct Blocks16 {
+  unsigned nat, tr_e, tr_o;
+  __device__ __forceinline__ void init(int lane, unsigned tile_base) {
+    const int g = lane >> 4, j = lane & 15;
+    nat = tile_base + j * 64 + 16 * (g ^ block_swap(j >> 2));
+    tr_e = tile_base + (4 * g + (j >> 2)) * 64 + 16 * (((j & 3) >> 1) ^ block_swap(g)) + 8 * (j & 1);
+    tr_o = tr_e ^ 32;
+  }
+};
+// lane i's 16 bytes at base + byte_off go to LDS address `at` + 16 i (lanes that are switched off write nothing).  They count as one
+// vector memory operation; the compiler does not know of it, so the caller waits (wait_vmem_all) before the barrier behind
+// which the tile is read.
+__device__ __forceinline__ void dma_b128(unsigned at, gptr_t base, unsigned byte_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(byte_off), "s"(base) : "memory");
+}
+
+// stores a transposed accumulator of 16 x 16 tiles (lane = an output row in each of NT tiles, HT column tiles), the row of
+// tile kt: columns 16 ht + 4 g + 0..3 of lane group g (add: onto what the row already holds)
+template <int HT, int NT>
+__device__ __forceinline__ void store_acc16(bf16_t* __restrict__ out_row, const f32x4 (&acc)[HT][NT], int kt, int g, float mul) {
+#pragma unroll
+  for (int ht = 0; ht < HT; ++ht) {
+    bf16x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (bf16_t)(acc[ht][kt][e] * mul);
+    *reinterpret_cast<bf16x4*>(out_row + 16 * ht + 4 * g) = v;
+  }
+}
+template <int HT, int NT>
+__device__ __forceinline__ void store_acc16(float* __restrict__ out_row, const f32x4 (&acc)[HT][NT], int kt, int g, float mul,
+                                            bool add = false) {
+#pragma unroll
+  for (int ht = 0; ht < HT; ++ht) {
+    f32x4* p = reinterpret_cast<f32x4*>(out_row + 16 * ht + 4 * g);
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = acc[ht][kt][e] * mul;
+    if (add) {
+      const f32x4 o = *p;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += o[e];
+    }
+    *p = v;
+  }
+}
+
 // XCD-aware work mapping.  MI355X has 8 XCDs, each with its own L2, and hands consecutive
 // workgroup ids to consecutive XCDs (id % 8).  All blocks of one head read the same K / V (or
 // Q / dO) rows, so they are placed on ONE XCD.  Two orders inside an XCD (k-th workgroup of XCD x,
