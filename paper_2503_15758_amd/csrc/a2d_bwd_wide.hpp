@@ -8,7 +8,7 @@ namespace a2d {
 namespace mfma {
 
 // Eight wavefronts, two per SIMD, each with 32 keys of its own and all four contractions: both the
-// dK^T and dV^T accumulators, K^T fragments in registers and V^T fragments too (H = 128: in LDS).  Against
+// dK^T and dV^T accumulators, K^T and V^T fragments in registers.  Against
 // the pairs of bwd_dkdv_kernel nothing passes between wavefronts (no mailbox: a fifth of the LDS
 // traffic), the two wavefronts of a SIMD run freely against each other, and a step - its barrier,
 // its staging, its LDS latencies - holds twice the MFMAs.  In program order the exponentials stand
@@ -21,18 +21,22 @@ namespace mfma {
 // (MFMAs alone on normal operands sustain 1.94-1.99 PFLOP/s against 1.72-1.76), and H = 80 fills five column tiles of 16
 // instead of three of 32.  64 x 4096 x 4096, H = 128 / 96 / 80 / 64: 1065 / 749 / 697 / 571 -> 1010 / 727 / 669 / 543 us, 1199 ->
 // 1183 with dS.  Each fragment still serves two MFMAs (the 32 keys of a wavefront), so the LDS reads are the same.
+// Q and dO go straight into LDS, which leaves the registers that V^T needs at H = 128 (from LDS it was a sixth of
+// the reads) and no writes of tiles in front of the barrier; three buffers, so that a step's requests have its whole length.
+// Calls at 64 x 4096 x 4096, recomputing: 1608 / 1278 / 1196 / 968 -> 1575 / 1262 / 1167 / 941 us; 96 x 4096 x 4096 with dS 2377 ->
+// 2302, 16 x 2048 x 2048 122.1 -> 116.6, 32 x 1999 x 2777 H = 80 causal 162.9 -> 156.3.
 // (One wavefront per SIMD with two tiles of 32 keys, which halves the LDS reads again, issues too
 // slowly: 2.8 us at H = 128.)
 // Not for tiles with few keys, whose workgroups it halves (see plan_bwd_mfma).
 constexpr int WK_KEYS = 256, WK_THREADS = 512;
-// LDS: two buffers { Q tile, dO tile } | two of { -lse / scale [32], -delta [32] } | a wavefront's piece
-// for turning dS | V (H = 128; rows of 272 bytes)
-__host__ __device__ constexpr int wk_tile(int hd) { return BQ * row_ld(hd); }
-__host__ __device__ constexpr int wk_stat(int hd) { return 4 * wk_tile(hd); }
-__host__ __device__ constexpr int wk_turn(int hd) { return wk_stat(hd) + 2 * DK_STAT_BUF; }
+// LDS: three buffers { Q tile, dO tile } in blocks | three of { -lse / scale [32], -delta [32] } | a wavefront's piece
+// for turning dS
+constexpr int WK_BUFS = 3;
+__host__ __device__ constexpr int wk_tile(int hd) { return BQ * 2 * hd; }
+__host__ __device__ constexpr int wk_stat(int hd) { return WK_BUFS * 2 * wk_tile(hd); }
+__host__ __device__ constexpr int wk_turn(int hd) { return wk_stat(hd) + WK_BUFS * DK_STAT_BUF; }
 constexpr int WK_TURN_BYTES = 32 * DS_TR_LD;
-__host__ __device__ constexpr int wk_v(int hd) { return wk_turn(hd) + 8 * WK_TURN_BYTES; }
-__host__ __device__ constexpr int wk_lds(int hd) { return wk_v(hd) + (hd == 128 ? WK_KEYS * row_ld(hd) : 0); }
+__host__ __device__ constexpr int wk_lds(int hd) { return wk_turn(hd) + 8 * WK_TURN_BYTES; }
 
 // GRID: all key blocks of an emulated grid (g.b).  The workgroup walks the query rows of its whole grid column and
 // writes rows of dK and dV of the sequence (of a split walk: a partial, [part][column][head][key]).  Contiguous blocks
@@ -45,10 +49,9 @@ __device__ __forceinline__ void dkdv_wide(
     const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dK, float* __restrict__ dV,
     bf16_t* __restrict__ dS) {
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-  constexpr int HD = padded_head(HR), H = HR, LD = row_ld(HD), TILE = wk_tile(HD), BUF = 2 * TILE;
+  constexpr int HD = padded_head(HR), H = HR, TILE = wk_tile(HD), BUF = 2 * TILE;
   constexpr int KS = HD / 32, HT = HR / 16;        // slices of H in the first two contractions, column tiles of the others
-  constexpr bool V_LDS = HD == 128;
-  // At H = 128 the accumulators and K^T leave 96 registers: shorter fragment rings, and per-lane addresses
+  // At H = 128 the accumulators, K^T and V^T leave 64 registers: shorter fragment rings, and per-lane addresses
   // that are used once a step are computed again in every step.
   constexpr bool TIGHT = HD == 128;
   const int kv_heads = d.heads / g.group;
@@ -78,7 +81,7 @@ __device__ __forceinline__ void dkdv_wide(
   V += (int64_t)head * d.lv.head + (GRID ? col * g.b.v : 0);
   lse += (int64_t)qh0 * head_rows;
   delta += (int64_t)qh0 * head_rows;
-  const float c = d.scale * kLog2e, inv_scale = 1.0f / d.scale;
+  const float c = uniform(d.scale * kLog2e), inv_scale = uniform(1.0f / d.scale);
 
   // ---- K^T and V^T fragments of the wavefront's 32 keys, two tiles of 16: lane = key.  Keys beyond nkv
   // re-read the last key; the mask zeroes their probabilities.  (Columns past the head size are zero.)
@@ -151,9 +154,9 @@ __device__ __forceinline__ void dkdv_wide(
   // cyclic: the row blocks before the column see a key a row later than the others
   const int late = CYCLIC && d.causal ? col : 0;
 
-  // ---- staging: thread moves chunk (tid & 15) of row (tid >> 4) of both tiles.  Step
-  // j + 2 is requested while step j is computed and written to LDS an iteration later; steps beyond the
-  // last re-stage it.  Rows beyond nq re-read the last row with a statistic of -inf (p = 0).
+  // ---- staging, straight into LDS: wavefront w loads the blocks w and w + 8 of { Q tile, dO tile }.  Step j + 2 is
+  // requested while step j is computed; steps beyond the last re-stage it.  Rows beyond nq re-read the last row with a
+  // statistic of -inf (p = 0).
   const gptr_t q_base = uniform_gptr(Q), g_base = uniform_gptr(dO);
   const unsigned q_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lq.row * 2);
   const unsigned g_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.row * 2);
@@ -161,22 +164,28 @@ __device__ __forceinline__ void dkdv_wide(
   const unsigned g_head_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.head * 2);
   const unsigned q_blk_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.q * 2)) : 0;
   const unsigned g_blk_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.g * 2)) : 0;
-  u32x4 qreg, greg;
-  float stat = 0.f;
+  float stat = 0.f;                                // (wavefront 0: lse of 32 rows, delta of 32 rows)
   bool stat_ok = false;
   int ld_s = s0, ld_r = r0, ld_row0 = h0 * head_rows, ld_left = total - 1;   // the step to be loaded next
   unsigned ld_qh = h0 * q_head_bytes, ld_gh = h0 * g_head_bytes;
-  auto load_step = [&]() {
-    const int tid = TIGHT ? wave * 64 + lane_again() : threadIdx.x;
-    const int st_row = tid >> 4, ld_ch = min(tid & 15, H / 8 - 1);
-    const int i0 = i_start + ld_s * BQ;
-    const unsigned r = (unsigned)min(i0 + st_row, nq - 1);
-    qreg = gload_b128(q_base, ld_qh + (CYCLIC ? ld_r * q_blk_bytes : 0u) + __umul24(r, q_row_bytes) + ld_ch * 16);
-    greg = gload_b128(g_base, ld_gh + (CYCLIC ? ld_r * g_blk_bytes : 0u) + __umul24(r, g_row_bytes) + ld_ch * 16);
-    const int ir = min(i0 + (tid & (BQ - 1)), nq - 1);
-    const int i = ld_row0 + (CYCLIC ? ir * side + ld_r : ir);
-    stat = (tid & BQ) ? delta[i] : lse[i];
-    stat_ok = (i0 + (tid & (BQ - 1))) < nq;
+  auto load_step = [&](unsigned at) {              // into the buffer at `at`
+    const int ln = TIGHT ? lane_again() : lane;
+    const int i0 = i_start + ld_s * BQ, ch = (ln & 3) ^ block_swap(ln >> 4);
+#pragma unroll
+    for (int p = 0; p < (4 * KS + 7) / 8; ++p) {
+      const int b = wave + 8 * p, m = b >= 2 * KS, t = (m ? b - 2 * KS : b) / KS, sl = (m ? b - 2 * KS : b) - t * KS;
+      if (4 * KS % 8 != 0 && b >= 4 * KS) break;
+      const unsigned r = (unsigned)min(i0 + 16 * t + (ln >> 2), nq - 1);
+      const unsigned run = m ? ld_gh + (CYCLIC ? ld_r * g_blk_bytes : 0u) : ld_qh + (CYCLIC ? ld_r * q_blk_bytes : 0u);
+      if (H == HD || 32 * sl + 8 * ch < H)
+        dma_b128(at + b * BLOCK, m ? g_base : q_base, run + __umul24(r, m ? g_row_bytes : q_row_bytes) + 64 * sl + 16 * ch);
+    }
+    if (wave == 0) {
+      const int ir = min(i0 + (ln & (BQ - 1)), nq - 1);
+      const int i = ld_row0 + (CYCLIC ? ir * side + ld_r : ir);
+      stat = (ln & BQ) ? delta[i] : lse[i];
+      stat_ok = (i0 + (ln & (BQ - 1))) < nq;
+    }
     bool more = ld_left > 0;
     ld_left -= more ? 1 : 0;
     if constexpr (CYCLIC) {                        // the next row block, then the next step
@@ -190,38 +199,30 @@ __device__ __forceinline__ void dkdv_wide(
     ld_gh += (more && wrap) ? g_head_bytes : 0u;
     ld_s = more ? (wrap ? 0 : ld_s + 1) : ld_s;
   };
-  auto store_step = [&](int buf) {
-    const int tid = TIGHT ? wave * 64 + lane_again() : threadIdx.x;
-    const int st_row = tid >> 4, st_ch = tid & 15;
-    const bool ch_data = st_ch * 8 < H, ch_tile = st_ch * 8 < HD;
-    char* b = lds + buf * BUF;
-    if (HD == 128 || ch_tile) {
-      const u32x4 zero = {0, 0, 0, 0};
-      const int off = st_row * LD + st_ch * 16;
-      *reinterpret_cast<u32x4*>(b + off) = (HD == 128 || ch_data) ? qreg : zero;
-      *reinterpret_cast<u32x4*>(b + TILE + off) = (HD == 128 || ch_data) ? greg : zero;
-    }
-    if (tid < 2 * BQ) {
+  auto store_stat = [&](int buf) {
+    if (wave == 0) {
+      const int ln = TIGHT ? lane_again() : lane;
       float v = -stat;
-      if (tid < BQ) v = (!stat_ok || v == INFINITY) ? -INFINITY : v * inv_scale;
+      if (ln < BQ) v = (!stat_ok || v == INFINITY) ? -INFINITY : v * inv_scale;
       else v = stat_ok ? v : 0.f;
-      reinterpret_cast<float*>(lds + wk_stat(HD) + buf * DK_STAT_BUF)[tid] = v;
+      reinterpret_cast<float*>(lds + wk_stat(HD) + buf * DK_STAT_BUF)[ln] = v;
     }
   };
-  if (total > 0) load_step();
-  wait_vmem_all();
+  if constexpr (H != HD) {                         // columns past the head size are zero for good
+    for (int i = tid; i < WK_BUFS * 2 * BQ * (HD - H) / 8; i += WK_THREADS) {
+      const int row = i % BQ, x = i / BQ, tile = x / ((HD - H) / 8), ch = H % 32 / 8 + x % ((HD - H) / 8);
+      *reinterpret_cast<u32x4*>(lds + tile * TILE + ((row >> 4) * KS + H / 32) * BLOCK + (row & 15) * 64 +
+                                16 * (ch ^ block_swap((row & 15) >> 2))) = u32x4{0, 0, 0, 0};
+    }
+  }
   if (total > 0) {
-    store_step(0);
-    load_step();
-  }
-  const unsigned v_nat = lds_base + wk_v(HD) + (wave * 32 + l16) * LD + 16 * grp;
-  if constexpr (V_LDS) {
 #pragma unroll
-    for (int x = 0; x < KS; ++x)
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-        *reinterpret_cast<__attribute__((address_space(3))) bf16x8*>((uintptr_t)(v_nat + 64 * x + 16 * kt * LD)) = vf[x][kt];
+    for (int b = 0; b < 2; ++b) {
+      load_step(lds_base + b * BUF);
+      store_stat(b);
+    }
   }
+  wait_vmem_all();
   __syncthreads();
 
   // dS hand-over: the wavefront's 32 keys are piece wave & 1 of key block 4 blk + wave / 2
@@ -232,8 +233,8 @@ __device__ __forceinline__ void dkdv_wide(
   if constexpr (WRITE_DS)
     ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) + qh0 * ds_head_bytes(d.nq, d.nkv));
 
-  Rows16 da;
-  da.init(lane, lds_base, LD);
+  Blocks16 da;
+  da.init(lane, lds_base);
   unsigned st_addr = lds_base + wk_stat(HD) + 16 * grp;
 
   // One step: S and dP of the 32 rows in tiles of 16 rows (t) x 16 keys (kt), lane = key, registers = rows 16 t + 4 grp + 0..3.
@@ -241,20 +242,17 @@ __device__ __forceinline__ void dkdv_wide(
   // fragment serves both key tiles.  Fragments in the order of their use: Q and dO rows (slice i >> 1, row tile i & 1),
   // transposed dO, transposed Q; each is requested RING fragments ahead.
   // (i0: its first row, `rows` those of a run - both one less where the keys are seen a row later)
+  constexpr int N1 = 2 * KS, N2 = 4 * KS, N3 = N2 + HT, N4 = N3 + HT, RING = TIGHT || N4 % 4 != 0 ? 2 : 4;
   auto compute = [&](int i0, int rows, unsigned ds_off, bool masked) {
-    constexpr int N1 = 2 * KS, N2 = 4 * KS, N3 = N2 + HT, N4 = N3 + HT, RING = TIGHT ? 2 : 4;
-    bf16x8 a[RING], va[4];
+    bf16x8 a[RING];
     auto ld = [&](auto I) {
       constexpr int i = decltype(I)::value;
-      if constexpr (i < N2) a[i % RING] = lds_load_b128(da.nat + (i < N1 ? 0 : TILE) + 64 * (i % N1 >> 1) + 16 * LD * (i & 1));
+      if constexpr (i < N2) a[i % RING] = lds_load_b128(da.nat + (i < N1 ? 0 : TILE) + ((i & 1) * KS + (i % N1 >> 1)) * BLOCK);
       else if constexpr (i < N4) {
-        const unsigned at = da.tr + (i < N3 ? TILE + 32 * (i - N2) : 32 * (i - N3));
-        a[i % RING] = lds_load_tr(at, at + 16 * LD);
+        constexpr int y = i < N3 ? i - N2 : i - N3;
+        const unsigned at = (y & 1 ? da.tr_o : da.tr_e) + (i < N3 ? TILE : 0) + (y >> 1) * BLOCK;
+        a[i % RING] = lds_load_tr(at, at + KS * BLOCK);
       }
-    };
-    auto ldv = [&](auto X) {                       // V^T fragment of slice x >> 1, key tile x & 1
-      constexpr int x = decltype(X)::value;
-      if constexpr (V_LDS && x < N1) va[x & 3] = lds_load_b128(v_nat + 64 * (x >> 1) + 16 * LD * (x & 1));
     };
     static_for<0, RING>(ld);
     f32x4 s[2][2], dp[2][2];
@@ -266,7 +264,6 @@ __device__ __forceinline__ void dkdv_wide(
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt) s[t][kt] = mma16(a[i % RING], kf[x][kt], s[t][kt]);
       ld(std::integral_constant<int, i + RING>{});
-      if constexpr (i + 2 >= N1) ldv(std::integral_constant<int, i + 2 - N1>{});
       __builtin_amdgcn_sched_barrier(0);
     });
 #pragma unroll
@@ -296,12 +293,11 @@ __device__ __forceinline__ void dkdv_wide(
     static_for<0, N1>([&](auto I) {
       constexpr int i = decltype(I)::value, x = i >> 1, t = i & 1;
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt) dp[t][kt] = mma16(a[(N1 + i) % RING], V_LDS ? va[(2 * x + kt) & 3] : vf[x][kt], dp[t][kt]);
+      for (int kt = 0; kt < 2; ++kt) dp[t][kt] = mma16(a[(N1 + i) % RING], vf[x][kt], dp[t][kt]);
       if constexpr (i == 0) mask();
 #pragma unroll
       for (int r = 16 * i / N1; r < 16 * (i + 1) / N1; ++r) prob(r);
       ld(std::integral_constant<int, N1 + i + RING>{});
-      ldv(std::integral_constant<int, i + 2>{});
       __builtin_amdgcn_sched_barrier(0);
     });
     static_for<0, HT>([&](auto Y) {
@@ -335,11 +331,13 @@ __device__ __forceinline__ void dkdv_wide(
   int buf = 0;
 #pragma nounroll
   for (int j = 0; j < total; ++j) {
-    store_step(buf ^ 1);
-    load_step();
+    const int free = buf == 0 ? 2 : buf - 1;       // the buffer of step j - 1 takes step j + 2
+    load_step(lds_base + free * BUF);
     const int i0 = i_start + cs * BQ;
     const int sh = CYCLIC && cr < late ? 1 : 0;
-    if (min(i0 + BQ - 1, nq - 1) - sh >= w_any) {
+    const bool here = min(i0 + BQ - 1, nq - 1) - sh >= w_any;
+    const int next = buf == 2 ? -2 * BUF : BUF;
+    if (here) {
       const unsigned off = (unsigned)rt * ds_row_stride + ds_wave_off;
       compute(i0 - sh, nq - sh, off, i0 - sh < w_all || i0 + BQ > nq);
     }
@@ -349,9 +347,12 @@ __device__ __forceinline__ void dkdv_wide(
       cs = wrap ? 0 : cs + 1;
       cr = 0;
     }
-    da.shift(buf ? -BUF : BUF);
-    st_addr += buf ? -DK_STAT_BUF : DK_STAT_BUF;
-    buf ^= 1;
+    da.nat += next; da.tr_e += next; da.tr_o += next;
+    st_addr += buf == 2 ? -2 * DK_STAT_BUF : DK_STAT_BUF;
+    store_stat(free);
+    buf = buf == 2 ? 0 : buf + 1;
+    // (the tiles of step j + 2 have arrived; a step's two stores of dS, its last requests, may be under way)
+    if (WRITE_DS && here) wait_vmem<2>(); else wait_vmem_all();
     __syncthreads();
   }
 

@@ -112,6 +112,8 @@ __device__ __forceinline__ Split query_head(int t, int group, int nblocks, bool 
 // those registers are complete, so that uses inside the main loop do not have to be guarded by
 // waits that would also cover the loop's own freshly issued prefetches.
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+template <int N>                                     // all but the last N (below 16) operations
+__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70 | N); }
 
 // Global-memory pointer that is the same in every lane, held in scalar registers, so that loads
 // through it use the scalar-base + 32-bit-lane-offset addressing form (no per-lane 64-bit address
@@ -126,6 +128,11 @@ __device__ __forceinline__ gptr_t uniform_gptr(const void* p) {
 }
 __device__ __forceinline__ u32x4 gload_b128(gptr_t base, unsigned byte_off) {
   return *reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(base + byte_off);
+}
+
+// a value that is the same in every lane, in a scalar register
+__device__ __forceinline__ float uniform(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
 }
 
 // LDS reads by byte address (address space 3)
@@ -209,7 +216,8 @@ struct Blocks16 {
 // vector memory operation; the compiler does not know of it, so the caller waits (wait_vmem_all) before the barrier behind
 // which the tile is read.
 __device__ __forceinline__ void dma_b128(unsigned at, gptr_t base, unsigned byte_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(byte_off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(at)),
+               "v"(byte_off), "s"(base) : "memory");
 }
 
 // stores a transposed accumulator of 16 x 16 tiles (lane = an output row in each of NT tiles, HT column tiles), the row of
