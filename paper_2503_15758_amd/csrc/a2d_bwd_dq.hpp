@@ -8,8 +8,8 @@ namespace a2d {
 namespace mfma {
 
 constexpr int BKS = 64;           // keys per step
-// LDS: [buf]{ K tile, V tile }
-__host__ __device__ constexpr int dq_buf(int hd) { return 2 * BKS * row_ld(hd); }
+// LDS: [buf]{ K tile, V tile }, in blocks
+__host__ __device__ constexpr int dq_buf(int hd) { return 2 * BKS * 2 * hd; }
 __host__ __device__ constexpr int dq_lds(int hd) { return 2 * dq_buf(hd); }
 // fragment ring depth (registers are tight above H = 64: 256 per wavefront)
 __host__ __device__ constexpr int dq_ring(int hd) { return hd == 64 ? 4 : 2; }
@@ -20,7 +20,7 @@ struct DqCtx {
   f32x4 dq[HT][2];              // column tiles x the wavefront's two tiles of 16 query rows
   bf16x8 qf[KS][2], gf[KS][2];  // slices of H x row tiles
   f32x4 start[2];               // -delta: what dP starts from, so that the contraction yields dP - delta
-  Rows16 ka;                    // K tile of the current buffer (the V tile stands dq_buf / 2 behind it)
+  Blocks16 ka;                  // K tile of the current buffer (the V tile stands dq_buf / 2 behind it)
   float c, lse2[2];
   int my_vis[2];                // number of leading local keys this lane's query rows see
   int grp;
@@ -30,15 +30,16 @@ struct DqCtx {
 // (qt), lane = query, registers = keys 16 kt + 4 grp + 0..3; the two key tiles' registers are the eight contraction
 // indices of a lane in dQ^T += K^T dS^T.  An A fragment serves both query tiles (slot i of the first contractions: slice
 // i >> 1 of H, key tile i & 1); fragments run DQ_RING slots ahead of their use.
-template <int T, bool MASK, int HR>
-__device__ __forceinline__ void dq_piece(DqCtx<HR>& cx, int key0) {
-  constexpr int HD = padded_head(HR), LD = row_ld(HD), DQ_RING = dq_ring(HD);
+// masked: some of the wavefront's rows do not see all of its keys.
+template <int T, int HR>
+__device__ __forceinline__ void dq_piece(DqCtx<HR>& cx, int key0, bool masked) {
+  constexpr int HD = padded_head(HR), DQ_RING = dq_ring(HD);
   constexpr int KS = DqCtx<HR>::KS, HT = DqCtx<HR>::HT, N = 2 * KS;
-  constexpr int RB = T * 32 * LD, VT = BKS * LD;
+  constexpr int RB = T * 2 * KS * BLOCK, VT = dq_buf(HD) / 2;
   bf16x8 kr[DQ_RING], vr[DQ_RING], kt[DQ_RING];
   auto ld1 = [&](auto X) {
     constexpr int x = decltype(X)::value;
-    const unsigned at = cx.ka.nat + RB + 64 * (x >> 1) + 16 * LD * (x & 1);
+    const unsigned at = cx.ka.nat + RB + ((x & 1) * KS + (x >> 1)) * BLOCK;
     kr[x % DQ_RING] = lds_load_b128(at);
     vr[x % DQ_RING] = lds_load_b128(at + VT);
     __builtin_amdgcn_sched_barrier(0);
@@ -46,8 +47,8 @@ __device__ __forceinline__ void dq_piece(DqCtx<HR>& cx, int key0) {
   // K^T fragments; the first ones are on their way during the exponentials
   auto ld2 = [&](auto I) {
     constexpr int i = decltype(I)::value;
-    const unsigned at = cx.ka.tr + RB + 32 * i;
-    kt[i % DQ_RING] = lds_load_tr(at, at + 16 * LD);
+    const unsigned at = (i & 1 ? cx.ka.tr_o : cx.ka.tr_e) + RB + (i >> 1) * BLOCK;
+    kt[i % DQ_RING] = lds_load_tr(at, at + KS * BLOCK);
     __builtin_amdgcn_sched_barrier(0);
   };
   static_for<0, DQ_RING>(ld1);
@@ -66,15 +67,23 @@ __device__ __forceinline__ void dq_piece(DqCtx<HR>& cx, int key0) {
     if constexpr (x + DQ_RING < N) ld1(std::integral_constant<int, x + DQ_RING>{});
     else ld2(std::integral_constant<int, x + DQ_RING - N>{});
   });
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e >> 2][q][e & 3] = fast_exp2(fmaf(s[e >> 2][q][e & 3], cx.c, -cx.lse2[q]));
+  if (A2D_SELDOM(masked)) {
+    asm volatile("" ::: "memory");                 // keep this a branch
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (key0 + 16 * (e >> 2) + 4 * cx.grp + (e & 3) >= cx.my_vis[q]) s[e >> 2][q][e & 3] = 0.f;
+  }
   bf16x8 dsb[2];
 #pragma unroll
   for (int q = 0; q < 2; ++q)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float p = fast_exp2(fmaf(s[e >> 2][q][e & 3], cx.c, -cx.lse2[q]));
-      if (MASK && (key0 + 16 * (e >> 2) + 4 * cx.grp + (e & 3) >= cx.my_vis[q])) p = 0.f;
-      dsb[q][e] = (bf16_t)(p * dp[e >> 2][q][e & 3]);
-    }
+    for (int e = 0; e < 8; ++e) dsb[q][e] = (bf16_t)(s[e >> 2][q][e & 3] * dp[e >> 2][q][e & 3]);
   __builtin_amdgcn_sched_barrier(0);
   static_for<0, HT>([&](auto I) {
     constexpr int i = decltype(I)::value;
@@ -104,7 +113,7 @@ __device__ __forceinline__ void dq_rows(
   constexpr int DQ_ROWS = 32 * RW;         // query rows per workgroup
   constexpr int DQ_THREADS = 64 * RW;      // threads of one key lane (they stage its tiles)
   constexpr int HD = padded_head(HR), H = HR;
-  constexpr int KS = DqCtx<HR>::KS, HT = DqCtx<HR>::HT, LD = row_ld(HD), DQ_BUF = dq_buf(HD), DQ_VT = DQ_BUF / 2;
+  constexpr int KS = DqCtx<HR>::KS, HT = DqCtx<HR>::HT, DQ_BUF = dq_buf(HD);
   const int kl = KL == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / DQ_THREADS);
   char* const lds = lds_all + kl * (2 * DQ_BUF);
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
@@ -135,7 +144,7 @@ __device__ __forceinline__ void dq_rows(
 
   DqCtx<HR> cx;
   cx.grp = lane >> 4;
-  cx.c = d.scale * kLog2e;
+  cx.c = uniform(d.scale * kLog2e);
   const int q_row = q0 + wave * 32 + (lane & 15);      // of the first row tile
   // rows beyond nq re-read the last row, lse2 = +inf; columns past the head size are zero
   int64_t stat_at[2];                                  // (lse and delta: of the tile, or of the whole sequence)
@@ -179,19 +188,11 @@ __device__ __forceinline__ void dq_rows(
 #pragma unroll
   for (int t = 0; t < HT; ++t) cx.dq[t][0] = cx.dq[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  cx.ka.init(lane, lds_base, LD);
+  cx.ka.init(lane, lds_base);
 
-  // ---- staging, in two halves of 32 key rows: thread moves chunk (tid & 15) of rows
-  // (tid >> 4) + ST_ROWS p of a half.  Rows beyond nkv re-read the last row (finite values,
-  // masked out).
-  constexpr int ST_ROWS = DQ_THREADS / 16, ST_N = 32 / ST_ROWS;
-  const int st_row = tid >> 4, st_ch = tid & 15;
-  u32x4 kreg[ST_N], vreg[ST_N];
-  // half hf of block j of the sub-block of seg_rows keys that starts at local key seg_start
-  // (a chunk past the row's end - head sizes below 128 - re-reads the row's last chunk and is
-  // stored as zeros or, past the padded head size, not at all)
-  const int ld_ch = min(st_ch, H / 8 - 1);
-  const bool ch_data = st_ch * 8 < H, ch_tile = st_ch * 8 < HD;
+  // ---- staging, straight into LDS: wavefront w of a key lane loads the blocks w, w + RW, ... of { K tile, V tile }.
+  // Block j of the sub-block of seg_rows keys that starts at local key seg_start; rows beyond its end re-read its last
+  // row (finite values, masked out).
   // (row strides in bytes, pinned in registers: read from the kernel arguments inside the loop they
   // would be scalar loads, which share a wait counter with the LDS reads in flight.  A head's rows
   // span less than 4 GiB - the API layer checks it - so row index times stride fits 32 bits.)
@@ -200,29 +201,26 @@ __device__ __forceinline__ void dq_rows(
   // (cyclic grids: seg_start is the number of the grid's column, whose first row that is in the sequence)
   const unsigned k_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.k * 2)) : k_row_bytes;
   const unsigned v_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.v * 2)) : v_row_bytes;
-  auto load_half = [&](int seg_start, int seg_rows, int j, int hf) {
+  const int ld_row = lane >> 2, ld_chunk = (lane & 3) ^ block_swap(lane >> 4);
+  auto load_tile = [&](int seg_start, int seg_rows, int j, int boff) {
     const gptr_t kb = uniform_gptr(reinterpret_cast<const char*>(K) + (seg_start * k_col_bytes + (unsigned)(j * BKS) * k_row_bytes));
     const gptr_t vb = uniform_gptr(reinterpret_cast<const char*>(V) + (seg_start * v_col_bytes + (unsigned)(j * BKS) * v_row_bytes));
     const int last = seg_rows - 1 - j * BKS;       // rows beyond the sub-block re-read its last row
 #pragma unroll
-    for (int p = 0; p < ST_N; ++p) {
-      const unsigned r = (unsigned)min(32 * hf + st_row + ST_ROWS * p, last);
-      kreg[p] = gload_b128(kb, __umul24(r, k_row_bytes) + ld_ch * 16);
-      vreg[p] = gload_b128(vb, __umul24(r, v_row_bytes) + ld_ch * 16);
+    for (int p = 0; p < 8 * KS / RW; ++p) {
+      const int b = wave + RW * p, is_v = b >= 4 * KS, t = (is_v ? b - 4 * KS : b) / KS, sl = (is_v ? b - 4 * KS : b) - t * KS;
+      const unsigned r = (unsigned)min(16 * t + ld_row, last);
+      const unsigned off = __umul24(r, is_v ? v_row_bytes : k_row_bytes) + 64 * sl + 16 * ld_chunk;
+      if (H == HD || 32 * sl + 8 * ld_chunk < H) dma_b128(lds_base + boff + b * BLOCK, is_v ? vb : kb, off);
     }
   };
-  auto store_half = [&](int buf, int hf) {
-    char* b = lds + buf * DQ_BUF;
-    if (HD == 128 || ch_tile) {
-      const u32x4 zero = {0, 0, 0, 0};
-#pragma unroll
-      for (int p = 0; p < ST_N; ++p) {
-        const int row = 32 * hf + st_row + ST_ROWS * p;
-        *reinterpret_cast<u32x4*>(b + row * LD + st_ch * 16) = (HD == 128 || ch_data) ? kreg[p] : zero;
-        *reinterpret_cast<u32x4*>(b + DQ_VT + row * LD + st_ch * 16) = (HD == 128 || ch_data) ? vreg[p] : zero;
-      }
+  if constexpr (H != HD) {                         // columns past the head size are zero for good
+    for (int i = tid; i < 4 * BKS * (HD - H) / 8; i += DQ_THREADS) {
+      const int row = i % BKS, x = i / BKS, tile = x / ((HD - H) / 8), ch = H % 32 / 8 + x % ((HD - H) / 8);
+      *reinterpret_cast<u32x4*>(lds + tile * (DQ_BUF / 2) + ((row >> 4) * KS + H / 32) * BLOCK + (row & 15) * 64 +
+                                16 * (ch ^ block_swap((row & 15) >> 2))) = u32x4{0, 0, 0, 0};
     }
-  };
+  }
 
   // Walk over the entries (sub-block, key block): lane part * KL + kl of parts * KL takes every
   // (parts * KL)-th entry.  The sub-block table lives in kernel-argument memory, and scalar loads
@@ -266,9 +264,9 @@ __device__ __forceinline__ void dq_rows(
   if (sb < segs) {
     enter_segment(sb);
     nx_start = seg_start(sb); nx_rows = seg_rows(sb);
-    load_half(nx_start, nx_rows, j, 0);
+    load_tile(nx_start, nx_rows, j, 0);
   }
-  wait_vmem_all();                                 // (the rows of Q, dO, O and the first half together)
+  wait_vmem_all();                                 // (the rows of Q, dO, O and the first tile together)
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const bool ok = q_row + 16 * q < d.nq;
@@ -288,13 +286,9 @@ __device__ __forceinline__ void dq_rows(
     cx.start[q] = f32x4{-del, -del, -del, -del};
     if (delta && part == 0 && kl == 0 && cx.grp == 0 && ok) delta[stat_at[q]] = del;
   }
-  if (sb < segs) {
-    store_half(0, 0);
-    load_half(nx_start, nx_rows, j, 1); store_half(0, 1);
-  }
   __syncthreads();
 
-  int buf = 0;
+  int boff = 0;
   while ((KL == 1 ? sb : lead_sb) < segs) {
     int nsb = sb, nj = j, nnblk = nblk;
     advance(stride, nsb, nj, nnblk);
@@ -303,22 +297,17 @@ __device__ __forceinline__ void dq_rows(
     else if (A2D_SELDOM(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
     const bool here = KL == 1 || sb < segs;         // this lane has a block in this round
     const int k0 = j * BKS + (CYCLIC && sb > shift_from);      // local to the sub-block
-    if (A2D_OFTEN(more)) load_half(nx_start, nx_rows, nj, 0);
-    if (here && k0 < nvis_wave) {
-      if (k0 + 32 > nfull_wave) dq_piece<0, true, HR>(cx, k0); else dq_piece<0, false, HR>(cx, k0);
-    }
-    if (A2D_OFTEN(more)) { store_half(buf ^ 1, 0); load_half(nx_start, nx_rows, nj, 1); }
-    if (here && k0 + 32 < nvis_wave) {
-      if (k0 + 64 > nfull_wave) dq_piece<1, true, HR>(cx, k0 + 32); else dq_piece<1, false, HR>(cx, k0 + 32);
-    }
-    if (A2D_OFTEN(more)) store_half(buf ^ 1, 1);
-    const int tog = buf ? -DQ_BUF : DQ_BUF;
-    cx.ka.shift(tog);
+    if (A2D_OFTEN(more)) load_tile(nx_start, nx_rows, nj, DQ_BUF - boff);
+    if (here && k0 < nvis_wave) dq_piece<0, HR>(cx, k0, k0 + 32 > nfull_wave);
+    if (here && k0 + 32 < nvis_wave) dq_piece<1, HR>(cx, k0 + 32, k0 + 64 > nfull_wave);
+    const int tog = boff ? -DQ_BUF : DQ_BUF;
+    cx.ka.nat += tog; cx.ka.tr_e += tog; cx.ka.tr_o += tog;
+    boff = DQ_BUF - boff;
+    wait_vmem_all();
     __syncthreads();
     if (!CYCLIC && A2D_SELDOM(more && nsb != sb)) enter_segment(nsb);
     if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
     sb = nsb; j = nj; nblk = nnblk;
-    buf ^= 1;
   }
   if constexpr (KL == 2) {
     // lane 1 hands its sums to lane 0 through LDS (the tiles are no longer read: every wavefront
