@@ -190,28 +190,32 @@ __device__ __forceinline__ void dq_rows(
 
   cx.ka.init(lane, lds_base);
 
-  // ---- staging, straight into LDS: wavefront w of a key lane loads the blocks w, w + RW, ... of { K tile, V tile }.
-  // Block j of the sub-block of seg_rows keys that starts at local key seg_start; rows beyond its end re-read its last
-  // row (finite values, masked out).
-  // (row strides in bytes, pinned in registers: read from the kernel arguments inside the loop they
+  // ---- staging, straight into LDS: of eight wavefronts 0 .. 3 load a row tile of K each and 4 .. 7 one of V, each of four
+  // one of both.  Block j of the sub-block of seg_rows keys that starts at local key seg_start; rows beyond its end
+  // re-read its last row: finite values, masked out of the scores.
+  // (Row strides in bytes, pinned in registers: read from the kernel arguments inside the loop they
   // would be scalar loads, which share a wait counter with the LDS reads in flight.  A head's rows
   // span less than 4 GiB - the API layer checks it - so row index times stride fits 32 bits.)
-  const unsigned k_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lk.row * 2);
-  const unsigned v_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lv.row * 2);
   // (cyclic grids: seg_start is the number of the grid's column, whose first row that is in the sequence)
-  const unsigned k_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.k * 2)) : k_row_bytes;
-  const unsigned v_col_bytes = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.v * 2)) : v_row_bytes;
-  const int ld_row = lane >> 2, ld_chunk = (lane & 3) ^ block_swap(lane >> 4);
-  auto load_tile = [&](int seg_start, int seg_rows, int j, int boff) {
-    const gptr_t kb = uniform_gptr(reinterpret_cast<const char*>(K) + (seg_start * k_col_bytes + (unsigned)(j * BKS) * k_row_bytes));
-    const gptr_t vb = uniform_gptr(reinterpret_cast<const char*>(V) + (seg_start * v_col_bytes + (unsigned)(j * BKS) * v_row_bytes));
-    const int last = seg_rows - 1 - j * BKS;       // rows beyond the sub-block re-read its last row
+  constexpr int LD_N = RW == 8 ? 1 : 2;            // matrices of a wavefront
+  const int ld_first = RW == 8 ? wave >> 2 : 0, ld_tile = wave & 3, ld_row = 16 * ld_tile + (lane >> 2);
+  const int ld_chunk = (lane & 3) ^ block_swap(lane >> 4);
+  const char* ld_base[LD_N];
+  unsigned ld_row_bytes[LD_N], ld_col_bytes[LD_N];
 #pragma unroll
-    for (int p = 0; p < 8 * KS / RW; ++p) {
-      const int b = wave + RW * p, is_v = b >= 4 * KS, t = (is_v ? b - 4 * KS : b) / KS, sl = (is_v ? b - 4 * KS : b) - t * KS;
-      const unsigned r = (unsigned)min(16 * t + ld_row, last);
-      const unsigned off = __umul24(r, is_v ? v_row_bytes : k_row_bytes) + 64 * sl + 16 * ld_chunk;
-      if (H == HD || 32 * sl + 8 * ld_chunk < H) dma_b128(lds_base + boff + b * BLOCK, is_v ? vb : kb, off);
+  for (int x = 0; x < LD_N; ++x) {
+    const bool v = ld_first + x != 0;
+    ld_base[x] = reinterpret_cast<const char*>(v ? V : K);
+    ld_row_bytes[x] = __builtin_amdgcn_readfirstlane((unsigned)(v ? d.lv.row : d.lk.row) * 2);
+    ld_col_bytes[x] = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)((v ? g.b.v : g.b.k) * 2)) : ld_row_bytes[x];
+  }
+  auto load_tile = [&](int seg_start, int seg_rows, int j, int boff) {
+    const int r = min(ld_row, seg_rows - 1 - j * BKS);
+#pragma unroll
+    for (int x = 0; x < LD_N; ++x) {
+      const gptr_t base = uniform_gptr(ld_base[x] + (seg_start * ld_col_bytes[x] + (unsigned)(j * BKS) * ld_row_bytes[x]));
+      dma_blocks<KS, H>(lds_base + boff + (4 * (ld_first + x) + ld_tile) * KS * BLOCK, base,
+                        __umul24(r, ld_row_bytes[x]) + 16 * ld_chunk, ld_chunk);
     }
   };
   if constexpr (H != HD) {                         // columns past the head size are zero for good

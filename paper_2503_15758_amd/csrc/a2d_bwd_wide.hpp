@@ -22,19 +22,23 @@ namespace mfma {
 // instead of three of 32.  64 x 4096 x 4096, H = 128 / 96 / 80 / 64: 1065 / 749 / 697 / 571 -> 1010 / 727 / 669 / 543 us, 1199 ->
 // 1183 with dS.  Each fragment still serves two MFMAs (the 32 keys of a wavefront), so the LDS reads are the same.
 // Q and dO go straight into LDS, which leaves the registers that V^T needs at H = 128 (from LDS it was a sixth of
-// the reads) and no writes of tiles in front of the barrier; three buffers, so that a step's requests have its whole length.
+// the reads) and no writes of tiles in front of the barrier.
 // Calls at 64 x 4096 x 4096, recomputing: 1608 / 1278 / 1196 / 968 -> 1575 / 1262 / 1167 / 941 us; 96 x 4096 x 4096 with dS 2377 ->
 // 2302, 16 x 2048 x 2048 122.1 -> 116.6, 32 x 1999 x 2777 H = 80 causal 162.9 -> 156.3.
 // (One wavefront per SIMD with two tiles of 32 keys, which halves the LDS reads again, issues too
 // slowly: 2.8 us at H = 128.)
 // Not for tiles with few keys, whose workgroups it halves (see plan_bwd_mfma).
 constexpr int WK_KEYS = 256, WK_THREADS = 512;
-// LDS: three buffers { Q tile, dO tile } in blocks | three of { -lse / scale [32], -delta [32] } | a wavefront's piece
+// A step is 64 query rows, computed 32 at a time: one barrier and one round of requests for twice the MFMAs (without the
+// barriers of 32-row steps the kernel was 6 % faster, without their requests 14 %: both wavefronts of a SIMD make these at
+// the same time).  64 x 4096 x 4096 as above 1548 / 1239 / 1136 / 912 -> 1522 / 1206 / 1111 / 891 us.
+constexpr int WK_ROWS = 64;
+// LDS: two buffers { Q tile, dO tile } in blocks | two of { -lse / scale [64], -delta [64] } | a wavefront's piece
 // for turning dS
-constexpr int WK_BUFS = 3;
-__host__ __device__ constexpr int wk_tile(int hd) { return BQ * 2 * hd; }
-__host__ __device__ constexpr int wk_stat(int hd) { return WK_BUFS * 2 * wk_tile(hd); }
-__host__ __device__ constexpr int wk_turn(int hd) { return wk_stat(hd) + WK_BUFS * DK_STAT_BUF; }
+__host__ __device__ constexpr int wk_tile(int hd) { return WK_ROWS * 2 * hd; }
+constexpr int WK_STAT_BUF = 2 * WK_ROWS * 4;
+__host__ __device__ constexpr int wk_stat(int hd) { return 4 * wk_tile(hd); }
+__host__ __device__ constexpr int wk_turn(int hd) { return wk_stat(hd) + 2 * WK_STAT_BUF; }
 constexpr int WK_TURN_BYTES = 32 * DS_TR_LD;
 __host__ __device__ constexpr int wk_lds(int hd) { return wk_turn(hd) + 8 * WK_TURN_BYTES; }
 
@@ -123,7 +127,7 @@ __device__ __forceinline__ void dkdv_wide(
   int wg_lo, wg_hi;
   first_row_range(k0, min(k0 + WK_KEYS, d.nkv), wg_lo, wg_hi);
   const int i_start = (wg_lo / BQ) * BQ;
-  int nsteps = (nq - i_start + BQ - 1) / BQ;       // steps per run of rows
+  const int nsteps = (nq - i_start + WK_ROWS - 1) / WK_ROWS;       // steps per run of rows
   // this part's steps: from step s0 of row block r0 of head h0 of the group on
   int total = nsteps * side * g.group, s0 = 0, r0 = 0, h0 = 0;
   if (parts > 1) {
@@ -154,73 +158,73 @@ __device__ __forceinline__ void dkdv_wide(
   // cyclic: the row blocks before the column see a key a row later than the others
   const int late = CYCLIC && d.causal ? col : 0;
 
-  // ---- staging, straight into LDS: wavefront w loads the blocks w and w + 8 of { Q tile, dO tile }.  Step j + 2 is
-  // requested while step j is computed; steps beyond the last re-stage it.  Rows beyond nq re-read the last row with a
-  // statistic of -inf (p = 0).
-  const gptr_t q_base = uniform_gptr(Q), g_base = uniform_gptr(dO);
-  const unsigned q_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lq.row * 2);
-  const unsigned g_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.row * 2);
-  const unsigned q_head_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lq.head * 2);
-  const unsigned g_head_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.ldo.head * 2);
-  const unsigned q_blk_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.q * 2)) : 0;
-  const unsigned g_blk_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.g * 2)) : 0;
-  float stat = 0.f;                                // (wavefront 0: lse of 32 rows, delta of 32 rows)
+  // ---- staging, straight into LDS: wavefronts 0 .. 3 load a row tile of Q each, 4 .. 7 of dO; wavefront 0 brings lse,
+  // wavefront 1 delta.  Step j + 1 is requested while step j is computed; the last one re-stages itself.  Rows beyond
+  // nq re-read the last row with a statistic of -inf (p = 0).  What a step's requests need is carried on by a few scalar
+  // additions: both wavefronts of a SIMD stand here right behind the barrier, with no MFMA under way.
+  const bool is_g = wave >= 4;
+  const int ld_tile = 16 * (wave & 3);
+  const bf16_t* const ld_base = is_g ? dO : Q;
+  const unsigned ld_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)(is_g ? d.ldo.row : d.lq.row) * 2);
+  const char* ld_at = nullptr;                     // the step to be loaded next: the wavefront's first row, ...
+  int ld_s = s0, ld_r = r0, ld_h = h0, ld_left = total - 1;   // ... its step, row block and head
+  auto open_run = [&]() {
+    ld_at = reinterpret_cast<const char*>(ld_base + ld_h * (is_g ? d.ldo.head : d.lq.head) + (CYCLIC ? ld_r * (is_g ? g.b.g : g.b.q) : 0)) +
+            (int64_t)(i_start + ld_s * WK_ROWS + ld_tile) * ld_row_bytes;
+  };
+  float stat = 0.f;
   bool stat_ok = false;
-  int ld_s = s0, ld_r = r0, ld_row0 = h0 * head_rows, ld_left = total - 1;   // the step to be loaded next
-  unsigned ld_qh = h0 * q_head_bytes, ld_gh = h0 * g_head_bytes;
-  auto load_step = [&](unsigned at) {              // into the buffer at `at`
+  auto load_step = [&](int buf) {
     const int ln = TIGHT ? lane_again() : lane;
-    const int i0 = i_start + ld_s * BQ, ch = (ln & 3) ^ block_swap(ln >> 4);
-#pragma unroll
-    for (int p = 0; p < (4 * KS + 7) / 8; ++p) {
-      const int b = wave + 8 * p, m = b >= 2 * KS, t = (m ? b - 2 * KS : b) / KS, sl = (m ? b - 2 * KS : b) - t * KS;
-      if (4 * KS % 8 != 0 && b >= 4 * KS) break;
-      const unsigned r = (unsigned)min(i0 + 16 * t + (ln >> 2), nq - 1);
-      const unsigned run = m ? ld_gh + (CYCLIC ? ld_r * g_blk_bytes : 0u) : ld_qh + (CYCLIC ? ld_r * q_blk_bytes : 0u);
-      if (H == HD || 32 * sl + 8 * ch < H)
-        dma_b128(at + b * BLOCK, m ? g_base : q_base, run + __umul24(r, m ? g_row_bytes : q_row_bytes) + 64 * sl + 16 * ch);
+    const int i0 = i_start + ld_s * WK_ROWS, ch = (ln & 3) ^ block_swap(ln >> 4);
+    int r = ln >> 2;
+    const char* at = ld_at;
+    if (A2D_SELDOM(i0 + WK_ROWS > nq)) {           // (from the step's first row on)
+      at -= ld_tile * ld_row_bytes;
+      r = min(r + ld_tile, nq - 1 - i0);
     }
-    if (wave == 0) {
-      const int ir = min(i0 + (ln & (BQ - 1)), nq - 1);
-      const int i = ld_row0 + (CYCLIC ? ir * side + ld_r : ir);
-      stat = (ln & BQ) ? delta[i] : lse[i];
-      stat_ok = (i0 + (ln & (BQ - 1))) < nq;
+    dma_blocks<KS, H>(lds_base + buf * BUF + wave * KS * BLOCK, uniform_gptr(at), __umul24(r, ld_row_bytes) + 16 * ch, ch);
+    if (wave < 2) {
+      const int ir = min(i0 + ln, nq - 1);
+      stat = (wave == 0 ? lse : delta)[(int64_t)ld_h * head_rows + (CYCLIC ? ir * side + ld_r : ir)];
+      stat_ok = i0 + ln < nq;
     }
-    bool more = ld_left > 0;
-    ld_left -= more ? 1 : 0;
-    if constexpr (CYCLIC) {                        // the next row block, then the next step
-      const bool last = ld_r + 1 == side;
-      ld_r = more ? (last ? 0 : ld_r + 1) : ld_r;
-      more = more && last;
+    if (ld_left > 0) {                             // the next step: of the next row block, or further down, or of the next head
+      --ld_left;
+      if (CYCLIC && ++ld_r < side) {
+        ld_at += (is_g ? g.b.g : g.b.q) * 2;
+      } else {
+        ++ld_s;
+        if (!CYCLIC && A2D_OFTEN(ld_s < nsteps)) {
+          ld_at += (int64_t)ld_row_bytes * WK_ROWS;
+        } else {
+          if (CYCLIC) ld_r = 0;
+          if (ld_s == nsteps) { ld_s = 0; ++ld_h; }
+          open_run();
+        }
+      }
     }
-    const bool wrap = ld_s + 1 == nsteps;
-    ld_row0 += (more && wrap) ? head_rows : 0;
-    ld_qh += (more && wrap) ? q_head_bytes : 0u;
-    ld_gh += (more && wrap) ? g_head_bytes : 0u;
-    ld_s = more ? (wrap ? 0 : ld_s + 1) : ld_s;
   };
   auto store_stat = [&](int buf) {
-    if (wave == 0) {
+    if (wave < 2) {
       const int ln = TIGHT ? lane_again() : lane;
       float v = -stat;
-      if (ln < BQ) v = (!stat_ok || v == INFINITY) ? -INFINITY : v * inv_scale;
+      if (wave == 0) v = (!stat_ok || v == INFINITY) ? -INFINITY : v * inv_scale;
       else v = stat_ok ? v : 0.f;
-      reinterpret_cast<float*>(lds + wk_stat(HD) + buf * DK_STAT_BUF)[ln] = v;
+      reinterpret_cast<float*>(lds + wk_stat(HD) + buf * WK_STAT_BUF)[wave * WK_ROWS + ln] = v;
     }
   };
   if constexpr (H != HD) {                         // columns past the head size are zero for good
-    for (int i = tid; i < WK_BUFS * 2 * BQ * (HD - H) / 8; i += WK_THREADS) {
-      const int row = i % BQ, x = i / BQ, tile = x / ((HD - H) / 8), ch = H % 32 / 8 + x % ((HD - H) / 8);
+    for (int i = tid; i < 4 * WK_ROWS * (HD - H) / 8; i += WK_THREADS) {
+      const int row = i % WK_ROWS, x = i / WK_ROWS, tile = x / ((HD - H) / 8), ch = H % 32 / 8 + x % ((HD - H) / 8);
       *reinterpret_cast<u32x4*>(lds + tile * TILE + ((row >> 4) * KS + H / 32) * BLOCK + (row & 15) * 64 +
                                 16 * (ch ^ block_swap((row & 15) >> 2))) = u32x4{0, 0, 0, 0};
     }
   }
   if (total > 0) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      load_step(lds_base + b * BUF);
-      store_stat(b);
-    }
+    open_run();
+    load_step(0);
+    store_stat(0);
   }
   wait_vmem_all();
   __syncthreads();
@@ -237,7 +241,7 @@ __device__ __forceinline__ void dkdv_wide(
   da.init(lane, lds_base);
   unsigned st_addr = lds_base + wk_stat(HD) + 16 * grp;
 
-  // One step: S and dP of the 32 rows in tiles of 16 rows (t) x 16 keys (kt), lane = key, registers = rows 16 t + 4 grp + 0..3.
+  // Half a step: S and dP of 32 rows in tiles of 16 rows (t) x 16 keys (kt), lane = key, registers = rows 16 t + 4 grp + 0..3.
   // The two row tiles' registers are the eight contraction indices of a lane in dV^T += dO^T P and dK^T += Q^T dS.  An A
   // fragment serves both key tiles.  Fragments in the order of their use: Q and dO rows (slice i >> 1, row tile i & 1),
   // transposed dO, transposed Q; each is requested RING fragments ahead.
@@ -267,7 +271,7 @@ __device__ __forceinline__ void dkdv_wide(
       __builtin_amdgcn_sched_barrier(0);
     });
 #pragma unroll
-    for (int t = 0; t < 2; ++t) dp[t][0] = dp[t][1] = lds_load_f32x4(st_addr + BQ * 4 + 64 * t);
+    for (int t = 0; t < 2; ++t) dp[t][0] = dp[t][1] = lds_load_f32x4(st_addr + WK_ROWS * 4 + 64 * t);
     bf16x8 pb[2], sb[2];
     // Hidden pairs, and rows past the end, are taken out of the finished scores, not by where these start from: q.k may
     // have overflowed there.
@@ -326,33 +330,36 @@ __device__ __forceinline__ void dkdv_wide(
     }
   };
 
-  int cs = s0, cr = r0;                            // step inside its run, row block
-  int rt = h0 * ds_row_tiles(d.nq) + s0 + i_start / BQ;   // dS row tile, counted over the group's heads
+  constexpr int HALF = 2 * KS * BLOCK;             // of a tile
+  int cs = s0, cr = r0, chd = h0;                  // step inside its run, row block, head
   int buf = 0;
 #pragma nounroll
   for (int j = 0; j < total; ++j) {
-    const int free = buf == 0 ? 2 : buf - 1;       // the buffer of step j - 1 takes step j + 2
-    load_step(lds_base + free * BUF);
-    const int i0 = i_start + cs * BQ;
+    load_step(buf ^ 1);
     const int sh = CYCLIC && cr < late ? 1 : 0;
-    const bool here = min(i0 + BQ - 1, nq - 1) - sh >= w_any;
-    const int next = buf == 2 ? -2 * BUF : BUF;
-    if (here) {
-      const unsigned off = (unsigned)rt * ds_row_stride + ds_wave_off;
-      compute(i0 - sh, nq - sh, off, i0 - sh < w_all || i0 + BQ > nq);
+    int stored = 0;
+#pragma nounroll
+    for (int h = 0; h < 2; ++h) {
+      const int i0 = i_start + cs * WK_ROWS + h * BQ;
+      if (i0 < nq && min(i0 + BQ - 1, nq - 1) - sh >= w_any) {
+        const unsigned off = (unsigned)(chd * ds_row_tiles(d.nq) + i0 / BQ) * ds_row_stride + ds_wave_off;
+        compute(i0 - sh, nq - sh, off, i0 - sh < w_all || i0 + BQ > nq);
+        stored += 2;
+      }
+      const int go = h == 0 ? HALF : buf ? -BUF - HALF : BUF - HALF;
+      da.nat += go; da.tr_e += go; da.tr_o += go;
+      st_addr += h == 0 ? BQ * 4 : buf ? -WK_STAT_BUF - BQ * 4 : WK_STAT_BUF - BQ * 4;
     }
     if (!CYCLIC || ++cr == side) {
-      const bool wrap = cs + 1 == nsteps;
-      rt += wrap ? 1 + i_start / BQ : 1;
-      cs = wrap ? 0 : cs + 1;
       cr = 0;
+      if (++cs == nsteps) { cs = 0; ++chd; }
     }
-    da.nat += next; da.tr_e += next; da.tr_o += next;
-    st_addr += buf == 2 ? -2 * DK_STAT_BUF : DK_STAT_BUF;
-    store_stat(free);
-    buf = buf == 2 ? 0 : buf + 1;
-    // (the tiles of step j + 2 have arrived; a step's two stores of dS, its last requests, may be under way)
-    if (WRITE_DS && here) wait_vmem<2>(); else wait_vmem_all();
+    buf ^= 1;
+    store_stat(buf);
+    // (the next tiles have arrived; a step's stores of dS, its last requests, may be under way)
+    if (WRITE_DS && stored == 4) wait_vmem<4>();
+    else if (WRITE_DS && stored == 2) wait_vmem<2>();
+    else wait_vmem_all();
     __syncthreads();
   }
 

@@ -212,12 +212,23 @@ struct Blocks16 {
     tr_o = tr_e ^ 32;
   }
 };
-// lane i's 16 bytes at base + byte_off go to LDS address `at` + 16 i (lanes that are switched off write nothing).  They count as one
+// Lane i's 16 bytes at base + byte_off go to LDS address `at` + 16 i (lanes that are switched off write nothing).  They count as one
 // vector memory operation; the compiler does not know of it, so the caller waits (wait_vmem_all) before the barrier behind
-// which the tile is read.
+// which the tile is read.  dma_blocks: the N blocks of a row tile, slice after slice of its rows - one lane offset and one
+// base for all (the instruction's offset counts for both addresses).
+template <int OFF>
 __device__ __forceinline__ void dma_b128(unsigned at, gptr_t base, unsigned byte_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(at)),
-               "v"(byte_off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(__builtin_amdgcn_readfirstlane(at - OFF)),
+               "v"(byte_off), "s"(base), "n"(OFF)
+               : "memory");
+}
+// (H: the head size; chunks past it are left alone)
+template <int N, int H>
+__device__ __forceinline__ void dma_blocks(unsigned at, gptr_t base, unsigned byte_off, int chunk) {
+  static_for<0, N>([&](auto X) {
+    constexpr int x = decltype(X)::value;
+    if (32 * x + 32 <= H || 32 * x + 8 * chunk < H) dma_b128<64 * x>(at + x * BLOCK, base, byte_off);
+  });
 }
 
 // stores a transposed accumulator of 16 x 16 tiles (lane = an output row in each of NT tiles, HT column tiles), the row of
