@@ -63,11 +63,10 @@ constexpr int DK_STAT_BUF = 2 * BQ * 4;
 // ---- dS hand-over to the dQ kernel (optional).  The dK/dV kernel can leave dS (bf16, already
 // multiplied out: P o (dP - delta)) in a workspace, so that the dQ kernel is a plain contraction
 // dQ = scale dS K instead of recomputing S and dP.  Workspace layout: per head, per 32-row tile rt,
-// per 64-key block kb one 4 KiB tile [piece T = 0, 1 (32 keys each)][u = 0, 1 (16 rows each)]
-// [lane 0..63][8 bf16]: lane (row = 16 u + (lane & 15), g = lane >> 4) holds, of the 32 keys
-// 64 kb + 32 T + .., the keys 4 g + {0..3} and 16 + 4 g + {0..3} - exactly the B
-// fragment of the dQ kernel's MFMA, so the consumer reads it with one coalesced 16-byte load per
-// lane and the producer writes it with one coalesced 16-byte store per lane.
+// per 64-key block kb one 4 KiB tile [piece T = 0, 1 (32 keys each)][kt = 0, 1 (16 keys each)]
+// [g = 0 .. 3][key][8 bf16]: rows 4 g + 0..3 and 16 + 4 g + 0..3 of key 64 kb + 32 T + 16 kt + key - what a lane of the dK/dV
+// kernel holds of its key, stored as it is.  The dQ kernel brings the tiles straight into LDS and has
+// the transposing read turn them.  (Turned by the producer, through LDS in every step, they cost it 3 %.)
 constexpr int DS_TILE_BYTES = 4096;
 __host__ __device__ inline int ds_row_tiles(int nq) { return (nq + 31) / 32; }
 __host__ __device__ inline int ds_key_blocks(int nkv) { return (nkv + 63) / 64; }
@@ -85,42 +84,6 @@ __device__ __forceinline__ gwptr_t uniform_gwptr(void* p) {
 __device__ __forceinline__ void gstore_b128(gwptr_t base, unsigned byte_off, bf16x8 v) {
   // streamed once, read back by another kernel: keep it from displacing the Q / dO tiles in L2
   __builtin_nontemporal_store(v, reinterpret_cast<__attribute__((address_space(1))) bf16x8*>(base + byte_off));
-}
-
-// The dK/dV wavefronts hold dS with lane = key and registers = query rows; the dQ kernel needs
-// lane = query row and registers = keys.  A wavefront turns its 32 x 32 piece around through LDS: each lane
-// writes its 4-row groups as 8-byte pieces of a [key][row] tile, and the transposing read returns, per lane,
-// four keys of one row.  Rows of 96 bytes (8 banks times an odd number, as row_ld), the two 16-byte chunks of a
-// pair swapped in every other eight keys: neither access has bank conflicts (rows of 80 bytes: twice the cycles).
-constexpr int DS_TR_LD = 96;
-// (rows: the first of four consecutive ones)
-__device__ __forceinline__ unsigned ds_turn_at(unsigned piece, int key, int rows) {
-  return piece + key * DS_TR_LD + ((2 * rows) ^ (16 * ((key >> 3) & 1)));
-}
-// 32 x 32 tiles: lane = key, register group q of the two fragments = rows 8 q + 4 half + 0..3
-__device__ __forceinline__ void ds_turn_write(unsigned piece, int l32, int half, const bf16x8 (&bf)[2]) {
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const u32x4 w = __builtin_bit_cast(u32x4, bf[u]);
-    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)ds_turn_at(piece, l32, 16 * u + 4 * half)) = u32x2{w[0], w[1]};
-    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)ds_turn_at(piece, l32, 16 * u + 8 + 4 * half)) = u32x2{w[2], w[3]};
-  }
-}
-// 16 x 16 tiles: fragment kt holds key 16 kt + (lane & 15), rows 4 g + 0..3 and 16 + 4 g + 0..3
-__device__ __forceinline__ void ds_turn_write16(unsigned piece, int lane, const bf16x8 (&bf)[2]) {
-  const unsigned a = ds_turn_at(piece, lane & 15, 4 * (lane >> 4));
-#pragma unroll
-  for (int kt = 0; kt < 2; ++kt) {
-    const u32x4 w = __builtin_bit_cast(u32x4, bf[kt]);
-    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * kt * DS_TR_LD)) = u32x2{w[0], w[1]};
-    *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)(a + 16 * kt * DS_TR_LD + 32)) = u32x2{w[2], w[3]};
-  }
-}
-__device__ __forceinline__ void ds_turn_read(unsigned piece, int lane, bf16x8 (&out)[2]) {
-  const int g = lane >> 4, j = lane & 15;
-  const unsigned a = ds_turn_at(piece, 4 * g + (j >> 2), 4 * (j & 3));
-#pragma unroll
-  for (int u = 0; u < 2; ++u) out[u] = lds_load_tr(a + 32 * u, a + 32 * u + 16 * DS_TR_LD);
 }
 
 }  // namespace mfma

@@ -67,39 +67,43 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_kernel(
 // ---------------------------------------------------------------------- dQ from a stored dS
 // Contraction-only dQ kernel: dQ^T += K^T dS^T with dS read back from the workspace the dK/dV
 // kernel filled (layout at ds_row_tiles above).  Workgroup = WAVES wavefronts of 32 query rows;
-// 64 keys per step: the K tile goes through LDS (dual layout, transposing reads only), the dS
-// fragments come straight from global memory, one contiguous 4 KiB tile per wavefront and step,
-// requested DSQ_SETS - 1 steps ahead through DSQ_SETS register sets (the stream is HBM-bound: 2 bytes per
-// score).  The sub-blocks of a gathered tile must start at multiples of 64 keys, so that a 64-key
-// block never straddles two of them.
+// 64 keys per step: the K tile and every wavefront's own 4 KiB tile of dS come straight into LDS, in three stages
+// where one workgroup has the compute unit (requests run two steps ahead), else two, and are read with the transposing
+// loads.  The stream is HBM-bound: 2 bytes per score.  The sub-blocks of a gathered tile must start at multiples of 64
+// keys, so that a 64-key block never straddles two of them.
 constexpr int DSQ_RING = 4;
-constexpr int DSQ_SETS = 3;  // register sets of dS fragments: requests run DSQ_SETS - 1 steps ahead
+__host__ __device__ constexpr int dsq_stages(int waves, int kl) { return waves == 8 && kl == 1 ? 3 : 2; }
+__host__ __device__ constexpr int dsq_stage(int rw, int hd) { return BKS * 2 * hd + rw * DS_TILE_BYTES; }   // { K tile, dS tiles }
+__host__ __device__ constexpr int dsq_lds(int waves, int hd, int kl) { return kl * dsq_stages(waves, kl) * dsq_stage(waves / kl, hd); }
 template <int HD>
 struct DsqCtx {
   f32x4 dq[HD / 16][2]; // column tiles x the wavefront's two tiles of 16 query rows
-  unsigned kt;          // transposed fragments of the K tile of the current buffer
+  unsigned kt_e, kt_o;  // transposed fragments of the K tile of the current stage (Blocks16), ...
+  unsigned ds;          // ... of the dS tile
   int my_vis[2];        // number of leading keys of the current sub-block this lane's query rows see
   int grp;
 };
 
-// one 32-key piece (T = 0, 1) of the step: ds[2T], ds[2T + 1] are its B fragments of the two row tiles;
-// key0 = the piece's first key, local to its sub-block
-template <int T, bool MASK, int HD>
-__device__ __forceinline__ void dsq_piece(DsqCtx<HD>& cx, const u32x4 (&ds)[4], int key0) {
-  constexpr int HT = HD / 16, LD = row_ld(HD);
-  bf16x8 kt[DSQ_RING];
+// one 32-key piece (T = 0, 1) of the step; key0 = its first key, local to its sub-block.  masked: some of the rows do not see
+// all of its keys.
+template <int T, int HD>
+__device__ __forceinline__ void dsq_piece(DsqCtx<HD>& cx, int key0, bool masked) {
+  constexpr int HT = HD / 16, KS = HD / 32;
+  bf16x8 kt[DSQ_RING], dsb[2];
   auto ld = [&](auto I) {
     constexpr int i = decltype(I)::value;
-    const unsigned at = cx.kt + T * 32 * LD + 32 * i;
-    kt[i % DSQ_RING] = lds_load_tr(at, at + 16 * LD);
+    const unsigned at = (i & 1 ? cx.kt_o : cx.kt_e) + (T * 2 * KS + (i >> 1)) * BLOCK;
+    kt[i % DSQ_RING] = lds_load_tr(at, at + KS * BLOCK);
     __builtin_amdgcn_sched_barrier(0);
   };
-  static_for<0, (DSQ_RING < HT ? DSQ_RING : HT)>(ld);
-  bf16x8 dsb[2];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    u32x4 w = ds[2 * T + u];
-    if (MASK) {
+  for (int u = 0; u < 2; ++u) dsb[u] = lds_load_tr(cx.ds + T * 2048 + 8 * u, cx.ds + T * 2048 + 1024 + 8 * u);
+  static_for<0, (DSQ_RING < HT ? DSQ_RING : HT)>(ld);
+  if (A2D_SELDOM(masked)) {
+    asm volatile("" ::: "memory");                 // keep this a branch
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      u32x4 w = __builtin_bit_cast(u32x4, dsb[u]);
       // element e of the fragment <-> key key0 + 16 (e >> 2) + 4 grp + (e & 3); two per word
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
@@ -107,8 +111,8 @@ __device__ __forceinline__ void dsq_piece(DsqCtx<HD>& cx, const u32x4 (&ds)[4], 
         const unsigned keep = (k < cx.my_vis[u] ? 0x0000FFFFu : 0u) | (k + 1 < cx.my_vis[u] ? 0xFFFF0000u : 0u);
         w[x] &= keep;
       }
+      dsb[u] = __builtin_bit_cast(bf16x8, w);
     }
-    dsb[u] = __builtin_bit_cast(bf16x8, w);
   }
   static_for<0, HT>([&](auto I) {
     constexpr int i = decltype(I)::value;
@@ -130,9 +134,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
   constexpr int RW = WAVES / KL;                       // wavefronts of one key lane
   constexpr int DQ_ROWS = 32 * RW, DQ_THREADS = 64 * RW;   // rows of the workgroup, threads of one key lane
+  constexpr int HD = padded_head(HR), H = HR, HT = HD / 16, KS = HD / 32;
+  constexpr int ST = dsq_stages(WAVES, KL), STAGE = dsq_stage(RW, HD), K_TILE = BKS * 2 * HD;
   const int kl = KL == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / DQ_THREADS);
-  constexpr int HD = padded_head(HR), H = HR, HT = HD / 16, LD = row_ld(HD), TILE = BKS * LD;
-  char* const lds = lds_all + kl * (2 * TILE);
+  char* const lds = lds_all + kl * (ST * STAGE);
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   const int nqb = (d.nq + DQ_ROWS - 1) / DQ_ROWS;
   // placement as in bwd_dq_kernel (grouped heads: the query heads of a key/value head share an XCD)
@@ -151,9 +156,11 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   const int q_row = q0 + wave * 32 + (lane & 15);      // of the first row tile
 #pragma unroll
   for (int t = 0; t < HT; ++t) cx.dq[t][0] = cx.dq[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  Rows16 at;
-  at.init(lane, lds_base, LD);
-  cx.kt = at.tr;
+  Blocks16 at;
+  at.init(lane, lds_base);
+  cx.kt_e = at.tr_e;
+  cx.kt_o = at.tr_o;
+  cx.ds = lds_base + K_TILE + wave * DS_TILE_BYTES + (lane & 3) * 256 + (4 * cx.grp + ((lane & 15) >> 2)) * 16;
 
   // this wavefront's row tile of dS (a wavefront past the last row reads the last tile; its
   // results are never stored)
@@ -212,35 +219,24 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     }
   };
 
-  // ---- K staging: thread moves chunk (tid & 15) of rows (tid >> 4) + ST_ROWS p of the 64-row tile
-  constexpr int ST_ROWS = DQ_THREADS / 16, ST_N = BKS / ST_ROWS;
-  static_assert(H == 128, "a thread's chunk is one of sixteen of the row");
-  const int st_row = tid >> 4, st_ch = tid & 15;
-  const gptr_t k_base = uniform_gptr(K);
+  // ---- staging, straight into LDS: a wavefront's own tile of dS, and its share of the K tile - half a row tile of eight
+  // wavefronts, a whole one of four.  Rows past the end re-read the last key.
+  static_assert(H == 128, "K blocks are dealt out whole");
+  constexpr int K_N = 4 * KS / RW, LOADS = K_N + 4;
+  const int ld_tile = wave & 3, ld_sl = RW == 8 ? (wave >> 2) * K_N : 0;
+  const int ld_chunk = (lane & 3) ^ block_swap(lane >> 4);
+  const char* const k_base = reinterpret_cast<const char*>(K) + 64 * ld_sl;
   const unsigned k_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lk.row * 2);
-  u32x4 kreg[ST_N];
-  auto load_k = [&](int id) {
-#pragma unroll
-    for (int p = 0; p < ST_N; ++p) {
-      const int row = min(id * BKS + st_row + ST_ROWS * p, d.nkv - 1);   // rows past the end re-read the last key
-      kreg[p] = gload_b128(k_base, __umul24((unsigned)row, k_row_bytes) + st_ch * 16);
-    }
-  };
-  auto store_k = [&](int buf) {
-    char* b = lds + buf * TILE;
-#pragma unroll
-    for (int p = 0; p < ST_N; ++p) *reinterpret_cast<u32x4*>(b + (st_row + ST_ROWS * p) * LD + st_ch * 16) = kreg[p];
-  };
-  u32x4 ds[DSQ_SETS][4];
-  auto load_ds = [&](int id, auto set_tag) {
-    constexpr int SET = decltype(set_tag)::value;
-    const unsigned off = (unsigned)id * DS_TILE_BYTES + lane * 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      // read once: keep the stream from displacing the K tiles in L2
-      ds[SET][i] = __builtin_nontemporal_load(
-          reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(ds_base + off + 1024 * i));
-    }
+  auto load = [&](int id, unsigned stage) {        // block id into the stage at `stage`
+    const int r = min(16 * ld_tile + (lane >> 2), d.nkv - 1 - id * BKS);
+    const gptr_t kb = uniform_gptr(k_base + (uint64_t)(unsigned)(id * BKS) * k_row_bytes);
+    dma_blocks<K_N, H>(stage + (ld_tile * KS + ld_sl) * BLOCK, kb, __umul24(r, k_row_bytes) + 16 * ld_chunk, ld_chunk);
+    const gptr_t from = ds_base + (unsigned)id * DS_TILE_BYTES;
+    // (dS is read once: kept from displacing the K tiles in L2)
+    static_for<0, 4>([&](auto I) {
+      constexpr int off = 1024 * decltype(I)::value;
+      dma_b128<off, true>(stage + K_TILE + wave * DS_TILE_BYTES + off, from, lane * 16);
+    });
   };
 
   auto store_rows = [&](float mul, bool add) {
@@ -258,49 +254,37 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   fetch_by(0);
   fetch_by(part * KL);
   if (KL > 1) fetch_by(kl);
-  load_k(f_id);
-  load_ds(f_id, std::integral_constant<int, 0>{});
-  store_k(0);
-  int idq[DSQ_SETS - 2];                           // blocks t + 1 .. t + DSQ_SETS - 2 of iteration t
-  static_for<1, DSQ_SETS - 1>([&](auto S) {        // blocks 1 .. DSQ_SETS - 2
+  load(f_id, lds_base);
+  if (ST == 3) {
     fetch_by(stride);
-    idq[decltype(S)::value - 1] = f_id;
-    load_ds(f_id, S);
-  });
+    load(f_id, lds_base + STAGE);
+  }
   compute_by(part * KL + kl);
+  wait_vmem<(ST - 2) * LOADS>();                   // (block 0 has arrived)
   __syncthreads();
 
-  int buf = 0;
-  // iteration t: K of block t + 1 and dS of block t + DSQ_SETS - 1 are requested (K first: the
-  // wait for it at the end of the iteration must not cover the dS loads behind it), block t is
-  // computed.
-  auto iteration = [&](auto cur_tag) {
-    constexpr int CUR = decltype(cur_tag)::value;
-    load_k(idq[0]);
+  // iteration t: block t + ST - 1 is requested into the stage of block t - 1, block t is computed, block t + 1 has arrived.
+  // (blocks past the last find nvis_wave = 0)
+  unsigned cur = 0;
+  for (int t = 0; t < (count + stride - 1) / stride; ++t) {
     fetch_by(stride);
-    load_ds(f_id, std::integral_constant<int, (CUR + DSQ_SETS - 1) % DSQ_SETS>{});
+    load(f_id, lds_base + (cur == 0 ? (ST - 1) * STAGE : cur - STAGE));
     const int k0 = c_j * BKS;                      // local to the sub-block
-    if (k0 < nvis_wave) {
-      if (k0 + 32 > nfull_wave) dsq_piece<0, true>(cx, ds[CUR], k0); else dsq_piece<0, false>(cx, ds[CUR], k0);
-    }
-    if (k0 + 32 < nvis_wave) {
-      if (k0 + 64 > nfull_wave) dsq_piece<1, true>(cx, ds[CUR], k0 + 32); else dsq_piece<1, false>(cx, ds[CUR], k0 + 32);
-    }
-    store_k(buf ^ 1);
-#pragma unroll
-    for (int x = 0; x + 1 < DSQ_SETS - 2; ++x) idq[x] = idq[x + 1];
-    idq[DSQ_SETS - 3] = f_id;
-    cx.kt += buf ? -TILE : TILE;
-    buf ^= 1;
+    if (k0 < nvis_wave) dsq_piece<0>(cx, k0, k0 + 32 > nfull_wave);
+    if (k0 + 32 < nvis_wave) dsq_piece<1>(cx, k0 + 32, k0 + 64 > nfull_wave);
+    const int go = cur == (ST - 1) * STAGE ? -(ST - 1) * STAGE : STAGE;
+    cx.kt_e += go; cx.kt_o += go; cx.ds += go;
+    cur += go;
     compute_by(stride);
+    wait_vmem<(ST - 2) * LOADS>();
     __syncthreads();
-  };
-  for (int t = 0; t < (count + stride - 1) / stride; t += DSQ_SETS)   // blocks past the last find nvis_wave = 0
-    static_for<0, DSQ_SETS>([&](auto S) { iteration(S); });
+  }
+  wait_vmem_all();                                 // (requests past the last block: LDS is the workgroup's until they have arrived)
   if constexpr (KL == 2) {
     // lane 1 hands its sums to lane 0 through LDS (the K tiles are no longer read: every wavefront
     // has passed the walk's last barrier); layout [row wavefront][value][lane]: conflict free
-    static_assert(RW * HT * 8 * 256 <= KL * 2 * TILE, "the exchange area must fit the K buffers");
+    static_assert(RW * HT * 8 * 256 <= dsq_lds(WAVES, HD, KL), "the exchange area must fit the stages");
+    __syncthreads();
     float* xch = reinterpret_cast<float*>(lds_all) + wave * (HT * 8 * 64) + lane;
     if (kl == 1) {
 #pragma unroll
@@ -343,7 +327,7 @@ template <int HR>
 hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                          const void* V, const void* dO, const float* lse, const float* delta, float* dQ, float* dK,
                          float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
-  constexpr int DSQ_LDS = 2 * BKS * row_ld(padded_head(HR));
+  constexpr int HD = padded_head(HR);
   const bool grouped = g.group > 1;
   hipError_t e = hipSuccess;
   SegList gk = g, gq = g;
@@ -356,9 +340,9 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
         : ensure_dynamic_lds(grouped ? reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, true, true>)
                                    : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, true>), DK_LDS);
     if (e != hipSuccess) return e;
-    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 2>), 2 * DSQ_LDS)
-                 : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 1>)
-                                          : reinterpret_cast<const void*>(bwd_dq_ds_kernel<4, HR, 1>), DSQ_LDS);
+    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 2>), dsq_lds(8, HD, 2))
+           : big ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_ds_kernel<8, HR, 1>), dsq_lds(8, HD, 1))
+                 : ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_ds_kernel<4, HR, 1>), dsq_lds(4, HD, 1));
   }
   dim3 grid_kv(xcd_grid(d.heads / g.group * parts.kv, (d.nkv + DK_KEYS - 1) / DK_KEYS));
   const int dq_rows = big ? 256 : 128;
@@ -376,13 +360,13 @@ hipError_t bwd_launch_ds(Phase ph, const a2d_tile_desc& d, const SegList& g, con
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (big)
-    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 1>), grid_q, dim3(512), DSQ_LDS, s, d, gq, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 1>), grid_q, dim3(512), dsq_lds(8, HD, 1), s, d, gq, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   else if (lanes)
-    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 2>), grid_q, dim3(512), 2 * DSQ_LDS, s, d, gq, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<8, HR, 2>), grid_q, dim3(512), dsq_lds(8, HD, 2), s, d, gq, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   else
-    A2D_LAUNCH((bwd_dq_ds_kernel<4, HR, 1>), grid_q, dim3(256), DSQ_LDS, s, d, gq, (const bf16_t*)K,
+    A2D_LAUNCH((bwd_dq_ds_kernel<4, HR, 1>), grid_q, dim3(256), dsq_lds(4, HD, 1), s, d, gq, (const bf16_t*)K,
                        (const bf16_t*)ds_ws, dQ);
   return hipGetLastError();
 }

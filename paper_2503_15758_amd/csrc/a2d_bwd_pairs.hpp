@@ -417,7 +417,8 @@ __device__ __forceinline__ void dkdv_pairs(
 
   // dS hand-over: this pair's 32 keys are piece T = pair & 1 of key block 2 blk + (pair >> 1)
   const unsigned ds_row_stride = (unsigned)ds_key_blocks(d.nkv) * DS_TILE_BYTES;
-  const unsigned ds_lane_off = (unsigned)(2 * blk + (pair >> 1)) * DS_TILE_BYTES + (pair & 1) * 2048 + lane * 16;
+  const unsigned ds_lane_off = (unsigned)(2 * blk + (pair >> 1)) * DS_TILE_BYTES + (pair & 1) * 2048 +
+                               (l32 >> 4) * 1024 + ((lane >> 5) * 16 + (l32 & 15)) * 16;
   gwptr_t ds_base = nullptr;
   if constexpr (WRITE_DS)
     ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) + qh0 * ds_head_bytes(d.nq, d.nkv));
@@ -504,21 +505,14 @@ __device__ __forceinline__ void dkdv_pairs(
         dk_mbox_pre(cx, pm);
         dk_second_pre(cx, t);
         dk_dscores(pm, dp, bf);
-        bf16x8 ds_out[2];
-        if constexpr (WRITE_DS) {
-          // turned around through LDS; requested BEFORE the contraction's own fragments are
-          // waited for (LDS answers in order), so the stores below find their data arrived
-          ds_turn_write(cx.mbox - lane * 16, l32, cx.half, bf);
-          ds_turn_read(cx.mbox - lane * 16, lane, ds_out);
-          __builtin_amdgcn_sched_barrier(0);
-        }
         dk_second(cx, t, bf);
         if constexpr (WRITE_DS) {
           // (measured: making these stores unconditional - skipped steps writing to a spill slot,
           // which keeps the compiler's load wait counts exact - is not faster)
           const unsigned off = (unsigned)p_rt * ds_row_stride + ds_lane_off;
-          gstore_b128(ds_base, off, ds_out[0]);
-          gstore_b128(ds_base, off + 1024, ds_out[1]);
+          // (register group q: rows 8 q + 4 half + 0..3, i.e. of groups g = half and 2 + half)
+          gstore_b128(ds_base, off, __builtin_shufflevector(bf[0], bf[1], 0, 1, 2, 3, 8, 9, 10, 11));
+          gstore_b128(ds_base, off + 512, __builtin_shufflevector(bf[0], bf[1], 4, 5, 6, 7, 12, 13, 14, 15));
         }
       }
       advance(SET ? DK_MBOX_SLOT : -DK_MBOX_SLOT);

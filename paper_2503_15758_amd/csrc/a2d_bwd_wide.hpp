@@ -33,14 +33,11 @@ constexpr int WK_KEYS = 256, WK_THREADS = 512;
 // barriers of 32-row steps the kernel was 6 % faster, without their requests 14 %: both wavefronts of a SIMD make these at
 // the same time).  64 x 4096 x 4096 as above 1548 / 1239 / 1136 / 912 -> 1522 / 1206 / 1111 / 891 us.
 constexpr int WK_ROWS = 64;
-// LDS: two buffers { Q tile, dO tile } in blocks | two of { -lse / scale [64], -delta [64] } | a wavefront's piece
-// for turning dS
+// LDS: two buffers { Q tile, dO tile } in blocks | two of { -lse / scale [64], -delta [64] }
 __host__ __device__ constexpr int wk_tile(int hd) { return WK_ROWS * 2 * hd; }
 constexpr int WK_STAT_BUF = 2 * WK_ROWS * 4;
 __host__ __device__ constexpr int wk_stat(int hd) { return 4 * wk_tile(hd); }
-__host__ __device__ constexpr int wk_turn(int hd) { return wk_stat(hd) + 2 * WK_STAT_BUF; }
-constexpr int WK_TURN_BYTES = 32 * DS_TR_LD;
-__host__ __device__ constexpr int wk_lds(int hd) { return wk_turn(hd) + 8 * WK_TURN_BYTES; }
+__host__ __device__ constexpr int wk_lds(int hd) { return wk_stat(hd) + 2 * WK_STAT_BUF; }
 
 // GRID: all key blocks of an emulated grid (g.b).  The workgroup walks the query rows of its whole grid column and
 // writes rows of dK and dV of the sequence (of a split walk: a partial, [part][column][head][key]).  Contiguous blocks
@@ -232,7 +229,6 @@ __device__ __forceinline__ void dkdv_wide(
   // dS hand-over: the wavefront's 32 keys are piece wave & 1 of key block 4 blk + wave / 2
   const unsigned ds_row_stride = (unsigned)ds_key_blocks(d.nkv) * DS_TILE_BYTES;
   const unsigned ds_wave_off = (unsigned)(8 * blk + wave) * (DS_TILE_BYTES / 2);
-  const unsigned turn = lds_base + wk_turn(HD) + wave * WK_TURN_BYTES;
   gwptr_t ds_base = nullptr;
   if constexpr (WRITE_DS)
     ds_base = uniform_gwptr(reinterpret_cast<char*>(dS) + qh0 * ds_head_bytes(d.nq, d.nkv));
@@ -322,11 +318,8 @@ __device__ __forceinline__ void dkdv_wide(
     });
     if constexpr (WRITE_DS) {
       const int ln = TIGHT ? lane_again() : lane;
-      bf16x8 out[2];
-      ds_turn_write16(turn, ln, sb);
-      ds_turn_read(turn, ln, out);
-      gstore_b128(ds_base, ds_off + 16 * ln, out[0]);
-      gstore_b128(ds_base, ds_off + 16 * ln + 1024, out[1]);
+      gstore_b128(ds_base, ds_off + 16 * ln, sb[0]);
+      gstore_b128(ds_base, ds_off + 16 * ln + 1024, sb[1]);
     }
   };
 

@@ -179,23 +179,6 @@ struct DualAddr {
 // byte offset inside a dual tile at which the 16-byte chunk `c` of row `r` is stored
 __device__ __forceinline__ int dual_store_off(int r, int c) { return r * DUAL_LD + ((c ^ ((r >> 2) & 3)) << 4); }
 
-// Tiles of the 16 x 16 x 32 kernels: rows of the padded head's bytes + 32, no swizzle.  The row stride is an odd multiple
-// of 8 banks (288, 224, 160 bytes), which makes both kinds of fragment reads conflict free:
-//   - natural fragment of rows RB + (lane & 15), slice sl of 32 columns: nat + 64 sl + RB ld;
-//   - transposed fragment of column tile ht (16 columns), rows RB + 4 g + 0..3 and RB + 16 + 4 g + 0..3 of lane group
-//     g = lane >> 4: tr + 32 ht + RB ld and 16 ld further on.
-// (272 bytes or a swizzle of the chunks cost the natural reads 1.55 times the cycles, the former the transposing ones too.)
-__host__ __device__ constexpr int row_ld(int hd) { return 2 * hd + 32; }
-struct Rows16 {
-  unsigned nat, tr;
-  __device__ __forceinline__ void init(int lane, unsigned tile_base, int ld) {
-    const int g = lane >> 4, j = lane & 15;
-    nat = tile_base + j * ld + 16 * g;
-    tr = tile_base + (4 * g + (j >> 2)) * ld + 8 * (j & 3);
-  }
-  __device__ __forceinline__ void shift(int delta) { nat += delta; tr += delta; }
-};
-
 // Tiles that are loaded straight into LDS (dma_b128: lane i of a wavefront writes the 16 bytes at i from a common address on,
 // so rows cannot be padded).  A tile is made of blocks of 16 rows x 32 columns, 1 KiB each, one wavefront's load: row r at 64 r,
 // its four 16-byte chunks c at c ^ block_swap(r >> 2).  With that both kinds of fragment reads are conflict free:
@@ -216,13 +199,18 @@ struct Blocks16 {
 // vector memory operation; the compiler does not know of it, so the caller waits (wait_vmem_all) before the barrier behind
 // which the tile is read.  dma_blocks: the N blocks of a row tile, slice after slice of its rows - one lane offset and one
 // base for all (the instruction's offset counts for both addresses).
-template <int OFF>
+// (NT: read once)
+#define A2D_DMA_B128(more)                                                                                                   \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" more ::"s"(                         \
+                   __builtin_amdgcn_readfirstlane(at - OFF)),                                                                \
+               "v"(byte_off), "s"(base), "n"(OFF)                                                                            \
+               : "memory")
+template <int OFF, bool NT = false>
 __device__ __forceinline__ void dma_b128(unsigned at, gptr_t base, unsigned byte_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(__builtin_amdgcn_readfirstlane(at - OFF)),
-               "v"(byte_off), "s"(base), "n"(OFF)
-               : "memory");
+  if constexpr (NT) A2D_DMA_B128(" nt"); else A2D_DMA_B128("");
 }
 // (H: the head size; chunks past it are left alone)
+#undef A2D_DMA_B128
 template <int N, int H>
 __device__ __forceinline__ void dma_blocks(unsigned at, gptr_t base, unsigned byte_off, int chunk) {
   static_for<0, N>([&](auto X) {
