@@ -10,7 +10,11 @@ namespace mfma {
 constexpr int BKS = 64;           // keys per step
 // LDS: [buf]{ K tile, V tile }, in blocks
 __host__ __device__ constexpr int dq_buf(int hd) { return 2 * BKS * 2 * hd; }
+// of a key lane (eight wavefronts also store 16 rows each at a time)
 __host__ __device__ constexpr int dq_lds(int hd) { return 2 * dq_buf(hd); }
+__host__ __device__ constexpr int dq_launch_lds(int hd, int kl) {
+  return kl * dq_lds(hd) > 8 * acc_area(hd / 16) ? kl * dq_lds(hd) : 8 * acc_area(hd / 16);
+}
 // fragment ring depth (registers are tight above H = 64: 256 per wavefront)
 __host__ __device__ constexpr int dq_ring(int hd) { return hd == 64 ? 4 : 2; }
 
@@ -331,16 +335,18 @@ __device__ __forceinline__ void dq_rows(
 #pragma unroll
       for (int r = 0; r < 8; ++r) cx.dq[t][r >> 2][r & 3] += xch[(8 * t + r) * 64];
   }
+  // (KL = 2: inside what this wavefront has read of the exchange)
+  char* const area = lds_all + wave * (KL == 2 ? HT * 8 * 256 : acc_area(HT));
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const int r = q_row + 16 * q;
-    if (r >= d.nq) continue;
+    const int first = q0 + wave * 32 + 16 * q;
     if (GRID && parts == 1) {
       bf16_t* const out = reinterpret_cast<bf16_t*>(dQ) + head * g.b.out[0].head + row_blk * g.b.out_step[0];
-      store_acc16(out + r * g.b.out[0].row, cx.dq, q, cx.grp, d.scale);
+      store_acc16(out + first * g.b.out[0].row, g.b.out[0].row, d.nq - first, area, cx.dq, q, lane, d.scale);
     } else {
       const int64_t slot = (int64_t)part * (GRID ? g.b.side : 1) + row_blk;
-      store_acc16(dQ + ((slot * d.heads + head) * d.nq + r) * H, cx.dq, q, cx.grp, d.scale, !GRID && g.acc != 0);
+      store_acc16(dQ + ((slot * d.heads + head) * d.nq + first) * H, H, d.nq - first, area, cx.dq, q, lane, d.scale,
+                  !GRID && g.acc != 0);
     }
   }
 }

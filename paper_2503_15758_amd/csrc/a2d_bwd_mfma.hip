@@ -239,11 +239,14 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     });
   };
 
+  // (KL = 2: inside what this wavefront has read of the exchange)
+  char* const area = lds_all + wave * (KL == 2 ? HT * 8 * 256 : acc_area(HT));
   auto store_rows = [&](float mul, bool add) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (q_row + 16 * u < d.nq)
-        store_acc16(dQ + (((int64_t)part * d.heads + head) * d.nq + q_row + 16 * u) * H, cx.dq, u, cx.grp, mul, add);
+    for (int u = 0; u < 2; ++u) {
+      const int first = q0 + wave * 32 + 16 * u;
+      store_acc16(dQ + (((int64_t)part * d.heads + head) * d.nq + first) * H, H, d.nq - first, area, cx.dq, u, lane, mul, add);
+    }
   };
   count = count > part * KL ? count - part * KL : 0;           // from this part's first block on
   if (count == 0) {                                // no visible key: dQ share is zero
@@ -279,7 +282,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     wait_vmem<(ST - 2) * LOADS>();
     __syncthreads();
   }
-  wait_vmem_all();                                 // (requests past the last block: LDS is the workgroup's until they have arrived)
+  wait_vmem_all();                                 // (requests past the last block, of every wavefront, before LDS is used otherwise or left)
+  __syncthreads();
   if constexpr (KL == 2) {
     // lane 1 hands its sums to lane 0 through LDS (the K tiles are no longer read: every wavefront
     // has passed the walk's last barrier); layout [row wavefront][value][lane]: conflict free
@@ -377,7 +381,7 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
                          float* dV, void* ds_ws, const BwdParts& parts, hipStream_t s) {
   if constexpr (HR == 128)                             // (dS is kept at H = 128 only, see plan_bwd_mfma)
     if (ds_ws) return bwd_launch_ds<HR>(ph, d, g, Q, K, V, dO, lse, delta, dQ, dK, dV, ds_ws, parts, s);
-  constexpr int DQ_LDS = dq_lds(padded_head(HR));
+  constexpr int DQ_LDS = dq_launch_lds(padded_head(HR), 1), DQ_LDS2 = dq_launch_lds(padded_head(HR), 2), DQ_LDS4 = dq_lds(padded_head(HR));
   const bool grouped = g.group > 1;
   // Q and dO in the plain layout: the variant with compile-time staging offsets
   const bool plain = d.lq.row == HR && d.ldo.row == HR && d.lq.head == (int64_t)d.nq * HR && d.ldo.head == d.lq.head;
@@ -394,9 +398,9 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
                                         : reinterpret_cast<const void*>(bwd_dkdv_kernel<HR, false, false, false>));
     e = parts.wide ? launch_dkdv_wide(ph, d, gk, Q, K, V, dO, lse, delta, dK, dV, nullptr, s) : ensure_dynamic_lds(dkdv, DK_LDS);
     if (e != hipSuccess) return e;
-    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 2>), 2 * DQ_LDS)
-                 : ensure_dynamic_lds(big ? reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 1>)
-                                          : reinterpret_cast<const void*>(bwd_dq_kernel<4, HR, 1>), DQ_LDS);
+    return lanes ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 2>), DQ_LDS2)
+           : big ? ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_kernel<8, HR, 1>), DQ_LDS)
+                 : ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_dq_kernel<4, HR, 1>), DQ_LDS4);
   }
   dim3 grid_kv(xcd_grid(d.heads / g.group * parts.kv, (d.nkv + DK_KEYS - 1) / DK_KEYS));
   const int dq_rows = big ? 256 : 128;
@@ -405,10 +409,10 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
     A2D_LAUNCH((bwd_dq_kernel<8, HR, 1>), grid_q, dim3(512), DQ_LDS, s, d, gq, (const bf16_t*)Q,
                        (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ);
   else if (lanes)
-    A2D_LAUNCH((bwd_dq_kernel<8, HR, 2>), grid_q, dim3(512), 2 * DQ_LDS, s, d, gq, (const bf16_t*)Q,
+    A2D_LAUNCH((bwd_dq_kernel<8, HR, 2>), grid_q, dim3(512), DQ_LDS2, s, d, gq, (const bf16_t*)Q,
                        (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ);
   else
-    A2D_LAUNCH((bwd_dq_kernel<4, HR, 1>), grid_q, dim3(256), DQ_LDS, s, d, gq, (const bf16_t*)Q,
+    A2D_LAUNCH((bwd_dq_kernel<4, HR, 1>), grid_q, dim3(256), DQ_LDS4, s, d, gq, (const bf16_t*)Q,
                        (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, (const bf16_t*)dO, lse, delta, dQ);
   e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -38,7 +38,7 @@ template <int HR, bool WIDE, int KL, int GRID>
 hipError_t go(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
               const void* O, const void* dO, const float* lse, const float* delta, float* dQ, float* dK, float* dV,
               const BwdParts& parts, hipStream_t s) {
-  constexpr int HD = padded_head(HR), kv_lds = WIDE ? wk_lds(HD) : DK_LDS, q_lds = KL * dq_lds(HD);
+  constexpr int HD = padded_head(HR), kv_lds = WIDE ? wk_lds(HD) : DK_LDS, q_lds = dq_launch_lds(HD, KL);
   constexpr int bytes = kv_lds > q_lds ? kv_lds : q_lds;
   if (ph == PREPARE) return ensure_dynamic_lds(reinterpret_cast<const void*>(bwd_one_kernel<HR, WIDE, KL, GRID>), bytes);
   constexpr int keys = WIDE ? WK_KEYS : DK_KEYS, rows = 256 / KL;

@@ -37,7 +37,10 @@ constexpr int WK_ROWS = 64;
 __host__ __device__ constexpr int wk_tile(int hd) { return WK_ROWS * 2 * hd; }
 constexpr int WK_STAT_BUF = 2 * WK_ROWS * 4;
 __host__ __device__ constexpr int wk_stat(int hd) { return 4 * wk_tile(hd); }
-__host__ __device__ constexpr int wk_lds(int hd) { return wk_stat(hd) + 2 * WK_STAT_BUF; }
+__host__ __device__ constexpr int wk_lds(int hd) {
+  const int walk = wk_stat(hd) + 2 * WK_STAT_BUF, rows = 8 * acc_area(hd / 16);      // (16 keys of every wavefront go out at a time)
+  return walk > rows ? walk : rows;
+}
 
 // GRID: all key blocks of an emulated grid (g.b).  The workgroup walks the query rows of its whole grid column and
 // writes rows of dK and dV of the sequence (of a split walk: a partial, [part][column][head][key]).  Contiguous blocks
@@ -356,19 +359,19 @@ __device__ __forceinline__ void dkdv_wide(
     __syncthreads();
   }
 
+  char* const area = lds + wave * acc_area(HT);
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt) {
-    const int k = key + 16 * kt;
-    if (k >= d.nkv) continue;
+    const int first = wk + 16 * kt, n = d.nkv - first;
     if (GRID && parts == 1) {
       bf16_t* const dkb = reinterpret_cast<bf16_t*>(dK) + head * g.b.out[1].head + col * g.b.out_step[1];
       bf16_t* const dvb = reinterpret_cast<bf16_t*>(dV) + head * g.b.out[2].head + col * g.b.out_step[2];
-      store_acc16(dvb + k * g.b.out[2].row, dv, kt, grp, 1.0f);
-      store_acc16(dkb + k * g.b.out[1].row, dk, kt, grp, d.scale);
+      store_acc16(dvb + first * g.b.out[2].row, g.b.out[2].row, n, area, dv, kt, lane, 1.0f);
+      store_acc16(dkb + first * g.b.out[1].row, g.b.out[1].row, n, area, dk, kt, lane, d.scale);
     } else {
-      const int64_t row = (int64_t)head * d.nkv + k;
-      store_acc16(dV + row * H, dv, kt, grp, 1.0f);
-      store_acc16(dK + row * H, dk, kt, grp, d.scale);
+      const int64_t at = ((int64_t)head * d.nkv + first) * H;
+      store_acc16(dV + at, H, n, area, dv, kt, lane, 1.0f);
+      store_acc16(dK + at, H, n, area, dk, kt, lane, d.scale);
     }
   }
 }

@@ -43,9 +43,9 @@ using namespace mfma;
 constexpr int BN = 64;             // keys per step
 __host__ __device__ constexpr int buf_bytes(int hd) { return 2 * BN * 2 * hd; }   // { K tile, V tile }, in blocks
 __host__ __device__ constexpr int lds_bytes(int hd) { return 2 * buf_bytes(hd); }          // of a key lane
-// of a launch: an accumulating call brings 16 rows of every wavefront in at a time
+// of a launch: 16 rows of every wavefront come in (accumulating calls) and go out at a time
 __host__ __device__ constexpr int fwd_lds(int waves, int hd, int kl) {
-  const int tiles = kl * lds_bytes(hd), rows = waves / kl * 16 * (4 * hd + 16);
+  const int tiles = kl * lds_bytes(hd), rows = waves / kl * acc_area(hd / 16);
   return tiles > rows ? tiles : rows;
 }
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
@@ -483,25 +483,26 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
       f[q] = 1.f;
     }
   }
-  // a lane's pieces of a row: columns 16 ht + 4 grp + 0..3
+  // (KL = 2: inside what this wavefront has read of the exchange)
+  char* const area = lds_all + wave * (KL == 2 ? (HT * 8 + 4) * 256 : acc_area(HT));
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const int r = q_row + 16 * q;
-    if (r >= d.nq) continue;
+    const int first = q0 + wave * 32 + 16 * q, r = first + (lane & 15);
+    const bool stat = grp == 0 && r < d.nq;
     if (g.norm) {
       // normalised partial: O' = N / l rounded to bf16, lse' = m + ln l (Sec. 3.2, footnote)
       // (GRID: the row of O and lse itself)
       const int64_t row = GRID ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, r) : (int64_t)head * d.nq + r;
-      const int64_t o_at = GRID ? head * d.lo.head + row_blk * g.b.o + r * d.lo.row : row * H;
+      const int64_t o_at = GRID ? head * d.lo.head + row_blk * g.b.o + first * d.lo.row : ((int64_t)head * d.nq + first) * H;
       const float fn = l_tot[q] > 0.f ? f[q] / l_tot[q] : 0.f;
-      store_acc16(reinterpret_cast<bf16_t*>(O_part) + o_at, st.o, q, grp, fn);
-      if (grp == 0) m_out[row] = l_tot[q] > 0.f ? m_row[q] * d.scale + logf(l_tot[q]) : -INFINITY;
+      store_acc16(reinterpret_cast<bf16_t*>(O_part) + o_at, GRID ? d.lo.row : H, d.nq - first, area, st.o, q, lane, fn);
+      if (stat) m_out[row] = l_tot[q] > 0.f ? m_row[q] * d.scale + logf(l_tot[q]) : -INFINITY;
     } else {
-      const int64_t row = (int64_t)head * d.nq + r;
-      store_acc16(O_part + row * H, st.o, q, grp, f[q]);
-      if (grp == 0) {
-        m_out[row] = m_row[q] * d.scale;      // -inf stays -inf (scale > 0)
-        l_out[row] = l_tot[q];
+      const int64_t row = (int64_t)head * d.nq + first;
+      store_acc16(O_part + row * H, H, d.nq - first, area, st.o, q, lane, f[q]);
+      if (stat) {
+        m_out[row + (lane & 15)] = m_row[q] * d.scale;      // -inf stays -inf (scale > 0)
+        l_out[row + (lane & 15)] = l_tot[q];
       }
     }
   }
