@@ -159,6 +159,10 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
   best_kv.n = xcd_grid(kv_heads * best->kv, side * ((d.nkv + keys - 1) / keys));
   best_q.n = xcd_grid(kv_heads * best->q, side * g.group * ((d.nq + rows - 1) / rows));
   *dealt = rest + (best->q_first ? dealt_time(best_q, best_kv, cus, w.uneven, kTail) : dealt_time(best_kv, best_q, cus, w.uneven, kTail));
+  // (Under a mask most key blocks may be seen by few rows or none, which leaves dK / dV one long walk and many short ones, each
+  // still with its prologue and its rows to store: behind them the dQ walks start late.  us, dK / dV first / dQ first: 40 x
+  // 496 x 2977, H = 128 53.8 / 41.7, 46 x 717 x 4521 86.8 / 71.5, 14 x 339 x 4617 34.6 / 29.2, 44 x 282 x 872, H = 80 22.9 / 19.6.)
+  if (w.uneven && !g.b.side && best_q.mean > best_kv.mean && best_kv.n + best_q.n > cus) best->q_first = 1;
   return least;
 }
 
