@@ -50,8 +50,10 @@ __host__ __device__ constexpr int fwd_lds(int waves, int hd, int kl) {
 }
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
 constexpr double kStepUs[3] = {1.25, 1.45, 1.66};   // a 64-key step of a 256-row workgroup, H = 64 / 96 / 128
-constexpr double kSmallRoundUs[3] = {0.95, 1.42, 1.65}, kSmallFixedUs[3] = {3.1, 3.5, 3.2};   // 256 keys of 32 rows
-constexpr double kPairRoundUs[3] = {0.95, 1.25, 1.37}, kPairFixedUs[3] = {4.1, 4.3, 4.4};     // 128 keys of 64 rows
+// a round of 256 keys of 32 rows, of 128 keys of 64 rows: in tiles (the fit to 720 shapes below); in calls over a grid, whose
+// walks of every length make them wait for each other (350 grids: 2.0 % off the best form with these and with the tiles')
+constexpr double kSmallRoundUs[2][3] = {{0.75, 1.03, 1.37}, {0.95, 1.42, 1.65}}, kSmallFixedUs[2][3] = {{2.5, 2.8, 2.55}, {3.1, 3.5, 3.2}};
+constexpr double kPairRoundUs[2][3] = {{0.71, 1.10, 1.21}, {0.95, 1.25, 1.37}}, kPairFixedUs[2][3] = {{4.2, 4.0, 3.9}, {4.1, 4.3, 4.4}};
 
 template <int HR>
 struct FwdState {
@@ -61,16 +63,6 @@ struct FwdState {
   float m_ref[2];        // reference the exponentials are taken against (raw units, same in the four lanes of a row)
   float l_run[2];        // this lane's share of the row sum, relative to m_ref
 };
-
-// maximum, sum over the four lanes of a row
-__device__ __forceinline__ float row_max(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16, 64));
-  return fmaxf(x, __shfl_xor(x, 32, 64));
-}
-__device__ __forceinline__ float row_sum(float x) {
-  x += __shfl_xor(x, 16, 64);
-  return x + __shfl_xor(x, 32, 64);
-}
 
 // One 64-key block for one wavefront; at: its buffer's offset from the addresses in rd.  S^T in tiles of 16 keys (k) x 16 queries (q): lane = query, registers = keys 16 k + 4 grp +
 // 0..3; the registers of two key tiles are the eight contraction indices of a lane in O^T += V^T P^T.
@@ -547,9 +539,10 @@ hipError_t fwd_form(Phase ph, const a2d_tile_desc& d, const SegList& g, const vo
 // is finer); 64- and 32-row workgroups whose four or eight key lanes share the walk (a2d_fwd_small.hip; a step is a round
 // of 128 or 256 keys).  By model, with parts > 1 where the blocks leave compute units idle and the walk is long.  The
 // constants are a fit to 95 shapes x three forms x up to five numbers of parts (1 x 128 x 128 to 96 x 1024 x
-// 2048, H = 64 and 128), to 149 shapes of few rows, H = 64 to 128 - 32 rows are taken up to about 256 such blocks, 64 rows up to
-// 256 of theirs, under a causal mask up to 512, with walks of 16 rounds at the most; there the choice is 0.3 % slower than the best
-// of 12 forms and parts, and 1.25 times as fast in the mean as without the two forms - and 73 of any size (worst miss 11 %).
+// 2048, H = 64 and 128), to 73 of any size (worst miss 11 %) and, those of few rows, to 720 tiles of up to 1100 blocks of 32 rows,
+// H = 64 to 128, x five forms x up to six numbers of parts - 32 rows are taken up to about 256 such blocks, 64 rows up to
+// 256 of theirs, under a causal mask up to 512, with walks of 16 rounds at the most; there the choice is 1.5 % slower than the
+// best in the mean, much of it the noise of calls of 6 us (2.7 % with the constants of the kernel before it loaded straight into LDS).
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t heads = (int64_t)d.heads * (g->b.side ? g->b.side : 1);
   double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2, mean = most;
@@ -568,8 +561,8 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   // (the walks of a causal grid are of every length down to a few steps, so that the last ones end nearly together; those of 32
   // and 64 rows wait for each other's loads all the same: 7 heads, 5166 tokens on 3 x 3, H = 128, cyclic 101 us with 0.1, 82 in pairs)
   const double tail = g->b.side ? 0.1 : 0.5, big = g->b.side ? fixed + 1.5 : fixed;
-  const int h = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0;
-  const double round = kSmallRoundUs[h], small = kSmallFixedUs[h];
+  const int h = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, over = g->b.side > 0;
+  const double round = kSmallRoundUs[over][h], small = kSmallFixedUs[over][h];
   // (plain calls write fp32 partials, 128 KiB a workgroup of 256 rows at H = 128: those that start and end together store
   // at the rate of the memory, two side by side on a compute unit one under the other's walk.  29 x 4679 x 359, H = 96: 49 us
   // in 256-row workgroups, 42 in pairs)
@@ -580,7 +573,7 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
                           {b128, cus, mean / 2, most / 2, step * 1.13, lanes_fix, 0, 0, nullptr, 0, tail},
                           {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, pair_fix, nullptr, 0, tail},
                           {b32, cus, mean / 4, most / 4, round, small, 0, 0, sorted, 0.25 / BN, 0.5, true},
-                          {b64, cus, mean / 2, most / 2, kPairRoundUs[h], kPairFixedUs[h], 0, 0, sorted, 0.5 / BN, 0.5, true, true}};
+                          {b64, cus, mean / 2, most / 2, kPairRoundUs[over][h], kPairFixedUs[over][h], 0, 0, sorted, 0.5 / BN, 0.5, true, true}};
   double least = 0;
   for (int f = 0; f < 5; ++f) {
     double t;

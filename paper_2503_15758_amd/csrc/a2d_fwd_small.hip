@@ -7,13 +7,19 @@
 // stages its slabs in a piece of LDS of its own.  (K read straight into the A operands, a lane a row, goes 32 lines at a
 // time through an L1 that eight wavefronts share: 13.5 us became 16.4 at 8 x 1024 x 1024, H = 128.)
 // What bounds it: launch, argument and first-load latencies below two rounds of slabs; then what a compute unit reads
-// from L2, 128 KiB a round at H = 128 (1.65 us; its MFMAs take 0.45), since every 32 rows read all keys they see.  For
+// from L2, 128 KiB a round at H = 128 (its MFMAs take a third of that time), since every 32 rows read all keys they see.  For
 // short calls that is cheaper than partial results and a second launch, for long ones not (see plan_fwd_mfma).
+// So that the reads are always under way: operands go straight into LDS, without registers in between, the next K slab as soon
+// as this one's scores are there, the next V behind the last product; Q once for the workgroup instead of once for each
+// wavefront.  Against a slab by way of registers, requested before the one at hand is computed, and 32 x 32 x 16 MFMAs:
+// H = 128 2 x 512 x 512 9.5 -> 7.9 us, 8 x 1024 x 1024 13.1 -> 10.8, 4 x 2048 x 2048 19.7 -> 16; H = 96 4 x 400 x 400 8.0 -> 6.8;
+// H = 80 8 x 700 x 900 10.6 -> 9.1; H = 64 2 x 512 x 512 6.2 -> 5.9, 4 x 2048 x 2048 11.9 -> 11.0.  (H = 64 with Q in LDS too is
+// 0.3 us slower: there the wavefronts' own loads of Q are the shorter way.)
 // Where 32-row blocks no longer run at once, 64 rows in four lanes of two wavefronts that stage their slabs together read half
-// as much and need a barrier a round (1.37 us for 128 keys): H = 128 16 x 1024 x 1024 22.4 -> 18.7 us, 8 x 2048 x 2048 36.3 ->
-// 29.2, 16 x 1500 x 1500 causal 32.1 -> 24.9; H = 64 32 x 512 x 512 11.6 -> 8.9.
-// Measured, against the best of the other forms: H = 128 2 x 512 x 512 causal 15.4 -> 9.3 us, 8 x 1024 x 1024 23.0 -> 12.8,
-// 4 x 2048 x 2048 26.5 -> 20; H = 64 2 x 512 x 512 10.8 -> 6.3, 8 x 1024 x 1024 16.6 -> 8.6.
+// as much and need a barrier a round: H = 128 16 x 1024 x 1024 16.2 us against 20.6 in 32 rows, 8 x 2048 x 2048 25.4 / 30.3;
+// H = 64 32 x 512 x 512 8.2 / 11.2.
+// Against the other forms of today (128 rows in two key lanes, unshared): 4 x 2048 x 2048 33.2 us for 16.2, 8 x 1024 x 1024 20.5
+// for 10.8.
 #include "a2d_mfma.hpp"
 
 namespace a2d {
@@ -22,12 +28,11 @@ namespace {
 using namespace mfma;
 
 constexpr int SB = 32, WAVES = 8;                  // keys of a slab, wavefronts
-// LDS: eight { K slab, V slab } (rows as in a2d_fwd_mfma.hip) | m, l of every wavefront's rows
-constexpr int KLD = 272, VLD = 320, V_AT = SB * KLD, SLAB_BYTES = SB * (KLD + VLD);
-constexpr int STAT = WAVES * SLAB_BYTES;
-constexpr int LDS_BYTES = STAT + 2 * WAVES * SB * 4;
+// LDS: eight { K slab, V slab } (in blocks, as in a2d_fwd_mfma.hip) | m, l of every wavefront's rows | the workgroup's Q
+constexpr int STAT = WAVES * 16 * 1024;            // (the slabs at H = 128; every wavefront's results at the end)
+constexpr int Q_AT = STAT + 2 * WAVES * SB * 4;
+constexpr int lds_bytes(int rg, int hd) { return Q_AT + (hd > 64 ? rg * 64 * hd : 0); }
 constexpr float kRescaleThreshold = 8.0f;          // log2 units
-static_assert(WAVES * 16 * 1024 <= STAT, "the pieces of four column tiles must fit the slabs");
 
 // RG: groups of 32 rows.  1: eight key lanes, each wavefront its own slab.  2: 64 rows and four lanes of two wavefronts that
 // stage a slab together, two buffers each: half the reads from L2, a barrier a round.
@@ -36,7 +41,9 @@ template <int HR, int RG, int GRID>
 __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
     const bf16_t* __restrict__ V, float* O_part, float* m_out, float* l_out, FwdInput in) {
-  constexpr int HD = padded_head(HR), H = HR, KS = (HR + 15) / 16, CT = HD / 32;
+  constexpr int HD = padded_head(HR), H = HR, KS = HD / 32, HT = HR / 16;
+  constexpr int V_AT = 2 * KS * BLOCK, SLAB_BYTES = 2 * V_AT;
+  static_assert(WAVES * SLAB_BYTES <= STAT && HT * 2 <= 16, "slabs and results must fit");
   constexpr bool PLAIN = GRID == 0, CYCLIC = GRID == 2;
   warm_arguments<9 * 8>();
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -44,7 +51,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
   constexpr int LANES = WAVES / RG, BM = 32 * RG;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int kl = wave / RG, rg = wave % RG;        // key lane, row group
-  const int half = lane >> 5, l32 = lane & 31;
+  const int grp = lane >> 4, l16 = lane & 15;
 
   const int nqb = (d.nq + BM - 1) / BM;
   int unit, blk;
@@ -70,13 +77,28 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
     l_out += slot;
   }
 
-  // ---- Q^T fragments; rows beyond nq re-read the last row
-  const int q_row = w0 + l32, q_ld = min(q_row, d.nq - 1);
-  bf16x8 qf[KS];
-  {
-    const bf16_t* qp = Q + (int64_t)q_ld * d.lq.row + 8 * half;
+  // ---- Q comes in once for all wavefronts, through LDS (at H = 64 it is little, and every wavefront loads its fragments);
+  // rows beyond nq re-read the last row, columns past the head size are zero
+  constexpr bool Q_LDS = HD > 64;
+  const int q_row = w0 + l16;                      // of the first of the wavefront's two tiles of 16
+  const int ld_chunk = (lane & 3) ^ block_swap(lane >> 4);
+  bf16x8 qf[KS][2];
+  if constexpr (Q_LDS) {
+    const unsigned q_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lq.row * 2);
 #pragma unroll
-    for (int x = 0; x < KS; ++x) qf[x] = *reinterpret_cast<const bf16x8*>(qp + 16 * x);
+    for (int p = 0; p < (2 * RG * KS + WAVES - 1) / WAVES; ++p) {
+      const int b = wave + WAVES * p, tile = b / KS, sl = b - tile * KS;
+      if (2 * RG * KS % WAVES != 0 && b >= 2 * RG * KS) break;
+      if (H == HD || 32 * sl + 8 * ld_chunk < H)
+        dma_b128<0>(lds_base + Q_AT + b * BLOCK, uniform_gptr(reinterpret_cast<const char*>(Q) + 64 * sl),
+                    __umul24((unsigned)min(q0 + 16 * tile + (lane >> 2), d.nq - 1), q_row_bytes) + 16 * ld_chunk);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int x = 0; x < KS; ++x)
+        qf[x][q] = *reinterpret_cast<const bf16x8*>(Q + (int64_t)min(q_row + 16 * q, d.nq - 1) * d.lq.row + 32 * x + 8 * grp);
   }
   const float c = d.scale * kLog2e;
 
@@ -94,11 +116,12 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
     const int64_t v = (int64_t)i + rel + 1;
     return v <= 0 ? 0 : (v < rows ? (int)v : rows);
   };
-  int nfull = 0, nvis = 0, my_vis = 0;             // keys of the current sub-block that all rows see, some row, the lane's
+  int nfull = 0, nvis = 0, my_vis[2] = {0, 0};     // keys of the current sub-block that all rows see, some row, the lane's
   auto enter_segment = [&]() {
     nfull = vis_count(min(w0, d.nq - 1));
     if (RG > 1) nvis = vis_count(min(w0 + 31, d.nq - 1));
-    my_vis = vis_count(q_ld);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) my_vis[q] = vis_count(min(q_row + 16 * q, d.nq - 1));
   };
   auto open_segment = [&](int s, int& sb, int& n) {
     for (n = 0; s < segs; ++s) {
@@ -129,41 +152,42 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
     }
   };
 
-  // ---- staging: a lane moves one 16-byte chunk of ST_N rows (64 columns: eight lanes a row, else sixteen; chunks past
-  // the head size: its last one once more, into columns whose results are not stored).  Rows beyond the sub-block
-  // re-read its last one.
-  constexpr int CHUNKS = HD == 64 ? 8 : 16, ST_ROWS = 64 / CHUNKS, ST_N = SB / ST_ROWS / RG;
+  // ---- staging, straight into LDS: a wavefront loads all blocks of its slab, or (RG > 1) those of one row tile.  Rows beyond
+  // the sub-block re-read its last one.
+  constexpr int ST_N = 2 / RG;                     // row tiles of a wavefront
   const unsigned k_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lk.row * 2);
   const unsigned v_row_bytes = __builtin_amdgcn_readfirstlane((unsigned)d.lv.row * 2);
   const unsigned k_col_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.k * 2)) : k_row_bytes;
   const unsigned v_col_bytes = CYCLIC ? __builtin_amdgcn_readfirstlane((unsigned)(g.b.v * 2)) : v_row_bytes;
-  const int st_row = lane / CHUNKS + rg * (SB / RG), st_chunk = lane % CHUNKS;
-  u32x4 kreg[ST_N], vreg[ST_N];
-  auto load = [&](int s, int j) {
-    if (CYCLIC) start = s;
-    const gptr_t ka = uniform_gptr(reinterpret_cast<const char*>(K) + (start * k_col_bytes + (unsigned)(j * SB) * k_row_bytes));
-    const gptr_t va = uniform_gptr(reinterpret_cast<const char*>(V) + (start * v_col_bytes + (unsigned)(j * SB) * v_row_bytes));
-    const int chunk = min(st_chunk, H / 8 - 1);
-#pragma unroll
-    for (int p = 0; p < ST_N; ++p)
-      kreg[p] = gload_b128(ka, __umul24((unsigned)min(st_row + ST_ROWS * p, rows - 1 - j * SB), k_row_bytes) + 16 * chunk);
-#pragma unroll
-    for (int p = 0; p < ST_N; ++p)
-      vreg[p] = gload_b128(va, __umul24((unsigned)min(st_row + ST_ROWS * p, rows - 1 - j * SB), v_row_bytes) + 16 * chunk);
-  };
+  const int ld_tile = RG > 1 ? rg : 0;
   const unsigned slab = lds_base + kl * RG * SLAB_BYTES;     // (RG > 1: the first of two)
-  const unsigned k_wr = slab + st_row * KLD + 16 * st_chunk, v_wr = slab + V_AT + st_row * VLD + 16 * st_chunk;
-  auto store = [&](unsigned buf) {
-#pragma unroll
-    for (int p = 0; p < ST_N; ++p)
-      *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(k_wr + buf + ST_ROWS * p * KLD)) = kreg[p];
-#pragma unroll
-    for (int p = 0; p < ST_N; ++p)
-      *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)(v_wr + buf + ST_ROWS * p * VLD)) = vreg[p];
+  gptr_t k_from, v_from;                           // of the slab to be loaded
+  int ld_last = 0;
+  auto locate = [&](int s, int j) {
+    if (CYCLIC) start = s;
+    k_from = uniform_gptr(reinterpret_cast<const char*>(K) + (start * k_col_bytes + (unsigned)(j * SB) * k_row_bytes));
+    v_from = uniform_gptr(reinterpret_cast<const char*>(V) + (start * v_col_bytes + (unsigned)(j * SB) * v_row_bytes));
+    ld_last = rows - 1 - j * SB;
   };
-  const int g16 = lane >> 4, j16 = lane & 15;
-  const unsigned k_rd = slab + l32 * KLD + 16 * half;
-  const unsigned v_rd = slab + V_AT + (4 * (g16 >> 1) + (j16 >> 2)) * VLD + (16 * (g16 & 1) + 4 * (j16 & 3)) * 2;
+  constexpr int LOADS = ST_N * KS;                 // of a K or V slab
+  auto load = [&](bool v, unsigned buf) {
+#pragma unroll
+    for (int t = 0; t < ST_N; ++t) {
+      const int tile = ld_tile + t, r = min(16 * tile + (lane >> 2), ld_last);
+      const unsigned off = __umul24(r, v ? v_row_bytes : k_row_bytes) + 16 * ld_chunk;
+      dma_blocks<KS, H>(slab + buf + (v ? V_AT : 0) + tile * KS * BLOCK, v ? v_from : k_from, off, ld_chunk);
+    }
+  };
+  if constexpr (H != HD) {
+    // the columns of Q and the K slabs past the head size are zero for good (those of V are not read)
+    for (int i = threadIdx.x; i < (WAVES + RG) * SB * (HD - H) / 8; i += 64 * WAVES) {
+      const int row = i % SB, x = i / SB, sl = x / ((HD - H) / 8), ch = H % 32 / 8 + x % ((HD - H) / 8);
+      *reinterpret_cast<u32x4*>(lds + (sl < WAVES ? sl * SLAB_BYTES : Q_AT + (sl - WAVES) * V_AT) + ((row >> 4) * KS + H / 32) * BLOCK + (row & 15) * 64 +
+                                16 * (ch ^ block_swap((row & 15) >> 2))) = u32x4{0, 0, 0, 0};
+    }
+  }
+  Blocks16 rd;
+  rd.init(lane, slab);
 
   // rounds of the workgroup's first lane, which has the longest walk (RG > 1: all lanes keep its barriers)
   int rounds = 0;
@@ -184,98 +208,145 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
   open_segment(0, sb, n);
   if (sb < segs) advance(part * LANES + kl, sb, j, n);
   if (sb < segs) {
-    load(sb, j);
+    locate(sb, j);
+    load(false, 0);
+    load(true, 0);
     enter_segment();
   }
 
-  f32x16 o[CT];
+  f32x4 o[HT][2];
 #pragma unroll
-  for (int t = 0; t < CT; ++t) o[t] = zero16();
-  float m_lane = -INFINITY, m_ref = -INFINITY, l_run = 0.f;
+  for (int t = 0; t < HT; ++t) o[t][0] = o[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_lane[2] = {-INFINITY, -INFINITY}, m_ref[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
   if (!GRID && g.acc && part == 0 && kl == 0) {
     // the first wavefront continues the stored partial (rows past nq: the last row's, never stored)
-    const int64_t row = (int64_t)head * d.nq + q_ld;
-    m_lane = m_ref = in.m[row] / d.scale;
-    l_run = half == 0 ? in.l[row] : 0.f;
-    const float* np = in.N + row * H + 4 * half;
 #pragma unroll
-    for (int t = 0; t < CT; ++t)
+    for (int q = 0; q < 2; ++q) {
+      const int64_t row = (int64_t)head * d.nq + min(q_row + 16 * q, d.nq - 1);
+      m_lane[q] = m_ref[q] = in.m[row] / d.scale;
+      l_run[q] = grp == 0 ? in.l[row] : 0.f;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (32 * t + 8 * q + 4 * half >= H) continue;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(np + 32 * t + 8 * q);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[t][4 * q + e] = v[e];
-      }
+      for (int t = 0; t < HT; ++t) o[t][q] = *reinterpret_cast<const f32x4*>(in.N + row * H + 16 * t + 4 * grp);
+    }
   }
 
-  auto compute = [&](unsigned buf) {
-    const unsigned k_at = k_rd + buf, v_at = v_rd + buf;
-    const int k0 = j * SB + (CYCLIC && sb > shift_from);
-    if (RG > 1 && k0 >= nvis) return;
-    f32x16 s = zero16();
+  bool more = false;                               // there is a next slab
+  auto wait_behind = [&] {
+    if (more) wait_vmem<LOADS>(); else wait_vmem_all();
+  };
+  if constexpr (Q_LDS) {
+    if (sb < segs) wait_vmem<2 * LOADS>(); else wait_vmem_all();     // this wavefront's share, then everybody's
+    __syncthreads();
 #pragma unroll
-    for (int x = 0; x < KS; ++x) s = mma(lds_load_b128(k_at + 32 * x), qf[x], s);
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int x = 0; x < KS; ++x) qf[x][q] = lds_load_b128(rd.nat - slab + lds_base + Q_AT + ((2 * rg + q) * KS + x) * BLOCK);
+  }
+  // S^T and O^T in tiles of 16 x 16, as in fwd_block.  behind: called when the K slab has been read.
+  auto compute = [&](unsigned buf, auto&& behind) {
+    const unsigned k_at = rd.nat + buf, v_e = rd.tr_e + buf + V_AT, v_o = rd.tr_o + buf + V_AT;
+    const int k0 = j * SB + (CYCLIC && sb > shift_from);
+    f32x4 s[2][2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) s[k][0] = s[k][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < KS; ++x)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const bf16x8 a = lds_load_b128(k_at + (k * KS + x) * BLOCK);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) s[k][q] = mma16(a, qf[x][q], s[k][q]);
+      }
+    behind();
     if (k0 + SB > nfull) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (k0 + 8 * (r >> 2) + 4 * half + (r & 3) >= my_vis) s[r] = -INFINITY;
-    }
-    float mx = s[0];
+      for (int q = 0; q < 2; ++q)
 #pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-    m_lane = fmaxf(m_lane, mx);
-    if (__builtin_amdgcn_ballot_w64((m_lane - m_ref) * c > kRescaleThreshold) != 0) {
+        for (int r = 0; r < 8; ++r)
+          if (k0 + 16 * (r >> 2) + 4 * grp + (r & 3) >= my_vis[q]) s[r >> 2][q][r & 3] = -INFINITY;
+    }
+    bool grow = false;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      float mx = m_lane[q];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) mx = fmaxf(mx, s[r >> 2][q][r & 3]);
+      m_lane[q] = mx;
+      grow |= (mx - m_ref[q]) * c > kRescaleThreshold;
+    }
+    if (__builtin_amdgcn_ballot_w64(grow) != 0) {
       asm volatile("" ::: "memory");               // (a real branch, as in fwd_block)
-      const float m_row = fmaxf(m_lane, __shfl_xor(m_lane, 32, 64));
-      const float m_use = (m_row == -INFINITY) ? 0.f : m_row;
-      const float alpha = fast_exp2((m_ref - m_use) * c);
-      m_ref = m_row;
-      l_run *= alpha;
 #pragma unroll
-      for (int t = 0; t < CT; ++t)
+      for (int q = 0; q < 2; ++q) {
+        const float m_row = row_max(m_lane[q]);
+        const float m_use = (m_row == -INFINITY) ? 0.f : m_row;
+        const float alpha = fast_exp2((m_ref[q] - m_use) * c);
+        m_ref[q] = m_row;
+        l_run[q] *= alpha;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
+        for (int t = 0; t < HT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o[t][q][r] *= alpha;
+      }
     }
-    const float mc = (m_ref == -INFINITY) ? 0.f : m_ref * c;
-    float psum = 0.f;
     bf16x8 pb[2];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float p = fast_exp2(fmaf(s[r], c, -mc));
-      psum += p;
-      pb[r >> 3][r & 7] = (bf16_t)p;
-    }
-    l_run += psum;
+    for (int q = 0; q < 2; ++q) {
+      const float mc = (m_ref[q] == -INFINITY) ? 0.f : m_ref[q] * c;
+      float psum = 0.f;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int t = 0; t < CT; ++t) {
-        const unsigned at = v_at + 16 * u * VLD + 64 * t;
-        o[t] = mma(lds_load_tr(at, at + 8 * VLD), pb[u], o[t]);
+      for (int r = 0; r < 8; ++r) {
+        const float p = fast_exp2(fmaf(s[r >> 2][q][r & 3], c, -mc));
+        psum += p;
+        pb[q][r] = (bf16_t)p;
       }
+      l_run[q] += psum;
+    }
+    if constexpr (RG == 1) wait_behind();   // V has arrived
+#pragma unroll
+    for (int t = 0; t < HT; ++t) {
+      const unsigned at = (t & 1 ? v_o : v_e) + (t >> 1) * BLOCK;
+      const bf16x8 a = lds_load_tr(at, at + KS * BLOCK);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) o[t][q] = mma16(a, pb[q], o[t][q]);
+    }
   };
   if constexpr (RG == 1) {
+    // One slab a wavefront: the next K goes where the last one was read from while the exponentials and V P^T are under way,
+    // the next V behind those.  (In flight at a time: V and the next K, the next K and V.)
+    if (sb < segs) wait_vmem<LOADS>();             // (K)
     while (sb < segs) {
       int nsb = sb, nj = j, nn = n;
       advance(stride, nsb, nj, nn);
-      store(0);
-      if (nsb < segs) load(nsb, nj);               // the next slab
-      compute(0);
-      if (!CYCLIC && nsb != sb && nsb < segs) enter_segment();
+      more = nsb < segs;
+      if (more) locate(nsb, nj);
+      compute(0, [&] {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (more) load(false, 0);
+      });
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (more) {
+        load(true, 0);
+        wait_vmem<LOADS>();
+      }
+      if (!CYCLIC && nsb != sb && more) enter_segment();
       sb = nsb; j = nj; n = nn;
     }
   } else {
-    if (sb < segs) store(0);
+    wait_vmem_all();
     __syncthreads();
     unsigned buf = 0;
     for (int r = 0; r < rounds; ++r) {
       int nsb = sb, nj = j, nn = n;
       advance(stride, nsb, nj, nn);
-      const bool more = nsb < segs;
-      if (more) load(nsb, nj);
-      if (sb < segs) compute(buf);
-      if (more) store(SLAB_BYTES - buf);
+      more = nsb < segs;
+      if (more) {
+        locate(nsb, nj);
+        load(false, SLAB_BYTES - buf);
+        load(true, SLAB_BYTES - buf);
+      }
+      if (sb < segs && j * SB + (CYCLIC && sb > shift_from) < nvis) compute(buf, [] {});
+      wait_vmem_all();
       __syncthreads();
       if (!CYCLIC && more && nsb != sb) enter_segment();
       sb = nsb; j = nj; n = nn;
@@ -284,63 +355,68 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
   }
 
   // ---- the wavefronts' (N, m, l) become one, as partials of one query block do (Alg. 2)
-  const float m_row = fmaxf(m_lane, __shfl_xor(m_lane, 32, 64));
-  const float f = (m_row == -INFINITY) ? 0.f : fast_exp2((m_ref - m_row) * c);
-  const float l_row = (l_run + __shfl_xor(l_run, 32, 64)) * f;
-  float* const xm = reinterpret_cast<float*>(lds + STAT) + rg * 32 + l32;
+  // (the lanes of a wavefront's first 32 hold its rows' sums in turn; row_pair hands all lanes those of their two rows)
+  float* const xm = reinterpret_cast<float*>(lds + STAT) + rg * 32 + (lane & 31);
   float* const xl = xm + WAVES * 32;
-  if (half == 0) {
-    xm[kl * BM] = m_row;
-    xl[kl * BM] = l_row;
+  float m_row[2], l_row[2], f[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    m_row[q] = row_max(m_lane[q]);
+    f[q] = (m_row[q] == -INFINITY) ? 0.f : fast_exp2((m_ref[q] - m_row[q]) * c);
+    l_row[q] = row_sum(l_run[q]) * f[q];
+  }
+  if (lane < 32) {
+    xm[kl * BM] = m_row[grp & 1];
+    xl[kl * BM] = l_row[grp & 1];
   }
   __syncthreads();
-  float mk[LANES], lk[LANES], m_new = -INFINITY;
+  f32x4* const x = reinterpret_cast<f32x4*>(lds);
+  const bool norm = g.norm != 0;
+  float m_new = -INFINITY, l_tot = 0.f, use[2], fn[2] = {0.f, 0.f};
 #pragma unroll
-  for (int k = 0; k < LANES; ++k) {
-    mk[k] = xm[k * BM];
-    lk[k] = xl[k * BM];
-    m_new = fmaxf(m_new, mk[k]);
+  for (int k = 0; k < LANES; ++k) m_new = fmaxf(m_new, xm[k * BM]);
+  const float m_use = m_new == -INFINITY ? 0.f : m_new;        // (2^-inf = 0 for the wavefronts that saw nothing)
+  row_pair(m_use, use);
+  if (norm || kl == 0) {
+#pragma unroll
+    for (int k = 0; k < LANES; ++k) l_tot += xl[k * BM] * fast_exp2((xm[k * BM] - m_use) * c);
+    row_pair(l_tot > 0.f ? 1.0f / l_tot : 0.f, fn);
   }
-  const float m_use = m_new == -INFINITY ? 0.f : m_new;      // (2^-inf = 0 for the wavefronts that saw nothing)
-  float l_tot = 0.f;
-#pragma unroll
-  for (int k = 0; k < LANES; ++k) l_tot += lk[k] * fast_exp2((mk[k] - m_use) * c);
-  const float a = f * fast_exp2((m_row - m_use) * c);
-  const bool norm = g.norm != 0, ok = q_row < d.nq;
-  const int64_t row = GRID && norm ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, q_row)
-                                   : (int64_t)head * d.nq + q_row;
-  const int64_t o_at = GRID && norm ? head * d.lo.head + row_blk * g.b.o + q_row * d.lo.row : row * H;
-  if (kl == 0 && half == 0 && ok) {
+  if (kl == 0 && lane < 32 && w0 + lane < d.nq) {
+    const int r = w0 + lane;
+    const int64_t row = GRID && norm ? (int64_t)head * g.b.side * d.nq + grid_token(g.b, d.nq, row_blk, r) : (int64_t)head * d.nq + r;
     if (norm) m_out[row] = l_tot > 0.f ? m_new * d.scale + logf(l_tot) : -INFINITY;
     else {
       m_out[row] = m_new * d.scale;                // -inf stays -inf (scale > 0)
       l_out[row] = l_tot;
     }
   }
-  // Every wavefront leaves its pieces of four columns, [wavefront][piece][lane], and adds up and stores 16 / LANES of its
-  // row group's.
-  f32x4* const x = reinterpret_cast<f32x4*>(lds);
-  const float fn = l_tot > 0.f ? 1.0f / l_tot : 0.f;
 #pragma unroll
-  for (int t = 0; t < CT; ++t)
+  for (int q = 0; q < 2; ++q) {
+    const float a = f[q] * fast_exp2((m_row[q] - use[q]) * c);
+    // Every wavefront leaves its pieces of four columns, [wavefront][piece][lane], and adds up and stores 16 / LANES of its
+    // row group's.
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      x[(wave * 16 + t * 4 + q) * 64 + lane] = f32x4{o[t][4 * q] * a, o[t][4 * q + 1] * a, o[t][4 * q + 2] * a, o[t][4 * q + 3] * a};
+    for (int t = 0; t < HT; ++t)
+      x[(wave * 16 + 2 * t + q) * 64 + lane] = f32x4{o[t][q][0] * a, o[t][q][1] * a, o[t][q][2] * a, o[t][q][3] * a};
+  }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 16 / LANES; ++i) {
-    const int piece = kl + LANES * i, col = 32 * (piece >> 2) + 8 * (piece & 3) + 4 * half;
-    if (piece >= 4 * CT || col >= H || !ok) continue;
+    const int piece = kl + LANES * i, q = piece & 1, col = 16 * (piece >> 1) + 4 * grp, r = q_row + 16 * q;   // (LANES is even)
+    if (piece >= 2 * HT || r >= d.nq) continue;
     f32x4 v = x[(rg * 16 + piece) * 64 + lane];
 #pragma unroll
     for (int k = 1; k < LANES; ++k) {
       const f32x4 w = x[((k * RG + rg) * 16 + piece) * 64 + lane];
       v[0] += w[0]; v[1] += w[1]; v[2] += w[2]; v[3] += w[3];
     }
+    const int64_t o_at = GRID && norm ? head * d.lo.head + row_blk * g.b.o + r * d.lo.row : ((int64_t)head * d.nq + r) * H;
     if (norm) {
+      const float by = q ? fn[1] : fn[0];
       bf16x4 b;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) b[e] = (bf16_t)(v[e] * fn);
+      for (int e = 0; e < 4; ++e) b[e] = (bf16_t)(v[e] * by);
       *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(O_part) + o_at + col) = b;
     } else {
       *reinterpret_cast<f32x4*>(O_part + o_at + col) = v;
@@ -351,9 +427,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
 template <int HR, int RG, int GRID>
 hipError_t go(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
               float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
-  if (ph == PREPARE) return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_small_kernel<HR, RG, GRID>), LDS_BYTES);
+  if (ph == PREPARE) return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_small_kernel<HR, RG, GRID>), lds_bytes(RG, padded_head(HR)));
   const dim3 grid(xcd_grid(d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * ((d.nq + 32 * RG - 1) / (32 * RG))));
-  A2D_LAUNCH((fwd_small_kernel<HR, RG, GRID>), grid, dim3(64 * WAVES), LDS_BYTES, s, d, g, (const bf16_t*)Q,
+  A2D_LAUNCH((fwd_small_kernel<HR, RG, GRID>), grid, dim3(64 * WAVES), lds_bytes(RG, padded_head(HR)), s, d, g, (const bf16_t*)Q,
              (const bf16_t*)K, (const bf16_t*)V, O_part, m, l, in);
   return hipGetLastError();
 }

@@ -219,6 +219,30 @@ __device__ __forceinline__ void dma_blocks(unsigned at, gptr_t base, unsigned by
   });
 }
 
+// maximum, sum over the four lanes of a row (16 apart).  The lane groups are exchanged in pairs by the vector ALU: shuffles
+// through LDS are four times the latency.
+template <class F>
+__device__ __forceinline__ float row_reduce(float x, F&& f) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned a0 = a[0], a1 = a[1];             // (a bit_cast of an element itself is one of the first)
+  const unsigned w = __builtin_bit_cast(unsigned, f(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1)));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  const unsigned b0 = b[0], b1 = b[1];
+  return f(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
+}
+__device__ __forceinline__ float row_max(float x) { return row_reduce(x, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float row_sum(float x) { return row_reduce(x, [](float a, float b) { return a + b; }); }
+
+// of lane i's rows i % 16 and i % 16 + 16: what lanes of row i % 32 hold
+__device__ __forceinline__ void row_pair(float x, float (&of)[2]) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned a0 = a[0], a1 = a[1];
+  of[0] = __builtin_bit_cast(float, a0);
+  of[1] = __builtin_bit_cast(float, a1);
+}
+
 // Stores 16 rows of a transposed accumulator of 16 x 16 tiles (lane j + 16 g: columns 16 ht + 4 g + 0..3 of row j, in each of
 // NT row tiles; here tile t), times `mul` of the lane's row, to out, out + row, ..; `n` of the rows exist.  They
 // pass through LDS (`area`, acc_area bytes of the wavefront's own), so that an instruction stores whole rows: a lane's pieces

@@ -2,6 +2,7 @@
 offset within a tile, against fp64 on the GPU."""
 import pytest
 
+import test_gpu_small_rows as forward
 from test_gpu_bwd_routes import _check
 
 pytestmark = pytest.mark.gpu
@@ -22,3 +23,20 @@ def test_backward_tile_edges(case, keep):
     assert route["keys"] == 256, route
     assert ("bwd_dq_ds_kernel" in route["kernels"]) == (keep and H == 128), route
     _check(case, keep)
+
+
+# the same with the rows of a workgroup that the route has to have
+FORWARD = [(rows, (heads, heads, nq, nkv, H, causal, q_off, None, False, 2))
+           for rows, heads, nq, nkv, H, causal, q_off in [
+               (32, 2, 15, 17, 64, True, 2), (32, 3, 17, 47, 80, True, 30), (32, 2, 47, 271, 96, True, 223), (32, 1, 49, 303, 128, True, 257),
+               (64, 150, 47, 129, 64, True, 81), (64, 40, 271, 303, 80, True, 33), (64, 40, 273, 287, 96, True, 15), (64, 40, 289, 305, 128, True, 16),
+               (128, 40, 783, 801, 64, True, 17), (128, 80, 783, 801, 96, True, 15), (128, 80, 1009, 1041, 128, True, 31),
+               (256, 64, 783, 801, 80, True, 33), (256, 64, 1009, 1041, 128, True, 17)]]
+
+
+@pytest.mark.parametrize("rows,case", FORWARD, ids=lambda c: "%dx%dH%d_%d" % (c[2], c[3], c[4], c[6]) if isinstance(c, tuple) else c)
+def test_forward_tile_edges(rows, case):
+    from paper_2503_15758_amd import binding as a2d
+    heads, _, nq, nkv, H, causal, q_off = case[:7]
+    assert a2d.tile_route(heads, nq, nkv, H, causal=causal, q_off=q_off)["rows"] == rows
+    forward.test_small_rows(case)
