@@ -3,16 +3,23 @@
 // fp32 throughout: v_mfma_f32_16x16x4_f32 multiplies and accumulates in fp32 (2048 flop in 32 cycles
 // of a SIMD, 157 TFLOP/s over the chip - twice what unpacked vector FMAs reach).
 //
-// What bounds them: the fp32 MFMA rate where there are many rows (78 % of it at 16 x 4096 x 4096, H = 128); at 16 x 700 x
-// 900 prologues, merges, uneven walks of a few steps and bank conflicts (50 % of the cycles in the matrix units).  A step of 16 keys (queries)
+// What bounds them: the fp32 MFMA rate where there are many rows (82 % of it at 16 x 4096 x 4096, H = 128, 84 % in the backward); at
+// 16 x 700 x 900 prologues, merges and uneven walks of a few steps (58 %).  A step of 16 keys (queries)
 // against 16 rows is H / 4 MFMAs of 32 cycles per contraction, on 8 KiB of operands at H = 128.
 //   - The backward's dQ and dK/dV workgroups go out in one launch, so that the end of the one kind overlaps the start of
 //     the other (two launches, dQ leaving delta for dK/dV: 2 x 128 x 128, H = 64 13.4 -> 7.1 us; 8 x 256 x 900, H = 80
 //     39 -> 26; 16 x 700 x 900, H = 96, causal 109 -> 100).
-//   - Operands of a step come in by whole rows (16 lanes on 256 bytes), one step ahead, and pass through
-//     a tile in LDS that is the wavefront's own (no barriers): a contraction over H needs lane = row, and
-//     loading that from memory is 64 separate accesses per instruction, which kept the matrix units
+//   - Operands of a step pass through a tile in LDS that is the wavefront's own (no barriers): a contraction over H needs
+//     lane = row, and loading that from memory is 64 separate accesses per instruction, which kept the matrix units
 //     half idle (16 heads x 1024 x 1024, H = 96: 6.4e7 cache accesses for 1.2 GB, 50 % MFMA busy).
+//   - The backward loads its tiles straight into LDS, each as soon as the last read of the one before is through: V behind dP, K
+//     behind half of dQ; Q behind half of dK, dO behind most of dV.  By way of registers, one step ahead, the rows of Q, dO and O took
+//     96 of them at H = 128 and left room for two workgroups a compute unit; now three fit up to H = 96 (at H = 96 where delta is read),
+//     whose prologues, exponentials and waits are covered by the others' MFMAs.  us, before -> now: H = 96 16 x 1024 x 1024
+//     213 -> 187, 16 x 700 x 900 150 -> 129, causal 99.6 -> 92, 16 x 256 x 256 20.8 -> 18.3; H = 128 12 x 300 x 300 causal 31.2 -> 25,
+//     16 x 4096 x 4096 3841 -> 3648; H = 64 2 x 128 x 128 7.0 -> 6.8; 170 shapes of 32 to 2500 rows 1.09 times as fast in the mean, none
+//     by more than 1 % slower.  (8 x 256 x 900, H = 80, 29.5 -> 31: long dQ walks with two neighbours.  The same stream of MFMAs with
+//     staging through registers gave nothing: it is the third workgroup and the registers that do.)
 //   - A wavefront owns 16 * RT rows and walks blocks of 16 keys (queries); the KL wavefronts of a
 //     workgroup own the SAME rows and take every KL-th block of the walk ("key lanes"), because fp32
 //     tiles are small: it is the walk that has to be spread over the SIMDs.  Their results are
@@ -24,16 +31,15 @@
 //     contracts the keys r, 4 + r, 8 + r, 12 + r.
 //   - Contractions over H read rows "naturally": lane (row l15, group g) reads the 16 bytes
 //     16 y + 4 g .. + 3 of its row, which serve four MFMAs (the contraction index may be permuted as
-//     long as both operands use the same permutation).  Tile rows are padded by 16 bytes (the backward kernels'
-//     LDS cycles are 28 % bank conflicts all the same, at 21 % of the time in LDS).
+//     long as both operands use the same permutation).
 //   - Contractions over rows need the transposed operand (lane = column): lane l15 loads 16 bytes of
 //     row 4 g + r, columns 64 G + 4 l15 + t, and MFMA t of the group takes one of the four, i.e. row
 //     i of its result is column 64 G + 4 i + t.  A lane then holds 16 consecutive columns of the
 //     result (64 G + 16 g + 4 r + t), stored as four 16-byte pieces.  (H = 96 and 80 end in a group of
 //     32 or 16 columns with 8- or 4-byte pieces: Cols<H> below.)
 // Measured against the vector-ALU kernels of a2d_generic.hip: 16 heads x 700 x 900, H = 96, causal,
-// backward call 1034 -> 100 us; 2 heads x 128 x 128, H = 64, forward 29 -> 5.2 us; 16 heads x 4096 x 4096, H = 128: forward
-// 1.07 ms (129 TFLOP/s, 82 % of the fp32 matrix peak), backward 3.87 ms (124 TFLOP/s executed).
+// backward call 1034 -> 92 us; 2 heads x 128 x 128, H = 64, forward 29 -> 5.0 us; 16 heads x 4096 x 4096, H = 128: forward
+// 1.07 ms (129 TFLOP/s, 82 % of the fp32 matrix peak), backward 3.65 ms (132 TFLOP/s executed).
 #include <cmath>
 
 #include "a2d_mfma.hpp"
@@ -42,6 +48,8 @@ namespace a2d {
 namespace {
 
 using mfma::gptr_t;
+using mfma::row_max;
+using mfma::row_sum;
 using mfma::static_for;
 using mfma::uniform_gptr;
 using mfma::xcd_grid;
@@ -87,13 +95,6 @@ struct Cols {
       b[0] = w[0]; b[1] = w[1];
     }
     if constexpr (REST == 16) b[0] = gload<float>(base, off + 256 * N4 + 4 * l15);
-  }
-  __device__ __forceinline__ float dot(const Cols& o) const {
-    float t = 0.f;
-#pragma unroll
-    for (int i = 0; i < H / 16; ++i)
-      t = fmaf(i < 4 * N4 ? a[i / 4][i % 4] : b[i - 4 * N4], i < 4 * N4 ? o.a[i / 4][i % 4] : o.b[i - 4 * N4], t);
-    return t;
   }
   template <int T>
   __device__ __forceinline__ float get() const {
@@ -141,6 +142,45 @@ struct Tile {
     if constexpr (REST == 16) c.b[0] = lload<float>(col - 12 * l15 + r * LD + 256 * N4);
   }
 };
+
+// A wavefront's tile of 16 rows that is loaded straight into LDS (see mfma::Blocks16: here a block is 16 rows x 16 columns).
+// Blocks lie 64 bytes more than their size apart, so that the columns' reads, which take 64 bytes of four blocks at a time,
+// meet every bank once too.
+template <int H>
+struct Blocks {
+  static constexpr int N = H / 16, N4 = Cols<H>::N4, REST = Cols<H>::REST, STRIDE = mfma::BLOCK + 64, BYTES = N * STRIDE;
+  lds_t base, nat, col, rest;                // + this lane's place for natural rows, for columns (row 4 g), for the last ones
+  __device__ __forceinline__ void init(lds_t b, int l15, int g4) {
+    const int swap = mfma::block_swap(g4);
+    base = b;
+    nat = b + l15 * 64 + 16 * (g4 ^ mfma::block_swap(l15 >> 2));
+    col = b + (l15 >> 2) * STRIDE + 256 * g4 + 16 * ((l15 & 3) ^ swap);
+    rest = b + 4 * N4 * STRIDE + 256 * g4 +
+           (REST == 32 ? (l15 >> 3) * STRIDE + 16 * ((l15 >> 1 & 3) ^ swap) + 8 * (l15 & 1) : 16 * ((l15 >> 2) ^ swap) + 4 * (l15 & 3));
+  }
+  // lane i's row i >> 2 of the tile is at byte `off` of from; + chunk(i)
+  static __device__ __forceinline__ unsigned chunk(int lane) { return 16 * ((lane & 3) ^ mfma::block_swap(lane >> 4)); }
+  __device__ __forceinline__ void load(gptr_t from, unsigned off) const {
+    static_for<0, N>([&](auto Y) {
+      constexpr int y = decltype(Y)::value;
+      mfma::dma_b128<64 * y>((unsigned)(uintptr_t)base + y * STRIDE, from, off);
+    });
+  }
+  __device__ __forceinline__ f32x4 row(int y) const { return lload<f32x4>(nat + y * STRIDE); }
+  // what this lane has loaded
+  __device__ __forceinline__ f32x4 own(int y, int lane) const { return lload<f32x4>(base + y * STRIDE + 16 * lane); }
+  __device__ __forceinline__ void cols(Cols<H>& c, int r) const {
+#pragma unroll
+    for (int G = 0; G < N4; ++G) c.a[G] = lload<f32x4>(col + 64 * r + 4 * G * STRIDE);
+    if constexpr (REST == 32) {
+      const f32x2 w = lload<f32x2>(rest + 64 * r);
+      c.b[0] = w[0]; c.b[1] = w[1];
+    }
+    if constexpr (REST == 16) c.b[0] = lload<float>(rest + 64 * r);
+  }
+};
+// before a load into a tile that has been read
+__device__ __forceinline__ void reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // D layout of the transposed results: acc[T][r] is column col<T>(g, r) of the lane's row (l15)
 template <int H>
@@ -245,6 +285,33 @@ __device__ __forceinline__ void contract_tile(Out<H>& acc, const Tile<H>& a, con
   });
 }
 
+// The backward's two contractions over H of a step, s = rows of `a` . fa and d = rows of `b` . fb, as one stream of MFMAs: the
+// tiles' pieces are requested two ahead of their use across the seam (`seam()`: before b's first), and what `between(y)` does
+// behind the MFMAs of d's piece y (s is complete from y = 1 on) runs while they do.
+template <int H, class S, class F>
+__device__ __forceinline__ void dot_two(f32x4& s, f32x4& d, const Blocks<H>& a, const Nat<H>& fa, const Blocks<H>& b,
+                                        const Nat<H>& fb, S&& seam, F&& between) {
+  constexpr int N = H / 16;
+  f32x4 acc[2][2] = {{zero4(), zero4()}, {zero4(), zero4()}}, ring[2] = {a.row(0), a.row(1)};
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<0, 2 * N>([&](auto I) {
+    constexpr int i = decltype(I)::value, of = i / N, y = i % N, next = i + 2;
+    const f32x4 v = ring[i & 1];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[of][e & 1] = mma4(v[e], (of ? fb : fa).v[y][e], acc[of][e & 1]);
+    if constexpr (next == N) seam();
+    if constexpr (next < 2 * N) ring[i & 1] = next < N ? a.row(next) : b.row(next - N);
+    if constexpr (i == N + 1) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[r] = acc[0][0][r] + acc[0][1][r];
+    }
+    if constexpr (of == 1) between(std::integral_constant<int, y>{});
+    __builtin_amdgcn_sched_barrier(0);
+  });
+#pragma unroll
+  for (int r = 0; r < 4; ++r) d[r] = acc[1][0][r] + acc[1][1][r];
+}
+
 // Sum of N results over the KL wavefronts of the workgroup, by halves: the upper half writes, the
 // lower half adds; wavefront 0 ends up with the total.  xch: KL / 2 areas of N * 64 16-byte pieces.
 template <int N, class Get>
@@ -314,24 +381,6 @@ __device__ __forceinline__ int vis_count(const a2d_tile_desc& d, const SegList& 
   if (!d.causal) return g.seg[s].rows;
   const int64_t v = (int64_t)i + g.seg[s].rel + 1;
   return v <= 0 ? 0 : (v < g.seg[s].rows ? (int)v : g.seg[s].rows);
-}
-
-// max / sum over the four groups of a row (lanes l15 + 16 g)
-__device__ __forceinline__ float row_max(float v) {
-  v = fmaxf(v, __shfl_xor(v, 16, 64));
-  return fmaxf(v, __shfl_xor(v, 32, 64));
-}
-__device__ __forceinline__ float row_sum(float v) {
-  v += __shfl_xor(v, 16, 64);
-  return v + __shfl_xor(v, 32, 64);
-}
-
-// sum over the 16 lanes of a group, left in all of them (see lane_swap)
-__device__ __forceinline__ float col_sum(float v) {
-  v += mfma::lane_swap<0xB1>(v);
-  v += mfma::lane_swap<0x4E>(v);
-  v += mfma::lane_swap<0x141>(v);
-  return v + mfma::lane_swap<0x140>(v);
 }
 
 // ------------------------------------------------------------------ forward
@@ -491,16 +540,16 @@ __device__ __forceinline__ void dq_rows(int id, char* const smem, const a2d_tile
   const unsigned k_row = (unsigned)d.lk.row * 4, v_row = (unsigned)d.lv.row * 4;
   const int q_row = q0 + l15, q_ld = min(q_row, d.nq - 1);
 
-  Nat<H> qf[1], gf[1], of;
-  qf[0].load(uniform_gptr(Q + (int64_t)head * d.lq.head), q_ld, (unsigned)d.lq.row * 4, g4);
-  gf[0].load(uniform_gptr(dO + (int64_t)head * d.ldo.head), q_ld, (unsigned)d.ldo.row * 4, g4);
+  Nat<H> qf, gf, of;
+  qf.load(uniform_gptr(Q + (int64_t)head * d.lq.head), q_ld, (unsigned)d.lq.row * 4, g4);
+  gf.load(uniform_gptr(dO + (int64_t)head * d.ldo.head), q_ld, (unsigned)d.ldo.row * 4, g4);
   of.load(uniform_gptr(O + (int64_t)head * d.lo.head), q_ld, (unsigned)d.lo.row * 4, g4);     // for delta only
   const float lse_i = q_row < d.nq ? lse[(int64_t)head * d.nq + q_ld] : -INFINITY;
   float del = 0.f;
 #pragma unroll
   for (int y = 0; y < H / 16; ++y)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) del = fmaf(gf[0].v[y][e], of.v[y][e], del);
+    for (int e = 0; e < 4; ++e) del = fmaf(gf.v[y][e], of.v[y][e], del);
   del = row_sum(del);
 
   const int blk_last = min(q0 + BLK, d.nq) - 1;
@@ -510,40 +559,51 @@ __device__ __forceinline__ void dq_rows(int id, char* const smem, const a2d_tile
   w.advance(part * KL + kl, g, seg_blocks);
   Out<H> dq;
   dq.zero();
-  Tile<H> kt, vt;
-  kt.init((lds_t)smem + 2 * kl * Tile<H>::BYTES, l15, g4);
-  vt.init((lds_t)smem + (2 * kl + 1) * Tile<H>::BYTES, l15, g4);
-  Cols<H> kc[4], vc[4];
-  auto load = [&](const Walk& x) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const unsigned row = x.start + min(x.j * BLK + 4 * g4 + r, x.rows - 1);
-      kc[r].load(kb, row, k_row, l15);
-      vc[r].load(vb, row, v_row, l15);
-    }
+  Blocks<H> kt, vt;
+  kt.init((lds_t)smem + 2 * kl * Blocks<H>::BYTES, l15, g4);
+  vt.init((lds_t)smem + (2 * kl + 1) * Blocks<H>::BYTES, l15, g4);
+  const auto load = [&](const Blocks<H>& to, gptr_t from, unsigned row_bytes) {
+    to.load(from, __umul24((unsigned)(w.start + min(w.j * BLK + (lane >> 2), w.rows - 1)), row_bytes) + Blocks<H>::chunk(lane));
   };
+  if (w.s < g.n) {
+    load(kt, kb, k_row);
+    load(vt, vb, v_row);
+  }
   int vis_s = -1, my_vis = 0;                         // keys of sub-block vis_s that this lane's row sees
-  if (w.s < g.n) load(w);
+  Cols<H> ring[2];
   while (w.s < g.n) {
     const int k0 = w.j * BLK;
     if (w.s != vis_s) { vis_s = w.s; my_vis = vis_count(d, g, q_ld, w.s); }
-    kt.store(kc, l15);
-    vt.store(vc, l15);
-    w.advance(lanes, g, seg_blocks);
-    if (w.s < g.n) load(w);
-    __builtin_amdgcn_sched_barrier(0);
-    f32x4 sx[1], dx[1];
-    dot_rows<H, 1>(sx, kt, qf);
-    dot_rows<H, 1>(dx, vt, gf);
-    const f32x4 sc = sx[0];
-    f32x4 ds = dx[0];
+    f32x4 p, ds;
+    mfma::wait_dma();
+    dot_two<H>(p, ds, kt, qf, vt, gf, [] {}, [&](auto Y) {
+      constexpr int y = decltype(Y)::value;
+      if constexpr (y == 1 || y == 2) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const bool vis = lse_i != -INFINITY && k0 + 4 * g4 + r < my_vis;
-      const float p = vis ? fast_exp2(fmaf(sc[r], d.scale, -lse_i) * kLog2e) : 0.f;
-      ds[r] = p * (ds[r] - del);
-    }
-    contract_tile(dq, kt, ds, l15);
+        for (int r = 2 * y - 2; r < 2 * y; ++r) {
+          const bool vis = lse_i != -INFINITY && k0 + 4 * g4 + r < my_vis;
+          p[r] = vis ? fast_exp2(fmaf(p[r], d.scale, -lse_i) * kLog2e) : 0.f;
+        }
+      }
+      if constexpr (y >= H / 16 - 2) kt.cols(ring[y - (H / 16 - 2)], y - (H / 16 - 2));
+    });
+    // the next tiles come in as soon as the pieces of these have been read: V behind dP, K behind half of the last contraction
+    reads_done();
+    w.advance(lanes, g, seg_blocks);
+    const bool more = w.s < g.n;
+    if (more) load(vt, vb, v_row);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) ds[r] = p[r] * (ds[r] - del);
+    static_for<0, 4>([&](auto R) {
+      constexpr int r = decltype(R)::value;
+      dq.contract(ring[r & 1], ds[r]);
+      if constexpr (r < 2) kt.cols(ring[r & 1], r + 2);
+      if constexpr (r == 2) {
+        reads_done();
+        if (more) load(kt, kb, k_row);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
   }
   merge_lanes<H / 16>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& { return dq.acc[i]; });
   if (kl != 0) return;
@@ -581,9 +641,9 @@ __device__ __forceinline__ void dkdv_keys(int id, char* const smem, const a2d_ti
   const unsigned q_row = (unsigned)d.lq.row * 4, g_row = (unsigned)d.ldo.row * 4, o_row = (unsigned)d.lo.row * 4;
   const unsigned q_head = (unsigned)d.lq.head * 4, g_head = (unsigned)d.ldo.head * 4, o_head = (unsigned)d.lo.head * 4;
 
-  Nat<H> kf[1], vf[1];
-  kf[0].load(uniform_gptr(K + (int64_t)head * d.lk.head), k_ld, (unsigned)d.lk.row * 4, g4);
-  vf[0].load(uniform_gptr(V + (int64_t)head * d.lv.head), k_ld, (unsigned)d.lv.row * 4, g4);
+  Nat<H> kf, vf;
+  kf.load(uniform_gptr(K + (int64_t)head * d.lk.head), k_ld, (unsigned)d.lk.row * 4, g4);
+  vf.load(uniform_gptr(V + (int64_t)head * d.lv.head), k_ld, (unsigned)d.lv.row * 4, g4);
 
   // first query row that sees this lane's key, and the first that sees any of the block's keys
   auto first_row = [&](int s, int k) -> int {
@@ -606,57 +666,95 @@ __device__ __forceinline__ void dkdv_keys(int id, char* const smem, const a2d_ti
   Out<H> dk, dv;
   dk.zero();
   dv.zero();
-  Tile<H> qt, gt;
-  qt.init((lds_t)smem + 2 * kl * Tile<H>::BYTES, l15, g4);
-  gt.init((lds_t)smem + (2 * kl + 1) * Tile<H>::BYTES, l15, g4);
-  Cols<H> qc[4], gc[4], oc[4];                        // the rows of the step to come, and their statistics
+  Blocks<H> qt, gt;
+  qt.init((lds_t)smem + 2 * kl * Blocks<H>::BYTES, l15, g4);
+  gt.init((lds_t)smem + (2 * kl + 1) * Blocks<H>::BYTES, l15, g4);
+  f32x4 oc[OWN_DELTA ? H / 16 : 1];                   // of the step to come: O where dO goes, and the rows' statistics
   float ln[4], dn[4];
   // position of walk step n: query head (inside the group) and first row
   const int n0 = part * KL + kl;
   int qh = 0, rb = n0;                                // of the next step to be loaded
   auto wrap = [&]() { while (rb >= nblk && qh < g.group) { rb -= nblk; ++qh; } };
   if (nblk > 0) wrap();
-  auto load = [&]() {
+  auto off = [&](unsigned head_bytes, unsigned row_bytes) {
+    const int ln = mfma::lane_again();
+    return qh * head_bytes + __umul24((unsigned)min((b0 + rb) * BLK + (ln >> 2), d.nq - 1), row_bytes) + Blocks<H>::chunk(ln);
+  };
+  auto load_stats = [&]() {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const unsigned row = min((b0 + rb) * BLK + 4 * g4 + r, d.nq - 1);
-      qc[r].load(qb + qh * q_head, row, q_row, l15);
-      gc[r].load(gb + qh * g_head, row, g_row, l15);
-      if constexpr (OWN_DELTA) oc[r].load(ob + qh * o_head, row, o_row, l15);
-      else dn[r] = del_b[qh * d.nq + row];
+      if constexpr (!OWN_DELTA) dn[r] = del_b[qh * d.nq + row];
       ln[r] = lse_b[qh * d.nq + row];
     }
+    if constexpr (OWN_DELTA) {
+      const unsigned at = off(o_head, o_row);
+#pragma unroll
+      for (int y = 0; y < H / 16; ++y) oc[y] = gload<f32x4>(ob, at + 64 * y);
+    }
   };
-  if (n0 < total) load();
+  if (n0 < total) {
+    load_stats();
+    qt.load(qb, off(q_head, q_row));
+    gt.load(gb, off(g_head, g_row));
+  }
+  Cols<H> ring[2];
   for (int n = n0; n < total; n += lanes) {
+    const bool more = n + lanes < total;
     const int i0 = (b0 + rb) * BLK;
     float ls[4], de[4];
+    f32x4 p, ds;
+    mfma::wait_dma<H / 16>();                         // Q, and the statistics
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       ls[r] = ln[r];
-      if constexpr (OWN_DELTA) de[r] = col_sum(gc[r].dot(oc[r]));
-      else de[r] = dn[r];
+      if constexpr (!OWN_DELTA) de[r] = dn[r];
     }
-    qt.store(qc, l15);
-    gt.store(gc, l15);
+    f32x4 own;
+    float del = 0.f;
+    auto own_delta = [&](int y) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) del = fmaf(own[e], oc[y][e], del);
+    };
+    dot_two<H>(p, ds, qt, kf, gt, vf, [] { mfma::wait_dma(); }, [&](auto Y) {
+      constexpr int y = decltype(Y)::value;
+      if constexpr (OWN_DELTA) {                      // of row lane >> 2, a piece at a time
+        if constexpr (y > 0) own_delta(y - 1);
+        own = gt.own(y, mfma::lane_again());
+      }
+      if constexpr (y == 1 || y == 2) {
+#pragma unroll
+        for (int r = 2 * y - 2; r < 2 * y; ++r) {
+          const int i = i0 + 4 * g4 + r;
+          const bool vis = i < d.nq && i >= my_first && ls[r] != -INFINITY;
+          p[r] = vis ? fast_exp2(fmaf(p[r], d.scale, -ls[r]) * kLog2e) : 0.f;
+        }
+      }
+      if constexpr (y >= H / 16 - 2) qt.cols(ring[y - (H / 16 - 2)], y - (H / 16 - 2));
+    });
+    if constexpr (OWN_DELTA) {                        // the row's sum in all four of its lanes, then those of rows 4 g + r
+      own_delta(H / 16 - 1);
+      del += mfma::lane_swap<0xB1>(del);
+      del += mfma::lane_swap<0x4E>(del);
+      static_for<0, 4>([&](auto R) { de[decltype(R)::value] = mfma::lane_swap<0x150 + 4 * decltype(R)::value>(del); });
+    }
     rb += lanes;
     wrap();
-    if (n + lanes < total) load();
-    __builtin_amdgcn_sched_barrier(0);
-    f32x4 px[1], dx[1];
-    dot_rows<H, 1>(px, qt, kf);
-    dot_rows<H, 1>(dx, gt, vf);
-    f32x4 p, ds;
+    if (more) load_stats();
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = i0 + 4 * g4 + r;
-      const bool vis = i < d.nq && i >= my_first && ls[r] != -INFINITY;
-      p[r] = vis ? fast_exp2(fmaf(px[0][r], d.scale, -ls[r]) * kLog2e) : 0.f;
-      ds[r] = p[r] * (dx[0][r] - de[r]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    contract_tile(dv, gt, p, l15);
-    contract_tile(dk, qt, ds, l15);
+    for (int r = 0; r < 4; ++r) ds[r] = p[r] * (ds[r] - de[r]);
+    static_for<0, 8>([&](auto R) {                    // dK, dV; the next tiles as in dq_rows, Q behind most of dV
+      constexpr int r = decltype(R)::value, next = r + 2;
+      if constexpr (r < 4) dk.contract(ring[r & 1], ds[r]); else dv.contract(ring[r & 1], p[r - 4]);
+      if constexpr (r == 2 || r == 6) {
+        reads_done();
+        if (more) {
+          if constexpr (r == 2) qt.load(qb, off(q_head, q_row)); else gt.load(gb, off(g_head, g_row));
+        }
+      }
+      if constexpr (next < 8) (next < 4 ? qt : gt).cols(ring[r & 1], next & 3);
+      __builtin_amdgcn_sched_barrier(0);
+    });
   }
   merge_lanes<H / 8>(reinterpret_cast<f32x4*>(smem), kl, lane, [&](int i) -> f32x4& {
     return i < H / 16 ? dk.acc[i] : dv.acc[i - H / 16];
@@ -672,7 +770,7 @@ __device__ __forceinline__ void dkdv_keys(int id, char* const smem, const a2d_ti
 // The two kinds of workgroups in one launch, `first` of the kind with the longer walks before the others (see
 // a2d_bwd_one.hip; here always: fp32 tiles are small).
 template <int H, bool OWN_DELTA>
-__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void bwd_f32_kernel(
+__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(H < 96 || (H == 96 && !OWN_DELTA) ? 3 : 2))) void bwd_f32_kernel(
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, const float* __restrict__ O, const float* __restrict__ dO,
     const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dQ, float* __restrict__ dK,
@@ -689,9 +787,9 @@ constexpr int most(int a, int b) { return a > b ? a : b; }
 template <int H, int RT>
 constexpr int fwd_lds() { return most(KL * Tile<H>::BYTES, KL / 2 * RT * (H / 16 + 1) * 1024); }
 template <int H>
-constexpr int dq_lds() { return most(2 * KL * Tile<H>::BYTES, KL / 2 * (H / 16) * 1024); }
+constexpr int dq_lds() { return most(2 * KL * Blocks<H>::BYTES, KL / 2 * (H / 16) * 1024); }
 template <int H>
-constexpr int dkdv_lds() { return most(2 * KL * Tile<H>::BYTES, KL / 2 * (H / 8) * 1024); }
+constexpr int dkdv_lds() { return most(2 * KL * Blocks<H>::BYTES, KL / 2 * (H / 8) * 1024); }
 static_assert(dkdv_lds<128>() <= 80 * 1024 && dq_lds<128>() <= 80 * 1024 && fwd_lds<128, 2>() <= 80 * 1024,
               "two workgroups per compute unit");
 
@@ -733,15 +831,6 @@ hipError_t bwd_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const
              (const float*)K, (const float*)V, (const float*)O, (const float*)dO, lse, delta, dQ, dK, dV,
              parts.q_first ? n_q : n_kv, parts.q_first, parts.q);
   return hipGetLastError();
-}
-// delta: from O by the dK/dV workgroups themselves; by a launch in front where there are more than four turns of them,
-// two a compute unit, and at H = 128, where the rows of O do not fit the registers beside the others, more than two (H = 128:
-// 16 x 300 x 300 43 us against 54 with the launch, 16 x 1024 x 1024 293 / 274; H = 64, 16 x 1024 x 1024 causal 83 / 85,
-// 16 x 4096 x 4096 2015 / 1987).
-bool delta_first(const a2d_tile_desc& d, const SegList& g, const BwdParts& parts, int cus) {
-  const int64_t wgs = (int64_t)d.heads * parts.q * ((d.nq + BLK - 1) / BLK) +
-                      (int64_t)(d.heads / g.group) * parts.kv * ((d.nkv + BLK - 1) / BLK);
-  return wgs > (d.hdim == 128 ? 2 : 4) * 2 * (int64_t)cus;
 }
 template <int H>
 hipError_t bwd_h(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
@@ -819,7 +908,7 @@ BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap
     }
   }
   // the kind with the longer walks first; under a mask the longest and the shortest count alike, so that short ones come
-  // last (16 x 700 x 900: dQ first 100 us, dK/dV first 104; 16 x 1024 x 1024, H = 64, causal 90 / 83)
+  // last (16 x 700 x 900: dQ first 92.0 us, dK/dV first 93.2; 16 x 1024 x 1024, H = 64, causal 87 / 80)
   double lq = sq, lk = sk, of_rows[8];
   if (g.by_size) {
     mean_visible_keys(d, g, of_rows);
@@ -830,7 +919,12 @@ BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap
   }
   p.q_first = 3 * (sq + lq) / p.q > 4 * (sk + lk) / p.kv;
   p.one = 1;
-  p.delta = delta_first(d, g, p, cus);
+  // delta: from O by the dK/dV workgroups themselves; by a launch in front where these take more than some steps a compute
+  // unit in all.  (own / launch, us: H = 96 12 x 700 x 900 causal 72 / 76, 16 x 700 x 900 92 / 96, 20 x 700 x 900 110 / 107, 16 x 700 x
+  // 900 unmasked 137 / 129; H = 64 16 x 1024 x 1024 causal 80 / 85; H = 128 4 x 300 x 300 20 / 24.  Earliest at H = 128, where the rows
+  // of O cost the registers of the next loads, then at H = 96, where they cost the third workgroup of a compute unit)
+  constexpr int kDeltaSteps[4] = {140, 140, 110, 80};
+  p.delta = (double)bq * mean / BLK > (double)kDeltaSteps[hx] * cus;
   return p;
 }
 

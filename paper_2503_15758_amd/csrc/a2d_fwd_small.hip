@@ -232,10 +232,10 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
 
   bool more = false;                               // there is a next slab
   auto wait_behind = [&] {
-    if (more) wait_vmem<LOADS>(); else wait_vmem_all();
+    if (more) wait_dma<LOADS>(); else wait_dma();
   };
   if constexpr (Q_LDS) {
-    if (sb < segs) wait_vmem<2 * LOADS>(); else wait_vmem_all();     // this wavefront's share, then everybody's
+    if (sb < segs) wait_dma<2 * LOADS>(); else wait_dma();     // this wavefront's share, then everybody's
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 2; ++q)
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
   if constexpr (RG == 1) {
     // One slab a wavefront: the next K goes where the last one was read from while the exponentials and V P^T are under way,
     // the next V behind those.  (In flight at a time: V and the next K, the next K and V.)
-    if (sb < segs) wait_vmem<LOADS>();             // (K)
+    if (sb < segs) wait_dma<LOADS>();             // (K)
     while (sb < segs) {
       int nsb = sb, nj = j, nn = n;
       advance(stride, nsb, nj, nn);
@@ -327,13 +327,13 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       if (more) {
         load(true, 0);
-        wait_vmem<LOADS>();
+        wait_dma<LOADS>();
       }
       if (!CYCLIC && nsb != sb && more) enter_segment();
       sb = nsb; j = nj; n = nn;
     }
   } else {
-    wait_vmem_all();
+    wait_dma();
     __syncthreads();
     unsigned buf = 0;
     for (int r = 0; r < rounds; ++r) {
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void fwd_small_kernel(
         load(true, SLAB_BYTES - buf);
       }
       if (sb < segs && j * SB + (CYCLIC && sb > shift_from) < nvis) compute(buf, [] {});
-      wait_vmem_all();
+      wait_dma();
       __syncthreads();
       if (!CYCLIC && more && nsb != sb) enter_segment();
       sb = nsb; j = nj; n = nn;

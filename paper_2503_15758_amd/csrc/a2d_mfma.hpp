@@ -114,6 +114,12 @@ __device__ __forceinline__ Split query_head(int t, int group, int nblocks, bool 
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 template <int N>                                     // all but the last N (below 16) operations
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70 | N); }
+// the same for loads into LDS that the wavefront itself reads, with no barrier in between: no read moves up past the wait
+template <int N = 0>
+__device__ __forceinline__ void wait_dma() {
+  wait_vmem<N>();
+  asm volatile("" ::: "memory");
+}
 
 // Global-memory pointer that is the same in every lane, held in scalar registers, so that loads
 // through it use the scalar-base + 32-bit-lane-offset addressing form (no per-lane 64-bit address
@@ -209,8 +215,8 @@ template <int OFF, bool NT = false>
 __device__ __forceinline__ void dma_b128(unsigned at, gptr_t base, unsigned byte_off) {
   if constexpr (NT) A2D_DMA_B128(" nt"); else A2D_DMA_B128("");
 }
-// (H: the head size; chunks past it are left alone)
 #undef A2D_DMA_B128
+// (H: the head size; chunks past it are left alone)
 template <int N, int H>
 __device__ __forceinline__ void dma_blocks(unsigned at, gptr_t base, unsigned byte_off, int chunk) {
   static_for<0, N>([&](auto X) {

@@ -1,7 +1,9 @@
 """The 16 x 16 tiles inside a wavefront's 32 rows and keys, at their edges: sizes one off multiples of 16, diagonals at every
 offset within a tile, against fp64 on the GPU."""
 import pytest
+import torch
 
+import test_gpu_f32_kernels as f32
 import test_gpu_small_rows as forward
 from test_gpu_bwd_routes import _check
 
@@ -40,3 +42,19 @@ def test_forward_tile_edges(rows, case):
     heads, _, nq, nkv, H, causal, q_off = case[:7]
     assert a2d.tile_route(heads, nq, nkv, H, causal=causal, q_off=q_off)["rows"] == rows
     forward.test_small_rows(case)
+
+
+# fp32 backward: steps of 16 rows and keys, four key lanes; delta by a launch in front (the last four) and by the tiles themselves
+F32 = [(1, 1, 1, 1, 64, False, 0, [(0, 1)]), (2, 2, 15, 17, 80, True, 2, [(0, 17)]), (3, 3, 17, 63, 96, True, 46, [(0, 63)]),
+       (2, 1, 65, 129, 128, True, 64, [(0, 129)]), (4, 2, 33, 79, 64, True, 46, [(0, 30), (40, 49)]), (5, 5, 79, 65, 96, False, 0, [(0, 65)]),
+       (60, 30, 513, 545, 64, True, 415, [(0, 545)]), (36, 36, 511, 767, 80, True, 255, [(0, 767)]),
+       (34, 34, 497, 769, 96, True, 271, [(0, 769)]), (16, 8, 529, 639, 128, False, 0, [(0, 639)])]
+
+
+@pytest.mark.parametrize("case", F32, ids=lambda c: "%dx%dH%d" % (c[2], c[3], c[4]))
+def test_f32_tile_edges(case):
+    from paper_2503_15758_amd import binding as a2d
+    heads, kvh, nq, nkv, H, causal, q_off, segs = case
+    route = a2d.tile_route(heads, nq, nkv, H, dtype=torch.float32, kv_heads=kvh, causal=causal, q_off=q_off, segments=segs, backward=True)
+    assert ("delta_kernel" in route["kernels"]) == (nq > 400), route
+    f32.test_f32_tiles_at_every_launch_shape(a2d, case)
