@@ -112,8 +112,11 @@ __device__ __forceinline__ Split query_head(int t, int group, int nblocks, bool 
 // those registers are complete, so that uses inside the main loop do not have to be guarded by
 // waits that would also cover the loop's own freshly issued prefetches.
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-template <int N>                                     // all but the last N (below 16) operations
-__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70 | N); }
+template <int N>                                     // all but the last N operations (the counter's upper bits stand apart)
+__device__ __forceinline__ void wait_vmem() {
+  static_assert(N >= 0 && N < 64, "the counter has six bits");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14);
+}
 // the same for loads into LDS that the wavefront itself reads, with no barrier in between: no read moves up past the wait
 template <int N = 0>
 __device__ __forceinline__ void wait_dma() {
