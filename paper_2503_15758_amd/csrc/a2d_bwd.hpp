@@ -47,13 +47,7 @@ __device__ __forceinline__ f32x4 lds_load_f32x4(unsigned addr) {
   return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>((uintptr_t)addr);
 }
 
-// natural fragment x of a dual tile (rows RB .. RB+31 relative to the per-lane bases in `a`)
-template <int X>
-__device__ __forceinline__ bf16x8 dual_nat(const DualAddr& a, int extra) {
-  return lds_load_b128(((X & 1) ? a.nat_o : a.nat_e) + 64 * (X >> 1) + extra);
-}
-
-// A step of the dK/dV kernels: BQ query rows, staged through LDS as a buffer { Q tile, dO tile } (dual
+// A step of the dK/dV pairs: BQ query rows, staged through LDS as a buffer { Q tile, dO tile } (dual
 // layout) and two statistics per row
 constexpr int BQ = 32;
 constexpr int DK_TILE = BQ * DUAL_LD;

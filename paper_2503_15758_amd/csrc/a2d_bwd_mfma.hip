@@ -31,8 +31,8 @@
 //                    dK/dV kernel filled (its WRITE_DS variant) and only contracts it with K, so that S
 //                    and dP are computed once (5 contractions for 5 counted ones instead of 7): large
 //                    tiles of H = 128, where the caller allows it.
-// Tiles that are read both ways (natural and transposed fragments) live in the "dual" LDS
-// layout of a2d_mfma.hpp: every fragment address is a per-lane base plus an immediate.
+// Tiles that are read both ways (natural and transposed fragments) live in LDS in the blocks of a2d_mfma.hpp (Blocks16), those of
+// bwd_dkdv_kernel in its "dual" layout: every fragment address is a per-lane base plus an immediate.
 #include <type_traits>
 
 #include "a2d_bwd_dq.hpp"

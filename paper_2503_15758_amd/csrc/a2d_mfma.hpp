@@ -9,7 +9,8 @@
 // v_mfma_f32_16x16x32_bf16, D(16x16) += A(16x32) * B(32x16):
 //   A, B fragments: lane holds row / column (lane & 15), contraction indices 8*(lane>>4) + 0..7
 //   D: lane holds column (lane & 15); register r is row 4*(lane>>4) + r
-// The large tiles' backward runs on the latter, which costs less power per flop (see a2d_bwd_wide.hpp).
+// All bf16 kernels but the dK/dV pairs and the backward of few rows run on the latter, which costs less power per flop (see
+// a2d_bwd_wide.hpp).
 // Two kinds of fragment reads from a row-major LDS tile (rows x padded head size, bf16):
 //   - "natural" fragments (contraction along H): one 128-bit read per lane;
 //   - "transposed" fragments (contraction along the row index): two ds_read_b64_tr_b16, where a
@@ -168,7 +169,6 @@ __device__ __forceinline__ bf16x8 lds_load_tr(unsigned addr_lo, unsigned addr_hi
 //   transposing reads of column tile ct, rows RB + {0..7 | 8..15}, RB a multiple of 16:
 //       (tr_lo | tr_hi) + 64 * ct + RB * 320
 constexpr int DUAL_LD = 320;
-constexpr int DUAL64_BYTES = 64 * DUAL_LD;
 struct DualAddr {
   unsigned nat_e, nat_o, tr_lo, tr_hi;
   __device__ __forceinline__ void init(int lane, unsigned tile_base) {
@@ -183,7 +183,6 @@ struct DualAddr {
     tr_lo = tile_base + row * DUAL_LD + 16 * (cl ^ (g16 >> 1)) + sub;
     tr_hi = tile_base + (row + 8) * DUAL_LD + 16 * (cl ^ ((g16 >> 1) + 2)) + sub;
   }
-  __device__ __forceinline__ void shift(int delta) { nat_e += delta; nat_o += delta; tr_lo += delta; tr_hi += delta; }
 };
 // byte offset inside a dual tile at which the 16-byte chunk `c` of row `r` is stored
 __device__ __forceinline__ int dual_store_off(int r, int c) { return r * DUAL_LD + ((c ^ ((r >> 2) & 3)) << 4); }
