@@ -50,10 +50,10 @@ __host__ __device__ constexpr int fwd_lds(int waves, int hd, int kl) {
 }
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
 constexpr double kStepUs[3] = {1.25, 1.45, 1.66};   // a 64-key step of a 256-row workgroup, H = 64 / 96 / 128
-// a round of 256 keys of 32 rows, of 128 keys of 64 rows: in tiles (the fit to 720 shapes below); in calls over a grid, whose
+// a round of 256 keys of 32 rows, of 128 keys of 64 rows: in tiles (the fits below); in calls over a grid, whose
 // walks of every length make them wait for each other (350 grids: 2.0 % off the best form with these and with the tiles')
-constexpr double kSmallRoundUs[2][3] = {{0.75, 1.03, 1.37}, {0.95, 1.42, 1.65}}, kSmallFixedUs[2][3] = {{2.5, 2.8, 2.55}, {3.1, 3.5, 3.2}};
-constexpr double kPairRoundUs[2][3] = {{0.71, 1.10, 1.21}, {0.95, 1.25, 1.37}}, kPairFixedUs[2][3] = {{4.2, 4.0, 3.9}, {4.1, 4.3, 4.4}};
+constexpr double kSmallRoundUs[2][3] = {{0.90, 1.18, 1.58}, {0.95, 1.42, 1.65}}, kSmallFixedUs[2][3] = {{2.9, 3.2, 2.95}, {3.1, 3.5, 3.2}};
+constexpr double kPairRoundUs[2][3] = {{0.85, 1.27, 1.28}, {0.95, 1.25, 1.37}}, kPairFixedUs[2][3] = {{4.06, 3.83, 3.83}, {4.1, 4.3, 4.4}};
 
 template <int HR>
 struct FwdState {
@@ -542,7 +542,10 @@ hipError_t fwd_form(Phase ph, const a2d_tile_desc& d, const SegList& g, const vo
 // 2048, H = 64 and 128), to 73 of any size (worst miss 11 %) and, those of few rows, to 720 tiles of up to 1100 blocks of 32 rows,
 // H = 64 to 128, x five forms x up to six numbers of parts - 32 rows are taken up to about 256 such blocks, 64 rows up to
 // 256 of theirs, under a causal mask up to 512, with walks of 16 rounds at the most; there the choice is 1.5 % slower than the
-// best in the mean, much of it the noise of calls of 6 us (2.7 % with the constants of the kernel before it loaded straight into LDS).
+// best in the mean, much of it the noise of calls of 6 us.  The costs of a round were then raised by what 413 tiles of 2e6 to 2.5e8 scores
+// asked for, each with unit-scale and with peaky logits (which rescale oftener): 2.3 / 1.6 / 1.8 % off the best -> some 0.6 / 0.5 / 1 % at
+// H = 64 / 80, 96 / 128, peaky 2.7 / 1.8 / 1.4 -> 0.7 / 0.4 / 0.6 (34 x 487 x 460, H = 64, causal, peaky: 14.1 us in 32 rows, 10.5 in 64;
+// 78 x 181 x 10950, H = 128, three blocks: 493 in 64 rows, 424 in 256 and parts.  Given up: 2 x 4286 x 6231, H = 128, causal 34 -> 40).
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t heads = (int64_t)d.heads * (g->b.side ? g->b.side : 1);
   double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2, mean = most;
