@@ -207,9 +207,10 @@ struct Blocks16 {
 // vector memory operation; the compiler does not know of it, so the caller waits (wait_vmem_all) before the barrier behind
 // which the tile is read.  dma_blocks: the N blocks of a row tile, slice after slice of its rows - one lane offset and one
 // base for all (the instruction's offset counts for both addresses).
-// (NT: read once)
+// (NT: read once.  The address goes in as m0 itself, so that the compiler knows of it; the instruction needs a wait state behind a
+// write of m0, which it does not put in front of assembly)
 #define A2D_DMA_B128(more)                                                                                                   \
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" more ::"s"(                         \
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" more ::"{m0}"(                                          \
                    __builtin_amdgcn_readfirstlane(at - OFF)),                                                                \
                "v"(byte_off), "s"(base), "n"(OFF)                                                                            \
                : "memory")
