@@ -55,7 +55,7 @@ __device__ __forceinline__ void dkdv_wide(
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   constexpr int HD = padded_head(HR), H = HR, TILE = wk_tile(HD), BUF = 2 * TILE;
   constexpr int KS = HD / 32, HT = HR / 16;        // slices of H in the first two contractions, column tiles of the others
-  // At H = 128 the accumulators, K^T and V^T leave 64 registers: shorter fragment rings, and per-lane addresses
+  // At H = 128 the accumulators, K^T and V^T leave 64 registers: shorter fragment rings, and per-lane values
   // that are used once a step are computed again in every step.
   constexpr bool TIGHT = HD == 128;
   const int kv_heads = d.heads / g.group;
@@ -160,7 +160,7 @@ __device__ __forceinline__ void dkdv_wide(
 
   // ---- staging, straight into LDS: wavefronts 0 .. 3 load a row tile of Q each, 4 .. 7 of dO; wavefront 0 brings lse,
   // wavefront 1 delta.  Step j + 1 is requested while step j is computed; the last one re-stages itself.  Rows beyond
-  // nq re-read the last row with a statistic of -inf (p = 0).  What a step's requests need is carried on by a few scalar
+  // nq re-read the last row (the mask takes them out).  What a step's requests need is carried on by a few scalar
   // additions: both wavefronts of a SIMD stand here right behind the barrier, with no MFMA under way.
   const bool is_g = wave >= 4;
   const int ld_tile = 16 * (wave & 3);
@@ -172,8 +172,7 @@ __device__ __forceinline__ void dkdv_wide(
     ld_at = reinterpret_cast<const char*>(ld_base + ld_h * (is_g ? d.ldo.head : d.lq.head) + (CYCLIC ? ld_r * (is_g ? g.b.g : g.b.q) : 0)) +
             (int64_t)(i_start + ld_s * WK_ROWS + ld_tile) * ld_row_bytes;
   };
-  float stat = 0.f;
-  bool stat_ok = false;
+  const auto stat_of = [&](int buf) { return lds_base + wk_stat(HD) + buf * WK_STAT_BUF + wave * (4 * WK_ROWS); };
   auto load_step = [&](int buf) {
     const int ln = TIGHT ? lane_again() : lane;
     const int i0 = i_start + ld_s * WK_ROWS, ch = (ln & 3) ^ block_swap(ln >> 4);
@@ -185,9 +184,9 @@ __device__ __forceinline__ void dkdv_wide(
     }
     dma_blocks<KS, H>(lds_base + buf * BUF + wave * KS * BLOCK, uniform_gptr(at), __umul24(r, ld_row_bytes) + 16 * ch, ch);
     if (wave < 2) {
-      const int ir = min(i0 + ln, nq - 1);
-      stat = (wave == 0 ? lse : delta)[(int64_t)ld_h * head_rows + (CYCLIC ? ir * side + ld_r : ir)];
-      stat_ok = i0 + ln < nq;
+      const unsigned ir = min(i0 + ln, nq - 1);
+      dma_b32<0>(stat_of(buf), uniform_gptr((wave == 0 ? lse : delta) + (int64_t)ld_h * head_rows + (CYCLIC ? ld_r : 0)),
+                 (CYCLIC ? ir * side : ir) * 4);
     }
     if (ld_left > 0) {                             // the next step: of the next row block, or further down, or of the next head
       --ld_left;
@@ -205,13 +204,18 @@ __device__ __forceinline__ void dkdv_wide(
       }
     }
   };
-  auto store_stat = [&](int buf) {
+  // What the wavefront has brought of lse or delta becomes what the scores or dP start from, half a step after its request.  (Loaded
+  // into a register that waits for its place to be free, it was one register too many at H = 128: kept in scratch, and the
+  // wait for it in front of the store is one for the tiles just requested.  Turned where it is read it would cost every
+  // wavefront some twenty vector instructions a half step.  With it, and c, 1 / scale and the mask's limits out of the vector registers,
+  // nothing is in scratch: us, 8192 tokens of 16 heads on 4 x 4, causal, both passes 1012 -> 992, 96 x 4096 x 4096 with dS 2059 ->
+  // 2049.)
+  auto turn_stat = [&](int buf) {
     if (wave < 2) {
-      const int ln = TIGHT ? lane_again() : lane;
-      float v = -stat;
-      if (wave == 0) v = (!stat_ok || v == INFINITY) ? -INFINITY : v * inv_scale;
-      else v = stat_ok ? v : 0.f;
-      reinterpret_cast<float*>(lds + wk_stat(HD) + buf * WK_STAT_BUF)[wave * WK_ROWS + ln] = v;
+      auto* const at = reinterpret_cast<__attribute__((address_space(3))) float*>((uintptr_t)(stat_of(buf) + 4 * (TIGHT ? lane_again() : lane)));
+      float v = -*at;
+      if (wave == 0) v = v == INFINITY ? -INFINITY : v * inv_scale;
+      *at = v;
     }
   };
   if constexpr (H != HD) {                         // columns past the head size are zero for good
@@ -224,9 +228,9 @@ __device__ __forceinline__ void dkdv_wide(
   if (total > 0) {
     open_run();
     load_step(0);
-    store_stat(0);
   }
-  wait_vmem_all();
+  wait_dma();
+  if (total > 0) turn_stat(0);
   __syncthreads();
 
   // dS hand-over: the wavefront's 32 keys are piece wave & 1 of key block 4 blk + wave / 2
@@ -253,7 +257,7 @@ __device__ __forceinline__ void dkdv_wide(
       if constexpr (i < N2) a[i % RING] = lds_load_b128(da.nat + (i < N1 ? 0 : TILE) + ((i & 1) * KS + (i % N1 >> 1)) * BLOCK);
       else if constexpr (i < N4) {
         constexpr int y = i < N3 ? i - N2 : i - N3;
-        const unsigned at = (y & 1 ? da.tr_o : da.tr_e) + (i < N3 ? TILE : 0) + (y >> 1) * BLOCK;
+        const unsigned at = (y & 1 ? da.tr_e ^ 32 : da.tr_e) + (i < N3 ? TILE : 0) + (y >> 1) * BLOCK;   // (da.tr_o: made where it is used)
         a[i % RING] = lds_load_tr(at, at + KS * BLOCK);
       }
     };
@@ -278,8 +282,10 @@ __device__ __forceinline__ void dkdv_wide(
       if (masked) {
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
-          const int first = i0 + 4 * grp - my_first[kt];
-          const unsigned limit = CYCLIC ? max(rows - my_first[kt], 0) : rows - my_first[kt];   // (padding keys: none)
+          int mine = my_first[kt];
+          if constexpr (TIGHT) asm volatile("" : "+v"(mine));   // (the limit would be kept for all steps)
+          const int first = i0 + 4 * (TIGHT ? lane_again() >> 4 : grp) - mine;
+          const unsigned limit = CYCLIC ? max(rows - mine, 0) : rows - mine;   // (padding keys: none)
 #pragma unroll
           for (int r = 0; r < 8; ++r)
             if ((unsigned)(first + 16 * (r >> 2) + (r & 3)) >= limit) s[r >> 2][kt][r & 3] = -INFINITY;
@@ -333,7 +339,7 @@ __device__ __forceinline__ void dkdv_wide(
   for (int j = 0; j < total; ++j) {
     load_step(buf ^ 1);
     const int sh = CYCLIC && cr < late ? 1 : 0;
-    int stored = 0;
+    int stored = 0;                                // vector memory operations since the requests: stores of dS, which may be under way
 #pragma nounroll
     for (int h = 0; h < 2; ++h) {
       const int i0 = i_start + cs * WK_ROWS + h * BQ;
@@ -343,35 +349,39 @@ __device__ __forceinline__ void dkdv_wide(
         stored += 2;
       }
       const int go = h == 0 ? HALF : buf ? -BUF - HALF : BUF - HALF;
-      da.nat += go; da.tr_e += go; da.tr_o += go;
+      da.nat += go; da.tr_e += go;
       st_addr += h == 0 ? BQ * 4 : buf ? -WK_STAT_BUF - BQ * 4 : WK_STAT_BUF - BQ * 4;
+      if (h == 0 && wave < 2) {                    // (requested half a step ago)
+        if (WRITE_DS && stored) wait_dma<2>(); else wait_dma();
+        turn_stat(buf ^ 1);
+      }
     }
     if (!CYCLIC || ++cr == side) {
       cr = 0;
       if (++cs == nsteps) { cs = 0; ++chd; }
     }
     buf ^= 1;
-    store_stat(buf);
-    // (the next tiles have arrived; a step's stores of dS, its last requests, may be under way)
-    if (WRITE_DS && stored == 4) wait_vmem<4>();
-    else if (WRITE_DS && stored == 2) wait_vmem<2>();
-    else wait_vmem_all();
+    // (the next tiles)
+    if (WRITE_DS && stored == 4) wait_dma<4>();
+    else if (WRITE_DS && stored == 2) wait_dma<2>();
+    else wait_dma();
     __syncthreads();
   }
 
   char* const area = lds + wave * acc_area(HT);
+  const int ln = TIGHT ? lane_again() : lane;      // (the one of the start would be kept in scratch until here)
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt) {
     const int first = wk + 16 * kt, n = d.nkv - first;
     if (GRID && parts == 1) {
       bf16_t* const dkb = reinterpret_cast<bf16_t*>(dK) + head * g.b.out[1].head + col * g.b.out_step[1];
       bf16_t* const dvb = reinterpret_cast<bf16_t*>(dV) + head * g.b.out[2].head + col * g.b.out_step[2];
-      store_acc16(dvb + first * g.b.out[2].row, g.b.out[2].row, n, area, dv, kt, lane, 1.0f);
-      store_acc16(dkb + first * g.b.out[1].row, g.b.out[1].row, n, area, dk, kt, lane, d.scale);
+      store_acc16(dvb + first * g.b.out[2].row, g.b.out[2].row, n, area, dv, kt, ln, 1.0f);
+      store_acc16(dkb + first * g.b.out[1].row, g.b.out[1].row, n, area, dk, kt, ln, d.scale);
     } else {
       const int64_t at = ((int64_t)head * d.nkv + first) * H;
-      store_acc16(dV + at, H, n, area, dv, kt, lane, 1.0f);
-      store_acc16(dK + at, H, n, area, dk, kt, lane, d.scale);
+      store_acc16(dV + at, H, n, area, dv, kt, ln, 1.0f);
+      store_acc16(dK + at, H, n, area, dk, kt, ln, d.scale);
     }
   }
 }

@@ -140,8 +140,10 @@ __device__ __forceinline__ u32x4 gload_b128(gptr_t base, unsigned byte_off) {
   return *reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(base + byte_off);
 }
 
-// a value that is the same in every lane, in a scalar register
+// A value that is the same in every lane, in a scalar register.  (The compiler may not know that it is the same: it would fold the
+// builtin away, and a product, which only the vector ALU makes, would keep a register of every lane.)
 __device__ __forceinline__ float uniform(float x) {
+  asm("" : "+v"(x));
   return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
 }
 
@@ -209,16 +211,21 @@ struct Blocks16 {
 // base for all (the instruction's offset counts for both addresses).
 // (NT: read once.  The address goes in as m0 itself, so that the compiler knows of it; the instruction needs a wait state behind a
 // write of m0, which it does not put in front of assembly)
-#define A2D_DMA_B128(more)                                                                                                   \
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" more ::"{m0}"(                                          \
+#define A2D_DMA(width, more)                                                                                                 \
+  asm volatile("s_nop 0\n\tglobal_load_lds_" width " %1, %2 offset:%3" more ::"{m0}"(                                        \
                    __builtin_amdgcn_readfirstlane(at - OFF)),                                                                \
                "v"(byte_off), "s"(base), "n"(OFF)                                                                            \
                : "memory")
 template <int OFF, bool NT = false>
 __device__ __forceinline__ void dma_b128(unsigned at, gptr_t base, unsigned byte_off) {
-  if constexpr (NT) A2D_DMA_B128(" nt"); else A2D_DMA_B128("");
+  if constexpr (NT) A2D_DMA("dwordx4", " nt"); else A2D_DMA("dwordx4", "");
 }
-#undef A2D_DMA_B128
+// (four bytes a lane, at `at` + 4 i)
+template <int OFF>
+__device__ __forceinline__ void dma_b32(unsigned at, gptr_t base, unsigned byte_off) {
+  A2D_DMA("dword", "");
+}
+#undef A2D_DMA
 // (H: the head size; chunks past it are left alone)
 template <int N, int H>
 __device__ __forceinline__ void dma_blocks(unsigned at, gptr_t base, unsigned byte_off, int chunk) {
