@@ -75,11 +75,30 @@ constexpr int DSQ_RING = 4;
 __host__ __device__ constexpr int dsq_stages(int waves, int kl) { return waves == 8 && kl == 1 ? 3 : 2; }
 __host__ __device__ constexpr int dsq_stage(int rw, int hd) { return BKS * 2 * hd + rw * DS_TILE_BYTES; }   // { K tile, dS tiles }
 __host__ __device__ constexpr int dsq_lds(int waves, int hd, int kl) { return kl * dsq_stages(waves, kl) * dsq_stage(waves / kl, hd); }
+// A piece's granules (rows 4 g + 0..3 and 16 + 4 g + 0..3 of a key, 16 bytes) in LDS, and what a transposing read takes of them:
+// 8 bytes a lane, of four g of eight keys at a time.  It meets every bank once with the keys of g = 2, 3 moved
+// and the other half taken where g is odd, so that tile u of the results is made of the rows 16 (u ^ (g & 1)) + 4 g + 0..3.  With the
+// granules in the order of memory and one half for all a bank was met four times (36 % of the kernel's LDS cycles at 96 x 4096 x 4096,
+// now none; the time is the memory's: 2108 -> 2095 us for the whole call).
+__host__ __device__ constexpr int dsq_granule(int g, int key) { return 16 * g + (key ^ (g >> 1 ? 12 : 0)); }
+__host__ __device__ constexpr int dsq_at(int lane) {        // of tile 0 (of tile 1: ^ 8)
+  return 16 * dsq_granule(lane & 3, 4 * (lane >> 4) + ((lane & 15) >> 2)) + 8 * (lane & 1);
+}
+__host__ __device__ constexpr int dsq_row(int u, int j) { return 16 * (u ^ (j >> 2 & 1)) + j; }
+constexpr bool dsq_banks_once() {
+  for (int first = 0; first < 64; first += 32) {             // half a wavefront's 8 bytes a lane are the 64 banks' width
+    unsigned banks = 0;
+    for (int l = first; l < first + 32; ++l) banks |= 1u << (dsq_at(l) / 8 % 32);
+    if (banks != ~0u) return false;
+  }
+  return true;
+}
+static_assert(dsq_banks_once(), "the reads of dS meet a bank more than once");
 template <int HD>
 struct DsqCtx {
-  f32x4 dq[HD / 16][2]; // column tiles x the wavefront's two tiles of 16 query rows
+  f32x4 dq[HD / 16][2]; // column tiles x the wavefront's two tiles of 16 query rows (dsq_row)
   unsigned kt_e, kt_o;  // transposed fragments of the K tile of the current stage (Blocks16), ...
-  unsigned ds;          // ... of the dS tile
+  unsigned ds[2];       // ... of the dS tile
   int my_vis[2];        // number of leading keys of the current sub-block this lane's query rows see
   int grp;
 };
@@ -97,7 +116,7 @@ __device__ __forceinline__ void dsq_piece(DsqCtx<HD>& cx, int key0, bool masked)
     __builtin_amdgcn_sched_barrier(0);
   };
 #pragma unroll
-  for (int u = 0; u < 2; ++u) dsb[u] = lds_load_tr(cx.ds + T * 2048 + 8 * u, cx.ds + T * 2048 + 1024 + 8 * u);
+  for (int u = 0; u < 2; ++u) dsb[u] = lds_load_tr(cx.ds[u] + T * 2048, cx.ds[u] + T * 2048 + 1024);
   static_for<0, (DSQ_RING < HT ? DSQ_RING : HT)>(ld);
   if (A2D_SELDOM(masked)) {
     asm volatile("" ::: "memory");                 // keep this a branch
@@ -153,14 +172,15 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
 
   DsqCtx<HD> cx;
   cx.grp = lane >> 4;
-  const int q_row = q0 + wave * 32 + (lane & 15);      // of the first row tile
+  const int w_row = q0 + wave * 32;                    // the wavefront's first row
 #pragma unroll
   for (int t = 0; t < HT; ++t) cx.dq[t][0] = cx.dq[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   Blocks16 at;
   at.init(lane, lds_base);
   cx.kt_e = at.tr_e;
   cx.kt_o = at.tr_o;
-  cx.ds = lds_base + K_TILE + wave * DS_TILE_BYTES + (lane & 3) * 256 + (4 * cx.grp + ((lane & 15) >> 2)) * 16;
+  cx.ds[0] = lds_base + K_TILE + wave * DS_TILE_BYTES + dsq_at(lane);
+  cx.ds[1] = cx.ds[0] ^ 8;
 
   // this wavefront's row tile of dS (a wavefront past the last row reads the last tile; its
   // results are never stored)
@@ -215,7 +235,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
       }
       nvis_wave = vis_count(w_last, c_sb);
       nfull_wave = vis_count(w_first, c_sb);
-      for (int u = 0; u < 2; ++u) cx.my_vis[u] = vis_count(min(q_row + 16 * u, d.nq - 1), c_sb);
+      for (int u = 0; u < 2; ++u) cx.my_vis[u] = vis_count(min(w_row + dsq_row(u, lane & 15), d.nq - 1), c_sb);
     }
   };
 
@@ -235,7 +255,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     // (dS is read once: kept from displacing the K tiles in L2)
     static_for<0, 4>([&](auto I) {
       constexpr int off = 1024 * decltype(I)::value;
-      dma_b128<off, true>(stage + K_TILE + wave * DS_TILE_BYTES + off, from, lane * 16);
+      dma_b128<off, true>(stage + K_TILE + wave * DS_TILE_BYTES + off, from, dsq_granule(lane >> 4, lane & 15) * 16);
     });
   };
 
@@ -243,10 +263,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
   char* const area = lds_all + wave * (KL == 2 ? HT * 8 * 256 : acc_area(HT));
   auto store_rows = [&](float mul, bool add) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int first = q0 + wave * 32 + 16 * u;
-      store_acc16(dQ + (((int64_t)part * d.heads + head) * d.nq + first) * H, H, d.nq - first, area, cx.dq, u, lane, mul, add);
-    }
+    for (int u = 0; u < 2; ++u)
+      store_acc16(dQ + (((int64_t)part * d.heads + head) * d.nq + w_row) * H, H, d.nq - w_row, area, cx.dq, u, lane, mul, add,
+                  [u](int r) { return dsq_row(u, r); });
   };
   count = count > part * KL ? count - part * KL : 0;           // from this part's first block on
   if (count == 0) {                                // no visible key: dQ share is zero
@@ -276,7 +295,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void bwd_dq_ds_kernel(
     if (k0 < nvis_wave) dsq_piece<0>(cx, k0, k0 + 32 > nfull_wave);
     if (k0 + 32 < nvis_wave) dsq_piece<1>(cx, k0 + 32, k0 + 64 > nfull_wave);
     const int go = cur == (ST - 1) * STAGE ? -(ST - 1) * STAGE : STAGE;
-    cx.kt_e += go; cx.kt_o += go; cx.ds += go;
+    cx.kt_e += go; cx.kt_o += go; cx.ds[0] += go; cx.ds[1] += go;
     cur += go;
     compute_by(stride);
     wait_vmem<(ST - 2) * LOADS>();

@@ -267,7 +267,7 @@ __device__ __forceinline__ void row_pair(float x, float (&of)[2]) {
 // us, pieces as they stand / whole rows / non-temporal: 256 workgroups of the forward at H = 128 with one step each 13.2 / 12.5 /
 // 11.4 (without any stores 6.7), 16 x 2048 x 2048 forward 37.9 / 37.5 / 36.2 and backward 113.9 / 110.9 / 108.7, backward
 // 96 x 4096 x 4096 with dS 2188 / 2173 / 2060.
-// (add: onto what the rows already hold)
+// (add: onto what the rows already hold; row_of: where row r of the tile goes)
 __host__ __device__ constexpr int acc_ld(int ht) { return 64 * ht + 16; }
 __host__ __device__ constexpr int acc_area(int ht) { return 16 * acc_ld(ht); }
 template <int HT, int NT>
@@ -283,16 +283,19 @@ __device__ __forceinline__ void acc_to_lds(char* area, const f32x4 (&acc)[HT][NT
   }
   asm volatile("" ::: "memory");
 }
-template <int HT, int NT>
+struct Ascending {
+  __device__ __forceinline__ int operator()(int r) const { return r; }
+};
+template <int HT, int NT, class RowOf = Ascending>
 __device__ __forceinline__ void store_acc16(float* out, int64_t row, int n, char* area, const f32x4 (&acc)[HT][NT], int t,
-                                            int lane, float mul, bool add = false) {
+                                            int lane, float mul, bool add = false, RowOf&& row_of = {}) {
   acc_to_lds(area, acc, t, lane, mul);
 #pragma unroll
   for (int x = 0; x < HT; ++x) {
-    const int i = lane + 64 * x, r = i / (4 * HT), ch = i - r * (4 * HT);
+    const int i = lane + 64 * x, r = i / (4 * HT), ch = i - r * (4 * HT), to = row_of(r);
     f32x4 v = *reinterpret_cast<const f32x4*>(area + r * acc_ld(HT) + 16 * ch);
-    if (r >= n) continue;
-    f32x4* const p = reinterpret_cast<f32x4*>(out + r * row + 4 * ch);
+    if (to >= n) continue;
+    f32x4* const p = reinterpret_cast<f32x4*>(out + to * row + 4 * ch);
     if (add) {
       const f32x4 o = *p;
 #pragma unroll
