@@ -6,7 +6,7 @@
 // workgroups compute it of their rows anyway, dK/dV workgroups in pairs of the rows they stage (OWN_DELTA: an
 // eighth more loads in a step, a dozen vector instructions; a launch of delta_kernel in front costs a small tile more).
 // Those of 256 keys have no registers for it at H = 128 and serve tiles where that launch costs 3 %: they read it.
-// The kind with the longer walks goes first (plan_bwd_mfma).
+// The kind with the longer walks goes first, but for masked tiles with many keys that few rows see (plan_bwd_one).
 #include "a2d_bwd_dq.hpp"
 #include "a2d_bwd_pairs.hpp"
 #include "a2d_bwd_wide.hpp"
@@ -156,13 +156,21 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
     return small;
   }
   const int keys = best->wide ? WK_KEYS : DK_KEYS, rows = best->form ? 128 : 256;
+  const Kind chosen_kv = best_kv, chosen_q = best_q;
   best_kv.n = xcd_grid(kv_heads * best->kv, side * ((d.nkv + keys - 1) / keys));
   best_q.n = xcd_grid(kv_heads * best->q, side * g.group * ((d.nq + rows - 1) / rows));
-  *dealt = rest + (best->q_first ? dealt_time(best_q, best_kv, cus, w.uneven, kTail) : dealt_time(best_kv, best_q, cus, w.uneven, kTail));
   // (Under a mask most key blocks may be seen by few rows or none, which leaves dK / dV one long walk and many short ones, each
   // still with its prologue and its rows to store: behind them the dQ walks start late.  us, dK / dV first / dQ first: 40 x
-  // 496 x 2977, H = 128 53.8 / 41.7, 46 x 717 x 4521 86.8 / 71.5, 14 x 339 x 4617 34.6 / 29.2, 44 x 282 x 872, H = 80 22.9 / 19.6.)
-  if (w.uneven && !g.b.side && best_q.mean > best_kv.mean && best_kv.n + best_q.n > cus) best->q_first = 1;
+  // 496 x 2977, H = 128 53.8 / 41.7, 46 x 717 x 4521 86.8 / 71.5, 14 x 339 x 4617 34.6 / 29.2, 44 x 282 x 872, H = 80 22.9 / 19.6.
+  // Both times are those of the order that is launched: of 13100 masked shapes of two to six turns 55 go out otherwise than by the
+  // times of the other order, 1.04 times as fast in the mean (124/31 x 782 x 5816, H = 64 133 -> 113, at worst 100/25 x 829 x 10756,
+  // H = 96 144 -> 157).  The shapes are chosen by the other one: with this one's times in
+  // that choice 39 of 28000 drawn shapes changed, as many for the worse, 20 x 572 x 9758, H = 80 56 -> 78, as for the better.)
+  if (w.uneven && !g.b.side && best_q.mean > best_kv.mean && best_kv.n + best_q.n > cus && !best->q_first) {
+    best->q_first = 1;
+    least = rest + one_time(chosen_q, chosen_kv, cus, true, kTail);
+  }
+  *dealt = rest + (best->q_first ? dealt_time(best_q, best_kv, cus, w.uneven, kTail) : dealt_time(best_kv, best_q, cus, w.uneven, kTail));
   return least;
 }
 

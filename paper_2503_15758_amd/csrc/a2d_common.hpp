@@ -221,7 +221,7 @@ inline double walk_time(const WalkModel& w, int parts) {
 // the best number of parts up to `cap` (ties: the smaller); a split costs merge_us, a launch behind the
 // tile kernel, and part_us per part to write and read back
 int best_parts(const WalkModel& w, int cap, double merge_us, double part_us, double* time);
-// The time of `a.n` workgroups, the ones that walk longer, followed by `b.n` others over the slots of the chip
+// The time of `a.n` workgroups, as a rule the ones that walk longer, followed by `b.n` others over the slots of the chip
 struct Kind {
   int64_t n;
   double mean, most;         // us of a workgroup, on average and at most

@@ -120,7 +120,8 @@ double one_time(const Kind& a, const Kind& b, int slots, bool uneven, double tai
   if (a.n + b.n <= slots) return a.most;
   if (uneven) {                                            // longest first
     const double even = (a.n * a.mean + b.n * b.mean) / slots + tail * b.mean;
-    return even > a.most ? even : a.most;
+    const double late = b.most > a.most ? a.n / slots * a.mean + b.most : a.most;   // (or the longest of the second kind)
+    return even > late ? even : late;
   }
   // whole turns of the first kind; then the slots it leaves free in its last turn, and the others, take the second
   const int64_t rest = a.n % slots, free = slots - rest;

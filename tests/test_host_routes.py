@@ -59,6 +59,10 @@ MEASURED = [
     (48, 6, 1282, 2778, 128, False, 0, 389.0, 516.0),
     (84, 84, 4318, 80, 80, False, 0, 118.5, 128.3),
     (2, 2, 146, 5176, 128, False, 0, 24.0, 35.0),
+    # many keys that few rows see: one launch with the dQ workgroups first, by the time of that order
+    (124, 31, 782, 5816, 64, True, 0, 133.2, 112.7),
+    (88, 22, 1364, 7717, 64, True, 0, 208.4, 179.1),
+    (24, 12, 4219, 10402, 128, True, 0, 487.7, 433.1),
 ]
 
 
