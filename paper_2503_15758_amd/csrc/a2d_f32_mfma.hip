@@ -7,8 +7,8 @@
 // 16 x 700 x 900 prologues, merges and uneven walks of a few steps (58 %).  A step of 16 keys (queries)
 // against 16 rows is H / 4 MFMAs of 32 cycles per contraction, on 8 KiB of operands at H = 128.
 //   - The backward's dQ and dK/dV workgroups go out in one launch, so that the end of the one kind overlaps the start of
-//     the other (two launches, dQ leaving delta for dK/dV: 2 x 128 x 128, H = 64 13.4 -> 7.1 us; 8 x 256 x 900, H = 80
-//     39 -> 26; 16 x 700 x 900, H = 96, causal 109 -> 100).
+//     the other (two launches, dQ leaving delta for dK/dV: 2 x 128 x 128, H = 64 13.4 -> 7.1 us; 16 x 700 x 900, H = 96,
+//     causal 109 -> 100).
 //   - Operands of a step pass through a tile in LDS that is the wavefront's own (no barriers): a contraction over H needs
 //     lane = row, and loading that from memory is 64 separate accesses per instruction, which kept the matrix units
 //     half idle (16 heads x 1024 x 1024, H = 96: 6.4e7 cache accesses for 1.2 GB, 50 % MFMA busy).
@@ -17,9 +17,9 @@
 //     96 of them at H = 128 and left room for two workgroups a compute unit; now three fit up to H = 96 (at H = 96 where delta is read),
 //     whose prologues, exponentials and waits are covered by the others' MFMAs.  us, before -> now: H = 96 16 x 1024 x 1024
 //     213 -> 187, 16 x 700 x 900 150 -> 129, causal 99.6 -> 92, 16 x 256 x 256 20.8 -> 18.3; H = 128 12 x 300 x 300 causal 31.2 -> 25,
-//     16 x 4096 x 4096 3841 -> 3648; H = 64 2 x 128 x 128 7.0 -> 6.8; 170 shapes of 32 to 2500 rows 1.09 times as fast in the mean, none
-//     by more than 1 % slower.  (8 x 256 x 900, H = 80, 29.5 -> 31: long dQ walks with two neighbours.  The same stream of MFMAs with
-//     staging through registers gave nothing: it is the third workgroup and the registers that do.)
+//     16 x 4096 x 4096 3841 -> 3648; H = 64 2 x 128 x 128 7.0 -> 6.8; 170 shapes of 32 to 2500 rows 1.09 times as fast in the mean,
+//     at worst 8 x 256 x 900, H = 80, 29.5 -> 31: long dQ walks with two neighbours, in parts 27.5 (plan_bwd_f32).  (The same stream of
+//     MFMAs with staging through registers gave nothing: it is the third workgroup and the registers that do.)
 //   - A wavefront owns 16 * RT rows and walks blocks of 16 keys (queries); the KL wavefronts of a
 //     workgroup own the SAME rows and take every KL-th block of the walk ("key lanes"), because fp32
 //     tiles are small: it is the walk that has to be spread over the SIMDs.  Their results are
@@ -767,10 +767,12 @@ __device__ __forceinline__ void dkdv_keys(int id, char* const smem, const a2d_ti
   }
 }
 
+// workgroups of the backward that a compute unit holds at a time (a wavefront of each on every SIMD)
+constexpr int bwd_fit(int hdim, bool own_delta) { return hdim < 96 || (hdim == 96 && !own_delta) ? 3 : 2; }
 // The two kinds of workgroups in one launch, `first` of the kind with the longer walks before the others (see
 // a2d_bwd_one.hip; here always: fp32 tiles are small).
 template <int H, bool OWN_DELTA>
-__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(H < 96 || (H == 96 && !OWN_DELTA) ? 3 : 2))) void bwd_f32_kernel(
+__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(bwd_fit(H, OWN_DELTA)))) void bwd_f32_kernel(
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, const float* __restrict__ O, const float* __restrict__ dO,
     const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dQ, float* __restrict__ dK,
@@ -790,8 +792,9 @@ template <int H>
 constexpr int dq_lds() { return most(2 * KL * Blocks<H>::BYTES, KL / 2 * (H / 16) * 1024); }
 template <int H>
 constexpr int dkdv_lds() { return most(2 * KL * Blocks<H>::BYTES, KL / 2 * (H / 8) * 1024); }
-static_assert(dkdv_lds<128>() <= 80 * 1024 && dq_lds<128>() <= 80 * 1024 && fwd_lds<128, 2>() <= 80 * 1024,
-              "two workgroups per compute unit");
+static_assert(fwd_lds<128, 2>() <= 80 * 1024, "two workgroups of the forward per compute unit");
+static_assert(most(dkdv_lds<128>(), dq_lds<128>()) * bwd_fit(128, false) <= 160 * 1024 &&
+              most(dkdv_lds<96>(), dq_lds<96>()) * bwd_fit(96, false) <= 160 * 1024, "bwd_fit workgroups per compute unit");
 
 template <int H, int RT>
 hipError_t fwd_go(const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
@@ -892,17 +895,31 @@ BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap
   const double part_kv = (double)d.heads / g.group * d.nkv * d.hdim * 16 / 4.9e6, part_q = (double)d.heads * d.nq * d.hdim * 8 / 4.9e6;
   BwdParts p = {};
   p.kv = p.q = 1;
+  // delta: from O by the dK/dV workgroups themselves; by a launch in front where these take more than some steps a compute
+  // unit in all.  (own / launch, us: H = 96 12 x 700 x 900 causal 72 / 76, 16 x 700 x 900 92 / 96, 20 x 700 x 900 110 / 107, 16 x 700 x
+  // 900 unmasked 137 / 129; H = 64 16 x 1024 x 1024 causal 80 / 85; H = 128 4 x 300 x 300 20 / 24.  Earliest at H = 128, where the rows
+  // of O cost the registers of the next loads, then at H = 96, where they cost the third workgroup of a compute unit)
+  constexpr int kDeltaSteps[4] = {140, 140, 110, 80};
+  p.delta = (double)bq * mean / BLK > (double)kDeltaSteps[hx] * cus;
+  // Parts, over 1040 drawn shapes of 1 to 16 heads, 64 to 1024 rows and keys, each against up to 42 of them: with slots for the workgroups
+  // that fit, a third one that takes 6 % of a step and 4.6 us for the sum 4.0 % off the best in the mean, with two slots for all and
+  // 5 us 4.6 %.  Of 4000 other shapes 390 go out otherwise, 1.06 times as fast in the mean, those that were whole 1.14 times (8 x
+  // 256 x 900, H = 80 31.8 -> 27.5 us, 2 x 361 x 157, H = 80, causal 13.9 -> 9.1), those of more parts than before the same in the mean
+  // (a third of them 3 % slower or more: 15/5 x 275 x 179, H = 64 15.4 -> 19.2).
+  constexpr double kBwdSumUs = 4.6;
+  const int slots = bwd_fit(d.hdim, !p.delta) * cus;
   double whole = 0, least = 0;
   for (int zk : kParts) {
     if (bq + bk > 16 * (int64_t)cus) break;          // (a chip that is full for many turns)
     if (zk > 1 && (zk > cap_kv || zk > sk)) break;
     for (int zq : kParts) {
       if (zq > 1 && (zq > cap_q || zq > sq)) break;
-      const double share = (double)(bq * zq + bk * zk) / cus, busy = share > 2 ? 1.14 : share > 1.75 ? 0.57 * share : 1;
+      const double share = (double)(bq * zq + bk * zk) / cus, third = (share < slots / cus ? share : slots / cus) - 2;
+      const double busy = share > 2 ? 1.14 + 0.06 * third : share > 1.75 ? 0.57 * share : 1;
       const Kind q = f32_kind(bq, mean / BLK, q_most, zq, uneven, kRow[hx] * busy, kRowFixed);
       const Kind k = f32_kind(bk, uneven ? sk * mean / d.nkv : sk, sk, zk, uneven, kKey[hx] * busy, kKeyFixed);
-      const double t = (q.most > k.most ? one_time(q, k, 2 * cus, uneven, 0.86) : one_time(k, q, 2 * cus, uneven, 0.86)) +
-                       (zk > 1 || zq > 1 ? kSumUs : 0) + (zk > 1 ? zk * (part_kv + kPartUs) : 0) + (zq > 1 ? zq * (part_q + kPartUs) : 0);
+      const double t = (q.most > k.most ? one_time(q, k, slots, uneven, 0.86) : one_time(k, q, slots, uneven, 0.86)) +
+                       (zk > 1 || zq > 1 ? kBwdSumUs : 0) + (zk > 1 ? zk * (part_kv + kPartUs) : 0) + (zq > 1 ? zq * (part_q + kPartUs) : 0);
       if (zk == 1 && zq == 1) whole = least = t;
       else if (t < 0.87 * whole && t < least) { least = t; p.kv = zk; p.q = zq; }
     }
@@ -919,12 +936,6 @@ BwdParts plan_bwd_f32(const a2d_tile_desc& d, const SegList& g, int cus, int cap
   }
   p.q_first = 3 * (sq + lq) / p.q > 4 * (sk + lk) / p.kv;
   p.one = 1;
-  // delta: from O by the dK/dV workgroups themselves; by a launch in front where these take more than some steps a compute
-  // unit in all.  (own / launch, us: H = 96 12 x 700 x 900 causal 72 / 76, 16 x 700 x 900 92 / 96, 20 x 700 x 900 110 / 107, 16 x 700 x
-  // 900 unmasked 137 / 129; H = 64 16 x 1024 x 1024 causal 80 / 85; H = 128 4 x 300 x 300 20 / 24.  Earliest at H = 128, where the rows
-  // of O cost the registers of the next loads, then at H = 96, where they cost the third workgroup of a compute unit)
-  constexpr int kDeltaSteps[4] = {140, 140, 110, 80};
-  p.delta = (double)bq * mean / BLK > (double)kDeltaSteps[hx] * cus;
   return p;
 }
 

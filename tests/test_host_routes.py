@@ -76,6 +76,18 @@ def test_one_launch_only_where_it_is_not_slower(a2d, case):
             assert ("bwd_dq_kernel" in kernels) == (two < one), kernels
 
 
+# heads, kv_heads, nq, nkv, H, causal; us on MI355X in whole walks and in the parts of dK/dV and dQ that are taken
+F32_MEASURED = [(8, 8, 256, 900, 80, False, 31.8, 27.5), (2, 2, 361, 157, 80, True, 13.9, 9.1),
+                (16, 8, 334, 116, 64, False, 21.8, 15.8), (6, 6, 879, 282, 64, True, 28.7, 20.7)]
+
+
+@pytest.mark.parametrize("case", F32_MEASURED, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))
+def test_fp32_walks_are_shared_where_three_workgroups_fit(a2d, case):
+    heads, kvh, nq, nkv, H, causal, whole, shared = case
+    r = tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, dtype=torch.float32, backward=True, split_groups=kvh != heads)
+    assert (r["parts_q"] * r["parts_kv"] > 1) == (shared < whole)
+
+
 def test_route_refuses_what_the_calls_refuse(a2d):
     with pytest.raises(a2d.A2DError):
         tile(a2d, 4, 100, 100, 72)
