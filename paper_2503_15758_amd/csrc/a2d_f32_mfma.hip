@@ -108,14 +108,13 @@ __device__ __forceinline__ T lload(lds_t p) { return *reinterpret_cast<__attribu
 template <typename T>
 __device__ __forceinline__ void lstore(lds_t p, T v) { *reinterpret_cast<__attribute__((address_space(3))) T*>(p) = v; }
 
-// A wavefront's tile of 16 rows in LDS.  It is written and read by that wavefront alone, whose LDS
+// A wavefront's tile of 16 rows in LDS (the forward's).  It is written, by columns, and read, by rows, by that wavefront alone, whose LDS
 // operations complete in order.
 template <int H>
 struct Tile {
   static constexpr int LD = H * 4 + 16, BYTES = 16 * LD;
-  lds_t base, nat, col;                      // + this lane's place for natural rows, and for columns (row 4 g)
+  lds_t nat, col;                            // this lane's place for natural rows, and for columns (row 4 g)
   __device__ __forceinline__ void init(lds_t b, int l15, int g4) {
-    base = b;
     nat = b + l15 * LD + 16 * g4;
     col = b + 4 * g4 * LD + 16 * l15;
   }
@@ -131,21 +130,12 @@ struct Tile {
     }
   }
   __device__ __forceinline__ f32x4 row(int y) const { return lload<f32x4>(nat + 64 * y); }
-  __device__ __forceinline__ void cols(Cols<H>& c, int r, int l15) const {
-    constexpr int N4 = Cols<H>::N4, REST = Cols<H>::REST;
-#pragma unroll
-    for (int G = 0; G < N4; ++G) c.a[G] = lload<f32x4>(col + r * LD + 256 * G);
-    if constexpr (REST == 32) {
-      const f32x2 w = lload<f32x2>(col - 8 * l15 + r * LD + 256 * N4);
-      c.b[0] = w[0]; c.b[1] = w[1];
-    }
-    if constexpr (REST == 16) c.b[0] = lload<float>(col - 12 * l15 + r * LD + 256 * N4);
-  }
 };
 
 // A wavefront's tile of 16 rows that is loaded straight into LDS (see mfma::Blocks16: here a block is 16 rows x 16 columns).
 // Blocks lie 64 bytes more than their size apart, so that the columns' reads, which take 64 bytes of four blocks at a time,
-// meet every bank once too.
+// meet every bank once too.  (Not so those of the last 32 columns at H = 96, which meet half of the banks twice, and of the last 16 at
+// H = 80, a quarter four times: 10 % of the kernel's LDS cycles at H = 96.)
 template <int H>
 struct Blocks {
   static constexpr int N = H / 16, N4 = Cols<H>::N4, REST = Cols<H>::REST, STRIDE = mfma::BLOCK + 64, BYTES = N * STRIDE;
@@ -268,21 +258,6 @@ __device__ __forceinline__ void dot_rows(f32x4 (&out)[RT], const Tile<H>& a, con
   for (int t = 0; t < RT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) out[t][r] += s1[t][r];
-}
-
-// acc += tile^T * b: rows 4 g + r in step r
-template <int H>
-__device__ __forceinline__ void contract_tile(Out<H>& acc, const Tile<H>& a, const f32x4& b, int l15) {
-  Cols<H> ring[2];
-  a.cols(ring[0], 0, l15);
-  a.cols(ring[1], 1, l15);
-  __builtin_amdgcn_sched_barrier(0);
-  static_for<0, 4>([&](auto R) {
-    constexpr int r = decltype(R)::value;
-    acc.contract(ring[r & 1], b[r]);
-    if constexpr (r < 2) a.cols(ring[r & 1], r + 2, l15);
-    __builtin_amdgcn_sched_barrier(0);
-  });
 }
 
 // The backward's two contractions over H of a step, s = rows of `a` . fa and d = rows of `b` . fb, as one stream of MFMAs: the
