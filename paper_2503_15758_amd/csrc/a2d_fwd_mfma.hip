@@ -49,11 +49,24 @@ __host__ __device__ constexpr int fwd_lds(int waves, int hd, int kl) {
   return tiles > rows ? tiles : rows;
 }
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
-constexpr double kStepUs[3] = {1.25, 1.45, 1.66};   // a 64-key step of a 256-row workgroup, H = 64 / 96 / 128
-// a round of 256 keys of 32 rows, of 128 keys of 64 rows: in tiles (the fits below); in calls over a grid, whose
-// walks of every length make them wait for each other (350 grids: 2.0 % off the best form with these and with the tiles')
-constexpr double kSmallRoundUs[2][3] = {{0.90, 1.18, 1.58}, {0.95, 1.42, 1.65}}, kSmallFixedUs[2][3] = {{2.9, 3.2, 2.95}, {3.1, 3.5, 3.2}};
-constexpr double kPairRoundUs[2][3] = {{0.85, 1.27, 1.28}, {0.95, 1.25, 1.37}}, kPairFixedUs[2][3] = {{4.06, 3.83, 3.83}, {4.1, 4.3, 4.4}};
+// The plan's costs in us, of tiles (the fit below) and of calls over a grid, whose walks of every length make them wait for each
+// other (350 grids: 2.0 % off the best form with these and with the tiles').  Three values: H = 64 / 80, 96 / 128.
+struct FwdCosts {
+  double step[3];                     // a 64-key step of a 256-row workgroup; ...
+  double lanes, alone, pair[3];       // ... as multiples of it, one of 128 rows in two key lanes, in four wavefronts, in two such side by side
+  double fixed, lanes_more, alone_more;   // the rest of a workgroup of 256 rows, and what the others' takes beyond
+  double big_store, lanes_store;      // more of a chip with several turns, H = 128
+  double pair_fixed, pair_store;      // of a pair, where pairs follow one another; by H / 128
+  double round32[3], fixed32[3];      // a round of 256 keys of 32 rows, of 128 keys of 64 rows
+  double round64[3], fixed64[3];
+  double merge, merge_few;            // a merge of parts: of forms of many rows, of few
+  double tail;
+};
+constexpr FwdCosts kFwdCosts[2] = {
+    {{1.056, 1.275, 1.626}, 1.134, 0.692, {1.02, 1.04, 1.173}, 4.75, 0.77, 0, 7.76, 1.11, 1.62, 3.72,
+     {0.836, 1.139, 1.396}, {3.08, 3.83, 4.19}, {0.821, 1.172, 1.289}, {4.13, 4.63, 4.96}, 4.53, 4.57, 0.412},
+    {{1.25, 1.45, 1.66}, 1.13, 0.76, {1.04, 1.04, 1.04}, 3.7, 0.8, 0.5, 0, 0, 0, 0,
+     {0.95, 1.42, 1.65}, {3.1, 3.5, 3.2}, {0.95, 1.25, 1.37}, {4.1, 4.3, 4.4}, 3.2, 4.5, 0.1}};
 
 template <int HR>
 struct FwdState {
@@ -558,29 +571,28 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
     mean = mean_visible_keys(d, *g, seen) / BN + 0.2;
   }
   const double* const sorted = mean < most ? seen : nullptr;
-  const double step = kStepUs[d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0], fixed = 3.7;
+  const int h = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0;
+  const FwdCosts& c = kFwdCosts[g->b.side > 0];
+  const double step = c.step[h];
   const double part_us = (double)heads * d.nq * (d.hdim + 2) * 8 / 4.5e6;      // written and read back at 4.5 TB/s
   const int64_t b256 = heads * ((d.nq + 255) / 256), b128 = heads * ((d.nq + 127) / 128), b64 = heads * ((d.nq + 63) / 64), b32 = heads * ((d.nq + 31) / 32);
-  // (the walks of a causal grid are of every length down to a few steps, so that the last ones end nearly together; those of 32
-  // and 64 rows wait for each other's loads all the same: 7 heads, 5166 tokens on 3 x 3, H = 128, cyclic 101 us with 0.1, 82 in pairs)
-  const double tail = g->b.side ? 0.1 : 0.5, big = g->b.side ? fixed + 1.5 : fixed;
-  const int h = d.hdim > 96 ? 2 : d.hdim > 64 ? 1 : 0, over = g->b.side > 0;
-  const double round = kSmallRoundUs[over][h], small = kSmallFixedUs[over][h];
   // (plain calls write fp32 partials, 128 KiB a workgroup of 256 rows at H = 128: those that start and end together store
   // at the rate of the memory, two side by side on a compute unit one under the other's walk.  29 x 4679 x 359, H = 96: 49 us
-  // in 256-row workgroups, 42 in pairs)
-  const double store = g->b.side ? 0 : d.hdim / 128.0;
-  const double big_fix = big + (b256 > cus ? 4.0 * store : 0), lanes_fix = fixed + 0.8 + (b128 > cus ? 2.0 * store : 0);
-  const double pair_fix = store > 0 && b128 > 2 * cus ? 2.4 + 6.1 * store : fixed + 0.5;
-  const WalkModel m[5] = {{b256, cus, mean, most, step, big_fix, 0, 0, nullptr, 0, tail},
-                          {b128, cus, mean / 2, most / 2, step * 1.13, lanes_fix, 0, 0, nullptr, 0, tail},
-                          {b128, cus, mean, most, step * 0.76, fixed, step * 1.04, pair_fix, nullptr, 0, tail},
-                          {b32, cus, mean / 4, most / 4, round, small, 0, 0, sorted, 0.25 / BN, 0.5, true},
-                          {b64, cus, mean / 2, most / 2, kPairRoundUs[over][h], kPairFixedUs[over][h], 0, 0, sorted, 0.5 / BN, 0.5, true, true}};
+  // in 256-row workgroups, 42 in pairs.  The walks of a causal grid are of every length down to a few steps, so that the last ones end
+  // nearly together; those of 32 and 64 rows wait for each other's loads all the same: 7 heads, 5166 tokens on 3 x 3, H = 128, cyclic
+  // 101 us with 0.1, 82 in pairs)
+  const double store = g->b.side ? 0 : d.hdim / 128.0, big = g->b.side ? c.fixed + 1.5 : c.fixed;
+  const double big_fix = big + (b256 > cus ? c.big_store * store : 0), lanes_fix = c.fixed + c.lanes_more + (b128 > cus ? c.lanes_store * store : 0);
+  const double pair_fix = store > 0 && b128 > 2 * cus ? c.pair_fixed + c.pair_store * store : c.fixed + c.alone_more;
+  const WalkModel m[5] = {{b256, cus, mean, most, step, big_fix, 0, 0, nullptr, 0, c.tail},
+                          {b128, cus, mean / 2, most / 2, step * c.lanes, lanes_fix, 0, 0, nullptr, 0, c.tail},
+                          {b128, cus, mean, most, step * c.alone, c.fixed, step * c.pair[h], pair_fix, nullptr, 0, c.tail},
+                          {b32, cus, mean / 4, most / 4, c.round32[h], c.fixed32[h], 0, 0, sorted, 0.25 / BN, 0.5, true},
+                          {b64, cus, mean / 2, most / 2, c.round64[h], c.fixed64[h], 0, 0, sorted, 0.5 / BN, 0.5, true, true}};
   double least = 0;
   for (int f = 0; f < 5; ++f) {
     double t;
-    const int z = best_parts(m[f], cap, f >= FWD_32 ? 4.5 : 3.2, part_us, &t);
+    const int z = best_parts(m[f], cap, f >= FWD_32 ? c.merge_few : c.merge, part_us, &t);
     if (f == 0 || t < (g->form == 0 ? 0.98 : 1.0) * least) { least = t; g->form = f; g->parts = z; }
   }
 }

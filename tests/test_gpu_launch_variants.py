@@ -64,6 +64,10 @@ ROUTES = [
     (34, 17, 142, 1108, 64, False, 0, 0),       # ... in 256 rows ...
     (17, 17, 205, 1287, 96, False, 0, 0),       # ... in four wavefronts
     (11, 11, 578, 1738, 128, True, 1393, 0),
+    (58, 29, 287, 326, 80, True, 109, 0),       # forward in two key lanes ...
+    (141, 141, 102, 398, 64, False, 0, 0),
+    (20, 10, 779, 299, 96, True, 169, 0),
+    (138, 138, 153, 133, 96, False, 0, 0),      # ... in 256 rows
 ]
 CASES = [
     (64, 64, 1100, 700, 96, True, 200, 0),      # diagonal through the tile, ragged rows and keys
