@@ -462,8 +462,11 @@ hipError_t bwd_launch_hd(Phase ph, const a2d_tile_desc& d, const SegList& g, con
 //   - with dS kept, where the caller allows it and the model says so: at H = 128 only.  Below, recomputing S and dP costs
 //     less than writing and reading dS (64 x 4096 x 4096 H = 64 1044 against 1157 us, H = 80 1268 / 1320, 16 x 2048 x 2048
 //     H = 64 79 / 103; of 262 drawn shapes of H = 64 to 96 15 % in the mean, 14 of them 2-11 % slower: 36 x 1413 x 2468, H = 96
-//     221 / 199).  At H = 128 it gains 5-9 % from two turns of unmasked tiles on (16 x 4096 x 4096 414
-//     against 445 us; 16 x 2048 x 2048, one turn, 138 / 130).
+//     221 / 199).  At H = 128, beyond six turns, it is
+//     always taken: 74 drawn shapes 1.03 times as fast in the mean, 96 x 4096 x 4096 2151 -> 2056 us, causal 1201 -> 1158, 64 x 4096 x
+//     4096 1424 -> 1355; ten of them slower, by 2 % in the mean but for 40/10 x 9013 x 522, 378 -> 429.  A whole step of 96 x 4096 x
+//     4096 tiles, forward and merges included, gains less, 5.71 -> 5.68 ms: the forward runs cooler behind a backward that recomputes.
+//     Up to six turns by the model (16 x 2048 x 2048, one turn, 138 us kept, 130 in one launch).
 //   - else dQ, recomputing, then dK/dV.
 // Parts of the dK/dV and dQ walks where their row blocks leave compute units idle, and the dQ kernels' workgroup
 // shape, as in plan_fwd_mfma; measured over 30 unmasked shapes (1 x 300 x 8000 to 32 x 2000 x 2700) and 44 causal ones.
