@@ -18,7 +18,7 @@ namespace mfma {
 // 32 x 1999 x 2777 H = 80 causal 217 -> 190 us.
 // Bound by the chip's power at 1.8-1.9 GHz with the matrix units 55 % busy, so the contractions run on
 // v_mfma_f32_16x16x32_bf16: an MFMA of 16 x 16 x 32 reads and writes half the accumulators per flop of one of 32 x 32 x 16
-// (MFMAs alone on normal operands sustain 1.94-1.99 PFLOP/s against 1.72-1.76), and H = 80 fills five column tiles of 16
+// (MFMAs alone on normal operands sustained 1.94-1.99 PFLOP/s against 1.72-1.76 in a probe that is not kept), and H = 80 fills five column tiles of 16
 // instead of three of 32.  64 x 4096 x 4096, H = 128 / 96 / 80 / 64: 1065 / 749 / 697 / 571 -> 1010 / 727 / 669 / 543 us, 1199 ->
 // 1183 with dS.  Each fragment still serves two MFMAs (the 32 keys of a wavefront), so the LDS reads are the same.
 // Q and dO go straight into LDS, which leaves the registers that V^T needs at H = 128 (from LDS it was a sixth of

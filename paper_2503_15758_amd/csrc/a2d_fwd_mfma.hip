@@ -550,15 +550,14 @@ hipError_t fwd_form(Phase ph, const a2d_tile_desc& d, const SegList& g, const vo
 // key lanes walk alternate key blocks, one per compute unit; 128-row workgroups of four wavefronts, two
 // per compute unit (each K / V tile is staged twice, but there is no merge of lanes and the last turn
 // is finer); 64- and 32-row workgroups whose four or eight key lanes share the walk (a2d_fwd_small.hip; a step is a round
-// of 128 or 256 keys).  By model, with parts > 1 where the blocks leave compute units idle and the walk is long.  The
-// constants are a fit to 95 shapes x three forms x up to five numbers of parts (1 x 128 x 128 to 96 x 1024 x
-// 2048, H = 64 and 128), to 73 of any size (worst miss 11 %) and, those of few rows, to 720 tiles of up to 1100 blocks of 32 rows,
-// H = 64 to 128, x five forms x up to six numbers of parts - 32 rows are taken up to about 256 such blocks, 64 rows up to
-// 256 of theirs, under a causal mask up to 512, with walks of 16 rounds at the most; there the choice is 1.5 % slower than the
-// best in the mean, much of it the noise of calls of 6 us.  The costs of a round were then raised by what 413 tiles of 2e6 to 2.5e8 scores
-// asked for, each with unit-scale and with peaky logits (which rescale oftener): 2.3 / 1.6 / 1.8 % off the best -> some 0.6 / 0.5 / 1 % at
-// H = 64 / 80, 96 / 128, peaky 2.7 / 1.8 / 1.4 -> 0.7 / 0.4 / 0.6 (34 x 487 x 460, H = 64, causal, peaky: 14.1 us in 32 rows, 10.5 in 64;
-// 78 x 181 x 10950, H = 128, three blocks: 493 in 64 rows, 424 in 256 and parts.  Given up: 2 x 4286 x 6231, H = 128, causal 34 -> 40).
+// of 128 or 256 keys).  By model, with parts > 1 where the blocks leave compute units idle and the walk is long.  The costs of tiles
+// are a fit to 2700 of 1 to 96 heads, 32 to 16384 rows and keys, H = 64 to 128, a fifth of them with peaky logits (which rescale
+// oftener), each in the five forms and up to nine numbers of parts: 0.7 % off the best of them in the mean, 2.0 % with the costs fitted
+// to earlier kernels.  Of 6000 other tiles 1009 went out otherwise than before, 1.065 times as fast in the mean (32/16 x 13289 x 131,
+// H = 96 70.6 -> 48.4 us, from 256 rows to pairs; a seventh of them slower by 3 % or more, at worst 70/35 x 855 x 2901, H = 128,
+// causal 24.3 -> 31.4).  32 rows are taken up to about 256 such blocks, 64 rows up to 256 of theirs, under a causal mask up to 512,
+// with walks of 16 rounds at the most.  Two at a time side by side cost more power than one of 256 rows, so that at H = 128 large tiles
+// stay there (96 x 4096 x 4096 720 us against 743, causal 400 / 406; H = 64 64 x 4096 x 4096 304 / 290).
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t heads = (int64_t)d.heads * (g->b.side ? g->b.side : 1);
   double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2, mean = most;
