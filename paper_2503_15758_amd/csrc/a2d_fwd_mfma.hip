@@ -50,11 +50,15 @@ __host__ __device__ constexpr int fwd_lds(int waves, int hd, int kl) {
 }
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
 // The plan's costs in us, of tiles (the fit below) and of calls over a grid, whose walks of every length make them wait for each
-// other (350 grids: 2.0 % off the best form with these and with the tiles').  Three values: H = 64 / 80, 96 / 128.
+// other.  Grids: a fit to 2000 of 1 to 280 heads, 8 to 2048 rows a column, 1 to 8 columns, both layouts, causal and not: 1.2 % off the
+// best form and parts in the mean, 2.2 % with the costs of earlier kernels.  Of 3000 others of 1 to 16 heads 232 go out otherwise, 1.07
+// times as fast in the mean (9 heads, 544 x 4 tokens, H = 80, causal 31.5 -> 22.2 us, from two key lanes and parts to 64 rows; a seventh
+// of them slower by 3 % or more, at worst 10/5 heads, 1095 x 3, H = 80 64.4 -> 72.8).  Three values: H = 64 / 80, 96 / 128.
 struct FwdCosts {
   double step[3];                     // a 64-key step of a 256-row workgroup; ...
   double lanes, alone, pair[3];       // ... as multiples of it, one of 128 rows in two key lanes, in four wavefronts, in two such side by side
   double fixed, lanes_more, alone_more;   // the rest of a workgroup of 256 rows, and what the others' takes beyond
+  double big_more;                    // of 256 rows
   double big_store, lanes_store;      // more of a chip with several turns, H = 128
   double pair_fixed, pair_store;      // of a pair, where pairs follow one another; by H / 128
   double round32[3], fixed32[3];      // a round of 256 keys of 32 rows, of 128 keys of 64 rows
@@ -63,10 +67,10 @@ struct FwdCosts {
   double tail;
 };
 constexpr FwdCosts kFwdCosts[2] = {
-    {{1.056, 1.275, 1.626}, 1.134, 0.692, {1.02, 1.04, 1.173}, 4.75, 0.77, 0, 7.76, 1.11, 1.62, 3.72,
-     {0.836, 1.139, 1.396}, {3.08, 3.83, 4.19}, {0.821, 1.172, 1.289}, {4.13, 4.63, 4.96}, 4.53, 4.57, 0.412},
-    {{1.25, 1.45, 1.66}, 1.13, 0.76, {1.04, 1.04, 1.04}, 3.7, 0.8, 0.5, 0, 0, 0, 0,
-     {0.95, 1.42, 1.65}, {3.1, 3.5, 3.2}, {0.95, 1.25, 1.37}, {4.1, 4.3, 4.4}, 3.2, 4.5, 0.1}};
+    {{1.099, 1.449, 1.586}, 1.13, 0.657, {0.994, 1.04, 1.086}, 3.899, 0.549, 0.64, 0, 4.97, 1.82, 1.67, 4.83,
+     {0.907, 1.211, 1.609}, {3.5, 3.39, 2.95}, {0.891, 1.288, 1.398}, {3.85, 3.78, 4.22}, 4.42, 4.65, 0.46},
+    {{1.314, 1.34, 1.62}, 1.138, 0.707, {1.033, 1.033, 1.033}, 4.06, 1.15, 0.19, 1.77, 0, 0, 0, 0,
+     {1.015, 1.119, 1.405}, {3.13, 3.84, 3.97}, {0.888, 1.125, 1.315}, {4.48, 4.18, 4.66}, 3.55, 4.66, 0.141}};
 
 template <int HR>
 struct FwdState {
@@ -552,12 +556,13 @@ hipError_t fwd_form(Phase ph, const a2d_tile_desc& d, const SegList& g, const vo
 // is finer); 64- and 32-row workgroups whose four or eight key lanes share the walk (a2d_fwd_small.hip; a step is a round
 // of 128 or 256 keys).  By model, with parts > 1 where the blocks leave compute units idle and the walk is long.  The costs of tiles
 // are a fit to 2700 of 1 to 96 heads, 32 to 16384 rows and keys, H = 64 to 128, a fifth of them with peaky logits (which rescale
-// oftener), each in the five forms and up to nine numbers of parts: 0.7 % off the best of them in the mean, 2.0 % with the costs fitted
-// to earlier kernels.  Of 6000 other tiles 1009 went out otherwise than before, 1.065 times as fast in the mean (32/16 x 13289 x 131,
-// H = 96 70.6 -> 48.4 us, from 256 rows to pairs; a seventh of them slower by 3 % or more, at worst 70/35 x 855 x 2901, H = 128,
-// causal 24.3 -> 31.4).  32 rows are taken up to about 256 such blocks, 64 rows up to 256 of theirs, under a causal mask up to 512,
-// with walks of 16 rounds at the most.  Two at a time side by side cost more power than one of 256 rows, so that at H = 128 large tiles
-// stay there (96 x 4096 x 4096 720 us against 743, causal 400 / 406; H = 64 64 x 4096 x 4096 304 / 290).
+// oftener), each in the five forms and up to nine numbers of parts, on three sets of inputs in turn (on one set, which stays in the caches,
+// the forms that read more come out too well): 0.7 % off the best of them in the mean, 2.0 % with the costs fitted to earlier kernels
+// (tiles that became slower count double in the fit).  Of 6000 other tiles 740 go out otherwise than before, 1.09 times as fast in
+// the mean (84/21 x 12746 x 306, H = 64 204 -> 139 us, from 256 rows to pairs; an eighth of them slower by 3 % or more, at worst 4/1 x
+// 10485 x 2347, H = 128, causal 62 -> 78).  32 rows are taken up to about 256 such blocks, 64 rows up to 256 of theirs, under a
+// causal mask up to 512, with walks of 16 rounds at the most.  Two at a time side by side cost more power than one of 256 rows, so
+// that at H = 128 large tiles stay there (96 x 4096 x 4096 720 us against 743, causal 400 / 406; H = 64 64 x 4096 x 4096 304 / 290).
 void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   const int64_t heads = (int64_t)d.heads * (g->b.side ? g->b.side : 1);
   double most = (double)visible_keys(d, *g, d.nq - 1) / BN + 0.2, mean = most;
@@ -580,7 +585,7 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
   // in 256-row workgroups, 42 in pairs.  The walks of a causal grid are of every length down to a few steps, so that the last ones end
   // nearly together; those of 32 and 64 rows wait for each other's loads all the same: 7 heads, 5166 tokens on 3 x 3, H = 128, cyclic
   // 101 us with 0.1, 82 in pairs)
-  const double store = g->b.side ? 0 : d.hdim / 128.0, big = g->b.side ? c.fixed + 1.5 : c.fixed;
+  const double store = g->b.side ? 0 : d.hdim / 128.0, big = c.fixed + c.big_more;
   const double big_fix = big + (b256 > cus ? c.big_store * store : 0), lanes_fix = c.fixed + c.lanes_more + (b128 > cus ? c.lanes_store * store : 0);
   const double pair_fix = store > 0 && b128 > 2 * cus ? c.pair_fixed + c.pair_store * store : c.fixed + c.alone_more;
   const WalkModel m[5] = {{b256, cus, mean, most, step, big_fix, 0, 0, nullptr, 0, c.tail},

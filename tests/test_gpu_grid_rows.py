@@ -42,6 +42,13 @@ CASES = [
     (3, 3, 1953, 4, 64),
     (40, 5, 140, 4, 96),
     (64, 8, 802, 4, 128),
+    (32, 32, 139, 6, 128),
+    (1, 1, 583, 9, 80),
+    (54, 27, 205, 6, 96),
+    (1, 1, 560, 9, 64),
+    (4, 2, 1634, 3, 80),
+    (27, 27, 139, 7, 80),
+    (27, 27, 142, 7, 64),
 ]
 
 

@@ -99,6 +99,19 @@ def test_route_refuses_what_the_calls_refuse(a2d):
     assert g2d.route(4, 128, 72, 2, compute_units=CUS) is None
 
 
+# heads, kv_heads, nq, nkv, H, causal, q_off; us on MI355X in the form before and in the one that is taken, its rows and key lanes
+FORWARD_MEASURED = [(84, 21, 12746, 306, 64, False, 0, 204, 139, (128, 1)), (88, 44, 16347, 158, 96, False, 0, 250, 180, (128, 1)),
+                    (60, 15, 14581, 193, 96, False, 0, 187, 134, (128, 1)), (1, 1, 65, 1125, 96, False, 0, 12.3, 8.7, (32, 8)),
+                    (96, 96, 4096, 4096, 128, False, 0, 743, 720, (256, 1)), (96, 96, 4096, 4096, 128, True, 0, 406, 400, (256, 1))]
+
+
+@pytest.mark.parametrize("case", FORWARD_MEASURED, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))
+def test_forward_takes_the_form_that_is_faster_now(a2d, case):
+    heads, kvh, nq, nkv, H, causal, q_off, _, _, form = case
+    r = tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, q_off=q_off)
+    assert (r["rows"], r["lanes"]) == form and r["parts_q"] == 1, r
+
+
 def test_parts_need_scratch_memory(a2d):
     for dtype in (torch.bfloat16, torch.float32):
         for backward in (False, True):
