@@ -152,7 +152,8 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
   // 2 x 2, H = 128, causal 144 us against 120; 15 heads, 936 tokens, H = 64 28 against 33)
   const double trust = n_kv + n_q <= 3 * (int64_t)cus ? 1.04 : w.uneven && hx == 0 ? 1.15 : 0.94;
   if (small < trust * least) {
-    *best = BwdParts{1, 1, 0, 0, 1, q_first, 1};
+    // (dK and dV apart where all workgroups run at once, see a2d_bwd_small.hip)
+    *best = BwdParts{1, 1, 0, 0, 1, q_first, n_q + 2 * n_kv <= cus ? 2 : 1};
     return small;
   }
   const int keys = best->wide ? WK_KEYS : DK_KEYS, rows = best->form ? 128 : 256;
@@ -177,7 +178,7 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
 hipError_t launch_bwd_one(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                           const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ,
                           float* dK, float* dV, const BwdParts& parts, hipStream_t s) {
-  if (parts.small) return launch_bwd_small(ph, d, g, Q, K, V, O, dO, lse, dQ, dK, dV, parts.q_first, s);
+  if (parts.small) return launch_bwd_small(ph, d, g, Q, K, V, O, dO, lse, dQ, dK, dV, parts.q_first, parts.small > 1, s);
   SegList go = g;
   go.parts = parts.kv;
   if (parts.q > 1) go.acc = 0;                             // (the sum over the parts adds)

@@ -256,7 +256,7 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap);
 struct BwdParts {
   int kv, q, form, wide;     // wide: dK/dV in workgroups of 256 keys (launch_dkdv_wide)
   int one, q_first;          // one launch (launch_bwd_one), its dQ workgroups first
-  int small;                 // that of launch_bwd_small
+  int small;                 // that of launch_bwd_small: 1, or 2: dK and dV in workgroups of their own
   int keep_ds;               // dS handed from dK/dV to dQ
   int delta;                 // fp32: delta by a launch of its own
 };
@@ -314,7 +314,7 @@ hipError_t launch_bwd_one(Phase ph, const a2d_tile_desc& d, const SegList& g, co
 // the same in 32-row and 32-key workgroups (a2d_bwd_small.hip); delta is not used
 hipError_t launch_bwd_small(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                             const void* V, const void* O, const void* dO, const float* lse, float* dQ, float* dK,
-                            float* dV, int q_first, hipStream_t s);
+                            float* dV, int q_first, int split, hipStream_t s);
 // (parts > 1: the outputs are the partial buffers, [parts][heads][rows][H] each)
 hipError_t launch_bwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,
                            const void* V, const void* O, const void* dO, const float* lse, float* delta, float* dQ,

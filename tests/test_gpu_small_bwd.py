@@ -24,8 +24,16 @@ PAIRS = [
     (2, 2, 32, 32, 128, False, 0, None, False),
     (3, 1, 255, 33, 80, True, -20, None, True),
 ]
+# more workgroups than compute units: dK and dV in one (heads x blocks of 32 queries + 2 x kv_heads x blocks of 32 keys > 256)
+BOTH = [
+    (40, 40, 65, 64, 128, False, 0, None, True),
+    (24, 24, 130, 130, 80, True, 5, None, False),
+    (14, 14, 330, 330, 64, True, -10, None, True),
+    (60, 12, 70, 200, 128, True, 140, [(0, 33), (60, 167)], False),
+    (34, 34, 64, 95, 96, False, 0, None, False),
+]
 
 
-@pytest.mark.parametrize("case", CASES + PAIRS, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))
+@pytest.mark.parametrize("case", CASES + PAIRS + BOTH, ids=lambda c: "%dq%dkv_%dx%dH%d_%s" % (*c[:5], "causal" if c[5] else "full"))
 def test_small_bwd(case):
     _check(case, False)

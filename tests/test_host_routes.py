@@ -221,7 +221,7 @@ def test_few_row_cases(a2d):
             if form == (64, 4):
                 rows64.add((H, causal and q_off < 0 or segs is not None))
     assert {H for H, _ in rows64} == set(SIZES) and {(64, True), (80, True), (96, True), (128, True)} <= rows64
-    for cases, small in ((b.CASES, True), (b.PAIRS, False)):
+    for cases, small in ((b.CASES, True), (b.PAIRS, False), (b.BOTH, True)):
         for heads, kvh, nq, nkv, H, causal, q_off, segs, _ in cases:
             r = tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, q_off=q_off, segments=segs, backward=True)
             assert ("bwd_small_kernel" in r["kernels"]) == small, (heads, nq, nkv, H)
