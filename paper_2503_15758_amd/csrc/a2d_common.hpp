@@ -83,6 +83,7 @@ struct SegList {
   int by_size;
   int parts;      // workgroups that share the walk of one block, each leaving a partial result (>= 1)
   int form;       // which of its workgroup shapes a forward / dQ launch takes (plan_* below)
+  int phased;     // a forward's wavefronts in opposite phases (plan_fwd_mfma)
   Segment seg[A2D_MAX_SEGMENTS];
   GridView b;     // (last: a tile's kernels do not read it)
 };

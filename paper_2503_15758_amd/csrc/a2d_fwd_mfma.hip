@@ -27,7 +27,13 @@
 // workgroups of four would stage each tile twice).  The mask is a branch around its selects inside the one copy of the
 // block: with a copy of its own per kind of block the compiler moved the accumulators between registers.
 //
-// Rescaling is lazy: a row's exponent reference m_ref follows its running maximum
+// The two wavefronts of a SIMD (w and w + 4) start a step with the scores, so that both want the matrix unit, then both the vector
+// ALU: at H = 128 the one is busy 48 % of the cycles, the other 48 %, both at once 11 %.  PHASED keeps them in opposite phases: in the
+// interval between two barriers one goes through the MFMAs of a step (scores of block t + 1, products of block t) and then the softmax of
+// block t + 1, the other through the softmax of block t and then the same MFMAs.  Both are busy 21 % of the cycles then, of which there are 10 %
+// fewer at a 5 % lower clock (the same power).  What is left: an MFMA of 16 cycles leaves the other wavefront two vector instructions, not
+// three, so that the 128 MFMAs and two softmaxes of a step take 2730 cycles at the least (both measured side by side); a step takes 3060.
+// Rescaling is lazy:// Rescaling is lazy: a row's exponent reference m_ref follows its running maximum
 // only when a score exceeds it by more than 2^8 (in the exponent's units) - a rare,
 // wave-uniform branch, and the only place where the lanes of a row talk to each
 // other.  Each lane tracks the true maximum of its own scores; at the end they
@@ -48,7 +54,10 @@ __host__ __device__ constexpr int fwd_lds(int waves, int hd, int kl) {
   const int tiles = kl * lds_bytes(hd), rows = waves / kl * acc_area(hd / 16);
   return tiles > rows ? tiles : rows;
 }
-constexpr float kRescaleThreshold = 8.0f;   // log2 units
+// log2 units.  (Peaky rows move their references often: at 32, 8 x 16384 x 16384, sigma 4 917 -> 874 us.  But a probability of 1, which the
+// maximum has where its row's reference has just moved, is rounded to itself, and such rows consist of little else: their results
+// were ten times as far off, 5e-4 of O instead of 3e-5.)
+constexpr float kRescaleThreshold = 8.0f;
 // The plan's costs in us, of tiles (the fit below) and of calls over a grid, whose walks of every length make them wait for each
 // other.  Grids: a fit to 2000 of 1 to 280 heads, 8 to 2048 rows a column, 1 to 8 columns, both layouts, causal and not: 1.2 % off the
 // best form and parts in the mean, 2.2 % with the costs of earlier kernels.  Of 3000 others of 1 to 16 heads 232 go out otherwise, 1.07
@@ -81,34 +90,54 @@ struct FwdState {
   float l_run[2];        // this lane's share of the row sum, relative to m_ref
 };
 
-// One 64-key block for one wavefront; at: its buffer's offset from the addresses in rd.  S^T in tiles of 16 keys (k) x 16 queries (q): lane = query, registers = keys 16 k + 4 grp +
-// 0..3; the registers of two key tiles are the eight contraction indices of a lane in O^T += V^T P^T.
-// masked: some of the wavefront's rows do not see all of its keys.
-template <int HR>
-__device__ __forceinline__ void fwd_block(FwdState<HR>& st, const bf16x8 (&qf)[padded_head(HR) / 32][2],
-                                          const Blocks16& rd, unsigned at, bool masked, int k0, const int (&my_vis)[2], int grp, float c) {
+// A 64-key block for one wavefront, in three pieces; at: its buffer's offset from the addresses in rd.  S^T in tiles of 16 keys (k) x 16
+// queries (q): lane = query, registers = keys 16 k + 4 grp + 0..3; the registers of two key tiles are the eight contraction indices of a
+// lane in O^T += V^T P^T.
+// Fragments of K and V go through rings four deep: each is requested four slots of two MFMAs before its use (the scheduling fences
+// keep the compiler from sinking the requests back to their uses), the first ones before the piece that uses them.
+using Scores = f32x4[4][2];
+using Ring = bf16x8[4];
+template <int HR, int I>                           // slot I of the scores: key tile I & 3, slice I >> 2 of H, both query tiles
+__device__ __forceinline__ void fwd_key(Ring& kr, const Blocks16& rd, unsigned at) {
+  kr[I & 3] = lds_load_b128(rd.nat + at + ((I & 3) * (padded_head(HR) / 32) + (I >> 2)) * BLOCK);
+}
+template <int HR, int I>                           // step I of the products: 32-key group I / HT, column tile I % HT
+__device__ __forceinline__ void fwd_value(Ring& vr, const Blocks16& rd, unsigned at) {
   constexpr int KS = padded_head(HR) / 32, HT = HR / 16, K_BYTES = buf_bytes(padded_head(HR)) / 2;
-  const unsigned k_rd = rd.nat + at, v_rd[2] = {rd.tr_e + at, rd.tr_o + at};
-  // K fragments go through a ring four deep: each is requested four slots of two MFMAs before its use (the
-  // scheduling fences keep the compiler from sinking the requests back to their uses)
-  f32x4 s[4][2];
+  const unsigned a = (I % HT & 1 ? rd.tr_o : rd.tr_e) + at + K_BYTES + ((I / HT) * 2 * KS + (I % HT >> 1)) * BLOCK;
+  vr[I & 3] = lds_load_tr(a, a + KS * BLOCK);
+}
+template <int HR>
+__device__ __forceinline__ void fwd_first_keys(Ring& kr, const Blocks16& rd, unsigned at) {
+  static_for<0, 4>([&](auto I) { fwd_key<HR, decltype(I)::value>(kr, rd, at); });
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <int HR>
+__device__ __forceinline__ void fwd_first_values(Ring& vr, const Blocks16& rd, unsigned at) {
+  static_for<0, 4>([&](auto I) { fwd_value<HR, decltype(I)::value>(vr, rd, at); });
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int HR>
+__device__ __forceinline__ void fwd_scores(Scores& s, Ring& kr, const bf16x8 (&qf)[padded_head(HR) / 32][2], const Blocks16& rd, unsigned at) {
+  constexpr int KS = padded_head(HR) / 32;
 #pragma unroll
   for (int k = 0; k < 4; ++k) s[k][0] = s[k][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 kr[4];
-  // slot I: key tile I & 3, slice I >> 2 of H, both query tiles
-  auto ldk = [&](auto I) {
-    constexpr int i = decltype(I)::value;
-    kr[i & 3] = lds_load_b128(k_rd + ((i & 3) * KS + (i >> 2)) * BLOCK);
-  };
-  static_for<0, 4>(ldk);
-  __builtin_amdgcn_sched_barrier(0);
   static_for<0, 4 * KS>([&](auto I) {
     constexpr int i = decltype(I)::value;
 #pragma unroll
     for (int q = 0; q < 2; ++q) s[i & 3][q] = mma16(kr[i & 3], qf[i >> 2][q], s[i & 3][q]);
-    if constexpr (i + 4 < 4 * KS) ldk(std::integral_constant<int, i + 4>{});
+    if constexpr (i + 4 < 4 * KS) fwd_key<HR, i + 4>(kr, rd, at);
     __builtin_amdgcn_sched_barrier(0);
   });
+}
+
+// masked: some of the wavefront's rows do not see all of the block's keys
+// (values: called in front of the exponentials)
+template <int HR, class F>
+__device__ __forceinline__ void fwd_softmax(FwdState<HR>& st, Scores& s, bf16x8 (&pb)[2][2], bool masked, int k0,
+                                            const int (&my_vis)[2], int grp, float c, F&& values) {
+  constexpr int HT = HR / 16;
   if (A2D_SELDOM(masked)) {
     asm volatile("" ::: "memory");   // keep this a branch
 #pragma unroll
@@ -144,17 +173,7 @@ __device__ __forceinline__ void fwd_block(FwdState<HR>& st, const bf16x8 (&qf)[p
         for (int r = 0; r < 4; ++r) st.o[t][q][r] *= alpha;
     }
   }
-  // V^T fragments (step I: 32-key group I / HT, column tile I % HT) go through a ring four deep
-  // as well; the first four are requested before the exponentials
-  bf16x8 vr[4];
-  auto ldv = [&](auto I) {
-    constexpr int i = decltype(I)::value;
-    const unsigned a = v_rd[i % HT & 1] + K_BYTES + ((i / HT) * 2 * KS + (i % HT >> 1)) * BLOCK;
-    vr[i & 3] = lds_load_tr(a, a + KS * BLOCK);
-  };
-  static_for<0, 4>(ldv);
-  __builtin_amdgcn_sched_barrier(0);
-  bf16x8 pb[2][2];
+  values();
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const float mc = (st.m_ref[q] == -INFINITY) ? 0.f : st.m_ref[q] * c;
@@ -168,11 +187,17 @@ __device__ __forceinline__ void fwd_block(FwdState<HR>& st, const bf16x8 (&qf)[p
     st.l_run[q] += psum;
   }
   __builtin_amdgcn_sched_barrier(0);
+}
+
+// O^T += V^T P^T
+template <int HR>
+__device__ __forceinline__ void fwd_products(FwdState<HR>& st, const bf16x8 (&pb)[2][2], Ring& vr, const Blocks16& rd, unsigned at) {
+  constexpr int HT = HR / 16;
   static_for<0, 2 * HT>([&](auto I) {
     constexpr int i = decltype(I)::value;
 #pragma unroll
     for (int q = 0; q < 2; ++q) st.o[i % HT][q] = mma16(vr[i & 3], pb[i / HT][q], st.o[i % HT][q]);
-    if constexpr (i + 4 < 2 * HT) ldv(std::integral_constant<int, i + 4>{});
+    if constexpr (i + 4 < 2 * HT) fwd_value<HR, i + 4>(vr, rd, at);
     __builtin_amdgcn_sched_barrier(0);
   });
 }
@@ -186,6 +211,7 @@ __device__ __forceinline__ void fwd_block(FwdState<HR>& st, const bf16x8 (&qf)[p
 //           blocks of the walk, each staging its own tiles into its own pair of LDS buffers, and
 //           their (N, m, l) are merged through LDS at the end exactly as two partials of one
 //           query block are (Alg. 2).
+// PHASED: see above; of two key lanes one is behind the other.
 // HR: head size = row length in memory (64, 80, 96 or 128); the LDS tiles and fragments are laid out
 // for the padded head size HD = padded_head(HR) (64, 96 or 128).
 // (O_part, m_out and l_out are not __restrict__: an accumulating call's `in` is the same memory)
@@ -194,7 +220,7 @@ __device__ __forceinline__ void fwd_block(FwdState<HR>& st, const bf16x8 (&qf)[p
 // the sequence (or, of a split walk, a partial of them: [part][row block][head][row]).  The tiles of a row of
 // contiguous blocks are one run of keys.  Of cyclic ones, block j of every column comes before block j + 1 of any:
 // the workgroups of a head, which see different numbers of keys, then read the same part of the sequence at a time.
-template <int WAVES, int HR, int KL, int GRID>
+template <int WAVES, int HR, int KL, int GRID, bool PHASED>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     a2d_tile_desc d, SegList g, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
     const bf16_t* __restrict__ V, float* O_part, float* m_out, float* l_out, FwdInput in) {
@@ -357,10 +383,15 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     ld_row_bytes[x] = __builtin_amdgcn_readfirstlane((unsigned)(v ? d.lv.row : d.lk.row) * 2);
     ld_col_bytes[x] = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)((v ? g.b.v : g.b.k) * 2)) : ld_row_bytes[x];
   }
-  auto load_tile = [&](int seg_start, int seg_rows, int j, int boff) {
-    const int r = min(ld_row, seg_rows - 1 - j * BN);
+  struct Entry {                                   // block j of the nblk of sub-block sb, which starts at `start`
+    int sb, j, nblk, start, rows;
+  };
+  // (which: bit 0 K, bit 1 V, of those that this wavefront loads)
+  auto load_tile = [&](int which, const Entry& e, int boff) {
+    const int seg_start = e.start, j = e.j, r = min(ld_row, e.rows - 1 - j * BN);
 #pragma unroll
     for (int x = 0; x < LD_N; ++x) {
+      if (!(which >> (ld_first + x) & 1)) continue;
       const gptr_t base = uniform_gptr(ld_base[x] + (seg_start * ld_col_bytes[x] + (unsigned)(j * BN) * ld_row_bytes[x]));
       dma_blocks<KS, H>(lds_base + boff + (4 * (ld_first + x) + ld_tile) * KS * BLOCK, base,
                         __umul24(r, ld_row_bytes[x]) + 16 * ld_chunk, ld_chunk);
@@ -414,39 +445,112 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // cyclic: query i sees the keys kk <= i of columns up to its row block's own, kk < i of the others - the mask of the
   // former with the keys numbered one higher
   const int shift_from = CYCLIC && d.causal ? row_blk : segs;
-  int sb, j = 0, nblk = 0;                         // this key lane's current entry
-  open_segment(0, sb, nblk);
-  advance(part * KL, sb, j, nblk);
-  int lead_sb = sb, lead_j = j, lead_nblk = nblk;  // key lane 0's: every lane of the workgroup loops while it exists
-  if (KL > 1) advance(kl, sb, j, nblk);
-  int nx_start = 0, nx_rows = 0;                   // start / rows of the next entry's sub-block
-  if (sb < segs) {
-    enter_segment(sb);
-    nx_start = seg_start(sb); nx_rows = seg_rows(sb);
-    load_tile(nx_start, nx_rows, j, 0);
+  auto step_to = [&](Entry& e, int by) {
+    const int old = e.sb;
+    advance(by, e.sb, e.j, e.nblk);
+    if (CYCLIC) e.start = e.sb;
+    else if (A2D_SELDOM(e.sb != old && e.sb < segs)) { e.start = seg_start(e.sb); e.rows = seg_rows(e.sb); }
+  };
+  Entry e0 = {0, 0, 0, 0, grid_rows};              // this key lane's current entry ...
+  open_segment(0, e0.sb, e0.nblk);
+  if (e0.sb < segs) { e0.start = seg_start(e0.sb); e0.rows = seg_rows(e0.sb); }
+  step_to(e0, part * KL);
+  Entry lead = e0;                                 // key lane 0's: every lane of the workgroup loops while it exists
+  if (KL > 1) step_to(e0, kl);
+  Entry e1 = e0;                                   // ... the next
+  if (e0.sb < segs) {
+    enter_segment(e0.sb);
+    load_tile(3, e0, 0);
+    step_to(e1, stride);
+    if (PHASED && e1.sb < segs) load_tile(1, e1, BUF_BYTES);
   }
-  // (one wait for the Q rows and the first tile: the two latencies overlap)
+  // (one wait for the Q rows and the first tiles: the latencies overlap)
   wait_vmem_all();
 #pragma unroll
   for (int q = 0; q < 2; ++q) st.m_lane[q] = st.m_ref[q] = m_in[q] / d.scale;      // -inf stays -inf
   __syncthreads();
 
-  int boff = 0;
-  while ((KL == 1 ? sb : lead_sb) < segs) {
-    int nsb = sb, nj = j, nnblk = nblk;
-    advance(stride, nsb, nj, nnblk);
-    const bool more = nsb < segs;
-    if (CYCLIC) nx_start = nsb;
-    else if (A2D_SELDOM(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
-    if (A2D_OFTEN(more)) load_tile(nx_start, nx_rows, nj, BUF_BYTES - boff);
-    const int k0 = j * BN + (CYCLIC && sb > shift_from);       // local to the sub-block
-    if ((KL == 1 || sb < segs) && k0 < nvis_wave) fwd_block<HR>(st, qf, rd, boff, k0 + BN > nfull_wave, k0, my_vis, grp, c);
-    wait_vmem_all();
-    __syncthreads();
-    if (!CYCLIC && A2D_SELDOM(more && nsb != sb)) enter_segment(nsb);
-    if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
-    sb = nsb; j = nj; nblk = nnblk;
-    boff = BUF_BYTES - boff;
+  Scores s;
+  Ring kr, vr;
+  bf16x8 pb[2][2];
+  int k0 = 0, boff = 0;
+  bool seen = false, masked = false;
+  auto look_at = [&](const Entry& e) {
+    k0 = e.j * BN + (CYCLIC && e.sb > shift_from);             // local to the sub-block
+    seen = e.sb < segs && k0 < nvis_wave;
+    masked = k0 + BN > nfull_wave;
+  };
+  if constexpr (PHASED) {
+    // Interval t lies between the barriers t and t + 1.  In it wavefronts that are `behind` do the softmax of block t and then
+    // the MFMAs - scores of block t + 1, products of block t -, the others these MFMAs and then the softmax of block t + 1: one sequence
+    // for both, with the barrier at another place.  Requested right behind barrier t, used from barrier t + 1 on: K of block t + 2 into the
+    // buffer of block t (its scores were made in the interval before), V of block t + 1 into that of block t - 1.
+    // (Fragments requested earlier - the first of V in front of the exponentials or of the scores, the products in front of the
+    // scores - cost 1-3 %: the wavefront that waits for them leaves the other one the vector ALU.)
+    const bool behind = KL == 2 ? kl == 1 : wave >= 4;
+    look_at(e0);
+    if (seen) {
+      fwd_first_keys<HR>(kr, rd, 0);
+      fwd_scores<HR>(s, kr, qf, rd, 0);
+    }
+    if (behind) __syncthreads();
+    while ((KL == 1 ? e0.sb : lead.sb) < segs) {
+      Entry e2 = e1;
+      if (e1.sb < segs) step_to(e2, stride);
+      auto request = [&]() {
+        if (A2D_OFTEN(e2.sb < segs)) load_tile(1, e2, boff);
+        if (A2D_OFTEN(e1.sb < segs)) load_tile(2, e1, BUF_BYTES - boff);
+      };
+      if (behind) request();                       // (the others: behind the barrier below)
+      const bool mine = seen;
+      if (mine)
+        fwd_softmax<HR>(st, s, pb, masked, k0, my_vis, grp, c, []() {});
+      if (!behind) {
+        wait_vmem_all();
+        __syncthreads();
+        request();
+      }
+      if (!CYCLIC && A2D_SELDOM(e1.sb != e0.sb && e1.sb < segs)) enter_segment(e1.sb);
+      __builtin_amdgcn_s_setprio(0);               // (the softmax first, where both want to issue)
+      look_at(e1);
+      if (seen) {
+        fwd_first_keys<HR>(kr, rd, BUF_BYTES - boff);
+        fwd_scores<HR>(s, kr, qf, rd, BUF_BYTES - boff);
+      }
+      if (mine) {
+        fwd_first_values<HR>(vr, rd, boff);
+        fwd_products<HR>(st, pb, vr, rd, boff);
+      }
+      __builtin_amdgcn_s_setprio(1);
+      if (behind) {
+        wait_vmem_all();
+        __syncthreads();
+      }
+      if (KL > 1) step_to(lead, stride);
+      e0 = e1;
+      e1 = e2;
+      boff = BUF_BYTES - boff;
+    }
+    if (!behind) __syncthreads();                  // (as many barriers for all)
+    __builtin_amdgcn_s_setprio(0);
+  } else {
+    while ((KL == 1 ? e0.sb : lead.sb) < segs) {
+      if (A2D_OFTEN(e1.sb < segs)) load_tile(3, e1, BUF_BYTES - boff);
+      look_at(e0);
+      if (seen) {
+        fwd_first_keys<HR>(kr, rd, boff);
+        fwd_scores<HR>(s, kr, qf, rd, boff);
+        fwd_softmax<HR>(st, s, pb, masked, k0, my_vis, grp, c, [&]() { fwd_first_values<HR>(vr, rd, boff); });
+        fwd_products<HR>(st, pb, vr, rd, boff);
+      }
+      wait_vmem_all();
+      __syncthreads();
+      if (!CYCLIC && A2D_SELDOM(e1.sb != e0.sb && e1.sb < segs)) enter_segment(e1.sb);
+      if (KL > 1) step_to(lead, stride);
+      e0 = e1;
+      if (e1.sb < segs) step_to(e1, stride);
+      boff = BUF_BYTES - boff;
+    }
   }
 
   // ---- epilogue: bring N and l to the true row maximum, store N, m (scaled units), l
@@ -520,14 +624,14 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
 }  // namespace
 
 namespace {
-template <int WAVES, int HR, int KL, int GRID>
+template <int WAVES, int HR, int KL, int GRID, bool PHASED = false>
 hipError_t fwd_launch(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K, const void* V,
                       float* O_part, float* m, float* l, const FwdInput& in, hipStream_t s) {
   constexpr int bytes = fwd_lds(WAVES, padded_head(HR), KL), BM = 32 * WAVES / KL;
   if (ph == PREPARE)
-    return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_mfma_kernel<WAVES, HR, KL, GRID>), bytes);
+    return ensure_dynamic_lds(reinterpret_cast<const void*>(fwd_mfma_kernel<WAVES, HR, KL, GRID, PHASED>), bytes);
   dim3 grid(xcd_grid(d.heads / g.group * g.parts, (GRID ? g.b.side : 1) * g.group * ((d.nq + BM - 1) / BM))), block(64 * WAVES);
-  A2D_LAUNCH((fwd_mfma_kernel<WAVES, HR, KL, GRID>), grid, block, bytes, s, d, g, (const bf16_t*)Q,
+  A2D_LAUNCH((fwd_mfma_kernel<WAVES, HR, KL, GRID, PHASED>), grid, block, bytes, s, d, g, (const bf16_t*)Q,
                      (const bf16_t*)K, (const bf16_t*)V, O_part, m, l, in);
   return hipGetLastError();
 }
@@ -542,6 +646,9 @@ hipError_t fwd_form(Phase ph, const a2d_tile_desc& d, const SegList& g, const vo
   return g.form == FWD_BIG     ? fwd_launch<8, HR, 1, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s) \
          : g.form == FWD_LANES ? fwd_launch<8, HR, 2, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s) \
                                : fwd_launch<4, HR, 1, GRID>(ph, d, g, Q, K, V, O_part, m, l, in, s)
+  if (d.hdim == 128 && g.phased)
+    return g.form == FWD_BIG ? fwd_launch<8, 128, 1, GRID, true>(ph, d, g, Q, K, V, O_part, m, l, in, s)
+                             : fwd_launch<8, 128, 2, GRID, true>(ph, d, g, Q, K, V, O_part, m, l, in, s);
   if (d.hdim == 128) { A2D_FWD(128); }
   if (d.hdim == 96) { A2D_FWD(96); }
   if (d.hdim == 80) { A2D_FWD(80); }
@@ -599,6 +706,14 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
     const int z = best_parts(m[f], cap, f >= FWD_32 ? c.merge_few : c.merge, part_us, &t);
     if (f == 0 || t < (g->form == 0 ? 0.98 : 1.0) * least) { least = t; g->form = f; g->parts = z; }
   }
+  // Opposite phases (PHASED), walks in order / in phases, us: 96 x 4096 x 4096, unmasked and then causal 1145 -> 1120, 21 x 2194 x 5272
+  // 132.9 -> 124.8, 16/2 x 2416 x 3675 94.6 -> 89.1, 16 x 2048 x 2048 38.2 -> 36.8, 40/8 x 1300 gathered 71.2 -> 68.0.  They begin and end
+  // with half a step that nothing stands beside, so that walks of a few steps lose: 9 x 2616 x 288 19.9 -> 20.9, 19 x 2218 x 213,
+  // causal 14.8 -> 15.3, 9/3 x 4618 x 796 34.0 -> 34.6; from some 14 steps on they win.  Below H = 128, where a step's softmax is as long
+  // as its MFMAs, they lose oftener than they win: 72/9 x 2302 x 7437, H = 96 487 -> 469, but 39 x 9559 x 1886, H = 80 916 -> 957, 9 x
+  // 4032 x 1332, H = 64 28.5 -> 31.4.
+  constexpr double kPhasedSteps = 14;
+  g->phased = d.hdim == 128 && g->form <= FWD_LANES && mean >= kPhasedSteps * g->parts * (g->form == FWD_LANES ? 2 : 1);
 }
 
 hipError_t launch_fwd_mfma(Phase ph, const a2d_tile_desc& d, const SegList& g, const void* Q, const void* K,

@@ -44,6 +44,30 @@ def test_forward_tile_edges(rows, case):
     forward.test_small_rows(case)
 
 
+# walks of 64-key steps: from one step on, and (H = 128, from 14 steps of a key lane on) those whose wavefronts go through them in
+# opposite phases; key lanes with unlike numbers of steps, sub-blocks that rows or all of a block see nothing of, in front, in between and behind
+WALKS = [(form, (heads, heads, nq, nkv, H, causal, q_off, segs, packed, 2))
+         for form, heads, nq, nkv, H, causal, q_off, segs, packed in [
+             ((256, 1), 250, 250, 1, 128, False, 0, None, False), ((256, 1), 250, 250, 65, 80, True, -100, None, True),
+             ((256, 1), 250, 250, 264, 96, True, 20, [(300, 64), (0, 130), (90, 70)], True),
+             ((128, 2), 120, 256, 385, 128, False, 0, None, False), ((128, 1), 250, 128, 700, 64, True, -60, None, False),
+             # opposite phases
+             ((256, 1), 200, 250, 897, 128, False, 0, None, False), ((256, 1), 200, 250, 961, 128, True, 900, None, True),
+             ((256, 1), 200, 250, 1218, 128, True, 1000, [(0, 65), (2000, 70), (90, 1018), (1100, 65)], False),
+             ((256, 1), 200, 250, 1100, 128, True, 960, [(1300, 64), (0, 965), (990, 71)], False),
+             ((128, 2), 120, 256, 1857, 128, False, 0, None, False), ((128, 2), 120, 256, 1921, 128, True, 1730, None, True),
+             ((128, 2), 120, 256, 2000, 128, True, 1900, [(2200, 64), (0, 1800), (1850, 71), (3000, 65)], False)]]
+
+
+@pytest.mark.parametrize("form,case", WALKS, ids=lambda c: "%dx%dH%d_%d" % (c[2], c[3], c[4], c[6]) if len(c) > 2 else "%dx%d" % c)
+def test_forward_walks(form, case):
+    from paper_2503_15758_amd import binding as a2d
+    heads, _, nq, nkv, H, causal, q_off, segs = case[:8]
+    route = a2d.tile_route(heads, nq, nkv, H, causal=causal, q_off=q_off, segments=segs)
+    assert (route["rows"], route["lanes"], route["parts_q"]) == (*form, 1), route
+    forward.test_small_rows(case)
+
+
 # fp32 backward: steps of 16 rows and keys, four key lanes; delta by a launch in front (the last four) and by the tiles themselves
 F32 = [(1, 1, 1, 1, 64, False, 0, [(0, 1)]), (2, 2, 15, 17, 80, True, 2, [(0, 17)]), (3, 3, 17, 63, 96, True, 46, [(0, 63)]),
        (2, 1, 65, 129, 128, True, 64, [(0, 129)]), (4, 2, 33, 79, 64, True, 46, [(0, 30), (40, 49)]), (5, 5, 79, 65, 96, False, 0, [(0, 65)]),
