@@ -2,10 +2,64 @@
 // plain-sum merge of gradient partials (Alg. 3 lines 4-5).  Both are pure
 // streaming kernels bound by HBM bandwidth: every input byte is read once with
 // 128-bit loads, all k loads of a thread are issued before the first use.
+#include <type_traits>
+
 #include "a2d_common.hpp"
 
 namespace a2d {
 namespace {
+
+// Each thread handles CPT 16-byte column groups and issues the loads of all of them (CPT * k
+// 128-bit loads) before the first use: the amount of data in flight per thread, not the
+// arithmetic, decides how close these kernels get to the HBM rate.
+// (read once: non-temporal loads measured 8-10 % faster than plain ones here)
+#define A2D_LD(p) __builtin_nontemporal_load(p)
+// CPT for `groups` column groups (weights: AttnFix, which holds m and l besides N).  us, one / two / four groups a thread:
+// 96 x 4096 x 128, k = 4 AttnFix 150 / 159 / 160, sum 148 / 155 / 155, k = 2 82.7 / 84.7 / 86.5; 30 x 2500 x 128, k = 6 sum 40.4 / 41.1 / 40.8,
+// AttnFix 42.6 / 42.2 / 42.8; k = 8 sum 16 x 2048 x 128 25.5 / 25.5 / 22.9, AttnFix 26.6 / 27.0 / 25.6 there, but 302 / 297 / 303 at 96 x 4096;
+// k = 16 AttnFix 16 x 8000 x 128 180 / 171, sum 179 / 169, but 75.0 / 76.8 and 72.6 / 73.1 at 16 x 4096 x 96.
+// half: groups of 8 bytes, a merge of normalised bf16 partials: 16 x 2048 x 128, k = 16 29.0 / 25.4, 96 x 4096, k = 2 one against four 63.0 / 58.2.
+constexpr int64_t kManyGroups = 1 << 21;
+constexpr int chunks_per_thread(int kmax, bool weights, int64_t groups, bool half = false) {
+  if (half && kmax == 2) return 4;
+  if (half && kmax == 16) return 2;
+  if (kmax <= 4 || kmax > 16) return 1;
+  if (kmax == 6) return 2;
+  if (kmax == 8) return weights && groups >= kManyGroups ? 2 : 4;
+  return groups >= kManyGroups ? 2 : 1;
+}
+
+// Which column groups a thread owns: its wavefront owns CPT * 64 CONSECUTIVE groups and lane l takes
+// the groups l, l + 64, ... of that run, so that every load instruction of a wavefront reads 1 KiB
+// in one piece and its CPT loads of one partial read CPT KiB in one piece.  (Measured on MI355X: a
+// read stream made of such per-wavefront runs of 4-16 KiB reaches 6.8-7.0 TB/s, the same bytes
+// requested one grid-sized stride apart 5.3-6.4 TB/s.)
+// A workgroup's groups are [first, first + rest); everything of a thread is numbered from `first` on, in 32 bits, and goes
+// through buffer descriptors of the workgroup's own share: no 64-bit arithmetic in a lane, and the loads past
+// the end give zeros without a branch (a sum of 8 partials, 96 x 4096 rows of 128: 283 -> 277 us).
+template <int CPT>
+struct Share {
+  int64_t first;
+  unsigned rest;
+  __device__ __forceinline__ explicit Share(int64_t total) {
+    first = (int64_t)blockIdx.x * (256 * CPT);
+    rest = (unsigned)min(total - first, (int64_t)(256 * CPT));
+  }
+  __device__ __forceinline__ unsigned at(int c) const { return (threadIdx.x >> 6) * (CPT * 64) + c * 64 + (threadIdx.x & 63); }
+};
+enum { NT = 2, THROUGH = 16 };                     // cache policies of the buffer instructions: read once; straight on to memory
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* p, int64_t bytes_before, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(p)) + bytes_before, 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t b, unsigned i) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, i * 4, 0, 0));
+}
+__device__ __forceinline__ void load_group(f32x4& v, __amdgpu_buffer_rsrc_t b, unsigned i) {
+  v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, i * 16, 0, NT));
+}
+__device__ __forceinline__ void load_group(bf16x4& v, __amdgpu_buffer_rsrc_t b, unsigned i) {
+  v = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(b, i * 8, 0, NT));
+}
 
 __device__ __forceinline__ void store_out4(float* O, int64_t off, f32x4 v) {
   *reinterpret_cast<f32x4*>(O + off) = v;
@@ -16,72 +70,90 @@ __device__ __forceinline__ void store_out4(bf16_t* O, int64_t off, f32x4 v) {
   *reinterpret_cast<bf16x4*>(O + off) = b;
 }
 
-// Where column group idx (4 columns, hv groups per row) of the merged output goes: plain, or row
-// r of head h (nq rows per head) at h * head + r * row elements.
-__device__ __forceinline__ int64_t out_offset(const OutMap& om, int64_t idx, int hv) {
-  if (om.plain) return idx * 4;
-  const int64_t row = idx / hv, h = row / om.nq;
-  return h * om.head + (row - h * om.nq) * om.row + (idx - row * hv) * 4;
-}
-
-// Each thread handles CPT 16-byte column groups and issues the loads of all of them (CPT * k
-// 128-bit loads) before the first use: the amount of data in flight per thread, not the
-// arithmetic, decides how close these kernels get to the HBM rate (64 in flight cost occupancy
-// and measured slower).
-// (read once: non-temporal loads measured 8-10 % faster than plain ones here)
-#define A2D_LD(p) __builtin_nontemporal_load(p)
-constexpr int kLoadsInFlight = 32;
-constexpr int chunks_per_thread(int kmax) { return kmax >= kLoadsInFlight ? 1 : kLoadsInFlight / kmax > 4 ? 4 : kLoadsInFlight / kmax; }
-// (AttnFix carries m and l besides N: with 8 partials two chunks per thread - 16 loads of N in
-// flight - leave room for more wavefronts and measured 3 % faster than four; 2, 4 and 16 partials
-// are fastest with the common rule)
-constexpr int chunks_per_thread_fix(int kmax) { return kmax == 8 ? 2 : chunks_per_thread(kmax); }
-
-// Which column groups a thread owns: its wavefront owns CPT * 64 CONSECUTIVE groups and lane l takes
-// the groups l, l + 64, ... of that run, so that every load instruction of a wavefront reads 1 KiB
-// in one piece and its CPT loads of one partial read CPT KiB in one piece.  (Measured on MI355X: a
-// read stream made of such per-wavefront runs of 4-16 KiB reaches 6.8-7.0 TB/s, the same bytes
-// requested one grid-sized stride apart 5.3-6.4 TB/s.)
-template <int CPT>
-__device__ __forceinline__ int64_t group_index(int c) {
-  const int64_t wave = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-  return wave * (CPT * 64) + c * 64 + (threadIdx.x & 63);
-}
+// Where column group i of the share goes: plain, or row r of head h (nq rows per head) at h * head + r * row elements.
+// Plain results are written through: the reads alone take 230 us at 96 x 4096 rows of 128 and 8 partials, a seventeenth as many bytes
+// of results another 50, as lines that the stream of reads drives out of the L2s one by one; sent on at once (device
+// scope) 277 -> 265, non-temporal 275, collected in LDS and stored in longer runs 270 to 305; fp32 results 254 -> 248, non-temporal 269.
+template <typename OutT>
+struct Results {
+  OutT* O;
+  const OutMap& om;
+  __amdgpu_buffer_rsrc_t b;
+  int64_t first, h0, r0;                           // the share's first group; strided: head and row in it of the share's first row
+  int hv;
+  template <int CPT>
+  __device__ __forceinline__ Results(OutT* o, const OutMap& m, const Share<CPT>& sh, int64_t row0, int h) : O(o), om(m), first(sh.first), hv(h) {
+    b = buffer(O, first * 4 * sizeof(OutT), sh.rest * 4 * sizeof(OutT));
+    h0 = om.plain ? 0 : row0 / om.nq;
+    r0 = om.plain ? 0 : row0 - h0 * om.nq;
+  }
+  // (row, col: its row, counted from the share's first one, and its place in it)
+  __device__ __forceinline__ void store(unsigned i, unsigned row, unsigned col, f32x4 v) const {
+    if (om.plain) {
+      if constexpr (sizeof(OutT) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, i * 16, 0, THROUGH);
+      } else {
+        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+        bf16x4 o;
+        o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), b, i * 8, 0, THROUGH);
+      }
+    } else {
+      const unsigned r = (unsigned)r0 + row, h = r / (unsigned)om.nq;
+      store_out4(O, (h0 + h) * om.head + (int64_t)(r - h * (unsigned)om.nq) * om.row + col * 4, v);
+    }
+  }
+};
 
 // A column group = 4 consecutive columns of one row; hv = H / 4 groups per row.
-// KMAX is the unroll bound (k <= KMAX); loads of absent partials are predicated off.
+// KMAX is the unroll bound (k <= KMAX).
 // TRIPLE: the merge alone (Alg. 2 over k inputs): the result stays an unnormalised partial
 // (N, m, l) - O receives N in fp32, lse receives m, l_out receives l.
 template <typename OutT, int KMAX, int CPT, bool TRIPLE = false>
 __global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t rows, int hv, OutMap om,
                                                   OutT* __restrict__ O, float* __restrict__ lse,
                                                   float* __restrict__ l_out) {
-  const int64_t total = rows * hv;
-
+  const Share<CPT> sh(rows * hv);
   f32x4 n[CPT][KMAX];
   float mk[CPT][KMAX], lk[CPT][KMAX];
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) {
-    const int64_t idx = group_index<CPT>(c);
-    const int64_t row = idx / hv;
+  for (int x = 0; x < KMAX; ++x) {
+    if (x < k) {
+      const auto b = buffer(p.o[x], sh.first * 16, sh.rest * 16);
 #pragma unroll
-    for (int x = 0; x < KMAX; ++x) {
-      if (x < k && idx < total) {
-        n[c][x] = A2D_LD(reinterpret_cast<const f32x4*>(p.o[x]) + idx);
-        mk[c][x] = p.m[x][row];
-        lk[c][x] = p.l[x][row];
-      } else {
-        n[c][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int c = 0; c < CPT; ++c) load_group(n[c][x], b, sh.at(c));
+    } else {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) n[c][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  const int64_t row0 = sh.first / hv;
+  const unsigned rem = (unsigned)(sh.first - row0 * hv), stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT)) * 4;
+  unsigned row[CPT];                               // counted from row0
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) row[c] = (rem + sh.at(c)) / (unsigned)hv;
+#pragma unroll
+  for (int x = 0; x < KMAX; ++x) {
+    if (x < k) {
+      const auto bm = buffer(p.m[x], row0 * 4, stat), bl = buffer(p.l[x], row0 * 4, stat);
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) {
+        mk[c][x] = load_f32(bm, row[c]);
+        lk[c][x] = load_f32(bl, row[c]);
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) {
         mk[c][x] = -INFINITY;
         lk[c][x] = 0.f;
       }
     }
   }
+  const Results<OutT> out(O, om, sh, row0, hv);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
-    const int64_t idx = group_index<CPT>(c);
-    if (idx >= total) continue;
-    const int64_t row = idx / hv;
+    const unsigned i = sh.at(c), col = rem + i - row[c] * (unsigned)hv;
+    if (i >= sh.rest) continue;
     float M = -INFINITY;
 #pragma unroll
     for (int x = 0; x < KMAX; ++x) M = fmaxf(M, mk[c][x]);
@@ -98,16 +170,16 @@ __global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t rows
       acc[3] = fmaf(w, n[c][x][3], acc[3]);
     }
     if constexpr (TRIPLE) {
-      store_out4(O, out_offset(om, idx, hv), acc);
-      if (idx == row * hv) {
-        lse[row] = M;
-        l_out[row] = D;
+      out.store(i, row[c], col, acc);
+      if (col == 0) {
+        lse[row0 + row[c]] = M;
+        l_out[row0 + row[c]] = D;
       }
     } else {
       const float inv = (D > 0.f) ? 1.0f / D : 0.f;
       acc[0] *= inv; acc[1] *= inv; acc[2] *= inv; acc[3] *= inv;
-      store_out4(O, out_offset(om, idx, hv), acc);
-      if (idx == row * hv) lse[row] = (D > 0.f) ? M + logf(D) : -INFINITY;
+      out.store(i, row[c], col, acc);
+      if (col == 0) lse[row0 + row[c]] = (D > 0.f) ? M + logf(D) : -INFINITY;
     }
   }
 }
@@ -115,27 +187,33 @@ __global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t rows
 template <typename OutT, int KMAX, int CPT>
 __global__ __launch_bounds__(256) void sum_kernel(SumPtrs p, int k, int64_t n4, int hv, OutMap om,
                                                   OutT* __restrict__ out) {
+  const Share<CPT> sh(n4);
   f32x4 v[CPT][KMAX];
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) {
-    const int64_t idx = group_index<CPT>(c);
+  for (int x = 0; x < KMAX; ++x) {
+    if (x < k) {
+      const auto b = buffer(p.p[x], sh.first * 16, sh.rest * 16);
 #pragma unroll
-    for (int x = 0; x < KMAX; ++x) {
-      if (x < k && idx < n4) v[c][x] = A2D_LD(reinterpret_cast<const f32x4*>(p.p[x]) + idx);
-      else v[c][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int c = 0; c < CPT; ++c) load_group(v[c][x], b, sh.at(c));
+    } else {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) v[c][x] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   }
+  const int64_t row0 = om.plain ? 0 : sh.first / hv;           // (plain results need no rows)
+  const unsigned rem = om.plain ? 0 : (unsigned)(sh.first - row0 * hv);
+  const Results<OutT> res(out, om, sh, row0, hv);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
-    const int64_t idx = group_index<CPT>(c);
-    if (idx >= n4) continue;
+    const unsigned i = sh.at(c), row = om.plain ? 0 : (rem + i) / (unsigned)hv;
+    if (i >= sh.rest) continue;
     // left-to-right sum over the partials (absent ones hold zeros)
     f32x4 acc = v[c][0];
 #pragma unroll
     for (int x = 1; x < KMAX; ++x) {
       acc[0] += v[c][x][0]; acc[1] += v[c][x][1]; acc[2] += v[c][x][2]; acc[3] += v[c][x][3];
     }
-    store_out4(out, out_offset(om, idx, hv), acc);
+    res.store(i, row, rem + i - row * (unsigned)hv, acc);
   }
 }
 
@@ -144,30 +222,42 @@ __global__ __launch_bounds__(256) void sum_kernel(SumPtrs p, int k, int64_t n4, 
 template <typename InT, typename OutT, int KMAX, int CPT>
 __global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_t rows, int hv, OutMap om,
                                                        OutT* __restrict__ O, float* __restrict__ lse) {
-  const int64_t total = rows * hv;
+  const Share<CPT> sh(rows * hv);
   typedef InT in4 __attribute__((ext_vector_type(4)));
   in4 n[CPT][KMAX];
   float lk[CPT][KMAX];
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) {
-    const int64_t idx = group_index<CPT>(c);
-    const int64_t row = idx / hv;
+  for (int x = 0; x < KMAX; ++x) {
+    if (x < k) {
+      const auto b = buffer(p.o[x], sh.first * (int)sizeof(in4), sh.rest * (unsigned)sizeof(in4));
 #pragma unroll
-    for (int x = 0; x < KMAX; ++x) {
-      if (x < k && idx < total) {
-        n[c][x] = A2D_LD(reinterpret_cast<const in4*>(p.o[x]) + idx);
-        lk[c][x] = p.lse[x][row];
-      } else {
-        n[c][x] = in4{(InT)0.f, (InT)0.f, (InT)0.f, (InT)0.f};
-        lk[c][x] = -INFINITY;
-      }
+      for (int c = 0; c < CPT; ++c) load_group(n[c][x], b, sh.at(c));
+    } else {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) n[c][x] = in4{(InT)0.f, (InT)0.f, (InT)0.f, (InT)0.f};
     }
   }
+  const int64_t row0 = sh.first / hv;
+  const unsigned rem = (unsigned)(sh.first - row0 * hv), stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT)) * 4;
+  unsigned row[CPT];
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) row[c] = (rem + sh.at(c)) / (unsigned)hv;
+#pragma unroll
+  for (int x = 0; x < KMAX; ++x) {
+    if (x < k) {
+      const auto b = buffer(p.lse[x], row0 * 4, stat);
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) lk[c][x] = load_f32(b, row[c]);
+    } else {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) lk[c][x] = -INFINITY;
+    }
+  }
+  const Results<OutT> out(O, om, sh, row0, hv);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
-    const int64_t idx = group_index<CPT>(c);
-    if (idx >= total) continue;
-    const int64_t row = idx / hv;
+    const unsigned i = sh.at(c), col = rem + i - row[c] * (unsigned)hv;
+    if (i >= sh.rest) continue;
     float M = -INFINITY;
 #pragma unroll
     for (int x = 0; x < KMAX; ++x) M = fmaxf(M, lk[c][x]);
@@ -185,8 +275,8 @@ __global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_
     }
     const float inv = (D > 0.f) ? 1.0f / D : 0.f;
     acc[0] *= inv; acc[1] *= inv; acc[2] *= inv; acc[3] *= inv;
-    store_out4(O, out_offset(om, idx, hv), acc);
-    if (idx == row * hv) lse[row] = (D > 0.f) ? M + logf(D) : -INFINITY;
+    out.store(i, row[c], col, acc);
+    if (col == 0) lse[row0 + row[c]] = (D > 0.f) ? M + logf(D) : -INFINITY;
   }
 }
 
@@ -302,21 +392,30 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(PartSets a) {
   *out = acc;
 }
 
+// (go(std::integral_constant<int, CPT>): launches)
+template <int KMAX, bool WEIGHTS, bool HALF = false, class F>
+void with_chunks(int64_t groups, F&& go) {
+  constexpr int FEW = chunks_per_thread(KMAX, WEIGHTS, 0, HALF), MANY = chunks_per_thread(KMAX, WEIGHTS, kManyGroups, HALF);
+  if (groups >= kManyGroups) go(std::integral_constant<int, MANY>{});
+  else go(std::integral_constant<int, FEW>{});
+}
+inline dim3 blocks_of(int64_t groups, int cpt) { return dim3((unsigned)((groups + 256 * cpt - 1) / (256 * cpt))); }
+
 template <typename OutT, int KMAX, bool TRIPLE = false>
 void fix_launch(int k, int64_t rows, int hv, const FixPtrs& p, const OutMap& om, OutT* O, float* lse, float* l_out,
                 hipStream_t s) {
-  constexpr int CPT = chunks_per_thread_fix(KMAX);
-  const int64_t per_block = 256 * CPT;
-  const dim3 grid((unsigned)((rows * hv + per_block - 1) / per_block)), block(256);
-  A2D_LAUNCH((fix_kernel<OutT, KMAX, CPT, TRIPLE>), grid, block, 0, s, p, k, rows, hv, om, O, lse, l_out);
+  with_chunks<KMAX, true>(rows * hv, [&](auto C) {
+    constexpr int CPT = decltype(C)::value;
+    A2D_LAUNCH((fix_kernel<OutT, KMAX, CPT, TRIPLE>), blocks_of(rows * hv, CPT), dim3(256), 0, s, p, k, rows, hv, om, O, lse, l_out);
+  });
 }
 
 template <typename OutT, int KMAX>
 void sum_launch(int k, int64_t n4, int hv, const SumPtrs& p, const OutMap& om, OutT* out, hipStream_t s) {
-  constexpr int CPT = chunks_per_thread(KMAX);
-  const int64_t per_block = 256 * CPT;
-  const dim3 grid((unsigned)((n4 + per_block - 1) / per_block)), block(256);
-  A2D_LAUNCH((sum_kernel<OutT, KMAX, CPT>), grid, block, 0, s, p, k, n4, hv, om, out);
+  with_chunks<KMAX, false>(n4, [&](auto C) {
+    constexpr int CPT = decltype(C)::value;
+    A2D_LAUNCH((sum_kernel<OutT, KMAX, CPT>), blocks_of(n4, CPT), dim3(256), 0, s, p, k, n4, hv, om, out);
+  });
 }
 
 template <typename OutT, bool TRIPLE = false>
@@ -324,7 +423,9 @@ hipError_t fix_dispatch(int k, int64_t rows, int hdim, const FixPtrs& p, const O
                         float* l_out, hipStream_t s) {
   const int hv = hdim / 4;
   if (k <= 2) fix_launch<OutT, 2, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
+  else if (k <= 3) fix_launch<OutT, 3, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
   else if (k <= 4) fix_launch<OutT, 4, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
+  else if (k <= 6) fix_launch<OutT, 6, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
   else if (k <= 8) fix_launch<OutT, 8, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
   else if (k <= 16) fix_launch<OutT, 16, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
   else fix_launch<OutT, 32, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
@@ -335,7 +436,9 @@ template <typename OutT>
 hipError_t sum_dispatch(int k, int64_t n, int hv, const SumPtrs& p, const OutMap& om, OutT* out, hipStream_t s) {
   const int64_t n4 = n / 4;
   if (k <= 2) sum_launch<OutT, 2>(k, n4, hv, p, om, out, s);
+  else if (k <= 3) sum_launch<OutT, 3>(k, n4, hv, p, om, out, s);
   else if (k <= 4) sum_launch<OutT, 4>(k, n4, hv, p, om, out, s);
+  else if (k <= 6) sum_launch<OutT, 6>(k, n4, hv, p, om, out, s);
   else if (k <= 8) sum_launch<OutT, 8>(k, n4, hv, p, om, out, s);
   else if (k <= 16) sum_launch<OutT, 16>(k, n4, hv, p, om, out, s);
   else sum_launch<OutT, 32>(k, n4, hv, p, om, out, s);
@@ -345,10 +448,10 @@ hipError_t sum_dispatch(int k, int64_t n, int hv, const SumPtrs& p, const OutMap
 
 template <typename InT, typename OutT, int KMAX>
 void fix_norm_launch(int k, int64_t rows, int hv, const NormPtrs& p, const OutMap& om, OutT* O, float* lse, hipStream_t s) {
-  constexpr int CPT = chunks_per_thread(KMAX);
-  const int64_t per_block = 256 * CPT;
-  const dim3 grid((unsigned)((rows * hv + per_block - 1) / per_block)), block(256);
-  A2D_LAUNCH((fix_norm_kernel<InT, OutT, KMAX, CPT>), grid, block, 0, s, p, k, rows, hv, om, O, lse);
+  with_chunks<KMAX, true, sizeof(InT) == 2>(rows * hv, [&](auto C) {
+    constexpr int CPT = decltype(C)::value;
+    A2D_LAUNCH((fix_norm_kernel<InT, OutT, KMAX, CPT>), blocks_of(rows * hv, CPT), dim3(256), 0, s, p, k, rows, hv, om, O, lse);
+  });
 }
 
 template <typename InT, typename OutT>
@@ -356,7 +459,9 @@ hipError_t fix_norm_dispatch(int k, int64_t rows, int hdim, const NormPtrs& p, c
                              hipStream_t s) {
   const int hv = hdim / 4;
   if (k <= 2) fix_norm_launch<InT, OutT, 2>(k, rows, hv, p, om, O, lse, s);
+  else if (k <= 3) fix_norm_launch<InT, OutT, 3>(k, rows, hv, p, om, O, lse, s);
   else if (k <= 4) fix_norm_launch<InT, OutT, 4>(k, rows, hv, p, om, O, lse, s);
+  else if (k <= 6) fix_norm_launch<InT, OutT, 6>(k, rows, hv, p, om, O, lse, s);
   else if (k <= 8) fix_norm_launch<InT, OutT, 8>(k, rows, hv, p, om, O, lse, s);
   else if (k <= 16) fix_norm_launch<InT, OutT, 16>(k, rows, hv, p, om, O, lse, s);
   else fix_norm_launch<InT, OutT, 32>(k, rows, hv, p, om, O, lse, s);
