@@ -19,8 +19,11 @@ namespace {
 // AttnFix 42.6 / 42.2 / 42.8; k = 8 sum 16 x 2048 x 128 25.5 / 25.5 / 22.9, AttnFix 26.6 / 27.0 / 25.6 there, but 302 / 297 / 303 at 96 x 4096;
 // k = 16 AttnFix 16 x 8000 x 128 180 / 171, sum 179 / 169, but 75.0 / 76.8 and 72.6 / 73.1 at 16 x 4096 x 96.
 // half: groups of 8 bytes, a merge of normalised bf16 partials: 16 x 2048 x 128, k = 16 29.0 / 25.4, 96 x 4096, k = 2 one against four 63.0 / 58.2.
-constexpr int64_t kManyGroups = 1 << 21;
+// One for merges of a few hundred workgroups at the most, which have to come to as many as they can (those of the split walk of 1 x 1000 x
+// 1000 fp32, H = 128 17.6 -> 15.3 with it, 2 x 100 x 1000, H = 96 12.2 -> 10.0).
+constexpr int64_t kSomeGroups = 1 << 17, kManyGroups = 1 << 21;
 constexpr int chunks_per_thread(int kmax, bool weights, int64_t groups, bool half = false) {
+  if (groups < kSomeGroups) return 1;
   if (half && kmax == 2) return 4;
   if (half && kmax == 16) return 2;
   if (kmax <= 4 || kmax > 16) return 1;
@@ -51,14 +54,28 @@ enum { NT = 2, THROUGH = 16 };                     // cache policies of the buff
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* p, int64_t bytes_before, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(p)) + bytes_before, 0, bytes, 0x00020000);
 }
-__device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t b, unsigned i) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, i * 4, 0, 0));
+__device__ __forceinline__ void load(float& v, __amdgpu_buffer_rsrc_t b, unsigned i) {
+  v = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, i * 4, 0, 0));
 }
-__device__ __forceinline__ void load_group(f32x4& v, __amdgpu_buffer_rsrc_t b, unsigned i) {
+__device__ __forceinline__ void load(f32x4& v, __amdgpu_buffer_rsrc_t b, unsigned i) {
   v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, i * 16, 0, NT));
 }
-__device__ __forceinline__ void load_group(bf16x4& v, __amdgpu_buffer_rsrc_t b, unsigned i) {
+__device__ __forceinline__ void load(bf16x4& v, __amdgpu_buffer_rsrc_t b, unsigned i) {
   v = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(b, i * 8, 0, NT));
+}
+// Partial x of k: v[c] = elements at[c] of the `n` from p + before on; zeros past them and of an absent partial.
+// No branch around absent ones, so that the pointers of all come in together: they have no size (us, with branches / without: AttnFix 8 x
+// 96 x 4096 297 / 292, 16 x 16 x 8000 171 / 169).  BRANCH: with one (sums of up to four: 4 x 16 x 2048 12.8 / 13.3).
+template <bool BRANCH, int KMAX, int CPT, typename T>
+__device__ __forceinline__ void load_partial(T (&v)[CPT][KMAX], int x, int k, const T* p, int64_t before, unsigned n, const unsigned (&at)[CPT]) {
+  if (BRANCH && x >= k) {
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) v[c][x] = T{};
+    return;
+  }
+  const auto b = buffer(p, before * (int)sizeof(T), x < k ? n * (unsigned)sizeof(T) : 0);
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) load(v[c][x], b, at[c]);
 }
 
 __device__ __forceinline__ void store_out4(float* O, int64_t off, f32x4 v) {
@@ -114,45 +131,60 @@ __global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t rows
                                                   OutT* __restrict__ O, float* __restrict__ lse,
                                                   float* __restrict__ l_out) {
   const Share<CPT> sh(rows * hv);
+  unsigned at[CPT];
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) at[c] = sh.at(c);
+  int64_t row0;
+  unsigned rem, row[CPT];                          // (rows counted from row0)
   f32x4 n[CPT][KMAX];
   float mk[CPT][KMAX], lk[CPT][KMAX];
+  const auto rows_of = [&]() {                     // (some hundred instructions: behind the large requests, 8 x 96 x 4096 300 -> 292 us)
+    row0 = sh.first / hv;
+    rem = (unsigned)(sh.first - row0 * hv);
 #pragma unroll
-  for (int x = 0; x < KMAX; ++x) {
-    if (x < k) {
-      const auto b = buffer(p.o[x], sh.first * 16, sh.rest * 16);
+    for (int c = 0; c < CPT; ++c) row[c] = (rem + at[c]) / (unsigned)hv;
+  };
+  if constexpr (KMAX > 16) {
+    // (more descriptors than scalar registers: plain pointers and one row a lane.  The split walk of 1 x 128 x 16384, whose
+    // merge is 16 workgroups, 16.8 -> 15.4 us)
+    static_assert(CPT == 1, "");
+    const int64_t idx = sh.first + at[0], r = idx / hv;
 #pragma unroll
-      for (int c = 0; c < CPT; ++c) load_group(n[c][x], b, sh.at(c));
-    } else {
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) n[c][x] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-  }
-  const int64_t row0 = sh.first / hv;
-  const unsigned rem = (unsigned)(sh.first - row0 * hv), stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT)) * 4;
-  unsigned row[CPT];                               // counted from row0
-#pragma unroll
-  for (int c = 0; c < CPT; ++c) row[c] = (rem + sh.at(c)) / (unsigned)hv;
-#pragma unroll
-  for (int x = 0; x < KMAX; ++x) {
-    if (x < k) {
-      const auto bm = buffer(p.m[x], row0 * 4, stat), bl = buffer(p.l[x], row0 * 4, stat);
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        mk[c][x] = load_f32(bm, row[c]);
-        lk[c][x] = load_f32(bl, row[c]);
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        mk[c][x] = -INFINITY;
-        lk[c][x] = 0.f;
+    for (int x = 0; x < KMAX; ++x) {
+      if (x < k && idx < rows * hv) {
+        n[0][x] = A2D_LD(reinterpret_cast<const f32x4*>(p.o[x]) + idx);
+        mk[0][x] = p.m[x][r];
+        lk[0][x] = p.l[x][r];
+      } else {
+        n[0][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+        mk[0][x] = -INFINITY;
+        lk[0][x] = 0.f;
       }
     }
+    row0 = r;                                      // (the lane's own row)
+    row[0] = 0;
+    rem = (unsigned)(idx - r * hv) - at[0];
+  } else {
+#pragma unroll
+    for (int x = 0; x < KMAX; ++x) load_partial<false>(n, x, k, reinterpret_cast<const f32x4*>(p.o[x]), sh.first, sh.rest, at);
+    __builtin_amdgcn_sched_barrier(0);
+    rows_of();
+    const unsigned stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT));
+#pragma unroll
+    for (int x = 0; x < KMAX; ++x) {
+      load_partial<false>(mk, x, k, p.m[x], row0, stat, row);
+      load_partial<false>(lk, x, k, p.l[x], row0, stat, row);
+    }
+#pragma unroll
+    for (int x = 0; x < KMAX; ++x)
+#pragma unroll
+      for (int c = 0; c < CPT; ++c)
+        if (x >= k) mk[c][x] = -INFINITY;
   }
   const Results<OutT> out(O, om, sh, row0, hv);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
-    const unsigned i = sh.at(c), col = rem + i - row[c] * (unsigned)hv;
+    const unsigned i = at[c], col = rem + i - row[c] * (unsigned)hv;
     if (i >= sh.rest) continue;
     float M = -INFINITY;
 #pragma unroll
@@ -188,24 +220,20 @@ template <typename OutT, int KMAX, int CPT>
 __global__ __launch_bounds__(256) void sum_kernel(SumPtrs p, int k, int64_t n4, int hv, OutMap om,
                                                   OutT* __restrict__ out) {
   const Share<CPT> sh(n4);
+  unsigned at[CPT];
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) at[c] = sh.at(c);
   f32x4 v[CPT][KMAX];
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    if (x < k) {
-      const auto b = buffer(p.p[x], sh.first * 16, sh.rest * 16);
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) load_group(v[c][x], b, sh.at(c));
-    } else {
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) v[c][x] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    load_partial<KMAX <= 4>(v, x, k, reinterpret_cast<const f32x4*>(p.p[x]), sh.first, sh.rest, at);
   }
   const int64_t row0 = om.plain ? 0 : sh.first / hv;           // (plain results need no rows)
   const unsigned rem = om.plain ? 0 : (unsigned)(sh.first - row0 * hv);
   const Results<OutT> res(out, om, sh, row0, hv);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
-    const unsigned i = sh.at(c), row = om.plain ? 0 : (rem + i) / (unsigned)hv;
+    const unsigned i = at[c], row = om.plain ? 0 : (rem + i) / (unsigned)hv;
     if (i >= sh.rest) continue;
     // left-to-right sum over the partials (absent ones hold zeros)
     f32x4 acc = v[c][0];
@@ -223,40 +251,34 @@ template <typename InT, typename OutT, int KMAX, int CPT>
 __global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_t rows, int hv, OutMap om,
                                                        OutT* __restrict__ O, float* __restrict__ lse) {
   const Share<CPT> sh(rows * hv);
+  unsigned at[CPT];
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) at[c] = sh.at(c);
   typedef InT in4 __attribute__((ext_vector_type(4)));
   in4 n[CPT][KMAX];
   float lk[CPT][KMAX];
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    if (x < k) {
-      const auto b = buffer(p.o[x], sh.first * (int)sizeof(in4), sh.rest * (unsigned)sizeof(in4));
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) load_group(n[c][x], b, sh.at(c));
-    } else {
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) n[c][x] = in4{(InT)0.f, (InT)0.f, (InT)0.f, (InT)0.f};
-    }
+    load_partial<false>(n, x, k, reinterpret_cast<const in4*>(p.o[x]), sh.first, sh.rest, at);
   }
   const int64_t row0 = sh.first / hv;
-  const unsigned rem = (unsigned)(sh.first - row0 * hv), stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT)) * 4;
+  const unsigned rem = (unsigned)(sh.first - row0 * hv), stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT));
   unsigned row[CPT];
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) row[c] = (rem + sh.at(c)) / (unsigned)hv;
+  for (int c = 0; c < CPT; ++c) row[c] = (rem + at[c]) / (unsigned)hv;
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    if (x < k) {
-      const auto b = buffer(p.lse[x], row0 * 4, stat);
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) lk[c][x] = load_f32(b, row[c]);
-    } else {
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) lk[c][x] = -INFINITY;
-    }
+    load_partial<false>(lk, x, k, p.lse[x], row0, stat, row);
   }
+#pragma unroll
+  for (int x = 0; x < KMAX; ++x)
+#pragma unroll
+    for (int c = 0; c < CPT; ++c)
+      if (x >= k) lk[c][x] = -INFINITY;
   const Results<OutT> out(O, om, sh, row0, hv);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
-    const unsigned i = sh.at(c), col = rem + i - row[c] * (unsigned)hv;
+    const unsigned i = at[c], col = rem + i - row[c] * (unsigned)hv;
     if (i >= sh.rest) continue;
     float M = -INFINITY;
 #pragma unroll
@@ -395,9 +417,10 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(PartSets a) {
 // (go(std::integral_constant<int, CPT>): launches)
 template <int KMAX, bool WEIGHTS, bool HALF = false, class F>
 void with_chunks(int64_t groups, F&& go) {
-  constexpr int FEW = chunks_per_thread(KMAX, WEIGHTS, 0, HALF), MANY = chunks_per_thread(KMAX, WEIGHTS, kManyGroups, HALF);
+  constexpr int FEW = chunks_per_thread(KMAX, WEIGHTS, kSomeGroups, HALF), MANY = chunks_per_thread(KMAX, WEIGHTS, kManyGroups, HALF);
   if (groups >= kManyGroups) go(std::integral_constant<int, MANY>{});
-  else go(std::integral_constant<int, FEW>{});
+  else if (groups >= kSomeGroups) go(std::integral_constant<int, FEW>{});
+  else go(std::integral_constant<int, chunks_per_thread(KMAX, WEIGHTS, 0, HALF)>{});
 }
 inline dim3 blocks_of(int64_t groups, int cpt) { return dim3((unsigned)((groups + 256 * cpt - 1) / (256 * cpt))); }
 
