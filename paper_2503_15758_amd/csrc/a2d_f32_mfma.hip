@@ -3,7 +3,7 @@
 // fp32 throughout: v_mfma_f32_16x16x4_f32 multiplies and accumulates in fp32 (2048 flop in 32 cycles
 // of a SIMD, 157 TFLOP/s over the chip - twice what unpacked vector FMAs reach).
 //
-// What bounds them: the fp32 MFMA rate where there are many rows (82 % of it at 16 x 4096 x 4096, H = 128, 84 % in the backward); at
+// What bounds them: the fp32 MFMA rate where there are many rows (84 % of it at 16 x 4096 x 4096, H = 128, in both passes); at
 // 16 x 700 x 900 prologues, merges and uneven walks of a few steps (58 %).  A step of 16 keys (queries)
 // against 16 rows is H / 4 MFMAs of 32 cycles per contraction, on 8 KiB of operands at H = 128.
 //   - The backward's dQ and dK/dV workgroups go out in one launch, so that the end of the one kind overlaps the start of
@@ -12,6 +12,12 @@
 //   - Operands of a step pass through a tile in LDS that is the wavefront's own (no barriers): a contraction over H needs
 //     lane = row, and loading that from memory is 64 separate accesses per instruction, which kept the matrix units
 //     half idle (16 heads x 1024 x 1024, H = 96: 6.4e7 cache accesses for 1.2 GB, 50 % MFMA busy).
+//   - The forward's K tile goes straight into LDS, the next block's as soon as the scores are there, and V by columns into registers as
+//     soon as the products are through.  With K one block ahead in registers and V requested at the start of its own step, two workgroups
+//     shared a compute unit; without these 20 to 32 registers three to four of 16 rows do.  us, before -> now: 16 x 1024 x 1024,
+//     H = 128 / 96 / 80 / 64 82 / 63 / 52 / 43.3 -> 76 / 59 / 50 / 42.0 (113 TFLOP/s, 72 % of the peak, at H = 128), 12 x 1024 x 600, H = 128
+//     42.2 -> 38.1, 8 x 500 x 1000, H = 80 19.0 -> 17.2, 3 x 600 x 1000, H = 64 14.0 -> 12.5, 16 x 700 x 900, H = 96, causal 31.8 -> 30.7;
+//     23 shapes 1.058 times as fast in the mean, no one slower.
 //   - The backward loads its tiles straight into LDS, each as soon as the last read of the one before is through: V behind dP, K
 //     behind half of dQ; Q behind half of dK, dO behind most of dV.  By way of registers, one step ahead, the rows of Q, dO and O took
 //     96 of them at H = 128 and left room for two workgroups a compute unit; now three fit up to H = 96 (at H = 96 where delta is read),
@@ -39,7 +45,7 @@
 //     32 or 16 columns with 8- or 4-byte pieces: Cols<H> below.)
 // Measured against the vector-ALU kernels of a2d_generic.hip: 16 heads x 700 x 900, H = 96, causal,
 // backward call 1034 -> 92 us; 2 heads x 128 x 128, H = 64, forward 29 -> 5.0 us; 16 heads x 4096 x 4096, H = 128: forward
-// 1.07 ms (129 TFLOP/s, 82 % of the fp32 matrix peak), backward 3.65 ms (132 TFLOP/s executed).
+// 1.04 ms (132 TFLOP/s, 84 % of the fp32 matrix peak), backward 3.65 ms (132 TFLOP/s executed).
 #include <cmath>
 
 #include "a2d_mfma.hpp"
@@ -107,30 +113,6 @@ template <typename T>
 __device__ __forceinline__ T lload(lds_t p) { return *reinterpret_cast<__attribute__((address_space(3))) T*>(p); }
 template <typename T>
 __device__ __forceinline__ void lstore(lds_t p, T v) { *reinterpret_cast<__attribute__((address_space(3))) T*>(p) = v; }
-
-// A wavefront's tile of 16 rows in LDS (the forward's).  It is written, by columns, and read, by rows, by that wavefront alone, whose LDS
-// operations complete in order.
-template <int H>
-struct Tile {
-  static constexpr int LD = H * 4 + 16, BYTES = 16 * LD;
-  lds_t nat, col;                            // this lane's place for natural rows, and for columns (row 4 g)
-  __device__ __forceinline__ void init(lds_t b, int l15, int g4) {
-    nat = b + l15 * LD + 16 * g4;
-    col = b + 4 * g4 * LD + 16 * l15;
-  }
-  // rows 4 g + r, as Cols holds them
-  __device__ __forceinline__ void store(const Cols<H> (&c)[4], int l15) {
-    constexpr int N4 = Cols<H>::N4, REST = Cols<H>::REST;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-#pragma unroll
-      for (int G = 0; G < N4; ++G) lstore(col + r * LD + 256 * G, c[r].a[G]);
-      if constexpr (REST == 32) lstore(col - 8 * l15 + r * LD + 256 * N4, f32x2{c[r].b[0], c[r].b[1]});
-      if constexpr (REST == 16) lstore(col - 12 * l15 + r * LD + 256 * N4, c[r].b[0]);
-    }
-  }
-  __device__ __forceinline__ f32x4 row(int y) const { return lload<f32x4>(nat + 64 * y); }
-};
 
 // A wavefront's tile of 16 rows that is loaded straight into LDS (see mfma::Blocks16: here a block is 16 rows x 16 columns).
 // Blocks lie 64 bytes more than their size apart, so that the columns' reads, which take 64 bytes of four blocks at a time,
@@ -233,7 +215,7 @@ struct Out {
 // 16 x 16 results of contractions over H of a tile's rows with RT sets of rows in registers (two
 // accumulators each).  The tile's pieces are requested one ahead of their use.
 template <int H, int RT>
-__device__ __forceinline__ void dot_rows(f32x4 (&out)[RT], const Tile<H>& a, const Nat<H> (&b)[RT]) {
+__device__ __forceinline__ void dot_rows(f32x4 (&out)[RT], const Blocks<H>& a, const Nat<H> (&b)[RT]) {
   constexpr int N = H / 16;
   f32x4 s1[RT], ring[2];
 #pragma unroll
@@ -360,8 +342,10 @@ __device__ __forceinline__ int vis_count(const a2d_tile_desc& d, const SegList& 
 
 // ------------------------------------------------------------------ forward
 // (O_part, m_out and l_out are not __restrict__: an accumulating call's `in` is the same memory)
+// workgroups of the forward that a compute unit holds at a time, by their registers (three of 32 rows at H = 96 kept six in scratch)
+constexpr int fwd_fit(int hdim, int rt) { return rt == 2 ? (hdim <= 80 ? 3 : 2) : hdim == 128 ? 3 : 4; }
 template <int H, int RT>
-__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) void fwd_f32_kernel(
+__global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(fwd_fit(H, RT)))) void fwd_f32_kernel(
     a2d_tile_desc d, SegList g, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, float* O_part, float* m_out, float* l_out, FwdInput in) {
   warm_arguments<6 * 8 + sizeof(FwdInput)>();
@@ -402,15 +386,24 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
   Walk w;
   w.open(g, seg_blocks);
   w.advance(part * KL + kl, g, seg_blocks);
-  Tile<H> kt;
-  kt.init((lds_t)smem + kl * Tile<H>::BYTES, l15, g4);
-  Cols<H> kc[4], vt[4];
-  auto load_k = [&](const Walk& x) {
+  // K comes in through LDS, the next block's as soon as the scores are there; V by columns into registers, the next block's as
+  // soon as the products are through.  (Past the walk's end both read a block of its last sub-block again.)
+  Blocks<H> kt;
+  kt.init((lds_t)smem + kl * Blocks<H>::BYTES, l15, g4);
+  Cols<H> vt[4];
+  constexpr int V_LOADS = 4 * (Cols<H>::N4 + (Cols<H>::REST != 0));
+  auto load_k = [&]() {
+    kt.load(kb, __umul24((unsigned)(w.start + min(w.j * BLK + (lane >> 2), w.rows - 1)), k_row) + Blocks<H>::chunk(lane));
+  };
+  auto load_v = [&]() {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) kc[r].load(kb, x.start + min(x.j * BLK + 4 * g4 + r, x.rows - 1), k_row, l15);
+    for (int r = 0; r < 4; ++r) vt[r].load(vb, w.start + min(w.j * BLK + 4 * g4 + r, w.rows - 1), v_row, l15);
   };
   int vis_s = -1, my_vis[RT];                         // keys of sub-block vis_s that this lane's rows see
-  if (w.s < g.n) load_k(w);
+  if (w.s < g.n) {
+    load_k();
+    load_v();
+  }
   while (w.s < g.n) {
     const int k0 = w.j * BLK;
     if (w.s != vis_s) {
@@ -418,14 +411,14 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
       for (int t = 0; t < RT; ++t) my_vis[t] = vis_count(d, g, min(q_row[t], d.nq - 1), w.s);
     }
-    kt.store(kc, l15);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) vt[r].load(vb, w.start + min(k0 + 4 * g4 + r, w.rows - 1), v_row, l15);
-    __builtin_amdgcn_sched_barrier(0);
     f32x4 p[RT];
+    mfma::wait_dma<V_LOADS>();
+    __builtin_amdgcn_sched_barrier(0);
     dot_rows<H, RT>(p, kt, qf);
     w.advance(lanes, g, seg_blocks);
-    if (w.s < g.n) load_k(w);
+    mfma::wait_vmem_all();                            // V: the products would wait for the next block's K too
+    reads_done();
+    load_k();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
@@ -454,7 +447,10 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int r = 0; r < 4; ++r)
 #pragma unroll
       for (int t = 0; t < RT; ++t) o[t].contract(vt[r], p[t][r]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_v();
   }
+  mfma::wait_vmem_all();
 
   // ---- to the true row maximum over all key lanes, then the sums over the lanes
   float m_all[RT];
@@ -762,7 +758,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(bwd_fit
 // LDS of a workgroup: the wavefronts' tiles, over which their results are merged at the end
 constexpr int most(int a, int b) { return a > b ? a : b; }
 template <int H, int RT>
-constexpr int fwd_lds() { return most(KL * Tile<H>::BYTES, KL / 2 * RT * (H / 16 + 1) * 1024); }
+constexpr int fwd_lds() { return most(KL * Blocks<H>::BYTES, KL / 2 * RT * (H / 16 + 1) * 1024); }
 template <int H>
 constexpr int dq_lds() { return most(2 * KL * Blocks<H>::BYTES, KL / 2 * (H / 16) * 1024); }
 template <int H>
