@@ -33,7 +33,7 @@
 // block t + 1, the other through the softmax of block t and then the same MFMAs.  Both are busy 21 % of the cycles then, of which there are 10 %
 // fewer at a 5 % lower clock (the same power).  What is left: an MFMA of 16 cycles leaves the other wavefront two vector instructions, not
 // three, so that the 128 MFMAs and two softmaxes of a step take 2730 cycles at the least (both measured side by side); a step takes 3060.
-// Rescaling is lazy:// Rescaling is lazy: a row's exponent reference m_ref follows its running maximum
+// Rescaling is lazy: a row's exponent reference m_ref follows its running maximum
 // only when a score exceeds it by more than 2^8 (in the exponent's units) - a rare,
 // wave-uniform branch, and the only place where the lanes of a row talk to each
 // other.  Each lane tracks the true maximum of its own scores; at the end they
