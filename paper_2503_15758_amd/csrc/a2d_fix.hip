@@ -16,19 +16,21 @@ namespace {
 #define A2D_LD(p) __builtin_nontemporal_load(p)
 // CPT for `groups` column groups (weights: AttnFix, which holds m and l besides N).  us, one / two / four groups a thread:
 // 96 x 4096 x 128, k = 4 AttnFix 150 / 159 / 160, sum 148 / 155 / 155, k = 2 82.7 / 84.7 / 86.5; 30 x 2500 x 128, k = 6 sum 40.4 / 41.1 / 40.8,
-// AttnFix 42.6 / 42.2 / 42.8; k = 8 sum 16 x 2048 x 128 25.5 / 25.5 / 22.9, AttnFix 26.6 / 27.0 / 25.6 there, but 302 / 297 / 303 at 96 x 4096;
+// AttnFix 42.6 / 42.2 / 42.8; k = 8 sum 16 x 2048 x 128 25.5 / 25.5 / 22.9, AttnFix 26.6 / 27.0 / 25.6 there, but 302 / 297 / 303 at 96 x 4096 and
+// - / 16.1 / 17.3 at 20 x 1000 (four: two workgroups a compute unit, 1.2 turns of them);
 // k = 16 AttnFix 16 x 8000 x 128 180 / 171, sum 179 / 169, but 75.0 / 76.8 and 72.6 / 73.1 at 16 x 4096 x 96.
 // half: groups of 8 bytes, a merge of normalised bf16 partials: 16 x 2048 x 128, k = 16 29.0 / 25.4, 96 x 4096, k = 2 one against four 63.0 / 58.2.
-// One for merges of a few hundred workgroups at the most, which have to come to as many as they can (those of the split walk of 1 x 1000 x
-// 1000 fp32, H = 128 17.6 -> 15.3 with it, 2 x 100 x 1000, H = 96 12.2 -> 10.0).
-constexpr int64_t kSomeGroups = 1 << 17, kManyGroups = 1 << 21;
+// One for merges of up to a thousand workgroups, which have to come to as many as they can (those of the split walk of 1 x 1000 x
+// 1000 fp32, H = 128 17.6 -> 15.3 with it, 2 x 100 x 1000, H = 96 12.2 -> 10.0; AttnFix of 8, 26 x 466 x 96 four against one 11.2 / 8.8).  AttnFix of
+// 6 and 8 partials of 5 to 20 MB each is up to 6 % slower than with plain stores and descriptors in no use (17 x 1370 x 80 13.0 -> 13.6).
+constexpr int64_t kSomeGroups = 1 << 19, kManyGroups = 1 << 21;
 constexpr int chunks_per_thread(int kmax, bool weights, int64_t groups, bool half = false) {
   if (groups < kSomeGroups) return 1;
   if (half && kmax == 2) return 4;
   if (half && kmax == 16) return 2;
   if (kmax <= 4 || kmax > 16) return 1;
   if (kmax == 6) return 2;
-  if (kmax == 8) return weights && groups >= kManyGroups ? 2 : 4;
+  if (kmax == 8) return weights ? 2 : 4;
   return groups >= kManyGroups ? 2 : 1;
 }
 
@@ -417,10 +419,10 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(PartSets a) {
 // (go(std::integral_constant<int, CPT>): launches)
 template <int KMAX, bool WEIGHTS, bool HALF = false, class F>
 void with_chunks(int64_t groups, F&& go) {
-  constexpr int FEW = chunks_per_thread(KMAX, WEIGHTS, kSomeGroups, HALF), MANY = chunks_per_thread(KMAX, WEIGHTS, kManyGroups, HALF);
-  if (groups >= kManyGroups) go(std::integral_constant<int, MANY>{});
-  else if (groups >= kSomeGroups) go(std::integral_constant<int, FEW>{});
-  else go(std::integral_constant<int, chunks_per_thread(KMAX, WEIGHTS, 0, HALF)>{});
+  const int cpt = chunks_per_thread(KMAX, WEIGHTS, groups, HALF);
+  constexpr int MOST = chunks_per_thread(KMAX, WEIGHTS, kManyGroups, HALF);
+  if (cpt == 1) go(std::integral_constant<int, 1>{});
+  else go(std::integral_constant<int, MOST>{});      // (the one other number that a number of partials has)
 }
 inline dim3 blocks_of(int64_t groups, int cpt) { return dim3((unsigned)((groups + 256 * cpt - 1) / (256 * cpt))); }
 
