@@ -22,7 +22,8 @@ namespace {
 // half: groups of 8 bytes, a merge of normalised bf16 partials: 16 x 2048 x 128, k = 16 29.0 / 25.4, 96 x 4096, k = 2 one against four 63.0 / 58.2.
 // One for merges of up to a thousand workgroups, which have to come to as many as they can (those of the split walk of 1 x 1000 x
 // 1000 fp32, H = 128 17.6 -> 15.3 with it, 2 x 100 x 1000, H = 96 12.2 -> 10.0; AttnFix of 8, 26 x 466 x 96 four against one 11.2 / 8.8).  AttnFix of
-// 6 and 8 partials of 5 to 20 MB each is up to 6 % slower than with plain stores and descriptors in no use (17 x 1370 x 80 13.0 -> 13.6).
+// 8 partials of 2 to 8 MB each, and some sums, are up to 6 % slower than before all this (17 x 1370 x 80 12.9 -> 13.6, plain stores 13.7); 20 merges
+// of that size 1.036 times as fast in the mean.
 constexpr int64_t kSomeGroups = 1 << 19, kManyGroups = 1 << 21;
 constexpr int chunks_per_thread(int kmax, bool weights, int64_t groups, bool half = false) {
   if (groups < kSomeGroups) return 1;
