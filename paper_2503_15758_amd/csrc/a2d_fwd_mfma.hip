@@ -145,7 +145,9 @@ __device__ __forceinline__ void fwd_softmax(FwdState<HR>& st, Scores& s, bf16x8 
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int key = k0 + 16 * (r >> 2) + 4 * grp + (r & 3);
-        if (key >= my_vis[q]) s[r >> 2][q][r & 3] = -INFINITY;
+        // (a select: of stores under conditions that imply each other the compiler made a chain that keeps all of them in scalar
+        // registers, 1 to 4 % of a walk of few steps: gathered 15/5 x 3479 x 148, H = 64 14.1 -> 13.3 us, 60 x 3832 x 133, H = 128 78.7 -> 75.3)
+        s[r >> 2][q][r & 3] = key >= my_vis[q] ? -INFINITY : s[r >> 2][q][r & 3];
       }
   }
   bool grow = false;
@@ -396,12 +398,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     ld_row_bytes[x] = __builtin_amdgcn_readfirstlane((unsigned)(v ? d.lv.row : d.lk.row) * 2);
     ld_col_bytes[x] = GRID == 2 ? __builtin_amdgcn_readfirstlane((unsigned)((v ? g.b.v : g.b.k) * 2)) : ld_row_bytes[x];
   }
-  struct Entry {                                   // block j of the nblk of sub-block sb, which starts at `start`
-    int sb, j, nblk, start, rows;
-  };
   // (which: bit 0 K, bit 1 V, of those that this wavefront loads)
-  auto load_tile = [&](int which, const Entry& e, int boff) {
-    const int seg_start = e.start, j = e.j, r = min(ld_row, e.rows - 1 - j * BN);
+  auto load_tile = [&](int which, int seg_start, int seg_rows, int j, int boff) {
+    const int r = min(ld_row, seg_rows - 1 - j * BN);
 #pragma unroll
     for (int x = 0; x < LD_N; ++x) {
       if (which != 3 && !(which >> (ld_first + x) & 1)) continue;
@@ -458,25 +457,26 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   // cyclic: query i sees the keys kk <= i of columns up to its row block's own, kk < i of the others - the mask of the
   // former with the keys numbered one higher
   const int shift_from = CYCLIC && d.causal ? row_blk : segs;
-  auto step_to = [&](Entry& e, int by) {
-    const int old = e.sb;
-    advance(by, e.sb, e.j, e.nblk);
-    if (CYCLIC) e.start = e.sb;
-    else if (A2D_SELDOM(e.sb != old && e.sb < segs)) { e.start = seg_start(e.sb); e.rows = seg_rows(e.sb); }
+  int sb, j = 0, nblk = 0;                         // this key lane's current entry
+  open_segment(0, sb, nblk);
+  advance(part * KL, sb, j, nblk);
+  int lead_sb = sb, lead_j = j, lead_nblk = nblk;  // key lane 0's: every lane of the workgroup loops while it exists
+  if (KL > 1) advance(kl, sb, j, nblk);
+  int nx_sb = sb, nx_j = j, nx_nblk = nblk;        // the next entry (PHASED)
+  int nx_start = 0, nx_rows = 0;                   // start / rows of its sub-block
+  auto step_next = [&](int& n_sb, int& n_j, int& n_nblk, int& start, int& rows) {
+    const int old = n_sb;
+    advance(stride, n_sb, n_j, n_nblk);
+    if (CYCLIC) start = n_sb;
+    else if (A2D_SELDOM(n_sb != old && n_sb < segs)) { start = seg_start(n_sb); rows = seg_rows(n_sb); }
   };
-  Entry e0 = {0, 0, 0, 0, grid_rows};              // this key lane's current entry ...
-  open_segment(0, e0.sb, e0.nblk);
-  if (e0.sb < segs) { e0.start = seg_start(e0.sb); e0.rows = seg_rows(e0.sb); }
-  step_to(e0, part * KL);
-  Entry lead = e0;                                 // key lane 0's: every lane of the workgroup loops while it exists
-  if (KL > 1) step_to(e0, kl);
-  Entry e1 = e0;                                   // ... the next
-  if (e0.sb < segs) {
-    enter_segment(e0.sb);
-    load_tile(3, e0, 0);
+  if (sb < segs) {
+    enter_segment(sb);
+    nx_start = seg_start(sb); nx_rows = seg_rows(sb);
+    load_tile(3, nx_start, nx_rows, j, 0);
     if constexpr (PHASED) {
-      step_to(e1, stride);
-      if (e1.sb < segs) load_tile(1, e1, BUF_BYTES);
+      step_next(nx_sb, nx_j, nx_nblk, nx_start, nx_rows);
+      if (nx_sb < segs) load_tile(1, nx_start, nx_rows, nx_j, BUF_BYTES);
     }
   }
   // (one wait for the Q rows and the first tiles: the latencies overlap)
@@ -492,9 +492,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     bf16x8 pb[2][2];
     int k0 = 0;
     bool seen = false, masked = false;
-    auto look_at = [&](const Entry& e) {
-      k0 = e.j * BN + (CYCLIC && e.sb > shift_from);           // local to the sub-block
-      seen = e.sb < segs && k0 < nvis_wave;
+    auto look_at = [&](int sb, int j) {
+      k0 = j * BN + (CYCLIC && sb > shift_from);               // local to the sub-block
+      seen = sb < segs && k0 < nvis_wave;
       masked = k0 + BN > nfull_wave;
     };
     // Interval t lies between the barriers t and t + 1.  In it wavefronts that are `behind` do the softmax of block t and then
@@ -504,18 +504,18 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
     // (Fragments requested earlier - the first of V in front of the exponentials or of the scores, the products in front of the
     // scores - cost 1-3 %: the wavefront that waits for them leaves the other one the vector ALU.)
     const bool behind = KL == 2 ? kl == 1 : wave >= 4;
-    look_at(e0);
+    look_at(sb, j);
     if (seen) {
       fwd_first_keys<HR>(kr, rd, 0);
       fwd_scores<HR>(s, kr, qf, rd, 0);
     }
     if (behind) __syncthreads();
-    while ((KL == 1 ? e0.sb : lead.sb) < segs) {
-      Entry e2 = e1;
-      if (e1.sb < segs) step_to(e2, stride);
+    while ((KL == 1 ? sb : lead_sb) < segs) {
+      int n2_sb = nx_sb, n2_j = nx_j, n2_nblk = nx_nblk, n2_start = nx_start, n2_rows = nx_rows;
+      if (nx_sb < segs) step_next(n2_sb, n2_j, n2_nblk, n2_start, n2_rows);
       auto request = [&]() {
-        if (A2D_OFTEN(e2.sb < segs)) load_tile(1, e2, boff);
-        if (A2D_OFTEN(e1.sb < segs)) load_tile(2, e1, BUF_BYTES - boff);
+        if (A2D_OFTEN(n2_sb < segs)) load_tile(1, n2_start, n2_rows, n2_j, boff);
+        if (A2D_OFTEN(nx_sb < segs)) load_tile(2, nx_start, nx_rows, nx_j, BUF_BYTES - boff);
       };
       if (behind) request();                       // (the others: behind the barrier below)
       const bool mine = seen;
@@ -526,9 +526,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
         __syncthreads();
         request();
       }
-      if (!CYCLIC && A2D_SELDOM(e1.sb != e0.sb && e1.sb < segs)) enter_segment(e1.sb);
+      if (!CYCLIC && A2D_SELDOM(nx_sb != sb && nx_sb < segs)) enter_segment(nx_sb);
       __builtin_amdgcn_s_setprio(0);               // (the softmax first, where both want to issue)
-      look_at(e1);
+      look_at(nx_sb, nx_j);
       if (seen) {
         fwd_first_keys<HR>(kr, rd, BUF_BYTES - boff);
         fwd_scores<HR>(s, kr, qf, rd, BUF_BYTES - boff);
@@ -542,9 +542,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
         wait_vmem_all();
         __syncthreads();
       }
-      if (KL > 1) advance(stride, lead.sb, lead.j, lead.nblk);
-      e0 = e1;
-      e1 = e2;
+      if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
+      sb = nx_sb;
+      nx_sb = n2_sb; nx_j = n2_j; nx_nblk = n2_nblk; nx_start = n2_start; nx_rows = n2_rows;
       boff = BUF_BYTES - boff;
     }
     if (!behind) __syncthreads();                  // (as many barriers for all)
@@ -552,21 +552,20 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void fwd_mfma_kernel(
   } else {
     // (the next entry is found in the step that requests it: found a step ahead, the loop is 2 % slower - 4 x 14885 x 4812, H = 64, causal, two
     // blocks 90.6 -> 92.7 us, 9 x 16075 x 321 53.4 -> 54.6)
-    while ((KL == 1 ? e0.sb : lead.sb) < segs) {
-      int nsb = e0.sb, nj = e0.j, nnblk = e0.nblk;
+    while ((KL == 1 ? sb : lead_sb) < segs) {
+      int nsb = sb, nj = j, nnblk = nblk;
       advance(stride, nsb, nj, nnblk);
       const bool more = nsb < segs;
-      if (CYCLIC) e1.start = nsb;
-      else if (A2D_SELDOM(more && nsb != e0.sb)) { e1.start = seg_start(nsb); e1.rows = seg_rows(nsb); }
-      e1.j = nj;
-      if (A2D_OFTEN(more)) load_tile(3, e1, BUF_BYTES - boff);
-      const int at = e0.j * BN + (CYCLIC && e0.sb > shift_from);   // local to the sub-block
-      if ((KL == 1 || e0.sb < segs) && at < nvis_wave) fwd_block<HR>(st, qf, rd, boff, at + BN > nfull_wave, at, my_vis, grp, c);
+      if (CYCLIC) nx_start = nsb;
+      else if (A2D_SELDOM(more && nsb != sb)) { nx_start = seg_start(nsb); nx_rows = seg_rows(nsb); }
+      if (A2D_OFTEN(more)) load_tile(3, nx_start, nx_rows, nj, BUF_BYTES - boff);
+      const int k0 = j * BN + (CYCLIC && sb > shift_from);     // local to the sub-block
+      if ((KL == 1 || sb < segs) && k0 < nvis_wave) fwd_block<HR>(st, qf, rd, boff, k0 + BN > nfull_wave, k0, my_vis, grp, c);
       wait_vmem_all();
       __syncthreads();
-      if (!CYCLIC && A2D_SELDOM(more && nsb != e0.sb)) enter_segment(nsb);
-      if (KL > 1) advance(stride, lead.sb, lead.j, lead.nblk);
-      e0.sb = nsb; e0.j = nj; e0.nblk = nnblk;
+      if (!CYCLIC && A2D_SELDOM(more && nsb != sb)) enter_segment(nsb);
+      if (KL > 1) advance(stride, lead_sb, lead_j, lead_nblk);
+      sb = nsb; j = nj; nblk = nnblk;
       boff = BUF_BYTES - boff;
     }
   }
