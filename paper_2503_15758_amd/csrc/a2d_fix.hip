@@ -47,8 +47,9 @@ template <int CPT>
 struct Share {
   int64_t first;
   unsigned rest;
-  __device__ __forceinline__ explicit Share(int64_t total) {
-    first = (int64_t)blockIdx.x * (256 * CPT);
+  // (from: the first group of the launch, see launch_slices)
+  __device__ __forceinline__ Share(int64_t from, int64_t total) {
+    first = from + (int64_t)blockIdx.x * (256 * CPT);
     rest = (unsigned)min(total - first, (int64_t)(256 * CPT));
   }
   __device__ __forceinline__ unsigned at(int c) const { return (threadIdx.x >> 6) * (CPT * 64) + c * 64 + (threadIdx.x & 63); }
@@ -130,10 +131,10 @@ struct Results {
 // TRIPLE: the merge alone (Alg. 2 over k inputs): the result stays an unnormalised partial
 // (N, m, l) - O receives N in fp32, lse receives m, l_out receives l.
 template <typename OutT, int KMAX, int CPT, bool TRIPLE = false>
-__global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t rows, int hv, OutMap om,
+__global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t from, int64_t rows, int hv, OutMap om,
                                                   OutT* __restrict__ O, float* __restrict__ lse,
                                                   float* __restrict__ l_out) {
-  const Share<CPT> sh(rows * hv);
+  const Share<CPT> sh(from, rows * hv);
   unsigned at[CPT];
 #pragma unroll
   for (int c = 0; c < CPT; ++c) at[c] = sh.at(c);
@@ -220,9 +221,9 @@ __global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t rows
 }
 
 template <typename OutT, int KMAX, int CPT>
-__global__ __launch_bounds__(256) void sum_kernel(SumPtrs p, int k, int64_t n4, int hv, OutMap om,
+__global__ __launch_bounds__(256) void sum_kernel(SumPtrs p, int k, int64_t from, int64_t n4, int hv, OutMap om,
                                                   OutT* __restrict__ out) {
-  const Share<CPT> sh(n4);
+  const Share<CPT> sh(from, n4);
   unsigned at[CPT];
 #pragma unroll
   for (int c = 0; c < CPT; ++c) at[c] = sh.at(c);
@@ -251,9 +252,9 @@ __global__ __launch_bounds__(256) void sum_kernel(SumPtrs p, int k, int64_t n4, 
 // Merge of k NORMALISED partials: L = log sum_k exp(lse_k), O = sum_k exp(lse_k - L) O'_k.  A
 // column group = 4 consecutive columns of one row, as in fix_kernel; InT is the partials' dtype.
 template <typename InT, typename OutT, int KMAX, int CPT>
-__global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_t rows, int hv, OutMap om,
+__global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_t from, int64_t rows, int hv, OutMap om,
                                                        OutT* __restrict__ O, float* __restrict__ lse) {
-  const Share<CPT> sh(rows * hv);
+  const Share<CPT> sh(from, rows * hv);
   unsigned at[CPT];
 #pragma unroll
   for (int c = 0; c < CPT; ++c) at[c] = sh.at(c);
@@ -417,30 +418,39 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(PartSets a) {
   *out = acc;
 }
 
-// (go(std::integral_constant<int, CPT>): launches)
+// (go(std::integral_constant<int, CPT>, first group, grid): launches)
+// HIP launches no 2^32 threads and more at a time: merges of more groups than that go out in slices of 2^31 threads.
+constexpr int64_t kSliceBlocks = (int64_t)1 << 23;
+template <int CPT, class F>
+void launch_slices(int64_t groups, F&& go) {
+  constexpr int64_t share = 256 * CPT;
+  for (int64_t from = 0; from < groups; from += kSliceBlocks * share) {
+    const int64_t blocks = (groups - from + share - 1) / share;
+    go(std::integral_constant<int, CPT>{}, from, dim3((unsigned)(blocks < kSliceBlocks ? blocks : kSliceBlocks)));
+  }
+}
 template <int KMAX, bool WEIGHTS, bool HALF = false, class F>
 void with_chunks(int64_t groups, F&& go) {
   const int cpt = chunks_per_thread(KMAX, WEIGHTS, groups, HALF);
   constexpr int MOST = chunks_per_thread(KMAX, WEIGHTS, kManyGroups, HALF);
-  if (cpt == 1) go(std::integral_constant<int, 1>{});
-  else go(std::integral_constant<int, MOST>{});      // (the one other number that a number of partials has)
+  if (cpt == 1) launch_slices<1>(groups, go);
+  else launch_slices<MOST>(groups, go);              // (the one other number that a number of partials has)
 }
-inline dim3 blocks_of(int64_t groups, int cpt) { return dim3((unsigned)((groups + 256 * cpt - 1) / (256 * cpt))); }
 
 template <typename OutT, int KMAX, bool TRIPLE = false>
 void fix_launch(int k, int64_t rows, int hv, const FixPtrs& p, const OutMap& om, OutT* O, float* lse, float* l_out,
                 hipStream_t s) {
-  with_chunks<KMAX, true>(rows * hv, [&](auto C) {
+  with_chunks<KMAX, true>(rows * hv, [&](auto C, int64_t from, dim3 grid) {
     constexpr int CPT = decltype(C)::value;
-    A2D_LAUNCH((fix_kernel<OutT, KMAX, CPT, TRIPLE>), blocks_of(rows * hv, CPT), dim3(256), 0, s, p, k, rows, hv, om, O, lse, l_out);
+    A2D_LAUNCH((fix_kernel<OutT, KMAX, CPT, TRIPLE>), grid, dim3(256), 0, s, p, k, from, rows, hv, om, O, lse, l_out);
   });
 }
 
 template <typename OutT, int KMAX>
 void sum_launch(int k, int64_t n4, int hv, const SumPtrs& p, const OutMap& om, OutT* out, hipStream_t s) {
-  with_chunks<KMAX, false>(n4, [&](auto C) {
+  with_chunks<KMAX, false>(n4, [&](auto C, int64_t from, dim3 grid) {
     constexpr int CPT = decltype(C)::value;
-    A2D_LAUNCH((sum_kernel<OutT, KMAX, CPT>), blocks_of(n4, CPT), dim3(256), 0, s, p, k, n4, hv, om, out);
+    A2D_LAUNCH((sum_kernel<OutT, KMAX, CPT>), grid, dim3(256), 0, s, p, k, from, n4, hv, om, out);
   });
 }
 
@@ -474,9 +484,9 @@ hipError_t sum_dispatch(int k, int64_t n, int hv, const SumPtrs& p, const OutMap
 
 template <typename InT, typename OutT, int KMAX>
 void fix_norm_launch(int k, int64_t rows, int hv, const NormPtrs& p, const OutMap& om, OutT* O, float* lse, hipStream_t s) {
-  with_chunks<KMAX, true, sizeof(InT) == 2>(rows * hv, [&](auto C) {
+  with_chunks<KMAX, true, sizeof(InT) == 2>(rows * hv, [&](auto C, int64_t from, dim3 grid) {
     constexpr int CPT = decltype(C)::value;
-    A2D_LAUNCH((fix_norm_kernel<InT, OutT, KMAX, CPT>), blocks_of(rows * hv, CPT), dim3(256), 0, s, p, k, rows, hv, om, O, lse);
+    A2D_LAUNCH((fix_norm_kernel<InT, OutT, KMAX, CPT>), grid, dim3(256), 0, s, p, k, from, rows, hv, om, O, lse);
   });
 }
 
