@@ -1,7 +1,7 @@
 // AttnFix (Alg. 2) folded over k partials + normalisation (Alg. 1 line 6), and the
 // plain-sum merge of gradient partials (Alg. 3 lines 4-5).  Both are pure
 // streaming kernels bound by HBM bandwidth: every input byte is read once with
-// 128-bit loads, all k loads of a thread are issued before the first use.
+// 128-bit loads, all k loads of a thread are issued before the first use (those of more than 16 partials one behind the other).
 #include <type_traits>
 
 #include "a2d_common.hpp"
@@ -68,16 +68,11 @@ __device__ __forceinline__ void load(bf16x4& v, __amdgpu_buffer_rsrc_t b, unsign
   v = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(b, i * 8, 0, NT));
 }
 // Partial x of k: v[c] = elements at[c] of the `n` from p + before on; zeros past them and of an absent partial.
-// No branch around absent ones, so that the pointers of all come in together: they have no size (us, with branches / without: AttnFix 8 x
-// 96 x 4096 297 / 292, 16 x 16 x 8000 171 / 169).  BRANCH: with one (sums of up to four: 4 x 16 x 2048 12.8 / 13.3).
-template <bool BRANCH, int KMAX, int CPT, typename T>
+// Up to four partials there is a kernel for each number; of more, absent ones have no size: no branch around them, so that the pointers of
+// all come in together (us, with branches / without: AttnFix 8 x 96 x 4096 297 / 292, 16 x 16 x 8000 171 / 169, sum 2 x 53212 x 64 7.0 / 6.5).
+template <int KMAX, int CPT, typename T>
 __device__ __forceinline__ void load_partial(T (&v)[CPT][KMAX], int x, int k, const T* p, int64_t before, unsigned n, const unsigned (&at)[CPT]) {
-  if (BRANCH && x >= k) {
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) v[c][x] = T{};
-    return;
-  }
-  const auto b = buffer(p, before * (int)sizeof(T), x < k ? n * (unsigned)sizeof(T) : 0);
+  const auto b = buffer(p, before * (int)sizeof(T), KMAX <= 4 || x < k ? n * (unsigned)sizeof(T) : 0);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) load(v[c][x], b, at[c]);
 }
@@ -127,7 +122,7 @@ struct Results {
 };
 
 // A column group = 4 consecutive columns of one row; hv = H / 4 groups per row.
-// KMAX is the unroll bound (k <= KMAX).
+// KMAX is the unroll bound (k <= KMAX; k itself up to four).
 // TRIPLE: the merge alone (Alg. 2 over k inputs): the result stays an unnormalised partial
 // (N, m, l) - O receives N in fp32, lse receives m, l_out receives l.
 template <typename OutT, int KMAX, int CPT, bool TRIPLE = false>
@@ -170,20 +165,20 @@ __global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t from
     rem = (unsigned)(idx - r * hv) - at[0];
   } else {
 #pragma unroll
-    for (int x = 0; x < KMAX; ++x) load_partial<false>(n, x, k, reinterpret_cast<const f32x4*>(p.o[x]), sh.first, sh.rest, at);
+    for (int x = 0; x < KMAX; ++x) load_partial(n, x, k, reinterpret_cast<const f32x4*>(p.o[x]), sh.first, sh.rest, at);
     __builtin_amdgcn_sched_barrier(0);
     rows_of();
     const unsigned stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT));
 #pragma unroll
     for (int x = 0; x < KMAX; ++x) {
-      load_partial<false>(mk, x, k, p.m[x], row0, stat, row);
-      load_partial<false>(lk, x, k, p.l[x], row0, stat, row);
+      load_partial(mk, x, k, p.m[x], row0, stat, row);
+      load_partial(lk, x, k, p.l[x], row0, stat, row);
     }
 #pragma unroll
     for (int x = 0; x < KMAX; ++x)
 #pragma unroll
       for (int c = 0; c < CPT; ++c)
-        if (x >= k) mk[c][x] = -INFINITY;
+        if (KMAX > 4 && x >= k) mk[c][x] = -INFINITY;
   }
   const Results<OutT> out(O, om, sh, row0, hv);
 #pragma unroll
@@ -230,7 +225,7 @@ __global__ __launch_bounds__(256) void sum_kernel(SumPtrs p, int k, int64_t from
   f32x4 v[CPT][KMAX];
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    load_partial<KMAX <= 4>(v, x, k, reinterpret_cast<const f32x4*>(p.p[x]), sh.first, sh.rest, at);
+    load_partial(v, x, k, reinterpret_cast<const f32x4*>(p.p[x]), sh.first, sh.rest, at);
   }
   const int64_t row0 = om.plain ? 0 : sh.first / hv;           // (plain results need no rows)
   const unsigned rem = om.plain ? 0 : (unsigned)(sh.first - row0 * hv);
@@ -263,7 +258,7 @@ __global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_
   float lk[CPT][KMAX];
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    load_partial<false>(n, x, k, reinterpret_cast<const in4*>(p.o[x]), sh.first, sh.rest, at);
+    load_partial(n, x, k, reinterpret_cast<const in4*>(p.o[x]), sh.first, sh.rest, at);
   }
   const int64_t row0 = sh.first / hv;
   const unsigned rem = (unsigned)(sh.first - row0 * hv), stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT));
@@ -272,13 +267,13 @@ __global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_
   for (int c = 0; c < CPT; ++c) row[c] = (rem + at[c]) / (unsigned)hv;
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    load_partial<false>(lk, x, k, p.lse[x], row0, stat, row);
+    load_partial(lk, x, k, p.lse[x], row0, stat, row);
   }
 #pragma unroll
   for (int x = 0; x < KMAX; ++x)
 #pragma unroll
     for (int c = 0; c < CPT; ++c)
-      if (x >= k) lk[c][x] = -INFINITY;
+      if (KMAX > 4 && x >= k) lk[c][x] = -INFINITY;
   const Results<OutT> out(O, om, sh, row0, hv);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
@@ -458,7 +453,8 @@ template <typename OutT, bool TRIPLE = false>
 hipError_t fix_dispatch(int k, int64_t rows, int hdim, const FixPtrs& p, const OutMap& om, OutT* O, float* lse,
                         float* l_out, hipStream_t s) {
   const int hv = hdim / 4;
-  if (k <= 2) fix_launch<OutT, 2, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
+  if (k <= 1) fix_launch<OutT, 1, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
+  else if (k <= 2) fix_launch<OutT, 2, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
   else if (k <= 3) fix_launch<OutT, 3, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
   else if (k <= 4) fix_launch<OutT, 4, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
   else if (k <= 6) fix_launch<OutT, 6, TRIPLE>(k, rows, hv, p, om, O, lse, l_out, s);
@@ -471,7 +467,8 @@ hipError_t fix_dispatch(int k, int64_t rows, int hdim, const FixPtrs& p, const O
 template <typename OutT>
 hipError_t sum_dispatch(int k, int64_t n, int hv, const SumPtrs& p, const OutMap& om, OutT* out, hipStream_t s) {
   const int64_t n4 = n / 4;
-  if (k <= 2) sum_launch<OutT, 2>(k, n4, hv, p, om, out, s);
+  if (k <= 1) sum_launch<OutT, 1>(k, n4, hv, p, om, out, s);
+  else if (k <= 2) sum_launch<OutT, 2>(k, n4, hv, p, om, out, s);
   else if (k <= 3) sum_launch<OutT, 3>(k, n4, hv, p, om, out, s);
   else if (k <= 4) sum_launch<OutT, 4>(k, n4, hv, p, om, out, s);
   else if (k <= 6) sum_launch<OutT, 6>(k, n4, hv, p, om, out, s);
@@ -494,7 +491,8 @@ template <typename InT, typename OutT>
 hipError_t fix_norm_dispatch(int k, int64_t rows, int hdim, const NormPtrs& p, const OutMap& om, OutT* O, float* lse,
                              hipStream_t s) {
   const int hv = hdim / 4;
-  if (k <= 2) fix_norm_launch<InT, OutT, 2>(k, rows, hv, p, om, O, lse, s);
+  if (k <= 1) fix_norm_launch<InT, OutT, 1>(k, rows, hv, p, om, O, lse, s);
+  else if (k <= 2) fix_norm_launch<InT, OutT, 2>(k, rows, hv, p, om, O, lse, s);
   else if (k <= 3) fix_norm_launch<InT, OutT, 3>(k, rows, hv, p, om, O, lse, s);
   else if (k <= 4) fix_norm_launch<InT, OutT, 4>(k, rows, hv, p, om, O, lse, s);
   else if (k <= 6) fix_norm_launch<InT, OutT, 6>(k, rows, hv, p, om, O, lse, s);
