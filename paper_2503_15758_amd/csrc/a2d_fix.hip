@@ -201,11 +201,11 @@ __global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t from
       acc[3] = fmaf(w, n[c][x][3], acc[3]);
     }
     if constexpr (TRIPLE) {
-      out.store(i, row[c], col, acc);
-      if (col == 0) {
+      if (col == 0) {                              // (first: behind the other store the wait for l would be one for it too)
         lse[row0 + row[c]] = M;
         l_out[row0 + row[c]] = D;
       }
+      out.store(i, row[c], col, acc);
     } else {
       const float inv = (D > 0.f) ? 1.0f / D : 0.f;
       acc[0] *= inv; acc[1] *= inv; acc[2] *= inv; acc[3] *= inv;

@@ -10,8 +10,8 @@ from test_host_registers import _code_objects
 OBJDUMP = os.path.join(os.path.dirname(os.path.dirname(lib_build.HIPCC)), "llvm", "bin", "llvm-objdump")
 
 
-def _listings(tmp_path):
-    """name -> instructions of the merges' kernels of up to 16 partials"""
+def _listings(tmp_path, most=16):
+    """name -> instructions of the merges' kernels of up to `most` partials"""
     found = {}
     for i, elf in enumerate(_code_objects(open(lib_build.LIB, "rb").read())):
         if b"sum_kernel" not in elf:
@@ -21,7 +21,7 @@ def _listings(tmp_path):
         text = subprocess.run([OBJDUMP, "--disassemble", "--no-show-raw-insn", "--no-leading-addr", str(path)], check=True, capture_output=True, text=True).stdout
         for block in re.split(r"\n(?=\S*<_Z)", text):
             m = re.match(r"\S*<(_Z\w*?(sum|fix|fix_norm)_kernelI\w*?Li(\d+)ELi(\d+)E\w*)>:", block)
-            if m and int(m[3]) <= 16:
+            if m and int(m[3]) <= most:
                 found[m[1]] = (m[2], int(m[3]), int(m[4]), [l.split("//")[0].strip() for l in block.splitlines()[1:]])
     return found
 
@@ -37,3 +37,12 @@ def test_no_wait_between_a_threads_loads(tmp_path):
         assert not [l for l in between if l.startswith("s_waitcnt") and "vmcnt" in l], name
         if kmax <= 4:
             assert not [l for l in between if l.startswith(("s_waitcnt", "s_cbranch", "s_branch"))], name
+
+
+def test_merge_alone_ends_with_its_wide_store(tmp_path):
+    """AttnFix without the division: a wait behind the store of N is a wait for that store."""
+    kernels = {n: code for n, (kind, _, cpt, code) in _listings(tmp_path, 32).items() if kind == "fix" and cpt == 1 and "ELb1EE" in n}
+    assert len(kernels) == 8
+    for name, code in kernels.items():
+        at = max(i for i, l in enumerate(code) if l.startswith("buffer_store_dwordx4"))
+        assert not [l for l in code[at:] if l.startswith("s_waitcnt") and "vmcnt" in l], name
