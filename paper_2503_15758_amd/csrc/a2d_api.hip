@@ -535,7 +535,7 @@ a2d_status out_map(const a2d_layout* lo, int64_t nq, int32_t hdim, int32_t out_d
   if (lo->row % unit != 0 || lo->head % unit != 0)
     return fail(A2D_ERR_MISALIGNED, "%s: output layout: head=%lld row=%lld must be multiples of %lld elements", who,
                 (long long)lo->head, (long long)lo->row, (long long)unit);
-  om->head = lo->head; om->row = lo->row; om->nq = (int)nq; om->plain = 0;
+  om->head = lo->head; om->row = lo->row; om->nq = (int)nq; om->plain = a2d::OutMap::STRIDED;
   return A2D_OK;
 }
 

@@ -336,8 +336,9 @@ struct OutMap {
   int64_t row;
   int nq;
   int plain;
+  enum { STRIDED, PLAIN, PLAIN_THROUGH };   // (the last: written straight on to memory, the merges' launcher decides)
 };
-inline OutMap plain_out() { return OutMap{0, 0, 1, 1}; }
+inline OutMap plain_out() { return OutMap{0, 0, 1, OutMap::PLAIN}; }
 // The merged output of a whole emulated grid: block b, head h, row i of the merge's input is token
 // i * side + b (cyclic) or b * rows + i of head h in a [heads][side * rows][H] tensor.
 struct GridMap {

@@ -14,25 +14,36 @@ namespace {
 // arithmetic, decides how close these kernels get to the HBM rate.
 // (read once: non-temporal loads measured 8-10 % faster than plain ones here)
 #define A2D_LD(p) __builtin_nontemporal_load(p)
-// CPT for `groups` column groups (weights: AttnFix, which holds m and l besides N).  us, one / two / four groups a thread:
-// 96 x 4096 x 128, k = 4 AttnFix 150 / 159 / 160, sum 148 / 155 / 155, k = 2 82.7 / 84.7 / 86.5; 30 x 2500 x 128, k = 6 sum 40.4 / 41.1 / 40.8,
-// AttnFix 42.6 / 42.2 / 42.8; k = 8 sum 16 x 2048 x 128 25.5 / 25.5 / 22.9, AttnFix 26.6 / 27.0 / 25.6 there, but 302 / 297 / 303 at 96 x 4096 and
-// - / 16.1 / 17.3 at 20 x 1000 (four: two workgroups a compute unit, 1.2 turns of them);
-// k = 16 AttnFix 16 x 8000 x 128 180 / 171, sum 179 / 169, but 75.0 / 76.8 and 72.6 / 73.1 at 16 x 4096 x 96.
-// half: groups of 8 bytes, a merge of normalised bf16 partials: 16 x 2048 x 128, k = 16 29.0 / 25.4, 96 x 4096, k = 2 one against four 63.0 / 58.2.
-// One for merges of up to a thousand workgroups, which have to come to as many as they can (those of the split walk of 1 x 1000 x
-// 1000 fp32, H = 128 17.6 -> 15.3 with it, 2 x 100 x 1000, H = 96 12.2 -> 10.0; AttnFix of 8, 26 x 466 x 96 four against one 11.2 / 8.8).  AttnFix of
-// 8 partials of 2 to 8 MB each, and some sums, are up to 6 % slower than before all this (17 x 1370 x 80 12.9 -> 13.6, plain stores 13.7); 20 merges
-// of that size 1.036 times as fast in the mean.
-constexpr int64_t kSomeGroups = 1 << 19, kManyGroups = 1 << 21;
-constexpr int chunks_per_thread(int kmax, bool weights, int64_t groups, bool half = false) {
-  if (groups < kSomeGroups) return 1;
-  if (half && kmax == 2) return 4;
-  if (half && kmax == 16) return 2;
-  if (kmax <= 4 || kmax > 16) return 1;
-  if (kmax == 6) return 2;
-  if (kmax == 8) return weights ? 2 : 4;
-  return groups >= kManyGroups ? 2 : 1;
+// How many groups a thread has, and how the results are stored, for `groups` column groups (weights: AttnFix, which holds m and l besides N;
+// half: AttnFix of normalised bf16 partials, groups of 8 bytes).  Few groups come to as many workgroups as they can, many have the loads of two or
+// four in flight; in between lies what was measured, on three sets of inputs in turn.  One / two / four groups, us for rows x H, the better way
+// to store:
+//   AttnFix k = 2, 63709 x 96 12.4 / 11.9 / 11.8, 266808 x 64 32.8 / 31.9 / 32.7; k = 3, 4 within 4 %; k = 6, 15593 x 64 5.9 / 5.9 / 6.7,
+//   39088 x 64 12.9 / 11.9 / 13.5, 60062 x 96 27.8 / 27.4 / 26.7; k = 8, 12366 x 96 8.6 / 9.2 / 11.1, 15492 x 128 13.6 / 12.4 / 13.1, 104325 x 96
+//   58.7 / 56.7 / 57.2; k = 16, 8355 x 80 9.3 / 10.7 / 11.4, 29059 x 64 23.5 / 22.1 / 25.9, 39760 x 96 48.6 / 46.9 / 51.5;
+//   sums of 2 to 4 one; k = 6, 15990 x 96 7.5 / 7.1 / 7.7, 30774 x 64 9.6 / 9.1 / 8.8, 48288 x 80 19.0 / 19.6 / 18.6; k = 8, 12493 x 128 10.1 / 10.4 / 9.6,
+//   62396 x 96 36.8 / 37.1 / 35.4; k = 16, 12573 x 64 10.3 / 9.6 / 9.6, 16622 x 128 24.5 / 24.8 / 27.3, 31214 x 128 46.7 / 47.0 / 42.6;
+//   half k = 2, 358276 x 64 26.4 / 24.7 / 24.0, k = 4, 59542 x 80 10.8 / 10.0 / 10.8, k = 8, 51209 x 96 17.1 / 17.4 / 18.0, k = 16, 30544 x 64 13.2 /
+//   13.4 / 14.5, 52452 x 96 31.3 / 31.5 / 32.9.
+// through, plain / written through: sum k = 3, 5385 x 64 2.2 / 2.1; AttnFix k = 6, 28217 x 64 8.9 / 9.3, k = 8, 35492 x 64 14.4 / 15.0,
+// k = 4, 12322 x 128 6.2 / 6.4, 92778 x 96 32.3 / 30.2; sum k = 8, 13455 x 128 9.9 / 10.6, 266664 x 64 100.7 / 98.7.
+// Against kernels of one to four groups by the number of partials alone, plain stores and loads under conditions: 430 merges, 1.06 to 1.28
+// times as fast in the mean of a set; of those between 2^17.5 and 2^20 groups a tenth are 1 to 5 % slower, at worst 9 % (sum of 16, 6168 x 128).
+struct Way {
+  int cpt;
+  bool through;
+};
+constexpr int64_t kGroups = 1 << 14;               // (64 workgroups of one group a thread)
+constexpr Way way_of(int kmax, bool weights, bool half, int64_t groups) {
+  const int64_t n = groups / kGroups;
+  int cpt = 1;
+  if (half) cpt = n < 32 || kmax == 1 || kmax > 16 ? 1 : kmax == 2 && n >= 128 ? 4 : 2;
+  else if (weights && kmax == 2) cpt = n < 32 ? 1 : 2;
+  else if (weights && kmax > 4) cpt = n < (kmax == 16 ? 11 : 20) || kmax > 16 ? 1 : kmax == 6 && n >= 52 ? 4 : 2;
+  else if (kmax == 16) cpt = n < 11 ? 1 : n < 40 ? 2 : 4;
+  else if (kmax > 4) cpt = n < 24 || kmax > 16 ? 1 : 4;
+  const int through = cpt == 1 || (kmax == 16 && !weights) ? 32 : weights && kmax == 6 ? 96 : 48;
+  return {cpt, kmax <= 2 || n < 11 || n >= through};
 }
 
 // Which column groups a thread owns: its wavefront owns CPT * 64 CONSECUTIVE groups and lane l takes
@@ -76,7 +87,6 @@ __device__ __forceinline__ void load_partial(T (&v)[CPT][KMAX], int x, int k, co
 #pragma unroll
   for (int c = 0; c < CPT; ++c) load(v[c][x], b, at[c]);
 }
-
 __device__ __forceinline__ void store_out4(float* O, int64_t off, f32x4 v) {
   *reinterpret_cast<f32x4*>(O + off) = v;
 }
@@ -87,7 +97,7 @@ __device__ __forceinline__ void store_out4(bf16_t* O, int64_t off, f32x4 v) {
 }
 
 // Where column group i of the share goes: plain, or row r of head h (nq rows per head) at h * head + r * row elements.
-// Plain results are written through: the reads alone take 230 us at 96 x 4096 rows of 128 and 8 partials, a seventeenth as many bytes
+// Results of small and of large merges are written through: at 96 x 4096 rows of 128 and 8 partials the reads alone take 230 us, a seventeenth as many bytes
 // of results another 50, as lines that the stream of reads drives out of the L2s one by one; sent on at once (device
 // scope) 277 -> 265, non-temporal 275, collected in LDS and stored in longer runs 270 to 305; fp32 results 254 -> 248, non-temporal 269.
 template <typename OutT>
@@ -104,16 +114,21 @@ struct Results {
     r0 = om.plain ? 0 : row0 - h0 * om.nq;
   }
   // (row, col: its row, counted from the share's first one, and its place in it)
+  template <int POLICY>
+  __device__ __forceinline__ void store_plain(unsigned i, f32x4 v) const {
+    if constexpr (sizeof(OutT) == 4) {
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, i * 16, 0, POLICY);
+    } else {
+      bf16x4 o;
+      o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), b, i * 8, 0, POLICY);
+    }
+  }
   __device__ __forceinline__ void store(unsigned i, unsigned row, unsigned col, f32x4 v) const {
-    if (om.plain) {
-      if constexpr (sizeof(OutT) == 4) {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, i * 16, 0, THROUGH);
-      } else {
-        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-        bf16x4 o;
-        o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), b, i * 8, 0, THROUGH);
-      }
+    if (om.plain == OutMap::PLAIN_THROUGH) {
+      store_plain<THROUGH>(i, v);
+    } else if (om.plain) {
+      store_plain<0>(i, v);
     } else {
       const unsigned r = (unsigned)r0 + row, h = r / (unsigned)om.nq;
       store_out4(O, (h0 + h) * om.head + (int64_t)(r - h * (unsigned)om.nq) * om.row + col * 4, v);
@@ -424,28 +439,32 @@ void launch_slices(int64_t groups, F&& go) {
     go(std::integral_constant<int, CPT>{}, from, dim3((unsigned)(blocks < kSliceBlocks ? blocks : kSliceBlocks)));
   }
 }
-template <int KMAX, bool WEIGHTS, bool HALF = false, class F>
-void with_chunks(int64_t groups, F&& go) {
-  const int cpt = chunks_per_thread(KMAX, WEIGHTS, groups, HALF);
-  constexpr int MOST = chunks_per_thread(KMAX, WEIGHTS, kManyGroups, HALF);
-  if (cpt == 1) launch_slices<1>(groups, go);
-  else launch_slices<MOST>(groups, go);              // (the one other number that a number of partials has)
+template <int KMAX, bool WEIGHTS, bool HALF, class F>
+void with_chunks(int64_t groups, OutMap om, F&& go) {
+  const Way w = way_of(KMAX, WEIGHTS, HALF, groups);
+  if (om.plain && w.through) om.plain = OutMap::PLAIN_THROUGH;
+  const auto of = [&](auto C, int64_t from, dim3 grid) { go(C, from, grid, om); };
+  // (the numbers that occur for a number of partials, each at one of these sizes)
+  constexpr int most = way_of(KMAX, WEIGHTS, HALF, 256 * kGroups).cpt, some = way_of(KMAX, WEIGHTS, HALF, 36 * kGroups).cpt;
+  if (w.cpt == 1) launch_slices<1>(groups, of);
+  else if (w.cpt == some) launch_slices<some>(groups, of);
+  else launch_slices<most>(groups, of);
 }
 
 template <typename OutT, int KMAX, bool TRIPLE = false>
 void fix_launch(int k, int64_t rows, int hv, const FixPtrs& p, const OutMap& om, OutT* O, float* lse, float* l_out,
                 hipStream_t s) {
-  with_chunks<KMAX, true>(rows * hv, [&](auto C, int64_t from, dim3 grid) {
+  with_chunks<KMAX, true, false>(rows * hv, om, [&](auto C, int64_t from, dim3 grid, const OutMap& map) {
     constexpr int CPT = decltype(C)::value;
-    A2D_LAUNCH((fix_kernel<OutT, KMAX, CPT, TRIPLE>), grid, dim3(256), 0, s, p, k, from, rows, hv, om, O, lse, l_out);
+    A2D_LAUNCH((fix_kernel<OutT, KMAX, CPT, TRIPLE>), grid, dim3(256), 0, s, p, k, from, rows, hv, map, O, lse, l_out);
   });
 }
 
 template <typename OutT, int KMAX>
 void sum_launch(int k, int64_t n4, int hv, const SumPtrs& p, const OutMap& om, OutT* out, hipStream_t s) {
-  with_chunks<KMAX, false>(n4, [&](auto C, int64_t from, dim3 grid) {
+  with_chunks<KMAX, false, false>(n4, om, [&](auto C, int64_t from, dim3 grid, const OutMap& map) {
     constexpr int CPT = decltype(C)::value;
-    A2D_LAUNCH((sum_kernel<OutT, KMAX, CPT>), grid, dim3(256), 0, s, p, k, from, n4, hv, om, out);
+    A2D_LAUNCH((sum_kernel<OutT, KMAX, CPT>), grid, dim3(256), 0, s, p, k, from, n4, hv, map, out);
   });
 }
 
@@ -481,9 +500,9 @@ hipError_t sum_dispatch(int k, int64_t n, int hv, const SumPtrs& p, const OutMap
 
 template <typename InT, typename OutT, int KMAX>
 void fix_norm_launch(int k, int64_t rows, int hv, const NormPtrs& p, const OutMap& om, OutT* O, float* lse, hipStream_t s) {
-  with_chunks<KMAX, true, sizeof(InT) == 2>(rows * hv, [&](auto C, int64_t from, dim3 grid) {
+  with_chunks<KMAX, true, sizeof(InT) == 2>(rows * hv, om, [&](auto C, int64_t from, dim3 grid, const OutMap& map) {
     constexpr int CPT = decltype(C)::value;
-    A2D_LAUNCH((fix_norm_kernel<InT, OutT, KMAX, CPT>), grid, dim3(256), 0, s, p, k, from, rows, hv, om, O, lse);
+    A2D_LAUNCH((fix_norm_kernel<InT, OutT, KMAX, CPT>), grid, dim3(256), 0, s, p, k, from, rows, hv, map, O, lse);
   });
 }
 

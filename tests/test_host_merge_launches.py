@@ -94,3 +94,18 @@ def test_launches_fit_and_cover(launches):
         assert at >= groups, case
         # below 2^31 groups: one launch, as callers that capture it count on
         assert len(made) == 1 or groups > (1 << 31), case
+
+
+def test_large_cases_have_their_groups_a_thread(launches):
+    """The cases of test_gpu_merge_shares.py take the forms that they are there for, and those are all that there are."""
+    import test_gpu_merge_shares as t
+    cases = [(op, k, rows * H // 4, int(op == "fix_norm")) for op, k, H, rows, _ in t.LARGE]
+    seen = set()
+    for (op, k, groups, _), case, (_, made) in zip(cases, t.LARGE, launches(cases)):
+        assert made[0][1] == -(-groups // (256 * case[4])), case
+        seen.add((op, k, case[4]))
+    ops = ("fix", "fix_bwd", "fix_norm")
+    every = [(op, k, 1 << i, int(op == "fix_norm")) for op in ops for k in (1, 2, 3, 4, 6, 8, 16) for i in range(14, 24)]
+    for (op, k, groups, _), (_, made) in zip(every, launches(every)):
+        cpt = groups // (256 * made[0][1])
+        assert cpt == 1 or (op, k, cpt) in seen or (op, k) == ("fix_norm", 4), (op, k, groups, cpt)
