@@ -98,7 +98,9 @@ __device__ __forceinline__ void small_rows(
   // into columns whose results are not stored; a branch around them costs 3 % at H = 96).  AHEAD: all of a turn's loads are under
   // way during the turn before (two accumulators leave registers for one slab at a time; and where a compute unit runs several
   // workgroups one after the other, or dK / dV need all the memory gives, one slab at a time is the better order: 13 heads, 404 tokens
-  // on 2 x 2, H = 128 24.6 us with all ahead in the dQ workgroups, 23.9 without, 6 x 1589 x 1902, H = 64 39.1 / 37.1).
+  // on 2 x 2, H = 128 24.6 us with all ahead in the dQ workgroups, 23.9 without, 6 x 1589 x 1902, H = 64 39.1 / 37.1).  dQ beside dK and dV
+  // apart: at H = 64 alone, where it is worth 1 %; at H = 80 and more walks of many keys lose up to a tenth by it, those of few a hundredth at most
+  // without (ahead / not: 2 x 197 x 1353, H = 80 13.5 / 12.4, H = 128 15.5 / 14.1, 1 x 560 x 1680, H = 128 19.0 / 17.3, 4 x 181 x 550, H = 80 8.6 / 8.0).
   constexpr int ST_ROWS = 64 / CHUNKS, ST_N = 32 / ST_ROWS;
   const int st_row = lane / CHUNKS, st_chunk = lane % CHUNKS;
   const unsigned first_area = lds_base + kl * 2 * SLAB;
@@ -506,7 +508,7 @@ __global__ __launch_bounds__(64 * LANES, 1) void bwd_small_kernel(
   if constexpr (SPLIT) {
     if (at < first) small_rows<HR, KEYS_DK, GRID, true>(at, lds, d, g, Q, K, V, O, dO, lse, dQ, dK, dV);
     else if (at < 2 * first) small_rows<HR, KEYS_DV, GRID, true>(at - first, lds, d, g, Q, K, V, O, dO, lse, dQ, dK, dV);
-    else small_rows<HR, ROWS_DQ, GRID, true>(at - 2 * first, lds, d, g, Q, K, V, O, dO, lse, dQ, dK, dV);
+    else small_rows<HR, ROWS_DQ, GRID, HR == 64>(at - 2 * first, lds, d, g, Q, K, V, O, dO, lse, dQ, dK, dV);
   } else {
     const int id = at < first ? at : at - first;
     if ((at < first) == (q_first != 0)) small_rows<HR, ROWS_DQ, GRID, false>(id, lds, d, g, Q, K, V, O, dO, lse, dQ, dK, dV);
