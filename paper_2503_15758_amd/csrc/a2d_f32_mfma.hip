@@ -387,8 +387,7 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(fwd_fit
   w.open(g, seg_blocks);
   w.advance(part * KL + kl, g, seg_blocks);
   // K comes in through LDS, the next block's as soon as the scores are there; V by columns into registers, the next block's as
-  // soon as the products are through.  (The walk is entered and gone round behind requests of both only: with a way in past them the
-  // compiler had to assume in each step that the rows of Q were still under way, and waited for V in front of the scores.)
+  // soon as the products are through.  (Past the walk's end both read a block of its last sub-block again.)
   Blocks<H> kt;
   kt.init((lds_t)smem + kl * Blocks<H>::BYTES, l15, g4);
   Cols<H> vt[4];
@@ -404,55 +403,54 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(fwd_fit
   if (w.s < g.n) {
     load_k();
     load_v();
-    while (true) {
-      const int k0 = w.j * BLK;
-      if (w.s != vis_s) {
-        vis_s = w.s;
-#pragma unroll
-        for (int t = 0; t < RT; ++t) my_vis[t] = vis_count(d, g, min(q_row[t], d.nq - 1), w.s);
-      }
-      f32x4 p[RT];
-      mfma::wait_dma<V_LOADS>();
-      __builtin_amdgcn_sched_barrier(0);
-      dot_rows<H, RT>(p, kt, qf);
-      w.advance(lanes, g, seg_blocks);
-      const bool more = w.s < g.n;
-      mfma::wait_vmem_all();                            // V: the products would wait for the next block's K too
-      reads_done();
-      if (more) load_k();
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int t = 0; t < RT; ++t) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (k0 + 4 * g4 + r >= my_vis[t]) p[t][r] = -INFINITY;
-          m_lane[t] = fmaxf(m_lane[t], p[t][r]);
-        }
-        // (m_lane - m_ref) is +inf on the first visible block, NaN (-> false) while nothing is visible
-        const bool grow = (m_lane[t] - m_ref[t]) * c > kRescaleThreshold;
-        if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-          const float m_row = row_max(m_lane[t]);
-          const float alpha = m_ref[t] == -INFINITY ? 0.f : fast_exp2((m_ref[t] - m_row) * c);
-          m_ref[t] = m_row;
-          l_run[t] *= alpha;
-          o[t].scale(alpha);
-        }
-        const float mr = m_ref[t] == -INFINITY ? 0.f : m_ref[t];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          p[t][r] = fast_exp2((p[t][r] - mr) * c);
-          l_run[t] += p[t][r];
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int t = 0; t < RT; ++t) o[t].contract(vt[r], p[t][r]);
-      __builtin_amdgcn_sched_barrier(0);
-      if (!more) break;
-      load_v();
-    }
   }
+  while (w.s < g.n) {
+    const int k0 = w.j * BLK;
+    if (w.s != vis_s) {
+      vis_s = w.s;
+#pragma unroll
+      for (int t = 0; t < RT; ++t) my_vis[t] = vis_count(d, g, min(q_row[t], d.nq - 1), w.s);
+    }
+    f32x4 p[RT];
+    mfma::wait_dma<V_LOADS>();
+    __builtin_amdgcn_sched_barrier(0);
+    dot_rows<H, RT>(p, kt, qf);
+    w.advance(lanes, g, seg_blocks);
+    mfma::wait_vmem_all();                            // V: the products would wait for the next block's K too
+    reads_done();
+    load_k();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (k0 + 4 * g4 + r >= my_vis[t]) p[t][r] = -INFINITY;
+        m_lane[t] = fmaxf(m_lane[t], p[t][r]);
+      }
+      // (m_lane - m_ref) is +inf on the first visible block, NaN (-> false) while nothing is visible
+      const bool grow = (m_lane[t] - m_ref[t]) * c > kRescaleThreshold;
+      if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+        const float m_row = row_max(m_lane[t]);
+        const float alpha = m_ref[t] == -INFINITY ? 0.f : fast_exp2((m_ref[t] - m_row) * c);
+        m_ref[t] = m_row;
+        l_run[t] *= alpha;
+        o[t].scale(alpha);
+      }
+      const float mr = m_ref[t] == -INFINITY ? 0.f : m_ref[t];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        p[t][r] = fast_exp2((p[t][r] - mr) * c);
+        l_run[t] += p[t][r];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) o[t].contract(vt[r], p[t][r]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_v();
+  }
+  mfma::wait_vmem_all();
 
   // ---- to the true row maximum over all key lanes, then the sums over the lanes
   float m_all[RT];

@@ -46,24 +46,3 @@ def test_merge_alone_ends_with_its_wide_store(tmp_path):
     for name, code in kernels.items():
         at = max(i for i, l in enumerate(code) if l.startswith("buffer_store_dwordx4"))
         assert not [l for l in code[at:] if l.startswith("s_waitcnt") and "vmcnt" in l], name
-
-
-def test_fp32_forward_scores_wait_for_nothing(tmp_path):
-    """Between the first and the last MFMA of a step's scores: V, requested just before, is still on its way."""
-    found = {}
-    for i, elf in enumerate(_code_objects(open(lib_build.LIB, "rb").read())):
-        if b"fwd_f32_kernel" not in elf:
-            continue
-        path = tmp_path / ("%d.elf" % i)
-        path.write_bytes(elf)
-        text = subprocess.run([OBJDUMP, "--disassemble", "--no-show-raw-insn", "--no-leading-addr", str(path)], check=True, capture_output=True, text=True).stdout
-        for block in re.split(r"\n(?=\S*<_Z)", text):
-            m = re.match(r"\S*<_Z\w*fwd_f32_kernelILi(\d+)ELi(\d+)E\w*>:", block)
-            if m:
-                found[int(m[1]), int(m[2])] = [l.split("//")[0].strip() for l in block.splitlines()[1:]]
-    assert len(found) == 8
-    for (hdim, tiles), code in found.items():
-        mfma = [i for i, l in enumerate(code) if l.startswith("v_mfma")]
-        assert len(mfma) == 2 * tiles * hdim // 4                 # scores, then products
-        scores = code[mfma[0]:mfma[tiles * hdim // 4 - 1]]
-        assert not [l for l in scores if l.startswith("s_waitcnt") and "vmcnt" in l], (hdim, tiles)
