@@ -387,7 +387,10 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(fwd_fit
   w.open(g, seg_blocks);
   w.advance(part * KL + kl, g, seg_blocks);
   // K comes in through LDS, the next block's as soon as the scores are there; V by columns into registers, the next block's as
-  // soon as the products are through.  (Past the walk's end both read a block of its last sub-block again.)
+  // soon as the products are through.  (Past the walk's end a block of K is read again, which is there before the products are through,
+  // and none of V, which would be waited for: 3 x 130 x 64, H = 128 5.6 -> 5.5 us, 6 x 491 x 355 11.9 -> 11.8; without that of K either the loop of
+  // longer walks is 1 % slower.  In the 32-row form the scores wait for V already, since the compiler takes the second tile of Q as possibly
+  // under way in every step; a loop entered and gone round behind requests alone has no such wait, and is 1 to 2 % slower at H = 64 and 80.)
   Blocks<H> kt;
   kt.init((lds_t)smem + kl * Blocks<H>::BYTES, l15, g4);
   Cols<H> vt[4];
@@ -448,9 +451,9 @@ __global__ __launch_bounds__(64 * KL) __attribute__((amdgpu_waves_per_eu(fwd_fit
 #pragma unroll
       for (int t = 0; t < RT; ++t) o[t].contract(vt[r], p[t][r]);
     __builtin_amdgcn_sched_barrier(0);
-    load_v();
+    if (w.s < g.n) load_v();
   }
-  mfma::wait_vmem_all();
+  mfma::wait_vmem_all();                              // (the K tile's place is written over below)
 
   // ---- to the true row maximum over all key lanes, then the sums over the lanes
   float m_all[RT];
