@@ -339,7 +339,8 @@ def tile_route(heads, nq, nkv, hdim, dtype=torch.bfloat16, kv_heads=None, q_off=
                backward=False, ds_handover=False, split_groups=False, scratch=True, compute_units=0):
     """Diagnostic: how a tile call of these sizes goes out, by the library's own plans and without a device (compute_units
     0: those of the current one).  A dict: "kernels" in launch order, "rows" and "lanes" (key lanes) of a forward or dQ
-    workgroup, "keys" of a dK/dV workgroup, "parts_q" and "parts_kv" (workgroups that share a walk).  scratch: whether
+    workgroup, "keys" of a dK/dV workgroup, "parts_q" and "parts_kv" (workgroups that share a walk), "phased" (a forward's
+    wavefronts in opposite phases), "apart" (dK and dV of a backward of few rows in workgroups of their own).  scratch: whether
     there is memory for partial results (this module's calls; not those of the C boundary)."""
     flags = 1 * bool(backward) | 2 * bool(ds_handover) | 4 * bool(split_groups) | 8 * bool(scratch)
     return _ext().tile_route(heads, kv_heads or heads, nq, nkv, hdim, dtype, q_off, kv_off, causal, segments, flags,

@@ -177,6 +177,7 @@ void route_fwd(const a2d_tile_desc& d, const SegList& g, Route* r) {
   r->lanes = kLanes[f32][g.form];
   r->parts_q = g.parts;
   r->parts_kv = 1;
+  r->phased = !f32 && g.phased;
 }
 
 void route_bwd(const a2d_tile_desc& d, const BwdParts& p, Route* r) {
@@ -192,6 +193,7 @@ void route_bwd(const a2d_tile_desc& d, const BwdParts& p, Route* r) {
   }
   if (p.small) {
     add(r, "bwd_small_kernel");
+    r->apart = p.small > 1;
     r->rows = r->keys = 32;
     r->lanes = 8;
     return;

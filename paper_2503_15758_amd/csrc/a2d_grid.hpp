@@ -27,6 +27,8 @@ struct Route {
   int rows, lanes;               // query rows of a forward or dQ workgroup; its key lanes, which share the walk
   int keys;                      // of a dK/dV workgroup (0: a forward)
   int parts_q, parts_kv;         // workgroups that share a walk of the one kind (forward and dQ) and the other
+  int phased;                    // a forward's wavefronts in opposite phases
+  int apart;                     // a backward of few rows: dK and dV in workgroups of their own
 };
 enum RouteFlags { ROUTE_BACKWARD = 1, ROUTE_KEEP_DS = 2, ROUTE_SPLIT_GROUPS = 4, ROUTE_SCRATCH = 8 };
 // a tile call on a chip of `cus` compute units (0: the current device); ROUTE_SCRATCH: with scratch memory on offer

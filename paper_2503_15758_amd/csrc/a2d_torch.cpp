@@ -711,8 +711,9 @@ PyObject* route_dict(const a2d::Route& r) {
     }
     PyTuple_SET_ITEM(k, i, name);
   }
-  PyObject* d = Py_BuildValue("{s:N,s:i,s:i,s:i,s:i,s:i}", "kernels", k, "rows", r.rows, "lanes", r.lanes, "keys", r.keys,
-                              "parts_q", r.parts_q, "parts_kv", r.parts_kv);
+  PyObject* d = Py_BuildValue("{s:N,s:i,s:i,s:i,s:i,s:i,s:N,s:N}", "kernels", k, "rows", r.rows, "lanes", r.lanes, "keys", r.keys,
+                              "parts_q", r.parts_q, "parts_kv", r.parts_kv, "phased", PyBool_FromLong(r.phased), "apart",
+                              PyBool_FromLong(r.apart));
   if (!d) throw PythonError();
   return d;
 }

@@ -50,11 +50,23 @@ CASES = [
     (27, 27, 139, 7, 80),
     (27, 27, 142, 7, 64),
 ]
+# walks whose forward keeps a SIMD's wavefronts in opposite phases: both workgroup shapes under the mask in each layout, unmasked ones
+# whole and shared (tests/test_host_routes.py)
+PHASED = [
+    (48, 48, 242, 7, 128),
+    (40, 8, 212, 8, 128),
+    (10, 5, 388, 8, 128),
+    (12, 12, 323, 8, 128),
+    (16, 8, 258, 7, 128),
+    (10, 5, 242, 7, 128),
+    (6, 6, 449, 6, 128),
+    (4, 2, 388, 8, 128),
+]
 
 
 @pytest.mark.parametrize("layout", ["cyclic", "contiguous"])
 @pytest.mark.parametrize("causal", [True, False], ids=["causal", "full"])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "%dq%dkv_%dx%d_H%d" % c)
+@pytest.mark.parametrize("case", CASES + PHASED, ids=lambda c: "%dq%dkv_%dx%d_H%d" % c)
 def test_grid_rows(case, causal, layout):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -1,5 +1,7 @@
 """The 16 x 16 tiles inside a wavefront's 32 rows and keys, at their edges: sizes one off multiples of 16, diagonals at every
 offset within a tile, against fp64 on the GPU."""
+import math
+
 import pytest
 import torch
 
@@ -65,7 +67,31 @@ def test_forward_walks(form, case):
     heads, _, nq, nkv, H, causal, q_off, segs = case[:8]
     route = a2d.tile_route(heads, nq, nkv, H, causal=causal, q_off=q_off, segments=segs)
     assert (route["rows"], route["lanes"], route["parts_q"]) == (*form, 1), route
+    assert route["phased"] == (nkv >= (1857 if form[1] == 2 else 897)), route
     forward.test_small_rows(case)
+
+
+@pytest.mark.parametrize("form,heads,nq,nkv,q_off", [((256, 1), 200, 250, 961, 900), ((128, 2), 120, 256, 1921, 1730)])
+def test_phased_walk_continues_a_partial(form, heads, nq, nkv, q_off):
+    """An accumulating call whose wavefronts are in opposite phases: it starts from the (N, m, l) of 70 keys, some rows' of none."""
+    from paper_2503_15758_amd import binding as a2d
+    H, scale = 128, 128 ** -0.5
+    route = a2d.tile_route(heads, nq, nkv, H, causal=True, q_off=q_off)
+    assert (route["rows"], route["lanes"], route["parts_q"], route["phased"]) == (*form, 1, True), route
+    gen = torch.Generator(device="cuda").manual_seed(nkv)
+    make = lambda n: torch.randn(heads, n, H, generator=gen, device="cuda").bfloat16()
+    Q, K1, V1, K2, V2 = make(nq), make(70), make(70), make(nkv), make(nkv)
+    at = torch.cat([torch.arange(70, device="cuda") + q_off + 100, torch.arange(nkv, device="cuda")])   # (the first rows see none of the 70)
+    out = a2d.partial_fwd(Q, K1, V1, q_off, q_off + 100, True, scale)
+    N, m, l = a2d.partial_fwd(Q, K2, V2, q_off, 0, True, scale, out=out, accumulate=True)
+    k, v = torch.cat([K1, K2], 1).double(), torch.cat([V1, V2], 1).double()
+    S = torch.bmm(Q.double(), k.transpose(1, 2).contiguous()) * scale
+    S.masked_fill_(at[None, None, :] > torch.arange(nq, device="cuda")[None, :, None] + q_off, -math.inf)
+    lse = torch.logsumexp(S, 2)
+    O = torch.bmm(torch.exp(S - lse[..., None]), v)
+    # (fp32 sums; P rounded to bf16, 2^-9 a term)
+    assert (m.double() + l.double().log() - lse).abs().max() < 1e-4
+    assert ((N / l[..., None]).double() - O).norm() / O.norm() < 5e-3
 
 
 # fp32 backward: steps of 16 rows and keys, four key lanes; delta by a launch in front (the last four) and by the tiles themselves

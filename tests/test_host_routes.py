@@ -221,11 +221,15 @@ def test_few_row_cases(a2d):
             if form == (64, 4):
                 rows64.add((H, causal and q_off < 0 or segs is not None))
     assert {H for H, _ in rows64} == set(SIZES) and {(64, True), (80, True), (96, True), (128, True)} <= rows64
+    apart = set()
     for cases, small in ((b.CASES, True), (b.PAIRS, False), (b.BOTH, True)):
         for heads, kvh, nq, nkv, H, causal, q_off, segs, _ in cases:
             r = tile(a2d, heads, nq, nkv, H, kv_heads=kvh, causal=causal, q_off=q_off, segments=segs, backward=True)
             assert ("bwd_small_kernel" in r["kernels"]) == small, (heads, nq, nkv, H)
-    assert {c[4] for c in b.CASES} == set(SIZES)
+            assert not (r["apart"] and cases is b.BOTH), (heads, nq, nkv, H)
+            if small:
+                apart.add((r["apart"], H))
+    assert {c[4] for c in b.CASES} == set(SIZES) and apart == every((False, True), SIZES)
 
 
 def test_backward_route_cases(a2d):
@@ -245,7 +249,7 @@ def test_grid_row_cases(a2d):
     import test_gpu_grid_rows as t
     from paper_2503_15758_amd import grid as g2d
     layouts = ("cyclic", "contiguous")
-    fwd, shared, sizes, bwd, heads_of = (set() for _ in range(5))
+    fwd, shared, sizes, bwd, heads_of, apart = (set() for _ in range(6))
     for heads, kvh, rows, side, H in t.CASES:
         for causal, layout in every((False, True), layouts):
             route = lambda backward: g2d.route(heads, rows * side, H, side, kvh, causal, layout, backward, CUS)
@@ -257,6 +261,8 @@ def test_grid_row_cases(a2d):
                 heads_of.add((form, heads > kvh))
             kind = (b["keys"], b["rows"], b["lanes"])
             bwd.add((kind, layout, causal))
+            if b["keys"] == 32:
+                apart.add((b["apart"], layout, causal))
             sizes.add((b["keys"], H))
             heads_of.add((b["keys"], heads > kvh))
     forms = FORMS + [(64, 4), (32, 8)]
@@ -264,5 +270,23 @@ def test_grid_row_cases(a2d):
     assert fwd == every(forms, layouts, (False, True)) and sizes == every(forms + [32, 128, 256], SIZES)
     # (the 64-row form shares unmasked walks only)
     assert shared == every(forms, layouts, (False, True)) - every([(64, 4)], layouts, [True])
-    assert bwd == every(kinds, layouts, (False, True))
+    assert bwd == every(kinds, layouts, (False, True)) and apart == every((False, True), layouts, (False, True))
     assert heads_of == every(forms + [32, 128, 256], (False, True))
+
+
+def test_phased_grid_cases(a2d):
+    import test_gpu_grid_rows as t
+    from paper_2503_15758_amd import grid as g2d
+    layouts, took, shared = ("cyclic", "contiguous"), set(), set()
+    for heads, kvh, rows, side, H in t.PHASED:
+        for causal, layout in every((False, True), layouts):
+            r = g2d.route(heads, rows * side, H, side, kvh, causal, layout, False, CUS)
+            if r["phased"]:
+                (shared if r["parts_q"] > 1 else took).add(((r["rows"], r["lanes"]), layout, causal))
+    assert took == every(FORMS[:2], layouts, (False, True)) and shared >= every(FORMS[:2], layouts, [False])
+
+
+def test_phases_need_long_walks_of_heads_of_128(a2d):
+    """us on MI355X in order / in phases: 16 x 2048 x 2048 38.2 / 36.8, 96 x 4096 x 4096 720 / 700; 9 x 2616 x 288 19.9 / 20.9, 39 x 9559 x 1886, H = 80 916 / 957."""
+    for heads, nq, nkv, H, phased in [(16, 2048, 2048, 128, True), (96, 4096, 4096, 128, True), (9, 2616, 288, 128, False), (39, 9559, 1886, 80, False)]:
+        assert tile(a2d, heads, nq, nkv, H)["phased"] == phased, (heads, nq, nkv, H)
