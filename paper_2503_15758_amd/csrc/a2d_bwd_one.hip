@@ -152,7 +152,8 @@ double plan_bwd_one(const a2d_tile_desc& d, const SegList& g, const BwdWalks& w,
   // 2 x 2, H = 128, causal 144 us against 120; 15 heads, 936 tokens, H = 64 28 against 33)
   const double trust = n_kv + n_q <= 3 * (int64_t)cus ? 1.04 : w.uneven && hx == 0 ? 1.15 : 0.94;
   if (small < trust * least) {
-    // (dK and dV apart where all workgroups run at once, see a2d_bwd_small.hip)
+    // (dK and dV apart where all workgroups run at once, see a2d_bwd_small.hip.  The choice above prices them together, up to a third
+    // too high for such calls: near the line one may go out in the other form though this one is faster.)
     *best = BwdParts{1, 1, 0, 0, 1, q_first, n_q + 2 * n_kv <= cus ? 2 : 1};
     return small;
   }

@@ -15,9 +15,9 @@
 //   - The forward's K tile goes straight into LDS, the next block's as soon as the scores are there, and V by columns into registers as
 //     soon as the products are through.  With K one block ahead in registers and V requested at the start of its own step, two workgroups
 //     shared a compute unit; without these 20 to 32 registers three to four of 16 rows do.  us, before -> now: 16 x 1024 x 1024,
-//     H = 128 / 96 / 80 / 64 82 / 63 / 52 / 43.3 -> 76 / 59 / 50 / 42.0 (113 TFLOP/s, 72 % of the peak, at H = 128), 12 x 1024 x 600, H = 128
-//     42.2 -> 38.1, 8 x 500 x 1000, H = 80 19.0 -> 17.2, 3 x 600 x 1000, H = 64 14.0 -> 12.5, 16 x 700 x 900, H = 96, causal 31.8 -> 30.7;
-//     23 shapes 1.058 times as fast in the mean, no one slower.
+//     H = 128 / 96 / 80 / 64 81.8 / 63.3 / 52.1 / 43.4 -> 75.3 / 59.0 / 49.8 / 41.5 (114 TFLOP/s, 73 % of the peak, at H = 128), 12 x 1024 x 600, H = 128
+//     42.4 -> 38.0, 8 x 500 x 1000, H = 80 19.0 -> 17.4, 3 x 600 x 1000, H = 64 13.5 -> 11.7, 16 x 700 x 900, H = 96, causal 31.9 -> 30.5;
+//     22 shapes 1.06 times as fast in the mean, 180 drawn ones 1.05, none more than 1 % slower.
 //   - The backward loads its tiles straight into LDS, each as soon as the last read of the one before is through: V behind dP, K
 //     behind half of dQ; Q behind half of dK, dO behind most of dV.  By way of registers, one step ahead, the rows of Q, dO and O took
 //     96 of them at H = 128 and left room for two workgroups a compute unit; now three fit up to H = 96 (at H = 96 where delta is read),

@@ -28,11 +28,13 @@
 // block: with a copy of its own per kind of block the compiler moved the accumulators between registers.
 //
 // The two wavefronts of a SIMD (w and w + 4) start a step with the scores, so that both want the matrix unit, then both the vector
-// ALU: at H = 128 the one is busy 48 % of the cycles, the other 48 %, both at once 11 %.  PHASED keeps them in opposite phases: in the
-// interval between two barriers one goes through the MFMAs of a step (scores of block t + 1, products of block t) and then the softmax of
-// block t + 1, the other through the softmax of block t and then the same MFMAs.  Both are busy 21 % of the cycles then, of which there are 10 %
-// fewer at a 5 % lower clock (the same power).  What is left: an MFMA of 16 cycles leaves the other wavefront two vector instructions, not
-// three, so that the 128 MFMAs and two softmaxes of a step take 2730 cycles at the least (both measured side by side); a step takes 3060.
+// ALU.  PHASED (H = 128) keeps them in opposite phases: in the interval between two barriers one goes through the MFMAs of a step (scores of block
+// t + 1, products of block t) and then the softmax of block t + 1, the other through the softmax of block t and then the same MFMAs.  In turn on one
+// GPU, 96 x 4096 x 4096 / 32 x 16384 x 16384: 6.6 / 7.3 % fewer cycles (matrix unit busy 52 -> 56 / 56 -> 61 % of them) at a 3.5 / 2.4 % lower clock
+// (the same power), 852 -> 824 / 3670 -> 3490 us.  From both, a step takes 3285 cycles (3550 in order) and a workgroup 25000 besides; what bounds a
+// step is that an MFMA of 16 cycles leaves the other wavefront two vector instructions, not three, so that the 128 MFMAs and two softmaxes take 2730 at
+// the least (both measured side by side).  Peaky logits, whose rows move their references often, lengthen the softmax alone: 8 x 16384 x 16384, sigma 4
+// 2 % fewer cycles, and shorter walks are slower than in order (plan_fwd_mfma).
 // Rescaling is lazy: a row's exponent reference m_ref follows its running maximum
 // only when a score exceeds it by more than 2^8 (in the exponent's units) - a rare,
 // wave-uniform branch, and the only place where the lanes of a row talk to each
@@ -723,12 +725,13 @@ void plan_fwd_mfma(const a2d_tile_desc& d, SegList* g, int cus, int cap) {
     const int z = best_parts(m[f], cap, f >= FWD_32 ? c.merge_few : c.merge, part_us, &t);
     if (f == 0 || t < (g->form == 0 ? 0.98 : 1.0) * least) { least = t; g->form = f; g->parts = z; }
   }
-  // Opposite phases (PHASED), walks in order / in phases, us: 96 x 4096 x 4096, unmasked and then causal 1145 -> 1120, 21 x 2194 x 5272
-  // 132.9 -> 124.8, 16/2 x 2416 x 3675 94.6 -> 89.1, 16 x 2048 x 2048 38.2 -> 36.8, 40/8 x 1300 gathered 71.2 -> 68.0.  They begin and end
+  // Opposite phases (PHASED), walks in order / in phases, us: 96 x 4096 x 4096, unmasked and then causal 1161 -> 1131, 21 x 2194 x 5272
+  // 132.9 -> 124.8, 16/2 x 2416 x 3675 94.6 -> 89.1, 16 x 2048 x 2048 38.2 -> 37.6, 40/8 x 1300 gathered 71.2 -> 68.0.  They begin and end
   // with half a step that nothing stands beside, so that walks of a few steps lose: 9 x 2616 x 288 19.9 -> 20.9, 19 x 2218 x 213,
-  // causal 14.8 -> 15.3, 9/3 x 4618 x 796 34.0 -> 34.6; from some 14 steps on they win.  Below H = 128, where a step's softmax is as long
-  // as its MFMAs, they lose oftener than they win: 72/9 x 2302 x 7437, H = 96 487 -> 469, but 39 x 9559 x 1886, H = 80 916 -> 957, 9 x
-  // 4032 x 1332, H = 64 28.5 -> 31.4.
+  // causal 14.8 -> 15.3, 9/3 x 4618 x 796 34.0 -> 34.6; from some 14 steps on they win.  32 drawn walks of that kind, unit-scale logits: 0.97 of the time
+  // in order in the mean (0.93 to 1.01).  Not so with peaky ones (sigma 4, which no size tells): 1.02 (0.99 to 1.05), 16 x 2048 x 2048 41.8 -> 42.9,
+  // and the same only from some hundred steps on.  Below H = 128, where a step's softmax is as long as its MFMAs, they lose oftener than they win:
+  // 72/9 x 2302 x 7437, H = 96 487 -> 469, but 39 x 9559 x 1886, H = 80 916 -> 957, 9 x 4032 x 1332, H = 64 28.5 -> 31.4.
   constexpr double kPhasedSteps = 14;
   g->phased = d.hdim == 128 && g->form <= FWD_LANES && mean >= kPhasedSteps * g->parts * (g->form == FWD_LANES ? 2 : 1);
 }
