@@ -18,7 +18,8 @@ namespace {
 // half: AttnFix of normalised bf16 partials, groups of 8 bytes).  Few groups come to as many workgroups as they can, many have the loads of two or
 // four in flight; in between lies what was measured, on three sets of inputs in turn.  One / two / four groups, us for rows x H, the better way
 // to store:
-//   AttnFix k = 2, 63709 x 96 12.4 / 11.9 / 11.8, 266808 x 64 32.8 / 31.9 / 32.7; k = 3, 4 within 4 %; k = 6, 15593 x 64 5.9 / 5.9 / 6.7,
+//   AttnFix k = 2, 63709 x 96 12.4 / 11.9 / 11.8, 266808 x 64 32.8 / 31.9 / 32.7; k = 4, 17278 x 96 6.9 / 7.1 / 7.4, 19386 x 128
+//   8.7 / 8.4 / 9.4, 32768 x 128 15.1 / 14.2 / 13.9, 51946 x 128 22.2 / 21.6 / 21.0, 65536 x 128 27.1 / 26.2 / 26.3; k = 6, 15593 x 64 5.9 / 5.9 / 6.7,
 //   39088 x 64 12.9 / 11.9 / 13.5, 60062 x 96 27.8 / 27.4 / 26.7; k = 8, 12366 x 96 8.6 / 9.2 / 11.1, 15492 x 128 13.6 / 12.4 / 13.1, 104325 x 96
 //   58.7 / 56.7 / 57.2; k = 16, 8355 x 80 9.3 / 10.7 / 11.4, 29059 x 64 23.5 / 22.1 / 25.9, 39760 x 96 48.6 / 46.9 / 51.5;
 //   sums of 2 to 4 one; k = 6, 15990 x 96 7.5 / 7.1 / 7.7, 30774 x 64 9.6 / 9.1 / 8.8, 48288 x 80 19.0 / 19.6 / 18.6; k = 8, 12493 x 128 10.1 / 10.4 / 9.6,
@@ -39,11 +40,13 @@ constexpr Way way_of(int kmax, bool weights, bool half, int64_t groups) {
   int cpt = 1;
   if (half) cpt = n < 32 || kmax == 1 || kmax > 16 ? 1 : kmax == 2 && n >= 128 ? 4 : 2;
   else if (weights && kmax == 2) cpt = n < 32 ? 1 : 2;
+  else if (weights && (kmax == 3 || kmax == 4)) cpt = n < 24 ? 1 : n >= (kmax == 3 ? 64 : 50) && n < 128 ? 4 : 2;
   else if (weights && kmax > 4) cpt = n < (kmax == 16 ? 11 : 20) || kmax > 16 ? 1 : kmax == 6 && n >= 52 ? 4 : 2;
   else if (kmax == 16) cpt = n < 11 ? 1 : n < 40 ? 2 : 4;
   else if (kmax > 4) cpt = n < 24 || kmax > 16 ? 1 : 4;
-  const int through = cpt == 1 || (kmax == 16 && !weights) ? 32 : weights && kmax == 6 ? 96 : 48;
-  return {cpt, kmax <= 2 || n < 11 || n >= through};
+  const int through = cpt == 1 || (kmax == 16 && !weights) ? 32 : !weights || half ? 48 : kmax <= 4 ? 128 : kmax == 6 ? 96 : 48;
+  const int plain = kmax == 3 || (kmax == 4 && !weights) ? 16 : 11;
+  return {cpt, kmax <= 2 || n < plain || n >= through};
 }
 
 // Which column groups a thread owns: its wavefront owns CPT * 64 CONSECUTIVE groups and lane l takes
@@ -81,8 +84,16 @@ __device__ __forceinline__ void load(bf16x4& v, __amdgpu_buffer_rsrc_t b, unsign
 // Partial x of k: v[c] = elements at[c] of the `n` from p + before on; zeros past them and of an absent partial.
 // Up to four partials there is a kernel for each number; of more, absent ones have no size: no branch around them, so that the pointers of
 // all come in together (us, with branches / without: AttnFix 8 x 96 x 4096 297 / 292, 16 x 16 x 8000 171 / 169, sum 2 x 53212 x 64 7.0 / 6.5).
-template <int KMAX, int CPT, typename T>
+// BRANCH, sums of three and four: with one, which makes a thread read a pointer, request its 16 bytes, and then read the next pointer.  The
+// requests, spread out like that, suit partials that lie a power of two apart, whose same places meet the same channels (4 x 16 x 1024 x 128
+// 7.1 / 7.4, 4 x 16 x 2048 13.0 / 13.5, 3 x 16 x 1024 5.8 / 6.1); others are the same from 2^18 groups on and 2 to 4 % slower below.
+template <bool BRANCH, int KMAX, int CPT, typename T>
 __device__ __forceinline__ void load_partial(T (&v)[CPT][KMAX], int x, int k, const T* p, int64_t before, unsigned n, const unsigned (&at)[CPT]) {
+  if (BRANCH && x >= k) {                          // (never taken: k is KMAX here)
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) v[c][x] = T{};
+    return;
+  }
   const auto b = buffer(p, before * (int)sizeof(T), KMAX <= 4 || x < k ? n * (unsigned)sizeof(T) : 0);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) load(v[c][x], b, at[c]);
@@ -180,14 +191,14 @@ __global__ __launch_bounds__(256) void fix_kernel(FixPtrs p, int k, int64_t from
     rem = (unsigned)(idx - r * hv) - at[0];
   } else {
 #pragma unroll
-    for (int x = 0; x < KMAX; ++x) load_partial(n, x, k, reinterpret_cast<const f32x4*>(p.o[x]), sh.first, sh.rest, at);
+    for (int x = 0; x < KMAX; ++x) load_partial<false>(n, x, k, reinterpret_cast<const f32x4*>(p.o[x]), sh.first, sh.rest, at);
     __builtin_amdgcn_sched_barrier(0);
     rows_of();
     const unsigned stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT));
 #pragma unroll
     for (int x = 0; x < KMAX; ++x) {
-      load_partial(mk, x, k, p.m[x], row0, stat, row);
-      load_partial(lk, x, k, p.l[x], row0, stat, row);
+      load_partial<false>(mk, x, k, p.m[x], row0, stat, row);
+      load_partial<false>(lk, x, k, p.l[x], row0, stat, row);
     }
 #pragma unroll
     for (int x = 0; x < KMAX; ++x)
@@ -240,7 +251,7 @@ __global__ __launch_bounds__(256) void sum_kernel(SumPtrs p, int k, int64_t from
   f32x4 v[CPT][KMAX];
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    load_partial(v, x, k, reinterpret_cast<const f32x4*>(p.p[x]), sh.first, sh.rest, at);
+    load_partial<KMAX == 3 || KMAX == 4>(v, x, k, reinterpret_cast<const f32x4*>(p.p[x]), sh.first, sh.rest, at);
   }
   const int64_t row0 = om.plain ? 0 : sh.first / hv;           // (plain results need no rows)
   const unsigned rem = om.plain ? 0 : (unsigned)(sh.first - row0 * hv);
@@ -273,7 +284,7 @@ __global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_
   float lk[CPT][KMAX];
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    load_partial(n, x, k, reinterpret_cast<const in4*>(p.o[x]), sh.first, sh.rest, at);
+    load_partial<false>(n, x, k, reinterpret_cast<const in4*>(p.o[x]), sh.first, sh.rest, at);
   }
   const int64_t row0 = sh.first / hv;
   const unsigned rem = (unsigned)(sh.first - row0 * hv), stat = (unsigned)min(rows - row0, (int64_t)(256 * CPT));
@@ -282,7 +293,7 @@ __global__ __launch_bounds__(256) void fix_norm_kernel(NormPtrs p, int k, int64_
   for (int c = 0; c < CPT; ++c) row[c] = (rem + at[c]) / (unsigned)hv;
 #pragma unroll
   for (int x = 0; x < KMAX; ++x) {
-    load_partial(lk, x, k, p.lse[x], row0, stat, row);
+    load_partial<false>(lk, x, k, p.lse[x], row0, stat, row);
   }
 #pragma unroll
   for (int x = 0; x < KMAX; ++x)
@@ -439,16 +450,23 @@ void launch_slices(int64_t groups, F&& go) {
     go(std::integral_constant<int, CPT>{}, from, dim3((unsigned)(blocks < kSliceBlocks ? blocks : kSliceBlocks)));
   }
 }
+constexpr bool occurs(int kmax, bool weights, bool half, int cpt) {        // (the rule changes last at 128 kGroups)
+  for (int n = 0; n <= 128; ++n)
+    if (way_of(kmax, weights, half, n * kGroups).cpt == cpt) return true;
+  return false;
+}
 template <int KMAX, bool WEIGHTS, bool HALF, class F>
 void with_chunks(int64_t groups, OutMap om, F&& go) {
   const Way w = way_of(KMAX, WEIGHTS, HALF, groups);
   if (om.plain && w.through) om.plain = OutMap::PLAIN_THROUGH;
   const auto of = [&](auto C, int64_t from, dim3 grid) { go(C, from, grid, om); };
-  // (the numbers that occur for a number of partials, each at one of these sizes)
-  constexpr int most = way_of(KMAX, WEIGHTS, HALF, 256 * kGroups).cpt, some = way_of(KMAX, WEIGHTS, HALF, 36 * kGroups).cpt;
-  if (w.cpt == 1) launch_slices<1>(groups, of);
-  else if (w.cpt == some) launch_slices<some>(groups, of);
-  else launch_slices<most>(groups, of);
+  if constexpr (occurs(KMAX, WEIGHTS, HALF, 2)) {
+    if (w.cpt == 2) return launch_slices<2>(groups, of);
+  }
+  if constexpr (occurs(KMAX, WEIGHTS, HALF, 4)) {
+    if (w.cpt == 4) return launch_slices<4>(groups, of);
+  }
+  launch_slices<1>(groups, of);
 }
 
 template <typename OutT, int KMAX, bool TRIPLE = false>

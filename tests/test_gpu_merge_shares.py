@@ -47,7 +47,8 @@ def test_shares(a2d, H, rows, k, out):
 
 # op, k, H, rows, groups a thread (held by test_host_merge_launches.py): rows that begin and end inside wavefronts and shares
 LARGE = [("fix", 2, 96, 22001, 2), ("fix", 6, 80, 17001, 2), ("fix", 6, 96, 36001, 4), ("fix", 8, 80, 17001, 2), ("fix", 8, 96, 36001, 2),
-         ("fix", 16, 96, 9001, 2), ("fix", 16, 80, 40003, 2), ("fix", 4, 80, 27001, 1),
+         ("fix", 16, 96, 9001, 2), ("fix", 16, 80, 40003, 2), ("fix", 4, 80, 27001, 2), ("fix", 3, 80, 27001, 2), ("fix", 3, 96, 45001, 4),
+         ("fix", 4, 96, 36001, 4), ("fix", 4, 96, 90001, 2),
          ("attnfix", 2, 80, 27001, 2), ("attnfix", 6, 96, 36001, 4), ("attnfix", 8, 80, 17001, 2), ("attnfix", 16, 96, 36001, 2),
          ("fix_bwd", 6, 80, 20001, 4), ("fix_bwd", 8, 96, 17001, 4), ("fix_bwd", 8, 80, 40001, 4), ("fix_bwd", 16, 80, 9501, 2),
          ("fix_bwd", 16, 96, 28001, 4), ("fix_bwd", 16, 80, 40001, 4), ("fix_bwd", 3, 80, 27001, 1),
