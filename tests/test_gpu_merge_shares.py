@@ -45,6 +45,23 @@ def test_shares(a2d, H, rows, k, out):
     assert_close(lw, nl, torch.float32, "fix_norm lse", rel=False)
 
 
+@pytest.mark.parametrize("k", [8, 16])
+def test_large_launches_as_small_ones(a2d, k):
+    """From 2^21 column groups on a thread has another number of them; the sums are the same, in the same order."""
+    rows, H, cut = 65536 + 77, 128, 40000
+    g = torch.Generator(device="cuda").manual_seed(k)
+    N = [torch.randn(rows, H, generator=g, device="cuda") for _ in range(k)]
+    m = [torch.randn(rows, generator=g, device="cuda") * 5 for _ in range(k)]
+    l = [torch.rand(rows, generator=g, device="cuda") + 1 for _ in range(k)]
+    cuts = lambda t: ([x[:cut].contiguous() for x in t], [x[cut:].contiguous() for x in t])
+    (Na, Nb), (ma, mb), (la, lb) = cuts(N), cuts(m), cuts(l)
+    for whole, a, b in ((a2d.fix(N, m, l), a2d.fix(Na, ma, la), a2d.fix(Nb, mb, lb)),
+                        (a2d.attnfix(N, m, l), a2d.attnfix(Na, ma, la), a2d.attnfix(Nb, mb, lb)),
+                        ((a2d.fix_bwd(N),), (a2d.fix_bwd(Na),), (a2d.fix_bwd(Nb),))):
+        for w, x, y in zip(whole, a, b):
+            assert torch.equal(w, torch.cat([x, y]))
+
+
 # op, k, H, rows, groups a thread (held by test_host_merge_launches.py): rows that begin and end inside wavefronts and shares
 LARGE = [("fix", 2, 96, 22001, 2), ("fix", 6, 80, 17001, 2), ("fix", 6, 96, 36001, 4), ("fix", 8, 80, 17001, 2), ("fix", 8, 96, 36001, 2),
          ("fix", 16, 96, 9001, 2), ("fix", 16, 80, 40003, 2), ("fix", 4, 80, 27001, 2), ("fix", 3, 80, 27001, 2), ("fix", 3, 96, 45001, 4),
@@ -68,7 +85,7 @@ def merge(a2d, op, N, m, l, out):
 
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 @pytest.mark.parametrize("op,k,H,rows,cpt", LARGE)
-def test_large_launches_as_small_ones(a2d, op, k, H, rows, cpt, out):
+def test_groups_a_thread_give_the_same_bits(a2d, op, k, H, rows, cpt, out):
     """The same arithmetic in the same order whatever number of groups a thread has and however the results are stored."""
     g = torch.Generator(device="cuda").manual_seed(rows + k)
     N = [torch.randn(rows, H, generator=g, device="cuda") for _ in range(k)]

@@ -34,15 +34,10 @@ def _kernels(elf):
             off = body + (desc + 3) // 4 * 4
 
 
-def _all_kernels():
+def test_no_vector_register_is_kept_in_scratch():
     data = open(lib_build.LIB, "rb").read()
     kernels = [k for elf in _code_objects(data) for k in _kernels(elf)]
     assert len(kernels) > 100
-    return kernels
-
-
-def test_no_vector_register_is_kept_in_scratch():
-    kernels = _all_kernels()
     spilled = {k[".name"]: k[".vgpr_spill_count"] for k in kernels if k[".vgpr_spill_count"]}
     assert not spilled, spilled
 
@@ -50,6 +45,7 @@ def test_no_vector_register_is_kept_in_scratch():
 def test_the_forward_does_not_keep_a_condition_per_masked_score():
     """Each is compared and used at once; kept in pairs of scalar registers, as the compiler does with stores under conditions that
     imply each other, they take 73 to 94 of them where 75 are enough for all, and the masked step of a short walk 1 to 4 % of its time."""
-    in_order = [k for k in _all_kernels() if "fwd_mfma_kernel" in k[".name"] and "ELb0EE" in k[".name"]]
+    data = open(lib_build.LIB, "rb").read()
+    in_order = [k for elf in _code_objects(data) for k in _kernels(elf) if "fwd_mfma_kernel" in k[".name"] and "ELb0EE" in k[".name"]]
     assert len(in_order) == 36
     assert max(k[".sgpr_count"] for k in in_order) <= 76
