@@ -287,6 +287,6 @@ def test_phased_grid_cases(a2d):
 
 
 def test_phases_need_long_walks_of_heads_of_128(a2d):
-    """us on MI355X in order / in phases: 16 x 2048 x 2048 38.2 / 36.8, 96 x 4096 x 4096 720 / 700; 9 x 2616 x 288 19.9 / 20.9, 39 x 9559 x 1886, H = 80 916 / 957."""
+    """us on MI355X in order / in phases: 16 x 2048 x 2048 38.2 / 37.6, 96 x 4096 x 4096 852 / 824; 9 x 2616 x 288 19.9 / 20.9, 39 x 9559 x 1886, H = 80 916 / 957."""
     for heads, nq, nkv, H, phased in [(16, 2048, 2048, 128, True), (96, 4096, 4096, 128, True), (9, 2616, 288, 128, False), (39, 9559, 1886, 80, False)]:
         assert tile(a2d, heads, nq, nkv, H)["phased"] == phased, (heads, nq, nkv, H)
